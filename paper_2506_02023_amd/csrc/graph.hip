@@ -569,15 +569,15 @@ k_mirror_pairs(int64_t N, const int64_t *__restrict__ row_ptr, const uint64_t *_
     }
 }
 
-// chunk_row[c] = first row whose first edge lies at or after c * kChunkEdges; chunk_row[n_chunks] = n_rows.
-__global__ void k_chunk_rows(int64_t n_rows, int64_t n_chunks, const int64_t *__restrict__ row_ptr,
+// chunk_row[c] = first row whose first edge lies at or after c * span; chunk_row[n_chunks] = n_rows.
+__global__ void k_chunk_rows(int64_t n_rows, int64_t n_chunks, int32_t span, const int64_t *__restrict__ row_ptr,
                              int32_t *__restrict__ chunk_row)
 {
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (c > n_chunks) return;
     int64_t lo = 0, hi = n_rows;
     if (c == n_chunks) lo = n_rows;
-    const int64_t v = c * kChunkEdges;
+    const int64_t v = c * span;
     while (lo < hi) {
         const int64_t mid = (lo + hi) >> 1;
         if (row_ptr[mid] < v) lo = mid + 1; else hi = mid;
@@ -942,8 +942,8 @@ k_local_fill_ghost(PartTab T, const int32_t *__restrict__ nodes, const int64_t *
 }
 
 // work-item tables of all partitions: entry c of partition q = first local row whose first edge lies at or after
-// c * kChunkEdges; the last entry = n_local
-__global__ void k_chunk_rows_parts(PartTab T, const int64_t *__restrict__ lrow_ptr, int32_t *__restrict__ chunk_row)
+// c * span; the last entry = n_local
+__global__ void k_chunk_rows_parts(PartTab T, int32_t span, const int64_t *__restrict__ lrow_ptr, int32_t *__restrict__ chunk_row)
 {
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= T.chunk0[T.P]) return;
@@ -953,7 +953,7 @@ __global__ void k_chunk_rows_parts(PartTab T, const int64_t *__restrict__ lrow_p
     const int64_t *rp = lrow_ptr + T.row0[q] + q;
     int64_t lo = 0, hi = n_rows;
     if (c == n_chunks) lo = n_rows;
-    const int64_t v = c * kChunkEdges;
+    const int64_t v = c * span;
     while (lo < hi) {
         const int64_t mid = (lo + hi) >> 1;
         if (rp[mid] < v) lo = mid + 1; else hi = mid;
@@ -1254,6 +1254,7 @@ struct PairArgs {   // one partition
 };
 struct PairBatch {   // rows, edges and work items numbered across the partitions
     int n;
+    int32_t span;   // edges per work item
     int64_t row_start[kPairBatch + 1], edge_start[kPairBatch + 1], chunk_start[kPairBatch + 1];
     PairArgs s[kPairBatch];
 };
@@ -1320,7 +1321,7 @@ __global__ void k_pair_rowptr(PairBatch B, const int32_t *__restrict__ scan)
     A.l_row_ptr[r] = A.row_ptr[r] - u;
 }
 
-// u_chunk_row[c] = first row whose first upper edge lies at or after c * kChunkEdges; u_chunk_row[n_chunks] = n_rows.
+// u_chunk_row[c] = first row whose first upper edge lies at or after c * span; u_chunk_row[n_chunks] = n_rows.
 __global__ void k_pair_chunks(PairBatch B)
 {
     const int64_t gc = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;   // work item, plus one closing entry per partition
@@ -1332,7 +1333,7 @@ __global__ void k_pair_chunks(PairBatch B)
     const int64_t c = gc - (B.chunk_start[part] + part);   // 0 .. n_chunks
     int64_t lo = 0, hi = A.n_rows;
     if (c == A.n_chunks) lo = A.n_rows;
-    const int64_t v = c * kChunkEdges;
+    const int64_t v = c * B.span;
     while (lo < hi) {
         const int64_t mid = (lo + hi) >> 1;
         if (A.u_row_ptr[mid] < v) lo = mid + 1; else hi = mid;
@@ -1358,10 +1359,14 @@ int build_pairs_impl(mlip_graph *g, SlabView *views, int P, bool slots_full, Car
         ptr = buf.as<T>();
         return MLIP_OK;
     };
+    int64_t n_upper_total = 0;   // (each view's share as below)
+    for (int p = 0; p < P; ++p) n_upper_total += views[p].n_edges / 2;
+    const int32_t span = chunk_span(n_upper_total * std::min(P, kPairBatch) / P);
     for (int p = 0; p < P; ++p) {
         SlabView &v = views[p];
         PairGraph &Q = v.pairs;
         Q.valid = false;
+        Q.span = span;
         const int64_t E = v.n_edges_owned, N = v.n_owned;
         // every pair of two owned-row edges has one upper edge; an owned-row edge from a ghost sender is an upper edge,
         // and the ghost rows hold exactly the reverse edges of those
@@ -1377,7 +1382,7 @@ int build_pairs_impl(mlip_graph *g, SlabView *views, int P, bool slots_full, Car
         MLIP_TRY(place(Q.b_u_eid, Ucap * 4, Q.u_eid));
         MLIP_TRY(place(Q.b_u_mirror, Ucap * 4, Q.u_mirror));
         MLIP_TRY(place(Q.b_u_d, Ucap * 4, Q.u_d));
-        MLIP_TRY(place(Q.b_u_chunk_row, (size_t)(chunks_of(Q.n_upper) + 1) * 4, Q.u_chunk_row));
+        MLIP_TRY(place(Q.b_u_chunk_row, (size_t)(chunks_of(Q.n_upper, Q.span) + 1) * 4, Q.u_chunk_row));
         const size_t Lcap = (size_t)std::max<int64_t>(Q.n_lower, 1);
         MLIP_TRY(place(Q.b_l_row_ptr, (Ncap + 1) * 8, Q.l_row_ptr));
         MLIP_TRY(place(Q.b_l_senders, Lcap * 4, Q.l_senders));
@@ -1387,6 +1392,7 @@ int build_pairs_impl(mlip_graph *g, SlabView *views, int P, bool slots_full, Car
     for (int p0 = 0; p0 < P; p0 += kPairBatch) {
         PairBatch b{};
         b.n = std::min(kPairBatch, P - p0);
+        b.span = span;
         b.row_start[0] = b.edge_start[0] = b.chunk_start[0] = 0;
         for (int q = 0; q < kPairBatch; ++q) {
             if (q >= b.n) {
@@ -1400,7 +1406,7 @@ int build_pairs_impl(mlip_graph *g, SlabView *views, int P, bool slots_full, Car
             PairArgs &a = b.s[q];
             a.n_rows = v.n_owned;
             a.n_edges_owned = v.n_edges_owned;
-            a.n_chunks = chunks_of(Q.n_upper);
+            a.n_chunks = chunks_of(Q.n_upper, Q.span);
             a.row_ptr = v.row_ptr;
             a.senders = v.senders;
             a.recv = v.recv;
@@ -1716,9 +1722,10 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
     MLIP_TRY(g->mirror.ensure((size_t)std::max<int64_t>(E, 1) * 4));
 
     {
-        const int64_t nc = chunks_of(E);
+        g->whole.span = chunk_span(E);
+        const int64_t nc = chunks_of(E, g->whole.span);
         MLIP_TRY(g->chunk_row.ensure((size_t)(nc + 1) * 4));
-        k_chunk_rows<<<blocks_for(nc + 1, 256), 256, 0, s>>>(N, nc, g->row_ptr.as<int64_t>(), g->chunk_row.as<int32_t>());
+        k_chunk_rows<<<blocks_for(nc + 1, 256), 256, 0, s>>>(N, nc, g->whole.span, g->row_ptr.as<int64_t>(), g->chunk_row.as<int32_t>());
         MLIP_HIP(hipGetLastError());
     }
 
@@ -1839,6 +1846,7 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
             set_error("internal error: an edge without its reverse edge");
             return MLIP_EHIP;
         }
+        const int32_t span = chunk_span(E * std::min(P, kPairBatch) / P);   // edges of one launch over up to kPairBatch partitions
         int64_t TE = 0;
         std::vector<int64_t> ebase(P + 1);
         for (int q = 0; q < P; ++q) {
@@ -1849,7 +1857,8 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
             TE += v.n_edges;
             T.n_edges[q] = v.n_edges;
             T.chunk0[q] = chunk_total;
-            chunk_total += chunks_of(v.n_edges) + 1;
+            v.span = span;
+            chunk_total += chunks_of(v.n_edges, span) + 1;
         }
         ebase[P] = TE;
         T.chunk0[P] = chunk_total;
@@ -1877,7 +1886,7 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
                 st.mirror.as<int32_t>());
             MLIP_HIP(hipGetLastError());
         }
-        k_chunk_rows_parts<<<blocks_for(chunk_total, 256), 256, 0, s>>>(T, st.row_ptr.as<int64_t>(), st.chunk_row.as<int32_t>());
+        k_chunk_rows_parts<<<blocks_for(chunk_total, 256), 256, 0, s>>>(T, span, st.row_ptr.as<int64_t>(), st.chunk_row.as<int32_t>());
         MLIP_HIP(hipGetLastError());
         for (int q = 0; q < P; ++q) {
             SlabView &v = g->slabs[q];

@@ -92,12 +92,20 @@ __device__ inline unsigned xcd_block() { return (blockIdx.x & 7u) * (gridDim.x >
 #endif
 inline unsigned grid8(int64_t blocks) { return (unsigned)(((blocks > 0 ? blocks : 1) + 7) / 8 * 8); }
 
-// Work item of the edge kernels: the rows whose first edge lies in one span of kChunkEdges edges.
-#ifndef MLIP_CHUNK
-#define MLIP_CHUNK 1024
-#endif
-constexpr int kChunkEdges = MLIP_CHUNK;
-inline int64_t chunks_of(int64_t n_edges) { return n_edges > 0 ? (n_edges + kChunkEdges - 1) / kChunkEdges : 1; }
+// Work item of the edge kernels: the rows whose first edge lies in one span of `span` edges.  A wavefront walks an item
+// serially (about 5 us per 32 edges when little else runs), so the span is taken from the edges of the launch: 8 items
+// for each of the 2048 wavefronts that are resident at once (256 compute units, 8 wavefronts of the reverse kernel on
+// each), at least 32 edges (one tile) and at most 1024 (longer items no longer pay for their pipeline fill, shorter ones
+// do at a million atoms).  Measured, us per pass of graph + energy + forces with 1024 edges throughout -> this rule: 500 atoms
+// 1587 -> 632, 4,000 atoms 1487 -> 643, 108,000 atoms in 8 slabs 4732 -> 4233, a million atoms unchanged; 4 items per
+// wavefront 4302 and 2 items 4591 at 108,000 atoms, a least span of 64 edges 697 at 500 atoms.
+constexpr int kEdgeWaves = 2048, kItemsPerWave = 8, kSpanMin = 32, kSpanMax = 1024;
+inline int32_t chunk_span(int64_t n_edges)
+{
+    const int64_t even = n_edges / (kEdgeWaves * kItemsPerWave);
+    return (int32_t)(even < kSpanMin ? kSpanMin : even > kSpanMax ? kSpanMax : even);
+}
+inline int64_t chunks_of(int64_t n_edges, int32_t span) { return n_edges > 0 ? (n_edges + span - 1) / span : 1; }
 
 // Bond graph of the three-body variant for one partition: the edges of its owned rows within the bond cutoff,
 // in edge order (all bonds of an owned centre belong to its partition).
@@ -141,7 +149,8 @@ struct PairGraph {
     // [n_upper]: sender row, receiver row, edge, reverse edge
     int32_t *u_senders = nullptr, *u_recv = nullptr, *u_eid = nullptr, *u_mirror = nullptr;
     float *u_d = nullptr;                             // [n_upper]
-    int32_t *u_chunk_row = nullptr;                   // [chunks_of(n_upper) + 1]
+    int32_t span = 0;                                 // edges per work item
+    int32_t *u_chunk_row = nullptr;                   // [chunks_of(n_upper, span) + 1]
 };
 
 // One partition as the model kernels see it.  The whole graph is the special
@@ -156,7 +165,8 @@ struct SlabView {
     const int32_t *recv = nullptr;         // receiver (local row) of every edge
     const int32_t *mirror = nullptr;       // position of every edge's reverse edge
     const float *d = nullptr;              // edge lengths
-    const int32_t *chunk_row = nullptr;    // [chunks_of(n_edges) + 1] first row of every work item, then n_local
+    int32_t span = 0;                      // edges per work item
+    const int32_t *chunk_row = nullptr;    // [chunks_of(n_edges, span) + 1] first row of every work item, then n_local
     const int32_t *ghost_owner = nullptr;  // [n_ghost] owning slab
     const int32_t *ghost_src = nullptr;    // [n_ghost] local index inside the owner
     const int32_t *owned_sorted = nullptr; // [n_owned] owned atoms, ascending global id
@@ -174,7 +184,7 @@ struct PartStore {
     DevBuf nodes, owned_sorted, ghost_owner, ghost_src;   // i32, pieces of n_local / n_owned / n_ghost entries
     DevBuf rowlen, row_abs, row_ptr;                      // i32 / i64 / i64, pieces of n_local + 1 entries
     DevBuf senders, recv, mirror, shiftp, d;              // pieces of n_edges entries
-    DevBuf chunk_row;                                     // i32, pieces of chunks_of(n_edges) + 1 entries
+    DevBuf chunk_row;                                     // i32, pieces of chunks_of(n_edges, span) + 1 entries
     DevBuf gbase, ghost_local;                            // i32 [N + 1] scan of popcount(needed_by); i32 [sum n_ghost]
     DevBuf sizes;                                         // i64 small read-back area
 };

@@ -309,7 +309,8 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
     MLIP_TRY(place(g->energy_part, (size_t)std::max<int64_t>(n_parts, 1) * sizeof(double), energy_part_f));
     MLIP_TRY(place(g->wpack, pk.total * sizeof(float), wp));
     float *work_f = nullptr;
-    const size_t work_n = (size_t)kWorkLaunches * 8 * kWorkCounterStride;
+    // one set of counters per edge-kernel launch: two per layer and batch of partitions
+    const size_t work_n = (size_t)std::max(1, 2 * L * ((P + kBatch - 1) / kBatch)) * 8 * kWorkCounterStride;
     MLIP_TRY(place(g->work, work_n * sizeof(int32_t), work_f));
     if (scratch && scratch->failed()) {
         set_error("this graph and model need more than the %zu bytes of static workspace", scratch->size);
@@ -621,7 +622,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
                 SlabView &v = views[p0 + q];
                 EdgeArgs &ea = eb.s[q];
                 ea.n_rows = v.n_owned;
-                ea.n_chunks = chunks_of(v.n_edges_owned);
+                ea.n_chunks = chunks_of(v.n_edges_owned, v.span);
                 ea.chunk_row = v.chunk_row;
                 ea.n_nodes = v.n_local;
                 ea.row_ptr = v.row_ptr;
@@ -635,7 +636,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
                 if (upper) {   // the same kernel on the partition's upper-edge graph: row sums of the upper edges, every
                                // edge's filter values kept one after another
                     const PairGraph &Q = v.pairs;
-                    ea.n_chunks = chunks_of(Q.n_upper);
+                    ea.n_chunks = chunks_of(Q.n_upper, Q.span);
                     ea.chunk_row = Q.u_chunk_row;
                     ea.row_ptr = Q.u_row_ptr;
                     ea.senders = Q.u_senders;
@@ -741,7 +742,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
                 SlabView &v = views[p0 + q];
                 EdgeArgs &ea = eb.s[q];
                 ea.n_rows = v.n_owned;
-                ea.n_chunks = chunks_of(v.n_edges_owned);
+                ea.n_chunks = chunks_of(v.n_edges_owned, v.span);
                 ea.chunk_row = v.chunk_row;
                 ea.n_nodes = v.n_local;
                 ea.row_ptr = v.row_ptr;
@@ -757,7 +758,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
                 ea.n_stored = need_gbar ? v.n_edges_owned : 0;
                 if (upper_bwd) {   // on the partition's upper-edge graph
                     const PairGraph &Q = v.pairs;
-                    ea.n_chunks = chunks_of(Q.n_upper);
+                    ea.n_chunks = chunks_of(Q.n_upper, Q.span);
                     ea.chunk_row = Q.u_chunk_row;
                     ea.row_ptr = Q.u_row_ptr;
                     ea.senders = Q.u_senders;

@@ -106,7 +106,7 @@ __device__ inline int32_t uniform_load(const int32_t *p, int64_t i)
     return reinterpret_cast<const_i32_ptr>(reinterpret_cast<uintptr_t>(p))[i];
 }
 
-// wavefront work item: the rows whose first edge lies in [chunk * kChunkEdges, (chunk + 1) * kChunkEdges)
+// wavefront work item: the rows whose first edge lies in [chunk * span, (chunk + 1) * span)
 __device__ inline bool chunk_rows(const EdgeArgs &A, int64_t chunk, int64_t &r0, int64_t &r1)
 {
     r0 = uniform_load(A.chunk_row, chunk);

@@ -1,0 +1,59 @@
+"""Launch shapes at their edges: systems whose rows are empty, longer than a work item, or fewer than a tile, so that
+work items, tiles and slabs come out empty or partly filled; energy and forces against the fp64 oracle."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from oracle import graph as og
+from oracle import model as om
+
+from gpu_util import gpu_energy_forces, gpu_graph
+
+pytestmark = pytest.mark.gpu
+
+
+def _spread(rng, n, side, least):
+    """n points in a cube, no two closer than `least`"""
+    out = [rng.uniform(0, side, 3)]
+    while len(out) < n:
+        p = rng.uniform(0, side, 3)
+        if min(np.linalg.norm(p - q) for q in out) >= least:
+            out.append(p)
+    return np.array(out)
+
+
+def _system(kind):
+    rng = np.random.default_rng(31)
+    cell = np.diag([90.0, 20.0, 20.0])
+    lone = np.array([[60.0 + 6.5 * k, 10.0, 10.0] for k in range(4)])       # no neighbours at all
+    if kind == "pair":
+        return np.array([[1.0, 1.0, 1.0], [3.0, 1.5, 1.0]]), cell
+    if kind == "ball":     # rows of 60 and more edges (more than the shortest work item) between empty rows
+        ball = _spread(rng, 70, 7.0, 1.1) + 5.0
+        return np.concatenate([lone[:2], ball, lone[2:]]), cell
+    if kind == "chain":    # two edges per row: many rows per tile and three rows inside one step
+        return np.concatenate([np.array([[4.0 * k + 0.3 * (k % 3), 10.0, 10.0] for k in range(14)]), lone]), cell
+    ball = _spread(rng, 33, 9.0, 1.4)   # "halves": two groups far apart, slabs between them own nothing
+    return np.concatenate([ball, ball[::-1] + np.array([45.0, 5.0, 5.0])]), cell
+
+
+@pytest.mark.parametrize("kind", ["pair", "ball", "chain", "halves"])
+@pytest.mark.parametrize("F,L", [(32, 1), (64, 3)])
+def test_rows_at_the_edges_of_items_and_tiles(kind, F, L):
+    import paper_2506_02023_amd as M
+    pos, cell = _system(kind)
+    species = (np.arange(len(pos)) % 4).astype(np.int32)
+    weights = wl.rmp_weights(4, F, L, 77)
+    ref_g = og.build_graph(pos, cell, 5.0)
+    ref = om.energy_forces(pos, cell, species, weights, ref_g, 5.0, 8, 6)
+    for P in (1, 2, 5):
+        g = gpu_graph(pos, cell, species, 5.0, n_slabs=P)
+        row_ptr, senders, _, _ = g.csr()
+        assert np.array_equal(row_ptr, ref_g.row_ptr) and np.array_equal(senders, ref_g.senders)
+        for precision in (0, 2):
+            e, f, eps = gpu_energy_forces(g, weights, 6, M.MODE_SLABS if P > 1 else M.MODE_WHOLE, precision)
+            what = f"{kind} F {F} L {L} P {P} precision {precision}"
+            scale = np.abs(ref["atom_energy"]).sum()
+            assert abs(e - ref["energy"]) <= 1e-5 * scale, what
+            assert np.abs(eps - ref["atom_energy"]).max() <= 1e-5 * np.abs(ref["atom_energy"]).max(), what
+            assert np.abs(f - ref["forces"]).max() <= 1e-4 * np.abs(ref["forces"]).max(), what
