@@ -57,3 +57,37 @@ def test_rows_at_the_edges_of_items_and_tiles(kind, F, L):
             assert abs(e - ref["energy"]) <= 1e-5 * scale, what
             assert np.abs(eps - ref["atom_energy"]).max() <= 1e-5 * np.abs(ref["atom_energy"]).max(), what
             assert np.abs(f - ref["forces"]).max() <= 1e-4 * np.abs(ref["forces"]).max(), what
+
+
+@pytest.mark.parametrize("case", ["one_cell", "thin", "crowded", "many_cells", "overflow"])
+def test_search_over_cells(case):
+    """Cells with no, few and more than 64 atoms, one cell in all, more than 64 surrounding cells, images of an atom
+    itself, more than 4096 cells, and rows longer than the staging rows hold: the graph bit for bit."""
+    rng = np.random.default_rng(5)
+    if case == "one_cell":      # every pair is seen through several images of the one cell
+        pos, cell, sp = wl.random_triclinic(9, 3, scale=3.2, skew=0.2, spread=2.0)
+    elif case == "thin":        # reach of 4 cells along the thin direction: 9 x 3 x 3 surrounding cells and more
+        cell = np.array([[1.7, 0.0, 0.0], [0.3, 14.0, 0.0], [0.0, 1.0, 16.0]])
+        pos = rng.uniform(0, 1, (11, 3)) @ cell
+    elif case == "crowded":     # a sparse system whose cells were widened: 150 atoms fall into a few of them
+        cell = np.diag([900.0, 900.0, 900.0])
+        pos = np.concatenate([_spread(rng, 150, 20.0, 1.2) + 400.0, rng.uniform(0, 900, (30, 3))])
+    elif case == "many_cells":  # 17^3 cells, most of them empty, four to a block
+        cell = np.diag([86.0, 87.0, 88.0])
+        pos = np.concatenate([_spread(rng, 120, 25.0, 1.0) + 70.0, rng.uniform(0, 86, (700, 3))])
+    else:                       # more than 64 finds of one atom: the build falls back to the two-pass search
+        cell = np.diag([30.0, 30.0, 30.0])
+        pos = _spread(rng, 260, 8.5, 0.75) + 3.0
+    sp = np.zeros(len(pos), np.int32)
+    ref = og.build_graph(pos, cell, 5.0)
+    if case == "overflow":
+        assert np.diff(ref.row_ptr).max() > 128
+    for P in (1, 3):
+        g = gpu_graph(pos, cell, sp, 5.0, n_slabs=P)
+        row_ptr, senders, shifts, d = g.csr()
+        assert np.array_equal(row_ptr, ref.row_ptr) and np.array_equal(senders, ref.senders)
+        assert np.array_equal(shifts, ref.shifts)
+        assert np.array_equal(d, og.geometry(pos, cell, ref)[0].astype(np.float32))
+        m = g.mirror()
+        recv = np.repeat(np.arange(len(pos)), np.diff(row_ptr))
+        assert np.array_equal(recv[m], senders) and np.array_equal(shifts[m], -shifts) and np.array_equal(m[m], np.arange(len(m)))
