@@ -391,32 +391,27 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
     // ---- pack weights (kept in the handle until a call comes with a different weight struct; the fixed block of
     // the static variant is shared by all handles, so there they are packed on every call)
     prof_begin(g, MLIP_PROF_NODE);
-    const unsigned pb = blocks_for((int64_t)F * F, 256);
     const bool repack = scratch != nullptr || !g->packed_w_valid || std::memcmp(&g->packed_w, w, sizeof(*w)) != 0;
     g->packed_w_valid = false;
-    for (int l = 0; repack && l < L; ++l) {
-        float *base = wp + pk.per_layer * l;
-        const size_t ff = (size_t)F * F;
-        k_pack_w1<<<blocks_for((F / 32) * 256, 256), 256, 0, s>>>(w->W1 + (size_t)l * 8 * F, F, 1.0f, base + pk.A1);
-        k_pack_w1<<<blocks_for((F / 32) * 256, 256), 256, 0, s>>>(w->W1 + (size_t)l * 8 * F, F, kSiluScale, base + pk.A1s);
-        if (prec == kPrecBf16) {   // the two W2 operands as bf16 packs (half of their slots)
-            k_pack_ff_bf16<<<pb, 256, 0, s>>>(w->W2 + l * ff, F, 1, kSiluScaleInv, reinterpret_cast<__bf16 *>(base + pk.W2t));
-            k_pack_ff_bf16<<<pb, 256, 0, s>>>(w->W2 + l * ff, F, 0, 1.0f, reinterpret_cast<__bf16 *>(base + pk.W2n));
-        } else if (prec == kPrecF16x3) {   // as split-fp16 packs (hi and lo halves)
-            k_pack_ff_f16x2<<<pb, 256, 0, s>>>(w->W2 + l * ff, F, 1, kSiluScaleInv, reinterpret_cast<_Float16 *>(base + pk.W2t));
-            k_pack_ff_f16x2<<<pb, 256, 0, s>>>(w->W2 + l * ff, F, 0, 1.0f, reinterpret_cast<_Float16 *>(base + pk.W2n));
-        } else {
-            k_pack_ff<<<pb, 256, 0, s>>>(w->W2 + l * ff, F, 1, kSiluScaleInv, base + pk.W2t);
-            k_pack_ff<<<pb, 256, 0, s>>>(w->W2 + l * ff, F, 0, 1.0f, base + pk.W2n);
-        }
-        k_pack_ff<<<pb, 256, 0, s>>>(w->Wm + l * ff, F, 1, 1.0f, base + pk.Wmt);
-        k_pack_ff<<<pb, 256, 0, s>>>(w->Wm + l * ff, F, 0, 1.0f, base + pk.Wmn);
-        k_pack_ff<<<pb, 256, 0, s>>>(w->Wo + l * ff, F, 1, 1.0f, base + pk.Wot);
-        k_pack_ff<<<pb, 256, 0, s>>>(w->Wo + l * ff, F, 0, 1.0f, base + pk.Won);
-    }
+    const int ff_kind = prec == kPrecBf16 ? PACK_FF_BF16 : prec == kPrecF16x3 ? PACK_FF_F16X2 : PACK_FF;   // the filter MLP's W2
     if (repack) {
-        k_pack_ff<<<pb, 256, 0, s>>>(w->Wr1, F, 1, 1.0f, wp + pk.readout_t);
-        k_pack_ff<<<pb, 256, 0, s>>>(w->Wr1, F, 0, 1.0f, wp + pk.readout_n);
+        PackBatch pb{};
+        pb.F = F;
+        const size_t ff = (size_t)F * F;
+        for (int l = 0; l < L; ++l) {
+            float *base = wp + pk.per_layer * l;
+            pb.add(w->W1 + (size_t)l * 8 * F, base + pk.A1, PACK_W1, 0, 1.0f);
+            pb.add(w->W1 + (size_t)l * 8 * F, base + pk.A1s, PACK_W1, 0, kSiluScale);
+            pb.add(w->W2 + l * ff, base + pk.W2t, ff_kind, 1, kSiluScaleInv);
+            pb.add(w->W2 + l * ff, base + pk.W2n, ff_kind, 0, 1.0f);
+            pb.add(w->Wm + l * ff, base + pk.Wmt, PACK_FF, 1, 1.0f);
+            pb.add(w->Wm + l * ff, base + pk.Wmn, PACK_FF, 0, 1.0f);
+            pb.add(w->Wo + l * ff, base + pk.Wot, PACK_FF, 1, 1.0f);
+            pb.add(w->Wo + l * ff, base + pk.Won, PACK_FF, 0, 1.0f);
+        }
+        pb.add(w->Wr1, wp + pk.readout_t, PACK_FF, 1, 1.0f);
+        pb.add(w->Wr1, wp + pk.readout_n, PACK_FF, 0, 1.0f);
+        k_pack<<<dim3(blocks_for((int64_t)F * F, 256), pb.n), 256, 0, s>>>(pb);
     }
     MLIP_HIP(hipGetLastError());
     if (!scratch) {
@@ -508,17 +503,10 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         const bool repack_b = !g->packed_bw_valid || std::memcmp(&g->packed_bw, bw, sizeof(*bw)) != 0 ||
                               std::memcmp(&g->packed_bw_w, w, sizeof(*w)) != 0;
         g->packed_bw_valid = false;
-        // the bond MLPs' F x F products follow the filter MLP's precision mode: fp32 pack, bf16 in the first half of the
-        // slot, or split-fp16 (hi and lo halves)
-        auto pack_bond = [&](const float *Wsrc, int trans, int slot) {
-            if (prec == kPrecBf16)
-                k_pack_ff_bf16<<<pb, 256, 0, s>>>(Wsrc, F, trans, 1.0f, reinterpret_cast<__bf16 *>(bpk + (size_t)slot * ffp));
-            else if (prec == kPrecF16x3)
-                k_pack_ff_f16x2<<<pb, 256, 0, s>>>(Wsrc, F, trans, 1.0f, reinterpret_cast<_Float16 *>(bpk + (size_t)slot * ffp));
-            else
-                k_pack_ff<<<pb, 256, 0, s>>>(Wsrc, F, trans, 1.0f, bpk + (size_t)slot * ffp);
-        };
-        if (repack_b) {
+        if (repack_b) {   // the bond MLPs' F x F products follow the filter MLP's precision mode
+            PackBatch pb{};
+            pb.F = F;
+            auto pack_bond = [&](const float *Wsrc, int trans, int slot) { pb.add(Wsrc, bpk + (size_t)slot * ffp, ff_kind, trans, 1.0f); };
             pack_bond(Wta, 1, 0);
             pack_bond(Wtb, 1, 1);
             pack_bond(bw->Wt2, 1, 2);
@@ -529,7 +517,8 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
                 pack_bond(bw->Wb + l * ffp, 1, 6 + l);
                 pack_bond(bw->Wb + l * ffp, 0, 6 + L + l);
             }
-            k_pack_w1<<<blocks_for(Dims<F>::PACK1, 256), 256, 0, s>>>(bw->We0, F, 1.0f, bpk + (size_t)(6 + 2 * L) * ffp);
+            pb.add(bw->We0, bpk + (size_t)(6 + 2 * L) * ffp, PACK_W1, 0, 1.0f);
+            k_pack<<<dim3(blocks_for((int64_t)F * F, 256), pb.n), 256, 0, s>>>(pb);
         }
         MLIP_HIP(hipGetLastError());
         g->packed_bw = *bw;

@@ -401,7 +401,7 @@ struct BondArgs {                      // one partition
     const float *d, *u, *du;           // [n] length, envelope at the bond cutoff, its derivative
     const int32_t *edge, *sender;      // [n] edge index, sender row of a bond
     const int32_t *recv;               // receiver row of an edge
-    const float *We0p;                 // We0 packed for the K = 8 product (k_pack_w1)
+    const float *We0p;                 // We0 packed for the K = 8 product (PACK_W1)
     BasisParams bp;                    // radial basis at the bond cutoff
     const float *W[4];                 // packed F x F operands of the stage (TAIL: Wt2, then the first layers' Wb;
                                        // EBAR: Wt2^T, then the first layers' Wb^T)

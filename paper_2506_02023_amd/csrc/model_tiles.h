@@ -120,69 +120,73 @@ __device__ inline void radial_basis(float d, const BasisParams &bp, float (&b)[8
 
 // ---------------------------------------------------------------- packed weights
 //
-// pack_ff: F x F matrix M[o][k] as MFMA A operands, index
+// PACK_FF: F x F matrix M[o][k] as MFMA A operands, index
 //   ((((bo * NB + bi) * 4 + a) * 64 + lane) * 4 + c)  ->  M[32 bo + lane % 32][32 bi + 8 a + 4 (lane / 32) + c]
 // with M[o][k] = W[k][o] (TRANS, y = x W) or W[o][k] (y = x W^T).
-// pack_w1: K = 8 rows, index ((bo * 4 + s) * 64 + lane) -> W1[2 s + lane / 32][32 bo + lane % 32].
-
-__global__ void k_pack_ff(const float *__restrict__ W, int F, int trans, float scale, float *__restrict__ out)
-{
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= F * F) return;
-    const int NB = F / 32;
-    const int c = idx & 3, lane = (idx >> 2) & 63, a = (idx >> 8) & 3, bb = idx >> 10;
-    const int bi = bb % NB, bo = bb / NB;
-    const int o = 32 * bo + (lane & 31);
-    const int k = 32 * bi + 8 * a + 4 * (lane >> 5) + c;
-    out[idx] = scale * (trans ? W[k * F + o] : W[o * F + k]);
-}
-
-__global__ void k_pack_w1(const float *__restrict__ W1, int F, float scale, float *__restrict__ out)
-{
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    const int NB = F / 32;
-    if (idx >= NB * 4 * 64) return;
-    const int lane = idx & 63, s = (idx >> 6) & 3, bo = idx >> 8;
-    out[idx] = scale * W1[(2 * s + (lane >> 5)) * F + 32 * bo + (lane & 31)];
-}
-
+// PACK_W1: K = 8 rows, index ((bo * 4 + s) * 64 + lane) -> W1[2 s + lane / 32][32 bo + lane % 32].
+//
 // bf16 form of an F x F operand for v_mfma_f32_32x32x16_bf16 (the bf16 precision mode: the W2 products of the
 // filter MLP run on the bf16 matrix pipeline with fp32 accumulation, at 1/16 of the fp32 MFMA time).
 // Index (((bo * NB + bi) * 2 + q) * 64 + lane) * 8 + t  ->  M[32 bo + lane % 32][32 bi + 8 (r / 4) + 4 (lane / 32) + r % 4],
 // r = 8 q + t: element t of lane-half h of MFMA (bi, q) pairs with accumulator register r of a chained product
 // (or with the same feature of an item-major LDS row).
-__global__ void k_pack_ff_bf16(const float *__restrict__ W, int F, int trans, float scale, __bf16 *__restrict__ out)
-{
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= F * F) return;
-    const int NB = F / 32;
-    const int t = idx & 7, lane = (idx >> 3) & 63, q = (idx >> 9) & 1, bb = idx >> 10;
-    const int bi = bb % NB, bo = bb / NB;
-    const int r = 8 * q + t;
-    const int o = 32 * bo + (lane & 31);
-    const int k = 32 * bi + 8 * (r / 4) + 4 * (lane >> 5) + (r & 3);
-    out[idx] = (__bf16)(scale * (trans ? W[k * F + o] : W[o * F + k]));
-}
-
+//
 // Split-fp16 form of the same operand: every fp32 value v is kept as hi + lo, hi = fp16(v), lo = fp16(v - hi)
 // (22 significant bits together); a product of two such values is taken as hi hi + hi lo + lo hi with fp32
 // accumulation.  What is dropped (lo lo, and the rounding of the two lo parts) is about 3 * 2^-22 of the term,
 // the size of the rounding an fp32 accumulation of 64 terms makes anyway, at 3/16 of the fp32 MFMA's matrix time.
 // hi parts first (F * F halves), then lo parts: together the bytes of the fp32 pack.
-__global__ void k_pack_ff_f16x2(const float *__restrict__ W, int F, int trans, float scale, _Float16 *__restrict__ out)
+//
+// Operand packs a call needs are made by one launch: one job per pack (blockIdx.y), one thread per element.  Every
+// pack in a launch of its own took 2 us of device time and a launch each, 20 to 26 per model.
+enum { PACK_W1 = 0, PACK_FF = 1, PACK_FF_BF16 = 2, PACK_FF_F16X2 = 3 };
+struct PackJob {
+    const float *W;
+    float *out;
+    float scale;
+    int16_t kind, trans;
+};
+constexpr int kPackJobs = 66;   // 8 layers x 8 packs and the readout's two; the bond part has 6 + 2 x 8 + 1
+struct PackBatch {
+    int n, F;
+    PackJob job[kPackJobs];
+    void add(const float *W, float *out, int kind, int trans, float scale) { job[n++] = PackJob{W, out, scale, (int16_t)kind, (int16_t)trans}; }
+};
+
+__global__ void k_pack(PackBatch B)
 {
+    const PackJob &J = B.job[blockIdx.y];
+    const int F = B.F, NB = F / 32;
+    const float *__restrict__ W = J.W;
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+    if (J.kind == PACK_W1) {
+        if (idx >= NB * 4 * 64) return;
+        const int lane = idx & 63, s = (idx >> 6) & 3, bo = idx >> 8;
+        J.out[idx] = J.scale * W[(2 * s + (lane >> 5)) * F + 32 * bo + (lane & 31)];
+        return;
+    }
     if (idx >= F * F) return;
-    const int NB = F / 32;
-    const int t = idx & 7, lane = (idx >> 3) & 63, q = (idx >> 9) & 1, bb = idx >> 10;
-    const int bi = bb % NB, bo = bb / NB;
-    const int r = 8 * q + t;
-    const int o = 32 * bo + (lane & 31);
-    const int k = 32 * bi + 8 * (r / 4) + 4 * (lane >> 5) + (r & 3);
-    const float v = scale * (trans ? W[k * F + o] : W[o * F + k]);
-    const _Float16 h = (_Float16)v;
-    out[idx] = h;
-    out[F * F + idx] = (_Float16)(v - (float)h);
+    const int bb = idx >> 10, bi = bb % NB, bo = bb / NB;
+    int o, k;
+    if (J.kind == PACK_FF) {
+        const int c = idx & 3, lane = (idx >> 2) & 63, a = (idx >> 8) & 3;
+        o = 32 * bo + (lane & 31);
+        k = 32 * bi + 8 * a + 4 * (lane >> 5) + c;
+    } else {
+        const int t = idx & 7, lane = (idx >> 3) & 63, q = (idx >> 9) & 1, r = 8 * q + t;
+        o = 32 * bo + (lane & 31);
+        k = 32 * bi + 8 * (r / 4) + 4 * (lane >> 5) + (r & 3);
+    }
+    const float v = J.scale * (J.trans ? W[k * F + o] : W[o * F + k]);
+    if (J.kind == PACK_FF) {
+        J.out[idx] = v;
+    } else if (J.kind == PACK_FF_BF16) {
+        reinterpret_cast<__bf16 *>(J.out)[idx] = (__bf16)v;
+    } else {
+        const _Float16 h = (_Float16)v;
+        reinterpret_cast<_Float16 *>(J.out)[idx] = h;
+        reinterpret_cast<_Float16 *>(J.out)[F * F + idx] = (_Float16)(v - (float)h);
+    }
 }
 
 __device__ inline void split_f16(const float (&v)[8], f16x8 &hi, f16x8 &lo)
