@@ -344,7 +344,7 @@ int mlip_graph_pairs(mlip_graph_t *g, int32_t p, mlip_pairs_t *out)
     if (p < -1 || p >= g->P || (p >= 0 && g->P < 2)) { set_error("partition index out of range"); return MLIP_EINVAL; }
     // all partitions of the mode at once, as mlip_forward builds them
     SlabView *views = (p < 0) ? &g->whole : g->slabs.data();
-    MLIP_TRY(build_pairs_impl(g, views, p < 0 ? 1 : g->P, /*slots_full=*/false, nullptr));
+    MLIP_TRY(build_pairs_impl(g, views, p < 0 ? 1 : g->P, nullptr));
     const PairGraph &Q = (p < 0) ? g->whole.pairs : g->slabs[p].pairs;
     out->n_upper = Q.n_upper;
     out->n_lower = Q.n_lower;
@@ -366,7 +366,7 @@ void mlip_graph_destroy(mlip_graph_t *g)
     DevBuf *bufs[] = {&g->pos, &g->species, &g->cell_of, &g->wrapp, &g->cell_cnt, &g->cell_start, &g->cell_fill,
                       &g->sid, &g->sx, &g->sy, &g->sz, &g->swrap, &g->counts, &g->keys, &g->stage, &g->pair_aux, &g->flags, &g->scan_tmp,
                       &g->small, &g->row_ptr, &g->senders, &g->recv, &g->mirror, &g->shiftp, &g->d, &g->chunk_row, &g->slab_of, &g->needed_by,
-                      &g->local_of, &g->local_in_owner, &g->class_cnt, &g->class_off, &g->wpack, &g->energy_part, &g->work, &g->pair_cnt, &g->pair_scan,
+                      &g->local_of, &g->local_in_owner, &g->class_cnt, &g->class_off, &g->wpack, &g->energy_part, &g->work, &g->pair_cnt, &g->pair_scan, &g->pair_rank,
                       &g->cand_row_ptr, &g->cand_senders, &g->cand_recv, &g->cand_shiftp, &g->cand_d, &g->cand_mirror, &g->ref_pos};
     for (DevBuf *b : bufs) b->release();
     g->bond_wpack.release();
@@ -378,7 +378,7 @@ void mlip_graph_destroy(mlip_graph_t *g)
                         &B.ubar, &B.dbond, &B.rbar};
         for (DevBuf *b : vb) b->release();
         PairGraph &Q = v.pairs;
-        DevBuf *pb[] = {&Q.b_u_row_ptr, &Q.b_wslot, &Q.b_u_senders, &Q.b_u_recv,
+        DevBuf *pb[] = {&Q.b_u_row_ptr, &Q.b_uslot, &Q.b_u_senders, &Q.b_u_recv,
                         &Q.b_u_eid, &Q.b_u_mirror, &Q.b_u_d, &Q.b_u_chunk_row,
                         &Q.b_l_row_ptr, &Q.b_l_senders, &Q.b_l_slot};
         for (DevBuf *b : pb) b->release();

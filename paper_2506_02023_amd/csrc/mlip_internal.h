@@ -131,19 +131,19 @@ struct BondGraph {
 
 // The edges of a partition's owned rows split into the upper and the lower edge of every edge / reverse-edge pair
 // (upper: the one with the smaller index; an edge whose reverse edge lies in a ghost row is an upper edge).  The
-// upper edges are compacted into a graph of their own (same rows, half the edges) on which the edge kernels run;
-// the lower edges' terms are added by row-wise kernels.  Built on first use after a graph build.
+// upper edges are compacted into a graph of their own (same rows, half the edges) on which the reverse edge kernel runs;
+// the lower edges' terms are added by a row-wise kernel.  Built on first use after a graph build.
 struct PairGraph {
     bool valid = false;
-    bool slots_full = false;   // what l_slot holds (below)
     int64_t n_upper = 0, n_lower = 0;
     // grow-only buffers behind the pointers below (unused when the arrays are carved from a caller-independent block)
-    DevBuf b_u_row_ptr, b_wslot, b_u_senders, b_u_recv, b_u_eid, b_u_mirror, b_u_d, b_u_chunk_row;
+    DevBuf b_u_row_ptr, b_uslot, b_u_senders, b_u_recv, b_u_eid, b_u_mirror, b_u_d, b_u_chunk_row;
     DevBuf b_l_row_ptr, b_l_senders, b_l_slot;
     int64_t *u_row_ptr = nullptr;                     // [n_owned + 1]
-    int32_t *wslot = nullptr;                         // [E_owned] upper edges: their index in the upper-edge graph
+    int32_t *uslot = nullptr;                         // [E_owned] upper edges: their index k in the upper-edge graph, where
+                                                      // their filter values are kept; lower edges: ~k, k upper edges before it
     // the lower edges of the owned rows, in their order: CSR [n_owned + 1], sender row, and where the pair's filter
-    // values are kept: the index of its upper edge in the upper-edge graph or (slots_full) in the full list
+    // values are kept: the index of its upper edge in the upper-edge graph
     int64_t *l_row_ptr = nullptr;
     int32_t *l_senders = nullptr, *l_slot = nullptr;  // [n_lower]
     // [n_upper]: sender row, receiver row, edge, reverse edge
@@ -240,7 +240,7 @@ struct mlip_graph {
     mlip::SlabView whole;
     // forward scratch shared by all views
     mlip::DevBuf wpack, energy_part;
-    mlip::DevBuf pair_cnt, pair_scan;   // upper-edge flags over the partitions' edges and their scan (scratch)
+    mlip::DevBuf pair_cnt, pair_scan, pair_rank;   // upper edges per row and their scan, ranks within the rows (scratch)
     mlip::DevBuf work;        // work counters of the edge kernels: one set of 8 per launch of a call, zeroed per call
     int32_t *work_ptr = nullptr;
     int work_next = 0;        // launches that have taken their counters in the current call
@@ -268,7 +268,7 @@ int unpack_shifts(const mlip_graph *g, int32_t *out);
 int build_bonds_impl(mlip_graph *g, SlabView &v, double r_bond, int p_envelope);
 // Upper / lower split of the views' owned-row edges (PairGraph), all views in the same launches; does nothing if all are valid.  With a block to carve from,
 // the arrays are taken from it (and the caller invalidates the structure when the block is given up).
-int build_pairs_impl(mlip_graph *g, SlabView *views, int n_views, bool slots_full, Carver *scratch);
+int build_pairs_impl(mlip_graph *g, SlabView *views, int n_views, Carver *scratch);
 int forward_bonds_impl(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t *bw, int32_t mode,
                        double *energy, float *forces, float *atom_energy);
 

@@ -59,9 +59,10 @@ Packs pack_layout(int F, int L)
     const size_t ff = (size_t)F * F, p1 = (size_t)(F / 32) * 4 * 64;
     p.A1 = 0;
     p.A1s = p1;
+    const size_t ff3 = ff * 3 / 2;   // the filter MLP's operands: three bf16 parts in fp32 mode
     p.W2t = 2 * p1;
-    p.W2n = p.W2t + ff;
-    p.Wmt = p.W2n + ff;
+    p.W2n = p.W2t + ff3;
+    p.Wmt = p.W2n + ff3;
     p.Wmn = p.Wmt + ff;
     p.Wot = p.Wmn + ff;
     p.Won = p.Wot + ff;
@@ -74,8 +75,8 @@ Packs pack_layout(int F, int L)
 
 template <int F> struct Lds {
     using D = Dims<F>;
-    static constexpr size_t edge_fwd = sizeof(float) * (D::PACKF + 4 * D::TILE);
-    static constexpr size_t edge_bwd = sizeof(float) * (D::PACKF + D::PACK1 + kBwdWaves * kQueue * D::FS);
+    static constexpr size_t edge_fwd(int prec) { return sizeof(float) * (pack_floats<F>(prec) + kFwdWaves * D::TILE); }
+    static constexpr size_t edge_bwd(int prec) { return sizeof(float) * (pack_floats<F>(prec) + D::PACK1 + kBwdWaves * kQueue * D::FS); }
     static constexpr size_t node1 = sizeof(float) * (D::PACKF + 4 * D::TILE);
     static constexpr size_t node2 = sizeof(float) * (2 * D::PACKF + 4 * D::TILE);
 };
@@ -160,38 +161,12 @@ int node_pass(mlip_graph *g, SlabView *views, int P, const float *P1, const floa
 // Edge-kernel launches of one call: two per layer and batch of partitions (L <= 8, at most 64 / kBatch batches).
 constexpr int kWorkLaunches = 2 * 8 * (64 / kBatch);
 
-// The reverse edge kernel the library runs is the one whose wavefronts alternate between the two phases.  Building
-// with -DMLIP_BWD_SIMD runs the fp32 mode's launches on the upper-edge graphs with the variant whose phases sit on
-// different SIMDs instead (same results; measured slightly slower, kept for that experiment).
-constexpr bool kUpperGraphs = true;
-template <int F, int PREC, bool COMPACT> struct BwdKernel {
-    static constexpr int threads = kBwdWaves * 64, item_waves = kBwdWaves;
-    static constexpr size_t lds = Lds<F>::edge_bwd;
-    static const void *fn() { return reinterpret_cast<const void *>(&k_edge_bwd<F, PREC, COMPACT>); }
-    static void launch(unsigned blocks, hipStream_t s, const EdgeBatch &b)
-    {
-        k_edge_bwd<F, PREC, COMPACT><<<blocks, threads, lds, s>>>(b);
-    }
-};
-#ifdef MLIP_BWD_SIMD
-template <int F> struct BwdKernel<F, kPrecF32, true> {
-    static constexpr int threads = kSimdWaves * 64, item_waves = kSimdStream;
-    static constexpr size_t lds = BwdSimdLds<F>::bytes;
-    static const void *fn() { return reinterpret_cast<const void *>(&k_edge_bwd_simd<F>); }
-    static void launch(unsigned blocks, hipStream_t s, const EdgeBatch &b) { k_edge_bwd_simd<F><<<blocks, threads, lds, s>>>(b); }
-};
-#endif
-
-enum { kEdgeFwd = 0, kEdgeBwd = 1, kEdgeBwdUpper = 2 };   // kEdgeBwdUpper: the launch runs on upper-edge graphs
-
-template <int F, int PREC, bool COMPACT = false> int launch_edge(mlip_graph *g, EdgeBatch &b, int kind)
+template <int F, int PREC> int launch_edge(mlip_graph *g, EdgeBatch &b, bool backward)
 {
-    if (kind == kEdgeBwdUpper && !COMPACT) return launch_edge<F, PREC, true>(g, b, kind);
-    using BK = BwdKernel<F, PREC, COMPACT>;
-    const bool backward = (kind != kEdgeFwd);
-    const size_t lds = backward ? BK::lds : Lds<F>::edge_fwd;
+    const size_t lds = backward ? Lds<F>::edge_bwd(PREC) : Lds<F>::edge_fwd(PREC);
+    const int threads = (backward ? kBwdWaves : kFwdWaves) * 64;
     // resident blocks per compute unit, queried once per kernel and handle
-    const void *fn = backward ? BK::fn() : reinterpret_cast<const void *>(&k_edge_fwd<F, PREC>);
+    const void *fn = backward ? reinterpret_cast<const void *>(&k_edge_bwd<F, PREC>) : reinterpret_cast<const void *>(&k_edge_fwd<F, PREC>);
     int slot = 0;
     MLIP_TRY(configure_kernel(g, fn, lds, &slot));
     int occ = g->fn_occ[slot].second;
@@ -199,10 +174,7 @@ template <int F, int PREC, bool COMPACT = false> int launch_edge(mlip_graph *g, 
         int dev = 0, o = 0;
         MLIP_HIP(hipGetDevice(&dev));
         MLIP_HIP(hipDeviceGetAttribute(&g->n_cu, hipDeviceAttributeMultiprocessorCount, dev));
-        if (backward)
-            MLIP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, fn, BK::threads, lds));
-        else
-            MLIP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, k_edge_fwd<F, PREC>, 256, lds));
+        MLIP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, fn, threads, lds));
         if (o < 1 || g->n_cu < 8) {
             set_error("edge kernel does not fit the device (occupancy %d, %d compute units)", o, g->n_cu);
             return MLIP_EHIP;
@@ -221,21 +193,16 @@ template <int F, int PREC, bool COMPACT = false> int launch_edge(mlip_graph *g, 
     if (items <= 0) return MLIP_OK;
     // persistent grid: what is resident at once, a multiple of the 8 XCDs, no more than the work needs
     const int64_t resident = (int64_t)(g->n_cu / 8) * occ;
-    const int nw = backward ? BK::item_waves : 4;
-    const int64_t needed = ((items + 7) / 8 + nw - 1) / nw;
+    const int64_t needed = (items + 7) / 8;   // few items: one per block, so that they spread over the compute units
     const unsigned blocks = (unsigned)(8 * std::max<int64_t>(1, std::min(resident, needed)));
     if (backward)
-        BK::launch(blocks, g->stream, b);
+        k_edge_bwd<F, PREC><<<blocks, threads, lds, g->stream>>>(b);
     else
-        k_edge_fwd<F, PREC><<<blocks, 256, lds, g->stream>>>(b);
+        k_edge_fwd<F, PREC><<<blocks, threads, lds, g->stream>>>(b);
     MLIP_HIP(hipGetLastError());
     ++g->work_next;   // only a launch that ran has used its counters
     return MLIP_OK;
 }
-
-// Kept filter values shared by the two edges of a pair on the full edge lists: a lower edge reads its reverse edge's
-// row through one buffer descriptor, whose 32-bit range (less the largest offset a load adds) must span the partition.
-inline bool fits_pairs(const SlabView &v, int F) { return (int64_t)v.n_edges_owned * F * 4 < ((int64_t)1 << 32) - (1 << 20); }
 
 // bw != nullptr: the three-body variant
 template <int F>
@@ -267,21 +234,12 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         ptr = buf.as<float>();
         return MLIP_OK;
     };
-    // With fp32 MFMA the edge kernels run on the partitions' upper-edge graphs (one edge per edge / reverse-edge pair:
-    // both edges have the same length, hence bit for bit the same filter values), and row-wise kernels add the lower
-    // edges' terms.  In the 16-bit product modes the matrix work is cheap and the forward step is faster on the full edge lists.
-    const bool upper = kUpperGraphs && prec == kPrecF32;
-    // Their reverse step, though, streams three rows per edge whatever the precision: it runs on the upper-edge graphs in
-    // those modes too wherever the pairs share their kept filter values (fits_pairs), which then stay where the
-    // forward step on the full lists put them, at the upper edges' own positions.
-    bool upper_bwd = upper;
-    if (kUpperGraphs && prec != kPrecF32 && L > 1) {
-        upper_bwd = true;
-        for (int p = 0; p < P; ++p) upper_bwd = upper_bwd && fits_pairs(views[p], F);
-    }
-    if (upper_bwd) {
+    // Both edges of an edge / reverse-edge pair have the same length, hence bit for bit the same filter values: the
+    // forward kernel keeps those of the upper edges, the reverse kernel runs on the partitions' upper-edge graphs and a
+    // row-wise kernel adds the lower edges' terms.
+    if (L > 0) {
         prof_begin(g, MLIP_PROF_GRAPH);
-        MLIP_TRY(build_pairs_impl(g, views, P, /*slots_full=*/!upper, scratch));
+        MLIP_TRY(build_pairs_impl(g, views, P, scratch));
         prof_end(g);
     }
     int64_t n_parts = 0;
@@ -298,10 +256,8 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         MLIP_TRY(place(v.g, nl * rowb * (size_t)std::max(L, 1), v.ws.g));
         MLIP_TRY(place(v.a, no * rowb * (size_t)std::max(L, 1), v.ws.a));
         v.ws.wst = nullptr;
-        if (L > 0)  // filter values of every layer: layers 1..L-1 are kept for the reverse pass instead of being recomputed,
-                    // and on the upper-edge graphs every layer's second pass reads what its first pass kept
-            MLIP_TRY(place(v.wst, (size_t)std::max<int64_t>(upper ? v.pairs.n_upper : v.n_edges_owned, 1) * rowb * (size_t)L,
-                           v.ws.wst));
+        if (L > 0)   // kept filter values, a slice per layer (layer 0's reverse step needs none: its slice stays empty)
+            MLIP_TRY(place(v.wst, (size_t)std::max<int64_t>(v.pairs.n_upper, 1) * rowb * (size_t)L, v.ws.wst));
         n_parts += (v.n_owned + 1023) / 1024;
     }
     const Packs pk = pack_layout(F, L);
@@ -322,8 +278,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
     MLIP_TRY(fill_zero(work_f, (int64_t)work_n, s));
 
 
-    // rows of one layer's kept filter values
-    auto wrows = [&](SlabView &v) { return (size_t)(upper ? v.pairs.n_upper : v.n_edges_owned); };
+    auto wslice = [&](SlabView &v, int l) { return v.ws.wst + (size_t)l * (size_t)v.pairs.n_upper * F; };
 
     // ---- batches for the small kernels (embedding, ghost transfers, forces, energy): up to kBatch partitions per launch
     enum { U_OWNED, U_GHOST, U_BORDER, U_LOCAL, U_KBLOCKS };
@@ -355,11 +310,11 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             a.eps = v.ws.eps;
             a.dsum = v.ws.dsum;
             a.d = v.d;
-            a.wstore = (layer >= 0 && v.ws.wst) ? v.ws.wst + (size_t)layer * wrows(v) * F : nullptr;
-            a.wslot = upper ? v.pairs.wslot : nullptr;
-            a.l_row_ptr = upper_bwd ? v.pairs.l_row_ptr : nullptr;
-            a.l_senders = upper_bwd ? v.pairs.l_senders : nullptr;
-            a.l_slot = upper_bwd ? v.pairs.l_slot : nullptr;
+            a.wstore = (layer >= 0 && v.ws.wst) ? wslice(v, layer) : nullptr;
+            a.uslot = v.pairs.uslot;
+            a.l_row_ptr = v.pairs.l_row_ptr;
+            a.l_senders = v.pairs.l_senders;
+            a.l_slot = v.pairs.l_slot;
             a.a = (layer >= 0) ? v.ws.a + (size_t)layer * (size_t)v.n_owned * F : nullptr;
             a.bond_of_edge = (bw && v.bonds.n > 0) ? v.bonds.of_edge.as<int32_t>() : nullptr;
             a.wb_bf16 = (prec == kPrecBf16);
@@ -393,6 +348,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
     prof_begin(g, MLIP_PROF_NODE);
     const bool repack = scratch != nullptr || !g->packed_w_valid || std::memcmp(&g->packed_w, w, sizeof(*w)) != 0;
     g->packed_w_valid = false;
+    const int w2_kind = prec == kPrecBf16 ? PACK_FF_BF16 : prec == kPrecF16x3 ? PACK_FF_F16X2 : PACK_FF_BF16X3;
     const int ff_kind = prec == kPrecBf16 ? PACK_FF_BF16 : prec == kPrecF16x3 ? PACK_FF_F16X2 : PACK_FF;   // the filter MLP's W2
     if (repack) {
         PackBatch pb{};
@@ -402,8 +358,8 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             float *base = wp + pk.per_layer * l;
             pb.add(w->W1 + (size_t)l * 8 * F, base + pk.A1, PACK_W1, 0, 1.0f);
             pb.add(w->W1 + (size_t)l * 8 * F, base + pk.A1s, PACK_W1, 0, kSiluScale);
-            pb.add(w->W2 + l * ff, base + pk.W2t, ff_kind, 1, kSiluScaleInv);
-            pb.add(w->W2 + l * ff, base + pk.W2n, ff_kind, 0, 1.0f);
+            pb.add(w->W2 + l * ff, base + pk.W2t, w2_kind, 1, kSiluScaleInv);
+            pb.add(w->W2 + l * ff, base + pk.W2n, w2_kind, 0, 1.0f);
             pb.add(w->Wm + l * ff, base + pk.Wmt, PACK_FF, 1, 1.0f);
             pb.add(w->Wm + l * ff, base + pk.Wmn, PACK_FF, 0, 1.0f);
             pb.add(w->Wo + l * ff, base + pk.Wot, PACK_FF, 1, 1.0f);
@@ -559,23 +515,8 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         prof_end(g);
     }
 
-    // Kept filter values on the full edge lists (16-bit product modes): both edges of a pair have the same ones bit for
-    // bit, so only the upper edge keeps them and the lower edge's reverse step reads its reverse edge's row.  That halves
-    // what the forward launches write, which is what bounds them there (1M-atom benchmark, split-fp16: forward
-    // 3.23 -> 2.71 ms, reverse 4.02 -> 4.12 ms per launch).  Needs every partition of the launch to have its kept rows
-    // within the 32-bit range of one buffer descriptor (otherwise every edge keeps its own); the same answer for the
-    // forward and the reverse launch of a layer.
-    auto w_pairs = [&](int p0, int n) {
-        if (upper || prec == kPrecF32) return 0;   // upper-edge graphs keep one row per pair by construction
-        for (int q = 0; q < n; ++q)
-            if (!fits_pairs(views[p0 + q], F)) return 0;
-        return 1;
-    };
     auto gslice = [&](SlabView &v, int l) { return v.ws.g + (size_t)l * (size_t)v.n_local * F; };
     auto aslice = [&](SlabView &v, int l) { return v.ws.a + (size_t)l * (size_t)v.n_owned * F; };
-    auto wslice = [&](SlabView &v, int l) {
-        return v.ws.wst + (size_t)l * wrows(v) * F;
-    };
 
     // ---- forward layers
     for (int l = 0; l < L; ++l) {
@@ -606,7 +547,6 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             eb.c.A1s = base + pk.A1s;
             eb.c.A2t = base + pk.W2t;
             eb.c.bp = bp;
-            eb.c.w_pairs = w_pairs(p0, eb.n);
             for (int q = 0; q < eb.n; ++q) {
                 SlabView &v = views[p0 + q];
                 EdgeArgs &ea = eb.s[q];
@@ -618,34 +558,15 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
                 ea.senders = v.senders;
                 ea.recv = v.recv;
                 ea.d = v.d;
-                ea.mirror = v.mirror;
                 ea.g = gslice(v, l);
                 ea.out = aslice(v, l);
-                ea.wstore = (l >= 1 || upper) ? wslice(v, l) : nullptr;
-                if (upper) {   // the same kernel on the partition's upper-edge graph: row sums of the upper edges, every
-                               // edge's filter values kept one after another
-                    const PairGraph &Q = v.pairs;
-                    ea.n_chunks = chunks_of(Q.n_upper, Q.span);
-                    ea.chunk_row = Q.u_chunk_row;
-                    ea.row_ptr = Q.u_row_ptr;
-                    ea.senders = Q.u_senders;
-                    ea.recv = Q.u_recv;
-                    ea.d = Q.u_d;
-                    ea.mirror = nullptr;
-                }
+                ea.uslot = v.pairs.uslot;
+                ea.wstore = l >= 1 ? wslice(v, l) : nullptr;
             }
             prof_begin(g, MLIP_PROF_EDGE_FWD);
-            MLIP_TRY(prec == kPrecBf16 ? (launch_edge<F, kPrecBf16>(g, eb, kEdgeFwd))
-                     : prec == kPrecF16x3 ? (launch_edge<F, kPrecF16x3>(g, eb, kEdgeFwd)) : (launch_edge<F, kPrecF32>(g, eb, kEdgeFwd)));
+            MLIP_TRY(prec == kPrecBf16 ? (launch_edge<F, kPrecBf16>(g, eb, false))
+                     : prec == kPrecF16x3 ? (launch_edge<F, kPrecF16x3>(g, eb, false)) : (launch_edge<F, kPrecF32>(g, eb, false)));
             prof_end(g);
-            if (upper) {   // second pass: the lower edges' terms, with the filter values the first pass kept
-                prof_begin(g, MLIP_PROF_EDGE_FWD_LOWER);
-                const SmallBatch sb = small_batch(p0, U_OWNED, l);
-                if (sb.start[sb.n] > 0)
-                    k_edge_lower<F, false><<<blocks_for(sb.start[sb.n], 4), 256, 0, s>>>(sb);
-                MLIP_HIP(hipGetLastError());
-                prof_end(g);
-            }
         }
         if (any_bonds) {   // bond term of the filters: a_i += sum_b wb_b * g_send(b)
             prof_begin(g, MLIP_PROF_BOND);
@@ -726,50 +647,35 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             eb.c.bp = bp;
             eb.c.need_gbar = need_gbar ? 1 : 0;
             eb.c.first = (l == L - 1) ? 1 : 0;
-            eb.c.w_pairs = w_pairs(p0, eb.n);
             for (int q = 0; q < eb.n; ++q) {
                 SlabView &v = views[p0 + q];
                 EdgeArgs &ea = eb.s[q];
+                const PairGraph &Q = v.pairs;
                 ea.n_rows = v.n_owned;
-                ea.n_chunks = chunks_of(v.n_edges_owned, v.span);
-                ea.chunk_row = v.chunk_row;
+                ea.n_chunks = chunks_of(Q.n_upper, Q.span);
+                ea.chunk_row = Q.u_chunk_row;
                 ea.n_nodes = v.n_local;
-                ea.row_ptr = v.row_ptr;
-                ea.senders = v.senders;
-                ea.recv = v.recv;
-                ea.d = v.d;
+                ea.row_ptr = Q.u_row_ptr;
+                ea.senders = Q.u_senders;
+                ea.recv = Q.u_recv;
+                ea.d = Q.u_d;
+                ea.mirror = Q.u_mirror;
+                ea.eid = Q.u_eid;
                 ea.g = gslice(v, l);
                 ea.abar = v.ws.abar;
                 ea.out = v.ws.gbar;
                 ea.dsum = v.ws.dsum;
-                ea.mirror = v.mirror;
                 ea.wstore = need_gbar ? wslice(v, l) : nullptr;
-                ea.n_stored = need_gbar ? v.n_edges_owned : 0;
-                if (upper_bwd) {   // on the partition's upper-edge graph
-                    const PairGraph &Q = v.pairs;
-                    ea.n_chunks = chunks_of(Q.n_upper, Q.span);
-                    ea.chunk_row = Q.u_chunk_row;
-                    ea.row_ptr = Q.u_row_ptr;
-                    ea.senders = Q.u_senders;
-                    ea.recv = Q.u_recv;
-                    ea.d = Q.u_d;
-                    ea.mirror = Q.u_mirror;
-                    ea.eid = Q.u_eid;
-                    // kept values in the order of the upper-edge graph, or (16-bit modes) at the upper edges' positions
-                    // in the full list
-                    if (upper) ea.n_stored = need_gbar ? Q.n_upper : 0;
-                }
             }
             prof_begin(g, MLIP_PROF_EDGE_BWD);
-            const int kind = upper_bwd ? kEdgeBwdUpper : kEdgeBwd;
-            MLIP_TRY(prec == kPrecBf16 ? (launch_edge<F, kPrecBf16>(g, eb, kind))
-                     : prec == kPrecF16x3 ? (launch_edge<F, kPrecF16x3>(g, eb, kind)) : (launch_edge<F, kPrecF32>(g, eb, kind)));
+            MLIP_TRY(prec == kPrecBf16 ? (launch_edge<F, kPrecBf16>(g, eb, true))
+                     : prec == kPrecF16x3 ? (launch_edge<F, kPrecF16x3>(g, eb, true)) : (launch_edge<F, kPrecF32>(g, eb, true)));
             prof_end(g);
-            if (upper_bwd && need_gbar) {   // second pass: the lower edges' terms of the rows' sums
+            if (need_gbar) {   // second pass: the lower edges' terms of the rows' sums
                 prof_begin(g, MLIP_PROF_EDGE_BWD_LOWER);
                 const SmallBatch sb = small_batch(p0, U_OWNED, l);
                 if (sb.start[sb.n] > 0)
-                    k_edge_lower<F, true><<<blocks_for(sb.start[sb.n], 4), 256, 0, s>>>(sb);
+                    k_edge_lower<F><<<blocks_for(sb.start[sb.n], 4), 256, 0, s>>>(sb);
                 MLIP_HIP(hipGetLastError());
                 prof_end(g);
             }

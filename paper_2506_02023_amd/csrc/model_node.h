@@ -200,8 +200,8 @@ struct SmallArgs {   // one partition
     const uint32_t *shiftp;
     float *h, *g, *gbar, *abar, *floc, *eps;
     float *a;                      // the layer's receiver sums (second pass of the pair-wise forward step)
-    // upper / lower split of the owned rows' edges (or nullptr: kept filter values sit at the edges' own indices)
-    const int32_t *wslot;          // [E_owned] upper edges: their index in the upper-edge graph, where their filter values are kept
+    // upper / lower split of the owned rows' edges
+    const int32_t *uslot;          // [E_owned] upper edges: their index in the upper-edge graph, where their filter values are kept
     const int64_t *l_row_ptr;      // the owned rows' lower edges: CSR, sender row, where the pair's filter values are kept
     const int32_t *l_senders, *l_slot;
     const float *dsum, *wstore, *d;
@@ -270,17 +270,14 @@ __global__ void k_zero_ghost_rows(SmallBatch B, int F)
     *reinterpret_cast<f32x4 *>(A.abar + (A.n_owned + k) * F + (idx % F4) * 4) = f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
-// gbar of the ghost rows: gbar_i = sum over the ghost's sub-row (its neighbours owned by this partition) of
-// w_e * abar_send(e).  w_e is the reverse edge's, which the forward pass kept (both edges of a pair have the
-// same length, hence the same filter value).  One wavefront per row, lane = feature, edges in row order.
-// Second pass of the edge steps that run on the upper-edge graphs: the lower edges' terms of the row sums, with the
-// filter values w read from the row of the edge's pair, which the forward edge kernel (on the upper-edge graph) filled.
-//   forward: a_i    += sum over the lower edges e = (i <- j) of row i of  w * g_j
-//   REVERSE: gbar_i += sum over the same edges of                         w * abar_j  One wavefront per row, lane = feature; the
-// lower edges of 64 edges at a time are taken kLowerChunk at a time, all their rows in flight together.
+// Second pass of the reverse edge step: the lower edges' terms of the row sums, with the filter values w read from the
+// row of the edge's pair, which the forward kernel kept: gbar_i += sum over the lower edges e = (i <- j) of row i of
+// w * abar_j.  One wavefront per row, lane = feature; the lower edges of 64 edges at a time are taken kLowerChunk at a
+// time, all their rows in flight together.  Bound by the kept rows' bytes: 1.21 ms at a million atoms for 5.9 GB of them,
+// 4.9 TB/s, what a large copy reaches on this card.
 constexpr int kLowerChunk = 16;   // lower edges whose rows are in flight together (32 measured no faster)
 
-template <int F, bool REVERSE>
+template <int F>
 __global__ void __launch_bounds__(256) k_edge_lower(SmallBatch B)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -307,16 +304,19 @@ __global__ void __launch_bounds__(256) k_edge_lower(SmallBatch B)
                 if (c + t < n) {   // wave-uniform: no load is issued for an edge that is not there
                     const int64_t j = __builtin_amdgcn_readlane(jl, c + t), m = __builtin_amdgcn_readlane(sl, c + t);
                     wv[t] = __builtin_nontemporal_load(A.wstore + m * F + f);
-                    gv[t] = (REVERSE ? A.abar : A.g)[j * F + f];
+                    gv[t] = A.abar[j * F + f];
                 }
             }
 #pragma unroll
             for (int t = 0; t < kLowerChunk; ++t) acc = fmaf(wv[t], gv[t], acc);
         }
     }
-    if (F == 64 || lane < F) (REVERSE ? A.gbar : A.a)[r * F + f] += acc;
+    if (F == 64 || lane < F) A.gbar[r * F + f] += acc;
 }
 
+// gbar of the ghost rows: gbar_i = sum over the ghost's sub-row (its neighbours owned by this partition) of
+// w_e * abar_send(e).  w_e is the reverse edge's, which the forward pass kept (both edges of a pair have the
+// same length, hence the same filter value).  One wavefront per row, lane = feature, edges in row order.
 template <int F>
 __global__ void __launch_bounds__(256) k_ghost_gbar(SmallBatch B)
 {
@@ -334,7 +334,7 @@ __global__ void __launch_bounds__(256) k_ghost_gbar(SmallBatch B)
         const int64_t el = min(eb + (lane & 15), e1 - 1);
         const int32_t jl = A.senders[el], ml = A.mirror[el];
         const int32_t bl = A.bond_of_edge ? A.bond_of_edge[ml] : -1;   // three-body variant: the reverse edge's bond
-        const int32_t sl = A.wslot ? A.wslot[ml] : ml;                 // where the reverse edge's filter values are kept
+        const int32_t sl = A.uslot[ml];   // where the reverse edge (an upper one: its sender is a ghost) keeps its filter values
         float wv[16], av[16];
 #pragma unroll
         for (int k = 0; k < 16; ++k) {

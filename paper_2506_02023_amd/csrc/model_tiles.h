@@ -139,7 +139,7 @@ __device__ inline void radial_basis(float d, const BasisParams &bp, float (&b)[8
 //
 // Operand packs a call needs are made by one launch: one job per pack (blockIdx.y), one thread per element.  Every
 // pack in a launch of its own took 2 us of device time and a launch each, 20 to 26 per model.
-enum { PACK_W1 = 0, PACK_FF = 1, PACK_FF_BF16 = 2, PACK_FF_F16X2 = 3 };
+enum { PACK_W1 = 0, PACK_FF = 1, PACK_FF_BF16 = 2, PACK_FF_F16X2 = 3, PACK_FF_BF16X3 = 4 };
 struct PackJob {
     const float *W;
     float *out;
@@ -182,6 +182,14 @@ __global__ void k_pack(PackBatch B)
         J.out[idx] = v;
     } else if (J.kind == PACK_FF_BF16) {
         reinterpret_cast<__bf16 *>(J.out)[idx] = (__bf16)v;
+    } else if (J.kind == PACK_FF_BF16X3) {
+        const __bf16 h = (__bf16)v;
+        const float r = v - (float)h;
+        const __bf16 m = (__bf16)r;
+        __bf16 *o3 = reinterpret_cast<__bf16 *>(J.out) + idx;
+        o3[0] = h;
+        o3[F * F] = m;
+        o3[2 * F * F] = (__bf16)(r - (float)m);
     } else {
         const _Float16 h = (_Float16)v;
         reinterpret_cast<_Float16 *>(J.out)[idx] = h;
@@ -216,12 +224,31 @@ __device__ inline bf16x8 to_bf16x8(const float (&v)[8])
     return o;
 }
 
+// v = h + m + l with three bf16 parts, exactly unless l underflows: 8 significant bits each, rounded to nearest, what
+// is left after each part is exact in fp32
+__device__ inline void split_bf16x3(const float (&v)[8], bf16x8 &h, bf16x8 &m, bf16x8 &l)
+{
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) {
+        const f32x2 p = {v[i], v[i + 1]};
+        const bf16x2 ph = __builtin_convertvector(p, bf16x2);
+        const f32x2 r = p - __builtin_convertvector(ph, f32x2);
+        const bf16x2 pm = __builtin_convertvector(r, bf16x2);
+        const f32x2 r2 = r - __builtin_convertvector(pm, f32x2);
+        const bf16x2 pl = __builtin_convertvector(r2, bf16x2);
+        h[i] = ph[0]; h[i + 1] = ph[1];
+        m[i] = pm[0]; m[i + 1] = pm[1];
+        l[i] = pl[0]; l[i + 1] = pl[1];
+    }
+}
+
 template <int F> struct Dims {
     static constexpr int NB = F / 32;
     static constexpr int FS = F + 4;      // LDS row stride of an item-major tile
     static constexpr int TILE = 32 * FS;  // floats per 32-item tile
     static constexpr int PACK1 = NB * 4 * 64;
     static constexpr int PACKF = F * F;
+    static constexpr int PACK3 = F * F * 3 / 2;   // floats of a three-part bf16 pack
 };
 
 // out[bo] = sum_k M[.][k] in[k][.], `in` held in accumulator layout (chained product)
@@ -445,6 +472,73 @@ __device__ inline void gemm_row_f16x3(const _Float16 *__restrict__ Ap, const flo
                 out[bo] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh, out[bo], 0, 0, 0);
             }
         }
+}
+
+// fp32 products as three-part bf16 operands: x y = (h + m + l)(h' + m' + l'), of which the six terms down to 2^-16 of the
+// product are taken, smallest first (l m', m l' and l l' are below 2^-25 of it, half an fp32 rounding).  24 MFMAs of a
+// chain round at full size for 64 terms, where the fp32 instruction makes 32.  The A operands of the next step are
+// requested before the MFMAs of this one.
+template <int F, bool ACCUMULATE, class Values>
+__device__ inline void gemm_bf16x3(const __bf16 *__restrict__ Ap, Values values, f32x16 (&out)[Dims<F>::NB], int lane)
+{
+    constexpr int NB = Dims<F>::NB, STEPS = NB * 2 * NB;
+    const bf16x8 *A = reinterpret_cast<const bf16x8 *>(Ap) + lane;
+    if (!ACCUMULATE)
+#pragma unroll
+        for (int bo = 0; bo < NB; ++bo)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) out[bo][r] = 0.f;
+    auto at = [](int st) { return ((st % NB) * NB * 2 + st / NB) * 64; };   // step st: k block st / NB, output block st % NB
+    bf16x8 a[3], bh, bm, bl;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) a[q] = A[at(0) + q * (F * F / 8)];
+#pragma unroll
+    for (int st = 0; st < STEPS; ++st) {
+        const int bo = st % NB;
+        bf16x8 an[3] = {a[0], a[1], a[2]};
+        if (st + 1 < STEPS)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) an[q] = A[at(st + 1) + q * (F * F / 8)];
+        if (bo == 0) {
+            float v[8];
+            values(st / NB, v);
+            split_bf16x3(v, bh, bm, bl);
+        }
+        out[bo] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2], bh, out[bo], 0, 0, 0);
+        out[bo] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], bl, out[bo], 0, 0, 0);
+        out[bo] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], bm, out[bo], 0, 0, 0);
+        out[bo] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], bh, out[bo], 0, 0, 0);
+        out[bo] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], bm, out[bo], 0, 0, 0);
+        out[bo] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], bh, out[bo], 0, 0, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) a[q] = an[q];
+    }
+}
+
+// the B operand in accumulator layout (chained product) ...
+template <int F, bool ACCUMULATE = false>
+__device__ inline void gemm_rl_bf16x3(const __bf16 *__restrict__ Ap, const f32x16 (&in)[Dims<F>::NB],
+                                      f32x16 (&out)[Dims<F>::NB], int lane)
+{
+    gemm_bf16x3<F, ACCUMULATE>(Ap, [&](int s, float (&v)[8]) {
+#pragma unroll
+        for (int t = 0; t < 8; ++t) v[t] = in[s / 2][8 * (s % 2) + t];
+    }, out, lane);
+}
+
+// ... or from an item-major LDS row of this lane's item
+template <int F, bool ACCUMULATE = false>
+__device__ inline void gemm_row_bf16x3(const __bf16 *__restrict__ Ap, const float *row, f32x16 (&out)[Dims<F>::NB], int lane)
+{
+    const int h = lane >> 5;
+    gemm_bf16x3<F, ACCUMULATE>(Ap, [&](int s, float (&v)[8]) {
+        const f32x4 lo4 = *reinterpret_cast<const f32x4 *>(row + 16 * s + 4 * h);
+        const f32x4 hi4 = *reinterpret_cast<const f32x4 *>(row + 16 * s + 8 + 4 * h);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) { v[t] = lo4[t]; v[4 + t] = hi4[t]; }
+    }, out, lane);
 }
 
 template <int F> struct RegPack1 {

@@ -91,3 +91,20 @@ def test_search_over_cells(case):
         m = g.mirror()
         recv = np.repeat(np.arange(len(pos)), np.diff(row_ptr))
         assert np.array_equal(recv[m], senders) and np.array_equal(shifts[m], -shifts) and np.array_equal(m[m], np.arange(len(m)))
+
+
+@pytest.mark.parametrize("F", [32, 64])
+def test_fp32_products_keep_the_range_of_fp32(F):
+    """Activations of the filter MLP far beyond the range of 16-bit floats (their three-part bf16 operands have the
+    exponent range of fp32), brought back by the second map."""
+    import paper_2506_02023_amd as M
+    pos, cell = _system("ball")
+    species = (np.arange(len(pos)) % 4).astype(np.int32)
+    weights = wl.rmp_weights(4, F, 2, 78)
+    weights["W1"] = weights["W1"] * np.float32(2.0 ** 20)
+    weights["W2"] = weights["W2"] * np.float32(2.0 ** -20)
+    ref_g = og.build_graph(pos, cell, 5.0)
+    ref = om.energy_forces(pos, cell, species, weights, ref_g, 5.0, 8, 6)
+    e, f, eps = gpu_energy_forces(gpu_graph(pos, cell, species, 5.0), weights, 6, M.MODE_WHOLE, 0)
+    assert abs(e - ref["energy"]) <= 1e-5 * np.abs(ref["atom_energy"]).sum()
+    assert np.abs(f - ref["forces"]).max() <= 1e-4 * np.abs(ref["forces"]).max()
