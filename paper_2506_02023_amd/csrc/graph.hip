@@ -98,45 +98,100 @@ template <class T> __device__ inline T block_exclusive_scan(T (&v)[kScanItems], 
     return total;
 }
 
-template <class Tin, class Tout>
-__global__ void k_tile_sums(const Tin *in, Tout *sums, int64_t n)
+// what a scan reads: an array, the sum of two, or the bit counts of one
+template <class T> struct ScanArray {
+    const T *p;
+    __device__ T operator()(int64_t i) const { return p[i]; }
+};
+struct ScanSum {
+    const int32_t *p, *q;
+    __device__ int32_t operator()(int64_t i) const { return p[i] + q[i]; }
+};
+struct ScanBits {
+    const unsigned long long *p;
+    __device__ int32_t operator()(int64_t i) const { return __popcll(p[i]); }
+};
+
+// Where the last block of a scan leaves the total and the flag words of the build for the host (pinned host memory: the
+// host reads them after a synchronisation, no copy is enqueued): host[0] = total, host[1..] = err[0..2].
+struct Publish {
+    int64_t *host;
+    const int32_t *err;
+};
+
+// sum over the block's threads, returned to all of them
+template <class T> __device__ inline T block_sum(T v, T *lds /*[4]*/)
 {
-    __shared__ Tout lds[kScanThreads / 64];
-    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-    Tout v[kScanItems];
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k) v[k] = (base + k < n) ? (Tout)in[base + k] : (Tout)0;
-    Tout total = block_exclusive_scan(v, lds);
-    if (threadIdx.x == 0) sums[blockIdx.x] = total;
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
+    __syncthreads();
+    T total = 0;
+#pragma unroll
+    for (int w = 0; w < kScanThreads / 64; ++w) total += lds[w];
+    __syncthreads();
+    return total;
 }
 
-// out[i] = offsets[tile] + exclusive prefix inside the tile; the last tile also writes out[n]
-template <class Tin, class Tout>
-__global__ void k_tile_scan(const Tin *in, const Tout *offsets, Tout *out, int64_t n)
+template <class In, class Tout>
+__global__ void k_tile_sums(In in, Tout *sums, int64_t n)
 {
     __shared__ Tout lds[kScanThreads / 64];
     const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
+    Tout sum = 0;
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) sum += (base + k < n) ? (Tout)in(base + k) : (Tout)0;
+    sum = block_sum(sum, lds);
+    if (threadIdx.x == 0) sums[blockIdx.x] = sum;
+}
+
+// out[i] = what lies before the tile + exclusive prefix inside the tile; the last tile also writes out[n].  What lies
+// before the tile is summed by the block itself, over the input (SCAN_DIRECT) or over the tiles' sums (SCAN_SUMS), or
+// read (SCAN_OFFSETS): one, two or more launches, and a launch costs more than re-reading a few thousand values.
+enum { SCAN_DIRECT = 0, SCAN_SUMS = 1, SCAN_OFFSETS = 2 };
+constexpr int64_t kDirectTiles = 16, kSumsTiles = 2048;
+template <class In, class Tout, int MODE>
+__global__ void k_tile_scan(In in, const Tout *pre, Tout *out, int64_t n, Publish pub)
+{
+    __shared__ Tout lds[kScanThreads / 64];
+    const int64_t tile0 = (int64_t)blockIdx.x * kScanTile;
+    const int64_t base = tile0 + (int64_t)threadIdx.x * kScanItems;
     Tout v[kScanItems];
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k) v[k] = (base + k < n) ? (Tout)in[base + k] : (Tout)0;
-    Tout total = block_exclusive_scan(v, lds);
-    const Tout off = offsets ? offsets[blockIdx.x] : (Tout)0;
+    for (int k = 0; k < kScanItems; ++k) v[k] = (base + k < n) ? (Tout)in(base + k) : (Tout)0;
+    Tout off = 0;
+    if (MODE == SCAN_DIRECT) {
+        for (int64_t i = threadIdx.x; i < tile0; i += kScanThreads) off += (Tout)in(i);
+        off = block_sum(off, lds);
+    } else if (MODE == SCAN_SUMS) {
+        for (int64_t i = threadIdx.x; i < blockIdx.x; i += kScanThreads) off += pre[i];
+        off = block_sum(off, lds);
+    } else {
+        off = pre[blockIdx.x];
+    }
+    const Tout total = block_exclusive_scan(v, lds);
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k)
         if (base + k < n) out[base + k] = off + v[k];
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = off + total;
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+        out[n] = off + total;
+        if (pub.host) {
+            pub.host[0] = (int64_t)(off + total);
+            for (int k = 0; k < 3; ++k) pub.host[1 + k] = pub.err[k];
+        }
+    }
 }
 
-template <class Tin, class Tout>
-int scan_impl(const Tin *in, Tout *out, int64_t n, char *tmp, size_t tmp_bytes, hipStream_t s)
+template <class In, class Tout>
+int scan_impl(In in, Tout *out, int64_t n, char *tmp, size_t tmp_bytes, hipStream_t s, Publish pub)
 {
     if (n <= 0) {
         if (n == 0) MLIP_HIP(hipMemsetAsync(out, 0, sizeof(Tout), s));
         return MLIP_OK;
     }
     const int64_t tiles = (n + kScanTile - 1) / kScanTile;
-    if (tiles == 1) {
-        k_tile_scan<Tin, Tout><<<1, kScanThreads, 0, s>>>(in, nullptr, out, n);
+    if (tiles <= kDirectTiles) {
+        k_tile_scan<In, Tout, SCAN_DIRECT><<<(unsigned)tiles, kScanThreads, 0, s>>>(in, nullptr, out, n, pub);
         MLIP_HIP(hipGetLastError());
         return MLIP_OK;
     }
@@ -145,10 +200,15 @@ int scan_impl(const Tin *in, Tout *out, int64_t n, char *tmp, size_t tmp_bytes, 
     if (tmp_bytes < need) { set_error("scan scratch too small"); return MLIP_EINVAL; }
     Tout *sums = reinterpret_cast<Tout *>(tmp);
     Tout *offs = sums + tiles;
-    k_tile_sums<Tin, Tout><<<(unsigned)tiles, kScanThreads, 0, s>>>(in, sums, n);
+    k_tile_sums<In, Tout><<<(unsigned)tiles, kScanThreads, 0, s>>>(in, sums, n);
     MLIP_HIP(hipGetLastError());
-    MLIP_TRY((scan_impl<Tout, Tout>(sums, offs, tiles, tmp + need, tmp_bytes - need, s)));
-    k_tile_scan<Tin, Tout><<<(unsigned)tiles, kScanThreads, 0, s>>>(in, offs, out, n);
+    if (tiles <= kSumsTiles) {
+        k_tile_scan<In, Tout, SCAN_SUMS><<<(unsigned)tiles, kScanThreads, 0, s>>>(in, sums, out, n, pub);
+        MLIP_HIP(hipGetLastError());
+        return MLIP_OK;
+    }
+    MLIP_TRY((scan_impl<ScanArray<Tout>, Tout>(ScanArray<Tout>{sums}, offs, tiles, tmp + need, tmp_bytes - need, s, Publish{})));
+    k_tile_scan<In, Tout, SCAN_OFFSETS><<<(unsigned)tiles, kScanThreads, 0, s>>>(in, offs, out, n, pub);
     MLIP_HIP(hipGetLastError());
     return MLIP_OK;
 }
@@ -164,19 +224,15 @@ size_t scan_scratch_bytes(int64_t n)
     return total + 256;
 }
 
+// device-wide exclusive scans (n + 1 outputs, out[n] = total); tmp is grown as needed
+template <class In, class Tout> int scan(In in, Tout *out, int64_t n, DevBuf &tmp, hipStream_t s, Publish pub = Publish{})
+{
+    MLIP_TRY(tmp.ensure(scan_scratch_bytes(n)));
+    return scan_impl<In, Tout>(in, out, n, tmp.as<char>(), tmp.cap, s, pub);
+}
+inline ScanArray<int32_t> scan_array(const int32_t *p) { return ScanArray<int32_t>{p}; }
+
 }  // namespace
-
-int scan_i32_to_i64(const int32_t *in, int64_t *out, int64_t n, DevBuf &tmp, hipStream_t s)
-{
-    MLIP_TRY(tmp.ensure(scan_scratch_bytes(n)));
-    return scan_impl<int32_t, int64_t>(in, out, n, tmp.as<char>(), tmp.cap, s);
-}
-
-int scan_i32_to_i32(const int32_t *in, int32_t *out, int64_t n, DevBuf &tmp, hipStream_t s)
-{
-    MLIP_TRY(tmp.ensure(scan_scratch_bytes(n)));
-    return scan_impl<int32_t, int32_t>(in, out, n, tmp.as<char>(), tmp.cap, s);
-}
 
 namespace {
 
@@ -188,9 +244,10 @@ __device__ inline double frac_k(const double *r, const double *n, double V)
 }
 
 // err[0] = flag bits, err[1] = max species seen, err[2] = min species seen
-__global__ void k_bin(int64_t N, const double *__restrict__ pos, const int32_t *__restrict__ species,
-                      CellParams cp, int32_t *cell_of, uint32_t *wrapp, int32_t *slab_of, int32_t *cell_cnt,
-                      int32_t *err)
+// (the handle's own copies of the positions and the species are made on the way, unless pos_copy is null)
+__global__ void k_bin(int64_t N, const double *__restrict__ pos, const int32_t *__restrict__ species, double *__restrict__ pos_copy,
+                      int32_t *__restrict__ species_copy, CellParams cp, int32_t *cell_of, uint32_t *wrapp, int32_t *slab_of,
+                      int32_t *cell_cnt, int32_t *in_cell, int32_t *err)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     {   // species range, one atomic pair per wavefront
@@ -209,6 +266,12 @@ __global__ void k_bin(int64_t N, const double *__restrict__ pos, const int32_t *
     }
     if (i >= N) return;
     const double r[3] = {pos[3 * i], pos[3 * i + 1], pos[3 * i + 2]};
+    if (pos_copy) {
+        pos_copy[3 * i] = r[0];
+        pos_copy[3 * i + 1] = r[1];
+        pos_copy[3 * i + 2] = r[2];
+        species_copy[i] = species[i];
+    }
     int b[3], w[3];
     int slab = 0;
     bool bad = false;
@@ -233,18 +296,18 @@ __global__ void k_bin(int64_t N, const double *__restrict__ pos, const int32_t *
     cell_of[i] = c;
     wrapp[i] = pack3(w[0], w[1], w[2]);
     slab_of[i] = slab;
-    atomicAdd(&cell_cnt[c], 1);
+    in_cell[i] = atomicAdd(&cell_cnt[c], 1);   // the atom's place among its cell's
 }
 
 __global__ void k_fill_cells(int64_t N, const double *__restrict__ pos, const int32_t *__restrict__ cell_of,
                              const uint32_t *__restrict__ wrapp, const int32_t *__restrict__ cell_start,
-                             int32_t *cell_fill, int32_t *sid, double *sx, double *sy, double *sz,
+                             const int32_t *__restrict__ in_cell, int32_t *sid, double *sx, double *sy, double *sz,
                              uint32_t *swrap)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= N) return;
     const int32_t c = cell_of[i];
-    const int32_t slot = cell_start[c] + atomicAdd(&cell_fill[c], 1);
+    const int32_t slot = cell_start[c] + in_cell[i];
     sid[slot] = (int32_t)i;
     sx[slot] = pos[3 * i];
     sy[slot] = pos[3 * i + 1];
@@ -552,12 +615,6 @@ __global__ void k_pair_partners(int64_t N, const int32_t *__restrict__ n_own, co
     }
 }
 
-__global__ void k_pair_counts(int64_t N, const int32_t *__restrict__ n_own, const int32_t *__restrict__ n_par, int32_t *counts)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < N) counts[i] = n_own[i] + n_par[i];
-}
-
 // k_sort_rows for the pair-wise search: the row's keys come from the atom's two staging rows; the rank of every
 // staging slot is kept for the reverse-edge index
 __global__ void __launch_bounds__(64)
@@ -731,6 +788,7 @@ __device__ inline int node_class(int s, unsigned long long nb, int q)
 // counts (first pass) or write positions (second pass) in its own LDS table; between the passes one flat scan over
 // cnt[bin][range] turns the counts into positions.
 constexpr int kRange = 512;
+inline int64_t class_entries(int64_t N, int32_t P) { return (int64_t)(P * (P + 2) + P) * ((N + kRange - 1) / kRange); }
 
 // What the local-CSR fill needs to know about a sender, in one 16-byte record per atom: its owner partition, its
 // row there, and the distance from a position in its global row to the same position in its owner's local row.
@@ -815,12 +873,6 @@ k_classes(int64_t N, int P, int64_t nranges, const int32_t *__restrict__ slab_of
     }
 }
 
-__global__ void k_popcount(int64_t N, const unsigned long long *__restrict__ needed_by, int32_t *out)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < N) out[i] = __popcll(needed_by[i]);
-}
-
 // span starts of every partition: out[q * (P + 3) + k] = start of span k of partition q in the concatenated node
 // array (k = P + 2: its end); out[P * (P + 3)] = number of ghost entries
 __global__ void k_gather_markers(const int32_t *__restrict__ off, int P, int64_t nranges, const int32_t *__restrict__ gbase,
@@ -857,12 +909,13 @@ __device__ inline int part_find(const int64_t *start, int P, int64_t x)
 // Length of each local row.  Owned rows keep their whole global row (one thread per owned atom, which knows its
 // partition and row from its owner record); ghost rows keep only the senders owned by the partition and also record
 // their owner and their row inside the owner (one wavefront per ghost row).  Partition q's lengths start at
-// rowlen[row0[q] + q] (one closing entry per partition, zero-filled beforehand, so that one scan yields every
+// rowlen[row0[q] + q] (one closing entry of zero per partition, so that one scan yields every
 // partition's n_local + 1 offsets).
 __global__ void k_owned_rowlen(int64_t N, PartTab T, const OwnRec *__restrict__ own_rec, const int64_t *__restrict__ row_ptr,
                                int32_t *rowlen)
 {
     const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (u < T.P) rowlen[T.row0[u + 1] + u] = 0;   // (N >= 1 blocks of 256 threads cover the 64 partitions)
     if (u >= N) return;
     const OwnRec rec = own_rec[u];
     rowlen[T.row0[rec.slab] + rec.slab + rec.local] = (int32_t)(row_ptr[u + 1] - row_ptr[u]);
@@ -897,7 +950,8 @@ k_ghost_rowlen(PartTab T, const int32_t *__restrict__ nodes, const int64_t *__re
 // row_ptr of every partition, starting at 0 (row_abs holds the scan over all partitions' lengths), and per
 // partition the edges of its owned rows and of all its rows
 __global__ void k_local_rowptr(PartTab T, const int64_t *__restrict__ row_abs, const int32_t *__restrict__ nodes,
-                               const int64_t *__restrict__ grow_ptr, int64_t *row_ptr, OwnRec *own_rec, int64_t *sizes)
+                               const int64_t *__restrict__ grow_ptr, int64_t *row_ptr, OwnRec *own_rec, int64_t *sizes,
+                               const int32_t *__restrict__ err)
 {
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t total = T.row0[T.P] + T.P;
@@ -915,6 +969,7 @@ __global__ void k_local_rowptr(PartTab T, const int64_t *__restrict__ row_abs, c
     if (idx == first) {
         sizes[2 * q] = row_abs[first + T.n_owned[q]] - base;
         sizes[2 * q + 1] = row_abs[T.row0[q + 1] + q] - base;
+        if (q == 0) sizes[2 * T.P] = err[0];
     }
 }
 
@@ -1254,7 +1309,7 @@ int build_bonds_impl(mlip_graph *g, SlabView &v, double r_bond, int p_envelope)
                                                        v.shiftp, B.flag.as<int32_t>());
         MLIP_HIP(hipGetLastError());
     }
-    MLIP_TRY(scan_i32_to_i32(B.flag.as<int32_t>(), B.scan.as<int32_t>(), E, g->scan_tmp, s));
+    MLIP_TRY(scan(scan_array(B.flag.as<int32_t>()), B.scan.as<int32_t>(), E, g->scan_tmp, s));
     int32_t *hp = static_cast<int32_t *>(g->pinned);
     MLIP_HIP(hipMemcpyAsync(hp, B.scan.as<int32_t>() + E, 4, hipMemcpyDeviceToHost, s));
     MLIP_HIP(hipStreamSynchronize(s));
@@ -1541,10 +1596,10 @@ int build_pairs_impl(mlip_graph *g, SlabView *views, int P, Carver *scratch)
             set_error("more than 2^31 edges in %d partitions", b.n);
             return MLIP_EINVAL;
         }
-        int32_t *cnt = nullptr, *scan = nullptr;
+        int32_t *cnt = nullptr, *scan_out = nullptr;
         uint16_t *rank = nullptr;
         MLIP_TRY(place(g->pair_cnt, (size_t)(rows + 1) * 4, cnt));
-        MLIP_TRY(place(g->pair_scan, (size_t)(rows + 1) * 4, scan));
+        MLIP_TRY(place(g->pair_scan, (size_t)(rows + 1) * 4, scan_out));
         MLIP_TRY(place(g->pair_rank, (size_t)(edges + 1) * 2, rank));
         if (scratch && scratch->failed()) return MLIP_OK;   // nothing may be launched on a failed carve; the caller reports it
         int64_t groups = 0;
@@ -1553,10 +1608,10 @@ int build_pairs_impl(mlip_graph *g, SlabView *views, int P, Carver *scratch)
             k_pair_count<<<grid8((groups + 3) / 4), 256, 0, s>>>(b, cnt, rank);
             MLIP_HIP(hipGetLastError());
         }
-        MLIP_TRY(scan_i32_to_i32(cnt, scan, rows, g->scan_tmp, s));
+        MLIP_TRY(scan(scan_array(cnt), scan_out, rows, g->scan_tmp, s));
         const int64_t edge_blocks = (edges + 255) / 256, row_blocks = (rows + b.n + 255) / 256;
         const int64_t chunk_blocks = (b.chunk_start[b.n] + b.n + 255) / 256;
-        k_pair_fill<<<grid8(edge_blocks + row_blocks + chunk_blocks), 256, 0, s>>>(b, scan, rank, edge_blocks, row_blocks);
+        k_pair_fill<<<grid8(edge_blocks + row_blocks + chunk_blocks), 256, 0, s>>>(b, scan_out, rank, edge_blocks, row_blocks);
         MLIP_HIP(hipGetLastError());
     }
     for (int p = 0; p < P; ++p) views[p].pairs.valid = (scratch == nullptr);   // arrays in a borrowed block do not outlive the call
@@ -1569,20 +1624,16 @@ struct CsrOut {   // where a neighbour search puts its receiver-sorted CSR (mirr
     DevBuf *row_ptr, *senders, *recv, *shiftp, *d, *mirror;
 };
 
-// reads the edge count and the flag words after the first pass of either route and turns the flags into errors
-int read_counts_and_flags(mlip_graph *g, const int64_t *row_ptr_end, int32_t *err, int64_t *E, int32_t *flags_out)
+// waits for the edge count and the flag words, which the scan of the row lengths published, and turns the flags into errors
+int read_counts_and_flags(mlip_graph *g, int64_t *E, int32_t *flags_out)
 {
-    hipStream_t s = g->stream;
-    int64_t *hp = static_cast<int64_t *>(g->pinned);
-    MLIP_HIP(hipMemcpyAsync(hp, row_ptr_end, 8, hipMemcpyDeviceToHost, s));
-    MLIP_HIP(hipMemcpyAsync(hp + 1, err, 12, hipMemcpyDeviceToHost, s));
-    MLIP_HIP(hipStreamSynchronize(s));
+    const int64_t *hp = static_cast<const int64_t *>(g->pinned);
+    MLIP_HIP(hipStreamSynchronize(g->stream));
     *E = hp[0];
-    const int32_t *herr = reinterpret_cast<int32_t *>(hp + 1);
-    const int32_t flags = herr[0];
+    const int32_t flags = (int32_t)hp[1];
     *flags_out = flags;
-    g->species_max = herr[1];
-    g->species_min = herr[2];
+    g->species_max = (int32_t)hp[2];
+    g->species_min = (int32_t)hp[3];
     if (flags & ERR_RANGE) {
         set_error("an atom lies more than 200 cells away from the origin cell (or has a non-finite coordinate)");
         return MLIP_ECELL;
@@ -1598,16 +1649,47 @@ int read_counts_and_flags(mlip_graph *g, const int64_t *row_ptr_end, int32_t *er
     return MLIP_OK;
 }
 
+// What a build needs at zero, in one block cleared by one memset: the flag words, and behind them the partition's bits and
+// counters, then the search's (n_par: edges handed to an atom by its partners).
+struct ZeroBlock {
+    int32_t *err;
+    unsigned long long *needed_by;
+    int32_t *class_cnt, *cell_cnt, *n_par;
+    size_t part_bytes, bytes;   // up to the end of the partition's share; all
+};
+int zero_block(mlip_graph *g, int64_t N, int32_t P, int64_t ncell, ZeroBlock &z)
+{
+    const int64_t nent = P > 1 ? class_entries(N, P) : 0;
+    const size_t bits = P > 1 ? (size_t)N * 8 : 0;
+    auto pad = [](size_t b) { return (b + 63) & ~(size_t)63; };
+    const size_t o_bits = 64, o_class = pad(o_bits + bits), o_cell = pad(o_class + (size_t)nent * 4),
+                 o_par = pad(o_cell + (size_t)(ncell + 1) * 4);
+    z.part_bytes = o_cell;
+    z.bytes = o_par + (size_t)N * 4;
+    MLIP_TRY(g->small.ensure(z.bytes));
+    char *p = g->small.as<char>();
+    z.err = reinterpret_cast<int32_t *>(p);
+    z.needed_by = reinterpret_cast<unsigned long long *>(p + o_bits);
+    z.class_cnt = reinterpret_cast<int32_t *>(p + o_class);
+    z.cell_cnt = reinterpret_cast<int32_t *>(p + o_cell);
+    z.n_par = reinterpret_cast<int32_t *>(p + o_par);
+    return MLIP_OK;
+}
+
 // Cell-list neighbour search for the cutoff in cp.rc2 over the positions and species held by the handle; writes the
-// canonical receiver-sorted CSR to `out`, slab_of and the species range; synchronises the stream once.
-int search_csr(mlip_graph *g, const CellParams &cp, int64_t N, CsrOut out, int64_t *E_out)
+// canonical receiver-sorted CSR to `out`, slab_of and the species range; synchronises the stream once.  positions and
+// species: the caller's arrays, copied into the handle on the way (null: the handle holds them already).  *unchecked is set
+// if a kernel behind that synchronisation may still have raised a flag.
+int search_csr(mlip_graph *g, const CellParams &cp, int64_t N, int32_t P, const double *positions, const int32_t *species,
+               CsrOut out, int64_t *E_out, bool *unchecked)
 {
     hipStream_t s = g->stream;
     const int64_t ncell = (int64_t)cp.nb[0] * cp.nb[1] * cp.nb[2];
+    ZeroBlock z;
+    MLIP_TRY(zero_block(g, N, P, ncell, z));
     MLIP_TRY(g->cell_of.ensure((size_t)N * 4));
     MLIP_TRY(g->wrapp.ensure((size_t)N * 4));
-    MLIP_TRY(g->cell_cnt.ensure((size_t)(ncell + 1) * 4));
-    MLIP_TRY(g->cell_fill.ensure((size_t)(ncell + 1) * 4));
+    MLIP_TRY(g->in_cell.ensure((size_t)N * 4));
     MLIP_TRY(g->cell_start.ensure((size_t)(ncell + 2) * 4));
     MLIP_TRY(g->sid.ensure((size_t)N * 4));
     MLIP_TRY(g->swrap.ensure((size_t)N * 4));
@@ -1615,18 +1697,19 @@ int search_csr(mlip_graph *g, const CellParams &cp, int64_t N, CsrOut out, int64
     MLIP_TRY(g->sy.ensure((size_t)N * 8));
     MLIP_TRY(g->sz.ensure((size_t)N * 8));
     MLIP_TRY(out.row_ptr->ensure((size_t)(N + 1) * 8));
-    int32_t *err = g->small.as<int32_t>();
-    MLIP_HIP(hipMemsetAsync(g->small.p, 0, 4096, s));
-    MLIP_HIP(hipMemsetAsync(g->cell_cnt.p, 0, (size_t)(ncell + 1) * 4, s));
-    MLIP_HIP(hipMemsetAsync(g->cell_fill.p, 0, (size_t)(ncell + 1) * 4, s));
+    int32_t *err = z.err;
+    const Publish publish{static_cast<int64_t *>(g->pinned), err};
+    MLIP_HIP(hipMemsetAsync(g->small.p, 0, z.bytes, s));
     const double *pos = g->pos.as<double>();
-    k_bin<<<blocks_for(N, 256), 256, 0, s>>>(N, pos, g->species.as<int32_t>(), cp, g->cell_of.as<int32_t>(),
-                                             g->wrapp.as<uint32_t>(), g->slab_of.as<int32_t>(),
-                                             g->cell_cnt.as<int32_t>(), err);
+    k_bin<<<blocks_for(N, 256), 256, 0, s>>>(N, positions ? positions : pos, species ? species : g->species.as<int32_t>(),
+                                             positions ? g->pos.as<double>() : nullptr,
+                                             positions ? g->species.as<int32_t>() : nullptr, cp, g->cell_of.as<int32_t>(),
+                                             g->wrapp.as<uint32_t>(), g->slab_of.as<int32_t>(), z.cell_cnt,
+                                             g->in_cell.as<int32_t>(), err);
     MLIP_HIP(hipGetLastError());
-    MLIP_TRY(scan_i32_to_i32(g->cell_cnt.as<int32_t>(), g->cell_start.as<int32_t>(), ncell, g->scan_tmp, s));
+    MLIP_TRY(scan(scan_array(z.cell_cnt), g->cell_start.as<int32_t>(), ncell, g->scan_tmp, s));
     k_fill_cells<<<blocks_for(N, 256), 256, 0, s>>>(N, pos, g->cell_of.as<int32_t>(), g->wrapp.as<uint32_t>(),
-                                                    g->cell_start.as<int32_t>(), g->cell_fill.as<int32_t>(),
+                                                    g->cell_start.as<int32_t>(), g->in_cell.as<int32_t>(),
                                                     g->sid.as<int32_t>(), g->sx.as<double>(), g->sy.as<double>(),
                                                     g->sz.as<double>(), g->swrap.as<uint32_t>());
     MLIP_HIP(hipGetLastError());
@@ -1638,12 +1721,11 @@ int search_csr(mlip_graph *g, const CellParams &cp, int64_t N, CsrOut out, int64
     bool done = false;
     if ((size_t)N * (kOwn + kPar) * 10 <= ((size_t)8 << 30)) {
         MLIP_TRY(g->stage.ensure((size_t)N * (kOwn + kPar) * 8));
-        MLIP_TRY(g->pair_aux.ensure((size_t)N * (8 + 2 * (kOwn + kPar))));
+        MLIP_TRY(g->pair_aux.ensure((size_t)N * (4 + 2 * (kOwn + kPar))));
         uint64_t *stage_own = g->stage.as<uint64_t>(), *stage_par = stage_own + (size_t)N * kOwn;
-        int32_t *n_own = g->pair_aux.as<int32_t>(), *n_par = n_own + N;
-        uint8_t *pslot_own = reinterpret_cast<uint8_t *>(n_par + N), *pslot_par = pslot_own + (size_t)N * kOwn;
+        int32_t *n_own = g->pair_aux.as<int32_t>(), *n_par = z.n_par;
+        uint8_t *pslot_own = reinterpret_cast<uint8_t *>(n_own + N), *pslot_par = pslot_own + (size_t)N * kOwn;
         uint8_t *rank_own = pslot_par + (size_t)N * kPar, *rank_par = rank_own + (size_t)N * kOwn;
-        MLIP_HIP(hipMemsetAsync(n_par, 0, (size_t)N * 4, s));
         // few cells: four wavefronts share each, so that the chip has something to do and a crowded cell is not one chain
         if (ncell < kSharedCells)
             k_neighbours_pairs<4><<<grid8(ncell), 256, 0, s>>>(
@@ -1656,10 +1738,8 @@ int search_csr(mlip_graph *g, const CellParams &cp, int64_t N, CsrOut out, int64
         MLIP_HIP(hipGetLastError());
         k_pair_partners<<<blocks_for(N * kOwn, 256), 256, 0, s>>>(N, n_own, stage_own, stage_par, pslot_own, pslot_par, n_par, err);
         MLIP_HIP(hipGetLastError());
-        k_pair_counts<<<blocks_for(N, 256), 256, 0, s>>>(N, n_own, n_par, g->counts.as<int32_t>());
-        MLIP_HIP(hipGetLastError());
-        MLIP_TRY(scan_i32_to_i64(g->counts.as<int32_t>(), out.row_ptr->as<int64_t>(), N, g->scan_tmp, s));
-        const int rc = read_counts_and_flags(g, out.row_ptr->as<int64_t>() + N, err, &E, &flags);   // first synchronisation
+        MLIP_TRY(scan(ScanSum{n_own, n_par}, out.row_ptr->as<int64_t>(), N, g->scan_tmp, s, publish));
+        const int rc = read_counts_and_flags(g, &E, &flags);   // first synchronisation
         if (!(flags & FLAG_STAGE_OVERFLOW)) {
             MLIP_TRY(rc);
             const size_t Ecap = (size_t)std::max<int64_t>(E, 1);
@@ -1688,8 +1768,9 @@ int search_csr(mlip_graph *g, const CellParams &cp, int64_t N, CsrOut out, int64
             g->sz.as<double>(), g->swrap.as<uint32_t>(), g->cell_of.as<int32_t>(), g->counts.as<int32_t>(), nullptr,
             nullptr, err);
         MLIP_HIP(hipGetLastError());
-        MLIP_TRY(scan_i32_to_i64(g->counts.as<int32_t>(), out.row_ptr->as<int64_t>(), N, g->scan_tmp, s));
-        MLIP_TRY(read_counts_and_flags(g, out.row_ptr->as<int64_t>() + N, err, &E, &flags));
+        MLIP_TRY(scan(scan_array(g->counts.as<int32_t>()), out.row_ptr->as<int64_t>(), N, g->scan_tmp, s, publish));
+        MLIP_TRY(read_counts_and_flags(g, &E, &flags));
+        *unchecked = true;   // (k_mirror)
         const size_t Ecap = (size_t)std::max<int64_t>(E, 1);
         MLIP_TRY(g->keys.ensure(Ecap * 8));
         MLIP_TRY(out.senders->ensure(Ecap * 4));
@@ -1719,11 +1800,13 @@ int search_csr(mlip_graph *g, const CellParams &cp, int64_t N, CsrOut out, int64
 
 // The exact neighbour list from the handle's candidate list; *valid = false (and nothing usable written) when some
 // atom has moved more than skin / 2 since the candidates were built.  Synchronises the stream once.
-int csr_from_candidates(mlip_graph *g, const CellParams &cp, int64_t N, int64_t *E_out, bool *valid)
+int csr_from_candidates(mlip_graph *g, const CellParams &cp, int64_t N, int32_t P, int64_t *E_out, bool *valid)
 {
     hipStream_t s = g->stream;
-    int32_t *err = g->small.as<int32_t>();
-    MLIP_HIP(hipMemsetAsync(g->small.p, 0, 4096, s));
+    ZeroBlock z;
+    MLIP_TRY(zero_block(g, N, P, 0, z));
+    int32_t *err = z.err;
+    MLIP_HIP(hipMemsetAsync(g->small.p, 0, z.part_bytes, s));
     MLIP_TRY(g->row_ptr.ensure((size_t)(N + 1) * 8));
     const double h2 = 0.25 * g->skin * g->skin;
     const double *pos = g->pos.as<double>();
@@ -1732,10 +1815,11 @@ int csr_from_candidates(mlip_graph *g, const CellParams &cp, int64_t N, int64_t 
         g->cand_senders.as<int32_t>(), g->cand_shiftp.as<uint32_t>(), g->counts.as<int32_t>(), g->slab_of.as<int32_t>(),
         nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, err);
     MLIP_HIP(hipGetLastError());
-    MLIP_TRY(scan_i32_to_i64(g->counts.as<int32_t>(), g->row_ptr.as<int64_t>(), N, g->scan_tmp, s));
+    MLIP_TRY(scan(scan_array(g->counts.as<int32_t>()), g->row_ptr.as<int64_t>(), N, g->scan_tmp, s,
+                  Publish{static_cast<int64_t *>(g->pinned), err}));
     int64_t E = 0;
     int32_t flags = 0;
-    const int rc = read_counts_and_flags(g, g->row_ptr.as<int64_t>() + N, err, &E, &flags);
+    const int rc = read_counts_and_flags(g, &E, &flags);
     if (flags & FLAG_DISPLACED) { *valid = false; return MLIP_OK; }   // (errors seen on the way are found again by the full search)
     MLIP_TRY(rc);
     const size_t Ecap = (size_t)std::max<int64_t>(E, 1);
@@ -1779,17 +1863,19 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
         sv.pairs.valid = false;
     }
     g->E = 0;
-    if (!g->pinned) MLIP_HIP(hipHostMalloc(&g->pinned, 65536, hipHostMallocDefault));
+    if (!g->pinned) MLIP_HIP(hipHostMalloc(&g->pinned, kPinnedBytes, hipHostMallocDefault));
     int64_t *hp = static_cast<int64_t *>(g->pinned);
 
     MLIP_TRY(g->pos.ensure((size_t)N * 3 * sizeof(double)));
     MLIP_TRY(g->species.ensure((size_t)N * sizeof(int32_t)));
-    MLIP_HIP(hipMemcpyAsync(g->pos.p, positions, (size_t)N * 3 * sizeof(double), hipMemcpyDeviceToDevice, s));
-    MLIP_HIP(hipMemcpyAsync(g->species.p, species, (size_t)N * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
+    if (g->skin > 0.0) {   // (the search copies them on the way)
+        MLIP_HIP(hipMemcpyAsync(g->pos.p, positions, (size_t)N * 3 * sizeof(double), hipMemcpyDeviceToDevice, s));
+        MLIP_HIP(hipMemcpyAsync(g->species.p, species, (size_t)N * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
+    }
     MLIP_TRY(g->slab_of.ensure((size_t)N * 4));
     MLIP_TRY(g->counts.ensure((size_t)(N + 1) * 4));
-    MLIP_TRY(g->small.ensure(4096));
-    int32_t *err = g->small.as<int32_t>();
+    if (P > 1 && class_entries(N, P) >= ((int64_t)1 << 31)) { set_error("too many atoms for this many slabs"); return MLIP_EINVAL; }
+    bool unchecked = false;   // a flag may have been raised after the flags were read
 
     prof_begin(g, MLIP_PROF_GRAPH);
     int64_t E = 0;
@@ -1800,14 +1886,15 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
         const bool usable = g->cand_valid && g->cand_N == N && g->cand_rcut == r_cut && g->cand_skin == g->skin &&
                             std::memcmp(g->cand_cell, cell, sizeof(g->cand_cell)) == 0;
         int rc = MLIP_OK;
-        if (usable) rc = csr_from_candidates(g, cp, N, &E, &valid);
+        unchecked = true;   // (k_skin_mirror)
+        if (usable) rc = csr_from_candidates(g, cp, N, P, &E, &valid);
         if (rc == MLIP_OK && !valid) {
             g->cand_valid = false;
             CellParams cps;
             rc = prepare_cell(cell, r_cut + g->skin, P, N, cps);
             if (rc == MLIP_OK)
-                rc = search_csr(g, cps, N, CsrOut{&g->cand_row_ptr, &g->cand_senders, &g->cand_recv, &g->cand_shiftp, &g->cand_d, &g->cand_mirror},
-                                &g->cand_E);
+                rc = search_csr(g, cps, N, P, nullptr, nullptr, CsrOut{&g->cand_row_ptr, &g->cand_senders, &g->cand_recv, &g->cand_shiftp, &g->cand_d, &g->cand_mirror},
+                                &g->cand_E, &unchecked);
             if (rc == MLIP_OK) rc = g->ref_pos.ensure((size_t)N * 3 * sizeof(double));
             if (rc == MLIP_OK) {
                 MLIP_HIP(hipMemcpyAsync(g->ref_pos.p, g->pos.p, (size_t)N * 3 * sizeof(double), hipMemcpyDeviceToDevice, s));
@@ -1817,7 +1904,7 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
                 std::memcpy(g->cand_cell, cell, sizeof(g->cand_cell));
                 g->cand_valid = true;
                 g->skin_builds += 1;
-                rc = csr_from_candidates(g, cp, N, &E, &valid);
+                rc = csr_from_candidates(g, cp, N, P, &E, &valid);
                 if (rc == MLIP_OK && !valid) { set_error("internal error: a fresh candidate list is not valid"); rc = MLIP_EHIP; }
             }
         } else if (rc == MLIP_OK) {
@@ -1825,11 +1912,10 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
         }
         if (rc != MLIP_OK) { prof_end(g); return rc; }
     } else {
-        const int rc = search_csr(g, cp, N, CsrOut{&g->row_ptr, &g->senders, &g->recv, &g->shiftp, &g->d, &g->mirror}, &E);
+        const int rc = search_csr(g, cp, N, P, positions, species, CsrOut{&g->row_ptr, &g->senders, &g->recv, &g->shiftp, &g->d, &g->mirror}, &E,
+                                  &unchecked);
         if (rc != MLIP_OK) { prof_end(g); return rc; }
     }
-    const double *pos = g->pos.as<double>();
-    (void)pos;
     MLIP_TRY(g->mirror.ensure((size_t)std::max<int64_t>(E, 1) * 4));
 
     {
@@ -1858,39 +1944,35 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
     if (P > 1) {
         if (g->slabs.size() < (size_t)P) g->slabs.resize(P);  // never shrunk: views own workspace
         PartStore &st = g->part;
-        MLIP_TRY(g->needed_by.ensure((size_t)N * 8));
+        ZeroBlock z;
+        MLIP_TRY(zero_block(g, N, P, 0, z));   // (grown by the search; cleared there)
+        g->needed_by = z.needed_by;
         MLIP_TRY(g->local_in_owner.ensure((size_t)N * sizeof(OwnRec)));   // one record per atom
         MLIP_TRY(st.gbase.ensure((size_t)(N + 1) * 4));
-        MLIP_HIP(hipMemsetAsync(g->needed_by.p, 0, (size_t)N * 8, s));
         k_needed_by<<<grid8((N + 15) / 16), 256, 0, s>>>(N, g->row_ptr.as<int64_t>(), g->senders.as<int32_t>(),
-                                               g->slab_of.as<int32_t>(), g->needed_by.as<unsigned long long>());
+                                               g->slab_of.as<int32_t>(), g->needed_by);
         MLIP_HIP(hipGetLastError());
         // ghost entries per atom and their scan: where the (partition -> local index) entries of an atom start
-        k_popcount<<<blocks_for(N, 256), 256, 0, s>>>(N, g->needed_by.as<unsigned long long>(), g->counts.as<int32_t>());
-        MLIP_HIP(hipGetLastError());
-        MLIP_TRY(scan_i32_to_i32(g->counts.as<int32_t>(), st.gbase.as<int32_t>(), N, g->scan_tmp, s));
+        MLIP_TRY(scan(ScanBits{g->needed_by}, st.gbase.as<int32_t>(), N, g->scan_tmp, s));
         // class counts of every (partition, span) bin per range of kRange atoms, one flat scan
         const int B1 = P * (P + 2), nbins = B1 + P;
         const int64_t nranges = (N + kRange - 1) / kRange;
-        const int64_t nent = (int64_t)nbins * nranges;
-        if (nent >= ((int64_t)1 << 31)) { prof_end(g); set_error("too many atoms for this many slabs"); return MLIP_EINVAL; }
-        MLIP_TRY(g->class_cnt.ensure((size_t)nent * 4));
+        const int64_t nent = class_entries(N, P);
         MLIP_TRY(g->class_off.ensure((size_t)(nent + 1) * 4));
-        MLIP_HIP(hipMemsetAsync(g->class_cnt.p, 0, (size_t)nent * 4, s));
         const int cwaves = ((size_t)nbins * 4 * 4 > 60000) ? 2 : 4;   // wavefronts per block: each keeps a table of nbins counters in LDS
         const size_t clds = (size_t)cwaves * nbins * 4;
         const unsigned cblocks = (unsigned)((nranges + cwaves - 1) / cwaves);
         k_classes<false><<<cblocks, cwaves * 64, clds, s>>>(N, P, nranges, g->slab_of.as<int32_t>(),
-                                                            g->needed_by.as<unsigned long long>(), g->class_cnt.as<int32_t>(),
+                                                            g->needed_by, z.class_cnt,
                                                             nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
         MLIP_HIP(hipGetLastError());
-        MLIP_TRY(scan_i32_to_i32(g->class_cnt.as<int32_t>(), g->class_off.as<int32_t>(), nent, g->scan_tmp, s));
+        MLIP_TRY(scan(scan_array(z.class_cnt), g->class_off.as<int32_t>(), nent, g->scan_tmp, s));
         const int nmark = P * (P + 3) + 1;
-        MLIP_TRY(st.sizes.ensure((size_t)(nmark + 2 * P + 8) * 8));
+        // published in pinned host memory: the spans' starts, later every partition's edge counts and the flags
+        static_assert((kMaxSlabs * (kMaxSlabs + 3) + 1 + 2 * kMaxSlabs + 1) * 8 <= kPinnedBytes, "published values fit the pinned area");
         k_gather_markers<<<blocks_for(nmark, 256), 256, 0, s>>>(g->class_off.as<int32_t>(), P, nranges, st.gbase.as<int32_t>(), N,
-                                                                st.sizes.as<int64_t>());
+                                                                hp);
         MLIP_HIP(hipGetLastError());
-        MLIP_HIP(hipMemcpyAsync(hp, st.sizes.p, (size_t)nmark * 8, hipMemcpyDeviceToHost, s));
         MLIP_HIP(hipStreamSynchronize(s));   // second synchronisation: the span starts of all partitions
         PartTab T{};
         T.P = P;
@@ -1929,12 +2011,11 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
         MLIP_TRY(st.row_abs.ensure((size_t)(TL + P + 1) * 8));
         MLIP_TRY(st.row_ptr.ensure((size_t)(TL + P + 1) * 8));
         k_classes<true><<<cblocks, cwaves * 64, clds, s>>>(N, P, nranges, g->slab_of.as<int32_t>(),
-                                                           g->needed_by.as<unsigned long long>(), nullptr,
+                                                           g->needed_by, nullptr,
                                                            g->class_off.as<int32_t>(), st.gbase.as<int32_t>(),
                                                            st.nodes.as<int32_t>(), st.owned_sorted.as<int32_t>(),
                                                            g->local_in_owner.as<OwnRec>(), st.ghost_local.as<int32_t>());
         MLIP_HIP(hipGetLastError());
-        MLIP_HIP(hipMemsetAsync(st.rowlen.p, 0, (size_t)(TL + P + 1) * 4, s));
         k_owned_rowlen<<<blocks_for(N, 256), 256, 0, s>>>(N, T, g->local_in_owner.as<OwnRec>(), g->row_ptr.as<int64_t>(),
                                                          st.rowlen.as<int32_t>());
         if (n_ghost_total > 0)
@@ -1943,16 +2024,14 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
                 g->local_in_owner.as<OwnRec>(), st.rowlen.as<int32_t>(), st.ghost_owner.as<int32_t>(),
                 st.ghost_src.as<int32_t>());
         MLIP_HIP(hipGetLastError());
-        MLIP_TRY(scan_i32_to_i64(st.rowlen.as<int32_t>(), st.row_abs.as<int64_t>(), TL + P, g->scan_tmp, s));
-        int64_t *dsz = st.sizes.as<int64_t>() + nmark;
+        MLIP_TRY(scan(scan_array(st.rowlen.as<int32_t>()), st.row_abs.as<int64_t>(), TL + P, g->scan_tmp, s));
+        int64_t *sizes = hp + nmark;
         k_local_rowptr<<<blocks_for(TL + P, 256), 256, 0, s>>>(T, st.row_abs.as<int64_t>(), st.nodes.as<int32_t>(),
                                                                g->row_ptr.as<int64_t>(), st.row_ptr.as<int64_t>(),
-                                                               g->local_in_owner.as<OwnRec>(), dsz);
+                                                               g->local_in_owner.as<OwnRec>(), sizes, z.err);
         MLIP_HIP(hipGetLastError());
-        MLIP_HIP(hipMemcpyAsync(hp, dsz, (size_t)2 * P * 8, hipMemcpyDeviceToHost, s));
-        MLIP_HIP(hipMemcpyAsync(hp + 2 * P, err, 4, hipMemcpyDeviceToHost, s));
         MLIP_HIP(hipStreamSynchronize(s));   // third and last synchronisation: the partitions' edge counts, the error flags
-        if (*reinterpret_cast<int32_t *>(hp + 2 * P) & ERR_MIRROR) {
+        if (sizes[2 * P] & ERR_MIRROR) {
             prof_end(g);
             set_error("internal error: an edge without its reverse edge");
             return MLIP_EHIP;
@@ -1962,8 +2041,8 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
         std::vector<int64_t> ebase(P + 1);
         for (int q = 0; q < P; ++q) {
             SlabView &v = g->slabs[q];
-            v.n_edges_owned = hp[2 * q];
-            v.n_edges = hp[2 * q + 1];
+            v.n_edges_owned = sizes[2 * q];
+            v.n_edges = sizes[2 * q + 1];
             ebase[q] = TE;
             TE += v.n_edges;
             T.n_edges[q] = v.n_edges;
@@ -1984,7 +2063,7 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
         if (E > 0) {
             k_local_fill_owned<<<grid8(blocks_for(E, 256)), 256, 0, s>>>(
                 E, T, g->recv.as<int32_t>(), g->senders.as<int32_t>(), g->shiftp.as<uint32_t>(), g->d.as<float>(),
-                g->mirror.as<int32_t>(), g->needed_by.as<unsigned long long>(), g->local_in_owner.as<OwnRec>(),
+                g->mirror.as<int32_t>(), g->needed_by, g->local_in_owner.as<OwnRec>(),
                 st.gbase.as<int32_t>(), st.ghost_local.as<int32_t>(), st.row_abs.as<int64_t>(), st.senders.as<int32_t>(),
                 st.recv.as<int32_t>(), st.shiftp.as<uint32_t>(), st.d.as<float>(), st.mirror.as<int32_t>());
             MLIP_HIP(hipGetLastError());
@@ -2014,9 +2093,11 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
             v.ghost_src = st.ghost_src.as<int32_t>() + T.ghost0[q];
         }
         prof_end(g);
+    } else if (!unchecked) {
+        prof_end(g);
     } else {
         prof_end(g);
-        MLIP_HIP(hipMemcpyAsync(hp, err, 4, hipMemcpyDeviceToHost, s));
+        MLIP_HIP(hipMemcpyAsync(hp, g->small.p, 4, hipMemcpyDeviceToHost, s));
         MLIP_HIP(hipStreamSynchronize(s));
         if (*reinterpret_cast<int32_t *>(hp) & ERR_MIRROR) {
             set_error("internal error: an edge without its reverse edge");

@@ -186,10 +186,9 @@ struct PartStore {
     DevBuf senders, recv, mirror, shiftp, d;              // pieces of n_edges entries
     DevBuf chunk_row;                                     // i32, pieces of chunks_of(n_edges, span) + 1 entries
     DevBuf gbase, ghost_local;                            // i32 [N + 1] scan of popcount(needed_by); i32 [sum n_ghost]
-    DevBuf sizes;                                         // i64 small read-back area
 };
 
-enum { kMaxSlabs = 64, kMaxEvents = 4096 };
+enum { kMaxSlabs = 64, kMaxEvents = 4096, kPinnedBytes = 65536 };
 
 struct Profiler {
     bool on = false;
@@ -222,7 +221,7 @@ struct mlip_graph {
     // inputs copied in
     mlip::DevBuf pos, species;
     // build scratch
-    mlip::DevBuf cell_of, wrapp, cell_cnt, cell_start, cell_fill, sid, sx, sy, sz, swrap, counts, keys, stage, pair_aux, flags,
+    mlip::DevBuf cell_of, wrapp, in_cell, cell_start, sid, sx, sy, sz, swrap, counts, keys, stage, pair_aux, flags,
         scan_tmp, small;
     // whole-graph CSR
     mlip::DevBuf row_ptr, senders, recv, mirror, shiftp, d, chunk_row;
@@ -234,7 +233,8 @@ struct mlip_graph {
     int64_t skin_builds = 0, skin_reuses = 0;
     mlip::DevBuf cand_row_ptr, cand_senders, cand_recv, cand_shiftp, cand_d, cand_mirror, ref_pos;
     // partition
-    mlip::DevBuf slab_of, needed_by, local_of, local_in_owner, class_cnt, class_off;
+    mlip::DevBuf slab_of, local_in_owner, class_off;
+    unsigned long long *needed_by = nullptr;   // [N] partitions that hold the atom as a ghost (in `small`)
     mlip::PartStore part;
     std::vector<mlip::SlabView> slabs;  // P views (empty when P == 1)
     mlip::SlabView whole;
@@ -246,14 +246,10 @@ struct mlip_graph {
     int work_next = 0;        // launches that have taken their counters in the current call
     mlip::Profiler prof;
     mlip::DevBuf bond_wpack;  // packed weights of the three-body variant's bond part
-    void *pinned = nullptr;  // small pinned host staging area
+    void *pinned = nullptr;  // pinned host area in which kernels leave counts and flags for the host
 };
 
 namespace mlip {
-
-// device-wide exclusive scans (n + 1 outputs, out[n] = total); tmp is grown as needed
-int scan_i32_to_i64(const int32_t *in, int64_t *out, int64_t n, DevBuf &tmp, hipStream_t s);
-int scan_i32_to_i32(const int32_t *in, int32_t *out, int64_t n, DevBuf &tmp, hipStream_t s);
 
 void prof_begin(mlip_graph *g, int group);
 void prof_end(mlip_graph *g);

@@ -331,7 +331,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
     };
     GhostIndex gidx{};
     if (slabs) {
-        gidx.needed_by = g->needed_by.as<unsigned long long>();
+        gidx.needed_by = g->needed_by;
         gidx.gbase = g->part.gbase.as<int32_t>();
         gidx.ghost_local = g->part.ghost_local.as<int32_t>();
     }
