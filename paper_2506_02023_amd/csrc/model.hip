@@ -56,13 +56,12 @@ struct Packs {  // offsets (floats) into the packed-weight buffer
 Packs pack_layout(int F, int L)
 {
     Packs p;
-    const size_t ff = (size_t)F * F, p1 = (size_t)(F / 32) * 4 * 64;
+    const size_t ff = (size_t)F * F * 3 / 2, p1 = (size_t)(F / 32) * 4 * 64;   // three bf16 parts
     p.A1 = 0;
     p.A1s = p1;
-    const size_t ff3 = ff * 3 / 2;   // the filter MLP's operands: three bf16 parts in fp32 mode
     p.W2t = 2 * p1;
-    p.W2n = p.W2t + ff3;
-    p.Wmt = p.W2n + ff3;
+    p.W2n = p.W2t + ff;
+    p.Wmt = p.W2n + ff;
     p.Wmn = p.Wmt + ff;
     p.Wot = p.Wmn + ff;
     p.Won = p.Wot + ff;
@@ -73,12 +72,12 @@ Packs pack_layout(int F, int L)
     return p;
 }
 
+constexpr int kNodeBlocks = 256;   // one per compute unit (512: 38 us against 27 for the largest of them at 32,000 atoms, 4 % slower at a million)
+
 template <int F> struct Lds {
     using D = Dims<F>;
     static constexpr size_t edge_fwd(int prec) { return sizeof(float) * (pack_floats<F>(prec) + kFwdWaves * D::TILE); }
     static constexpr size_t edge_bwd(int prec) { return sizeof(float) * (pack_floats<F>(prec) + D::PACK1 + kBwdWaves * kQueue * D::FS); }
-    static constexpr size_t node1 = sizeof(float) * (D::PACKF + 4 * D::TILE);
-    static constexpr size_t node2 = sizeof(float) * (2 * D::PACKF + 4 * D::TILE);
 };
 
 // Dynamic LDS size of a kernel, set once per handle (a handle lives on one device and is used by one thread at a
@@ -94,25 +93,10 @@ int configure_kernel(mlip_graph *g, const void *fn, size_t lds, int *slot)
     return MLIP_OK;
 }
 
-__global__ void k_fill_zero(float *p, int64_t n)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0.f;
-}
-
-// zero-fill with a kernel (not hipMemsetAsync: memset nodes of a captured stream have misbehaved on replay)
-int fill_zero(float *p, int64_t n, hipStream_t s)
-{
-    if (n <= 0) return MLIP_OK;
-    k_fill_zero<<<blocks_for(n, 256), 256, 0, s>>>(p, n);
-    MLIP_HIP(hipGetLastError());
-    return MLIP_OK;
-}
-
 template <int F, int OP> int launch_node(mlip_graph *g, NodeBatch &b)
 {
-    constexpr bool TWO = (OP == OP_READOUT || OP == OP_BWD_UPDATE);
-    const size_t lds = TWO ? Lds<F>::node2 : Lds<F>::node1;
+    using N = NodeOp<OP>;
+    const size_t lds = sizeof(float) * N::NPACK * Dims<F>::PACK3;
     int slot = 0;
     MLIP_TRY(configure_kernel(g, reinterpret_cast<const void *>(&k_node<F, OP>), lds, &slot));
     b.tile_start[0] = 0;
@@ -120,9 +104,9 @@ template <int F, int OP> int launch_node(mlip_graph *g, NodeBatch &b)
     for (int q = b.n; q < kBatch; ++q) b.tile_start[q + 1] = b.tile_start[b.n];
     const int64_t n_tiles = b.tile_start[b.n];
     if (n_tiles <= 0) return MLIP_OK;
-    // each block keeps its weight pack in LDS, so let it walk several tiles
-    const unsigned blocks = (unsigned)std::min<int64_t>((n_tiles + 3) / 4, 2048);
-    k_node<F, OP><<<blocks, 256, lds, g->stream>>>(b);
+    // every block keeps the weights in LDS and walks several tiles
+    const unsigned blocks = (unsigned)std::min<int64_t>(n_tiles, kNodeBlocks);
+    k_node<F, OP><<<blocks, N::NW * 64, lds, g->stream>>>(b);
     MLIP_HIP(hipGetLastError());
     return MLIP_OK;
 }
@@ -142,18 +126,25 @@ template <int F, int STAGE, int PREC> int launch_bond_mlp(mlip_graph *g, const B
     return MLIP_OK;
 }
 
-// Runs one node operation over all partitions, kBatch per launch; fill(view, args) sets the rows.
-template <int F, int OP, class Fill>
-int node_pass(mlip_graph *g, SlabView *views, int P, const float *P1, const float *P2, const float *wr2, Fill fill)
+// Runs one node operation over all partitions, kBatch per launch; common holds what they share, fill(view, args) sets the rows.
+template <int F, int OP, class Fill> int node_pass(mlip_graph *g, SlabView *views, int P, const NodeBatch &common, Fill fill)
 {
+    int n_clear = common.n_clear;   // by the first launch that has rows
     for (int p0 = 0; p0 < P; p0 += kBatch) {
-        NodeBatch nb{};
+        NodeBatch nb = common;
+        nb.n_clear = n_clear;
         nb.n = std::min(kBatch, P - p0);
-        nb.P1 = P1;
-        nb.P2 = P2;
-        nb.wr2 = wr2;
-        for (int q = 0; q < nb.n; ++q) fill(views[p0 + q], nb.s[q]);
+        for (int q = 0; q < nb.n; ++q) {
+            SlabView &v = views[p0 + q];
+            NodeArgs &na = nb.s[q];
+            na = NodeArgs{};
+            na.n_rows = v.n_owned;
+            na.n_pure = v.n_pure;
+            na.nodes = v.nodes;
+            fill(v, na);
+        }
         MLIP_TRY((launch_node<F, OP>(g, nb)));
+        if (nb.tile_start[nb.n] > 0) n_clear = 0;
     }
     return MLIP_OK;
 }
@@ -248,7 +239,12 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         const size_t no = (size_t)std::max<int64_t>(v.n_owned, 1), nl = (size_t)std::max<int64_t>(v.n_local, 1);
         MLIP_TRY(place(v.h, no * rowb, v.ws.h));
         MLIP_TRY(place(v.hbar, no * rowb, v.ws.hbar));
-        MLIP_TRY(place(v.abar, nl * rowb, v.ws.abar));
+        if (bw) {   // every layer's is kept for the bonds' own reverse step
+            MLIP_TRY(v.bonds.abar_keep.ensure(nl * rowb * (size_t)std::max(L, 1)));
+            v.ws.abar = v.bonds.abar_keep.as<float>();
+        } else {
+            MLIP_TRY(place(v.abar, nl * rowb, v.ws.abar));
+        }
         MLIP_TRY(place(v.gbar, nl * rowb, v.ws.gbar));
         MLIP_TRY(place(v.eps, no * sizeof(float), v.ws.eps));
         MLIP_TRY(place(v.dsum, (size_t)std::max<int64_t>(v.n_edges, 1) * sizeof(float), v.ws.dsum));
@@ -256,9 +252,10 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         MLIP_TRY(place(v.g, nl * rowb * (size_t)std::max(L, 1), v.ws.g));
         MLIP_TRY(place(v.a, no * rowb * (size_t)std::max(L, 1), v.ws.a));
         v.ws.wst = nullptr;
-        if (L > 0)   // kept filter values, a slice per layer (layer 0's reverse step needs none: its slice stays empty)
-            MLIP_TRY(place(v.wst, (size_t)std::max<int64_t>(v.pairs.n_upper, 1) * rowb * (size_t)L, v.ws.wst));
-        n_parts += (v.n_owned + 1023) / 1024;
+        if (L > 0)   // kept filter values, a slice per layer (layer 0's reverse step needs none: its slice stays empty, and
+                     // the fixed block holds none for it)
+            MLIP_TRY(place(v.wst, (size_t)std::max<int64_t>(v.pairs.n_upper, 1) * rowb * (size_t)(scratch ? L - 1 : L), v.ws.wst));
+        n_parts += (v.n_owned + 31) / 32;
     }
     const Packs pk = pack_layout(F, L);
     float *wp = nullptr, *energy_part_f = nullptr;
@@ -275,13 +272,12 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
     double *energy_part = reinterpret_cast<double *>(energy_part_f);
     g->work_ptr = reinterpret_cast<int32_t *>(work_f);
     g->work_next = 0;
-    MLIP_TRY(fill_zero(work_f, (int64_t)work_n, s));
-
-
-    auto wslice = [&](SlabView &v, int l) { return v.ws.wst + (size_t)l * (size_t)v.pairs.n_upper * F; };
+    auto wslice = [&](SlabView &v, int l) { return v.ws.wst + (size_t)(scratch ? l - 1 : l) * (size_t)v.pairs.n_upper * F; };   // l >= 1
+    // dE/da of a layer: one array for all layers in turn, or one per layer where the three-body variant keeps them
+    auto abarslice = [&](SlabView &v, int l) { return v.ws.abar + (bw ? (size_t)l * (size_t)v.n_local * F : 0); };
 
     // ---- batches for the small kernels (embedding, ghost transfers, forces, energy): up to kBatch partitions per launch
-    enum { U_OWNED, U_GHOST, U_BORDER, U_LOCAL, U_KBLOCKS };
+    enum { U_OWNED, U_GHOST, U_LOCAL };
     auto small_batch = [&](int p0, int unit, int layer) {
         SmallBatch sb{};
         sb.n = std::min(kBatch, P - p0);
@@ -302,29 +298,24 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             a.senders = v.senders;
             a.mirror = v.mirror;
             a.shiftp = v.shiftp;
-            a.h = v.ws.h;
-            a.g = (layer >= 0) ? v.ws.g + (size_t)layer * (size_t)v.n_local * F : nullptr;
             a.gbar = v.ws.gbar;
-            a.abar = v.ws.abar;
+            a.abar = abarslice(v, std::max(layer, 0));
             a.floc = v.ws.floc;
             a.eps = v.ws.eps;
             a.dsum = v.ws.dsum;
             a.d = v.d;
-            a.wstore = (layer >= 0 && v.ws.wst) ? wslice(v, layer) : nullptr;
+            a.wstore = layer >= 1 ? wslice(v, layer) : nullptr;
             a.uslot = v.pairs.uslot;
             a.l_row_ptr = v.pairs.l_row_ptr;
             a.l_senders = v.pairs.l_senders;
             a.l_slot = v.pairs.l_slot;
-            a.a = (layer >= 0) ? v.ws.a + (size_t)layer * (size_t)v.n_owned * F : nullptr;
             a.bond_of_edge = (bw && v.bonds.n > 0) ? v.bonds.of_edge.as<int32_t>() : nullptr;
             a.wb_bf16 = (prec == kPrecBf16);
             a.wb = (bw && v.bonds.n > 0 && layer >= 0)
                        ? static_cast<char *>(v.bonds.wb.p) + (size_t)layer * (size_t)std::max<int64_t>(v.bonds.n, 1) * F *
                                                                    (a.wb_bf16 ? sizeof(__bf16) : sizeof(float))
                        : nullptr;
-            const int64_t items = unit == U_OWNED ? v.n_owned : unit == U_GHOST ? v.n_ghost
-                                  : unit == U_BORDER ? v.n_owned - v.n_pure : unit == U_LOCAL ? v.n_local
-                                  : (v.n_owned + 1023) / 1024;
+            const int64_t items = unit == U_OWNED ? v.n_owned : unit == U_GHOST ? v.n_ghost : v.n_local;
             sb.start[q + 1] = sb.start[q] + std::max<int64_t>(items, 0);
         }
         return sb;
@@ -353,20 +344,20 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
     if (repack) {
         PackBatch pb{};
         pb.F = F;
-        const size_t ff = (size_t)F * F;
+        const size_t ff = (size_t)F * F;   // floats of a weight matrix
         for (int l = 0; l < L; ++l) {
             float *base = wp + pk.per_layer * l;
             pb.add(w->W1 + (size_t)l * 8 * F, base + pk.A1, PACK_W1, 0, 1.0f);
             pb.add(w->W1 + (size_t)l * 8 * F, base + pk.A1s, PACK_W1, 0, kSiluScale);
             pb.add(w->W2 + l * ff, base + pk.W2t, w2_kind, 1, kSiluScaleInv);
             pb.add(w->W2 + l * ff, base + pk.W2n, w2_kind, 0, 1.0f);
-            pb.add(w->Wm + l * ff, base + pk.Wmt, PACK_FF, 1, 1.0f);
-            pb.add(w->Wm + l * ff, base + pk.Wmn, PACK_FF, 0, 1.0f);
-            pb.add(w->Wo + l * ff, base + pk.Wot, PACK_FF, 1, 1.0f);
-            pb.add(w->Wo + l * ff, base + pk.Won, PACK_FF, 0, 1.0f);
+            pb.add(w->Wm + l * ff, base + pk.Wmt, PACK_FF_BF16X3, 1, 1.0f);
+            pb.add(w->Wm + l * ff, base + pk.Wmn, PACK_FF_BF16X3, 0, 1.0f);
+            pb.add(w->Wo + l * ff, base + pk.Wot, PACK_FF_BF16X3, 1, 1.0f);
+            pb.add(w->Wo + l * ff, base + pk.Won, PACK_FF_BF16X3, 0, 1.0f);
         }
-        pb.add(w->Wr1, wp + pk.readout_t, PACK_FF, 1, 1.0f);
-        pb.add(w->Wr1, wp + pk.readout_n, PACK_FF, 0, 1.0f);
+        pb.add(w->Wr1, wp + pk.readout_t, PACK_FF_BF16X3, 1, 1.0f);
+        pb.add(w->Wr1, wp + pk.readout_n, PACK_FF_BF16X3, 0, 1.0f);
         k_pack<<<dim3(blocks_for((int64_t)F * F, 256), pb.n), 256, 0, s>>>(pb);
     }
     MLIP_HIP(hipGetLastError());
@@ -375,14 +366,6 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         g->packed_w_valid = true;
     }
 
-    // ---- embedding
-    const int32_t *species = g->species.as<int32_t>();
-    for (int p0 = 0; p0 < P; p0 += kBatch) {
-        const SmallBatch sb = small_batch(p0, U_OWNED, -1);
-        if (sb.start[sb.n] > 0)
-            k_embed<<<blocks_for(sb.start[sb.n] * (F / 4), 256), 256, 0, s>>>(sb, F, species, w->emb);
-    }
-    MLIP_HIP(hipGetLastError());
     prof_end(g);
 
     // ---- three-body variant: bond lists, bond embedding, triplet update, bond terms of the layers' filters.
@@ -422,7 +405,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         a.m = BG.m.p;
         a.wb = BG.wb.p;
         a.abar = BG.abar_keep.as<float>();
-        a.abar_stride = (size_t)std::max<int64_t>(v.n_owned, 1) * F;
+        a.abar_stride = (size_t)v.n_local * F;
         a.g = v.ws.g;
         a.g_stride = (size_t)v.n_local * F;
         a.e1bar = BG.e1bar.p;
@@ -446,7 +429,6 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             DevBuf *fb[] = {&BG.P, &BG.Q, &BG.S, &BG.m, &BG.e1bar, &BG.Sbar, &BG.Pbar, &BG.Qbar};
             for (DevBuf *b : fb) MLIP_TRY(b->ensure(bs * belem));
             MLIP_TRY(BG.wb.ensure(bs * belem * (size_t)std::max(L, 1)));
-            MLIP_TRY(BG.abar_keep.ensure((size_t)std::max<int64_t>(views[p].n_owned, 1) * rowb * (size_t)std::max(L, 1)));
             MLIP_TRY(BG.ubar.ensure(nb1 * sizeof(float)));
             MLIP_TRY(BG.dbond.ensure(nb1 * sizeof(float)));
             MLIP_TRY(BG.rbar.ensure(nb1 * 3 * sizeof(float)));
@@ -518,28 +500,48 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
     auto gslice = [&](SlabView &v, int l) { return v.ws.g + (size_t)l * (size_t)v.n_local * F; };
     auto aslice = [&](SlabView &v, int l) { return v.ws.a + (size_t)l * (size_t)v.n_owned * F; };
 
+    // what the node launches share; the ghost rows' addresses are set per launch
+    NodeBatch common{};
+    common.wr2 = w->wr2;
+    common.emb = w->emb;
+    common.species = g->species.as<int32_t>();
+    common.ghosts = gidx;
+    auto ghost_tab = [&](auto &&array_of) {
+        if (slabs)
+            for (int q = 0; q < P; ++q) common.tab.p[q] = array_of(views[q]);
+    };
+    auto layer_pack = [&](int l) { return wp + pk.per_layer * l; };
+    int64_t tiles_before = 0;
+    auto tile_sums = [&](SlabView &v) {
+        double *at = energy_part + tiles_before;
+        tiles_before += (v.n_owned + 31) / 32;
+        return at;
+    };
+
     // ---- forward layers
     for (int l = 0; l < L; ++l) {
-        const float *base = wp + pk.per_layer * l;
+        const float *base = layer_pack(l);
         prof_begin(g, MLIP_PROF_NODE);
-        MLIP_TRY((node_pass<F, OP_PROJ>(g, views, P, base + pk.Wmt, nullptr, nullptr, [&](SlabView &v, NodeArgs &na) {
-            na.n_rows = v.n_owned;   // sender projection on owned rows
-            na.X = v.ws.h;
-            na.Y = gslice(v, l);
-        })));
-        prof_end(g);
-        if (slabs) {
-            prof_begin(g, MLIP_PROF_GHOST);
-            PtrTable tab{};
-            for (int q = 0; q < P; ++q) tab.p[q] = gslice(views[q], l);
-            for (int p0 = 0; p0 < P; p0 += kBatch) {   // border-node transfer: ghost rows <- owners
-                const SmallBatch sb = small_batch(p0, U_GHOST, l);
-                if (sb.start[sb.n] > 0)
-                    k_ghost_copy<<<blocks_for(sb.start[sb.n] * (F / 4), 256), 256, 0, s>>>(sb, F, tab);
-            }
-            MLIP_HIP(hipGetLastError());
-            prof_end(g);
+        ghost_tab([&](SlabView &v) { return gslice(v, l); });
+        if (l == 0) {
+            common.P[0] = base + pk.Wmt;
+            common.clear = g->work_ptr;
+            common.n_clear = (int)work_n;
+            MLIP_TRY((node_pass<F, OP_EMBED>(g, views, P, common, [&](SlabView &v, NodeArgs &na) {
+                na.Z = v.ws.h;
+                na.Y = gslice(v, 0);
+            })));
+            common.n_clear = 0;
+        } else {
+            common.P[0] = layer_pack(l - 1) + pk.Wot;
+            common.P[1] = base + pk.Wmt;
+            MLIP_TRY((node_pass<F, OP_UPDATE>(g, views, P, common, [&](SlabView &v, NodeArgs &na) {
+                na.X = aslice(v, l - 1);
+                na.Z = v.ws.h;
+                na.Y = gslice(v, l);
+            })));
         }
+        prof_end(g);
         for (int p0 = 0; p0 < P; p0 += kBatch) {   // the partitions in order, up to kBatch per launch
             EdgeBatch eb{};
             eb.n = std::min(kBatch, P - p0);
@@ -583,60 +585,44 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             MLIP_HIP(hipGetLastError());
             prof_end(g);
         }
-        prof_begin(g, MLIP_PROF_NODE);
-        MLIP_TRY((node_pass<F, OP_UPDATE>(g, views, P, base + pk.Wot, nullptr, nullptr, [&](SlabView &v, NodeArgs &na) {
-            na.n_rows = v.n_owned;
-            na.X = aslice(v, l);
-            na.Z = v.ws.h;
-        })));
-        prof_end(g);
     }
 
-    // ---- readout (energy and dE/dh of the last layer in one pass)
+    // ---- the last layer's update, the readout and the first step back
     prof_begin(g, MLIP_PROF_NODE);
-    MLIP_TRY((node_pass<F, OP_READOUT>(g, views, P, wp + pk.readout_t, wp + pk.readout_n, w->wr2,
-                                       [&](SlabView &v, NodeArgs &na) {
-                                           na.n_rows = v.n_owned;
-                                           na.X = v.ws.h;
-                                           na.Y = v.ws.hbar;
-                                           na.eps = v.ws.eps;
-                                       })));
-    prof_end(g);
-    prof_begin(g, MLIP_PROF_FORCE);
-    {
-        int64_t off = 0;
-        double *part = energy_part;
-        for (int p0 = 0; p0 < P; p0 += kBatch) {
-            const SmallBatch sb = small_batch(p0, U_KBLOCKS, -1);
-            const int64_t nb = sb.start[sb.n];
-            if (nb > 0) k_energy_partial<<<(unsigned)nb, 256, 0, s>>>(sb, part + off);
-            off += nb;
-        }
-        k_energy_final<<<1, 256, 0, s>>>(off, part, energy);
-        MLIP_HIP(hipGetLastError());
+    if (L > 0) {
+        common.P[0] = layer_pack(L - 1) + pk.Wot;
+        common.P[1] = wp + pk.readout_t;
+        common.P[2] = wp + pk.readout_n;
+        common.P[3] = layer_pack(L - 1) + pk.Won;
+        MLIP_TRY((node_pass<F, OP_TURN>(g, views, P, common, [&](SlabView &v, NodeArgs &na) {
+            na.X = aslice(v, L - 1);
+            na.Z = v.ws.h;
+            na.hbar = L > 1 ? v.ws.hbar : nullptr;   // (layer 0's step back is the last one)
+            na.Y = abarslice(v, L - 1);
+            na.eps = v.ws.eps;
+            na.tile_sum = tile_sums(v);
+        })));
+    } else {
+        common.P[0] = wp + pk.readout_t;
+        MLIP_TRY((node_pass<F, OP_READ>(g, views, P, common, [&](SlabView &v, NodeArgs &na) {
+            na.eps = v.ws.eps;
+            na.tile_sum = tile_sums(v);
+        })));
     }
     prof_end(g);
+    const EnergySum energy_sum{tiles_before, energy_part, energy};
 
     // ---- reverse pass
     if (L > 0)   // ghost rows carry no dE/da: zero once, no kernel ever writes them
         for (int p0 = 0; p0 < P; p0 += kBatch) {
             const SmallBatch sb = small_batch(p0, U_GHOST, -1);
             if (sb.start[sb.n] > 0)
-                k_zero_ghost_rows<<<blocks_for(sb.start[sb.n] * (F / 4), 256), 256, 0, s>>>(sb, F);
+                k_zero_ghost_rows<<<dim3(blocks_for(sb.start[sb.n] * (F / 4), 256), bw ? L : 1), 256, 0, s>>>(sb, F);
         }
     MLIP_HIP(hipGetLastError());
     for (int l = L - 1; l >= 0; --l) {
         const float *base = wp + pk.per_layer * l;
         const bool need_gbar = l > 0;  // dE/dh0 is never used: the embedding does not depend on positions
-        prof_begin(g, MLIP_PROF_NODE);
-        MLIP_TRY((node_pass<F, OP_BWD_UPDATE>(g, views, P, base + pk.Wot, base + pk.Won, nullptr,
-                                              [&](SlabView &v, NodeArgs &na) {
-                                                  na.n_rows = v.n_owned;
-                                                  na.X = aslice(v, l);
-                                                  na.Z = v.ws.hbar;
-                                                  na.Y = v.ws.abar;
-                                              })));
-        prof_end(g);
         for (int p0 = 0; p0 < P; p0 += kBatch) {
             EdgeBatch eb{};
             eb.n = std::min(kBatch, P - p0);
@@ -662,7 +648,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
                 ea.mirror = Q.u_mirror;
                 ea.eid = Q.u_eid;
                 ea.g = gslice(v, l);
-                ea.abar = v.ws.abar;
+                ea.abar = abarslice(v, l);
                 ea.out = v.ws.gbar;
                 ea.dsum = v.ws.dsum;
                 ea.wstore = need_gbar ? wslice(v, l) : nullptr;
@@ -680,20 +666,17 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
                 prof_end(g);
             }
         }
-        if (any_bonds) {   // bond term: its share of gbar; this layer's abar is kept for the bonds' own reverse step
+        if (any_bonds && need_gbar) {   // bond term: its share of gbar
             prof_begin(g, MLIP_PROF_BOND);
             for (int p = 0; p < P; ++p) {
                 SlabView &v = views[p];
                 BondGraph &BG = v.bonds;
                 if (BG.n > 0)
-                    MLIP_HIP(hipMemcpyAsync(BG.abar_keep.as<float>() + (size_t)l * (size_t)v.n_owned * F, v.ws.abar,
-                                            (size_t)v.n_owned * rowb, hipMemcpyDeviceToDevice, s));
-                if (BG.n > 0 && need_gbar)
                     bond_elem([&](auto zero) {
                         using BT = decltype(zero);
                         k_bond_gbar<F, BT><<<blocks_for(v.n_owned, 4), 256, 0, s>>>(
                             v.n_owned, BG.ptr.as<int64_t>(), BG.sender.as<int32_t>(), BG.mirror.as<int32_t>(),
-                            static_cast<const BT *>(wbslice(v, l)), v.ws.abar, v.ws.gbar);
+                            static_cast<const BT *>(wbslice(v, l)), abarslice(v, l), v.ws.gbar);
                     });
             }
             MLIP_HIP(hipGetLastError());
@@ -702,26 +685,25 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         if (need_gbar) {
             if (slabs) {
                 prof_begin(g, MLIP_PROF_GHOST);
-                PtrTable tab{};
-                for (int q = 0; q < P; ++q) tab.p[q] = views[q].ws.gbar;
-                for (int p0 = 0; p0 < P; p0 += kBatch) {   // the ghost rows' gradients ...
+                for (int p0 = 0; p0 < P; p0 += kBatch) {   // the ghost rows' gradients; the owners collect them below
                     const SmallBatch sb = small_batch(p0, U_GHOST, l);
                     if (sb.start[sb.n] > 0)
                         k_ghost_gbar<F><<<blocks_for(sb.start[sb.n], 4), 256, 0, s>>>(sb);
-                }
-                for (int p0 = 0; p0 < P; p0 += kBatch) {   // ... go back to their owners
-                    const SmallBatch sb = small_batch(p0, U_BORDER, l);
-                    if (sb.start[sb.n] > 0)
-                        k_border_add<<<blocks_for(sb.start[sb.n] * (F / 4), 256), 256, 0, s>>>(sb, F, tab, gidx);
                 }
                 MLIP_HIP(hipGetLastError());
                 prof_end(g);
             }
             prof_begin(g, MLIP_PROF_NODE);
-            MLIP_TRY((node_pass<F, OP_BWD_PROJ>(g, views, P, base + pk.Wmn, nullptr, nullptr, [&](SlabView &v, NodeArgs &na) {
-                na.n_rows = v.n_owned;
+            common.P[0] = base + pk.Wmn;
+            common.P[1] = layer_pack(l - 1) + pk.Wot;
+            common.P[2] = layer_pack(l - 1) + pk.Won;
+            ghost_tab([&](SlabView &v) { return v.ws.gbar; });
+            MLIP_TRY((node_pass<F, OP_BACK>(g, views, P, common, [&](SlabView &v, NodeArgs &na) {
                 na.X = v.ws.gbar;
+                na.X2 = aslice(v, l - 1);
                 na.Z = v.ws.hbar;
+                na.hbar = l > 1 ? v.ws.hbar : nullptr;   // (layer 0's step back is the last one)
+                na.Y = abarslice(v, l - 1);
             })));
             prof_end(g);
         }
@@ -766,18 +748,10 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         prof_end(g);
     }
 
-    // ---- forces
+    // ---- forces: the bonds' part first, the radial rows add theirs
     prof_begin(g, MLIP_PROF_FORCE);
     const double *pos = g->pos.as<double>();
-    for (int p0 = 0; p0 < P; p0 += kBatch) {
-        const SmallBatch sb = small_batch(p0, U_LOCAL, -1);
-        if (sb.start[sb.n] <= 0) continue;
-        if (L > 0)
-            k_force_rows<<<(unsigned)((sb.start[sb.n] + 15) / 16), 256, 0, s>>>(sb, pos, g->cell);
-        else
-            k_zero_floc<<<blocks_for(sb.start[sb.n], 256), 256, 0, s>>>(sb);
-    }
-    if (bw)
+    if (any_bonds && L > 0)
         for (int p = 0; p < P; ++p) {
             SlabView &v = views[p];
             if (v.bonds.n <= 0) continue;
@@ -790,7 +764,20 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
                     v.n_ghost, v.n_owned, v.row_ptr, v.mirror, BG.of_edge.as<int32_t>(), BG.dbond.as<float>(),
                     BG.rbar.as<float>(), BG.rhat.as<float>(), BG.d.as<float>(), v.ws.floc);
         }
-    {   // owned rows to the caller's arrays; a border atom also collects what its ghost rows gathered elsewhere
+    const bool direct = !slabs && L > 0;   // no ghost rows: the rows' sums are the forces
+    for (int p0 = 0; p0 < P; p0 += kBatch) {
+        const SmallBatch sb = small_batch(p0, U_LOCAL, -1);
+        EnergySum es = energy_sum;
+        if (p0 > 0) es.energy = nullptr;
+        const unsigned force_blocks = (unsigned)((sb.start[sb.n] + 15) / 16 + (es.energy ? 1 : 0));
+        if (L > 0 && force_blocks > 0)
+            k_force_rows<<<force_blocks, 256, 0, s>>>(sb, pos, g->cell, direct ? forces : nullptr, atom_energy, es);
+        else if (L == 0 && sb.start[sb.n] > 0)
+            k_zero_floc<<<blocks_for(sb.start[sb.n], 256), 256, 0, s>>>(sb);
+        MLIP_HIP(hipGetLastError());
+    }
+    if (L == 0) k_energy_total<<<1, 256, 0, s>>>(energy_sum);
+    if (!direct) {   // owned rows to the caller's arrays; a border atom also collects what its ghost rows gathered elsewhere
         PtrTable tab{};
         for (int q = 0; q < P; ++q) tab.p[q] = views[q].ws.floc;
         for (int p0 = 0; p0 < P; p0 += kBatch) {

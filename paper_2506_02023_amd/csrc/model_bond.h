@@ -378,9 +378,9 @@ __global__ void k_bond_force(int64_t N, const int64_t *__restrict__ bptr, const 
             fz += sgn * fmaf(dbond[q], z, (az - dot * z) * inv);
         }
     }
-    floc[3 * i] += fx;
-    floc[3 * i + 1] += fy;
-    floc[3 * i + 2] += fz;
+    floc[3 * i] = fx;   // (the radial part's rows add to it)
+    floc[3 * i + 1] = fy;
+    floc[3 * i + 2] = fz;
 }
 
 // ---- F x F products over the bonds, fused with what surrounds them

@@ -5,23 +5,238 @@
 
 // ---------------------------------------------------------------- node kernels
 
-enum { OP_PROJ = 0, OP_UPDATE = 1, OP_READOUT = 2, OP_BWD_UPDATE = 3, OP_BWD_PROJ = 4 };
+// One launch between two edge steps, over all atoms of all partitions: everything a row needs there is done while the row is
+// in registers.
+//   EMBED     h = Emb[z];  g_0 = h Wm_0
+//   UPDATE    h += SiLU(a Wo);  g of the next layer = h Wm
+//   TURN      the last layer's update, the readout and the first step back: h' = h + SiLU(q), q = a Wo;  x = h' Wr1;
+//             eps = SiLU(x) . wr2;  hbar = (wr2 SiLU'(x)) Wr1^T;  abar = (hbar SiLU'(q)) Wo^T
+//   BACK      hbar += gbar Wm^T;  q = a Wo of the layer before;  abar = (hbar SiLU'(q)) Wo^T
+//   READ      a model without layers: eps of h = Emb[z] only
+// A wavefront takes 32 rows.  Rows are loaded in the accumulator layout of the MFMAs (lane (c, h) holds features 8 i + 4 h + 0..3
+// of row c), which is the layout of a product's other operand as well, so the products chain in registers with no transposition
+// and no LDS but for the packed weights.  The next tile's rows are requested before this one's products.  Bound by memory at a
+// million atoms, where the step takes 1.7 ms in them (2.3 ms in 13 launches of one fp32 MFMA product each and separate
+// ghost copies, whose rows were read and written again in between), by the launches' own length below ten thousand:
+// 61 us a step at 4,000 atoms against 134.
+enum { OP_EMBED = 0, OP_UPDATE = 1, OP_TURN = 2, OP_BACK = 3, OP_READ = 4 };
 
 struct NodeArgs {      // one partition
     int64_t n_rows;
-    const float *X;    // GEMM input rows
-    float *Y;          // primary output rows
-    float *Z;          // secondary in/out rows (h for UPDATE, hbar for BWD_*)
-    float *eps;
+    const float *X;    // a (UPDATE, TURN), gbar (BACK); EMBED and READ take the atoms' rows of the embedding table
+    const float *X2;   // BACK: a of the layer before
+    float *Z;          // h (EMBED: out, UPDATE: in and out, TURN: in); hbar (BACK: in and out)
+    float *Y;          // g (EMBED, UPDATE); abar (TURN, BACK)
+    float *hbar;       // TURN: out (or null); BACK: Z is written back unless null
+    float *eps;        // TURN, READ
+    double *tile_sum;  // TURN, READ: energy of every 32-row tile of this launch
+    int64_t n_pure;    // border rows (n_pure .. n_rows) have ghost rows in other partitions
+    const int32_t *nodes;
 };
 
+// What a border atom's owner needs to reach the atom's ghost rows in the other partitions: the partitions that
+// hold it as a ghost (bits of needed_by) and its row in each of them (ghost_local, starting at gbase[atom]).
+struct GhostIndex {
+    const unsigned long long *needed_by;
+    const int32_t *gbase, *ghost_local;
+};
+struct PtrTable { float *p[kMaxSlabs]; };
+
 struct NodeBatch {     // up to kBatch partitions per launch, 32-row tiles numbered across them
-    const float *P1, *P2;
-    const float *wr2;
+    const float *P[4]; // packed weights, in the order of the products
+    const float *wr2, *emb;
+    const int32_t *species;
+    int32_t *clear;    // EMBED: words to clear (the edge kernels' work counters)
+    int n_clear;
     int n;
     int64_t tile_start[kBatch + 1];
     NodeArgs s[kBatch];
+    GhostIndex ghosts;
+    PtrTable tab;      // EMBED, UPDATE: the g arrays of all partitions; BACK: their gbar arrays (slab mode)
 };
+
+template <int OP> struct NodeOp {
+    static constexpr int NPACK = OP == OP_EMBED ? 1 : OP == OP_UPDATE ? 2 : OP == OP_TURN ? 4 : OP == OP_BACK ? 3 : 1;
+    static constexpr int NW = OP == OP_TURN ? 4 : 8;   // wavefronts per block (TURN needs more than 256 registers: 394 us against 520 with 8)
+};
+
+template <int F, int OP>
+__global__ void __launch_bounds__(NodeOp<OP>::NW * 64) k_node(NodeBatch B)
+{
+    constexpr int NB = Dims<F>::NB, NP = NodeOp<OP>::NPACK, NW = NodeOp<OP>::NW, PACK = Dims<F>::PACK3;
+    extern __shared__ float lds[];
+#pragma unroll
+    for (int q = 0; q < NP; ++q)
+        for (int i = threadIdx.x; i < PACK / 4; i += NW * 64)
+            reinterpret_cast<f32x4 *>(lds + q * PACK)[i] = reinterpret_cast<const f32x4 *>(B.P[q])[i];
+    if (OP == OP_EMBED)
+        for (int64_t i = (int64_t)blockIdx.x * (NW * 64) + threadIdx.x; i < B.n_clear; i += (int64_t)gridDim.x * (NW * 64)) B.clear[i] = 0;
+    __syncthreads();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int c32 = lane & 31, h4 = 4 * (lane >> 5);
+    auto pack = [&](int q) { return reinterpret_cast<const __bf16 *>(lds + q * PACK); };
+    auto load = [&](f32x16 (&v)[NB], const float *Y, int64_t row, bool ok) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                f32x4 x = {0.f, 0.f, 0.f, 0.f};
+                if (ok) x = *reinterpret_cast<const f32x4 *>(Y + row * F + 32 * b + 8 * a + h4);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[b][4 * a + c] = x[c];
+            }
+    };
+    auto store = [&](const f32x16 (&v)[NB], float *Y, int64_t row, bool ok) {
+        if (ok)
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int a = 0; a < 4; ++a)
+                    *reinterpret_cast<f32x4 *>(Y + row * F + 32 * b + 8 * a + h4) =
+                        f32x4{v[b][4 * a], v[b][4 * a + 1], v[b][4 * a + 2], v[b][4 * a + 3]};
+    };
+    const int64_t n_tiles = B.tile_start[B.n];
+    const int64_t stride = (int64_t)gridDim.x * NW;
+    int64_t ti = (int64_t)wave * gridDim.x + blockIdx.x;   // few tiles: one per block
+    f32x16 x[NB], z[NB];   // X and Z rows of the tile at hand
+    auto fetch = [&](int64_t t) {
+        const int part = batch_find(B.tile_start, B.n, t);
+        const NodeArgs &A = B.s[part];
+        const int64_t row = (t - B.tile_start[part]) * 32 + c32;
+        const bool ok = row < A.n_rows;
+        if (OP == OP_EMBED || OP == OP_READ) {
+            const float *e = B.emb;   // the caller's table: no alignment assumed
+            if (ok) e += (int64_t)B.species[A.nodes ? A.nodes[row] : row] * F;
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int a = 0; a < 4; ++a)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) x[b][4 * a + c] = e[32 * b + 8 * a + h4 + c];
+            return;
+        }
+        load(x, A.X, row, ok);
+        if (OP == OP_UPDATE || OP == OP_TURN || OP == OP_BACK) load(z, A.Z, row, ok);
+    };
+    if (ti < n_tiles) fetch(ti);
+    for (; ti < n_tiles; ti += stride) {
+        const int part = batch_find(B.tile_start, B.n, ti);
+        const NodeArgs &A = B.s[part];
+        const int64_t row = (ti - B.tile_start[part]) * 32 + c32;
+        const bool ok = row < A.n_rows;
+        const bool border = ok && row >= A.n_pure;
+        f32x16 y[NB];
+        // rows of g also go to the atom's ghost rows in the other partitions (the border-node transfer)
+        auto store_g = [&](const f32x16 (&v)[NB]) {
+            store(v, A.Y, row, ok);
+            if (border) {
+                const int32_t u = A.nodes[row];
+                unsigned long long nb = B.ghosts.needed_by[u];
+                const int32_t *loc = B.ghosts.ghost_local + B.ghosts.gbase[u];
+                while (nb) {
+                    const int qq = __builtin_ctzll(nb);
+                    nb &= nb - 1;
+                    store(v, B.tab.p[qq], *loc++, true);
+                }
+            }
+        };
+        if (OP == OP_EMBED) {
+            store(x, A.Z, row, ok);
+            gemm_rl_bf16x3<F>(pack(0), x, y, lane);
+            if (ti + stride < n_tiles) fetch(ti + stride);
+            store_g(y);
+        } else if (OP == OP_UPDATE) {
+            f32x16 hn[NB];
+            gemm_rl_bf16x3<F>(pack(0), x, y, lane);
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) hn[b][r] = z[b][r] + y[b][r] * sigmoidf_fast(y[b][r]);
+            if (ti + stride < n_tiles) fetch(ti + stride);   // in flight during the second product
+            store(hn, A.Z, row, ok);
+            gemm_rl_bf16x3<F>(pack(1), hn, y, lane);
+            store_g(y);
+        } else if (OP == OP_TURN || OP == OP_READ) {
+            f32x16 q[NB];
+            if (OP == OP_TURN) {
+                gemm_rl_bf16x3<F>(pack(0), x, q, lane);
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const float sg = sigmoidf_fast(q[b][r]);
+                        z[b][r] = z[b][r] + q[b][r] * sg;
+                        q[b][r] = sg * (1.0f + q[b][r] * (1.0f - sg));   // SiLU'(q)
+                    }
+                gemm_rl_bf16x3<F>(pack(1), z, y, lane);
+            } else {
+                gemm_rl_bf16x3<F>(pack(0), x, y, lane);
+            }
+            if (ti + stride < n_tiles) fetch(ti + stride);
+            float part_eps = 0.f;
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int a = 0; a < 4; ++a)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const float wv = B.wr2[32 * b + 8 * a + h4 + c], v = y[b][4 * a + c];
+                        const float sg = sigmoidf_fast(v);
+                        part_eps += v * sg * wv;
+                        y[b][4 * a + c] = wv * sg * (1.0f + v * (1.0f - sg));
+                    }
+            part_eps += __shfl_xor(part_eps, 32, 64);
+            if (ok && h4 == 0) A.eps[row] = part_eps;
+            double e = ok ? (double)part_eps : 0.0;   // the tile's energy, in a fixed order
+#pragma unroll
+            for (int off = 16; off > 0; off >>= 1) e += __shfl_xor(e, off, 64);
+            if (lane == 0) A.tile_sum[ti - B.tile_start[part]] = e;
+            if (OP == OP_TURN) {
+                f32x16 hb[NB];
+                gemm_rl_bf16x3<F>(pack(2), y, hb, lane);
+                if (A.hbar) store(hb, A.hbar, row, ok);
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) hb[b][r] *= q[b][r];
+                gemm_rl_bf16x3<F>(pack(3), hb, y, lane);
+                store(y, A.Y, row, ok);
+            }
+        } else {   // OP_BACK
+            f32x16 a2[NB];
+            load(a2, A.X2, row, ok);
+            if (border) {   // what the atom's ghost rows gathered comes back, in ascending partition order
+                const int32_t u = A.nodes[row];
+                unsigned long long nb = B.ghosts.needed_by[u];
+                const int32_t *loc = B.ghosts.ghost_local + B.ghosts.gbase[u];
+                while (nb) {
+                    const int qq = __builtin_ctzll(nb);
+                    nb &= nb - 1;
+                    f32x16 gq[NB];
+                    load(gq, B.tab.p[qq], *loc++, true);
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) x[b] += gq[b];
+                }
+            }
+            f32x16 hb[NB];
+            gemm_rl_bf16x3<F>(pack(0), x, hb, lane);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) hb[b] += z[b];
+            if (ti + stride < n_tiles) fetch(ti + stride);
+            if (A.hbar) store(hb, A.hbar, row, ok);
+            gemm_rl_bf16x3<F>(pack(1), a2, y, lane);
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const float sg = sigmoidf_fast(y[b][r]);
+                    hb[b][r] *= sg * (1.0f + y[b][r] * (1.0f - sg));
+                }
+            gemm_rl_bf16x3<F>(pack(2), hb, y, lane);
+            store(y, A.Y, row, ok);
+        }
+    }
+}
 
 // A 32-row tile of X travels global memory -> registers -> LDS in two halves, so that the loads of the next
 // tile can be in flight while the current one is multiplied.
@@ -54,137 +269,6 @@ template <int F, typename T_> __device__ inline void stash_tile(const TileRegs<F
     for (int r = 0; r < 32; r += RPI) *reinterpret_cast<f32x4 *>(tile + (r + rr) * FS + cc) = Elem<T_>::widen4(T.v[r / RPI]);
 }
 
-template <int F, int OP>
-__global__ void __launch_bounds__(256) k_node(NodeBatch B)
-{
-    using D = Dims<F>;
-    constexpr bool TWO = (OP == OP_READOUT || OP == OP_BWD_UPDATE);
-    extern __shared__ float lds[];
-    float *P1 = lds;
-    float *P2 = P1 + D::PACKF;
-    float *tiles = P2 + (TWO ? D::PACKF : 0);
-    for (int i = threadIdx.x; i < D::PACKF; i += 256) {
-        P1[i] = B.P1[i];
-        if (TWO) P2[i] = B.P2[i];
-    }
-    __syncthreads();
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int c32 = lane & 31, h = lane >> 5;
-    float *tile = tiles + wave * D::TILE;
-    const int64_t n_tiles = B.tile_start[B.n];
-    const int64_t stride = (int64_t)gridDim.x * 4;
-    TileRegs<F> pre;
-    auto fetch = [&](int64_t ti) {
-        const int part = batch_find(B.tile_start, B.n, ti);
-        fetch_tile<F>(pre, B.s[part].X, (ti - B.tile_start[part]) * 32, B.s[part].n_rows, lane);
-    };
-    int64_t ti = (int64_t)blockIdx.x * 4 + wave;
-    if (ti < n_tiles) fetch(ti);
-    for (; ti < n_tiles; ti += stride) {
-        const int part = batch_find(B.tile_start, B.n, ti);
-        const NodeArgs A = B.s[part];
-        const int64_t row0 = (ti - B.tile_start[part]) * 32;
-        const int64_t row = row0 + c32;
-        const bool ok = row < A.n_rows;
-        stash_tile<F>(pre, tile, lane);
-        wave_lds_fence();
-        // rows of Z this tile combines with its product, requested before the product as well
-        constexpr bool READS_Z = (OP == OP_UPDATE || OP == OP_BWD_PROJ || OP == OP_BWD_UPDATE);
-        f32x4 zv[D::NB][4];
-        if (READS_Z)
-#pragma unroll
-            for (int b = 0; b < D::NB; ++b)
-#pragma unroll
-                for (int a = 0; a < 4; ++a) {
-                    zv[b][a] = f32x4{0.f, 0.f, 0.f, 0.f};
-                    if (ok) zv[b][a] = *reinterpret_cast<const f32x4 *>(A.Z + row * F + 32 * b + 8 * a + 4 * h);
-                }
-        if (ti + stride < n_tiles) fetch(ti + stride);   // in flight during this tile's products
-        f32x16 acc[D::NB];
-        gemm_lds<F>(P1, tile, acc, lane);
-        wave_lds_fence();
-        if (OP == OP_PROJ) {
-            if (ok)
-#pragma unroll
-                for (int b = 0; b < D::NB; ++b)
-#pragma unroll
-                    for (int a = 0; a < 4; ++a) {
-                        f32x4 v = {acc[b][4 * a], acc[b][4 * a + 1], acc[b][4 * a + 2], acc[b][4 * a + 3]};
-                        *reinterpret_cast<f32x4 *>(A.Y + row * F + 32 * b + 8 * a + 4 * h) = v;
-                    }
-        } else if (OP == OP_UPDATE || OP == OP_BWD_PROJ) {
-            // UPDATE:   Z = h,    h    += SiLU(a Wo)
-            // BWD_PROJ: Z = hbar, hbar += gbar Wm^T
-            if (ok)
-#pragma unroll
-                for (int b = 0; b < D::NB; ++b)
-#pragma unroll
-                    for (int a = 0; a < 4; ++a) {
-                        float *zp = A.Z + row * F + 32 * b + 8 * a + 4 * h;
-                        f32x4 v = zv[b][a];
-#pragma unroll
-                        for (int c = 0; c < 4; ++c) {
-                            const float q = acc[b][4 * a + c];
-                            v[c] += (OP == OP_UPDATE) ? q * sigmoidf_fast(q) : q;
-                        }
-                        *reinterpret_cast<f32x4 *>(zp) = v;
-                    }
-        } else if (OP == OP_READOUT) {
-            // eps = SiLU(h Wr1) . wr2 ;  hbar = (wr2 * SiLU'(h Wr1)) Wr1^T
-            float part = 0.f;
-#pragma unroll
-            for (int b = 0; b < D::NB; ++b)
-#pragma unroll
-                for (int a = 0; a < 4; ++a) {
-                    const f32x4 wv = *reinterpret_cast<const f32x4 *>(B.wr2 + 32 * b + 8 * a + 4 * h);
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const float x = acc[b][4 * a + c];
-                        const float sg = sigmoidf_fast(x);
-                        part += x * sg * wv[c];
-                        acc[b][4 * a + c] = wv[c] * sg * (1.0f + x * (1.0f - sg));
-                    }
-                }
-            part += __shfl_xor(part, 32, 64);
-            if (ok && h == 0) A.eps[row] = part;
-            f32x16 hb[D::NB];
-            gemm_regs<F>(P2, acc, hb, lane);
-            if (ok)
-#pragma unroll
-                for (int b = 0; b < D::NB; ++b)
-#pragma unroll
-                    for (int a = 0; a < 4; ++a) {
-                        f32x4 v = {hb[b][4 * a], hb[b][4 * a + 1], hb[b][4 * a + 2], hb[b][4 * a + 3]};
-                        *reinterpret_cast<f32x4 *>(A.Y + row * F + 32 * b + 8 * a + 4 * h) = v;
-                    }
-        } else if (OP == OP_BWD_UPDATE) {
-            // q = a Wo ; qbar = hbar * SiLU'(q) ; abar = qbar Wo^T       (X = a, Z = hbar, Y = abar)
-#pragma unroll
-            for (int b = 0; b < D::NB; ++b)
-#pragma unroll
-                for (int a = 0; a < 4; ++a) {
-                    const f32x4 hv = zv[b][a];
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const float x = acc[b][4 * a + c];
-                        const float sg = sigmoidf_fast(x);
-                        acc[b][4 * a + c] = hv[c] * sg * (1.0f + x * (1.0f - sg));
-                    }
-                }
-            f32x16 ab[D::NB];
-            gemm_regs<F>(P2, acc, ab, lane);
-            if (ok)
-#pragma unroll
-                for (int b = 0; b < D::NB; ++b)
-#pragma unroll
-                    for (int a = 0; a < 4; ++a) {
-                        f32x4 v = {ab[b][4 * a], ab[b][4 * a + 1], ab[b][4 * a + 2], ab[b][4 * a + 3]};
-                        *reinterpret_cast<f32x4 *>(A.Y + row * F + 32 * b + 8 * a + 4 * h) = v;
-                    }
-        }
-    }
-}
-
 // ---------------------------------------------------------------- small kernels
 //
 // Embedding, ghost transfers, force assembly and the energy partial sums run over all partitions in one launch
@@ -208,7 +292,6 @@ struct SmallArgs {   // one partition
     const int32_t *bond_of_edge;   // three-body variant (or nullptr)
     const void *wb;                // bond filter rows of the layer: fp32, or bf16 if wb_bf16
     int wb_bf16;
-    double *energy_part;
 };
 
 struct SmallBatch {
@@ -218,46 +301,7 @@ struct SmallBatch {
     SmallArgs s[kBatch];
 };
 
-struct PtrTable { float *p[kMaxSlabs]; };
-
-// What a border atom's owner needs to collect the atom's ghost rows from the other partitions: the partitions that
-// hold it as a ghost (bits of needed_by) and its row in each of them (ghost_local, starting at gbase[atom]).
-struct GhostIndex {
-    const unsigned long long *needed_by;
-    const int32_t *gbase, *ghost_local;
-};
-
-__global__ void k_embed(SmallBatch B, int F, const int32_t *__restrict__ species, const float *__restrict__ emb)
-{
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;   // one float4 per thread
-    const int F4 = F / 4;
-    const int64_t row = idx / F4;
-    if (row >= B.start[B.n]) return;
-    const int part = batch_find(B.start, B.n, row);
-    const SmallArgs &A = B.s[part];
-    const int64_t r = row - B.start[part];
-    const int c = (int)(idx % F4) * 4;
-    const int64_t u = A.nodes ? A.nodes[r] : r;
-    const float *e = emb + (int64_t)species[u] * F + c;   // the caller's table: no alignment assumed
-    *reinterpret_cast<f32x4 *>(A.h + r * F + c) = f32x4{e[0], e[1], e[2], e[3]};
-}
-
-// ghost rows of every partition's g  <-  the owners' rows (tab: the g arrays of all partitions)
-__global__ void k_ghost_copy(SmallBatch B, int F, PtrTable tab)
-{
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int F4 = F / 4;
-    const int64_t gk = idx / F4;
-    if (gk >= B.start[B.n]) return;
-    const int part = batch_find(B.start, B.n, gk);
-    const SmallArgs &A = B.s[part];
-    const int64_t k = gk - B.start[part];
-    const int c = (int)(idx % F4) * 4;
-    const float *sp = tab.p[A.ghost_owner[k]] + (int64_t)A.ghost_src[k] * F + c;
-    *reinterpret_cast<f32x4 *>(A.g + (A.n_owned + k) * F + c) = *reinterpret_cast<const f32x4 *>(sp);
-}
-
-// ghost rows of abar are zero (ghost rows carry no dE/da)
+// ghost rows of abar are zero (ghost rows carry no dE/da); blockIdx.y: the layer, where every layer's abar is kept
 __global__ void k_zero_ghost_rows(SmallBatch B, int F)
 {
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -267,7 +311,7 @@ __global__ void k_zero_ghost_rows(SmallBatch B, int F)
     const int part = batch_find(B.start, B.n, gk);
     const SmallArgs &A = B.s[part];
     const int64_t k = gk - B.start[part];
-    *reinterpret_cast<f32x4 *>(A.abar + (A.n_owned + k) * F + (idx % F4) * 4) = f32x4{0.f, 0.f, 0.f, 0.f};
+    *reinterpret_cast<f32x4 *>(A.abar + ((int64_t)blockIdx.y * A.n_local + A.n_owned + k) * F + (idx % F4) * 4) = f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
 // Second pass of the reverse edge step: the lower edges' terms of the row sums, with the filter values w read from the
@@ -353,32 +397,6 @@ __global__ void __launch_bounds__(256) k_ghost_gbar(SmallBatch B)
     if (F == 64 || lane < F) A.gbar[r * F + f] = acc;
 }
 
-// Ghost-row gradients go back to the owners (the reverse of the border-node transfer): every border row adds the
-// rows its atom has as a ghost in the other partitions, in ascending partition order.  Gathered from the owner's
-// side, so one launch covers all partitions without two writers on a row (tab: the gbar arrays of all partitions).
-__global__ void k_border_add(SmallBatch B, int F, PtrTable tab, GhostIndex G)
-{
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int F4 = F / 4;
-    const int64_t bk = idx / F4;
-    if (bk >= B.start[B.n]) return;
-    const int part = batch_find(B.start, B.n, bk);
-    const SmallArgs &A = B.s[part];
-    const int64_t r = A.n_pure + (bk - B.start[part]);
-    const int c = (int)(idx % F4) * 4;
-    const int32_t u = A.nodes[r];
-    unsigned long long nb = G.needed_by[u];
-    const int32_t *loc = G.ghost_local + G.gbase[u];
-    float *dp = A.gbar + r * F + c;
-    f32x4 v = *reinterpret_cast<const f32x4 *>(dp);
-    while (nb) {
-        const int qq = __builtin_ctzll(nb);
-        nb &= nb - 1;
-        v += *reinterpret_cast<const f32x4 *>(tab.p[qq] + (int64_t)(*loc++) * F + c);
-    }
-    *reinterpret_cast<f32x4 *>(dp) = v;
-}
-
 // Three-body variant, ghost rows: a ghost atom i is the sender of bonds (j <- i) held by this partition; each pulls
 // on it with +dE/dDelta.  Gathered over the ghost's sub-row through the reverse edges.
 __global__ void k_bond_force_ghost(int64_t n_ghost, int64_t n_owned, const int64_t *__restrict__ row_ptr,
@@ -401,9 +419,9 @@ __global__ void k_bond_force_ghost(int64_t n_ghost, int64_t n_owned, const int64
         fy -= fmaf(dbond[q], y, (ay - dot * y) * inv);
         fz -= fmaf(dbond[q], z, (az - dot * z) * inv);
     }
-    floc[3 * r] += fx;
-    floc[3 * r + 1] += fy;
-    floc[3 * r + 2] += fz;
+    floc[3 * r] = fx;   // (the radial part's rows add to it)
+    floc[3 * r + 1] = fy;
+    floc[3 * r + 2] = fz;
 }
 
 __device__ inline void unpack_shift(uint32_t p, int &a, int &b, int &c)
@@ -413,10 +431,32 @@ __device__ inline void unpack_shift(uint32_t p, int &a, int &b, int &c)
     c = (int)(p & 1023u) - 512;
 }
 
-// F_loc[r] = sum_{e in local row r} dsum_e * rhat_e, edge vectors from fp64 positions; 16 lanes per row, 16 rows per block
-__global__ void __launch_bounds__(256)
-k_force_rows(SmallBatch B, const double *__restrict__ pos, CellParams cp)
+// total energy: the tiles' fp64 sums in a fixed order, by one block
+__device__ inline void energy_total(int64_t n, const double *__restrict__ part, double *__restrict__ energy)
 {
+    __shared__ double sh[4];
+    double s = 0;
+    for (int64_t k = threadIdx.x; k < n; k += 256) s += part[k];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) *energy = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+}
+
+struct EnergySum { int64_t n; const double *part; double *energy; };   // energy == nullptr: not in this launch
+
+// F_loc[r] = sum_{e in local row r} dsum_e * rhat_e (plus the bond part's F_loc, if any), edge vectors from fp64 positions;
+// 16 lanes per row, 16 rows per block.  Without ghost rows a row's sum is the atom's force and goes to the caller's arrays
+// (forces != nullptr), the atom's energy with it.  The block behind those of the rows adds up the energy.
+__global__ void __launch_bounds__(256)
+k_force_rows(SmallBatch B, const double *__restrict__ pos, CellParams cp, float *__restrict__ forces,
+             float *__restrict__ atom_energy, EnergySum E)
+{
+    if (E.energy && blockIdx.x == gridDim.x - 1) {
+        energy_total(E.n, E.part, E.energy);
+        return;
+    }
     const int64_t gr = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
     if (gr >= B.start[B.n]) return;   // whole groups of 16 lanes leave together; the shuffles below stay inside a group
     const int part = batch_find(B.start, B.n, gr);
@@ -449,9 +489,18 @@ k_force_rows(SmallBatch B, const double *__restrict__ pos, CellParams cp)
         fz += __shfl_xor(fz, off, 64);
     }
     if ((threadIdx.x & 15) == 0) {
-        A.floc[3 * r] = (float)fx;
-        A.floc[3 * r + 1] = (float)fy;
-        A.floc[3 * r + 2] = (float)fz;
+        float *fl = A.floc + 3 * r;
+        float x = (float)fx, y = (float)fy, z = (float)fz;
+        if (A.bond_of_edge) {   // three-body variant: the bonds' part is there already
+            x += fl[0];
+            y += fl[1];
+            z += fl[2];
+        }
+        float *to = forces ? forces + 3 * ig : fl;
+        to[0] = x;
+        to[1] = y;
+        to[2] = z;
+        if (forces && atom_energy) atom_energy[ig] = A.eps[r];
     }
 }
 
@@ -498,35 +547,6 @@ __global__ void k_store_owned(SmallBatch B, PtrTable tab, GhostIndex G, float *_
     if (atom_energy) atom_energy[u] = A.eps[r];
 }
 
-// fixed-shape fp64 reduction of the per-atom energies: 1024-element blocks, then one block over the partials
-__global__ void __launch_bounds__(256) k_energy_partial(SmallBatch B, double *__restrict__ part)
-{
-    __shared__ double sh[4];
-    // start[] counts 1024-element blocks here; the partial sums of all partitions sit one after another in `part`
-    const int q = batch_find(B.start, B.n, (int64_t)blockIdx.x);
-    const int64_t n = B.s[q].n_owned;
-    const float *eps = B.s[q].eps;
-    const int64_t base = ((int64_t)blockIdx.x - B.start[q]) * 1024;
-    double s = 0;
-    for (int k = threadIdx.x; k < 1024; k += 256)
-        if (base + k < n) s += (double)eps[base + k];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) part[blockIdx.x] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
-}
-
-__global__ void __launch_bounds__(256) k_energy_final(int64_t n, const double *__restrict__ part, double *__restrict__ energy)
-{
-    __shared__ double sh[4];
-    double s = 0;
-    for (int64_t k = threadIdx.x; k < n; k += 256) s += part[k];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) *energy = (sh[0] + sh[1]) + (sh[2] + sh[3]);
-}
+__global__ void __launch_bounds__(256) k_energy_total(EnergySum E) { energy_total(E.n, E.part, E.energy); }
 
 #endif  // MLIP_MODEL_NODE_H
