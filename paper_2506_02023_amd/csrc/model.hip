@@ -114,13 +114,12 @@ template <int F, int OP> int launch_node(mlip_graph *g, NodeBatch &b)
 template <int F, int STAGE, int PREC> int launch_bond_mlp(mlip_graph *g, const BondArgs &a)
 {
     constexpr int NW = BondStage<STAGE>::NW;
-    constexpr size_t lds = sizeof(float) * (BondStage<STAGE>::NPACK * Dims<F>::PACKF + NW * Dims<F>::TILE);
+    constexpr size_t lds = sizeof(float) * (BondStage<STAGE>::NPACK * pack_floats<F>(PREC) + NW * BondStage<STAGE>::TILE);
     int slot = 0;
     MLIP_TRY(configure_kernel(g, reinterpret_cast<const void *>(&k_bond_mlp<F, STAGE, PREC>), lds, &slot));
     if (a.n <= 0) return MLIP_OK;
-    const int64_t n_tiles = (a.n + 31) / 32;
-    // each block keeps its operand packs in LDS, so let it walk several tiles
-    const unsigned blocks = (unsigned)std::min<int64_t>((n_tiles + NW - 1) / NW, 8192 / NW);
+    // every block keeps its operand packs in LDS and walks several tiles
+    const unsigned blocks = (unsigned)std::min<int64_t>((a.n + 31) / 32, BondStage<STAGE>::BLOCKS);
     k_bond_mlp<F, STAGE, PREC><<<blocks, NW * 64, lds, g->stream>>>(a);
     MLIP_HIP(hipGetLastError());
     return MLIP_OK;
@@ -309,9 +308,13 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             a.l_row_ptr = v.pairs.l_row_ptr;
             a.l_senders = v.pairs.l_senders;
             a.l_slot = v.pairs.l_slot;
-            a.bond_of_edge = (bw && v.bonds.n > 0) ? v.bonds.of_edge.as<int32_t>() : nullptr;
+            const bool bonds = bw && v.bonds.n > 0;
+            a.b_ptr = bonds ? v.bonds.ptr.as<int64_t>() : nullptr;
+            a.b_sender = bonds ? v.bonds.sender.as<int32_t>() : nullptr;
+            a.b_mirror = bonds ? v.bonds.mirror.as<int32_t>() : nullptr;
+            a.bond_of_edge = bonds ? v.bonds.of_edge.as<int32_t>() : nullptr;
             a.wb_bf16 = (prec == kPrecBf16);
-            a.wb = (bw && v.bonds.n > 0 && layer >= 0)
+            a.wb = (bonds && layer >= 0)
                        ? static_cast<char *>(v.bonds.wb.p) + (size_t)layer * (size_t)std::max<int64_t>(v.bonds.n, 1) * F *
                                                                    (a.wb_bf16 ? sizeof(__bf16) : sizeof(float))
                        : nullptr;
@@ -340,7 +343,6 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
     const bool repack = scratch != nullptr || !g->packed_w_valid || std::memcmp(&g->packed_w, w, sizeof(*w)) != 0;
     g->packed_w_valid = false;
     const int w2_kind = prec == kPrecBf16 ? PACK_FF_BF16 : prec == kPrecF16x3 ? PACK_FF_F16X2 : PACK_FF_BF16X3;
-    const int ff_kind = prec == kPrecBf16 ? PACK_FF_BF16 : prec == kPrecF16x3 ? PACK_FF_F16X2 : PACK_FF;   // the filter MLP's W2
     if (repack) {
         PackBatch pb{};
         pb.F = F;
@@ -371,7 +373,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
     // ---- three-body variant: bond lists, bond embedding, triplet update, bond terms of the layers' filters.
     // All bonds and triplets of an owned centre are local to its partition, so this part needs no transfer.
     float *bpk = nullptr;        // packed F x F operands of the bond part
-    const size_t ffp = (size_t)F * F;
+    const size_t ffp = (size_t)Dims<F>::PACK3;   // floats of an operand slot
     // operand slots: 0 Wta (y = x W), 1 Wtb, 2 Wt2, 3 Wta^T, 4 Wtb^T, 5 Wt2^T, 6 + l Wb_l, 6 + L + l Wb_l^T; after them We0
     // packed for the K = 8 product
     BasisParams bpb = bp;
@@ -437,14 +439,15 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         MLIP_TRY(g->bond_wpack.ensure(((size_t)(6 + 2 * L) * ffp + Dims<F>::PACK1) * sizeof(float)));
         bpk = g->bond_wpack.as<float>();
         prof_begin(g, MLIP_PROF_BOND);
-        const float *Wta = bw->Wt1, *Wtb = bw->Wt1 + ffp, *Wtc = bw->Wt1 + 2 * ffp;
+        const size_t ff = (size_t)F * F;   // floats of a weight matrix
+        const float *Wta = bw->Wt1, *Wtb = bw->Wt1 + ff, *Wtc = bw->Wt1 + 2 * ff;
         const bool repack_b = !g->packed_bw_valid || std::memcmp(&g->packed_bw, bw, sizeof(*bw)) != 0 ||
                               std::memcmp(&g->packed_bw_w, w, sizeof(*w)) != 0;
         g->packed_bw_valid = false;
         if (repack_b) {   // the bond MLPs' F x F products follow the filter MLP's precision mode
             PackBatch pb{};
             pb.F = F;
-            auto pack_bond = [&](const float *Wsrc, int trans, int slot) { pb.add(Wsrc, bpk + (size_t)slot * ffp, ff_kind, trans, 1.0f); };
+            auto pack_bond = [&](const float *Wsrc, int trans, int slot) { pb.add(Wsrc, bpk + (size_t)slot * ffp, w2_kind, trans, 1.0f); };
             pack_bond(Wta, 1, 0);
             pack_bond(Wtb, 1, 1);
             pack_bond(bw->Wt2, 1, 2);
@@ -452,8 +455,8 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             pack_bond(Wtb, 0, 4);
             pack_bond(bw->Wt2, 0, 5);
             for (int l = 0; l < L; ++l) {
-                pack_bond(bw->Wb + l * ffp, 1, 6 + l);
-                pack_bond(bw->Wb + l * ffp, 0, 6 + L + l);
+                pack_bond(bw->Wb + l * ff, 1, 6 + l);
+                pack_bond(bw->Wb + l * ff, 0, 6 + L + l);
             }
             pb.add(bw->We0, bpk + (size_t)(6 + 2 * L) * ffp, PACK_W1, 0, 1.0f);
             k_pack<<<dim3(blocks_for((int64_t)F * F, 256), pb.n), 256, 0, s>>>(pb);
@@ -666,22 +669,6 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
                 prof_end(g);
             }
         }
-        if (any_bonds && need_gbar) {   // bond term: its share of gbar
-            prof_begin(g, MLIP_PROF_BOND);
-            for (int p = 0; p < P; ++p) {
-                SlabView &v = views[p];
-                BondGraph &BG = v.bonds;
-                if (BG.n > 0)
-                    bond_elem([&](auto zero) {
-                        using BT = decltype(zero);
-                        k_bond_gbar<F, BT><<<blocks_for(v.n_owned, 4), 256, 0, s>>>(
-                            v.n_owned, BG.ptr.as<int64_t>(), BG.sender.as<int32_t>(), BG.mirror.as<int32_t>(),
-                            static_cast<const BT *>(wbslice(v, l)), abarslice(v, l), v.ws.gbar);
-                    });
-            }
-            MLIP_HIP(hipGetLastError());
-            prof_end(g);
-        }
         if (need_gbar) {
             if (slabs) {
                 prof_begin(g, MLIP_PROF_GHOST);
@@ -712,7 +699,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
     // ---- reverse of the bond update: e1 = e0 + u SiLU(m), m = S Wt2, S = triplet sum, e0 = bbond(d) We0
     if (any_bonds) {
         prof_begin(g, MLIP_PROF_BOND);
-        const float *Wtc = bw->Wt1 + 2 * ffp;
+        const float *Wtc = bw->Wt1 + 2 * (size_t)F * F;
         for (int p = 0; p < P; ++p) {   // e1bar = sum_l dE/dwb_l Wb_l^T, ubar, Sbar = (e1bar u SiLU'(m)) Wt2^T
             BondArgs a = bond_args(views[p]);
             a.W[0] = bpk + 5 * ffp;
@@ -756,11 +743,11 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             SlabView &v = views[p];
             if (v.bonds.n <= 0) continue;
             BondGraph &BG = v.bonds;
-            k_bond_force<<<blocks_for(v.n_owned, 128), 128, 0, s>>>(v.n_owned, BG.ptr.as<int64_t>(), BG.mirror.as<int32_t>(),
+            k_bond_force<<<blocks_for(v.n_owned, 16), 256, 0, s>>>(v.n_owned, BG.ptr.as<int64_t>(), BG.mirror.as<int32_t>(),
                                                                     BG.dbond.as<float>(), BG.rbar.as<float>(),
                                                                     BG.rhat.as<float>(), BG.d.as<float>(), v.ws.floc);
             if (v.n_ghost > 0)
-                k_bond_force_ghost<<<blocks_for(v.n_ghost, 128), 128, 0, s>>>(
+                k_bond_force_ghost<<<blocks_for(v.n_ghost, 16), 256, 0, s>>>(
                     v.n_ghost, v.n_owned, v.row_ptr, v.mirror, BG.of_edge.as<int32_t>(), BG.dbond.as<float>(),
                     BG.rbar.as<float>(), BG.rhat.as<float>(), BG.d.as<float>(), v.ws.floc);
         }

@@ -127,7 +127,8 @@ k_triplet_fwd(int64_t N, const int64_t *__restrict__ bptr, const float *__restri
     }
 }
 
-// bond term of a layer's aggregation: a[i] += sum over the bonds b = (i <- j) of wb[b] * g[j]
+// bond term of a layer's aggregation: a[i] += sum over the bonds b = (i <- j) of wb[b] * g[j].  One wavefront per centre, lane =
+// feature, 16 bonds' rows in flight together; 215 us per layer at 2.4 M bonds (622 MB of bond rows).  The share of gbar, in which the reverse bonds' filters appear, is taken by k_edge_lower.
 template <int F, typename BT>
 __global__ void __launch_bounds__(256)
 k_bond_aggregate(int64_t N, const int64_t *__restrict__ bptr, const int32_t *__restrict__ sender,
@@ -137,30 +138,25 @@ k_bond_aggregate(int64_t N, const int64_t *__restrict__ bptr, const int32_t *__r
     const int64_t i = (int64_t)blockIdx.x * 4 + wave;
     if (i >= N) return;
     const int f = lane & (F - 1);
+    const int64_t b0 = __builtin_amdgcn_readfirstlane((int32_t)bptr[i]), b1 = __builtin_amdgcn_readfirstlane((int32_t)bptr[i + 1]);
+    const float before = a[i * F + f];   // (requested with the indices)
     float acc = 0.f;
-    for (int64_t b = bptr[i]; b < bptr[i + 1]; ++b) acc = fmaf(Elem<BT>::load(wb + b * F + f), g[(int64_t)sender[b] * F + f], acc);
-    if (F == 64 || lane < F) a[i * F + f] += acc;
-}
-
-// reverse of the bond term, the share of gbar: gbar[i] += sum_b wb[mirror(b)] * abar[j]
-// (the reverse bond (j <- i) is the one whose filter multiplies g_i in row j)
-template <int F, typename BT>
-__global__ void __launch_bounds__(256)
-k_bond_gbar(int64_t N, const int64_t *__restrict__ bptr, const int32_t *__restrict__ sender,
-            const int32_t *__restrict__ bmirror, const BT *__restrict__ wb, const float *__restrict__ abar,
-            float *gbar)
-{
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int64_t i = (int64_t)blockIdx.x * 4 + wave;
-    if (i >= N) return;
-    const int f = lane & (F - 1);
-    float acc = 0.f;
-    for (int64_t b = bptr[i]; b < bptr[i + 1]; ++b) {
-        const int64_t j = sender[b];
-        const int64_t bm = bmirror[b];   // -1: the sender is a ghost row (abar_j = 0 here, its owner adds that term)
-        if (bm >= 0) acc = fmaf(Elem<BT>::load(wb + bm * F + f), abar[j * F + f], acc);
+    for (int64_t bb = b0; bb < b1; bb += 16) {
+        const int n = (int)min((int64_t)16, b1 - bb);
+        const int32_t jl = sender[min(bb + (lane & 15), b1 - 1)];
+        float wv[16], gv[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            wv[k] = gv[k] = 0.f;
+            if (k < n) {
+                wv[k] = Elem<BT>::load(wb + (bb + k) * F + f);
+                gv[k] = g[(int64_t)__builtin_amdgcn_readlane(jl, k) * F + f];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 16; ++k) acc = fmaf(wv[k], gv[k], acc);
     }
-    if (F == 64 || lane < F) gbar[i * F + f] += acc;
+    if (F == 64 || lane < F) a[i * F + f] = before + acc;
 }
 
 // sum over the 64 lanes of a wavefront on the data-parallel-primitive path (no LDS); the total is returned
@@ -355,45 +351,100 @@ k_triplet_bwd(int64_t N, const int64_t *__restrict__ bptr, const float *__restri
 }
 
 // Forces of the bond part.  dE/dDelta_b = dbond rhat + (rbar - (rbar . rhat) rhat) / d for the bond vector
-// Delta_b = r_j + S C - r_i; it pulls on j with + and on i with -.  Gathered per centre: the bonds in which i
-// is the sender are the reverse bonds of its own.   F_i += sum_b (gDelta_b - gDelta_mirror(b))
-__global__ void k_bond_force(int64_t N, const int64_t *__restrict__ bptr, const int32_t *__restrict__ bmirror,
-                             const float *__restrict__ dbond, const float *__restrict__ rbar,
-                             const float *__restrict__ rhat, const float *__restrict__ bd, float *floc)
+// Delta_b = r_j + S C - r_i; it pulls on j with + and on i with -.
+__device__ inline void bond_gdelta(int64_t q, const float *__restrict__ dbond, const float *__restrict__ rbar,
+                                   const float *__restrict__ rhat, const float *__restrict__ bd, float (&gd)[3])
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
+    const float x = rhat[3 * q], y = rhat[3 * q + 1], z = rhat[3 * q + 2];
+    const float ax = rbar[3 * q], ay = rbar[3 * q + 1], az = rbar[3 * q + 2];
+    const float dot = fmaf(ax, x, fmaf(ay, y, az * z));
+    const float inv = 1.0f / bd[q];
+    gd[0] = fmaf(dbond[q], x, (ax - dot * x) * inv);
+    gd[1] = fmaf(dbond[q], y, (ay - dot * y) * inv);
+    gd[2] = fmaf(dbond[q], z, (az - dot * z) * inv);
+}
+
+// sum over the 16 lanes of a group
+__device__ inline float sum16(float v)
+{
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
+// Gathered per centre, 16 lanes each (a thread per centre took its bonds one after another: 292 us at 2.4 M bonds, against
+// 54): the bonds in which i is the sender are the reverse bonds of its own.   F_i = sum_b (gDelta_b - gDelta_mirror(b))
+__global__ void __launch_bounds__(256)
+k_bond_force(int64_t N, const int64_t *__restrict__ bptr, const int32_t *__restrict__ bmirror,
+             const float *__restrict__ dbond, const float *__restrict__ rbar,
+             const float *__restrict__ rhat, const float *__restrict__ bd, float *floc)
+{
+    const int64_t i = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+    if (i >= N) return;   // whole groups of 16 lanes leave together
     float fx = 0.f, fy = 0.f, fz = 0.f;
-    for (int64_t b = bptr[i]; b < bptr[i + 1]; ++b) {
-        for (int side = 0; side < 2; ++side) {
-            const int64_t q = side ? (int64_t)bmirror[b] : b;
-            if (q < 0) continue;   // reverse bond held by the sender's partition (it reaches this atom as a ghost there)
-            const float x = rhat[3 * q], y = rhat[3 * q + 1], z = rhat[3 * q + 2];
-            const float ax = rbar[3 * q], ay = rbar[3 * q + 1], az = rbar[3 * q + 2];
-            const float dot = fmaf(ax, x, fmaf(ay, y, az * z));
-            const float inv = 1.0f / bd[q];
-            const float sgn = side ? -1.f : 1.f;
-            fx += sgn * fmaf(dbond[q], x, (ax - dot * x) * inv);
-            fy += sgn * fmaf(dbond[q], y, (ay - dot * y) * inv);
-            fz += sgn * fmaf(dbond[q], z, (az - dot * z) * inv);
-        }
+    const int64_t b1 = bptr[i + 1];
+    for (int64_t b = bptr[i] + (threadIdx.x & 15); b < b1; b += 16) {
+        const int64_t q = bmirror[b];   // -1: reverse bond held by the sender's partition (it reaches this atom as a ghost there)
+        float own[3], rev[3] = {0.f, 0.f, 0.f};
+        bond_gdelta(b, dbond, rbar, rhat, bd, own);
+        if (q >= 0) bond_gdelta(q, dbond, rbar, rhat, bd, rev);
+        fx += own[0] - rev[0];
+        fy += own[1] - rev[1];
+        fz += own[2] - rev[2];
     }
-    floc[3 * i] = fx;   // (the radial part's rows add to it)
-    floc[3 * i + 1] = fy;
-    floc[3 * i + 2] = fz;
+    fx = sum16(fx);
+    fy = sum16(fy);
+    fz = sum16(fz);
+    if ((threadIdx.x & 15) == 0) {
+        floc[3 * i] = fx;   // (the radial part's rows add to it)
+        floc[3 * i + 1] = fy;
+        floc[3 * i + 2] = fz;
+    }
+}
+
+// Ghost rows: a ghost atom i is the sender of bonds (j <- i) held by this partition; each pulls on it with +dE/dDelta.
+// Gathered over the ghost's sub-row through the reverse edges, 16 lanes each.
+__global__ void __launch_bounds__(256)
+k_bond_force_ghost(int64_t n_ghost, int64_t n_owned, const int64_t *__restrict__ row_ptr,
+                   const int32_t *__restrict__ mirror, const int32_t *__restrict__ bond_of_edge,
+                   const float *__restrict__ dbond, const float *__restrict__ rbar,
+                   const float *__restrict__ rhat, const float *__restrict__ bd, float *floc)
+{
+    const int64_t k = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+    if (k >= n_ghost) return;
+    const int64_t r = n_owned + k, e1 = row_ptr[r + 1];
+    float fx = 0.f, fy = 0.f, fz = 0.f;
+    for (int64_t e = row_ptr[r] + (threadIdx.x & 15); e < e1; e += 16) {
+        const int64_t q = bond_of_edge[mirror[e]];
+        if (q < 0) continue;
+        float gd[3];
+        bond_gdelta(q, dbond, rbar, rhat, bd, gd);
+        fx -= gd[0];
+        fy -= gd[1];
+        fz -= gd[2];
+    }
+    fx = sum16(fx);
+    fy = sum16(fy);
+    fz = sum16(fz);
+    if ((threadIdx.x & 15) == 0) {
+        floc[3 * r] = fx;   // (the radial part's rows add to it)
+        floc[3 * r + 1] = fy;
+        floc[3 * r + 2] = fz;
+    }
 }
 
 // ---- F x F products over the bonds, fused with what surrounds them
 //
-// Same tile scheme as the node kernel (32 bonds per wavefront step, packed operands in LDS, features x items
-// accumulators); each stage reads or writes every [bonds x F] array it touches once.
+// As in the node kernel, a wavefront takes 32 bonds whose rows are loaded in the accumulator layout, so the products chain in
+// registers and only the packed operands sit in LDS; each stage reads or writes every [bonds x F] array it touches once.
 //   HEAD       e0 = bbond(d) We0 (registers only, never stored: TAIL recomputes it);  P = e0 Wta;  Q = e0 Wtb
 //   TAIL       m = S Wt2;  e1 = e0 + u SiLU(m) (registers only);  wb_l = e1 Wb_l for every layer l
-//   EBAR       e1bar = sum over the layers l of (abar_l,recv * g_l,send) Wb_l^T, each factor tile built in LDS from the
-//              kept per-layer abar and g rows;  ubar = sum_f e1bar SiLU(m);  mbar = e1bar u SiLU'(m) (registers only);
-//              Sbar = mbar Wt2^T
+//   EBAR       e1bar = sum over the layers l of (abar_l,recv * g_l,send) Wb_l^T, from the kept per-layer abar and g rows;
+//              ubar = sum_f e1bar SiLU(m);  mbar = e1bar u SiLU'(m) (registers only);  Sbar = mbar Wt2^T
 //   E0BAR      e0bar = e1bar + Pbar Wta^T + Qbar Wtb^T (registers only);
 //              dbond = sum_f e0bar (We0^T dbbond/dd) + ubar du/dd
+// Bound by the arrays' bytes.  At 2.4 M bonds, 622 MB per fp32 array, in us with fp32 MFMA and the rows staged through LDS ->
+// here: HEAD 492 -> 356, TAIL 951 -> 816, EBAR 1354 -> 857, E0BAR 463 -> 360.
 enum { BOND_HEAD = 0, BOND_TAIL = 1, BOND_EBAR = 2, BOND_E0BAR = 3 };
 
 struct BondArgs {                      // one partition
@@ -423,12 +474,15 @@ struct BondArgs {                      // one partition
 
 template <int STAGE> struct BondStage {
     static constexpr bool PER_LAYER = (STAGE == BOND_TAIL || STAGE == BOND_EBAR);   // one operand pack per layer
-    static constexpr int NW = PER_LAYER ? 8 : 4;   // wavefronts per block
     static constexpr int NPACK = PER_LAYER ? 4 : 2;
+    static constexpr int NW = 8;                          // wavefronts per block
+    static constexpr int STAGE_FS = 36;                   // EBAR: row stride of a wavefront's 32 x 32 staging tile
+    static constexpr int TILE = STAGE == BOND_EBAR ? 32 * STAGE_FS : 0;
+    static constexpr int BLOCKS = PER_LAYER ? 256 : 512;  // blocks in flight
 };
 
-// PREC: the F x F products follow the precision mode of the filter MLP's (fp32 MFMA; bf16 operands; split-fp16 triples;
-// packs prepared accordingly, activations converted in registers, fp32 accumulation); the K = 8 products stay fp32.
+// PREC: the F x F products follow the precision mode of the filter MLP's (fp32 as three-part bf16; bf16 operands; split-fp16
+// triples; packs prepared accordingly, activations converted in registers, fp32 accumulation); the K = 8 products stay fp32.
 // The [bonds x F] arrays are bf16 in the bf16 mode and fp32 otherwise.
 template <int PREC> struct BondElem { typedef float type; };
 template <> struct BondElem<kPrecBf16> { typedef __bf16 type; };
@@ -436,39 +490,43 @@ template <> struct BondElem<kPrecBf16> { typedef __bf16 type; };
 template <int F, int STAGE, int PREC>
 __global__ void __launch_bounds__(BondStage<STAGE>::NW * 64) k_bond_mlp(BondArgs A)
 {
-    using D = Dims<F>;
     using BT = typename BondElem<PREC>::type;
     using IO = Elem<BT>;
-    constexpr int NB = D::NB, FS = D::FS;
-    constexpr int NW = BondStage<STAGE>::NW, NPACK = BondStage<STAGE>::NPACK;
-    constexpr int LPR = TileRegs<F>::LPR, RPI = TileRegs<F>::RPI;
-    extern __shared__ float lds[];
-    float *packs = lds;
-    float *tiles = packs + NPACK * D::PACKF;
+    constexpr int NB = Dims<F>::NB, NW = BondStage<STAGE>::NW, NPACK = BondStage<STAGE>::NPACK, PACK = pack_floats<F>(PREC);
+    extern __shared__ float packs[];
     const int n_lds_layers = BondStage<STAGE>::PER_LAYER ? min(A.n_layers, 3) : 0;
     const int n_packs = BondStage<STAGE>::PER_LAYER ? 1 + n_lds_layers : NPACK;
-    for (int q = 0; q < n_packs; ++q)   // (a bf16 pack fills the first half of its slot)
-        for (int i = threadIdx.x; i < (PREC == kPrecBf16 ? D::PACKF / 2 : D::PACKF); i += NW * 64) packs[q * D::PACKF + i] = A.W[q][i];
+    for (int q = 0; q < n_packs; ++q)
+        for (int i = threadIdx.x; i < PACK / 4; i += NW * 64)
+            reinterpret_cast<f32x4 *>(packs + q * PACK)[i] = reinterpret_cast<const f32x4 *>(A.W[q])[i];
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int c32 = lane & 31, h = lane >> 5;
-    const int rr = lane / LPR, cc = (lane % LPR) * 4;   // this lane's row and first feature within a tile row group
+    const int c32 = lane & 31, h4 = 4 * (lane >> 5);
     RegPack1<F> W0;   // We0 as the A operands of the K = 8 product
     if (STAGE == BOND_HEAD || STAGE == BOND_TAIL || STAGE == BOND_E0BAR) load_pack1<F>(W0, A.We0p, lane);
-    float *tile = tiles + wave * D::TILE;
     const int64_t n_tiles = (A.n + 31) / 32;
     const int64_t stride = (int64_t)gridDim.x * NW;
 
-    // rows of a [bonds x F] array in accumulator layout: lane (c32, h) holds features 32 b + 8 a + 4 h + (0..3) of bond c32
+    // rows in accumulator layout: lane (c32, h) holds features 32 b + 8 a + 4 h + (0..3) of bond c32, as loaded until used
     typedef typename IO::raw4 raw4;
-    auto load_rows = [&](const void *Yv, int64_t row, bool ok, raw4 (&v)[NB][4]) {   // as loaded: widen at the use
+    auto load_rows = [&](const void *Yv, int64_t row, bool ok, raw4 (&v)[NB][4]) {
         const BT *Y = static_cast<const BT *>(Yv);
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
             for (int a = 0; a < 4; ++a) {
-                v[b][a] = raw4{};
-                if (ok) v[b][a] = IO::load4_raw(Y + row * F + 32 * b + 8 * a + 4 * h);
+                v[b][a] = raw4{};   // all-zero bits are 0.0 in either type
+                if (ok) v[b][a] = IO::load4_raw(Y + row * F + 32 * b + 8 * a + h4);
+            }
+    };
+    auto widen_rows = [&](const raw4 (&v)[NB][4], f32x16 (&x)[NB]) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                const f32x4 w = IO::widen4(v[b][a]);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) x[b][4 * a + c] = w[c];
             }
     };
     auto store_rows = [&](void *Yv, int64_t row, bool ok, const f32x16 (&acc)[NB]) {
@@ -479,34 +537,74 @@ __global__ void __launch_bounds__(BondStage<STAGE>::NW * 64) k_bond_mlp(BondArgs
 #pragma unroll
                 for (int a = 0; a < 4; ++a) {
                     const f32x4 v = {acc[b][4 * a], acc[b][4 * a + 1], acc[b][4 * a + 2], acc[b][4 * a + 3]};
-                    IO::store4(Y + row * F + 32 * b + 8 * a + 4 * h, v);
+                    IO::store4(Y + row * F + 32 * b + 8 * a + h4, v);
                 }
     };
-
-    // out (+)= M x, x a 32-bond tile in LDS (this lane's bond = tile row c32) or a tile held in accumulator layout
-    auto mul_tile = [&](auto accumulate, const float *pack, const float *t, f32x16 (&out)[NB]) {
+    // out (+)= M in
+    auto mul = [&](auto accumulate, const float *pack, const f32x16 (&in)[NB], f32x16 (&out)[NB]) {
         constexpr bool ACC = decltype(accumulate)::value;
-        if (PREC == kPrecBf16) gemm_row_bf16<F, ACC>(reinterpret_cast<const __bf16 *>(pack), t + c32 * FS, out, lane);
-        else if (PREC == kPrecF16x3) gemm_row_f16x3<F, ACC>(reinterpret_cast<const _Float16 *>(pack), t + c32 * FS, out, lane);
-        else gemm_lds<F, ACC>(pack, t, out, lane);
-    };
-    auto mul_regs = [&](const float *pack, const f32x16 (&in)[NB], f32x16 (&out)[NB]) {
-        if (PREC == kPrecBf16) gemm_rl_bf16<F>(reinterpret_cast<const __bf16 *>(pack), in, out, lane);
-        else if (PREC == kPrecF16x3) gemm_rl_f16x3<F>(reinterpret_cast<const _Float16 *>(pack), in, out, lane);
-        else gemm_regs<F>(pack, in, out, lane);
+        if (PREC == kPrecBf16) gemm_rl_bf16<F, ACC>(reinterpret_cast<const __bf16 *>(pack), in, out, lane);
+        else if (PREC == kPrecF16x3) gemm_rl_f16x3<F, ACC>(reinterpret_cast<const _Float16 *>(pack), in, out, lane);
+        else gemm_rl_bf16x3<F, ACC>(reinterpret_cast<const __bf16 *>(pack), in, out, lane);
     };
     using Fresh = std::false_type;
     using Add = std::true_type;
 
-    TileRegs<F, BT> pre, pre2;
-    int64_t ti = (int64_t)blockIdx.x * NW + wave;
-    if (ti < n_tiles) {
-        if (STAGE == BOND_TAIL) fetch_tile<F, BT>(pre, static_cast<const BT *>(A.S), ti * 32, A.n, lane);
-        if (STAGE == BOND_E0BAR) fetch_tile<F, BT>(pre, static_cast<const BT *>(A.Pbar), ti * 32, A.n, lane);
-    }
+    raw4 pre[NB][4], pre2[NB][4];
+    int64_t ti = (int64_t)wave * gridDim.x + blockIdx.x;   // few tiles: one per block
+    // EBAR gathers its rows 8 lanes to 128 consecutive bytes of a row and turns them into the accumulator layout through a small
+    // LDS tile (gathered in that layout directly, 16 bytes a lane, every line was fetched several times: 1586 us against 857 us)
+    f32x4 fa[NB][4], fg[NB][4];
+    int32_t gi[4], gj[4];   // receiver and sender rows of tile rows 8 q + lane / 8 (-1: past the end)
+    auto load_factors = [&](int l) {   // dE/dwb_l of a bond = abar_l[receiver] * g_l[sender]
+        const float *al = A.abar + (size_t)l * A.abar_stride, *gl = A.g + (size_t)l * A.g_stride;
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                fa[b][q] = fg[b][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (gi[q] >= 0) {
+                    fa[b][q] = *reinterpret_cast<const f32x4 *>(al + (int64_t)gi[q] * F + 32 * b + 4 * (lane & 7));
+                    fg[b][q] = *reinterpret_cast<const f32x4 *>(gl + (int64_t)gj[q] * F + 32 * b + 4 * (lane & 7));
+                }
+            }
+    };
+    auto turn_factors = [&](f32x16 (&x)[NB]) {
+        constexpr int FS = BondStage<STAGE>::STAGE_FS;
+        float *tile = packs + NPACK * PACK + wave * BondStage<STAGE>::TILE;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<f32x4 *>(tile + (8 * q + (lane >> 3)) * FS + 4 * (lane & 7)) = fa[b][q] * fg[b][q];
+            wave_lds_fence();
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                const f32x4 v = *reinterpret_cast<const f32x4 *>(tile + c32 * FS + 8 * a + h4);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) x[b][4 * a + c] = v[c];
+            }
+            wave_lds_fence();
+        }
+    };
+    auto fetch = [&](int64_t t) {   // what a tile needs first
+        const int64_t row = t * 32 + c32;
+        const bool ok = row < A.n;
+        if (STAGE == BOND_TAIL) load_rows(A.S, row, ok, pre);
+        if (STAGE == BOND_E0BAR) load_rows(A.Pbar, row, ok, pre);
+        if (STAGE == BOND_EBAR) {
+            const int32_t ri = ok ? A.recv[A.edge[row]] : -1, rj = ok ? A.sender[row] : -1;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                gi[q] = __shfl(ri, 8 * q + (lane >> 3), 64);
+                gj[q] = __shfl(rj, 8 * q + (lane >> 3), 64);
+            }
+            if (A.n_layers > 0) load_factors(0);
+        }
+    };
+    if (ti < n_tiles) fetch(ti);
     for (; ti < n_tiles; ti += stride) {
-        const int64_t row0 = ti * 32;
-        const int64_t row = row0 + c32;
+        const int64_t row = ti * 32 + c32;
         const bool ok = row < A.n;
         const bool more = ti + stride < n_tiles;
         f32x16 acc[NB];
@@ -516,20 +614,18 @@ __global__ void __launch_bounds__(BondStage<STAGE>::NW * 64) k_bond_mlp(BondArgs
             radial_basis<false>(ok ? A.d[row] : A.bp.rc, A.bp, bb, db);   // 0 at the cutoff
             f32x16 e0[NB];
             gemm_k8r<F>(W0, bb, e0, lane);
-            mul_regs(packs, e0, acc);
+            mul(Fresh{}, packs, e0, acc);
             store_rows(A.P, row, ok, acc);
-            mul_regs(packs + D::PACKF, e0, acc);
+            mul(Fresh{}, packs + PACK, e0, acc);
             store_rows(A.Q, row, ok, acc);
         } else if (STAGE == BOND_TAIL) {
-            stash_tile<F>(pre, tile, lane);
-            wave_lds_fence();
+            f32x16 e1[NB];
+            widen_rows(pre, e1);
             const float uc = ok ? A.u[row] : 0.f;
             const float dc = ok ? A.d[row] : A.bp.rc;
-            if (more) fetch_tile<F, BT>(pre, static_cast<const BT *>(A.S), (ti + stride) * 32, A.n, lane);
-            mul_tile(Fresh{}, packs, tile, acc);
-            wave_lds_fence();
+            if (more) fetch(ti + stride);
+            mul(Fresh{}, packs, e1, acc);
             store_rows(A.m, row, ok, acc);
-            f32x16 e1[NB];
             {
                 float bb[8], db[8];
                 radial_basis<false>(dc, A.bp, bb, db);
@@ -539,94 +635,58 @@ __global__ void __launch_bounds__(BondStage<STAGE>::NW * 64) k_bond_mlp(BondArgs
             for (int b = 0; b < NB; ++b)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) e1[b][r] = fmaf(uc, silu_f(acc[b][r]), e1[b][r]);
-            for (int l = 0; l < n_lds_layers; ++l) {
-                mul_regs(packs + (1 + l) * D::PACKF, e1, acc);
-                store_rows(static_cast<BT *>(A.wb) + (size_t)l * A.wb_stride, row, ok, acc);
-            }
-            for (int l = 3; l < A.n_layers; ++l) {
-                mul_regs(A.Wx + (size_t)(l - 3) * D::PACKF, e1, acc);
+            for (int l = 0; l < A.n_layers; ++l) {
+                mul(Fresh{}, l < 3 ? packs + (1 + l) * PACK : A.Wx + (size_t)(l - 3) * Dims<F>::PACK3, e1, acc);
                 store_rows(static_cast<BT *>(A.wb) + (size_t)l * A.wb_stride, row, ok, acc);
             }
         } else if (STAGE == BOND_EBAR) {
-            raw4 mv[NB][4];
-            load_rows(A.m, row, ok, mv);   // needed after the products
+            load_rows(A.m, row, ok, pre);   // needed after the products
             const float uc = ok ? A.u[row] : 0.f;
-            int32_t ri[32 / RPI], rj[32 / RPI];   // receiver and sender rows of this lane's tile rows
-#pragma unroll
-            for (int r = 0; r < 32; r += RPI) {
-                const int64_t rw = row0 + r + rr;
-                ri[r / RPI] = rj[r / RPI] = -1;
-                if (rw < A.n) {
-                    ri[r / RPI] = A.recv[A.edge[rw]];
-                    rj[r / RPI] = A.sender[rw];
-                }
-            }
 #pragma unroll
             for (int b = 0; b < NB; ++b)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
-            auto factor_tile = [&](int l) {   // dE/dwb_l of the tile's bonds = abar_l[receiver] * g_l[sender]
-                const float *al = A.abar + (size_t)l * A.abar_stride, *gl = A.g + (size_t)l * A.g_stride;
-#pragma unroll
-                for (int r = 0; r < 32; r += RPI) {
-                    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-                    if (ri[r / RPI] >= 0)
-                        v = *reinterpret_cast<const f32x4 *>(al + (int64_t)ri[r / RPI] * F + cc) *
-                            *reinterpret_cast<const f32x4 *>(gl + (int64_t)rj[r / RPI] * F + cc);
-                    *reinterpret_cast<f32x4 *>(tile + (r + rr) * FS + cc) = v;
-                }
-                wave_lds_fence();
-            };
-            for (int l = 0; l < n_lds_layers; ++l) {
-                factor_tile(l);
-                mul_tile(Add{}, packs + (1 + l) * D::PACKF, tile, acc);
-                wave_lds_fence();
-            }
-            for (int l = 3; l < A.n_layers; ++l) {
-                factor_tile(l);
-                mul_tile(Add{}, A.Wx + (size_t)(l - 3) * D::PACKF, tile, acc);
-                wave_lds_fence();
+            f32x16 x[NB];
+            for (int l = 0; l < A.n_layers; ++l) {
+                turn_factors(x);
+                if (l + 1 < A.n_layers) load_factors(l + 1);   // in flight during this layer's product
+                else if (more) fetch(ti + stride);
+                mul(Add{}, l < 3 ? packs + (1 + l) * PACK : A.Wx + (size_t)(l - 3) * Dims<F>::PACK3, x, acc);
             }
             store_rows(A.e1bar, row, ok, acc);
             float part = 0.f;
-            f32x16 mb[NB];
 #pragma unroll
             for (int b = 0; b < NB; ++b)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     float sv, ds;
-                    silu_both(IO::widen4(mv[b][r / 4])[r % 4], sv, ds);
+                    silu_both(IO::widen4(pre[b][r / 4])[r % 4], sv, ds);
                     part = fmaf(acc[b][r], sv, part);
-                    mb[b][r] = acc[b][r] * uc * ds;
+                    x[b][r] = acc[b][r] * uc * ds;   // mbar
                 }
             part += __shfl_xor(part, 32, 64);
-            if (ok && h == 0) A.ubar[row] = part;
-            mul_regs(packs, mb, acc);
+            if (ok && h4 == 0) A.ubar[row] = part;
+            mul(Fresh{}, packs, x, acc);
             store_rows(A.Sbar, row, ok, acc);
         } else {   // BOND_E0BAR
-            stash_tile<F>(pre, tile, lane);
-            wave_lds_fence();
-            fetch_tile<F, BT>(pre2, static_cast<const BT *>(A.Qbar), row0, A.n, lane);   // in flight during the first product
-            raw4 zv[NB][4];
-            load_rows(A.e1bar, row, ok, zv);
-            mul_tile(Fresh{}, packs, tile, acc);
-            wave_lds_fence();
-            stash_tile<F>(pre2, tile, lane);
-            wave_lds_fence();
-            if (more) fetch_tile<F, BT>(pre, static_cast<const BT *>(A.Pbar), (ti + stride) * 32, A.n, lane);
-            mul_tile(Add{}, packs + D::PACKF, tile, acc);
-            wave_lds_fence();
+            f32x16 x[NB];
+            widen_rows(pre, x);
+            load_rows(A.Qbar, row, ok, pre);   // in flight during the first product
+            load_rows(A.e1bar, row, ok, pre2);
+            mul(Fresh{}, packs, x, acc);
+            widen_rows(pre, x);
+            if (more) fetch(ti + stride);
+            mul(Add{}, packs + PACK, x, acc);
             float bb[8], db[8];
             radial_basis<true>(ok ? A.d[row] : A.bp.rc, A.bp, bb, db);
-            f32x16 vv[NB];   // We0^T dbbond/dd
-            gemm_k8r<F>(W0, db, vv, lane);
+            gemm_k8r<F>(W0, db, x, lane);   // We0^T dbbond/dd
             float part = 0.f;
 #pragma unroll
             for (int b = 0; b < NB; ++b)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) part = fmaf(IO::widen4(zv[b][r / 4])[r % 4] + acc[b][r], vv[b][r], part);
+                for (int r = 0; r < 16; ++r) part = fmaf(IO::widen4(pre2[b][r / 4])[r % 4] + acc[b][r], x[b][r], part);
             part += __shfl_xor(part, 32, 64);
-            if (ok && h == 0) A.dbond[row] = fmaf(A.ubar[row], A.du[row], part);
+            if (ok && h4 == 0) A.dbond[row] = fmaf(A.ubar[row], A.du[row], part);
         }
     }
 }

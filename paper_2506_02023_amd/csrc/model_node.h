@@ -238,37 +238,6 @@ __global__ void __launch_bounds__(NodeOp<OP>::NW * 64) k_node(NodeBatch B)
     }
 }
 
-// A 32-row tile of X travels global memory -> registers -> LDS in two halves, so that the loads of the next
-// tile can be in flight while the current one is multiplied.
-template <int F, typename T_ = float> struct TileRegs {
-    static constexpr int LPR = F / 4;        // lanes per row (four elements each)
-    static constexpr int RPI = 64 / LPR;     // rows per wave instruction
-    typename Elem<T_>::raw4 v[32 / RPI];     // as loaded; widened to fp32 when the tile goes to LDS
-};
-
-template <int F, typename T_>
-__device__ inline void fetch_tile(TileRegs<F, T_> &T, const T_ *__restrict__ X, int64_t row0, int64_t n_rows, int lane)
-{
-    constexpr int LPR = TileRegs<F>::LPR, RPI = TileRegs<F>::RPI;
-    const int rr = lane / LPR, cc = (lane % LPR) * 4;
-#pragma unroll
-    for (int r = 0; r < 32; r += RPI) {
-        const int64_t row = row0 + r + rr;
-        typename Elem<T_>::raw4 v = {};   // all-zero bits are 0.0 in either type
-        if (row < n_rows) v = Elem<T_>::load4_raw(X + row * F + cc);
-        T.v[r / RPI] = v;
-    }
-}
-
-template <int F, typename T_> __device__ inline void stash_tile(const TileRegs<F, T_> &T, float *tile, int lane)
-{
-    constexpr int FS = Dims<F>::FS;
-    constexpr int LPR = TileRegs<F>::LPR, RPI = TileRegs<F>::RPI;
-    const int rr = lane / LPR, cc = (lane % LPR) * 4;
-#pragma unroll
-    for (int r = 0; r < 32; r += RPI) *reinterpret_cast<f32x4 *>(tile + (r + rr) * FS + cc) = Elem<T_>::widen4(T.v[r / RPI]);
-}
-
 // ---------------------------------------------------------------- small kernels
 //
 // Embedding, ghost transfers, force assembly and the energy partial sums run over all partitions in one launch
@@ -289,7 +258,9 @@ struct SmallArgs {   // one partition
     const int64_t *l_row_ptr;      // the owned rows' lower edges: CSR, sender row, where the pair's filter values are kept
     const int32_t *l_senders, *l_slot;
     const float *dsum, *wstore, *d;
-    const int32_t *bond_of_edge;   // three-body variant (or nullptr)
+    const int32_t *bond_of_edge;   // three-body variant (or nullptr): bond of an edge, bonds per owned row, sender, reverse bond
+    const int64_t *b_ptr;
+    const int32_t *b_sender, *b_mirror;
     const void *wb;                // bond filter rows of the layer: fp32, or bf16 if wb_bf16
     int wb_bf16;
 };
@@ -334,6 +305,7 @@ __global__ void __launch_bounds__(256) k_edge_lower(SmallBatch B)
     // the row's lower edges (wave-uniform, kept scalar; edge indices fit 32 bits)
     const int64_t e0 = __builtin_amdgcn_readfirstlane((int32_t)A.l_row_ptr[r]);
     const int64_t e1 = __builtin_amdgcn_readfirstlane((int32_t)A.l_row_ptr[r + 1]);
+    const float before = A.gbar[r * F + f];   // (requested with the indices)
     float acc = 0.f;
     for (int64_t eb = e0; eb < e1; eb += 64) {
         const int n = (int)min((int64_t)64, e1 - eb);
@@ -355,7 +327,29 @@ __global__ void __launch_bounds__(256) k_edge_lower(SmallBatch B)
             for (int t = 0; t < kLowerChunk; ++t) acc = fmaf(wv[t], gv[t], acc);
         }
     }
-    if (F == 64 || lane < F) A.gbar[r * F + f] += acc;
+    if (A.b_ptr) {   // three-body variant: gbar_i += sum_b wb[mirror(b)] * abar_j (the reverse bond (j <- i) is the one whose
+                     // filter multiplies g_i in row j; none here if the sender is a ghost row: abar_j = 0, its owner adds that term)
+        const int64_t b0 = __builtin_amdgcn_readfirstlane((int32_t)A.b_ptr[r]), b1 = __builtin_amdgcn_readfirstlane((int32_t)A.b_ptr[r + 1]);
+        for (int64_t bb = b0; bb < b1; bb += 16) {
+            const int n = (int)min((int64_t)16, b1 - bb);
+            const int64_t bl = min(bb + (lane & 15), b1 - 1);
+            const int32_t jl = A.b_sender[bl], ml = A.b_mirror[bl];
+            float wv[16], gv[16];
+#pragma unroll
+            for (int t = 0; t < 16; ++t) {
+                wv[t] = gv[t] = 0.f;
+                const int64_t m = __builtin_amdgcn_readlane(ml, t);
+                if (t < n && m >= 0) {
+                    wv[t] = A.wb_bf16 ? Elem<__bf16>::load(static_cast<const __bf16 *>(A.wb) + m * F + f)
+                                      : static_cast<const float *>(A.wb)[m * F + f];
+                    gv[t] = A.abar[(int64_t)__builtin_amdgcn_readlane(jl, t) * F + f];
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < 16; ++t) acc = fmaf(wv[t], gv[t], acc);
+        }
+    }
+    if (F == 64 || lane < F) A.gbar[r * F + f] = before + acc;
 }
 
 // gbar of the ghost rows: gbar_i = sum over the ghost's sub-row (its neighbours owned by this partition) of
@@ -395,33 +389,6 @@ __global__ void __launch_bounds__(256) k_ghost_gbar(SmallBatch B)
             if (k < n) acc = fmaf(wv[k], av[k], acc);
     }
     if (F == 64 || lane < F) A.gbar[r * F + f] = acc;
-}
-
-// Three-body variant, ghost rows: a ghost atom i is the sender of bonds (j <- i) held by this partition; each pulls
-// on it with +dE/dDelta.  Gathered over the ghost's sub-row through the reverse edges.
-__global__ void k_bond_force_ghost(int64_t n_ghost, int64_t n_owned, const int64_t *__restrict__ row_ptr,
-                                   const int32_t *__restrict__ mirror, const int32_t *__restrict__ bond_of_edge,
-                                   const float *__restrict__ dbond, const float *__restrict__ rbar,
-                                   const float *__restrict__ rhat, const float *__restrict__ bd, float *floc)
-{
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n_ghost) return;
-    const int64_t r = n_owned + k;
-    float fx = 0.f, fy = 0.f, fz = 0.f;
-    for (int64_t e = row_ptr[r]; e < row_ptr[r + 1]; ++e) {
-        const int64_t q = bond_of_edge[mirror[e]];
-        if (q < 0) continue;
-        const float x = rhat[3 * q], y = rhat[3 * q + 1], z = rhat[3 * q + 2];
-        const float ax = rbar[3 * q], ay = rbar[3 * q + 1], az = rbar[3 * q + 2];
-        const float dot = fmaf(ax, x, fmaf(ay, y, az * z));
-        const float inv = 1.0f / bd[q];
-        fx -= fmaf(dbond[q], x, (ax - dot * x) * inv);
-        fy -= fmaf(dbond[q], y, (ay - dot * y) * inv);
-        fz -= fmaf(dbond[q], z, (az - dot * z) * inv);
-    }
-    floc[3 * r] = fx;   // (the radial part's rows add to it)
-    floc[3 * r + 1] = fy;
-    floc[3 * r + 2] = fz;
 }
 
 __device__ inline void unpack_shift(uint32_t p, int &a, int &b, int &c)

@@ -120,26 +120,25 @@ __device__ inline void radial_basis(float d, const BasisParams &bp, float (&b)[8
 
 // ---------------------------------------------------------------- packed weights
 //
-// PACK_FF: F x F matrix M[o][k] as MFMA A operands, index
-//   ((((bo * NB + bi) * 4 + a) * 64 + lane) * 4 + c)  ->  M[32 bo + lane % 32][32 bi + 8 a + 4 (lane / 32) + c]
-// with M[o][k] = W[k][o] (TRANS, y = x W) or W[o][k] (y = x W^T).
-// PACK_W1: K = 8 rows, index ((bo * 4 + s) * 64 + lane) -> W1[2 s + lane / 32][32 bo + lane % 32].
-//
-// bf16 form of an F x F operand for v_mfma_f32_32x32x16_bf16 (the bf16 precision mode: the W2 products of the
-// filter MLP run on the bf16 matrix pipeline with fp32 accumulation, at 1/16 of the fp32 MFMA time).
-// Index (((bo * NB + bi) * 2 + q) * 64 + lane) * 8 + t  ->  M[32 bo + lane % 32][32 bi + 8 (r / 4) + 4 (lane / 32) + r % 4],
+// F x F operands are packed as the A operands of v_mfma_f32_32x32x16_{bf16,f16}: matrix M[o][k] = W[k][o] (trans, y = x W) or
+// W[o][k] (y = x W^T), index
+//   (((bo * NB + bi) * 2 + q) * 64 + lane) * 8 + t  ->  M[32 bo + lane % 32][32 bi + 8 (r / 4) + 4 (lane / 32) + r % 4],
 // r = 8 q + t: element t of lane-half h of MFMA (bi, q) pairs with accumulator register r of a chained product
 // (or with the same feature of an item-major LDS row).
+// PACK_W1: K = 8 rows, index ((bo * 4 + s) * 64 + lane) -> W1[2 s + lane / 32][32 bo + lane % 32].
+//
+// PACK_FF_BF16X3: every fp32 value as three bf16 parts (split_bf16x3), one pack of each after the other; the fp32 mode and
+// the node kernels.  PACK_FF_BF16: rounded to bf16; the bf16 mode.
 //
 // Split-fp16 form of the same operand: every fp32 value v is kept as hi + lo, hi = fp16(v), lo = fp16(v - hi)
 // (22 significant bits together); a product of two such values is taken as hi hi + hi lo + lo hi with fp32
 // accumulation.  What is dropped (lo lo, and the rounding of the two lo parts) is about 3 * 2^-22 of the term,
 // the size of the rounding an fp32 accumulation of 64 terms makes anyway, at 3/16 of the fp32 MFMA's matrix time.
-// hi parts first (F * F halves), then lo parts: together the bytes of the fp32 pack.
+// hi parts first (F * F halves), then lo parts.
 //
 // Operand packs a call needs are made by one launch: one job per pack (blockIdx.y), one thread per element.  Every
 // pack in a launch of its own took 2 us of device time and a launch each, 20 to 26 per model.
-enum { PACK_W1 = 0, PACK_FF = 1, PACK_FF_BF16 = 2, PACK_FF_F16X2 = 3, PACK_FF_BF16X3 = 4 };
+enum { PACK_W1 = 0, PACK_FF_BF16 = 1, PACK_FF_F16X2 = 2, PACK_FF_BF16X3 = 3 };
 struct PackJob {
     const float *W;
     float *out;
@@ -167,20 +166,11 @@ __global__ void k_pack(PackBatch B)
     }
     if (idx >= F * F) return;
     const int bb = idx >> 10, bi = bb % NB, bo = bb / NB;
-    int o, k;
-    if (J.kind == PACK_FF) {
-        const int c = idx & 3, lane = (idx >> 2) & 63, a = (idx >> 8) & 3;
-        o = 32 * bo + (lane & 31);
-        k = 32 * bi + 8 * a + 4 * (lane >> 5) + c;
-    } else {
-        const int t = idx & 7, lane = (idx >> 3) & 63, q = (idx >> 9) & 1, r = 8 * q + t;
-        o = 32 * bo + (lane & 31);
-        k = 32 * bi + 8 * (r / 4) + 4 * (lane >> 5) + (r & 3);
-    }
+    const int t = idx & 7, lane = (idx >> 3) & 63, q = (idx >> 9) & 1, r = 8 * q + t;
+    const int o = 32 * bo + (lane & 31);
+    const int k = 32 * bi + 8 * (r / 4) + 4 * (lane >> 5) + (r & 3);
     const float v = J.scale * (J.trans ? W[k * F + o] : W[o * F + k]);
-    if (J.kind == PACK_FF) {
-        J.out[idx] = v;
-    } else if (J.kind == PACK_FF_BF16) {
+    if (J.kind == PACK_FF_BF16) {
         reinterpret_cast<__bf16 *>(J.out)[idx] = (__bf16)v;
     } else if (J.kind == PACK_FF_BF16X3) {
         const __bf16 h = (__bf16)v;
@@ -251,115 +241,8 @@ template <int F> struct Dims {
     static constexpr int PACK3 = F * F * 3 / 2;   // floats of a three-part bf16 pack
 };
 
-// out[bo] = sum_k M[.][k] in[k][.], `in` held in accumulator layout (chained product)
-template <int F>
-__device__ inline void gemm_regs(const float *__restrict__ Ap, const f32x16 (&in)[Dims<F>::NB],
-                                 f32x16 (&out)[Dims<F>::NB], int lane)
-{
-    constexpr int NB = Dims<F>::NB;
-#pragma unroll
-    for (int bo = 0; bo < NB; ++bo)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) out[bo][r] = 0.f;
-#pragma unroll
-    for (int bi = 0; bi < NB; ++bi)
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int bo = 0; bo < NB; ++bo) {
-                const f32x4 av = *reinterpret_cast<const f32x4 *>(Ap + ((((bo * NB + bi) * 4 + a) * 64 + lane) * 4));
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    out[bo] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[c], in[bi][4 * a + c], out[bo], 0, 0, 0);
-            }
-}
-
-// same product with the B operand read from an item-major LDS tile [32][FS]; A and B operand
-// loads of step k+1 are issued before the MFMAs of step k
-template <int F, bool ACCUMULATE = false>
-__device__ inline void gemm_lds(const float *__restrict__ Ap, const float *tile, f32x16 (&out)[Dims<F>::NB], int lane)
-{
-    constexpr int NB = Dims<F>::NB;
-    constexpr int FS = Dims<F>::FS;
-    constexpr int STEPS = NB * 4;
-    const int c32 = lane & 31, h = lane >> 5;
-    if (!ACCUMULATE)
-#pragma unroll
-        for (int bo = 0; bo < NB; ++bo)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) out[bo][r] = 0.f;
-    const float *bp = tile + c32 * FS + 4 * h;
-    const float *ap = Ap + lane * 4;
-    f32x4 bv = *reinterpret_cast<const f32x4 *>(bp);
-    f32x4 av[NB];
-#pragma unroll
-    for (int bo = 0; bo < NB; ++bo) av[bo] = *reinterpret_cast<const f32x4 *>(ap + ((bo * NB) * 4) * 256);
-#pragma unroll
-    for (int st = 0; st < STEPS; ++st) {
-        f32x4 bn = bv, an[NB];
-#pragma unroll
-        for (int bo = 0; bo < NB; ++bo) an[bo] = av[bo];
-        if (st + 1 < STEPS) {
-            const int bi = (st + 1) / 4, a = (st + 1) % 4;
-            bn = *reinterpret_cast<const f32x4 *>(bp + 32 * bi + 8 * a);
-#pragma unroll
-            for (int bo = 0; bo < NB; ++bo)
-                an[bo] = *reinterpret_cast<const f32x4 *>(ap + (((bo * NB + bi) * 4 + a)) * 256);
-        }
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int bo = 0; bo < NB; ++bo)
-                out[bo] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[bo][c], bv[c], out[bo], 0, 0, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, NB + 1, 0);  // the next step's LDS reads first
-        __builtin_amdgcn_sched_group_barrier(0x008, 4 * NB, 0);  // then this step's MFMAs
-        bv = bn;
-#pragma unroll
-        for (int bo = 0; bo < NB; ++bo) av[bo] = an[bo];
-    }
-}
-
-// chained product with the weights in LDS (packed A operands), B operand in registers; the A
-// operands of step k+1 are fetched while the MFMAs of step k run
-template <int F>
-__device__ inline void gemm_rl(const float *__restrict__ Ap, const f32x16 (&in)[Dims<F>::NB],
-                               f32x16 (&out)[Dims<F>::NB], int lane)
-{
-    constexpr int NB = Dims<F>::NB;
-    constexpr int STEPS = NB * 4;
-#pragma unroll
-    for (int bo = 0; bo < NB; ++bo)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) out[bo][r] = 0.f;
-    const float *ap = Ap + lane * 4;
-    f32x4 av[NB];
-#pragma unroll
-    for (int bo = 0; bo < NB; ++bo) av[bo] = *reinterpret_cast<const f32x4 *>(ap + ((bo * NB) * 4) * 256);
-#pragma unroll
-    for (int st = 0; st < STEPS; ++st) {
-        const int bi = st / 4, a = st % 4;
-        f32x4 an[NB];
-#pragma unroll
-        for (int bo = 0; bo < NB; ++bo) an[bo] = av[bo];
-        if (st + 1 < STEPS) {
-            const int bi2 = (st + 1) / 4, a2 = (st + 1) % 4;
-#pragma unroll
-            for (int bo = 0; bo < NB; ++bo)
-                an[bo] = *reinterpret_cast<const f32x4 *>(ap + (((bo * NB + bi2) * 4 + a2)) * 256);
-        }
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int bo = 0; bo < NB; ++bo)
-                out[bo] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[bo][c], in[bi][4 * a + c], out[bo], 0, 0, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, NB, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 4 * NB, 0);
-#pragma unroll
-        for (int bo = 0; bo < NB; ++bo) av[bo] = an[bo];
-    }
-}
-
-// gemm_rl in bf16: weights as a bf16 pack in LDS, the chained B operand rounded to bf16, fp32 accumulation
+// out[bo] = sum_k M[.][k] in[k][.], `in` held in accumulator layout (chained product), in bf16: weights as a bf16 pack in
+// LDS, the chained operand rounded to bf16, fp32 accumulation
 template <int F, bool ACCUMULATE = false>
 __device__ inline void gemm_rl_bf16(const __bf16 *__restrict__ Ap, const f32x16 (&in)[Dims<F>::NB],
                                     f32x16 (&out)[Dims<F>::NB], int lane)
