@@ -149,7 +149,7 @@ __global__ void k_tile_sums(In in, Tout *sums, int64_t n)
 // before the tile is summed by the block itself, over the input (SCAN_DIRECT) or over the tiles' sums (SCAN_SUMS), or
 // read (SCAN_OFFSETS): one, two or more launches, and a launch costs more than re-reading a few thousand values.
 enum { SCAN_DIRECT = 0, SCAN_SUMS = 1, SCAN_OFFSETS = 2 };
-constexpr int64_t kDirectTiles = 16, kSumsTiles = 2048;
+constexpr int64_t kDirectTiles = 8, kSumsTiles = 2048;
 template <class In, class Tout, int MODE>
 __global__ void k_tile_scan(In in, const Tout *pre, Tout *out, int64_t n, Publish pub)
 {
@@ -161,6 +161,7 @@ __global__ void k_tile_scan(In in, const Tout *pre, Tout *out, int64_t n, Publis
     for (int k = 0; k < kScanItems; ++k) v[k] = (base + k < n) ? (Tout)in(base + k) : (Tout)0;
     Tout off = 0;
     if (MODE == SCAN_DIRECT) {
+#pragma unroll 8
         for (int64_t i = threadIdx.x; i < tile0; i += kScanThreads) off += (Tout)in(i);
         off = block_sum(off, lds);
     } else if (MODE == SCAN_SUMS) {
@@ -243,27 +244,30 @@ __device__ inline double frac_k(const double *r, const double *n, double V)
     return ((r[0] * n[0] + r[1] * n[1]) + r[2] * n[2]) / V;
 }
 
-// err[0] = flag bits, err[1] = max species seen, err[2] = min species seen
+// err[0] = flag bits, err[1] = max species seen, err[2] = min species seen (both start at 0); one atomic pair per wavefront
+__device__ inline void track_species(int z, int32_t *err)
+{
+    int zmax = z, zmin = z;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        zmax = max(zmax, __shfl_xor(zmax, off, 64));
+        zmin = min(zmin, __shfl_xor(zmin, off, 64));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        // the running extremes only move one way, so a wavefront that cannot move them skips its atomics
+        // (thousands of atomics on one address would serialise and dominate the kernel)
+        if (zmax > __atomic_load_n(err + 1, __ATOMIC_RELAXED)) atomicMax(err + 1, zmax);
+        if (zmin < __atomic_load_n(err + 2, __ATOMIC_RELAXED)) atomicMin(err + 2, zmin);
+    }
+}
+
 // (the handle's own copies of the positions and the species are made on the way, unless pos_copy is null)
 __global__ void k_bin(int64_t N, const double *__restrict__ pos, const int32_t *__restrict__ species, double *__restrict__ pos_copy,
                       int32_t *__restrict__ species_copy, CellParams cp, int32_t *cell_of, uint32_t *wrapp, int32_t *slab_of,
                       int32_t *cell_cnt, int32_t *in_cell, int32_t *err)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    {   // species range, one atomic pair per wavefront
-        int zmax = i < N ? species[i] : 0, zmin = zmax;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            zmax = max(zmax, __shfl_xor(zmax, off, 64));
-            zmin = min(zmin, __shfl_xor(zmin, off, 64));
-        }
-        if ((threadIdx.x & 63) == 0) {
-            // the running extremes only move one way, so a wavefront that cannot move them skips its atomics
-            // (thousands of atomics on one address would serialise and dominate this kernel)
-            if (zmax > __atomic_load_n(err + 1, __ATOMIC_RELAXED)) atomicMax(err + 1, zmax);
-            if (zmin < __atomic_load_n(err + 2, __ATOMIC_RELAXED)) atomicMin(err + 2, zmin);
-        }
-    }
+    track_species(i < N ? species[i] : 0, err);
     if (i >= N) return;
     const double r[3] = {pos[3 * i], pos[3 * i + 1], pos[3 * i + 2]};
     if (pos_copy) {
@@ -784,11 +788,14 @@ __device__ inline int node_class(int s, unsigned long long nb, int q)
 // needed_by[u] (span FROM_q[slab(u)]).  The node arrays of all partitions sit one after another in one array, each
 // laid out PURE | BORDER | FROM[0] | ... | FROM[P-1] with every span in ascending atom id: a stable counting sort
 // with the bins (q, c), c = 0 PURE, 1 BORDER, 2 + s FROM[s]  (P (P + 2) bins), followed by P pseudo-bins "owned by
-// q" for the ascending list of owned atoms.  One wavefront walks kRange consecutive atoms and keeps its bins'
+// q" for the ascending list of owned atoms.  One wavefront walks a range of consecutive atoms and keeps its bins'
 // counts (first pass) or write positions (second pass) in its own LDS table; between the passes one flat scan over
 // cnt[bin][range] turns the counts into positions.
-constexpr int kRange = 512;
-inline int64_t class_entries(int64_t N, int32_t P) { return (int64_t)(P * (P + 2) + P) * ((N + kRange - 1) / kRange); }
+// A range is shorter for few partitions: below a hundred thousand atoms the wavefronts' walks are what takes the time (55 us
+// with 512 atoms at 63,000 atoms in 4 slabs, against 19), while the table of bins x ranges grows with P^2 N / range.
+inline int class_range(int32_t P) { return P <= 8 ? 128 : 512; }
+inline int64_t class_ranges(int64_t N, int32_t P) { return (N + class_range(P) - 1) / class_range(P); }
+inline int64_t class_entries(int64_t N, int32_t P) { return (int64_t)(P * (P + 2) + P) * class_ranges(N, P); }
 
 // What the local-CSR fill needs to know about a sender, in one 16-byte record per atom: its owner partition, its
 // row there, and the distance from a position in its global row to the same position in its owner's local row.
@@ -806,7 +813,7 @@ __device__ inline unsigned long long wave_or(unsigned long long v)
 
 template <bool SCATTER>
 __global__ void __launch_bounds__(256)
-k_classes(int64_t N, int P, int64_t nranges, const int32_t *__restrict__ slab_of,
+k_classes(int64_t N, int P, int range, int64_t nranges, const int32_t *__restrict__ slab_of,
           const unsigned long long *__restrict__ needed_by, int32_t *cnt, const int32_t *__restrict__ off,
           const int32_t *__restrict__ gbase, int32_t *nodes, int32_t *owned_sorted, OwnRec *own_rec,
           int32_t *ghost_local)
@@ -833,8 +840,8 @@ k_classes(int64_t N, int P, int64_t nranges, const int32_t *__restrict__ slab_of
         }
         return __builtin_amdgcn_readfirstlane(pos);
     };
-    for (int c = 0; c < kRange / 64; ++c) {
-        const int64_t u = w * kRange + c * 64 + lane;
+    for (int c = 0; c < range / 64; ++c) {
+        const int64_t u = w * range + c * 64 + lane;
         const bool valid = u < N;
         const int s = valid ? slab_of[u] : 0;
         const unsigned long long nb = valid ? needed_by[u] : 0ull;
@@ -1071,8 +1078,10 @@ __global__ void k_chunk_rows_parts(PartTab T, int32_t span, const int64_t *__res
 // The candidates of atom i are its neighbour list for the cutoff r_cut + skin at some earlier positions (`ref`),
 // sorted like the final rows.  While no atom has moved further than skin / 2 from `ref`, every pair within r_cut is
 // among them, so the exact neighbour list is the candidates that pass the fp64 test at the current positions, in
-// the same order.  One wavefront per atom; the first pass counts (and checks the displacement, assigns the slab and
-// tracks the species range as the binning kernel does), the second writes the rows.
+// the same order.  One wavefront per atom; the first pass counts, the second writes the rows.  The blocks of the first
+// pass behind those of the atoms check the displacements, assign the slabs and track the species range as the binning
+// kernel does, one atom per lane (by each atom's wavefront, with a division and two reads of the same flag words in
+// every one of them, that took longer than the counting: 259 us at 256,000 atoms, against 95).
 enum { FLAG_DISPLACED = 16 };
 template <bool FILL>
 __global__ void __launch_bounds__(256)
@@ -1082,10 +1091,12 @@ k_skin_rows(int64_t N, CellParams cp, const double *__restrict__ pos, const doub
             int32_t *senders, int32_t *recv, uint32_t *shiftp, float *d, int32_t *newpos, int32_t *err)
 {
     const int lane = threadIdx.x & 63;
-    const int64_t i = (int64_t)xcd_block() * 4 + (threadIdx.x >> 6);
-    if (i >= N) return;
-    const double xi = pos[3 * i], yi = pos[3 * i + 1], zi = pos[3 * i + 2];
-    if (!FILL && lane == 0) {
+    const int64_t row_blocks = (N + 3) / 4;
+    if (!FILL && xcd_block() >= row_blocks) {
+        const int64_t i = ((int64_t)xcd_block() - row_blocks) * 256 + threadIdx.x;
+        track_species(i < N ? species[i] : 0, err);
+        if (i >= N) return;
+        const double xi = pos[3 * i], yi = pos[3 * i + 1], zi = pos[3 * i + 2];
         const double u0 = xi - ref[3 * i], u1 = yi - ref[3 * i + 1], u2 = zi - ref[3 * i + 2];
         if (!((u0 * u0 + u1 * u1) + u2 * u2 <= half_skin2)) atomicOr(err, FLAG_DISPLACED);   // (a NaN counts as moved)
         const double r[3] = {xi, yi, zi};
@@ -1096,10 +1107,11 @@ k_skin_rows(int64_t N, CellParams cp, const double *__restrict__ pos, const doub
         int sl = (int)floor(fr * (double)cp.n_slabs);
         sl = sl > cp.n_slabs - 1 ? cp.n_slabs - 1 : sl;
         slab_of[i] = sl < 0 ? 0 : sl;
-        const int z = species[i];
-        if (z > __atomic_load_n(err + 1, __ATOMIC_RELAXED)) atomicMax(err + 1, z);
-        if (z < __atomic_load_n(err + 2, __ATOMIC_RELAXED)) atomicMin(err + 2, z);
+        return;
     }
+    const int64_t i = (int64_t)xcd_block() * 4 + (threadIdx.x >> 6);
+    if (i >= N) return;
+    const double xi = pos[3 * i], yi = pos[3 * i + 1], zi = pos[3 * i + 2];
     const int64_t e1 = crow[i + 1];
     int64_t out = FILL ? row_ptr[i] : 0;
     int cnt = 0;
@@ -1810,7 +1822,7 @@ int csr_from_candidates(mlip_graph *g, const CellParams &cp, int64_t N, int32_t 
     MLIP_TRY(g->row_ptr.ensure((size_t)(N + 1) * 8));
     const double h2 = 0.25 * g->skin * g->skin;
     const double *pos = g->pos.as<double>();
-    k_skin_rows<false><<<grid8((N + 3) / 4), 256, 0, s>>>(
+    k_skin_rows<false><<<grid8((N + 3) / 4 + (N + 255) / 256), 256, 0, s>>>(
         N, cp, pos, g->ref_pos.as<double>(), h2, g->species.as<int32_t>(), g->cand_row_ptr.as<int64_t>(),
         g->cand_senders.as<int32_t>(), g->cand_shiftp.as<uint32_t>(), g->counts.as<int32_t>(), g->slab_of.as<int32_t>(),
         nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, err);
@@ -1954,15 +1966,15 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
         MLIP_HIP(hipGetLastError());
         // ghost entries per atom and their scan: where the (partition -> local index) entries of an atom start
         MLIP_TRY(scan(ScanBits{g->needed_by}, st.gbase.as<int32_t>(), N, g->scan_tmp, s));
-        // class counts of every (partition, span) bin per range of kRange atoms, one flat scan
+        // class counts of every (partition, span) bin per range of atoms, one flat scan
         const int B1 = P * (P + 2), nbins = B1 + P;
-        const int64_t nranges = (N + kRange - 1) / kRange;
+        const int64_t nranges = class_ranges(N, P);
         const int64_t nent = class_entries(N, P);
         MLIP_TRY(g->class_off.ensure((size_t)(nent + 1) * 4));
         const int cwaves = ((size_t)nbins * 4 * 4 > 60000) ? 2 : 4;   // wavefronts per block: each keeps a table of nbins counters in LDS
         const size_t clds = (size_t)cwaves * nbins * 4;
         const unsigned cblocks = (unsigned)((nranges + cwaves - 1) / cwaves);
-        k_classes<false><<<cblocks, cwaves * 64, clds, s>>>(N, P, nranges, g->slab_of.as<int32_t>(),
+        k_classes<false><<<cblocks, cwaves * 64, clds, s>>>(N, P, class_range(P), nranges, g->slab_of.as<int32_t>(),
                                                             g->needed_by, z.class_cnt,
                                                             nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
         MLIP_HIP(hipGetLastError());
@@ -2010,7 +2022,7 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
         MLIP_TRY(st.rowlen.ensure((size_t)(TL + P + 1) * 4));
         MLIP_TRY(st.row_abs.ensure((size_t)(TL + P + 1) * 8));
         MLIP_TRY(st.row_ptr.ensure((size_t)(TL + P + 1) * 8));
-        k_classes<true><<<cblocks, cwaves * 64, clds, s>>>(N, P, nranges, g->slab_of.as<int32_t>(),
+        k_classes<true><<<cblocks, cwaves * 64, clds, s>>>(N, P, class_range(P), nranges, g->slab_of.as<int32_t>(),
                                                            g->needed_by, nullptr,
                                                            g->class_off.as<int32_t>(), st.gbase.as<int32_t>(),
                                                            st.nodes.as<int32_t>(), st.owned_sorted.as<int32_t>(),

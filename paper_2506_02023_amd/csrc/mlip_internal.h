@@ -95,15 +95,16 @@ inline unsigned grid8(int64_t blocks) { return (unsigned)(((blocks > 0 ? blocks 
 // Work item of the edge kernels: the rows whose first edge lies in one span of `span` edges.  A wavefront walks an item
 // serially (about 5 us per 32 edges when little else runs), so the span is taken from the edges of the launch: 8 items
 // for each of the 2048 wavefronts that are resident at once (256 compute units, 8 wavefronts of the reverse kernel on
-// each), at least 32 edges (one tile) and at most 1024 (longer items no longer pay for their pipeline fill, shorter ones
-// do at a million atoms).  Measured, us per pass of graph + energy + forces with 1024 edges throughout -> this rule: 500 atoms
-// 1587 -> 632, 4,000 atoms 1487 -> 643, 108,000 atoms in 8 slabs 4732 -> 4233, a million atoms unchanged; 4 items per
-// wavefront 4302 and 2 items 4591 at 108,000 atoms, a least span of 64 edges 697 at 500 atoms.
-constexpr int kEdgeWaves = 2048, kItemsPerWave = 8, kSpanMin = 32, kSpanMax = 1024;
+// each), at most 1024 edges (longer items no longer pay for their pipeline fill, shorter ones do at a million atoms), and
+// at least two tiles of 32, or one where there are not even 1024 items of two.  Measured, us per pass of graph + energy +
+// forces: 1024 edges throughout -> 8 items per wavefront 500 atoms 1587 -> 632, 108,000 atoms in 8 slabs 4732 -> 4233, a
+// million unchanged (4 items 4302 and 2 items 4591 at 108,000); least span 32 -> 64 later 4,000 atoms 367 -> 347, four
+// models on 16,000 atoms 1190 -> 1106, but 500 atoms 252 -> 275.
+constexpr int kEdgeWaves = 2048, kItemsPerWave = 8, kSpanMin = 64, kSpanMax = 1024;
 inline int32_t chunk_span(int64_t n_edges)
 {
-    const int64_t even = n_edges / (kEdgeWaves * kItemsPerWave);
-    return (int32_t)(even < kSpanMin ? kSpanMin : even > kSpanMax ? kSpanMax : even);
+    const int64_t even = n_edges / (kEdgeWaves * kItemsPerWave), least = n_edges < 1024 * kSpanMin ? kSpanMin / 2 : kSpanMin;
+    return (int32_t)(even < least ? least : even > kSpanMax ? kSpanMax : even);
 }
 inline int64_t chunks_of(int64_t n_edges, int32_t span) { return n_edges > 0 ? (n_edges + span - 1) / span : 1; }
 
