@@ -14,6 +14,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 namespace mlip {
 
@@ -103,9 +104,9 @@ template <class T> struct ScanArray {
     const T *p;
     __device__ T operator()(int64_t i) const { return p[i]; }
 };
-struct ScanSum {
-    const int32_t *p, *q;
-    __device__ int32_t operator()(int64_t i) const { return p[i] + q[i]; }
+struct ScanSum {   // (in another order)
+    const int32_t *p, *q, *at;
+    __device__ int32_t operator()(int64_t i) const { return p[at[i]] + q[at[i]]; }
 };
 struct ScanBits {
     const unsigned long long *p;
@@ -305,13 +306,14 @@ __global__ void k_bin(int64_t N, const double *__restrict__ pos, const int32_t *
 
 __global__ void k_fill_cells(int64_t N, const double *__restrict__ pos, const int32_t *__restrict__ cell_of,
                              const uint32_t *__restrict__ wrapp, const int32_t *__restrict__ cell_start,
-                             const int32_t *__restrict__ in_cell, int32_t *sid, double *sx, double *sy, double *sz,
+                             int32_t *__restrict__ in_cell, int32_t *sid, double *sx, double *sy, double *sz,
                              uint32_t *swrap)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= N) return;
     const int32_t c = cell_of[i];
     const int32_t slot = cell_start[c] + in_cell[i];
+    in_cell[i] = slot;   // from here on: the atom's place in cell order
     sid[slot] = (int32_t)i;
     sx[slot] = pos[3 * i];
     sy[slot] = pos[3 * i + 1];
@@ -462,38 +464,40 @@ k_sort_rows(int64_t N, CellParams cp, const double *__restrict__ pos, const int6
 // Every pair {(i <- j, S), (j <- i, -S)} is tested once, by the atom that comes first in cell order: the atom at
 // sorted position s looks only at positions q > s (cells before its own in the cell order are skipped; q = s only
 // for images of the atom itself, of which the one with the larger packed shift is taken).  The edge predicate is symmetric bit for bit (negating every term negates the
-// differences exactly), so one test decides both edges.  The finder parks the key of its own edge in its "own"
+// differences exactly), so one test decides both edges.  Staging rows, counters and ranks are numbered in cell order (an
+// atom's partners are near it there, whatever the order of the input: handing over the reverse edges took 123 us by input
+// order for 63,000 shuffled atoms, 32 us in cell order).  The finder parks the key of its own edge in its "own"
 // staging row (slots in the order of its finds) and the key of the reverse edge in the partner's "partner" staging row (atomic
-// counter), and notes in each entry the slot of the other one.  After the rows are sorted, the reverse-edge index
+// counter), and notes the partner's place and the slot there with its own entry.  After the rows are sorted, the reverse-edge index
 // follows from these notes without any search: half the candidate loads of the one-sided search and no binary
 // searches.  Rows are sorted afterwards, so the order in which the atomics hand out slots does not matter.
 constexpr int64_t kSharedCells = 4096;   // below this many cells four wavefronts share one (four cells fit a block otherwise)
 constexpr int kOwn = 64, kPar = 64;   // staging slots per atom for edges found by the atom itself / by its partners
 
-// One cell per WPC wavefronts.  The candidates of a cell's atoms are the same: lanes first take the surrounding cells (64
+// One cell per wavefront or (SHARED) per block of four.  The candidates of a cell's atoms are the same: lanes first take the surrounding cells (64
 // at a time: first atom, length, image), then their atoms, flattened (a cell holds about 11), 64 at a time; every lane
 // keeps one candidate in registers and the cell's own atoms are tested against it one after another, their records
-// broadcast from the lanes that loaded them.  The wavefronts of a cell share its atoms (round-robin).  A candidate is loaded once
+// broadcast from the lanes that loaded them.  Wavefronts that share a cell take its candidates in turn and count an
+// atom's finds in LDS.  A candidate is loaded once
 // per cell instead of once per atom, and nothing waits in a chain of dependent loads: one thread per atom walking the
 // cells was bound by that chain, 118 us at any size below 60,000 atoms and 544 us at a million;
-// here 21 us at 500 atoms, 28 us at 32,000 and 379 us at a million.
-template <int WPC>
+// here 19 us at 500 atoms, 28 us at 32,000 and 390 us at a million.
+template <bool SHARED>
 __global__ void __launch_bounds__(256)
 k_neighbours_pairs(int64_t n_cells, CellParams cp, const int32_t *__restrict__ cell_start,
                    const int32_t *__restrict__ sid, const double *__restrict__ sx,
                    const double *__restrict__ sy, const double *__restrict__ sz,
-                   const uint32_t *__restrict__ swrap, uint64_t *__restrict__ stage_own, int32_t *__restrict__ n_own,
-                   int32_t *err)
+                   const uint32_t *__restrict__ swrap, uint64_t *__restrict__ stage_own,
+                   int32_t *__restrict__ stage_q, int32_t *__restrict__ n_own, int32_t *err)
 {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t unit = (int64_t)xcd_block() * 4 + wave;
-    const int64_t c64 = unit / WPC;
-    if (c64 >= n_cells) return;
+    __shared__ int32_t found[64];   // SHARED: edges found so far by the cell's atoms
+    const int64_t c64 = SHARED ? (int64_t)xcd_block() : (int64_t)xcd_block() * 4 + wave;
+    if (c64 >= n_cells) return;   // (SHARED: the whole block)
     const int32_t c = (int32_t)c64;
-    const int part = (int)(unit % WPC);   // which of the cell's atoms this wavefront takes: part, part + WPC, ...
     const int32_t h0 = __builtin_amdgcn_readfirstlane(cell_start[c]);
     const int32_t h1 = __builtin_amdgcn_readfirstlane(cell_start[c + 1]);
-    if (h0 + part >= h1) return;
+    if (h0 >= h1) return;
     int cr = c;
     const int b2 = cr % cp.nb[2];
     cr /= cp.nb[2];
@@ -503,11 +507,15 @@ k_neighbours_pairs(int64_t n_cells, CellParams cp, const int32_t *__restrict__ c
     const int64_t n_around = (int64_t)w0 * w1 * w2;
     bool coincident = false, overflow = false;
 
-    // the cell's own atoms, up to 64 of this wavefront's share at a time: lane k holds the k-th one
-    for (int32_t hb = h0 + part; hb < h1; hb += 64 * WPC) {
-        const int n_home = min(64, (h1 - hb + WPC - 1) / WPC);
-        const int32_t hq = min(hb + lane * WPC, h1 - 1);
-        const int32_t hid = sid[hq];
+    // the cell's own atoms, up to 64 at a time: lane k holds the k-th one
+    for (int32_t hb = h0; hb < h1; hb += 64) {
+        const int n_home = min(64, h1 - hb);
+        const int32_t hq = min(hb + lane, h1 - 1);
+        if (SHARED) {
+            __syncthreads();
+            if (threadIdx.x < 64) found[threadIdx.x] = 0;
+            __syncthreads();
+        }
         const uint32_t hw = swrap[hq];
         const double hx = sx[hq], hy = sy[hq], hz = sz[hq];
         int32_t cnt = 0;   // lane k: edges found by the k-th atom
@@ -531,7 +539,7 @@ k_neighbours_pairs(int64_t n_cells, CellParams cp, const int32_t *__restrict__ c
             }
             const int32_t inc = wave_inclusive_scan(len);
             const int32_t total = __builtin_amdgcn_readlane(inc, 63);
-            for (int32_t t0 = 0; t0 < total; t0 += 64) {
+            for (int32_t t0 = SHARED ? 64 * wave : 0; t0 < total; t0 += SHARED ? 256 : 64) {
                 // lane = candidate t: the cell it lies in is the first whose running total exceeds t
                 const int32_t t = t0 + lane;
                 int k = 0;
@@ -566,7 +574,7 @@ k_neighbours_pairs(int64_t n_cells, CellParams cp, const int32_t *__restrict__ c
                         s1 = ((double)S0 * cp.C[1] + (double)S1 * cp.C[4]) + (double)S2 * cp.C[7];
                         s2 = ((double)S0 * cp.C[2] + (double)S1 * cp.C[5]) + (double)S2 * cp.C[8];
                     }
-                    const int32_t s = hb + hk * WPC;
+                    const int32_t s = hb + hk;
                     const double t0d = (xj - readlane_f64(hx, hk)) + s0;
                     const double t1d = (yj - readlane_f64(hy, hk)) + s1;
                     const double t2d = (zj - readlane_f64(hz, hk)) + s2;
@@ -577,19 +585,33 @@ k_neighbours_pairs(int64_t n_cells, CellParams cp, const int32_t *__restrict__ c
                     const bool hit = mine && d2 <= cp.rc2;
                     const unsigned long long m = __ballot(hit);
                     if (m == 0) continue;
-                    const int32_t at = __builtin_amdgcn_readlane(cnt, hk);
+                    int32_t at;
+                    if (SHARED) {
+                        int32_t v = 0;
+                        if (lane == 0) v = atomicAdd(&found[hk], __popcll(m));
+                        at = __builtin_amdgcn_readfirstlane(v);
+                    } else {
+                        at = __builtin_amdgcn_readlane(cnt, hk);
+                        if (lane == hk) cnt += __popcll(m);
+                    }
                     if (hit) {
                         if (d2 == 0.0) coincident = true;
                         const int slot = at + __popcll(m & ((1ull << lane) - 1ull));
-                        const int64_t i = __builtin_amdgcn_readlane(hid, hk);
-                        if (slot < kOwn) stage_own[i * kOwn + slot] = ((uint64_t)(uint32_t)j << 32) | sp;
-                        else overflow = true;
+                        if (slot < kOwn) {
+                            stage_own[(int64_t)s * kOwn + slot] = ((uint64_t)(uint32_t)j << 32) | sp;
+                            stage_q[(int64_t)s * kOwn + slot] = q;
+                        } else {
+                            overflow = true;
+                        }
                     }
-                    if (lane == hk) cnt += __popcll(m);
                 }
             }
         }
-        if (lane < n_home) n_own[hid] = cnt;
+        if (SHARED) {
+            __syncthreads();
+            cnt = found[lane];
+        }
+        if (lane < n_home && (!SHARED || wave == 0)) n_own[hb + lane] = cnt;
     }
     if (overflow) atomicOr(err, FLAG_STAGE_OVERFLOW);
     if (coincident) atomicOr(err, ERR_COINCIDENT);
@@ -598,51 +620,49 @@ k_neighbours_pairs(int64_t n_cells, CellParams cp, const int32_t *__restrict__ c
 // The reverse edges, in a pass of their own over what the search parked (one thread per own slot): the slot that a
 // partner's counter hands out is not needed during the search, and the atomics travel past the L2, so they are
 // issued from as many threads as possible instead of one after another inside the search loop.
-__global__ void k_pair_partners(int64_t N, const int32_t *__restrict__ n_own, const uint64_t *__restrict__ stage_own,
-                                uint64_t *stage_par, uint8_t *pslot_own, uint8_t *pslot_par, int32_t *n_par, int32_t *err)
+__global__ void k_pair_partners(int64_t N, const int32_t *__restrict__ sid, const int32_t *__restrict__ n_own,
+                                const uint64_t *__restrict__ stage_own, const int32_t *__restrict__ stage_q,
+                                uint64_t *stage_par, uint8_t *pslot_own, int32_t *n_par, int32_t *err)
 {
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t i = idx / kOwn;
+    const int64_t s = idx / kOwn;
     const int a = (int)(idx % kOwn);
-    if (i >= N || a >= n_own[i]) return;
+    if (s >= N || a >= n_own[s]) return;
     const uint64_t key = stage_own[idx];
-    const int64_t j = (int64_t)(key >> 32);
+    const int64_t q = stage_q[idx];
     int S0, S1, S2;
     unpack3((uint32_t)key, S0, S1, S2);
-    const int b = atomicAdd(&n_par[j], 1);
+    const int b = atomicAdd(&n_par[q], 1);
     pslot_own[idx] = (uint8_t)(b < 255 ? b : 255);
-    if (b < kPar) {
-        stage_par[j * kPar + b] = ((uint64_t)(uint32_t)i << 32) | pack3(-S0, -S1, -S2);
-        pslot_par[j * kPar + b] = (uint8_t)a;
-    } else {
-        atomicOr(err, FLAG_STAGE_OVERFLOW);
-    }
+    if (b < kPar) stage_par[q * kPar + b] = ((uint64_t)(uint32_t)sid[s] << 32) | pack3(-S0, -S1, -S2);
+    else atomicOr(err, FLAG_STAGE_OVERFLOW);
 }
 
 // k_sort_rows for the pair-wise search: the row's keys come from the atom's two staging rows; the rank of every
 // staging slot is kept for the reverse-edge index
 __global__ void __launch_bounds__(64)
-k_sort_rows_pairs(int64_t N, CellParams cp, const double *__restrict__ pos, const int64_t *__restrict__ row_ptr,
-                  const uint64_t *__restrict__ stage_own, const uint64_t *__restrict__ stage_par,
+k_sort_rows_pairs(int64_t N, CellParams cp, const double *__restrict__ pos, const int32_t *__restrict__ sid,
+                  const int64_t *__restrict__ row_ptr, const uint64_t *__restrict__ stage_own, const uint64_t *__restrict__ stage_par,
                   const int32_t *__restrict__ n_own, uint8_t *rank_own, uint8_t *rank_par, int32_t *senders, int32_t *recv,
                   uint32_t *shiftp, float *d)
 {
     __shared__ uint64_t lds[kOwn + kPar];
-    const int64_t i = xcd_block();
-    if (i >= N) return;   // (whole block: the grid is rounded up to a multiple of 8)
+    const int64_t s = xcd_block();
+    if (s >= N) return;   // (whole block: the grid is rounded up to a multiple of 8)
     const int lane = threadIdx.x;
+    const int64_t i = sid[s];
+    const int no = n_own[s];
     const int64_t base = row_ptr[i];
     const int n = (int)(row_ptr[i + 1] - base);
-    const int no = n_own[i];
     for (int m = lane; m < n; m += 64)
-        lds[m] = (m < no) ? stage_own[i * kOwn + m] : stage_par[i * kPar + (m - no)];
+        lds[m] = (m < no) ? stage_own[s * kOwn + m] : stage_par[s * kPar + (m - no)];
     __syncthreads();
     const double xi = pos[3 * i], yi = pos[3 * i + 1], zi = pos[3 * i + 2];
     for (int m = lane; m < n; m += 64) {
         const uint64_t key = lds[m];
         int rank = 0;
         for (int t = 0; t < n; ++t) rank += (lds[t] < key) ? 1 : 0;
-        if (m < no) rank_own[i * kOwn + m] = (uint8_t)rank; else rank_par[i * kPar + (m - no)] = (uint8_t)rank;
+        if (m < no) rank_own[s * kOwn + m] = (uint8_t)rank; else rank_par[s * kPar + (m - no)] = (uint8_t)rank;
         const int64_t e = base + rank;
         const int32_t j = (int32_t)(key >> 32);
         const uint32_t sp = (uint32_t)key;
@@ -662,19 +682,20 @@ k_sort_rows_pairs(int64_t N, CellParams cp, const double *__restrict__ pos, cons
 // reverse-edge index from the pair notes: the edge in own slot a of atom i and the edge in partner slot b of atom j
 // are each other's reverse; 32 lanes per atom
 __global__ void __launch_bounds__(256)
-k_mirror_pairs(int64_t N, const int64_t *__restrict__ row_ptr, const uint64_t *__restrict__ stage_own,
+k_mirror_pairs(int64_t N, const int32_t *__restrict__ sid, const int64_t *__restrict__ row_ptr,
+               const uint64_t *__restrict__ stage_own, const int32_t *__restrict__ stage_q,
                const uint8_t *__restrict__ pslot_own, const int32_t *__restrict__ n_own,
                const uint8_t *__restrict__ rank_own, const uint8_t *__restrict__ rank_par, int32_t *__restrict__ mirror)
 {
-    const int64_t i = (int64_t)xcd_block() * 8 + (threadIdx.x >> 5);
-    if (i >= N) return;
-    const int no = n_own[i];
-    const int64_t rp = row_ptr[i];
+    const int64_t s = (int64_t)xcd_block() * 8 + (threadIdx.x >> 5);
+    if (s >= N) return;
+    const int no = n_own[s];
+    const int64_t rp = row_ptr[sid[s]];
     for (int a = threadIdx.x & 31; a < no; a += 32) {
-        const int64_t j = (int64_t)(stage_own[i * kOwn + a] >> 32);
-        const int b = pslot_own[i * kOwn + a];
-        const int32_t e = (int32_t)(rp + rank_own[i * kOwn + a]);
-        const int32_t m = (int32_t)(row_ptr[j] + rank_par[j * kPar + b]);
+        const int64_t j = (int64_t)(stage_own[s * kOwn + a] >> 32), q = stage_q[s * kOwn + a];
+        const int b = pslot_own[s * kOwn + a];
+        const int32_t e = (int32_t)(rp + rank_own[s * kOwn + a]);
+        const int32_t m = (int32_t)(row_ptr[j] + rank_par[q * kPar + b]);
         mirror[e] = m;
         mirror[m] = e;
     }
@@ -1728,29 +1749,31 @@ int search_csr(mlip_graph *g, const CellParams &cp, int64_t N, int32_t P, const 
     int64_t E = 0;
     int32_t flags = 0;
     // Pair-wise search (every pair tested once, reverse-edge index without a search) unless its staging rows
-    // (1.25 KB per atom) would take more than 8 GB; an atom with more neighbours than the staging rows hold
+    // (1.5 KB per atom) would take more than 8 GB; an atom with more neighbours than the staging rows hold
     // (kOwn found by itself, kPar by its partners) sets FLAG_STAGE_OVERFLOW and the one-sided search below runs instead
     bool done = false;
     if ((size_t)N * (kOwn + kPar) * 10 <= ((size_t)8 << 30)) {
         MLIP_TRY(g->stage.ensure((size_t)N * (kOwn + kPar) * 8));
-        MLIP_TRY(g->pair_aux.ensure((size_t)N * (4 + 2 * (kOwn + kPar))));
+        MLIP_TRY(g->pair_aux.ensure((size_t)N * (4 + 4 * kOwn + 2 * kOwn + kPar)));
         uint64_t *stage_own = g->stage.as<uint64_t>(), *stage_par = stage_own + (size_t)N * kOwn;
         int32_t *n_own = g->pair_aux.as<int32_t>(), *n_par = z.n_par;
-        uint8_t *pslot_own = reinterpret_cast<uint8_t *>(n_own + N), *pslot_par = pslot_own + (size_t)N * kOwn;
-        uint8_t *rank_own = pslot_par + (size_t)N * kPar, *rank_par = rank_own + (size_t)N * kOwn;
+        int32_t *stage_q = n_own + N;
+        uint8_t *pslot_own = reinterpret_cast<uint8_t *>(stage_q + (size_t)N * kOwn);
+        uint8_t *rank_own = pslot_own + (size_t)N * kOwn, *rank_par = rank_own + (size_t)N * kOwn;
         // few cells: four wavefronts share each, so that the chip has something to do and a crowded cell is not one chain
-        if (ncell < kSharedCells)
-            k_neighbours_pairs<4><<<grid8(ncell), 256, 0, s>>>(
+        auto search = [&](auto shared) {
+            constexpr bool SHARED = decltype(shared)::value;
+            k_neighbours_pairs<SHARED><<<grid8(SHARED ? ncell : (ncell + 3) / 4), 256, 0, s>>>(
                 ncell, cp, g->cell_start.as<int32_t>(), g->sid.as<int32_t>(), g->sx.as<double>(), g->sy.as<double>(),
-                g->sz.as<double>(), g->swrap.as<uint32_t>(), stage_own, n_own, err);
-        else
-            k_neighbours_pairs<1><<<grid8((ncell + 3) / 4), 256, 0, s>>>(
-                ncell, cp, g->cell_start.as<int32_t>(), g->sid.as<int32_t>(), g->sx.as<double>(), g->sy.as<double>(),
-                g->sz.as<double>(), g->swrap.as<uint32_t>(), stage_own, n_own, err);
+                g->sz.as<double>(), g->swrap.as<uint32_t>(), stage_own, stage_q, n_own, err);
+        };
+        if (ncell < kSharedCells) search(std::true_type{});
+        else search(std::false_type{});
         MLIP_HIP(hipGetLastError());
-        k_pair_partners<<<blocks_for(N * kOwn, 256), 256, 0, s>>>(N, n_own, stage_own, stage_par, pslot_own, pslot_par, n_par, err);
+        k_pair_partners<<<blocks_for(N * kOwn, 256), 256, 0, s>>>(N, g->sid.as<int32_t>(), n_own, stage_own, stage_q, stage_par,
+                                                                  pslot_own, n_par, err);
         MLIP_HIP(hipGetLastError());
-        MLIP_TRY(scan(ScanSum{n_own, n_par}, out.row_ptr->as<int64_t>(), N, g->scan_tmp, s, publish));
+        MLIP_TRY(scan(ScanSum{n_own, n_par, g->in_cell.as<int32_t>()}, out.row_ptr->as<int64_t>(), N, g->scan_tmp, s, publish));
         const int rc = read_counts_and_flags(g, &E, &flags);   // first synchronisation
         if (!(flags & FLAG_STAGE_OVERFLOW)) {
             MLIP_TRY(rc);
@@ -1759,14 +1782,15 @@ int search_csr(mlip_graph *g, const CellParams &cp, int64_t N, int32_t P, const 
             MLIP_TRY(out.shiftp->ensure(Ecap * 4));
             MLIP_TRY(out.recv->ensure(Ecap * 4));
             MLIP_TRY(out.d->ensure(Ecap * 4));
-            k_sort_rows_pairs<<<grid8(N), 64, 0, s>>>(N, cp, pos, out.row_ptr->as<int64_t>(), stage_own, stage_par, n_own,
+            k_sort_rows_pairs<<<grid8(N), 64, 0, s>>>(N, cp, pos, g->sid.as<int32_t>(), out.row_ptr->as<int64_t>(), stage_own, stage_par, n_own,
                                                       rank_own, rank_par, out.senders->as<int32_t>(),
                                                       out.recv->as<int32_t>(), out.shiftp->as<uint32_t>(),
                                                       out.d->as<float>());
             MLIP_HIP(hipGetLastError());
             if (out.mirror) {
                 MLIP_TRY(out.mirror->ensure(Ecap * 4));
-                k_mirror_pairs<<<grid8((N + 7) / 8), 256, 0, s>>>(N, out.row_ptr->as<int64_t>(), stage_own, pslot_own, n_own,
+                k_mirror_pairs<<<grid8((N + 7) / 8), 256, 0, s>>>(N, g->sid.as<int32_t>(), out.row_ptr->as<int64_t>(),
+                                                                  stage_own, stage_q, pslot_own, n_own,
                                                                   rank_own, rank_par, out.mirror->as<int32_t>());
                 MLIP_HIP(hipGetLastError());
             }
