@@ -56,7 +56,7 @@ struct Packs {  // offsets (floats) into the packed-weight buffer
 Packs pack_layout(int F, int L)
 {
     Packs p;
-    const size_t ff = (size_t)F * F * 3 / 2, p1 = (size_t)(F / 32) * 4 * 64;   // three bf16 parts
+    const size_t ff = (size_t)F * F * 3 / 2, p1 = (size_t)(F / 32) * 3 * 64 * 2;   // three bf16 parts
     p.A1 = 0;
     p.A1s = p1;
     p.W2t = 2 * p1;
@@ -76,7 +76,7 @@ constexpr int kNodeBlocks = 256;   // one per compute unit (512: 38 us against 2
 
 template <int F> struct Lds {
     using D = Dims<F>;
-    static constexpr size_t edge_fwd(int prec) { return sizeof(float) * (pack_floats<F>(prec) + kFwdWaves * D::TILE); }
+    static constexpr size_t edge_fwd(int prec) { return sizeof(float) * (pack_floats<F>(prec) + D::PACK1 + kFwdWaves * D::TILE); }
     static constexpr size_t edge_bwd(int prec) { return sizeof(float) * (pack_floats<F>(prec) + D::PACK1 + kBwdWaves * kQueue * D::FS); }
 };
 

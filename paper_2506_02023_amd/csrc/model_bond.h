@@ -502,8 +502,6 @@ __global__ void __launch_bounds__(BondStage<STAGE>::NW * 64) k_bond_mlp(BondArgs
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int c32 = lane & 31, h4 = 4 * (lane >> 5);
-    RegPack1<F> W0;   // We0 as the A operands of the K = 8 product
-    if (STAGE == BOND_HEAD || STAGE == BOND_TAIL || STAGE == BOND_E0BAR) load_pack1<F>(W0, A.We0p, lane);
     const int64_t n_tiles = (A.n + 31) / 32;
     const int64_t stride = (int64_t)gridDim.x * NW;
 
@@ -610,10 +608,10 @@ __global__ void __launch_bounds__(BondStage<STAGE>::NW * 64) k_bond_mlp(BondArgs
         f32x16 acc[NB];
 
         if (STAGE == BOND_HEAD) {
-            float bb[8], db[8];
-            radial_basis<false>(ok ? A.d[row] : A.bp.rc, A.bp, bb, db);   // 0 at the cutoff
+            float bb[4], db[4];
+            radial_basis<false>(ok ? A.d[row] : A.bp.rc, A.bp, lane >> 5, bb, db);   // 0 at the cutoff
             f32x16 e0[NB];
-            gemm_k8r<F>(W0, bb, e0, lane);
+            gemm_k8<F>(A.We0p, bb, e0, lane);
             mul(Fresh{}, packs, e0, acc);
             store_rows(A.P, row, ok, acc);
             mul(Fresh{}, packs + PACK, e0, acc);
@@ -627,9 +625,9 @@ __global__ void __launch_bounds__(BondStage<STAGE>::NW * 64) k_bond_mlp(BondArgs
             mul(Fresh{}, packs, e1, acc);
             store_rows(A.m, row, ok, acc);
             {
-                float bb[8], db[8];
-                radial_basis<false>(dc, A.bp, bb, db);
-                gemm_k8r<F>(W0, bb, e1, lane);   // e0, as in HEAD
+                float bb[4], db[4];
+                radial_basis<false>(dc, A.bp, lane >> 5, bb, db);
+                gemm_k8<F>(A.We0p, bb, e1, lane);   // e0, as in HEAD
             }
 #pragma unroll
             for (int b = 0; b < NB; ++b)
@@ -677,9 +675,9 @@ __global__ void __launch_bounds__(BondStage<STAGE>::NW * 64) k_bond_mlp(BondArgs
             widen_rows(pre, x);
             if (more) fetch(ti + stride);
             mul(Add{}, packs + PACK, x, acc);
-            float bb[8], db[8];
-            radial_basis<true>(ok ? A.d[row] : A.bp.rc, A.bp, bb, db);
-            gemm_k8r<F>(W0, db, x, lane);   // We0^T dbbond/dd
+            float bb[4], db[4];
+            radial_basis<true>(ok ? A.d[row] : A.bp.rc, A.bp, lane >> 5, bb, db);
+            gemm_k8<F>(A.We0p, db, x, lane);   // We0^T dbbond/dd
             float part = 0.f;
 #pragma unroll
             for (int b = 0; b < NB; ++b)

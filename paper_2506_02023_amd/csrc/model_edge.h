@@ -156,7 +156,10 @@ __global__ void __launch_bounds__(kFwdWaves * 64, 3) k_edge_fwd(EdgeBatch B)
     using D = Dims<F>;
     extern __shared__ float lds[];
     float *A2t = lds;
-    float *tiles = A2t + pack_floats<F>(PREC);
+    float *A1s = A2t + pack_floats<F>(PREC);
+    float *tiles = A1s + D::PACK1;
+    for (int i = threadIdx.x; i < D::PACK1 / 4; i += kFwdWaves * 64)
+        reinterpret_cast<f32x4 *>(A1s)[i] = reinterpret_cast<const f32x4 *>(B.c.A1s)[i];
     for (int i = threadIdx.x; i < pack_floats<F>(PREC) / 4; i += kFwdWaves * 64)
         reinterpret_cast<f32x4 *>(A2t)[i] = reinterpret_cast<const f32x4 *>(B.c.A2t)[i];
     __syncthreads();
@@ -165,8 +168,6 @@ __global__ void __launch_bounds__(kFwdWaves * 64, 3) k_edge_fwd(EdgeBatch B)
     const unsigned f = lane & (F - 1);
     float *tile = tiles + wave * D::TILE;
     const EdgeCommon &C = B.c;
-    RegPack1<F> W1;
-    load_pack1<F>(W1, C.A1s, lane);
     const ItemQueue items = edge_items(B.chunk_start[B.n], B.work, wave, kFwdWaves);
     int64_t item = items.first;
     int32_t drawn = 0;
@@ -209,8 +210,8 @@ __global__ void __launch_bounds__(kFwdWaves * 64, 3) k_edge_fwd(EdgeBatch B)
     }
     for (int32_t tb = e_lo; tb < e_hi; tb += 32) {
         const bool valid = tb + c32 < e_hi;
-        float b[8], db[8];
-        radial_basis<false>(valid ? dv : C.bp.rc, C.bp, b, db);
+        float b[4], db[4];
+        radial_basis<false>(valid ? dv : C.bp.rc, C.bp, lane >> 5, b, db);
         // sender rows of this tile: issued now, consumed after the MFMA chain.  An edge past the end gathers the
         // row of the item's last edge; its filter is zero.
         float gv[32];
@@ -229,7 +230,7 @@ __global__ void __launch_bounds__(kFwdWaves * 64, 3) k_edge_fwd(EdgeBatch B)
         if (keep_w) uv = A.uslot[en];
         __builtin_amdgcn_sched_barrier(0);
         f32x16 t[D::NB], w[D::NB];
-        gemm_k8r<F>(W1, b, t, lane);
+        gemm_k8<F>(A1s, b, t, lane);
 #pragma unroll
         for (int bb = 0; bb < D::NB; ++bb)
 #pragma unroll
@@ -326,7 +327,8 @@ __global__ void __launch_bounds__(kBwdWaves * 64, kBwdWaves == 4 ? 2 : 1) k_edge
     float *queues = A1l + D::PACK1;
     for (int i = threadIdx.x; i < pack_floats<F>(PREC) / 4; i += kBwdWaves * 64)
         reinterpret_cast<f32x4 *>(A2n)[i] = reinterpret_cast<const f32x4 *>(B.c.A2n)[i];
-    for (int i = threadIdx.x; i < D::PACK1; i += kBwdWaves * 64) A1l[i] = B.c.A1[i];
+    for (int i = threadIdx.x; i < D::PACK1 / 4; i += kBwdWaves * 64)
+        reinterpret_cast<f32x4 *>(A1l)[i] = reinterpret_cast<const f32x4 *>(B.c.A1)[i];
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int c32 = lane & 31;
@@ -490,26 +492,6 @@ __global__ void __launch_bounds__(kBwdWaves * 64, kBwdWaves == 4 ? 2 : 1) k_edge
         const float d_q = rec[2];
         const int32_t e2 = valid ? e_q : 0, m2 = valid ? m_q : 0;
         const float d2 = valid ? d_q : C.bp.rc;   // rc: zero derivative
-        float b[8], db[8];
-        radial_basis<true>(d2, C.bp, b, db);
-#pragma unroll
-        for (int n = 0; n < 8; ++n) b[n] *= kSiluScale;   // pre-activations come out as t' = c t
-        f32x16 t[D::NB];   // ds_k/dd = SiLU'(t_k) c_k, one block of 32 features at a time (fewer live registers)
-#pragma unroll
-        for (int bb = 0; bb < D::NB; ++bb) {
-            f32x16 cg;
-            RegPack1<F> W1;   // this block's W1 operands, from LDS
-#pragma unroll
-            for (int s4 = 0; s4 < 4; ++s4) W1.v[bb][s4] = A1l[(bb * 4 + s4) * 64 + lane];
-            gemm_k8r_block<F>(W1, b, bb, t[bb], lane);
-            gemm_k8r_block<F>(W1, db, bb, cg, lane);
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float sg = sigmoid_scaled(t[bb][r]);
-                const float ss = t[bb][r] * sg * kSiluScaleInv;               // SiLU(t)
-                t[bb][r] = fmaf(ss, 1.0f - sg, sg) * cg[r];
-            }
-        }
         f32x16 sb[D::NB];
         if (PREC == kPrecBf16)   // sbar[k] = sum_f W2[k][f] wsym[f]
             gemm_row_bf16<F>(reinterpret_cast<const __bf16 *>(A2n), Q + slot * FS, sb, lane);
@@ -517,11 +499,24 @@ __global__ void __launch_bounds__(kBwdWaves * 64, kBwdWaves == 4 ? 2 : 1) k_edge
             gemm_row_f16x3<F>(reinterpret_cast<const _Float16 *>(A2n), Q + slot * FS, sb, lane);
         else
             gemm_row_bf16x3<F>(reinterpret_cast<const __bf16 *>(A2n), Q + slot * FS, sb, lane);
-        float part = 0.f;
+        float b[4], db[4];
+        radial_basis<true>(d2, C.bp, lane >> 5, b, db);
 #pragma unroll
-        for (int bb = 0; bb < D::NB; ++bb)
+        for (int n = 0; n < 4; ++n) b[n] *= kSiluScale;   // pre-activations come out as t' = c t
+        const Basis3 b3 = basis_operands(b), db3 = basis_operands(db);
+        float part = 0.f;   // sum_k sbar_k ds_k/dd, ds_k/dd = SiLU'(t_k) c_k, one block of 32 features at a time (fewer live registers)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) part = fmaf(sb[bb][r], t[bb][r], part);
+        for (int bb = 0; bb < D::NB; ++bb) {
+            f32x16 t, cg;
+            gemm_k8_block<F>(A1l, b3, bb, t, lane);
+            gemm_k8_block<F>(A1l, db3, bb, cg, lane);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float sg = sigmoid_scaled(t[r]);
+                const float ss = t[r] * sg * kSiluScaleInv;               // SiLU(t)
+                part = fmaf(sb[bb][r], fmaf(ss, 1.0f - sg, sg) * cg[r], part);
+            }
+        }
         part += __shfl_xor(part, 32, 64);
         if (valid && lane < 32) {
             // every edge is written by exactly one pair per launch; after the first layer the value is
