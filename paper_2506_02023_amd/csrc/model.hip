@@ -375,7 +375,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
     float *bpk = nullptr;        // packed F x F operands of the bond part
     const size_t ffp = (size_t)Dims<F>::PACK3;   // floats of an operand slot
     // operand slots: 0 Wta (y = x W), 1 Wtb, 2 Wt2, 3 Wta^T, 4 Wtb^T, 5 Wt2^T, 6 + l Wb_l, 6 + L + l Wb_l^T; after them We0
-    // packed for the K = 8 product
+    // and Wtc packed for the K = 8 products
     BasisParams bpb = bp;
     auto bstride = [&](SlabView &v) { return (size_t)std::max<int64_t>(v.bonds.n, 1) * F; };   // elements per [n][F] array
     // the [bonds x F] arrays are bf16 in the bf16 mode, fp32 otherwise
@@ -436,7 +436,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             MLIP_TRY(BG.rbar.ensure(nb1 * 3 * sizeof(float)));
             any_bonds = any_bonds || BG.n > 0;
         }
-        MLIP_TRY(g->bond_wpack.ensure(((size_t)(6 + 2 * L) * ffp + Dims<F>::PACK1) * sizeof(float)));
+        MLIP_TRY(g->bond_wpack.ensure(((size_t)(6 + 2 * L) * ffp + 2 * Dims<F>::PACK1) * sizeof(float)));
         bpk = g->bond_wpack.as<float>();
         prof_begin(g, MLIP_PROF_BOND);
         const size_t ff = (size_t)F * F;   // floats of a weight matrix
@@ -459,6 +459,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
                 pack_bond(bw->Wb + l * ff, 0, 6 + L + l);
             }
             pb.add(bw->We0, bpk + (size_t)(6 + 2 * L) * ffp, PACK_W1, 0, 1.0f);
+            pb.add(Wtc, bpk + (size_t)(6 + 2 * L) * ffp + Dims<F>::PACK1, PACK_W1, 0, 1.0f);
             k_pack<<<dim3(blocks_for((int64_t)F * F, 256), pb.n), 256, 0, s>>>(pb);
         }
         MLIP_HIP(hipGetLastError());
@@ -482,7 +483,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
                     using BT = decltype(zero);
                     k_triplet_fwd<F, BT><<<blocks_for(v.n_owned, 4), 256, 0, s>>>(
                         v.n_owned, BG.ptr.as<int64_t>(), BG.rhat.as<float>(), BG.u.as<float>(), BG.P.as<BT>(), BG.Q.as<BT>(), Wtc,
-                        BG.S.as<BT>());
+                        bpk + (size_t)(6 + 2 * L) * ffp + Dims<F>::PACK1, BG.S.as<BT>());
                 });
         }
         MLIP_HIP(hipGetLastError());
@@ -719,7 +720,8 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
                     using BT = decltype(zero);
                     k_triplet_bwd<F, BT><<<blocks_for(v.n_owned, 4), 256, 0, s>>>(
                         v.n_owned, BG.ptr.as<int64_t>(), BG.rhat.as<float>(), BG.u.as<float>(), BG.P.as<BT>(), BG.Q.as<BT>(), Wtc,
-                        BG.Sbar.as<BT>(), BG.Pbar.as<BT>(), BG.Qbar.as<BT>(), BG.ubar.as<float>(), BG.rbar.as<float>());
+                        bpk + (size_t)(6 + 2 * L) * ffp + Dims<F>::PACK1, BG.Sbar.as<BT>(), BG.Pbar.as<BT>(), BG.Qbar.as<BT>(),
+                        BG.ubar.as<float>(), BG.rbar.as<float>());
                 });
         }
         MLIP_HIP(hipGetLastError());

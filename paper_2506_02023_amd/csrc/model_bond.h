@@ -22,7 +22,7 @@ __device__ inline void silu_both(float x, float &s, float &ds)
 {
     const float sg = __builtin_amdgcn_rcpf(1.0f + __expf(-x));
     s = x * sg;
-    ds = sg * (1.0f + x * (1.0f - sg));
+    ds = fmaf(s, 1.0f - sg, sg);
 }
 
 // value of lane k (wave-uniform k) of a float register, as a wave-uniform value
@@ -47,61 +47,98 @@ __device__ inline void chebyshev(float c, float (&T)[kAngle], float (&dT)[kAngle
     }
 }
 
-// S[b1][f] = sum_{b2 != b1, same centre} u[b2] SiLU(P[b1][f] + Q[b2][f] + sum_n T_n(c) Wtc[n][f])
-// One wavefront per centre, lane = feature.  The angle basis does not depend on the feature: for a fixed b1 it is
-// evaluated for 64 bonds b2 at once (lane = b2) and handed to the feature lanes through wave-uniform registers.
-// Centres with at most kPairBondsFwd bonds are processed by unordered pairs {a, o}: T(c) Wtc is shared by the
-// triplets (a, o) and (o, a); the term of bond a accumulates in a register, the term of bond o in a per-lane LDS row.
-constexpr int kPairBondsFwd = 32;
+// ---- angle terms of a centre's pairs of bonds on the matrix units
+//
+// Centres with at most kPairRegs bonds (12 on the benchmark's lattice) are processed by unordered pairs {a, o}, a < o, lane =
+// feature, everything in registers: the bonds' rows and accumulators as arrays indexed by bond, the loops over a and o unrolled.
+// T(c) Wtc (and dT/dc Wtc) of the pairs of two bonds a come from one tile of 32: pair (2 k, o) is row o, pair (2 k + 1, o) row
+// 16 + o, the rows' cosines and Chebyshev values worked out with lane = pair.  With the pairs as the product's rows and
+// the features as its columns a lane of the result holds one feature of half the pairs, and exchanging the halves
+// of two result blocks leaves lane = feature with one register per pair: no LDS and no broadcast.
+constexpr int kPairRegs = 16;
 
+// T_n(c) = cos(n theta) or, DERIV, dT_n/dc = n U_{n-1}(c) as operands of the K = 8 product: lane half h takes n = 2 t + h,
+// t = 0..3.   T_{n+2} = 2 T_2 T_n - T_{n-2}, the same for U
+template <bool DERIV> __device__ inline Basis3 angle_operands(float c, int h)
+{
+    const float t2 = fmaf(2.0f * c, c, -1.0f), k2 = 2.0f * t2;
+    float v[4];
+    v[0] = DERIV ? (h ? 1.0f : 0.0f) : (h ? c : 1.0f);
+    v[1] = DERIV ? (h ? k2 + 1.0f : 2.0f * c) : (h ? c * (k2 - 1.0f) : t2);
+    v[2] = fmaf(k2, v[1], -v[0]);
+    v[3] = fmaf(k2, v[2], -v[1]);
+    if (DERIV)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[t] *= (float)(2 * t) + (h ? 1.0f : 0.0f);
+    return basis_operands(v);
+}
+
+template <int F> struct AngleWeights {   // Wtc packed as PACK_W1, per 32 features the three operands of gemm_k8_block
+    bf16x8 hl[Dims<F>::NB], mm[Dims<F>::NB], hh[Dims<F>::NB];
+    __device__ explicit AngleWeights(const float *__restrict__ pack, int lane)
+    {
+#pragma unroll
+        for (int bo = 0; bo < Dims<F>::NB; ++bo) {
+            const bf16x4 *A = reinterpret_cast<const bf16x4 *>(pack) + (bo * 3) * 64 + lane;
+            const bf16x4 h = A[0], m = A[64], l = A[128];
+            hl[bo] = __builtin_shufflevector(h, l, 0, 1, 2, 3, 4, 5, 6, 7);
+            mm[bo] = __builtin_shufflevector(m, m, 0, 1, 2, 3, 4, 5, 6, 7);
+            hh[bo] = __builtin_shufflevector(h, h, 0, 1, 2, 3, 4, 5, 6, 7);
+        }
+    }
+    // one block of 32 features; PAIRS: the pairs are the result's rows and the features its columns (lanes), else the reverse
+    template <bool PAIRS> __device__ f32x16 block(const Basis3 &v, int bo) const
+    {
+        f32x16 d;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) d[r] = 0.f;
+        d = PAIRS ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(v.lh, hl[bo], d, 0, 0, 0) : __builtin_amdgcn_mfma_f32_32x32x16_bf16(hl[bo], v.lh, d, 0, 0, 0);
+        d = PAIRS ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(v.hm, mm[bo], d, 0, 0, 0) : __builtin_amdgcn_mfma_f32_32x32x16_bf16(mm[bo], v.hm, d, 0, 0, 0);
+        return PAIRS ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(v.hm, hh[bo], d, 0, 0, 0) : __builtin_amdgcn_mfma_f32_32x32x16_bf16(hh[bo], v.hm, d, 0, 0, 0);
+    }
+    // out[p]: this lane's feature of row p's product (F = 32: both halves of the wavefront hold all features)
+    __device__ void rows(const Basis3 &v, float (&out)[32]) const
+    {
+        constexpr int NB = Dims<F>::NB;
+        f32x16 d[NB];
+#pragma unroll
+        for (int bo = 0; bo < NB; ++bo) d[bo] = block<true>(v, bo);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            // register r of half h holds row 8 (r / 4) + 4 h + r % 4; the upper half of block 0 and the lower half of the last
+            // block change places
+            const float lo = d[0][r], up = d[NB - 1][r];   // (a bit cast of a vector's element takes element 0)
+            const unsigned x = __builtin_bit_cast(unsigned, lo), y = __builtin_bit_cast(unsigned, up);
+            const auto sw = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+            out[8 * (r / 4) + (r & 3)] = __builtin_bit_cast(float, (unsigned)sw[0]);
+            out[8 * (r / 4) + 4 + (r & 3)] = __builtin_bit_cast(float, (unsigned)sw[1]);
+        }
+    }
+};
+
+// cosines of tile k's pairs: lane (p, h) has pair (2 k + p / 16, p % 16); x, y, z: lane = bond (mod 16)
+__device__ inline float pair_cosine(int k, int lane, float x, float y, float z)
+{
+    const int a = 2 * k + ((lane >> 4) & 1);
+    return fmaf(__shfl(x, a, 64), x, fmaf(__shfl(y, a, 64), y, __shfl(z, a, 64) * z));
+}
+
+// S[b1][f] = sum_{b2 != b1, same centre} u[b2] SiLU(P[b1][f] + Q[b2][f] + sum_n T_n(c) Wtc[n][f])
+// One wavefront per centre, lane = feature.  Bound by the vector unit: two SiLUs of two transcendentals each per pair and
+// feature.  13.4 M pairs, fp32: 1566 us with vector angle terms, lane broadcasts and LDS accumulators, 687 us here; a branch
+// per pair instead of one per four bonds took 1681 us (the chains of transcendentals had nothing to overlap with).
+// Any number of bonds: ordered pairs, the angle basis of 64 bonds b2 at a time (lane = b2) handed to the feature lanes through
+// wave-uniform registers.
 template <int F, typename BT>
-__global__ void __launch_bounds__(256)
-k_triplet_fwd(int64_t N, const int64_t *__restrict__ bptr, const float *__restrict__ rhat, const float *__restrict__ u,
-              const BT *__restrict__ P, const BT *__restrict__ Q, const float *__restrict__ Wtc, BT *__restrict__ S)
+__device__ inline void triplet_fwd_any(int64_t b0, int64_t b1e, int lane, const float *__restrict__ rhat, const float *__restrict__ u,
+                                       const BT *__restrict__ P, const BT *__restrict__ Q, const float *__restrict__ Wtc,
+                                       BT *__restrict__ S)
 {
     using IO = Elem<BT>;
-    constexpr int NB = kPairBondsFwd;
-    __shared__ float acc_lds[4][NB * 64];
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int64_t i = (int64_t)blockIdx.x * 4 + wave;
-    if (i >= N) return;
     const int f = lane & (F - 1);
     float wc[kAngle];
 #pragma unroll
     for (int n = 0; n < kAngle; ++n) wc[n] = Wtc[n * F + f];
-    const int64_t b0 = bptr[i], b1e = bptr[i + 1];
-    const int nb = (int)(b1e - b0);
-    if (nb <= 0) return;
-    if (nb <= NB) {
-        float *accS = acc_lds[wave];
-        for (int b = 0; b < nb; ++b) accS[b * 64 + lane] = 0.f;
-        const int64_t bl = min(b0 + lane, b1e - 1);
-        const float xl = rhat[3 * bl], yl = rhat[3 * bl + 1], zl = rhat[3 * bl + 2], ul = u[bl];   // lane = bond
-        for (int a = 0; a < nb; ++a) {
-            const int64_t ba = b0 + a;
-            const float pa = IO::load(P + ba * F + f), qa = IO::load(Q + ba * F + f);
-            const float ua = readlane_f32(ul, a);
-            float T[kAngle], dT[kAngle];
-            chebyshev(fmaf(readlane_f32(xl, a), xl, fmaf(readlane_f32(yl, a), yl, readlane_f32(zl, a) * zl)), T, dT);   // lane = o
-            float acc = 0.f;
-            for (int o = a + 1; o < nb; ++o) {
-                float tw = wc[0];   // T_0 = 1
-#pragma unroll
-                for (int n = 1; n < kAngle; ++n) tw = fmaf(readlane_f32(T[n], o), wc[n], tw);
-                const float po = IO::load(P + (b0 + o) * F + f), qo = IO::load(Q + (b0 + o) * F + f);
-                const float so = accS[o * 64 + lane];   // per-lane slot (read early, written at the end of the step;
-                                                        // LDS float atomics measured an order of magnitude slower)
-                acc = fmaf(readlane_f32(ul, o), silu_f(pa + qo + tw), acc);       // triplet (b1 = a, b2 = o)
-                accS[o * 64 + lane] = fmaf(ua, silu_f(po + qa + tw), so);        // triplet (b1 = o, b2 = a)
-            }
-            accS[a * 64 + lane] += acc;
-        }
-        wave_lds_fence();
-        if (F == 64 || lane < F)
-            for (int b = 0; b < nb; ++b) IO::store(S + (b0 + b) * F + f, accS[b * 64 + lane]);
-        return;
-    }
-    // any number of bonds, no LDS: ordered pairs, bonds b2 in groups of 64
     for (int64_t c0 = b0; c0 < b1e; c0 += 64) {   // bonds b2 in groups of 64 (one group unless the centre has more)
         const int nl = (int)min((int64_t)64, b1e - c0);
         const int64_t bl = min(c0 + lane, b1e - 1);
@@ -125,6 +162,115 @@ k_triplet_fwd(int64_t N, const int64_t *__restrict__ bptr, const float *__restri
             }
         }
     }
+}
+
+// 17 to kPairBondsFwd bonds: unordered pairs as well, T(c) Wtc from wave-uniform registers, bond a's sum in a register and bond
+// o's in a per-lane LDS row (accS, kPairBondsFwd rows of 64).
+constexpr int kPairBondsFwd = 32;
+template <int F, typename BT>
+__device__ inline void triplet_fwd_lds(int nb, int64_t b0, int64_t b1e, int lane, float *accS, const float *__restrict__ rhat,
+                                       const float *__restrict__ u, const BT *__restrict__ P, const BT *__restrict__ Q,
+                                       const float *__restrict__ Wtc, BT *__restrict__ S)
+{
+    using IO = Elem<BT>;
+    const int f = lane & (F - 1);
+    float wc[kAngle];
+#pragma unroll
+    for (int n = 0; n < kAngle; ++n) wc[n] = Wtc[n * F + f];
+    for (int b = 0; b < nb; ++b) accS[b * 64 + lane] = 0.f;
+    const int64_t bl = min(b0 + lane, b1e - 1);
+    const float xl = rhat[3 * bl], yl = rhat[3 * bl + 1], zl = rhat[3 * bl + 2], ul = u[bl];   // lane = bond
+    for (int a = 0; a < nb; ++a) {
+        const int64_t ba = b0 + a;
+        const float pa = IO::load(P + ba * F + f), qa = IO::load(Q + ba * F + f);
+        const float ua = readlane_f32(ul, a);
+        float T[kAngle], dT[kAngle];
+        chebyshev(fmaf(readlane_f32(xl, a), xl, fmaf(readlane_f32(yl, a), yl, readlane_f32(zl, a) * zl)), T, dT);   // lane = o
+        float acc = 0.f;
+        for (int o = a + 1; o < nb; ++o) {
+            float tw = wc[0];   // T_0 = 1
+#pragma unroll
+            for (int n = 1; n < kAngle; ++n) tw = fmaf(readlane_f32(T[n], o), wc[n], tw);
+            const float po = IO::load(P + (b0 + o) * F + f), qo = IO::load(Q + (b0 + o) * F + f);
+            const float so = accS[o * 64 + lane];   // per-lane slot (read early, written at the end of the step;
+                                                    // LDS float atomics measured an order of magnitude slower)
+            acc = fmaf(readlane_f32(ul, o), silu_f(pa + qo + tw), acc);       // triplet (b1 = a, b2 = o)
+            accS[o * 64 + lane] = fmaf(ua, silu_f(po + qa + tw), so);        // triplet (b1 = o, b2 = a)
+        }
+        accS[a * 64 + lane] += acc;
+    }
+    wave_lds_fence();
+    if (F == 64 || lane < F)
+        for (int b = 0; b < nb; ++b) IO::store(S + (b0 + b) * F + f, accS[b * 64 + lane]);
+}
+
+template <int F, typename BT>
+__device__ inline void triplet_fwd_regs(int n, int64_t b0, int lane, const float *__restrict__ rhat, const float *__restrict__ u,
+                                        const BT *__restrict__ P, const BT *__restrict__ Q, const float *__restrict__ WtcP,
+                                        BT *__restrict__ S)
+{
+    using IO = Elem<BT>;
+    constexpr int NR = kPairRegs;
+    const int f = lane & (F - 1);
+    const AngleWeights<F> W(WtcP, lane);
+    const int64_t bl = b0 + min(lane & (NR - 1), n - 1);
+    const float xl = rhat[3 * bl], yl = rhat[3 * bl + 1], zl = rhat[3 * bl + 2];   // lane = bond (mod 16)
+    const float ul = (lane & (NR - 1)) < n ? u[bl] : 0.f;
+    float Pr[NR], Qr[NR], Sr[NR];
+#pragma unroll
+    for (int o = 0; o < NR; ++o) {
+        Pr[o] = Qr[o] = Sr[o] = 0.f;
+        if (o < n) {
+            Pr[o] = IO::load(P + (b0 + o) * F + f);
+            Qr[o] = IO::load(Q + (b0 + o) * F + f);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < NR / 2; ++k) {
+        if (2 * k + 1 >= n) break;
+        float tw[32];
+        W.rows(angle_operands<false>(pair_cosine(k, lane, xl, yl, zl), lane >> 5), tw);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int a = 2 * k + q;
+            const float ua = readlane_f32(ul, a);
+#pragma unroll
+            for (int g = 0; g < NR; g += 4)   // bonds from n on have u = 0, their own sums are not stored
+                if (g + 3 > a && g < n)
+#pragma unroll
+                    for (int o = g; o < g + 4; ++o)
+                        if (o > a) {
+                            const float t = tw[16 * q + o];
+                            Sr[a] = fmaf(readlane_f32(ul, o), silu_f(Pr[a] + Qr[o] + t), Sr[a]);   // triplet (b1 = a, b2 = o)
+                            Sr[o] = fmaf(ua, silu_f(Pr[o] + Qr[a] + t), Sr[o]);                    // triplet (b1 = o, b2 = a)
+                        }
+        }
+    }
+    if (F == 64 || lane < F)
+#pragma unroll
+        for (int o = 0; o < NR; ++o)
+            if (o < n) IO::store(S + (b0 + o) * F + f, Sr[o]);
+}
+
+template <int F, typename BT>
+__global__ void __launch_bounds__(256, 4)
+k_triplet_fwd(int64_t N, const int64_t *__restrict__ bptr, const float *__restrict__ rhat, const float *__restrict__ u,
+              const BT *__restrict__ P, const BT *__restrict__ Q, const float *__restrict__ Wtc, const float *__restrict__ WtcP,
+              BT *__restrict__ S)
+{
+    __shared__ float acc_lds[4][kPairBondsFwd * 64];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int64_t i = (int64_t)blockIdx.x * 4 + wave;
+    if (i >= N) return;
+    const int64_t b0 = bptr[i], b1e = bptr[i + 1];
+    const int nb = __builtin_amdgcn_readfirstlane((int)(b1e - b0));
+    if (nb <= 0) return;
+    if (nb <= kPairRegs) {
+        triplet_fwd_regs<F, BT>(nb, b0, lane, rhat, u, P, Q, WtcP, S);
+        return;
+    }
+    if (nb <= kPairBondsFwd) triplet_fwd_lds<F, BT>(nb, b0, b1e, lane, acc_lds[wave], rhat, u, P, Q, Wtc, S);
+    else triplet_fwd_any<F, BT>(b0, b1e, lane, rhat, u, P, Q, Wtc, S);
 }
 
 // bond term of a layer's aggregation: a[i] += sum over the bonds b = (i <- j) of wb[b] * g[j].  One wavefront per centre, lane =
@@ -248,98 +394,125 @@ triplet_bwd_sweep(int64_t i, int lane, const int64_t *__restrict__ bptr, const f
 }
 
 
-constexpr int kPairBonds = 16;   // bonds per centre up to which the pair-wise reverse triplet kernel applies
-
-// Reverse of k_triplet_fwd, one centre per wavefront, lane = feature.  Centres with at most kPairBonds bonds
-// (12 on the benchmark's lattice) are processed by unordered pairs {a, o}: the angle terms T(c) Wtc and
-// dT/dc Wtc are shared by the triplets (a, o) and (o, a), and each triplet is evaluated once.  What a pair
-// contributes to bond a stays in registers; what it contributes to bond o goes to per-lane accumulators in LDS
-// (rows accP, accQ, accU of 64 floats per bond), and dE/dc of the pair, reduced over the features, into a small
-// table from which rbar is assembled at the end with lane = bond.
+// Reverse of k_triplet_fwd, one centre per wavefront, lane = feature.  Centres with at most kPairRegs bonds by unordered pairs,
+// every triplet evaluated once: what a pair contributes to its two bonds stays in registers, and dE/dc of the pair, a sum over
+// the features, goes through an LDS tile that is summed with lane = pair; rbar is assembled from a small table at the end with
+// lane = bond.  Other centres by triplet_bwd_sweep.  Bound by the vector unit as the forward kernel.  13.4 M pairs, fp32:
+// 2672 us with vector angle terms and LDS accumulators, 1480 us here; three wavefronts per SIMD with 7 registers spilled against
+// two without: the same there, 122 against 135 us in bf16 at 30,000 centres.
 template <int F, typename BT>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, 3)
 k_triplet_bwd(int64_t N, const int64_t *__restrict__ bptr, const float *__restrict__ rhat, const float *__restrict__ u,
-              const BT *__restrict__ P, const BT *__restrict__ Q, const float *__restrict__ Wtc,
+              const BT *__restrict__ P, const BT *__restrict__ Q, const float *__restrict__ Wtc, const float *__restrict__ WtcP,
               const BT *__restrict__ Sbar, BT *__restrict__ Pbar, BT *__restrict__ Qbar,
               float *__restrict__ ubar, float *__restrict__ rbar)
 {
     using IO = Elem<BT>;
-    constexpr int NB = kPairBonds;
-    __shared__ float acc_lds[4][3 * NB * 64 + NB * NB];
+    constexpr int NR = kPairRegs, FS = Dims<64>::FS;
+    __shared__ __align__(16) float tile_lds[4][32 * FS], dsym_lds[4][NR * NR];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int64_t i = (int64_t)blockIdx.x * 4 + wave;
     if (i >= N) return;
     const int64_t b0 = bptr[i];
-    const int n = (int)(bptr[i + 1] - b0);
-    if (n > NB) {
+    const int n = __builtin_amdgcn_readfirstlane((int)(bptr[i + 1] - b0));
+    if (n > NR) {
         triplet_bwd_sweep<F, BT>(i, lane, bptr, rhat, u, P, Q, Wtc, Sbar, Pbar, Qbar, ubar, rbar);
         return;
     }
     if (n <= 0) return;
     const int f = lane & (F - 1);
-    const bool on = (F == 64 || lane < F);
-    float wc[kAngle];
+    const AngleWeights<F> W(WtcP, lane);
+    const int64_t bl = b0 + min(lane & (NR - 1), n - 1);
+    const float xl = rhat[3 * bl], yl = rhat[3 * bl + 1], zl = rhat[3 * bl + 2];   // lane = bond (mod 16)
+    const float ul = (lane & (NR - 1)) < n ? u[bl] : 0.f;
+    float *tile = tile_lds[wave], *dsym = dsym_lds[wave];
+    float Pr[NR], Qr[NR], Sr[NR], aP[NR], aQ[NR], aU[NR];
 #pragma unroll
-    for (int k = 0; k < kAngle; ++k) wc[k] = Wtc[k * F + f];
-    float *accP = acc_lds[wave], *accQ = accP + NB * 64, *accU = accQ + NB * 64, *dsym = accU + NB * 64;
-    for (int b = 0; b < n; ++b) {
-        accP[b * 64 + lane] = 0.f;
-        accQ[b * 64 + lane] = 0.f;
-        accU[b * 64 + lane] = 0.f;
-    }
-    for (int a = 0; a < n; ++a) {
-        const int64_t ba = b0 + a;
-        const float xa = rhat[3 * ba], ya = rhat[3 * ba + 1], za = rhat[3 * ba + 2];
-        const float pa = IO::load(P + ba * F + f), qa = IO::load(Q + ba * F + f), sa = IO::load(Sbar + ba * F + f), ua = u[ba];
-        float pacc = 0.f, qacc = 0.f, uacc = 0.f;
-        float drow = 0.f;   // lane o: dE/dc of the pair {a, o}
-        for (int o = a + 1; o < n; ++o) {
-            const int64_t bo = b0 + o;
-            const float c = fmaf(xa, rhat[3 * bo], fmaf(ya, rhat[3 * bo + 1], za * rhat[3 * bo + 2]));
-            float T[kAngle], dT[kAngle];
-            chebyshev(c, T, dT);
-            float tw = 0.f, dw = 0.f;   // T(c) Wtc and dT(c)/dc Wtc for this lane's feature
-#pragma unroll
-            for (int k = 0; k < kAngle; ++k) {
-                tw = fmaf(T[k], wc[k], tw);
-                dw = fmaf(dT[k], wc[k], dw);
-            }
-            const float po = IO::load(P + bo * F + f), qo = IO::load(Q + bo * F + f), so = IO::load(Sbar + bo * F + f), uo = u[bo];
-            // bond o's accumulators: per-lane slots, read here and written at the end of the step (LDS float
-            // atomics measured an order of magnitude slower than this read-modify-write)
-            const float aq = accQ[o * 64 + lane], ap = accP[o * 64 + lane], au = accU[o * 64 + lane];
-            float s1, ds1, s2, ds2;
-            silu_both(pa + qo + tw, s1, ds1);   // triplet (b1 = a, b2 = o)
-            silu_both(po + qa + tw, s2, ds2);   // triplet (b1 = o, b2 = a)
-            const float h1 = sa * uo * ds1, h2 = so * ua * ds2;
-            pacc += h1;
-            qacc += h2;
-            uacc = fmaf(so, s2, uacc);
-            accQ[o * 64 + lane] = aq + h1;
-            accP[o * 64 + lane] = ap + h2;
-            accU[o * 64 + lane] = fmaf(sa, s1, au);
-            const float tot = wave_sum(on ? (h1 + h2) * dw : 0.f);
-            drow = (lane == o) ? tot : drow;
+    for (int o = 0; o < NR; ++o) {
+        Pr[o] = Qr[o] = Sr[o] = aP[o] = aQ[o] = aU[o] = 0.f;
+        if (o < n) {
+            Pr[o] = IO::load(P + (b0 + o) * F + f);
+            Qr[o] = IO::load(Q + (b0 + o) * F + f);
+            Sr[o] = IO::load(Sbar + (b0 + o) * F + f);
         }
-        accP[a * 64 + lane] += pacc;
-        accQ[a * 64 + lane] += qacc;
-        accU[a * 64 + lane] += uacc;
-        if (lane < NB) dsym[a * NB + lane] = drow;   // entries o > a
+    }
+#pragma unroll
+    for (int k = 0; k < NR / 2; ++k) {
+        if (2 * k + 1 >= n) break;
+        const float c = pair_cosine(k, lane, xl, yl, zl);
+        float tw[32];
+        W.rows(angle_operands<false>(c, lane >> 5), tw);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int a = 2 * k + q;
+            const float ua = readlane_f32(ul, a);
+#pragma unroll
+            for (int g = 0; g < NR; g += 4)   // bonds from n on have u = 0 and sbar = 0
+                if (g + 3 > a && g < n)
+#pragma unroll
+                    for (int o = g; o < g + 4; ++o)
+                        if (o > a) {
+                            const float t = tw[16 * q + o], uo = readlane_f32(ul, o);
+                            float s1, ds1, s2, ds2;
+                            silu_both(Pr[a] + Qr[o] + t, s1, ds1);   // triplet (b1 = a, b2 = o)
+                            silu_both(Pr[o] + Qr[a] + t, s2, ds2);   // triplet (b1 = o, b2 = a)
+                            const float h1 = Sr[a] * uo * ds1, h2 = Sr[o] * ua * ds2;
+                            aP[a] += h1;
+                            aQ[o] += h1;
+                            aP[o] += h2;
+                            aQ[a] += h2;
+                            aU[o] = fmaf(Sr[a], s1, aU[o]);
+                            aU[a] = fmaf(Sr[o], s2, aU[a]);
+                            tile[(16 * q + o) * FS + lane] = h1 + h2;
+                        }
+        }
+        wave_lds_fence();
+        {   // dE/dc = sum_f (dT/dc Wtc)_f (h1 + h2)_f, lane (p, h) half the features of pair p (rows without a pair: not used)
+            const Basis3 dT = angle_operands<true>(c, lane >> 5);
+            float s = 0.f;
+#pragma unroll
+            for (int bo = 0; bo < Dims<F>::NB; ++bo) {
+                const f32x16 dw = W.template block<false>(dT, bo);
+#pragma unroll
+                for (int r = 0; r < 16; r += 4) {
+                    const f32x4 hs = *reinterpret_cast<const f32x4 *>(tile + (lane & 31) * FS + 32 * bo + 2 * r + 4 * (lane >> 5));
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) s = fmaf(dw[r + t], hs[t], s);
+                }
+            }
+            s += __shfl_xor(s, 32, 64);
+            const int a = 2 * k + ((lane >> 4) & 1), o = lane & 15;
+            if (lane < 32 && o > a && o < n) dsym[a * NR + o] = s;
+        }
+        wave_lds_fence();
+    }
+    const bool on = (F == 64 || lane < F);
+#pragma unroll
+    for (int o = 0; o < NR; ++o) {
+        tile[o * FS + lane] = aU[o];
+        if (on && o < n) {
+            IO::store(Pbar + (b0 + o) * F + f, aP[o]);
+            IO::store(Qbar + (b0 + o) * F + f, aQ[o]);
+        }
     }
     wave_lds_fence();
-    for (int b = 0; b < n; ++b) {
-        if (on) {
-            IO::store(Pbar + (b0 + b) * F + f, accP[b * 64 + lane]);
-            IO::store(Qbar + (b0 + b) * F + f, accQ[b * 64 + lane]);
+    {   // ubar: lane (bond, quarter of the features)
+        const float *row = tile + (lane & 15) * FS + (F / 4) * (lane >> 4);
+        float s = 0.f;
+#pragma unroll
+        for (int c = 0; c < F / 4; c += 4) {
+            const f32x4 v = *reinterpret_cast<const f32x4 *>(row + c);
+            s += (v[0] + v[1]) + (v[2] + v[3]);
         }
-        const float ub = wave_sum(on ? accU[b * 64 + lane] : 0.f);
-        if (lane == 0) ubar[b0 + b] += ub;
+        s += __shfl_xor(s, 16, 64);
+        s += __shfl_xor(s, 32, 64);
+        if (lane < n) ubar[b0 + lane] += s;   // n <= 16
     }
     if (lane < n) {   // lane = bond: rbar_b = sum over the other bonds o of dE/dc{b, o} rhat_o
         float rx = 0.f, ry = 0.f, rz = 0.f;
         for (int o = 0; o < n; ++o) {
             if (o == lane) continue;
-            const float dv = (o > lane) ? dsym[lane * NB + o] : dsym[o * NB + lane];
+            const float dv = (o > lane) ? dsym[lane * NR + o] : dsym[o * NR + lane];
             rx = fmaf(dv, rhat[3 * (b0 + o)], rx);
             ry = fmaf(dv, rhat[3 * (b0 + o) + 1], ry);
             rz = fmaf(dv, rhat[3 * (b0 + o) + 2], rz);

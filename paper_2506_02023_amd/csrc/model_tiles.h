@@ -151,7 +151,7 @@ struct PackJob {
     float scale;
     int16_t kind, trans;
 };
-constexpr int kPackJobs = 66;   // 8 layers x 8 packs and the readout's two; the bond part has 6 + 2 x 8 + 1
+constexpr int kPackJobs = 66;   // 8 layers x 8 packs and the readout's two; the bond part has 6 + 2 x 8 + 2
 struct PackBatch {
     int n, F;
     PackJob job[kPackJobs];
@@ -434,7 +434,7 @@ __device__ inline void gemm_row_bf16x3(const __bf16 *__restrict__ Ap, const floa
 // gemm_bf16x3.  A lane's four values fill half of its eight places along k of an MFMA, so three MFMAs hold the six terms:
 // (l + h)(h' + l') as l h' + h l', (h + m) m', (h + m) h'.
 // The work of 8 fp32 MFMAs of half the rate, and each lane evaluates the four basis functions it feeds in, not all eight:
-// 3.31 -> 3.18 ms for the forward, 2.90 -> 2.87 ms for the reverse launch at a million atoms (66 M edges); forces against 64 bits
+// 3.31 -> 3.18 ms for the forward, 2.90 -> 2.87 ms for the reverse launch at a million atoms (44 M edges); forces against 64 bits
 // 8.0e-7 (8.1e-7 before; rms relative, geometric mean of 41 systems).
 struct Basis3 { bf16x8 hm, lh; };   // an item's values as the MFMAs' B operands
 __device__ inline Basis3 basis_operands(const float (&v)[4])

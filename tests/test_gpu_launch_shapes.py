@@ -108,3 +108,42 @@ def test_fp32_products_keep_the_range_of_fp32(F):
     e, f, eps = gpu_energy_forces(gpu_graph(pos, cell, species, 5.0), weights, 6, M.MODE_WHOLE, 0)
     assert abs(e - ref["energy"]) <= 1e-5 * np.abs(ref["atom_energy"]).sum()
     assert np.abs(f - ref["forces"]).max() <= 1e-4 * np.abs(ref["forces"]).max()
+
+
+@pytest.mark.parametrize("F,L", [(32, 1), (64, 3)])
+def test_bonds_per_centre_at_the_edges(F, L):
+    """Clusters whose atoms are all bonded to one another: 0, 1, 2, 3, 4, 5, 15, 16 (the most that the triplet kernels hold in
+    registers), 17, 32 (the most that the forward kernel holds in LDS) and 33 bonds per centre, whole and in slabs."""
+    import torch
+    import paper_2506_02023_amd as M
+    from oracle import three_body as tb
+    rng = np.random.default_rng(8)
+    sizes, parts = [1, 2, 3, 4, 5, 6, 16, 17, 18, 33, 34], []
+    for k, n in enumerate(sizes):
+        pts = []
+        while len(pts) < n:    # in a ball of radius 2.2: no two farther apart than the bonds reach
+            q = rng.uniform(-2.2, 2.2, 3)
+            if np.linalg.norm(q) < 2.2 and all(np.linalg.norm(q - r) >= 0.9 for r in pts):
+                pts.append(q)
+        parts.append(np.array(pts) + [6.0 + 12.0 * k, 7.0, 7.0])
+    pos, cell, r_cut, r_bond, K, p = np.concatenate(parts), np.diag([12.0 * len(sizes), 14.0, 14.0]), 5.0, 4.6, 8, 6
+    species = (np.arange(len(pos)) % 4).astype(np.int32)
+    weights = wl.rmp_weights(4, F, L, 78)
+    weights.update(wl.three_body_weights(F, L, 78))
+    ref_g = og.build_graph(pos, cell, r_cut)
+    ref = tb.energy_forces3(pos, cell, species, weights, ref_g, r_cut, r_bond, K, p)
+    assert sorted(set(np.diff(ref["bptr"]))) == [n - 1 for n in sizes]
+    BW = M.BondWeights(weights, r_bond, 8)
+    # fp32 and split fp16: the bounds of the three-body tests.  bf16: every rounding is within 2^-9 of its value, and one cluster
+    # carries most of the energy and force, so the roundings on the way may all point one way.  Energy: filter product, P and Q,
+    # S, wb; forces: two operands in each of the 2 L filter products and the 8 bond arrays of both directions.
+    u = 2.0 ** -9
+    for P in (1, 2, 5):
+        g = gpu_graph(pos, cell, species, r_cut, n_slabs=P)
+        for precision, e_tol, f_tol in ((0, 1e-5, 1e-4), (2, 1e-5, 1e-4), (1, 4 * u, (4 * L + 8) * u)):
+            W = M.Weights({k: weights[k] for k in ("emb", "W1", "W2", "Wm", "Wo", "Wr1", "wr2")}, p, precision=precision)
+            e, f, eps = M.mlip_forward_bonds(g, W, BW, M.MODE_SLABS if P > 1 else M.MODE_WHOLE)
+            torch.cuda.synchronize()
+            what = f"F {F} L {L} P {P} precision {precision}"
+            assert abs(float(e[0]) - ref["energy"]) <= e_tol * np.abs(ref["atom_energy"]).sum(), what
+            assert np.abs(f.cpu().numpy() - ref["forces"]).max() <= f_tol * np.abs(ref["forces"]).max(), what
