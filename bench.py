@@ -15,15 +15,17 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-PEAK_FP32_MFMA_TFLOPS = 157.3
+# The products run on the bf16 / fp16 matrix pipeline (2.5 PFLOP/s dense): an fp32 product as the six terms of operands in
+# three bf16 parts, a split-fp16 one as three.  The peak of a mode is that of the pipeline by the number of terms.
+PEAK_MFMA16_TFLOPS = 2500.0
+PRODUCT_TERMS = {"f32": 6, "f32split": 3, "bf16": 1}
 # Algorithmic flops per directed edge and layer, i.e. of the operation as it is defined:
 #   forward: filter MLP, t = b W1 (2 K F) and w = SiLU(t) W2 (2 F F);
 #   reverse: pre-activations t = b W1 (2 K F), sbar = wbar W2^T (2 F F), dt/dd contraction through W1 (2 K F);
-#            the filter value w_e itself is not recomputed, the forward pass keeps it in HBM (layers >= 1).
-# The reverse kernel runs this dense work once per edge / reverse-edge pair (both have the same length), so the
-# MFMA units execute half of the reverse figure per directed edge; with fp32 MFMA the edge kernels run on the upper
-# edge of every pair only (the forward one then evaluates the filter MLP once per pair too), and memory-bound second
-# passes add the lower edges' terms.  A kernel's roofline fraction is taken on what it executes; the rate of the
+#            the filter value w_e itself is not recomputed, the forward pass keeps it in HBM.
+# The forward kernel runs on every edge.  The reverse kernel runs its dense work once per edge / reverse-edge pair (both
+# have the same length), so the MFMA units execute half of the reverse figure per directed edge; a memory-bound second
+# pass adds the lower edges' terms.  A kernel's roofline fraction is taken on what it executes; the rate of the
 # operation as defined is reported beside it ("as_defined_tflops").
 def flops_fwd_edge(F, K=8):
     return 2 * K * F + 2 * F * F
@@ -46,10 +48,9 @@ def flops_bwd_edge(F, K=8):
 # WRITE_SIZE)
 TRAFFIC_SOURCE = ("profiled constant, not measured by this run: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of this kernel on "
                   "this workload, profiles/edge_traffic_configs3_8slabs.md")
-TRAFFIC_BWD_LAUNCH_BYTES = (6196767 * 1.9976 + 1003909) * 1024         # k_edge_bwd on the upper-edge graphs
-TRAFFIC_FWD_LAUNCH_BYTES = (1369693 * 1.9976 + 6367675) * 1024         # k_edge_fwd on the upper-edge graphs
-TRAFFIC_FWD_LOWER_LAUNCH_BYTES = (3853592 * 1.9976 + 250047) * 1024    # k_edge_lower, forward
-TRAFFIC_BWD_LOWER_LAUNCH_BYTES = (3853695 * 1.9976 + 250047) * 1024    # k_edge_lower, reverse
+TRAFFIC_BWD_LAUNCH_BYTES = (6232198 * 1.9976 + 1002206) * 1024         # k_edge_bwd on the upper-edge graphs
+TRAFFIC_FWD_LAUNCH_BYTES = (3108844 * 1.9976 + 4329365) * 1024         # k_edge_fwd on the full edge lists
+TRAFFIC_BWD_LOWER_LAUNCH_BYTES = (3861533 * 1.9976 + 250047) * 1024    # k_edge_lower
 
 
 # fp32 vector peak that applies to this build: 256 CUs x 4 SIMDs x 16 lanes x 2 flop per FMA x 2.4 GHz = 78.6 TFLOP/s.
@@ -192,56 +193,42 @@ def main():
         per_launch = E * flops_edge * L * args.steps / max(n, 1)
         avg_ms = ms / max(n, 1)
         ach = per_launch / (avg_ms * 1e-3) / 1e12 if avg_ms > 0 else 0.0
-        r = {"kernel": kernel, "bound": "mfma", "achieved": ach, "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
-             "frac": ach / PEAK_FP32_MFMA_TFLOPS, "traffic": traffic if default_workload else None,
+        peak = PEAK_MFMA16_TFLOPS / PRODUCT_TERMS[args.precision]
+        r = {"kernel": kernel, "bound": "mfma", "achieved": ach, "peak": peak, "unit": "TFLOP/s",
+             "frac": ach / peak, "traffic": traffic if default_workload else None,
              "traffic_source": TRAFFIC_SOURCE if default_workload else None,
              "avg_launch_ms": avg_ms, "launches": int(n), "flops_per_launch": per_launch,
              "ms_per_step": ms / args.steps}
         if as_defined is not None:   # rate of the operation as defined (twice the executed work), not a utilisation
             r["as_defined_tflops"] = ach * as_defined / flops_edge
             r["flops_per_edge_layer"] = {"executed": flops_edge, "as_defined": as_defined}
-        if args.precision != "f32":
-            r["note"] = ("the W2 products run on the 16-bit matrix pipeline; frac is the algorithmic rate against the fp32 "
-                         "MFMA peak of the default mode, not a utilisation of the units used")
+        r["note"] = f"peak: 16-bit matrix pipeline, {PRODUCT_TERMS[args.precision]} term(s) per product"
         return r
 
     F = c["F"]
     roof_bwd = edge_roofline("edge_bwd", f"k_edge_bwd<{F}> (reverse edge step)", flops_bwd_edge(F),
                              TRAFFIC_BWD_LAUNCH_BYTES, flops_bwd_edge_as_defined(F))
-    two_pass = prof["edge_fwd_lower"][1] > 0   # edge kernels on the pairs' upper edges, lower edges in second passes
-    if two_pass:
-        roof_fwd = edge_roofline("edge_fwd", f"k_edge_fwd<{F}> on the upper-edge graphs (forward edge step, first pass)",
-                                 flops_fwd_edge(F) // 2, TRAFFIC_FWD_LAUNCH_BYTES, flops_fwd_edge(F))
-        # the operation as defined takes both passes: price it on their summed time
-        both_ms = prof["edge_fwd"][0] + prof["edge_fwd_lower"][0]
-        roof_fwd["as_defined_tflops"] = E * flops_fwd_edge(F) * L * args.steps / (both_ms * 1e-3) / 1e12
-        roof_fwd["as_defined_ms_per_step"] = both_ms / args.steps
-    else:
-        roof_fwd = edge_roofline("edge_fwd", f"k_edge_fwd<{F}> (forward edge step)", flops_fwd_edge(F),
-                                 TRAFFIC_FWD_LAUNCH_BYTES)
-    if two_pass:   # the reverse operation as defined takes both of its passes
+    roof_fwd = edge_roofline("edge_fwd", f"k_edge_fwd<{F}> (forward edge step)", flops_fwd_edge(F), TRAFFIC_FWD_LAUNCH_BYTES)
+    if prof["edge_bwd_lower"][1] > 0:   # the reverse operation as defined takes both of its passes
         both_ms = prof["edge_bwd"][0] + prof["edge_bwd_lower"][0]
         roof_bwd["kernel"] = f"k_edge_bwd<{F}> on the upper-edge graphs (reverse edge step, first pass)"
         roof_bwd["as_defined_tflops"] = E * flops_bwd_edge_as_defined(F) * L * args.steps / (both_ms * 1e-3) / 1e12
         roof_bwd["as_defined_ms_per_step"] = both_ms / args.steps
     roof = roof_fwd if roof_fwd["ms_per_step"] >= roof_bwd["ms_per_step"] else roof_bwd   # the dominant kernel
     roof_lower = {}
-    if two_pass:   # bound by their row traffic; compulsory bytes: per lower edge the kept filter values (read once), per
-                   # atom the row that is gathered (once if the caches were perfect) and the sum (read, written)
-        for group, what, traffic in (("edge_fwd_lower", "forward", TRAFFIC_FWD_LOWER_LAUNCH_BYTES),
-                                     ("edge_bwd_lower", "reverse", TRAFFIC_BWD_LOWER_LAUNCH_BYTES)):
-            ms, n = prof[group]
-            if n == 0:
-                continue
-            per_launch = E / 2 * F * 4 + N * 3 * F * 4
-            avg_ms = ms / n
-            ach = per_launch / (avg_ms * 1e-3) / 1e9 if avg_ms > 0 else 0.0
-            roof_lower[group] = {"kernel": f"k_edge_lower<{F}> ({what} edge step, second pass: lower edges)", "bound": "hbm",
-                                 "achieved": ach, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": ach / PEAK_HBM_GBS,
-                                 "traffic": traffic if default_workload else None,
-                                 "traffic_source": TRAFFIC_SOURCE if default_workload else None,
-                                 "avg_launch_ms": avg_ms, "launches": int(n),
-                                 "bytes_per_launch": per_launch, "ms_per_step": ms / args.steps}
+    ms, n = prof["edge_bwd_lower"]
+    if n > 0:   # bound by its row traffic; compulsory bytes: per lower edge the kept filter values (read once), per
+                # atom the row that is gathered (once if the caches were perfect) and the sum (read, written)
+        per_launch = E / 2 * F * 4 + N * 3 * F * 4
+        avg_ms = ms / n
+        ach = per_launch / (avg_ms * 1e-3) / 1e9 if avg_ms > 0 else 0.0
+        roof_lower["edge_bwd_lower"] = {"kernel": f"k_edge_lower<{F}> (reverse edge step, second pass: lower edges)",
+                                        "bound": "hbm", "achieved": ach, "peak": PEAK_HBM_GBS, "unit": "GB/s",
+                                        "frac": ach / PEAK_HBM_GBS,
+                                        "traffic": TRAFFIC_BWD_LOWER_LAUNCH_BYTES if default_workload else None,
+                                        "traffic_source": TRAFFIC_SOURCE if default_workload else None,
+                                        "avg_launch_ms": avg_ms, "launches": int(n),
+                                        "bytes_per_launch": per_launch, "ms_per_step": ms / args.steps}
     roof_trip = {}
     if three_body:
         _, bptr = g.bonds()

@@ -50,7 +50,8 @@ typedef enum {
 
 enum { MLIP_MODE_WHOLE = 0, MLIP_MODE_SLABS = 1 };
 /*
- * MLIP_PRECISION_FP32: everything from the basis on in fp32 (fp32 MFMA).
+ * MLIP_PRECISION_FP32: everything from the basis on in fp32 (products as exact sums of three bf16 parts per operand on the
+ *   bf16 matrix units, all terms down to 2^-24, accumulated in fp32).
  * MLIP_PRECISION_BF16: the F x F products of the filter MLP (forward w = SiLU(t) W2, reverse sbar = wbar W2^T)
  *   take bf16 operands with fp32 accumulation (benchmark configuration 4: "edge MLPs in bf16 with fp32
  *   accumulation"), and in mlip_forward_bonds the F x F products of the bond MLPs as well; everything else stays
@@ -165,7 +166,7 @@ typedef struct {
  *              rebuilt in place and reuses its device buffers (grow-only)
  *
  * Edges are stored sorted by (receiver, sender, Sx, Sy, Sz).  The call synchronises the
- * stream a few times (edge and partition sizes are needed on the host).
+ * stream once for a whole graph and up to three times with slabs (edge and partition sizes are needed on the host).
  * Positions and species are copied into the handle.
  */
 int mlip_build_graph(const double *positions, const double *cell, const int32_t *species,
@@ -218,7 +219,7 @@ int mlip_forward(mlip_graph_t *graph, const mlip_weights_t *weights, int32_t mod
  * weights, energy partial sums) is carved from one fixed device array inside the library of
  * mlip_static_scratch_bytes() = 64 MiB per GPU, held until the process ends; the call allocates and frees
  * nothing and clears what must start at zero with fill kernels.  A graph and model whose workspace
- * (about n_local (4 + 2 L) F 4 + n_edges (36 + L F 2) bytes summed over the partitions of the mode - the kept
+ * (about n_local (4 + 2 L) F 4 + n_edges (36 + (L - 1) F 2) bytes summed over the partitions of the mode - the kept
  * filter values take one row per edge pair and layer, the lists of the pairs' edges are rebuilt in the array on
  * every call - plus the packed weights) exceeds the array are rejected with MLIP_EINVAL; with the event profiler enabled the call
  * returns MLIP_ESTATE.  All calls on one GPU, from any handle, share the array and find the previous call's
@@ -269,9 +270,9 @@ int mlip_graph_bonds(const mlip_graph_t *graph, int32_t p, const int32_t **bond_
 
 /*
  * Upper / lower split of the edges of partition p's owned rows (p = -1: of the whole graph), the form in which the
- * fp32 edge kernels walk them.  The filter of the radial message-passing layer is a function of the edge length
+ * reverse edge kernels walk them.  The filter of the radial message-passing layer is a function of the edge length
  * alone (benchmark description: w_e = MLP(basis(d_e))), and the two edges of an edge / reverse-edge pair have the
- * same length, so the filter is evaluated for one of them, the "upper" one: the edge whose reverse edge lies at a
+ * same length, so its values are kept for one of them, the "upper" one: the edge whose reverse edge lies at a
  * larger index of the partition's edge list.  (An edge from a ghost sender is always upper: its reverse edge is in
  * a ghost row, behind all owned rows.)  All other edges of the owned rows are "lower".
  * Borrowed DEVICE pointers, valid until the next mlip_build_graph on the handle:
@@ -357,9 +358,9 @@ enum {
     MLIP_PROF_BOND = 6,    /* three-body variant: bond list and the kernels over bonds */
     MLIP_PROF_TRIPLET_FWD = 7,   /* three-body variant: the triplet sum           */
     MLIP_PROF_TRIPLET_BWD = 8,   /* three-body variant: its reverse               */
-    MLIP_PROF_EDGE_FWD_LOWER = 9, /* forward edge step, second pass (where the edge kernels run on one edge per edge /
-                                     reverse-edge pair: the terms of the pairs' lower edges, from the kept filter values) */
-    MLIP_PROF_EDGE_BWD_LOWER = 10, /* reverse edge step, second pass (the same for the gradients of the projected rows) */
+    MLIP_PROF_EDGE_FWD_LOWER = 9,  /* no launches: the forward edge step is one pass over the full edge list */
+    MLIP_PROF_EDGE_BWD_LOWER = 10, /* reverse edge step, second pass: the lower edges' share of the projected rows' gradients, from
+                                     the kept filter values; in the three-body variant the bonds' share too */
     MLIP_PROF_COUNT = 11
 };
 int mlip_profile_enable(mlip_graph_t *graph, int32_t on);

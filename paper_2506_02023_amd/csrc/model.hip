@@ -10,13 +10,12 @@
 // reverse pass.
 //
 // Kernel design
-//  * All dense contractions (filter MLP per edge, F x F maps per node) run on
-//    v_mfma_f32_32x32x2_f32 with items (edges or nodes) as the 32 MFMA columns
-//    and features as rows.  In that orientation the accumulator layout of one
-//    product is directly the B operand of the next one if the contraction index
-//    is visited in the order the accumulator registers hold it; the weight (A)
-//    operands are pre-packed in that order, so chained products need no
-//    transposition or lane exchange.
+//  * All dense contractions (filter MLP per edge, F x F maps per node and per bond) run on the 16-bit matrix
+//    pipeline: fp32 products as exact three-part bf16 sums with fp32 accumulation, with items (edges, nodes or
+//    bonds) as the 32 MFMA columns and features as rows.  In that orientation the accumulator layout of one
+//    product is directly the B operand of the next one if the contraction index is visited in the order the
+//    accumulator registers hold it; the weight (A) operands are pre-packed in that order, so chained products
+//    need no transposition or lane exchange.
 //  * The per-receiver reduction is LDS-staged: a 32-edge tile of filter outputs
 //    is written to LDS edge-major, then each lane owns one feature, reads the
 //    tile row by row, multiplies with the gathered sender row (one coalesced

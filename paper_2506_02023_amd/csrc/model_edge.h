@@ -149,7 +149,7 @@ __device__ inline uint32_t row_ends(int32_t rk, int32_t rn_first, bool valid, in
     return (uint32_t)__ballot(valid && rnext != rk);
 }
 
-// PREC selects how the F x F product with W2 runs: kPrecF32 fp32 MFMA, kPrecBf16 bf16 operands, kPrecF16x3 split fp16
+// PREC selects how the F x F product with W2 runs: kPrecF32 three-part bf16, kPrecBf16 bf16 operands, kPrecF16x3 split fp16
 template <int F, int PREC>
 __global__ void __launch_bounds__(kFwdWaves * 64, 3) k_edge_fwd(EdgeBatch B)
 {
