@@ -163,7 +163,8 @@ typedef struct {
  *              computed as ((x n_x + y n_y) + z n_z) / V with n = a_{k+1} x a_{k+2}, V = a_k . n
  *   stream     hipStream_t as void*
  *   graph      in/out HOST: *graph == NULL creates a handle; a handle from an earlier call is
- *              rebuilt in place and reuses its device buffers (grow-only)
+ *              rebuilt in place and reuses its device buffers (grow-only); on another stream than
+ *              before, the call waits for what the handle has queued on the old one first
  *
  * Edges are stored sorted by (receiver, sender, Sx, Sy, Sz).  The call synchronises the
  * stream once for a whole graph and up to three times with slabs (edge and partition sizes are needed on the host).

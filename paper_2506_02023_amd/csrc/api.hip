@@ -194,7 +194,14 @@ int mlip_build_graph(const double *positions, const double *cell, const int32_t 
         g = new (std::nothrow) mlip_graph();
         if (!g) { set_error("host allocation failed"); return MLIP_ENOMEM; }
     }
-    g->stream = static_cast<hipStream_t>(stream);
+    // The end of a build is not waited for.  What earlier calls queued on another stream ends before this build touches the
+    // handle's buffers (its pinned area is there since the first build).
+    const hipStream_t next = static_cast<hipStream_t>(stream);
+    if (g->pinned && g->stream != next && hipStreamSynchronize(g->stream) != hipSuccess) {
+        (void)hipGetLastError();   // the caller may have destroyed that stream since
+        MLIP_HIP(hipDeviceSynchronize());
+    }
+    g->stream = next;
     if (g->prof.on && g->prof.used + 64 > (size_t)kMaxEvents) (void)prof_collect(g);
     int rc = MLIP_EHIP;
     AllocScope scope(g);

@@ -2129,7 +2129,7 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
             v.ghost_src = st.ghost_src.as<int32_t>() + T.ghost0[q];
         }
         prof_end(g);
-    } else if (!unchecked) {
+    } else if (!unchecked && s != hipStreamPerThread) {   // (that name is another stream in another thread: wait as below)
         prof_end(g);
     } else {
         prof_end(g);
