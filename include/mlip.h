@@ -307,7 +307,8 @@ int mlip_graph_sizes(const mlip_graph_t *graph, int64_t *n_atoms, int64_t *n_edg
  * Whole-graph CSR, borrowed DEVICE pointers: row_ptr[N+1], senders[E], d[E] (fp32 edge lengths).  This is what the
  * paper's graph object exposes as src_nodes / dst_nodes (appendix "Parallelizing a Model in DistMLIP"): edge e of
  * row i has destination (receiver) i and source senders[e]; the neighbour list itself is the one of Methods,
- * "Graph-Parallel Message Passing".
+ * "Graph-Parallel Message Passing".  The arrays are complete when the call returns (so are mlip_graph_mirror's): the
+ * first call after a build waits for the build's last kernels if they may still run.
  */
 int mlip_graph_csr(const mlip_graph_t *graph, const int64_t **row_ptr, const int32_t **senders,
                    const float **d);

@@ -412,9 +412,25 @@ int mlip_graph_sizes(const mlip_graph_t *g, int64_t *n_atoms, int64_t *n_edges, 
     return MLIP_OK;
 }
 
+// The whole graph's edge arrays are handed out complete, whatever stream the caller reads them on; a stream that is being
+// captured cannot be waited for (and its captured work comes after the build).
+static int finish_build(const mlip_graph_t *g)
+{
+    if (!g->tail) return MLIP_OK;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(g->stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return MLIP_OK;
+    }
+    MLIP_HIP(hipStreamSynchronize(g->stream));
+    g->tail = false;
+    return MLIP_OK;
+}
+
 int mlip_graph_csr(const mlip_graph_t *g, const int64_t **row_ptr, const int32_t **senders, const float **d)
 {
     if (!g || g->N <= 0) { set_error("no graph"); return MLIP_ESTATE; }
+    MLIP_TRY(finish_build(g));
     if (row_ptr) *row_ptr = g->row_ptr.as<int64_t>();
     if (senders) *senders = g->senders.as<int32_t>();
     if (d) *d = g->d.as<float>();
@@ -425,6 +441,7 @@ int mlip_graph_mirror(const mlip_graph_t *g, const int32_t **mirror)
 {
     if (!g || g->N <= 0) { set_error("no graph"); return MLIP_ESTATE; }
     if (!mirror) { set_error("null pointer argument"); return MLIP_EINVAL; }
+    MLIP_TRY(finish_build(g));
     *mirror = g->mirror.as<int32_t>();
     return MLIP_OK;
 }

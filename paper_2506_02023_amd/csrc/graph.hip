@@ -1899,6 +1899,7 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
         sv.pairs.valid = false;
     }
     g->E = 0;
+    g->tail = false;
     if (!g->pinned) MLIP_HIP(hipHostMalloc(&g->pinned, kPinnedBytes, hipHostMallocDefault));
     int64_t *hp = static_cast<int64_t *>(g->pinned);
 
@@ -2131,6 +2132,7 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
         prof_end(g);
     } else if (!unchecked && s != hipStreamPerThread) {   // (that name is another stream in another thread: wait as below)
         prof_end(g);
+        g->tail = true;
     } else {
         prof_end(g);
         MLIP_HIP(hipMemcpyAsync(hp, g->small.p, 4, hipMemcpyDeviceToHost, s));

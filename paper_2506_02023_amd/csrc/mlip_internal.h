@@ -247,6 +247,7 @@ struct mlip_graph {
     int work_next = 0;        // launches that have taken their counters in the current call
     mlip::Profiler prof;
     mlip::DevBuf bond_wpack;  // packed weights of the three-body variant's bond part
+    mutable bool tail = false;   // the last build's final kernels (edge arrays, reverse edges) may still run
     void *pinned = nullptr;  // pinned host area in which kernels leave counts and flags for the host
 };
 

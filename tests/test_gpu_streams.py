@@ -48,3 +48,35 @@ def test_rebuild_on_another_stream(allocator, forward_between):
         torch.cuda.synchronize()
         assert torch.equal(e.cpu(), fresh[k][1]) and torch.equal(f.cpu(), fresh[k][2]), turn
     g.destroy()
+
+
+class _DeviceArray:
+    """a borrowed device pointer as torch takes it"""
+
+    def __init__(self, ptr, count, typestr):
+        self.__cuda_array_interface__ = {"data": (ptr, False), "shape": (count,), "typestr": typestr, "version": 2}
+
+
+@pytest.mark.parametrize("which", ["csr", "mirror"])
+def test_edge_arrays_are_complete_when_handed_out(which):
+    """The whole graph's arrays read on another stream right after the call that returns their addresses."""
+    import ctypes
+    import torch
+    import paper_2506_02023_amd as M
+    c, pos, sp = next(_systems())
+    ref = M.mlip_build_graph(pos, c["cell"], sp, c["r_cut"])
+    _, senders, _, d = ref.csr()
+    want = [senders, d] if which == "csr" else [ref.mirror()]
+    side = torch.cuda.Stream()
+    g = M.mlip_build_graph(pos, c["cell"], sp, c["r_cut"])
+    E, a, b = g.sizes()[1], ctypes.c_void_p(), ctypes.c_void_p()
+    if which == "csr":
+        assert M.lib().mlip_graph_csr(g._h, None, ctypes.byref(a), ctypes.byref(b)) == 0
+        views = [_DeviceArray(a.value, E, "<i4"), _DeviceArray(b.value, E, "<f4")]
+    else:
+        assert M.lib().mlip_graph_mirror(g._h, ctypes.byref(a)) == 0
+        views = [_DeviceArray(a.value, E, "<i4")]
+    with torch.cuda.stream(side):
+        got = [torch.as_tensor(v, device="cuda").clone() for v in views]
+    side.synchronize()
+    assert all(np.array_equal(x.cpu().numpy(), y) for x, y in zip(got, want))
