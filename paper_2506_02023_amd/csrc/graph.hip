@@ -187,11 +187,8 @@ __global__ void k_tile_scan(In in, const Tout *pre, Tout *out, int64_t n, Publis
 template <class In, class Tout>
 int scan_impl(In in, Tout *out, int64_t n, char *tmp, size_t tmp_bytes, hipStream_t s, Publish pub)
 {
-    if (n <= 0) {
-        if (n == 0) MLIP_HIP(hipMemsetAsync(out, 0, sizeof(Tout), s));
-        return MLIP_OK;
-    }
-    const int64_t tiles = (n + kScanTile - 1) / kScanTile;
+    if (n < 0) return MLIP_OK;
+    const int64_t tiles = n > 0 ? (n + kScanTile - 1) / kScanTile : 1;   // (an empty scan writes its total by a kernel as well: it may be captured)
     if (tiles <= kDirectTiles) {
         k_tile_scan<In, Tout, SCAN_DIRECT><<<(unsigned)tiles, kScanThreads, 0, s>>>(in, nullptr, out, n, pub);
         MLIP_HIP(hipGetLastError());

@@ -80,3 +80,55 @@ def test_edge_arrays_are_complete_when_handed_out(which):
         got = [torch.as_tensor(v, device="cuda").clone() for v in views]
     side.synchronize()
     assert all(np.array_equal(x.cpu().numpy(), y) for x, y in zip(got, want))
+
+
+def _graph_node_types(graph):
+    """hipGraphNodeType of every node of a captured graph"""
+    import ctypes
+    with open("/proc/self/maps") as f:
+        hip = ctypes.CDLL(next(w for line in f for w in line.split()[-1:] if "libamdhip64" in w))
+    raw, n = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(n)) == 0
+    nodes, out = (ctypes.c_void_p * n.value)(), []
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(n)) == 0
+    for node in nodes:
+        t = ctypes.c_int()
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(t)) == 0
+        out.append(t.value)
+    return out
+
+
+@pytest.mark.parametrize("n_slabs", [1, 3, 64])
+def test_static_call_under_capture(n_slabs):
+    """mlip_forward_static captured and replayed, other work and synchronisations between the replays: every replay gives
+    the eager result, and the graph holds kernels only, also where whole batches of slabs own nothing (64)."""
+    import torch
+    import paper_2506_02023_amd as M
+    rng = np.random.default_rng(4)
+    pos = np.concatenate([rng.uniform(0.5, 9.5, (40, 3)) * np.array([1.0, 0.6, 0.6]), np.array([[41.0, 3.0, 3.0]])])
+    cell, species = np.diag([64.0, 7.0, 7.0]), (np.arange(41) % 4).astype(np.int32)
+    W = M.Weights(wl.rmp_weights(4, 32, 2, 12), 6)
+    mode = M.MODE_SLABS if n_slabs > 1 else M.MODE_WHOLE
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        tp, ts = torch.as_tensor(pos, device="cuda"), torch.as_tensor(species, device="cuda")
+        g = M.mlip_build_graph(tp, cell, ts, 5.0, n_slabs=n_slabs)
+        eager = [x.clone() for x in M.mlip_forward_static(g, W, mode)]
+        out = [torch.empty_like(x) for x in eager]
+        M.mlip_forward_static(g, W, mode, out=out)
+        side.synchronize()
+        graph = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(graph, stream=side):
+            M.mlip_forward_static(g, W, mode, out=out)
+    assert set(_graph_node_types(graph)) == {0}     # hipGraphNodeTypeKernel
+    c = wl.make_config(0)
+    other = M.mlip_build_graph(torch.as_tensor(c["positions"], device="cuda"), c["cell"], torch.as_tensor(c["species"], device="cuda"), 5.0)
+    for k in range(4):
+        for x in out:
+            x.fill_(float("nan"))
+        if k % 2:      # a call from another handle leaves its contents in the shared workspace
+            M.mlip_forward_static(other, W)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(x, y) for x, y in zip(out, eager)), k
