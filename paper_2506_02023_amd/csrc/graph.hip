@@ -40,10 +40,11 @@ __device__ inline int floordiv(int a, int b)
     return q;
 }
 
-enum { ERR_RANGE = 1, ERR_COINCIDENT = 2, ERR_MIRROR = 4, FLAG_STAGE_OVERFLOW = 8 };
+enum { ERR_RANGE = 1, ERR_COINCIDENT = 2, ERR_MIRROR = 4, FLAG_STAGE_OVERFLOW = 8, FLAG_DISPLACED = 16, FLAG_CROWDED = 32 };
 // neighbours found by the counting pass are parked in a fixed-width row per atom, from where the sort picks them
 // up; an atom with more neighbours than this sets FLAG_STAGE_OVERFLOW and the rows are filled by a second pass
 constexpr int kStage = 96;
+constexpr int kCrowd = 32;   // a cell with more atoms is crowded (k_neighbours_pairs)
 
 // ---------------------------------------------------------------- scans
 
@@ -298,7 +299,9 @@ __global__ void k_bin(int64_t N, const double *__restrict__ pos, const int32_t *
     cell_of[i] = c;
     wrapp[i] = pack3(w[0], w[1], w[2]);
     slab_of[i] = slab;
-    in_cell[i] = atomicAdd(&cell_cnt[c], 1);   // the atom's place among its cell's
+    const int32_t place = atomicAdd(&cell_cnt[c], 1);   // the atom's place among its cell's
+    in_cell[i] = place;
+    if (place == kCrowd) atomicOr(err, FLAG_CROWDED);
 }
 
 __global__ void k_fill_cells(int64_t N, const double *__restrict__ pos, const int32_t *__restrict__ cell_of,
@@ -471,30 +474,25 @@ k_sort_rows(int64_t N, CellParams cp, const double *__restrict__ pos, const int6
 constexpr int64_t kSharedCells = 4096;   // below this many cells four wavefronts share one (four cells fit a block otherwise)
 constexpr int kOwn = 64, kPar = 64;   // staging slots per atom for edges found by the atom itself / by its partners
 
-// One cell per wavefront or (SHARED) per block of four.  The candidates of a cell's atoms are the same: lanes first take the surrounding cells (64
+struct PairSearch {   // arrays of the pair-wise search
+    const int32_t *cell_start, *sid;
+    const double *sx, *sy, *sz;
+    const uint32_t *swrap;
+    uint64_t *stage_own;
+    int32_t *stage_q, *n_own;
+};
+
+// n_home (at most kCrowd) atoms of cell c, in cell order from hb on, against the candidates of the cell, by one wavefront or
+// (SHARED) by the four of a block.  The candidates of a cell's atoms are the same: lanes first take the surrounding cells (64
 // at a time: first atom, length, image), then their atoms, flattened (a cell holds about 11), 64 at a time; every lane
-// keeps one candidate in registers and the cell's own atoms are tested against it one after another, their records
+// keeps one candidate in registers and the home atoms are tested against it one after another, their records
 // broadcast from the lanes that loaded them.  Wavefronts that share a cell take its candidates in turn and count an
-// atom's finds in LDS.  A candidate is loaded once
-// per cell instead of once per atom, and nothing waits in a chain of dependent loads: one thread per atom walking the
-// cells was bound by that chain, 118 us at any size below 60,000 atoms and 544 us at a million;
-// here 19 us at 500 atoms, 28 us at 32,000 and 390 us at a million.
+// atom's finds in LDS.
 template <bool SHARED>
-__global__ void __launch_bounds__(256)
-k_neighbours_pairs(int64_t n_cells, CellParams cp, const int32_t *__restrict__ cell_start,
-                   const int32_t *__restrict__ sid, const double *__restrict__ sx,
-                   const double *__restrict__ sy, const double *__restrict__ sz,
-                   const uint32_t *__restrict__ swrap, uint64_t *__restrict__ stage_own,
-                   int32_t *__restrict__ stage_q, int32_t *__restrict__ n_own, int32_t *err)
+__device__ inline void search_home(int32_t c, int32_t hb, int n_home, const CellParams &cp, const PairSearch &A, int32_t *found,
+                                   bool &coincident, bool &overflow)
 {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    __shared__ int32_t found[64];   // SHARED: edges found so far by the cell's atoms
-    const int64_t c64 = SHARED ? (int64_t)xcd_block() : (int64_t)xcd_block() * 4 + wave;
-    if (c64 >= n_cells) return;   // (SHARED: the whole block)
-    const int32_t c = (int32_t)c64;
-    const int32_t h0 = __builtin_amdgcn_readfirstlane(cell_start[c]);
-    const int32_t h1 = __builtin_amdgcn_readfirstlane(cell_start[c + 1]);
-    if (h0 >= h1) return;
     int cr = c;
     const int b2 = cr % cp.nb[2];
     cr /= cp.nb[2];
@@ -502,113 +500,151 @@ k_neighbours_pairs(int64_t n_cells, CellParams cp, const int32_t *__restrict__ c
     const int b0 = cr / cp.nb[1];
     const int w0 = 2 * cp.reach[0] + 1, w1 = 2 * cp.reach[1] + 1, w2 = 2 * cp.reach[2] + 1;
     const int64_t n_around = (int64_t)w0 * w1 * w2;
-    bool coincident = false, overflow = false;
-
-    // the cell's own atoms, up to 64 at a time: lane k holds the k-th one
-    for (int32_t hb = h0; hb < h1; hb += 64) {
-        const int n_home = min(64, h1 - hb);
-        const int32_t hq = min(hb + lane, h1 - 1);
-        if (SHARED) {
-            __syncthreads();
-            if (threadIdx.x < 64) found[threadIdx.x] = 0;
-            __syncthreads();
-        }
-        const uint32_t hw = swrap[hq];
-        const double hx = sx[hq], hy = sy[hq], hz = sz[hq];
-        int32_t cnt = 0;   // lane k: edges found by the k-th atom
-        for (int64_t a0 = 0; a0 < n_around; a0 += 64) {
-            // lane = one surrounding cell: its first atom at or after this cell's first, how many, and the image it is seen in
-            const int64_t a = a0 + lane;
-            int32_t q0 = 0, len = 0, ip = 0;
-            if (a < n_around) {
-                const int dz = (int)(a % w2), dy = (int)((a / w2) % w1), dx = (int)(a / ((int64_t)w2 * w1));
-                int c0 = b0 + dx - cp.reach[0], c1 = b1 + dy - cp.reach[1], c2 = b2 + dz - cp.reach[2];
-                const int i0 = floordiv(c0, cp.nb[0]), i1 = floordiv(c1, cp.nb[1]), i2 = floordiv(c2, cp.nb[2]);
-                c0 -= i0 * cp.nb[0];
-                c1 -= i1 * cp.nb[1];
-                c2 -= i2 * cp.nb[2];
-                const int32_t cc = (c0 * cp.nb[1] + c1) * cp.nb[2] + c2;
-                if (cc >= c) {   // the atoms of the cells before this one find the pair themselves
-                    q0 = cell_start[cc];
-                    len = cell_start[cc + 1] - q0;
-                    ip = (int)pack3(i0, i1, i2);
-                }
+    const int32_t hq = hb + min(lane, n_home - 1);   // lane k holds the k-th home atom
+    if (SHARED) {
+        __syncthreads();
+        if (threadIdx.x < kCrowd) found[threadIdx.x] = 0;
+        __syncthreads();
+    }
+    const uint32_t hw = A.swrap[hq];
+    const double hx = A.sx[hq], hy = A.sy[hq], hz = A.sz[hq];
+    int32_t cnt = 0;   // lane k: edges found by the k-th atom
+    for (int64_t a0 = 0; a0 < n_around; a0 += 64) {
+        // lane = one surrounding cell: its first atom at or after this cell's first, how many, and the image it is seen in
+        const int64_t a = a0 + lane;
+        int32_t q0 = 0, len = 0, ip = 0;
+        if (a < n_around) {
+            const int dz = (int)(a % w2), dy = (int)((a / w2) % w1), dx = (int)(a / ((int64_t)w2 * w1));
+            int c0 = b0 + dx - cp.reach[0], c1 = b1 + dy - cp.reach[1], c2 = b2 + dz - cp.reach[2];
+            const int i0 = floordiv(c0, cp.nb[0]), i1 = floordiv(c1, cp.nb[1]), i2 = floordiv(c2, cp.nb[2]);
+            c0 -= i0 * cp.nb[0];
+            c1 -= i1 * cp.nb[1];
+            c2 -= i2 * cp.nb[2];
+            const int32_t cc = (c0 * cp.nb[1] + c1) * cp.nb[2] + c2;
+            if (cc >= c) {   // the atoms of the cells before this one find the pair themselves
+                q0 = A.cell_start[cc];
+                len = A.cell_start[cc + 1] - q0;
+                ip = (int)pack3(i0, i1, i2);
             }
-            const int32_t inc = wave_inclusive_scan(len);
-            const int32_t total = __builtin_amdgcn_readlane(inc, 63);
-            for (int32_t t0 = SHARED ? 64 * wave : 0; t0 < total; t0 += SHARED ? 256 : 64) {
-                // lane = candidate t: the cell it lies in is the first whose running total exceeds t
-                const int32_t t = t0 + lane;
-                int k = 0;
+        }
+        const int32_t inc = wave_inclusive_scan(len);
+        const int32_t total = __builtin_amdgcn_readlane(inc, 63);
+        for (int32_t t0 = SHARED ? 64 * wave : 0; t0 < total; t0 += SHARED ? 256 : 64) {
+            // lane = candidate t: the cell it lies in is the first whose running total exceeds t
+            const int32_t t = t0 + lane;
+            int k = 0;
 #pragma unroll
-                for (int step = 32; step > 0; step >>= 1)
-                    if (__shfl(inc, k + step - 1, 64) <= t) k += step;   // (at most 63 for t < total)
-                const bool there = t < total;
-                k = there ? k : 0;
-                const int32_t before = __shfl(inc, k, 64) - __shfl(len, k, 64);
-                const int32_t qk = __shfl(q0, k, 64);
-                const uint32_t ik = (uint32_t)__shfl(ip, k, 64);
-                const int32_t q = there ? qk + (t - before) : h0;
-                const int32_t j = sid[q];
-                const uint32_t wj = swrap[q];
-                const double xj = sx[q], yj = sy[q], zj = sz[q];
-                int i0, i1, i2, wj0, wj1, wj2;
-                unpack3(ik, i0, i1, i2);
-                unpack3(wj, wj0, wj1, wj2);
-                uint32_t w_cur = 0;   // wrap counts of the atom the shift below was worked out for (0: none)
-                int S0 = 0, S1 = 0, S2 = 0;
-                double s0 = 0, s1 = 0, s2 = 0;
-                for (int hk = 0; hk < n_home; ++hk) {
-                    const uint32_t wi = (uint32_t)__builtin_amdgcn_readlane((int)hw, hk);
-                    if (wi != w_cur) {   // wave-uniform; atoms of one cell mostly share their wrap counts
-                        w_cur = wi;
-                        int wi0, wi1, wi2;
-                        unpack3(wi, wi0, wi1, wi2);
-                        S0 = i0 - wj0 + wi0;
-                        S1 = i1 - wj1 + wi1;
-                        S2 = i2 - wj2 + wi2;
-                        s0 = ((double)S0 * cp.C[0] + (double)S1 * cp.C[3]) + (double)S2 * cp.C[6];
-                        s1 = ((double)S0 * cp.C[1] + (double)S1 * cp.C[4]) + (double)S2 * cp.C[7];
-                        s2 = ((double)S0 * cp.C[2] + (double)S1 * cp.C[5]) + (double)S2 * cp.C[8];
-                    }
-                    const int32_t s = hb + hk;
-                    const double t0d = (xj - readlane_f64(hx, hk)) + s0;
-                    const double t1d = (yj - readlane_f64(hy, hk)) + s1;
-                    const double t2d = (zj - readlane_f64(hz, hk)) + s2;
-                    const double d2 = (t0d * t0d + t1d * t1d) + t2d * t2d;
-                    const uint32_t sp = pack3(S0, S1, S2);
-                    // positions after this atom's, or an image of the atom itself (of the two the one with the larger shift)
-                    const bool mine = there && (q > s || (q == s && sp > pack3(-S0, -S1, -S2)));
-                    const bool hit = mine && d2 <= cp.rc2;
-                    const unsigned long long m = __ballot(hit);
-                    if (m == 0) continue;
-                    int32_t at;
-                    if (SHARED) {
-                        int32_t v = 0;
-                        if (lane == 0) v = atomicAdd(&found[hk], __popcll(m));
-                        at = __builtin_amdgcn_readfirstlane(v);
+            for (int step = 32; step > 0; step >>= 1)
+                if (__shfl(inc, k + step - 1, 64) <= t) k += step;   // (at most 63 for t < total)
+            const bool there = t < total;
+            k = there ? k : 0;
+            const int32_t before = __shfl(inc, k, 64) - __shfl(len, k, 64);
+            const int32_t qk = __shfl(q0, k, 64);
+            const uint32_t ik = (uint32_t)__shfl(ip, k, 64);
+            const int32_t q = there ? qk + (t - before) : hb;
+            const int32_t j = A.sid[q];
+            const uint32_t wj = A.swrap[q];
+            const double xj = A.sx[q], yj = A.sy[q], zj = A.sz[q];
+            int i0, i1, i2, wj0, wj1, wj2;
+            unpack3(ik, i0, i1, i2);
+            unpack3(wj, wj0, wj1, wj2);
+            uint32_t w_cur = 0;   // wrap counts of the atom the shift below was worked out for (0: none)
+            int S0 = 0, S1 = 0, S2 = 0;
+            double s0 = 0, s1 = 0, s2 = 0;
+            for (int hk = 0; hk < n_home; ++hk) {
+                const uint32_t wi = (uint32_t)__builtin_amdgcn_readlane((int)hw, hk);
+                if (wi != w_cur) {   // wave-uniform; atoms of one cell mostly share their wrap counts
+                    w_cur = wi;
+                    int wi0, wi1, wi2;
+                    unpack3(wi, wi0, wi1, wi2);
+                    S0 = i0 - wj0 + wi0;
+                    S1 = i1 - wj1 + wi1;
+                    S2 = i2 - wj2 + wi2;
+                    s0 = ((double)S0 * cp.C[0] + (double)S1 * cp.C[3]) + (double)S2 * cp.C[6];
+                    s1 = ((double)S0 * cp.C[1] + (double)S1 * cp.C[4]) + (double)S2 * cp.C[7];
+                    s2 = ((double)S0 * cp.C[2] + (double)S1 * cp.C[5]) + (double)S2 * cp.C[8];
+                }
+                const int32_t s = hb + hk;
+                const double t0d = (xj - readlane_f64(hx, hk)) + s0;
+                const double t1d = (yj - readlane_f64(hy, hk)) + s1;
+                const double t2d = (zj - readlane_f64(hz, hk)) + s2;
+                const double d2 = (t0d * t0d + t1d * t1d) + t2d * t2d;
+                const uint32_t sp = pack3(S0, S1, S2);
+                // positions after this atom's, or an image of the atom itself (of the two the one with the larger shift)
+                const bool mine = there && (q > s || (q == s && sp > pack3(-S0, -S1, -S2)));
+                const bool hit = mine && d2 <= cp.rc2;
+                const unsigned long long m = __ballot(hit);
+                if (m == 0) continue;
+                int32_t at;
+                if (SHARED) {
+                    int32_t v = 0;
+                    if (lane == 0) v = atomicAdd(&found[hk], __popcll(m));
+                    at = __builtin_amdgcn_readfirstlane(v);
+                } else {
+                    at = __builtin_amdgcn_readlane(cnt, hk);
+                    if (lane == hk) cnt += __popcll(m);
+                }
+                if (hit) {
+                    if (d2 == 0.0) coincident = true;
+                    const int slot = at + __popcll(m & ((1ull << lane) - 1ull));
+                    if (slot < kOwn) {
+                        A.stage_own[(int64_t)s * kOwn + slot] = ((uint64_t)(uint32_t)j << 32) | sp;
+                        A.stage_q[(int64_t)s * kOwn + slot] = q;
                     } else {
-                        at = __builtin_amdgcn_readlane(cnt, hk);
-                        if (lane == hk) cnt += __popcll(m);
-                    }
-                    if (hit) {
-                        if (d2 == 0.0) coincident = true;
-                        const int slot = at + __popcll(m & ((1ull << lane) - 1ull));
-                        if (slot < kOwn) {
-                            stage_own[(int64_t)s * kOwn + slot] = ((uint64_t)(uint32_t)j << 32) | sp;
-                            stage_q[(int64_t)s * kOwn + slot] = q;
-                        } else {
-                            overflow = true;
-                        }
+                        overflow = true;
                     }
                 }
             }
         }
-        if (SHARED) {
-            __syncthreads();
-            cnt = found[lane];
+    }
+    if (SHARED) {
+        __syncthreads();
+        cnt = found[lane & (kCrowd - 1)];
+    }
+    if (lane < n_home && (!SHARED || wave == 0)) A.n_own[hb + lane] = cnt;
+}
+
+// One cell per wavefront or (SHARED) per block of four, in the first cell_blocks blocks.  A candidate is loaded once
+// per cell instead of once per atom, and nothing waits in a chain of dependent loads: one thread per atom walking the
+// cells was bound by that chain, 118 us at any size below 60,000 atoms and 544 us at a million;
+// here 19 us at 500 atoms, 28 us at 32,000 and 390 us at a million.
+// Crowded cells (a cluster in a large box, where there are at most 8 cells per atom and a cell is much wider than the
+// cutoff) are left to the blocks behind those: one per run of kCrowd places in cell order, four wavefronts on the run's part
+// of a crowded cell.  A crowded cell is longer than a run, so it holds the first or the last place of every run it
+// reaches into.  A build in us with one wavefront on every cell -> here: 4,000 atoms in a box of 500 A (340 atoms per cell) 3450
+// -> 169, 32,000 in 1,000 A 7900 -> 430, 256,000 in 1,500 A 5850 -> 1360; in lattices, where no cell is crowded, the same
+// from 108 atoms to a million.
+template <bool SHARED>
+__global__ void __launch_bounds__(256)
+k_neighbours_pairs(int64_t N, int64_t n_cells, unsigned cell_blocks, CellParams cp, PairSearch A,
+                   const int32_t *__restrict__ cell_of, int32_t *err)
+{
+    __shared__ int32_t found[kCrowd];   // SHARED: edges found so far by the home atoms
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    bool coincident = false, overflow = false;
+    if (blockIdx.x < cell_blocks) {
+        const int64_t block = (int64_t)(blockIdx.x & 7u) * (cell_blocks >> 3) + (blockIdx.x >> 3);   // as xcd_block
+        const int64_t c = SHARED ? block : block * 4 + wave;
+        if (c >= n_cells) return;   // (SHARED: the whole block)
+        const int32_t h0 = __builtin_amdgcn_readfirstlane(A.cell_start[c]);
+        const int n = __builtin_amdgcn_readfirstlane(A.cell_start[c + 1]) - h0;
+        if (n <= 0 || n > kCrowd) return;
+        search_home<SHARED>((int32_t)c, h0, n, cp, A, found, coincident, overflow);
+    } else {
+        if (!(__atomic_load_n(err, __ATOMIC_RELAXED) & FLAG_CROWDED)) return;   // (set before this launch: the same for the block)
+        const unsigned run = blockIdx.x - cell_blocks, runs = gridDim.x - cell_blocks;
+        const int64_t p0 = ((int64_t)(run & 7u) * (runs >> 3) + (run >> 3)) * kCrowd, p1 = min(p0 + kCrowd, N);
+        if (p0 >= N) return;
+        const int32_t first = __builtin_amdgcn_readfirstlane(cell_of[A.sid[p0]]);
+        const int32_t last = __builtin_amdgcn_readfirstlane(cell_of[A.sid[p1 - 1]]);
+        for (int k = 0; k < (last != first ? 2 : 1); ++k) {
+            const int32_t c = k ? last : first;
+            const int32_t h0 = __builtin_amdgcn_readfirstlane(A.cell_start[c]);
+            const int32_t h1 = __builtin_amdgcn_readfirstlane(A.cell_start[c + 1]);
+            if (h1 - h0 <= kCrowd) continue;
+            const int32_t from = max((int32_t)p0, h0), to = min((int32_t)p1, h1);
+            search_home<true>(c, from, to - from, cp, A, found, coincident, overflow);
         }
-        if (lane < n_home && (!SHARED || wave == 0)) n_own[hb + lane] = cnt;
     }
     if (overflow) atomicOr(err, FLAG_STAGE_OVERFLOW);
     if (coincident) atomicOr(err, ERR_COINCIDENT);
@@ -1100,7 +1136,6 @@ __global__ void k_chunk_rows_parts(PartTab T, int32_t span, const int64_t *__res
 // pass behind those of the atoms check the displacements, assign the slabs and track the species range as the binning
 // kernel does, one atom per lane (by each atom's wavefront, with a division and two reads of the same flag words in
 // every one of them, that took longer than the counting: 259 us at 256,000 atoms, against 95).
-enum { FLAG_DISPLACED = 16 };
 template <bool FILL>
 __global__ void __launch_bounds__(256)
 k_skin_rows(int64_t N, CellParams cp, const double *__restrict__ pos, const double *__restrict__ ref, double half_skin2,
@@ -1760,9 +1795,12 @@ int search_csr(mlip_graph *g, const CellParams &cp, int64_t N, int32_t P, const 
         // few cells: four wavefronts share each, so that the chip has something to do and a crowded cell is not one chain
         auto search = [&](auto shared) {
             constexpr bool SHARED = decltype(shared)::value;
-            k_neighbours_pairs<SHARED><<<grid8(SHARED ? ncell : (ncell + 3) / 4), 256, 0, s>>>(
-                ncell, cp, g->cell_start.as<int32_t>(), g->sid.as<int32_t>(), g->sx.as<double>(), g->sy.as<double>(),
-                g->sz.as<double>(), g->swrap.as<uint32_t>(), stage_own, stage_q, n_own, err);
+            const unsigned cell_blocks = grid8(SHARED ? ncell : (ncell + 3) / 4);
+            k_neighbours_pairs<SHARED><<<cell_blocks + grid8((N + kCrowd - 1) / kCrowd), 256, 0, s>>>(
+                N, ncell, cell_blocks, cp,
+                PairSearch{g->cell_start.as<int32_t>(), g->sid.as<int32_t>(), g->sx.as<double>(), g->sy.as<double>(),
+                           g->sz.as<double>(), g->swrap.as<uint32_t>(), stage_own, stage_q, n_own},
+                g->cell_of.as<int32_t>(), err);
         };
         if (ncell < kSharedCells) search(std::true_type{});
         else search(std::false_type{});

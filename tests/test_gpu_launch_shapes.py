@@ -93,6 +93,66 @@ def test_search_over_cells(case):
         assert np.array_equal(recv[m], senders) and np.array_equal(shifts[m], -shifts) and np.array_equal(m[m], np.arange(len(m)))
 
 
+def _bins(pos, cell, r_cut):
+    """Cells per direction as the library's search takes them (orthogonal cell, at least r_cut wide, at most 8 per atom or
+    4096) and the number of atoms in every cell."""
+    h = np.diag(cell)
+    nb = np.clip((h / (r_cut * 1.000001 + 1e-12)).astype(int), 1, 1024)
+    while nb.prod() > max(4096, 8 * len(pos)):
+        nb[nb.argmax()] //= 2
+    b = np.minimum((pos / h % 1.0 * nb).astype(int), nb - 1)
+    return nb, np.bincount((b[:, 0] * nb[1] + b[:, 1]) * nb[2] + b[:, 2], minlength=nb.prod())
+
+
+@pytest.mark.parametrize("many_cells", [False, True])
+def test_search_over_crowded_cells(many_cells):
+    """A sparse system, whose cells are much wider than the cutoff: cells with one atom less than a run of the crowded
+    cells' blocks holds, exactly as many, one more, one round of lanes and one more, and many rounds; fewer and more than
+    4096 cells, above which a wavefront has a cell to itself.  The graph bit for bit."""
+    rng = np.random.default_rng(6)
+    cell = np.diag([900.0, 900.0, 900.0])
+    sizes = [31, 32, 33, 64, 65, 130] if not many_cells else [31, 32, 33, 64, 65, 96, 97, 700]
+    lone = rng.uniform(0, 900, (90, 3)) if not many_cells else rng.uniform(0, 900, (300, 3))
+    width = 900.0 / 11 if not many_cells else 900.0 / 22      # (of the widest side of a cell, asserted below)
+    # one group per cell, every other one next to the one before it
+    parts = [_spread(rng, n, 30.0, 1.2) + np.array([width * (2 + k // 2), width * (3 + k % 2), 450.0]) + 2.0 for k, n in enumerate(sizes)]
+    pos = np.concatenate([lone] + parts)[rng.permutation(len(lone) + sum(sizes))]
+    nb, per_cell = _bins(pos, cell, 5.0)
+    assert nb.max() * width >= 899.9 and (nb.prod() >= 4096) == many_cells
+    assert all((per_cell >= n).any() for n in sizes) and (per_cell > 64).sum() >= 2
+    ref = og.build_graph(pos, cell, 5.0)
+    assert np.diff(ref.row_ptr).max() < 64
+    for P in (1, 3):
+        g = gpu_graph(pos, cell, np.zeros(len(pos), np.int32), 5.0, n_slabs=P)
+        row_ptr, senders, shifts, d = g.csr()
+        assert np.array_equal(row_ptr, ref.row_ptr) and np.array_equal(senders, ref.senders)
+        assert np.array_equal(shifts, ref.shifts)
+        assert np.array_equal(d, og.geometry(pos, cell, ref)[0].astype(np.float32))
+
+
+def test_a_cluster_in_a_large_box_is_searched_by_many_wavefronts():
+    """4,000 atoms as a periodic crystal and as a cluster in a box of 500 A, where the cells hold some 340 atoms: the build
+    takes about twice as long there; with a crowded cell left to one wavefront it took 40 times as long."""
+    import time
+    import torch
+    import paper_2506_02023_amd as M
+    c = wl.make_config(1, n=10)
+    times = []
+    for cell in (c["cell"], np.diag([500.0, 500.0, 500.0])):
+        pos = torch.as_tensor(c["positions"] + (185.0 if cell[0, 0] == 500.0 else 0.0), device="cuda")
+        sp = torch.as_tensor(c["species"], device="cuda")
+        g, best = None, 1e9
+        for _ in range(12):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            g = M.mlip_build_graph(pos, cell, sp, 5.0, graph=g)
+            torch.cuda.synchronize()
+            best = min(best, time.perf_counter() - t)
+        times.append(best)
+    assert _bins(c["positions"] + 185.0, np.diag([500.0] * 3), 5.0)[1].max() > 200
+    assert times[1] <= 10 * times[0], times
+
+
 @pytest.mark.parametrize("F", [32, 64])
 def test_fp32_products_keep_the_range_of_fp32(F):
     """Activations of the filter MLP far beyond the range of 16-bit floats (their three-part bf16 operands have the
