@@ -19,7 +19,7 @@ SOURCES = {"api.hip": [], "graph.hip": ["-ffp-contract=off"], "model.hip": []}
 
 
 def build(verbose=False, defines=(), lib=LIB, build_dir=BUILD):
-    """defines: extra -D macros (timing experiments, e.g. MLIP_TIMING_SKIP_PAIR_PHASE); such a build goes to another
+    """defines: extra -D macros (other launch shapes, e.g. MLIP_BWD_WAVES=12); such a build goes to another
     `lib` path, never to the library the binding loads."""
     os.makedirs(build_dir, exist_ok=True)
 

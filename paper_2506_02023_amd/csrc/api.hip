@@ -371,7 +371,7 @@ void mlip_graph_destroy(mlip_graph_t *g)
     if (!g) return;
     (void)hipStreamSynchronize(g->stream);   // once, here: the buffers' release below need not synchronise again
     DevBuf *bufs[] = {&g->pos, &g->species, &g->cell_of, &g->wrapp, &g->in_cell, &g->cell_start,
-                      &g->sid, &g->sx, &g->sy, &g->sz, &g->swrap, &g->counts, &g->keys, &g->stage, &g->pair_aux, &g->flags, &g->scan_tmp,
+                      &g->sid, &g->sx, &g->sy, &g->sz, &g->swrap, &g->counts, &g->keys, &g->stage, &g->pair_aux, &g->scan_tmp,
                       &g->small, &g->row_ptr, &g->senders, &g->recv, &g->mirror, &g->shiftp, &g->d, &g->chunk_row, &g->slab_of,
                       &g->local_in_owner, &g->class_off, &g->wpack, &g->energy_part, &g->work, &g->pair_cnt, &g->pair_scan, &g->pair_rank,
                       &g->cand_row_ptr, &g->cand_senders, &g->cand_recv, &g->cand_shiftp, &g->cand_d, &g->cand_mirror, &g->ref_pos};
@@ -394,7 +394,7 @@ void mlip_graph_destroy(mlip_graph_t *g)
     for (auto &v : g->slabs) drop_view(v);
     {
         PartStore &st = g->part;
-        DevBuf *sb[] = {&st.nodes, &st.owned_sorted, &st.ghost_owner, &st.ghost_src, &st.rowlen, &st.row_abs, &st.row_ptr,
+        DevBuf *sb[] = {&st.nodes, &st.owned_sorted, &st.rowlen, &st.row_abs, &st.row_ptr,
                         &st.senders, &st.recv, &st.mirror, &st.shiftp, &st.d, &st.chunk_row, &st.gbase, &st.ghost_local};
         for (DevBuf *b : sb) b->release();
     }

@@ -41,9 +41,6 @@ __device__ inline int floordiv(int a, int b)
 }
 
 enum { ERR_RANGE = 1, ERR_COINCIDENT = 2, ERR_MIRROR = 4, FLAG_STAGE_OVERFLOW = 8, FLAG_DISPLACED = 16, FLAG_CROWDED = 32 };
-// neighbours found by the counting pass are parked in a fixed-width row per atom, from where the sort picks them
-// up; an atom with more neighbours than this sets FLAG_STAGE_OVERFLOW and the rows are filled by a second pass
-constexpr int kStage = 96;
 constexpr int kCrowd = 32;   // a cell with more atoms is crowded (k_neighbours_pairs)
 
 // ---------------------------------------------------------------- scans
@@ -321,10 +318,9 @@ __global__ void k_fill_cells(int64_t N, const double *__restrict__ pos, const in
     swrap[slot] = wrapp[i];
 }
 
-// One thread per atom, atoms taken in cell order so that a wavefront walks the
-// same candidate cells.  FILL = false counts and, if `keys` is given, parks the first kStage unsorted keys
-// (sender << 32 | packed shift) in the atom's staging row keys[i * kStage ...]; FILL = true writes the keys
-// into the atom's CSR row.
+// One-sided search, for rows that the staging rows of the pair-wise search (below) do not hold.  One thread per atom, atoms
+// taken in cell order so that a wavefront walks the same candidate cells.  FILL = false counts; FILL = true writes the
+// unsorted keys (sender << 32 | packed shift) into the atom's CSR row.
 // The search is bound by the latency of its dependent loads, not by the fp64 pair tests: the next candidate's
 // record is requested before the current one is tested.  (Requesting all 27 bin ranges at once and streaming the
 // candidates across bin boundaries needs twice the registers and measured slower.)
@@ -348,7 +344,6 @@ __global__ void k_neighbours(int64_t N, CellParams cp, const int32_t *__restrict
     const int b0 = c / cp.nb[1];
     int64_t base = 0, cap = 0;
     if (FILL) { base = row_ptr[i]; cap = row_ptr[i + 1] - base; }
-    else base = (int64_t)i * kStage;
     int32_t cnt = 0;
     bool coincident = false;
 
@@ -376,7 +371,7 @@ __global__ void k_neighbours(int64_t N, CellParams cp, const int32_t *__restrict
         const double d2 = (t0 * t0 + t1 * t1) + t2 * t2;
         if (d2 <= cp.rc2) {
             if (d2 == 0.0) coincident = true;
-            if (FILL ? cnt < cap : (keys != nullptr && cnt < kStage))
+            if (FILL && cnt < cap)
                 keys[base + cnt] = ((uint64_t)(uint32_t)r.j << 32) | pack3(S0, S1, S2);
             ++cnt;
         }
@@ -407,10 +402,7 @@ __global__ void k_neighbours(int64_t N, CellParams cp, const int32_t *__restrict
             }
         }
     }
-    if (!FILL) {
-        counts[i] = cnt;
-        if (keys != nullptr && cnt > kStage) atomicOr(err, FLAG_STAGE_OVERFLOW);
-    }
+    if (!FILL) counts[i] = cnt;
     if (coincident) atomicOr(err, ERR_COINCIDENT);
 }
 
@@ -419,7 +411,7 @@ __global__ void k_neighbours(int64_t N, CellParams cp, const int32_t *__restrict
 constexpr int kRowLds = 512;
 __global__ void __launch_bounds__(64)
 k_sort_rows(int64_t N, CellParams cp, const double *__restrict__ pos, const int64_t *__restrict__ row_ptr,
-            const uint64_t *__restrict__ keys_in, int staged_rows, int32_t *senders, int32_t *recv, uint32_t *shiftp,
+            const uint64_t *__restrict__ keys, int32_t *senders, int32_t *recv, uint32_t *shiftp,
             float *d)
 {
     __shared__ uint64_t lds[kRowLds];
@@ -428,8 +420,6 @@ k_sort_rows(int64_t N, CellParams cp, const double *__restrict__ pos, const int6
     const int lane = threadIdx.x;
     const int64_t base = row_ptr[i];
     const int64_t n = row_ptr[i + 1] - base;
-    // unsorted keys of the row: in the staging row of the atom, or already at the row's place
-    const uint64_t *keys = staged_rows ? keys_in + i * kStage - base : keys_in;
     const bool staged = n <= kRowLds;
     if (staged)
         for (int64_t m = lane; m < n; m += 64) lds[m] = keys[base + m];
@@ -751,46 +741,35 @@ __global__ void k_chunk_rows(int64_t n_rows, int64_t n_chunks, int32_t span, con
 }
 
 // mirror[e] = position of the reverse edge (send(e) <- recv(e), -S).  The edge predicate is symmetric
-// bit for bit, so the reverse edge always exists; rows are sorted by (global sender id, shift), which
-// makes this a binary search in the sender's row.  nodes == nullptr: row and sender ids are global.
-//   PAIRS: only the edge of each pair whose sender id is the larger one (for a self-image pair: the larger
-//          packed shift) searches, and writes both entries of the pair (whole graph);
-//   else:  only edges whose sender is at or after min_sender search (local graphs: the senders that are
-//          ghost rows; all other entries follow from the whole graph's index, see k_local_fill).
-template <bool PAIRS>
+// bit for bit, so the reverse edge always exists; rows are sorted by (sender id, shift), which makes this a binary
+// search in the sender's row.  Only the edge of each pair whose sender id is the larger one (for a self-image pair: the
+// larger packed shift) searches, and writes both entries of the pair.
 __global__ void k_mirror(int64_t E, const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ senders,
                          const int32_t *__restrict__ recv, const uint32_t *__restrict__ shiftp,
-                         const int32_t *__restrict__ nodes, int32_t min_sender, int32_t *__restrict__ mirror,
-                         int32_t *err)
+                         int32_t *__restrict__ mirror, int32_t *err)
 {
     const int64_t e = (int64_t)xcd_block() * blockDim.x + threadIdx.x;
     if (e >= E) return;
     const int32_t r = recv[e], sd = senders[e];
-    if (sd < min_sender) return;
     const uint32_t sp = shiftp[e];
     int a, b, c;
     unpack3(sp, a, b, c);
     const uint32_t sneg = pack3(-a, -b, -c);
-    if (PAIRS && (sd < r || (sd == r && sp < sneg))) return;
-    const uint32_t want_id = (uint32_t)(nodes ? nodes[r] : r);
+    if (sd < r || (sd == r && sp < sneg)) return;
     int64_t lo = row_ptr[sd], hi = row_ptr[sd + 1];
     const int64_t end = hi;
     while (lo < hi) {
         const int64_t mid = (lo + hi) >> 1;
         const int32_t sm = senders[mid];
-        const uint32_t id = (uint32_t)(nodes ? nodes[sm] : sm);
-        bool less = id < want_id;
-        if (id == want_id) less = shiftp[mid] < sneg;   // several images of one neighbour: small cells only
+        bool less = sm < r;
+        if (sm == r) less = shiftp[mid] < sneg;   // several images of one neighbour: small cells only
         if (less) lo = mid + 1; else hi = mid;
     }
     bool ok = false;
-    if (lo < end) {
-        const int32_t sm = senders[lo];
-        ok = (uint32_t)(nodes ? nodes[sm] : sm) == want_id && shiftp[lo] == sneg;
-    }
+    if (lo < end) ok = senders[lo] == r && shiftp[lo] == sneg;
     if (ok) {
         mirror[e] = (int32_t)lo;
-        if (PAIRS) mirror[lo] = (int32_t)e;
+        mirror[lo] = (int32_t)e;
     } else {
         mirror[e] = (int32_t)e;
         atomicOr(err, ERR_MIRROR);
@@ -956,7 +935,6 @@ struct PartTab {
     int64_t n_owned[kMaxSlabs];
     int64_t ghost0[kMaxSlabs + 1];  // first ghost entry
     int64_t chunk0[kMaxSlabs + 1];  // first work-item table entry
-    int64_t n_edges[kMaxSlabs];
 };
 
 __device__ inline int part_find(const int64_t *start, int P, int64_t x)
@@ -968,10 +946,9 @@ __device__ inline int part_find(const int64_t *start, int P, int64_t x)
 }
 
 // Length of each local row.  Owned rows keep their whole global row (one thread per owned atom, which knows its
-// partition and row from its owner record); ghost rows keep only the senders owned by the partition and also record
-// their owner and their row inside the owner (one wavefront per ghost row).  Partition q's lengths start at
-// rowlen[row0[q] + q] (one closing entry of zero per partition, so that one scan yields every
-// partition's n_local + 1 offsets).
+// partition and row from its owner record); ghost rows keep only the senders owned by the partition (one wavefront per
+// ghost row).  Partition q's lengths start at rowlen[row0[q] + q] (one closing entry of zero per partition, so that one
+// scan yields every partition's n_local + 1 offsets).
 __global__ void k_owned_rowlen(int64_t N, PartTab T, const OwnRec *__restrict__ own_rec, const int64_t *__restrict__ row_ptr,
                                int32_t *rowlen)
 {
@@ -985,7 +962,7 @@ __global__ void k_owned_rowlen(int64_t N, PartTab T, const OwnRec *__restrict__ 
 __global__ void __launch_bounds__(256)
 k_ghost_rowlen(PartTab T, const int32_t *__restrict__ nodes, const int64_t *__restrict__ row_ptr,
                const int32_t *__restrict__ senders, const int32_t *__restrict__ slab_of,
-               const OwnRec *__restrict__ own_rec, int32_t *rowlen, int32_t *ghost_owner, int32_t *ghost_src)
+               int32_t *rowlen)
 {
     const int lane = threadIdx.x & 63;
     const int64_t k = (int64_t)xcd_block() * 4 + (threadIdx.x >> 6);   // ghost entry, numbered across the partitions
@@ -1001,11 +978,7 @@ k_ghost_rowlen(PartTab T, const int32_t *__restrict__ nodes, const int64_t *__re
         const bool keep = e < e1 && slab_of[senders[e]] == q;
         cnt += __popcll(__ballot(keep));
     }
-    if (lane == 0) {
-        rowlen[x + q] = cnt;
-        ghost_owner[k] = own_rec[u].slab;
-        ghost_src[k] = own_rec[u].local;
-    }
+    if (lane == 0) rowlen[x + q] = cnt;
 }
 
 // row_ptr of every partition, starting at 0 (row_abs holds the scan over all partitions' lengths), and per
@@ -1853,15 +1826,15 @@ int search_csr(mlip_graph *g, const CellParams &cp, int64_t N, int32_t P, const 
             g->sz.as<double>(), g->swrap.as<uint32_t>(), g->cell_of.as<int32_t>(), nullptr, out.row_ptr->as<int64_t>(),
             g->keys.as<uint64_t>(), err);
         MLIP_HIP(hipGetLastError());
-        k_sort_rows<<<grid8(N), 64, 0, s>>>(N, cp, pos, out.row_ptr->as<int64_t>(), g->keys.as<uint64_t>(), 0,
+        k_sort_rows<<<grid8(N), 64, 0, s>>>(N, cp, pos, out.row_ptr->as<int64_t>(), g->keys.as<uint64_t>(),
                                             out.senders->as<int32_t>(), out.recv->as<int32_t>(), out.shiftp->as<uint32_t>(),
                                             out.d->as<float>());
         MLIP_HIP(hipGetLastError());
         if (out.mirror && E > 0) {
             MLIP_TRY(out.mirror->ensure(Ecap * 4));
-            k_mirror<true><<<grid8(blocks_for(E, 256)), 256, 0, s>>>(E, out.row_ptr->as<int64_t>(), out.senders->as<int32_t>(),
-                                                                     out.recv->as<int32_t>(), out.shiftp->as<uint32_t>(), nullptr,
-                                                                     0, out.mirror->as<int32_t>(), err);
+            k_mirror<<<grid8(blocks_for(E, 256)), 256, 0, s>>>(E, out.row_ptr->as<int64_t>(), out.senders->as<int32_t>(),
+                                                               out.recv->as<int32_t>(), out.shiftp->as<uint32_t>(),
+                                                               out.mirror->as<int32_t>(), err);
             MLIP_HIP(hipGetLastError());
         }
     }
@@ -2077,8 +2050,6 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
         MLIP_TRY(st.nodes.ensure((size_t)TL * 4));
         MLIP_TRY(st.owned_sorted.ensure((size_t)N * 4));
         MLIP_TRY(st.ghost_local.ensure(ng1 * 4));
-        MLIP_TRY(st.ghost_owner.ensure(ng1 * 4));
-        MLIP_TRY(st.ghost_src.ensure(ng1 * 4));
         MLIP_TRY(st.rowlen.ensure((size_t)(TL + P + 1) * 4));
         MLIP_TRY(st.row_abs.ensure((size_t)(TL + P + 1) * 8));
         MLIP_TRY(st.row_ptr.ensure((size_t)(TL + P + 1) * 8));
@@ -2093,8 +2064,7 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
         if (n_ghost_total > 0)
             k_ghost_rowlen<<<grid8((n_ghost_total + 3) / 4), 256, 0, s>>>(
                 T, st.nodes.as<int32_t>(), g->row_ptr.as<int64_t>(), g->senders.as<int32_t>(), g->slab_of.as<int32_t>(),
-                g->local_in_owner.as<OwnRec>(), st.rowlen.as<int32_t>(), st.ghost_owner.as<int32_t>(),
-                st.ghost_src.as<int32_t>());
+                st.rowlen.as<int32_t>());
         MLIP_HIP(hipGetLastError());
         MLIP_TRY(scan(scan_array(st.rowlen.as<int32_t>()), st.row_abs.as<int64_t>(), TL + P, g->scan_tmp, s));
         int64_t *sizes = hp + nmark;
@@ -2117,7 +2087,6 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
             v.n_edges = sizes[2 * q + 1];
             ebase[q] = TE;
             TE += v.n_edges;
-            T.n_edges[q] = v.n_edges;
             T.chunk0[q] = chunk_total;
             v.span = span;
             chunk_total += chunks_of(v.n_edges, span) + 1;
@@ -2161,8 +2130,6 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
             v.mirror = st.mirror.as<int32_t>() + ebase[q];
             v.d = st.d.as<float>() + ebase[q];
             v.chunk_row = st.chunk_row.as<int32_t>() + T.chunk0[q];
-            v.ghost_owner = st.ghost_owner.as<int32_t>() + T.ghost0[q];
-            v.ghost_src = st.ghost_src.as<int32_t>() + T.ghost0[q];
         }
         prof_end(g);
     } else if (!unchecked && s != hipStreamPerThread) {   // (that name is another stream in another thread: wait as below)

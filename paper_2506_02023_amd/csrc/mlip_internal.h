@@ -168,8 +168,6 @@ struct SlabView {
     const float *d = nullptr;              // edge lengths
     int32_t span = 0;                      // edges per work item
     const int32_t *chunk_row = nullptr;    // [chunks_of(n_edges, span) + 1] first row of every work item, then n_local
-    const int32_t *ghost_owner = nullptr;  // [n_ghost] owning slab
-    const int32_t *ghost_src = nullptr;    // [n_ghost] local index inside the owner
     const int32_t *owned_sorted = nullptr; // [n_owned] owned atoms, ascending global id
     std::vector<int64_t> markers;          // host, P + 3
     // model workspace (sized in mlip_forward)
@@ -182,7 +180,7 @@ struct SlabView {
 // Device arrays of all partitions, each array holding the partitions' pieces one after another (one allocation and
 // one kernel launch per step of the partition build instead of one per slab).
 struct PartStore {
-    DevBuf nodes, owned_sorted, ghost_owner, ghost_src;   // i32, pieces of n_local / n_owned / n_ghost entries
+    DevBuf nodes, owned_sorted;                           // i32, pieces of n_local / n_owned entries
     DevBuf rowlen, row_abs, row_ptr;                      // i32 / i64 / i64, pieces of n_local + 1 entries
     DevBuf senders, recv, mirror, shiftp, d;              // pieces of n_edges entries
     DevBuf chunk_row;                                     // i32, pieces of chunks_of(n_edges, span) + 1 entries
@@ -222,7 +220,7 @@ struct mlip_graph {
     // inputs copied in
     mlip::DevBuf pos, species;
     // build scratch
-    mlip::DevBuf cell_of, wrapp, in_cell, cell_start, sid, sx, sy, sz, swrap, counts, keys, stage, pair_aux, flags,
+    mlip::DevBuf cell_of, wrapp, in_cell, cell_start, sid, sx, sy, sz, swrap, counts, keys, stage, pair_aux,
         scan_tmp, small;
     // whole-graph CSR
     mlip::DevBuf row_ptr, senders, recv, mirror, shiftp, d, chunk_row;

@@ -279,7 +279,6 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
     auto small_batch = [&](int p0, int unit, int layer) {
         SmallBatch sb{};
         sb.n = std::min(kBatch, P - p0);
-        sb.first = p0;
         sb.start[0] = 0;
         for (int q = 0; q < kBatch; ++q) {
             if (q >= sb.n) { sb.start[q + 1] = sb.start[q]; continue; }
@@ -287,11 +286,8 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             SmallArgs &a = sb.s[q];
             a.n_owned = v.n_owned;
             a.n_pure = v.n_pure;
-            a.n_ghost = v.n_ghost;
             a.n_local = v.n_local;
             a.nodes = v.nodes;
-            a.ghost_owner = v.ghost_owner;
-            a.ghost_src = v.ghost_src;
             a.row_ptr = v.row_ptr;
             a.senders = v.senders;
             a.mirror = v.mirror;

@@ -305,23 +305,6 @@ k_bond_aggregate(int64_t N, const int64_t *__restrict__ bptr, const int32_t *__r
     if (F == 64 || lane < F) a[i * F + f] = before + acc;
 }
 
-// sum over the 64 lanes of a wavefront on the data-parallel-primitive path (no LDS); the total is returned
-// as a wave-uniform value
-template <int CTRL, int ROW_MASK, bool BOUND> __device__ inline float dpp_shifted(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROW_MASK, 0xf, BOUND));
-}
-__device__ inline float wave_sum(float v)
-{
-    v += dpp_shifted<0x111, 0xf, true>(v);    // row_shr:1  (lanes shifted in from outside a row of 16 read 0)
-    v += dpp_shifted<0x112, 0xf, true>(v);    // row_shr:2
-    v += dpp_shifted<0x114, 0xf, true>(v);    // row_shr:4
-    v += dpp_shifted<0x118, 0xf, true>(v);    // row_shr:8: lane 15 of every row holds the row's sum
-    v += dpp_shifted<0x142, 0xa, false>(v);   // row_bcast:15 into rows 1 and 3
-    v += dpp_shifted<0x143, 0xc, false>(v);   // row_bcast:31 into rows 2 and 3: lane 63 holds the total
-    return readlane_f32(v, 63);
-}
-
 // Reverse of k_triplet_fwd for one centre, any number of bonds, no LDS.  Pbar[b1] and rbar[b1] accumulate over the
 // inner loop in registers; Qbar[b2], ubar[b2] and rbar[b2] are indexed by the inner bond, so they are accumulated
 // in a second sweep with the roles of the loops exchanged (h is recomputed there): every triplet is evaluated twice.

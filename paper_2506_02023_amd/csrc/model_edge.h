@@ -343,11 +343,6 @@ __global__ void __launch_bounds__(kBwdWaves * 64, kBwdWaves == 4 ? 2 : 1) k_edge
     const bool need_gbar = C.need_gbar != 0;
     int q_head = 0, q_count = 0;   // first queued slot, queued pairs
     int q_tail = 0;                // (q_head + q_count) % kQueue, the slot the next pair goes to
-#ifdef MLIP_TIMING_PHASES
-    // timing experiment only: shader-clock cycles this wavefront spends in the dense phase, printed by one wavefront
-    long long t_start = clock64(), t_dense = 0;
-    int n_dense = 0;
-#endif
 
     const ItemQueue items = edge_items(B.chunk_start[B.n], B.work, wave, kBwdWaves);
     int64_t item = items.first;
@@ -466,20 +461,6 @@ __global__ void __launch_bounds__(kBwdWaves * 64, kBwdWaves == 4 ? 2 : 1) k_edge
         q_tail -= (q_tail >= kQueue) ? kQueue : 0;
     };
     auto phase2 = [&]() {
-#ifdef MLIP_TIMING_PHASES
-        const long long t_in = clock64();
-#endif
-#ifdef MLIP_TIMING_SKIP_PAIR_PHASE
-        // timing experiment only (results are wrong): drop the queued pairs without the dense work, which leaves
-        // the streaming phase of the kernel to be timed on its own
-        {
-            const int nv = min(q_count, 32);
-            q_head += nv;
-            q_head -= (q_head >= kQueue) ? kQueue : 0;
-            q_count -= nv;
-            return;
-        }
-#endif
         // ---------------- up to 32 queued pairs
         wave_lds_fence();
         const int nval = min(q_count, 32);
@@ -533,10 +514,6 @@ __global__ void __launch_bounds__(kBwdWaves * 64, kBwdWaves == 4 ? 2 : 1) k_edge
         q_head -= (q_head >= kQueue) ? kQueue : 0;
         q_count -= nval;
         wave_lds_fence();
-#ifdef MLIP_TIMING_PHASES
-        t_dense += clock64() - t_in;
-        ++n_dense;
-#endif
     };
 
     for (; item < part_end; item = items.resolve(drawn)) {
@@ -580,13 +557,6 @@ __global__ void __launch_bounds__(kBwdWaves * 64, kBwdWaves == 4 ? 2 : 1) k_edge
     }   // work items
     while (q_count > 0) phase2();   // queued pairs index this partition's arrays
     }   // partitions
-#ifdef MLIP_TIMING_PHASES
-    long long t_total = clock64() - t_start;
-    asm volatile("" : "+s"(t_total));   // taken before the print starts
-    if (lane == 0 && wave == 0 && blockIdx.x % 37 == 0)
-        printf("k_edge_bwd prec %d first %d block %d : %lld cycles, %lld in %d dense phases\n", PREC, (int)B.c.first,
-               (int)blockIdx.x, t_total, t_dense, n_dense);
-#endif
 }
 
 

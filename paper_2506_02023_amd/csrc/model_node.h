@@ -245,14 +245,12 @@ __global__ void __launch_bounds__(NodeOp<OP>::NW * 64) k_node(NodeBatch B)
 // partitions, start[q] is the first item of partition q.
 
 struct SmallArgs {   // one partition
-    int64_t n_owned, n_pure, n_ghost, n_local;
+    int64_t n_owned, n_pure, n_local;
     const int32_t *nodes;          // local -> global (nullptr: identity)
-    const int32_t *ghost_owner, *ghost_src;
     const int64_t *row_ptr;
     const int32_t *senders, *mirror;
     const uint32_t *shiftp;
-    float *h, *g, *gbar, *abar, *floc, *eps;
-    float *a;                      // the layer's receiver sums (second pass of the pair-wise forward step)
+    float *gbar, *abar, *floc, *eps;
     // upper / lower split of the owned rows' edges
     const int32_t *uslot;          // [E_owned] upper edges: their index in the upper-edge graph, where their filter values are kept
     const int64_t *l_row_ptr;      // the owned rows' lower edges: CSR, sender row, where the pair's filter values are kept
@@ -267,7 +265,6 @@ struct SmallArgs {   // one partition
 
 struct SmallBatch {
     int n;
-    int first;                     // partition index of s[0]
     int64_t start[kBatch + 1];
     SmallArgs s[kBatch];
 };

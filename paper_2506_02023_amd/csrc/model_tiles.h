@@ -243,7 +243,6 @@ template <int F> struct Dims {
     static constexpr int FS = F + 4;      // LDS row stride of an item-major tile
     static constexpr int TILE = 32 * FS;  // floats per 32-item tile
     static constexpr int PACK1 = NB * 3 * 64 * 2;   // floats of a K = 8 pack
-    static constexpr int PACKF = F * F;
     static constexpr int PACK3 = F * F * 3 / 2;   // floats of a three-part bf16 pack
 };
 
