@@ -16,9 +16,19 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 # The products run on the bf16 / fp16 matrix pipeline (2.5 PFLOP/s dense): an fp32 product as the six terms of operands in
-# three bf16 parts, a split-fp16 one as three.  The peak of a mode is that of the pipeline by the number of terms.
+# three bf16 parts, a split-fp16 one as three.  The precision mode applies to the F x F products; those with the K = 8 basis
+# functions are fp32 in every mode.  A kernel's peak is that of the pipeline by the terms it executes per counted flop.
 PEAK_MFMA16_TFLOPS = 2500.0
 PRODUCT_TERMS = {"f32": 6, "f32split": 3, "bf16": 1}
+BASIS_TERMS = 6
+
+
+def matrix_peak_tflops(precision, F, n_basis, K=8):
+    """Peak of a kernel with one F x F product and n_basis products with the basis per item."""
+    ff, basis = 2 * F * F, n_basis * 2 * K * F
+    return PEAK_MFMA16_TFLOPS * (ff + basis) / (PRODUCT_TERMS[precision] * ff + BASIS_TERMS * basis)
+
+
 # Algorithmic flops per directed edge and layer, i.e. of the operation as it is defined:
 #   forward: filter MLP, t = b W1 (2 K F) and w = SiLU(t) W2 (2 F F);
 #   reverse: pre-activations t = b W1 (2 K F), sbar = wbar W2^T (2 F F), dt/dd contraction through W1 (2 K F);
@@ -188,12 +198,12 @@ def main():
     L = c["L"]
     default_workload = args.config == 3 and args.cells is None and args.precision == "f32"   # what the traffic constants were profiled on
 
-    def edge_roofline(group, kernel, flops_edge, traffic, as_defined=None):
+    def edge_roofline(group, kernel, flops_edge, n_basis, traffic, as_defined=None):
         ms, n = prof[group]
         per_launch = E * flops_edge * L * args.steps / max(n, 1)
         avg_ms = ms / max(n, 1)
         ach = per_launch / (avg_ms * 1e-3) / 1e12 if avg_ms > 0 else 0.0
-        peak = PEAK_MFMA16_TFLOPS / PRODUCT_TERMS[args.precision]
+        peak = matrix_peak_tflops(args.precision, c["F"], n_basis)
         r = {"kernel": kernel, "bound": "mfma", "achieved": ach, "peak": peak, "unit": "TFLOP/s",
              "frac": ach / peak, "traffic": traffic if default_workload else None,
              "traffic_source": TRAFFIC_SOURCE if default_workload else None,
@@ -202,13 +212,14 @@ def main():
         if as_defined is not None:   # rate of the operation as defined (twice the executed work), not a utilisation
             r["as_defined_tflops"] = ach * as_defined / flops_edge
             r["flops_per_edge_layer"] = {"executed": flops_edge, "as_defined": as_defined}
-        r["note"] = f"peak: 16-bit matrix pipeline, {PRODUCT_TERMS[args.precision]} term(s) per product"
+        r["note"] = (f"peak: 16-bit matrix pipeline, {PRODUCT_TERMS[args.precision]} term(s) per F x F product, "
+                     f"{BASIS_TERMS} per product with the basis")
         return r
 
     F = c["F"]
-    roof_bwd = edge_roofline("edge_bwd", f"k_edge_bwd<{F}> (reverse edge step)", flops_bwd_edge(F),
+    roof_bwd = edge_roofline("edge_bwd", f"k_edge_bwd<{F}> (reverse edge step)", flops_bwd_edge(F), 2,
                              TRAFFIC_BWD_LAUNCH_BYTES, flops_bwd_edge_as_defined(F))
-    roof_fwd = edge_roofline("edge_fwd", f"k_edge_fwd<{F}> (forward edge step)", flops_fwd_edge(F), TRAFFIC_FWD_LAUNCH_BYTES)
+    roof_fwd = edge_roofline("edge_fwd", f"k_edge_fwd<{F}> (forward edge step)", flops_fwd_edge(F), 1, TRAFFIC_FWD_LAUNCH_BYTES)
     if prof["edge_bwd_lower"][1] > 0:   # the reverse operation as defined takes both of its passes
         both_ms = prof["edge_bwd"][0] + prof["edge_bwd_lower"][0]
         roof_bwd["kernel"] = f"k_edge_bwd<{F}> on the upper-edge graphs (reverse edge step, first pass)"
