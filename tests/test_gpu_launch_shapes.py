@@ -59,22 +59,41 @@ def test_rows_at_the_edges_of_items_and_tiles(kind, F, L):
             assert np.abs(f - ref["forces"]).max() <= 1e-4 * np.abs(ref["forces"]).max(), what
 
 
+def _bins(pos, cell, r_cut):
+    """Cells per direction as the library's search takes them (orthogonal cell, at least r_cut wide, at most 8 per atom or
+    4096) and the number of atoms in every cell."""
+    h = np.diag(cell)
+    nb = np.clip((h / (r_cut * 1.000001 + 1e-12)).astype(int), 1, 1024)
+    while nb.prod() > max(4096, 8 * len(pos)):
+        nb[nb.argmax()] //= 2
+    b = np.minimum((pos / h % 1.0 * nb).astype(int), nb - 1)
+    return nb, np.bincount((b[:, 0] * nb[1] + b[:, 1]) * nb[2] + b[:, 2], minlength=nb.prod())
+
+
 @pytest.mark.parametrize("case", ["one_cell", "thin", "crowded", "many_cells", "overflow"])
 def test_search_over_cells(case):
     """Cells with no, few and more than 64 atoms, one cell in all, more than 64 surrounding cells, images of an atom
-    itself, more than 4096 cells, and rows longer than the staging rows hold: the graph bit for bit."""
+    itself, more than 4096 cells, and rows longer than the staging rows hold (the build then falls back to the two-pass
+    search): the graph bit for bit."""
     rng = np.random.default_rng(5)
     if case == "one_cell":      # every pair is seen through several images of the one cell
         pos, cell, sp = wl.random_triclinic(9, 3, scale=3.2, skew=0.2, spread=2.0)
-    elif case == "thin":        # reach of 4 cells along the thin direction: 9 x 3 x 3 surrounding cells and more
-        cell = np.array([[1.7, 0.0, 0.0], [0.3, 14.0, 0.0], [0.0, 1.0, 16.0]])
+    elif case == "thin":        # reach of 4 cells and more along the thin direction: at least 9 x 3 x 3 surrounding cells
+        cell = np.array([[1.2, 0.0, 0.0], [0.3, 14.0, 0.0], [0.0, 1.0, 16.0]])
         pos = rng.uniform(0, 1, (11, 3)) @ cell
-    elif case == "crowded":     # a sparse system whose cells were widened: 150 atoms fall into a few of them
+        heights = 1.0 / np.linalg.norm(np.linalg.inv(cell), axis=0)
+        nb = np.maximum((heights / 5.00001).astype(int), 1)
+        around = 2 * np.ceil(5.0 / (heights / nb)).astype(int) + 1
+        assert around[0] >= 9 and around.prod() > 64
+    elif case == "crowded":     # a sparse system whose cells were widened: 150 atoms fall into one of them
         cell = np.diag([900.0, 900.0, 900.0])
-        pos = np.concatenate([_spread(rng, 150, 20.0, 1.2) + 400.0, rng.uniform(0, 900, (30, 3))])
+        pos = np.concatenate([_spread(rng, 150, 20.0, 1.2) + 415.0, rng.uniform(0, 900, (30, 3))])
+        nb, per_cell = _bins(pos, cell, 5.0)
+        assert nb.prod() < 4096 and per_cell.max() >= 150
     elif case == "many_cells":  # 17^3 cells, most of them empty, four to a block
         cell = np.diag([86.0, 87.0, 88.0])
         pos = np.concatenate([_spread(rng, 120, 25.0, 1.0) + 70.0, rng.uniform(0, 86, (700, 3))])
+        assert _bins(pos, cell, 5.0)[0].prod() > 4096
     else:                       # more than 64 finds of one atom: the build falls back to the two-pass search
         cell = np.diag([30.0, 30.0, 30.0])
         pos = _spread(rng, 260, 8.5, 0.75) + 3.0
@@ -91,17 +110,6 @@ def test_search_over_cells(case):
         m = g.mirror()
         recv = np.repeat(np.arange(len(pos)), np.diff(row_ptr))
         assert np.array_equal(recv[m], senders) and np.array_equal(shifts[m], -shifts) and np.array_equal(m[m], np.arange(len(m)))
-
-
-def _bins(pos, cell, r_cut):
-    """Cells per direction as the library's search takes them (orthogonal cell, at least r_cut wide, at most 8 per atom or
-    4096) and the number of atoms in every cell."""
-    h = np.diag(cell)
-    nb = np.clip((h / (r_cut * 1.000001 + 1e-12)).astype(int), 1, 1024)
-    while nb.prod() > max(4096, 8 * len(pos)):
-        nb[nb.argmax()] //= 2
-    b = np.minimum((pos / h % 1.0 * nb).astype(int), nb - 1)
-    return nb, np.bincount((b[:, 0] * nb[1] + b[:, 1]) * nb[2] + b[:, 2], minlength=nb.prod())
 
 
 @pytest.mark.parametrize("many_cells", [False, True])
