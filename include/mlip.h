@@ -51,7 +51,9 @@ typedef enum {
 enum { MLIP_MODE_WHOLE = 0, MLIP_MODE_SLABS = 1 };
 /*
  * MLIP_PRECISION_FP32: everything from the basis on in fp32 (products as exact sums of three bf16 parts per operand on the
- *   bf16 matrix units, all terms down to 2^-24, accumulated in fp32).
+ *   bf16 matrix units, all terms down to 2^-24, accumulated in fp32).  An operand beyond the bf16 range (3.39e38; fp32 ends
+ *   at 3.40e38) or infinite makes its row of the product NaN, as it does in the fp32 products of the other modes: a result
+ *   that is not finite may be NaN where an fp32 multiplication would have given an infinity.
  * MLIP_PRECISION_BF16: the F x F products of the filter MLP (forward w = SiLU(t) W2, reverse sbar = wbar W2^T)
  *   take bf16 operands with fp32 accumulation (benchmark configuration 4: "edge MLPs in bf16 with fp32
  *   accumulation"), and in mlip_forward_bonds the F x F products of the bond MLPs as well; everything else stays
@@ -166,9 +168,12 @@ typedef struct {
  *              rebuilt in place and reuses its device buffers (grow-only); on another stream than
  *              before, the call waits for what the handle has queued on the old one first
  *
- * Edges are stored sorted by (receiver, sender, Sx, Sy, Sz).  The call synchronises the
- * stream once for a whole graph and up to three times with slabs (edge and partition sizes are needed on the host).
- * Positions and species are copied into the handle.
+ * Edges are stored sorted by (receiver, sender, Sx, Sy, Sz).  The call synchronises the stream where it needs sizes or
+ * error flags on the host: for the edge count, and with slabs twice more (span starts; edge counts of the partitions).
+ * Further waits: one where an atom has more neighbours than the search's staging rows hold (64 found by itself, 64 by its
+ * partners), and then, as in every build with a skin or of more than 6.7 million atoms, one at the end of a whole graph;
+ * one or two where a skin's candidate list is made or made anew.  The build's last kernels may still run when the call
+ * returns.  Positions and species are copied into the handle.
  */
 int mlip_build_graph(const double *positions, const double *cell, const int32_t *species,
                      int64_t n_atoms, double r_cut, int32_t n_slabs, void *stream,

@@ -1754,7 +1754,7 @@ int search_csr(mlip_graph *g, const CellParams &cp, int64_t N, int32_t P, const 
     int64_t E = 0;
     int32_t flags = 0;
     // Pair-wise search (every pair tested once, reverse-edge index without a search) unless its staging rows
-    // (1.5 KB per atom) would take more than 8 GB; an atom with more neighbours than the staging rows hold
+    // and their slots (1.5 KB per atom) would take about 10 GB; an atom with more neighbours than the staging rows hold
     // (kOwn found by itself, kPar by its partners) sets FLAG_STAGE_OVERFLOW and the one-sided search below runs instead
     bool done = false;
     if ((size_t)N * (kOwn + kPar) * 10 <= ((size_t)8 << 30)) {

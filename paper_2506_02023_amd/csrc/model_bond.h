@@ -638,7 +638,8 @@ template <int STAGE> struct BondStage {
 };
 
 // PREC: the F x F products follow the precision mode of the filter MLP's (fp32 as three-part bf16; bf16 operands; split-fp16
-// triples; packs prepared accordingly, activations converted in registers, fp32 accumulation); the K = 8 products stay fp32.
+// triples; packs prepared accordingly, activations converted in registers, fp32 accumulation); the K = 8 products are fp32 products
+// (three-part bf16) in every mode.
 // The [bonds x F] arrays are bf16 in the bf16 mode and fp32 otherwise.
 template <int PREC> struct BondElem { typedef float type; };
 template <> struct BondElem<kPrecBf16> { typedef __bf16 type; };

@@ -285,8 +285,8 @@ __global__ void k_zero_ghost_rows(SmallBatch B, int F)
 // Second pass of the reverse edge step: the lower edges' terms of the row sums, with the filter values w read from the
 // row of the edge's pair, which the forward kernel kept: gbar_i += sum over the lower edges e = (i <- j) of row i of
 // w * abar_j.  One wavefront per row, lane = feature; the lower edges of 64 edges at a time are taken kLowerChunk at a
-// time, all their rows in flight together.  Bound by the kept rows' bytes: 1.21 ms at a million atoms for 5.9 GB of them,
-// 4.9 TB/s, what a large copy reaches on this card.
+// time, all their rows in flight together.  Bound by the kept rows' bytes: 1.21 ms at a million atoms for 5.9 GB of them, 8.0 GB
+// with the gathered rows as measured, 6.6 TB/s (a large copy reaches 4.67 TB/s on this card, a large read 6 to 7).
 constexpr int kLowerChunk = 16;   // lower edges whose rows are in flight together (32 measured no faster)
 
 template <int F>

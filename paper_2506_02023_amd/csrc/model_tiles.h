@@ -221,7 +221,7 @@ __device__ inline bf16x8 to_bf16x8(const float (&v)[8])
 }
 
 // v = h + m + l with three bf16 parts, exactly unless l underflows: 8 significant bits each, rounded to nearest, what
-// is left after each part is exact in fp32
+// is left after each part is exact in fp32.  An infinity (and what rounds to one: beyond 3.39e38) becomes NaN.
 __device__ inline void split_bf16x3(const float (&v)[8], bf16x8 &h, bf16x8 &m, bf16x8 &l)
 {
 #pragma unroll
@@ -362,8 +362,8 @@ __device__ inline void gemm_row_f16x3(const _Float16 *__restrict__ Ap, const flo
         }
 }
 
-// fp32 products as three-part bf16 operands: x y = (h + m + l)(h' + m' + l'), of which the six terms down to 2^-16 of the
-// product are taken, smallest first (l m', m l' and l l' are below 2^-25 of it, half an fp32 rounding).  24 MFMAs of a
+// fp32 products as three-part bf16 operands: x y = (h + m + l)(h' + m' + l'), of which the six largest terms (down to
+// 2^-18 of the product) are taken, smallest first (l m', m l' and l l' are together below 2^-25 of it, half an fp32 rounding).  24 MFMAs of a
 // chain round at full size for 64 terms, where the fp32 instruction makes 32.  The A operands of the next step are
 // requested before the MFMAs of this one.
 template <int F, bool ACCUMULATE, class Values>

@@ -178,6 +178,28 @@ def test_fp32_products_keep_the_range_of_fp32(F):
     assert np.abs(f - ref["forces"]).max() <= 1e-4 * np.abs(ref["forces"]).max()
 
 
+@pytest.mark.parametrize("precision", [0, 1, 2])
+def test_a_non_finite_atom_spoils_only_what_depends_on_it(precision):
+    """Two groups out of each other's reach, their atoms alternating in the arrays (so they share tiles): the embedding of a
+    species that one group alone has is infinite.  Everything that depends on it comes out non-finite, the other group's
+    energies and forces are those of that group by itself."""
+    import paper_2506_02023_amd as M
+    pos, cell = _system("halves")
+    n = len(pos) // 2
+    pos = np.stack([pos[:n], pos[n:]], 1).reshape(-1, 3)      # even: one group, odd: the other
+    species = np.zeros(2 * n, np.int32)
+    species[0::2], species[1::2] = 3, np.arange(n) % 3
+    weights = wl.rmp_weights(4, 64, 2, 79)
+    _, f_ref, eps_ref = gpu_energy_forces(gpu_graph(pos, cell, species, 5.0), weights, 6, M.MODE_WHOLE, precision)
+    weights["emb"][3, 5] = np.inf
+    for P in (1, 3):
+        mode = M.MODE_SLABS if P > 1 else M.MODE_WHOLE
+        e, f, eps = gpu_energy_forces(gpu_graph(pos, cell, species, 5.0, n_slabs=P), weights, 6, mode, precision)
+        assert not np.isfinite(e) and not np.isfinite(eps[0::2]).any()
+        assert np.array_equal(eps[1::2], eps_ref[1::2])
+        assert np.abs(f[1::2] - f_ref[1::2]).max() <= (2e-2 if precision == 1 else 1e-4) * np.abs(f_ref[1::2]).max()
+
+
 @pytest.mark.parametrize("F,L", [(32, 1), (64, 3)])
 def test_bonds_per_centre_at_the_edges(F, L):
     """Clusters whose atoms are all bonded to one another: 0, 1, 2, 3, 4, 5, 15, 16 (the most that the triplet kernels hold in
