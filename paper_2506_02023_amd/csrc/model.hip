@@ -353,7 +353,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             pb.add(w->Wo + l * ff, base + pk.Wot, PACK_FF_BF16X3, 1, 1.0f);
             pb.add(w->Wo + l * ff, base + pk.Won, PACK_FF_BF16X3, 0, 1.0f);
         }
-        pb.add(w->Wr1, wp + pk.readout_t, PACK_FF_BF16X3, 1, 1.0f);
+        pb.add(w->Wr1, wp + pk.readout_t, PACK_FF_BF16X3_ALT, 1, 1.0f);
         pb.add(w->Wr1, wp + pk.readout_n, PACK_FF_BF16X3, 0, 1.0f);
         k_pack<<<dim3(blocks_for((int64_t)F * F, 256), pb.n), 256, 0, s>>>(pb);
     }

@@ -180,7 +180,7 @@ __global__ void __launch_bounds__(NodeOp<OP>::NW * 64) k_node(NodeBatch B)
                 for (int a = 0; a < 4; ++a)
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
-                        const float wv = B.wr2[32 * b + 8 * a + h4 + c], v = y[b][4 * a + c];
+                        const float wv = B.wr2[32 * b + 8 * a + h4 + c], v = c & 1 ? -y[b][4 * a + c] : y[b][4 * a + c];
                         const float sg = sigmoidf_fast(v);
                         part_eps += v * sg * wv;
                         y[b][4 * a + c] = wv * sg * (1.0f + v * (1.0f - sg));

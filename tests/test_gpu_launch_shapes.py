@@ -237,3 +237,38 @@ def test_bonds_per_centre_at_the_edges(F, L):
             what = f"F {F} L {L} P {P} precision {precision}"
             assert abs(float(e[0]) - ref["energy"]) <= e_tol * np.abs(ref["atom_energy"]).sum(), what
             assert np.abs(f.cpu().numpy() - ref["forces"]).max() <= f_tol * np.abs(ref["forces"]).max(), what
+
+
+@pytest.mark.parametrize("F", [32, 64])
+def test_readout_products_do_not_shift_the_energy(F):
+    """The matrix unit cuts bits off (towards minus infinity) where it aligns the products of one instruction, which shifts
+    every sum of the readout the same way; weights wr2 of one sign would carry that into the total energy of any system.
+    4,096 atoms of as many species without neighbours: the mean error of dense products against that of exact ones
+    (a unit matrix), which have the same sigmoid.  Of the shift, 1.0e-8 of the energy, no more than a third may be left
+    (1.9e-9 with fp32 matrix instructions; the means' own scatter is 1e-7 over the square root of 4 x 4,096 x F values)."""
+    import paper_2506_02023_amd as M
+    n = 16
+    pos = np.stack(np.meshgrid(*[np.arange(n) * 6.0] * 3, indexing="ij"), -1).reshape(-1, 3)
+    cell, species = np.diag([6.0 * n] * 3), np.arange(n ** 3).astype(np.int32)
+    g = gpu_graph(pos, cell, species, 5.0)
+    assert g.sizes()[1] == 0
+    shift = {}
+    for kind in ("exact", "dense"):
+        off, scale = 0.0, 0.0
+        for seed in range(4):
+            rng = np.random.default_rng([seed, 21])
+            h = rng.standard_normal((n ** 3, F)).astype(np.float32)
+            Wr1 = (rng.standard_normal((F, F)) / np.sqrt(F)).astype(np.float32)
+            if kind == "exact":   # one term per sum, both factors with 8 significant bits
+                h, Wr1 = (h.view(np.int32) & -65536).view(np.float32), np.eye(F, dtype=np.float32)
+            w = {k: v[:0] if k in ("W1", "W2", "Wm", "Wo") else v for k, v in wl.rmp_weights(4, F, 1, seed).items()}
+            w.update(emb=h, Wr1=Wr1, wr2=np.full(F, -0.125, np.float32))
+            g.invalidate_weights()   # (the next model's arrays may lie where the last one's did)
+            e, _, _ = gpu_energy_forces(g, w, 6, M.MODE_WHOLE)
+            y = h.astype(np.float64) @ Wr1.astype(np.float64)
+            s = y / (1.0 + np.exp(-y))
+            off += e + 0.125 * s.sum()
+            scale += 0.125 * np.abs(s).sum()
+        shift[kind] = off / scale
+    print(F, shift)
+    assert abs(shift["dense"] - shift["exact"]) <= 1.0e-8 / 3, shift
