@@ -6,6 +6,7 @@ The names mirror include/mlip.h.
 from __future__ import annotations
 
 import ctypes
+import itertools
 import os
 
 import numpy as np
@@ -145,6 +146,7 @@ class Graph:
 
     def __init__(self, allocator=None):
         self._h = ctypes.c_void_p(None)
+        self._weights = (None, None)   # serial numbers of the weights its packed operands belong to
         self.allocator = TorchAllocator() if allocator is None else (allocator or None)
         if self.allocator is not None:
             _check(lib().mlip_graph_create(ctypes.byref(self.allocator.c), ctypes.byref(self._h)))
@@ -286,6 +288,19 @@ def mlip_build_graph(positions, cell, species, r_cut, n_slabs=1, graph=None):
     return g
 
 
+_serial = itertools.count()   # one number per Weights / BondWeights object
+
+
+def _note_weights(graph, weights, bond_weights=None):
+    """The library keeps the packed operands of a weight struct and knows it by its addresses, at which the arrays of
+    another object may lie once the first one's are freed: drop them when a call comes with another object."""
+    last, bond_last = graph._weights
+    now = (weights.serial, bond_last if bond_weights is None else bond_weights.serial)
+    if (last is not None and last != now[0]) or (bond_last is not None and bond_last != now[1]):
+        graph.invalidate_weights()
+    graph._weights = now
+
+
 class Weights:
     """Device copies of the model weights plus the POD struct the library takes."""
 
@@ -294,6 +309,7 @@ class Weights:
         2 = those products as split-fp16 triples (fp32-grade results)."""
         self.t = {k: torch.as_tensor(np.ascontiguousarray(weights[k], np.float32)).to(device).contiguous()
                   for k in ("emb", "W1", "W2", "Wm", "Wo", "Wr1", "wr2")}
+        self.serial = next(_serial)
         S, F = self.t["emb"].shape
         L = self.t["W1"].shape[0]
         self.F, self.L = F, L
@@ -307,6 +323,7 @@ class BondWeights:
     def __init__(self, weights, r_bond, A=8, device="cuda"):
         self.t = {k: torch.as_tensor(np.ascontiguousarray(weights[k], np.float32)).to(device).contiguous()
                   for k in ("We0", "Wt1", "Wt2", "Wb")}
+        self.serial = next(_serial)
         self.c = _BondWeights(float(r_bond), int(A), *[self.t[k].data_ptr() for k in ("We0", "Wt1", "Wt2", "Wb")])
 
 
@@ -319,6 +336,7 @@ def mlip_forward_bonds(graph, weights, bond_weights, mode=MODE_WHOLE, out=None, 
         atom_e = torch.empty(N, dtype=torch.float32, device="cuda") if want_atom_energy else None
     else:
         energy, forces, atom_e = out
+    _note_weights(graph, weights, bond_weights)
     _check(lib().mlip_forward_bonds(graph._h, ctypes.byref(weights.c), ctypes.byref(bond_weights.c), int(mode),
                                     ctypes.c_void_p(energy.data_ptr()), ctypes.c_void_p(forces.data_ptr()),
                                     ctypes.c_void_p(atom_e.data_ptr() if atom_e is not None else None)))
@@ -339,6 +357,7 @@ def mlip_forward(graph, weights, mode=MODE_WHOLE, out=None, want_atom_energy=Tru
         atom_e = torch.empty(N, dtype=torch.float32, device="cuda") if want_atom_energy else None
     else:
         energy, forces, atom_e = out
+    _note_weights(graph, weights)
     _check(getattr(lib(), _fn)(graph._h, ctypes.byref(weights.c), int(mode), ctypes.c_void_p(energy.data_ptr()),
                               ctypes.c_void_p(forces.data_ptr()),
                               ctypes.c_void_p(atom_e.data_ptr() if atom_e is not None else None)))

@@ -118,3 +118,27 @@ def test_packed_weights_are_cached_and_invalidated():
     assert_energy_forces(r4[0], r4[1], ref2, "other precision")
     r5 = _run(g, c, M.MODE_WHOLE, weights=W)
     assert r5[0] == _run(M.mlip_build_graph(pos, c["cell"], sp, c["r_cut"]), c, M.MODE_WHOLE, weights=W)[0]
+
+
+def test_weights_at_the_addresses_of_freed_ones():
+    """A second model whose arrays lie where those of a first, freed one lay: its results are its own, without the caller
+    having to say that the values changed; the same for the bond part's weights."""
+    import torch
+    import paper_2506_02023_amd as M
+    c = wl.make_config(4, n=4)
+    two = ("emb", "W1", "W2", "Wm", "Wo", "Wr1", "wr2")
+    pos, sp = torch.as_tensor(c["positions"], device="cuda"), torch.as_tensor(c["species"], device="cuda")
+    models = [{**wl.rmp_weights(c["S"], 64, 3, s), **wl.three_body_weights(64, 3, s)} for s in (1, 2)]
+    g = M.mlip_build_graph(pos, c["cell"], sp, c["r_cut"])
+    energies, before = [], None
+    for w in models:
+        now = M.Weights({k: w[k] for k in two}, c["p"]), M.BondWeights(w, c["r_bond"])
+        if before:       # what the caching allocator does when the first objects are gone: the new arrays in their blocks
+            for a, b in zip(now, before):
+                a.t, a.c = {k: b.t[k].copy_(v) for k, v in a.t.items()}, b.c
+        energies.append([float(x[0].cpu()[0]) for x in (M.mlip_forward(g, now[0]), M.mlip_forward_bonds(g, *now))])
+        before = now
+    fresh = M.mlip_build_graph(pos, c["cell"], sp, c["r_cut"])
+    W, BW = M.Weights({k: models[1][k] for k in two}, c["p"]), M.BondWeights(models[1], c["r_bond"])
+    assert energies[1] == [float(x[0].cpu()[0]) for x in (M.mlip_forward(fresh, W), M.mlip_forward_bonds(fresh, W, BW))]
+    assert energies[0] != energies[1]
