@@ -213,7 +213,7 @@ int mlip_graph_skin_stats(const mlip_graph_t *graph, int64_t *list_builds, int64
  *
  * The weights are re-laid-out for the matrix units on the first call and kept in the handle: a later call whose
  * mlip_weights_t (pointers, dimensions, precision) is identical reuses them.  After changing weight VALUES in
- * place, call mlip_graph_invalidate_weights.
+ * place, or when another model's arrays have come to lie at the same addresses, call mlip_graph_invalidate_weights.
  */
 int mlip_forward(mlip_graph_t *graph, const mlip_weights_t *weights, int32_t mode,
                  double *energy, float *forces, float *atom_energy);
