@@ -264,25 +264,29 @@ int mlip_forward(mlip_graph_t *g, const mlip_weights_t *w, int32_t mode, double 
 // for hipGetSymbolAddress, whose result (per device) is what kernels and fills are given.
 #define MLIP_STATIC_SCRATCH_BYTES (64u << 20)
 static __device__ __align__(256) unsigned char scratch[MLIP_STATIC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char table_scratch[kStaticTableBytes];   // filter tables, beside the workspace
 
 enum { kMaxDevices = 64 };
 static std::mutex g_scratch_mutex;
-static void *g_scratch_ptr[kMaxDevices] = {nullptr};
+static void *g_scratch_ptr[kMaxDevices][2] = {};
 
-// device address of the array on the current device, looked up once per device
-static int static_scratch(void **out)
+// device addresses of the workspace and of the tables on the current device, looked up once per device
+static int static_scratch(void *(&out)[2])
 {
     int dev = -1;
     MLIP_HIP(hipGetDevice(&dev));
     if (dev < 0 || dev >= kMaxDevices) { set_error("device index %d out of range", dev); return MLIP_EHIP; }
     std::lock_guard<std::mutex> lock(g_scratch_mutex);
-    if (!g_scratch_ptr[dev]) {
-        void *ptr = nullptr;
+    if (!g_scratch_ptr[dev][0]) {
+        void *ptr = nullptr, *tab = nullptr;
         MLIP_HIP(hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)));
-        if (!ptr) { set_error("hipGetSymbolAddress returned a null address for the static workspace"); return MLIP_EHIP; }
-        g_scratch_ptr[dev] = ptr;
+        MLIP_HIP(hipGetSymbolAddress(&tab, HIP_SYMBOL(table_scratch)));
+        if (!ptr || !tab) { set_error("hipGetSymbolAddress returned a null address for the static workspace"); return MLIP_EHIP; }
+        g_scratch_ptr[dev][0] = ptr;
+        g_scratch_ptr[dev][1] = tab;
     }
-    *out = g_scratch_ptr[dev];
+    out[0] = g_scratch_ptr[dev][0];
+    out[1] = g_scratch_ptr[dev][1];
     return MLIP_OK;
 }
 
@@ -296,10 +300,12 @@ int mlip_forward_static(mlip_graph_t *g, const mlip_weights_t *w, int32_t mode, 
         set_error("mlip_forward_static does not run with the event profiler enabled");
         return MLIP_ESTATE;
     }
-    void *base = nullptr;
-    MLIP_TRY(static_scratch(&base));
+    void *base[2] = {nullptr, nullptr};
+    MLIP_TRY(static_scratch(base));
+    if (table_bytes(w->F, w->L) > kStaticTableBytes) { set_error("filter tables larger than their fixed block"); return MLIP_ESTATE; }
     Carver carve;
-    carve.base = static_cast<char *>(base);
+    carve.base = static_cast<char *>(base[0]);
+    carve.tables = base[1];
     carve.size = (size_t)MLIP_STATIC_SCRATCH_BYTES;
     try {
         return forward_impl(g, w, mode, energy, forces, atom_energy, &carve);
@@ -377,6 +383,7 @@ void mlip_graph_destroy(mlip_graph_t *g)
                       &g->cand_row_ptr, &g->cand_senders, &g->cand_recv, &g->cand_shiftp, &g->cand_d, &g->cand_mirror, &g->ref_pos};
     for (DevBuf *b : bufs) b->release();
     g->bond_wpack.release();
+    g->tables.release();
     auto drop_view = [](SlabView &v) {
         BondGraph &B = v.bonds;
         DevBuf *vb[] = {&v.h, &v.hbar, &v.abar, &v.gbar, &v.eps, &v.dsum, &v.floc, &v.g, &v.a, &v.wst,

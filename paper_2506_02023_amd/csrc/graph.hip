@@ -1418,8 +1418,10 @@ __device__ inline int pair_find(const int64_t *start, int n, int64_t w)
 // has 256 of them in flight.
 constexpr uint32_t kRankMax = 65535u;
 constexpr int kCountRows = 4;
-__global__ void __launch_bounds__(256) k_pair_count(PairBatch B, int32_t *__restrict__ cnt, uint16_t *__restrict__ rank)
+__global__ void __launch_bounds__(256) k_pair_count(PairBatch B, int32_t *__restrict__ cnt, uint16_t *__restrict__ rank,
+                                                    const int32_t *gate)
 {
+    if (gate && *gate == 0) return;
     const int lane = threadIdx.x & 63;
     // wavefronts are numbered over groups of kCountRows rows, every partition's last group may be short
     int64_t gw = (int64_t)xcd_block() * 4 + (threadIdx.x >> 6);
@@ -1477,8 +1479,10 @@ __global__ void __launch_bounds__(256) k_pair_count(PairBatch B, int32_t *__rest
 // edges write the row pointers and the work-item tables: u_chunk_row[c] = first row whose first upper edge lies at or
 // after c * span, the last entry = n_rows.
 __global__ void __launch_bounds__(256)
-k_pair_fill(PairBatch B, const int32_t *__restrict__ scan, const uint16_t *__restrict__ rank, int64_t edge_blocks, int64_t row_blocks)
+k_pair_fill(PairBatch B, const int32_t *__restrict__ scan, const uint16_t *__restrict__ rank, int64_t edge_blocks, int64_t row_blocks,
+            const int32_t *gate)
 {
+    if (gate && *gate == 0) return;
     const int64_t block = (int64_t)xcd_block();
     if (block >= edge_blocks + row_blocks) {
         const int64_t gc = (block - edge_blocks - row_blocks) * 256 + threadIdx.x;   // work item, plus one closing entry per partition
@@ -1546,7 +1550,7 @@ k_pair_fill(PairBatch B, const int32_t *__restrict__ scan, const uint16_t *__res
 
 }  // namespace
 
-int build_pairs_impl(mlip_graph *g, SlabView *views, int P, Carver *scratch)
+int build_pairs_impl(mlip_graph *g, SlabView *views, int P, Carver *scratch, const int32_t *gate, bool launch)
 {
     bool all_valid = true;
     for (int p = 0; p < P; ++p) all_valid = all_valid && views[p].pairs.valid;
@@ -1639,20 +1643,20 @@ int build_pairs_impl(mlip_graph *g, SlabView *views, int P, Carver *scratch)
         MLIP_TRY(place(g->pair_cnt, (size_t)(rows + 1) * 4, cnt));
         MLIP_TRY(place(g->pair_scan, (size_t)(rows + 1) * 4, scan_out));
         MLIP_TRY(place(g->pair_rank, (size_t)(edges + 1) * 2, rank));
-        if (scratch && scratch->failed()) return MLIP_OK;   // nothing may be launched on a failed carve; the caller reports it
+        if (!launch || (scratch && scratch->failed())) continue;   // nothing may be launched on a failed carve; the caller reports it
         int64_t groups = 0;
         for (int q = 0; q < b.n; ++q) groups += (b.row_start[q + 1] - b.row_start[q] + kCountRows - 1) / kCountRows;
         if (rows > 0) {
-            k_pair_count<<<grid8((groups + 3) / 4), 256, 0, s>>>(b, cnt, rank);
+            k_pair_count<<<grid8((groups + 3) / 4), 256, 0, s>>>(b, cnt, rank, gate);
             MLIP_HIP(hipGetLastError());
         }
         MLIP_TRY(scan(scan_array(cnt), scan_out, rows, g->scan_tmp, s));
         const int64_t edge_blocks = (edges + 255) / 256, row_blocks = (rows + b.n + 255) / 256;
         const int64_t chunk_blocks = (b.chunk_start[b.n] + b.n + 255) / 256;
-        k_pair_fill<<<grid8(edge_blocks + row_blocks + chunk_blocks), 256, 0, s>>>(b, scan_out, rank, edge_blocks, row_blocks);
+        k_pair_fill<<<grid8(edge_blocks + row_blocks + chunk_blocks), 256, 0, s>>>(b, scan_out, rank, edge_blocks, row_blocks, gate);
         MLIP_HIP(hipGetLastError());
     }
-    for (int p = 0; p < P; ++p) views[p].pairs.valid = (scratch == nullptr);   // arrays in a borrowed block do not outlive the call
+    for (int p = 0; p < P; ++p) views[p].pairs.valid = !scratch && !gate && launch;   // arrays in a borrowed block do not outlive the call
     return MLIP_OK;
 }
 
@@ -1908,7 +1912,10 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
     }
     g->E = 0;
     g->tail = false;
-    if (!g->pinned) MLIP_HIP(hipHostMalloc(&g->pinned, kPinnedBytes, hipHostMallocDefault));
+    if (!g->pinned) {
+        MLIP_HIP(hipHostMalloc(&g->pinned, kPinnedBytes, hipHostMallocDefault));
+        static_cast<int64_t *>(g->pinned)[kPinnedTableWord] = 0;   // no word about filter tables yet
+    }
     int64_t *hp = static_cast<int64_t *>(g->pinned);
 
     MLIP_TRY(g->pos.ensure((size_t)N * 3 * sizeof(double)));
@@ -1964,7 +1971,7 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
     MLIP_TRY(g->mirror.ensure((size_t)std::max<int64_t>(E, 1) * 4));
 
     {
-        g->whole.span = chunk_span(E);
+        g->whole.span = chunk_span(E, kSpanTable);
         const int64_t nc = chunks_of(E, g->whole.span);
         MLIP_TRY(g->chunk_row.ensure((size_t)(nc + 1) * 4));
         k_chunk_rows<<<blocks_for(nc + 1, 256), 256, 0, s>>>(N, nc, g->whole.span, g->row_ptr.as<int64_t>(), g->chunk_row.as<int32_t>());
@@ -2014,7 +2021,7 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
         MLIP_TRY(scan(scan_array(z.class_cnt), g->class_off.as<int32_t>(), nent, g->scan_tmp, s));
         const int nmark = P * (P + 3) + 1;
         // published in pinned host memory: the spans' starts, later every partition's edge counts and the flags
-        static_assert((kMaxSlabs * (kMaxSlabs + 3) + 1 + 2 * kMaxSlabs + 1) * 8 <= kPinnedBytes, "published values fit the pinned area");
+        static_assert((kMaxSlabs * (kMaxSlabs + 3) + 1 + 2 * kMaxSlabs + 1) <= kPinnedTableWord, "published values fit the pinned area");
         k_gather_markers<<<blocks_for(nmark, 256), 256, 0, s>>>(g->class_off.as<int32_t>(), P, nranges, st.gbase.as<int32_t>(), N,
                                                                 hp);
         MLIP_HIP(hipGetLastError());
@@ -2078,7 +2085,7 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
             set_error("internal error: an edge without its reverse edge");
             return MLIP_EHIP;
         }
-        const int32_t span = chunk_span(E * std::min(P, kPairBatch) / P);   // edges of one launch over up to kPairBatch partitions
+        const int32_t span = chunk_span(E * std::min(P, kPairBatch) / P, kSpanTable);   // edges of one launch over up to kPairBatch partitions
         int64_t TE = 0;
         std::vector<int64_t> ebase(P + 1);
         for (int q = 0; q < P; ++q) {

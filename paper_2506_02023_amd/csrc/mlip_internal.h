@@ -54,6 +54,7 @@ struct AllocScope {
 struct Carver {
     char *base = nullptr;
     size_t size = 0, used = 0;
+    void *tables = nullptr;   // a block of its own for the filter tables (kTableBytes)
     void *take(size_t bytes)
     {
         const size_t at = (used + 255) & ~(size_t)255;
@@ -67,7 +68,7 @@ struct Carver {
 // Workspace of one partition for the forward call in progress (from the view's buffers, or carved from a fixed block).
 struct ViewWs {
     float *h = nullptr, *hbar = nullptr, *abar = nullptr, *gbar = nullptr, *eps = nullptr, *dsum = nullptr,
-          *floc = nullptr, *g = nullptr, *a = nullptr, *wst = nullptr;
+          *dsum2 = nullptr, *floc = nullptr, *g = nullptr, *a = nullptr, *wst = nullptr;
 };
 
 // Cell geometry prepared on the host, passed to kernels by value.
@@ -100,11 +101,11 @@ inline unsigned grid8(int64_t blocks) { return (unsigned)(((blocks > 0 ? blocks 
 // forces: 1024 edges throughout -> 8 items per wavefront 500 atoms 1587 -> 632, 108,000 atoms in 8 slabs 4732 -> 4233, a
 // million unchanged (4 items 4302 and 2 items 4591 at 108,000); least span 32 -> 64 later 4,000 atoms 367 -> 347, four
 // models on 16,000 atoms 1190 -> 1106, but 500 atoms 252 -> 275.
-constexpr int kEdgeWaves = 2048, kItemsPerWave = 8, kSpanMin = 64, kSpanMax = 1024;
-inline int32_t chunk_span(int64_t n_edges)
+constexpr int kEdgeWaves = 2048, kItemsPerWave = 8, kSpanMin = 64, kSpanMax = 1024, kSpanTable = 256;
+inline int32_t chunk_span(int64_t n_edges, int32_t most = kSpanMax)
 {
     const int64_t even = n_edges / (kEdgeWaves * kItemsPerWave), least = n_edges < 1024 * kSpanMin ? kSpanMin / 2 : kSpanMin;
-    return (int32_t)(even < least ? least : even > kSpanMax ? kSpanMax : even);
+    return (int32_t)(even < least ? least : even > most ? most : even);
 }
 inline int64_t chunks_of(int64_t n_edges, int32_t span) { return n_edges > 0 ? (n_edges + span - 1) / span : 1; }
 
@@ -187,7 +188,7 @@ struct PartStore {
     DevBuf gbase, ghost_local;                            // i32 [N + 1] scan of popcount(needed_by); i32 [sum n_ghost]
 };
 
-enum { kMaxSlabs = 64, kMaxEvents = 4096, kPinnedBytes = 65536 };
+enum { kMaxSlabs = 64, kMaxEvents = 4096, kPinnedBytes = 65536, kPinnedTableWord = kPinnedBytes / 8 - 1 };
 
 struct Profiler {
     bool on = false;
@@ -244,6 +245,11 @@ struct mlip_graph {
     int32_t *work_ptr = nullptr;
     int work_next = 0;        // launches that have taken their counters in the current call
     mlip::Profiler prof;
+    // filter tables of the edge kernels, made with the packed weights; the device leaves word in the pinned area whether they represent the filters
+    mlip::DevBuf tables;
+    int64_t table_generation = 0, kept_generation = 0;   // of the tables made last (the static variant's among them), of those in the handle
+    double table_rcut = 0.0;  // the cutoff they were made for
+    bool table_good = false, table_failed = false;   // whether a model's tables have represented its filters / ever did not, as far as the host has heard
     mlip::DevBuf bond_wpack;  // packed weights of the three-body variant's bond part
     mutable bool tail = false;   // the last build's final kernels (edge arrays, reverse edges) may still run
     void *pinned = nullptr;  // pinned host area in which kernels leave counts and flags for the host
@@ -257,6 +263,9 @@ void prof_end(mlip_graph *g);
 int build_graph_impl(mlip_graph *g, const double *positions, const double *cell, const int32_t *species,
                      int64_t n_atoms, double r_cut, int32_t n_slabs);
 // scratch != nullptr: every piece of workspace is carved from it (nothing is allocated, nothing cached)
+// bytes of the filter tables of an L-layer model (and of the words in front of them)
+size_t table_bytes(int F, int L);
+constexpr size_t kStaticTableBytes = (size_t)2605312;   // table_bytes(64, 8): what the static variant holds beside its workspace
 int forward_impl(mlip_graph *g, const mlip_weights_t *w, int32_t mode, double *energy, float *forces,
                  float *atom_energy, Carver *scratch);
 int unpack_shifts(const mlip_graph *g, int32_t *out);
@@ -264,7 +273,8 @@ int unpack_shifts(const mlip_graph *g, int32_t *out);
 int build_bonds_impl(mlip_graph *g, SlabView &v, double r_bond, int p_envelope);
 // Upper / lower split of the views' owned-row edges (PairGraph), all views in the same launches; does nothing if all are valid.  With a block to carve from,
 // the arrays are taken from it (and the caller invalidates the structure when the block is given up).
-int build_pairs_impl(mlip_graph *g, SlabView *views, int n_views, Carver *scratch);
+// gate != nullptr: the lists are made only if *gate != 0 when the kernels run.  launch = false: only their place is taken.
+int build_pairs_impl(mlip_graph *g, SlabView *views, int n_views, Carver *scratch, const int32_t *gate = nullptr, bool launch = true);
 int forward_bonds_impl(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t *bw, int32_t mode,
                        double *energy, float *forces, float *atom_energy);
 

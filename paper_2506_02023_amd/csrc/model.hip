@@ -10,6 +10,8 @@
 // reverse pass.
 //
 // Kernel design
+//  * Every edge's filter is a function of its length: where the weights allow it (decided on the device), the layers run on tables of
+//    it (model_table.h), and what follows on pair lists, kept filter values and the edge kernels is the way without.
 //  * All dense contractions (filter MLP per edge, F x F maps per node and per bond) run on the 16-bit matrix
 //    pipeline: fp32 products as exact three-part bf16 sums with fp32 accumulation, with items (edges, nodes or
 //    bonds) as the 32 MFMA columns and features as rows.  In that orientation the accumulator layout of one
@@ -43,6 +45,7 @@ namespace {
 #include "model_edge.h"
 #include "model_node.h"
 #include "model_bond.h"
+#include "model_table.h"
 
 inline unsigned blocks_for(int64_t n, int threads) { return (unsigned)((n + threads - 1) / threads); }
 
@@ -176,7 +179,7 @@ template <int F, int PREC> int launch_edge(mlip_graph *g, EdgeBatch &b, bool bac
     }
     b.work = g->work_ptr + (size_t)g->work_next * (8 * kWorkCounterStride);
     b.chunk_start[0] = 0;
-    for (int q = 0; q < b.n; ++q) b.chunk_start[q + 1] = b.chunk_start[q] + (b.s[q].n_rows > 0 ? b.s[q].n_chunks : 0);
+    for (int q = 0; q < b.n; ++q) b.chunk_start[q + 1] = b.chunk_start[q] + (b.s[q].n_rows > 0 ? (b.s[q].n_chunks + b.c.group - 1) / b.c.group : 0);
     for (int q = b.n; q < kBatch; ++q) b.chunk_start[q + 1] = b.chunk_start[b.n];
     const int64_t items = b.chunk_start[b.n];
     if (items <= 0) return MLIP_OK;
@@ -189,7 +192,45 @@ template <int F, int PREC> int launch_edge(mlip_graph *g, EdgeBatch &b, bool bac
     else
         k_edge_fwd<F, PREC><<<blocks, threads, lds, g->stream>>>(b);
     MLIP_HIP(hipGetLastError());
-    ++g->work_next;   // only a launch that ran has used its counters
+    return MLIP_OK;
+}
+
+// Upper edges of a view: every pair of two owned-row edges has one, and an owned-row edge from a ghost sender is one, whose
+// reverse edge is in a ghost row (as build_pairs_impl counts them).
+int64_t upper_edges(const SlabView &v)
+{
+    const int64_t n_ghost_edges = v.n_edges - v.n_edges_owned;
+    return (v.n_edges_owned - n_ghost_edges) / 2 + n_ghost_edges;
+}
+
+// Edge steps on tables, one launch for up to kBatch partitions: K is the forward kernel or one of the reverse ones.
+template <int F> int launch_edge_tab(mlip_graph *g, TabBatch &b, void (*kernel)(TabBatch), int waves)
+{
+    constexpr int NH = F / 32;   // blocks of 32 features, each with a table of its own
+    constexpr size_t lds = kTabLds;
+    const void *fn = reinterpret_cast<const void *>(kernel);
+    int slot = 0;
+    MLIP_TRY(configure_kernel(g, fn, lds, &slot));
+    if (g->n_cu == 0) {
+        int dev = 0;
+        MLIP_HIP(hipGetDevice(&dev));
+        MLIP_HIP(hipDeviceGetAttribute(&g->n_cu, hipDeviceAttributeMultiprocessorCount, dev));
+    }
+    // A few rows at a time, so that the rows all workers of an XCD are at, with their neighbours, stay in its L2 (a million atoms: 1.8 GB
+    // fetched by a forward launch; 8.2 with 22 rows at a time; 3, 6 and 12 rows: 15.4, 15.4 and 15.6 ms a pass); less where
+    // there are not even eight items for every worker.
+    int64_t rows = 0;
+    for (int q = 0; q < b.n; ++q) rows += b.s[q].n_rows;
+    const int64_t workers = (int64_t)(g->n_cu / NH) * waves * 2;
+    b.rows = (int)std::min<int64_t>(kTabRows, std::max<int64_t>(1, rows / (8 * workers)));
+    b.edge_start[0] = 0;
+    for (int q = 0; q < kBatch; ++q) b.edge_start[q + 1] = b.edge_start[q] + (q < b.n ? b.s[q].n_edges : 0);
+    if (rows <= 0) return MLIP_OK;
+    // persistent grid: one block per compute unit (the table fills its LDS), fewer where there are not even kTabDeal items for each
+    const int64_t items = (rows + b.rows - 1) / b.rows;
+    const int64_t slots = std::max<int64_t>(1, std::min<int64_t>(g->n_cu / 8 / NH, (items + 8 * kTabDeal - 1) / (8 * kTabDeal)));
+    kernel<<<(unsigned)(8 * NH * slots), waves * 64, lds, g->stream>>>(b);
+    MLIP_HIP(hipGetLastError());
     return MLIP_OK;
 }
 
@@ -223,12 +264,96 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         ptr = buf.as<float>();
         return MLIP_OK;
     };
-    // Both edges of an edge / reverse-edge pair have the same length, hence bit for bit the same filter values: the
+    // ---- packed weights and filter tables: kept in the handle until a call comes with a different weight struct or cutoff; the
+    // fixed block of the static variant is shared by all handles, so there they are made on every call
+    const Packs pk = pack_layout(F, L);
+    float *wp = nullptr;
+    MLIP_TRY(place(g->wpack, pk.total * sizeof(float), wp));
+    char *tables = nullptr;
+    if (L > 0) {
+        if (!scratch) MLIP_TRY(g->tables.ensure(table_bytes(F, L)));
+        tables = static_cast<char *>(scratch ? scratch->tables : g->tables.p);
+    }
+    TabState *tab_state = reinterpret_cast<TabState *>(tables);
+    float *tab0 = reinterpret_cast<float *>(tables + kTabHeader);
+    auto layer_table = [&](int l) { return tab0 + (size_t)l * (F / 32) * kTabFloats; };
+    const float tab_inv_h = (float)(kTabUnits / g->r_cut);
+    const bool repack = scratch != nullptr || !g->packed_w_valid || std::memcmp(&g->packed_w, w, sizeof(*w)) != 0 || g->table_rcut != g->r_cut;
+    const int w2_kind = prec == kPrecBf16 ? PACK_FF_BF16 : prec == kPrecF16x3 ? PACK_FF_F16X2 : PACK_FF_BF16X3;
+    int64_t *verdict = static_cast<int64_t *>(g->pinned) + kPinnedTableWord;
+    if (repack && !(scratch && scratch->failed())) {
+        prof_begin(g, MLIP_PROF_NODE);
+        g->packed_w_valid = false;
+        PackBatch pb{};
+        pb.F = F;
+        pb.clear = L > 0 ? &tab_state->bad : nullptr;
+        const size_t ff = (size_t)F * F;   // floats of a weight matrix
+        for (int l = 0; l < L; ++l) {
+            float *base = wp + pk.per_layer * l;
+            pb.add(w->W1 + (size_t)l * 8 * F, base + pk.A1, PACK_W1, 0, 1.0f);
+            pb.add(w->W1 + (size_t)l * 8 * F, base + pk.A1s, PACK_W1, 0, kSiluScale);
+            pb.add(w->W2 + l * ff, base + pk.W2t, w2_kind, 1, kSiluScaleInv);
+            pb.add(w->W2 + l * ff, base + pk.W2n, w2_kind, 0, 1.0f);
+            pb.add(w->Wm + l * ff, base + pk.Wmt, PACK_FF_BF16X3, 1, 1.0f);
+            pb.add(w->Wm + l * ff, base + pk.Wmn, PACK_FF_BF16X3, 0, 1.0f);
+            pb.add(w->Wo + l * ff, base + pk.Wot, PACK_FF_BF16X3, 1, 1.0f);
+            pb.add(w->Wo + l * ff, base + pk.Won, PACK_FF_BF16X3, 0, 1.0f);
+        }
+        pb.add(w->Wr1, wp + pk.readout_t, PACK_FF_BF16X3_ALT, 1, 1.0f);
+        pb.add(w->Wr1, wp + pk.readout_n, PACK_FF_BF16X3, 0, 1.0f);
+        k_pack<<<dim3(blocks_for((int64_t)F * F, 256), pb.n), 256, 0, s>>>(pb);
+        if (L > 0) {
+            TabJob job{};
+            job.W1 = w->W1;
+            job.W2 = w->W2;
+            job.tab = tab0;
+            job.state = tab_state;
+            job.publish = verdict;
+            job.generation = ++g->table_generation;
+            job.inv_h = (double)tab_inv_h;
+            job.rc = g->r_cut;
+            job.p = w->p;
+            job.F = F;
+            job.bf16 = prec == kPrecBf16;
+            k_filter_table<F><<<dim3(kTabN, L), kTabNodes * 64, 0, s>>>(job);
+        }
+        MLIP_HIP(hipGetLastError());
+        if (!scratch) {
+            g->packed_w = *w;
+            g->packed_w_valid = true;
+            g->table_rcut = g->r_cut;
+            g->kept_generation = g->table_generation;
+        }
+        prof_end(g);
+    }
+    // Whether the tables represent this model's filters is decided on the device when they are made.  Until the host has seen the word, a handle
+    // on which they always did goes by them, and the launches fall back by themselves should it be different this time; any other handle
+    // launches the edge steps both ways, and those of the other way end at once.
+    enum { BY_TABLE, BY_MLP, BOTH_WAYS };
+    int by = BOTH_WAYS;
+    bool decided = false;
+    int64_t most_edges = 0;
+    for (int p = 0; p < P; ++p) most_edges = std::max(most_edges, views[p].n_edges);
+    if (L == 0 || most_edges >= (int64_t)1 << 29) {   // the steps on tables address an edge's 8 bytes of sums by 32-bit offsets
+        by = BY_MLP;
+    } else {
+        const int64_t word = __atomic_load_n(verdict, __ATOMIC_RELAXED);
+        if (word >> 1) ((word & 1) ? g->table_failed : g->table_good) = true;
+        decided = !repack && word >> 1 == g->kept_generation;
+        if (decided) by = (word & 1) ? BY_MLP : BY_TABLE;
+        else if (g->table_good && !g->table_failed) by = BY_TABLE;
+    }
+    const int32_t *verdict_dev = decided || by == BY_MLP ? nullptr : &tab_state->bad;
+    const int32_t *gate = by == BOTH_WAYS ? verdict_dev : nullptr;   // != null: the launches of both ways look at it
+
+    const int dsum_step = F == 64 && !scratch ? 2 : 1;   // on tables: the halves' sums of an edge side by side, in the fixed block one array each
+
+    // By MLP: both edges of an edge / reverse-edge pair have the same length, hence bit for bit the same filter values: the
     // forward kernel keeps those of the upper edges, the reverse kernel runs on the partitions' upper-edge graphs and a
     // row-wise kernel adds the lower edges' terms.
-    if (L > 0) {
+    if (L > 0 && (by != BY_TABLE || scratch)) {   // (the fixed block has their place in any case: its limit does not depend on the way)
         prof_begin(g, MLIP_PROF_GRAPH);
-        MLIP_TRY(build_pairs_impl(g, views, P, scratch));
+        MLIP_TRY(build_pairs_impl(g, views, P, scratch, scratch ? gate : nullptr, by != BY_TABLE));   // (kept for later calls unless they are carved)
         prof_end(g);
     }
     int64_t n_parts = 0;
@@ -245,20 +370,28 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         }
         MLIP_TRY(place(v.gbar, nl * rowb, v.ws.gbar));
         MLIP_TRY(place(v.eps, no * sizeof(float), v.ws.eps));
-        MLIP_TRY(place(v.dsum, (size_t)std::max<int64_t>(v.n_edges, 1) * sizeof(float), v.ws.dsum));
+        const size_t ne = (size_t)std::max<int64_t>(v.n_edges, 1);
+        MLIP_TRY(place(v.dsum, ne * sizeof(float) * (scratch ? 1 : F / 32), v.ws.dsum));
         MLIP_TRY(place(v.floc, nl * 3 * sizeof(float), v.ws.floc));
         MLIP_TRY(place(v.g, nl * rowb * (size_t)std::max(L, 1), v.ws.g));
         MLIP_TRY(place(v.a, no * rowb * (size_t)std::max(L, 1), v.ws.a));
         v.ws.wst = nullptr;
         if (L > 0)   // kept filter values, a slice per layer (layer 0's reverse step needs none: its slice stays empty, and
                      // the fixed block holds none for it)
-            MLIP_TRY(place(v.wst, (size_t)std::max<int64_t>(v.pairs.n_upper, 1) * rowb * (size_t)(scratch ? L - 1 : L), v.ws.wst));
+            MLIP_TRY(place(v.wst, (size_t)std::max<int64_t>(upper_edges(v), 1) * rowb * (size_t)(scratch ? L - 1 : L), v.ws.wst));
+        v.ws.dsum2 = nullptr;
+        if (F == 64 && L > 0 && by != BY_MLP) {   // on tables every block of 32 features has its own sums
+            if (!scratch) v.ws.dsum2 = v.ws.dsum + 1;
+            // in the fixed block the second ones lie where the way by MLP has its kept filter values (F per pair, at least one per
+            // edge) or, in a model of one layer, its gradients of g: its limit does not depend on the way
+            else if (L >= 2) v.ws.dsum2 = v.ws.wst;
+            else if (v.n_edges <= (int64_t)nl * F) v.ws.dsum2 = v.ws.gbar;
+            else v.ws.dsum2 = static_cast<float *>(scratch->take(ne * sizeof(float)));
+        }
         n_parts += (v.n_owned + 31) / 32;
     }
-    const Packs pk = pack_layout(F, L);
-    float *wp = nullptr, *energy_part_f = nullptr;
+    float *energy_part_f = nullptr;
     MLIP_TRY(place(g->energy_part, (size_t)std::max<int64_t>(n_parts, 1) * sizeof(double), energy_part_f));
-    MLIP_TRY(place(g->wpack, pk.total * sizeof(float), wp));
     float *work_f = nullptr;
     // one set of counters per edge-kernel launch: two per layer and batch of partitions
     const size_t work_n = (size_t)std::max(1, 2 * L * ((P + kBatch - 1) / kBatch)) * 8 * kWorkCounterStride;
@@ -270,7 +403,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
     double *energy_part = reinterpret_cast<double *>(energy_part_f);
     g->work_ptr = reinterpret_cast<int32_t *>(work_f);
     g->work_next = 0;
-    auto wslice = [&](SlabView &v, int l) { return v.ws.wst + (size_t)(scratch ? l - 1 : l) * (size_t)v.pairs.n_upper * F; };   // l >= 1
+    auto wslice = [&](SlabView &v, int l) { return v.ws.wst + (size_t)(scratch ? l - 1 : l) * (size_t)upper_edges(v) * F; };   // l >= 1
     // dE/da of a layer: one array for all layers in turn, or one per layer where the three-body variant keeps them
     auto abarslice = [&](SlabView &v, int l) { return v.ws.abar + (bw ? (size_t)l * (size_t)v.n_local * F : 0); };
 
@@ -278,6 +411,8 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
     enum { U_OWNED, U_GHOST, U_LOCAL };
     auto small_batch = [&](int p0, int unit, int layer) {
         SmallBatch sb{};
+        sb.tables = by == BY_TABLE;
+        sb.gate = gate;
         sb.n = std::min(kBatch, P - p0);
         sb.start[0] = 0;
         for (int q = 0; q < kBatch; ++q) {
@@ -297,6 +432,8 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             a.floc = v.ws.floc;
             a.eps = v.ws.eps;
             a.dsum = v.ws.dsum;
+            a.dsum2 = v.ws.dsum2;
+            a.dsum_step = dsum_step;
             a.d = v.d;
             a.wstore = layer >= 1 ? wslice(v, layer) : nullptr;
             a.uslot = v.pairs.uslot;
@@ -331,39 +468,6 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
     bp.p = w->p;
     const double pd = (double)w->p;
     bp.pc0 = (float)(pd * (pd + 1) * (pd + 2) / 2);
-
-    // ---- pack weights (kept in the handle until a call comes with a different weight struct; the fixed block of
-    // the static variant is shared by all handles, so there they are packed on every call)
-    prof_begin(g, MLIP_PROF_NODE);
-    const bool repack = scratch != nullptr || !g->packed_w_valid || std::memcmp(&g->packed_w, w, sizeof(*w)) != 0;
-    g->packed_w_valid = false;
-    const int w2_kind = prec == kPrecBf16 ? PACK_FF_BF16 : prec == kPrecF16x3 ? PACK_FF_F16X2 : PACK_FF_BF16X3;
-    if (repack) {
-        PackBatch pb{};
-        pb.F = F;
-        const size_t ff = (size_t)F * F;   // floats of a weight matrix
-        for (int l = 0; l < L; ++l) {
-            float *base = wp + pk.per_layer * l;
-            pb.add(w->W1 + (size_t)l * 8 * F, base + pk.A1, PACK_W1, 0, 1.0f);
-            pb.add(w->W1 + (size_t)l * 8 * F, base + pk.A1s, PACK_W1, 0, kSiluScale);
-            pb.add(w->W2 + l * ff, base + pk.W2t, w2_kind, 1, kSiluScaleInv);
-            pb.add(w->W2 + l * ff, base + pk.W2n, w2_kind, 0, 1.0f);
-            pb.add(w->Wm + l * ff, base + pk.Wmt, PACK_FF_BF16X3, 1, 1.0f);
-            pb.add(w->Wm + l * ff, base + pk.Wmn, PACK_FF_BF16X3, 0, 1.0f);
-            pb.add(w->Wo + l * ff, base + pk.Wot, PACK_FF_BF16X3, 1, 1.0f);
-            pb.add(w->Wo + l * ff, base + pk.Won, PACK_FF_BF16X3, 0, 1.0f);
-        }
-        pb.add(w->Wr1, wp + pk.readout_t, PACK_FF_BF16X3_ALT, 1, 1.0f);
-        pb.add(w->Wr1, wp + pk.readout_n, PACK_FF_BF16X3, 0, 1.0f);
-        k_pack<<<dim3(blocks_for((int64_t)F * F, 256), pb.n), 256, 0, s>>>(pb);
-    }
-    MLIP_HIP(hipGetLastError());
-    if (!scratch) {
-        g->packed_w = *w;
-        g->packed_w_valid = true;
-    }
-
-    prof_end(g);
 
     // ---- three-body variant: bond lists, bond embedding, triplet update, bond terms of the layers' filters.
     // All bonds and triplets of an owned centre are local to its partition, so this part needs no transfer.
@@ -510,6 +614,39 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             for (int q = 0; q < P; ++q) common.tab.p[q] = array_of(views[q]);
     };
     auto layer_pack = [&](int l) { return wp + pk.per_layer * l; };
+    auto tab_batch = [&](int p0, int l, bool backward) {   // the edge steps on tables: forward over the owned rows, reverse over the ghost rows
+        TabBatch b{};                                      // too, as what they get goes back to their owners
+        b.n = std::min(kBatch, P - p0);
+        b.tab = layer_table(l);
+        b.gate = verdict_dev;
+        b.exact = by == BY_TABLE;
+        b.W1 = w->W1 + (size_t)l * 8 * F;
+        b.W2 = w->W2 + (size_t)l * F * F;
+        b.bp = bp;
+        b.bf16 = prec == kPrecBf16;
+        b.inv_h = tab_inv_h;
+        b.first = l == L - 1;
+        for (int q = 0; q < b.n; ++q) {
+            SlabView &v = views[p0 + q];
+            TabArgs &a = b.s[q];
+            a.n_rows = (int32_t)(backward ? v.n_local : v.n_owned);
+            a.n_edges = (int32_t)(backward ? v.n_edges : v.n_edges_owned);
+            a.n_nodes = (int32_t)v.n_local;
+            a.row_ptr = v.row_ptr;
+            a.chunk_row = v.chunk_row;
+            a.span = v.span;
+            a.senders = v.senders;
+            a.recv = v.recv;
+            a.d = v.d;
+            a.g = gslice(v, l);
+            a.abar = backward ? abarslice(v, l) : nullptr;
+            a.out = backward ? v.ws.gbar : aslice(v, l);
+            a.dsum[0] = v.ws.dsum;
+            a.dsum[1] = v.ws.dsum2;
+            a.dsum_step = dsum_step;
+        }
+        return b;
+    };
     int64_t tiles_before = 0;
     auto tile_sums = [&](SlabView &v) {
         double *at = energy_part + tiles_before;
@@ -542,31 +679,42 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         }
         prof_end(g);
         for (int p0 = 0; p0 < P; p0 += kBatch) {   // the partitions in order, up to kBatch per launch
-            EdgeBatch eb{};
-            eb.n = std::min(kBatch, P - p0);
-            eb.c.A1 = base + pk.A1;
-            eb.c.A1s = base + pk.A1s;
-            eb.c.A2t = base + pk.W2t;
-            eb.c.bp = bp;
-            for (int q = 0; q < eb.n; ++q) {
-                SlabView &v = views[p0 + q];
-                EdgeArgs &ea = eb.s[q];
-                ea.n_rows = v.n_owned;
-                ea.n_chunks = chunks_of(v.n_edges_owned, v.span);
-                ea.chunk_row = v.chunk_row;
-                ea.n_nodes = v.n_local;
-                ea.row_ptr = v.row_ptr;
-                ea.senders = v.senders;
-                ea.recv = v.recv;
-                ea.d = v.d;
-                ea.g = gslice(v, l);
-                ea.out = aslice(v, l);
-                ea.uslot = v.pairs.uslot;
-                ea.wstore = l >= 1 ? wslice(v, l) : nullptr;
-            }
             prof_begin(g, MLIP_PROF_EDGE_FWD);
-            MLIP_TRY(prec == kPrecBf16 ? (launch_edge<F, kPrecBf16>(g, eb, false))
-                     : prec == kPrecF16x3 ? (launch_edge<F, kPrecF16x3>(g, eb, false)) : (launch_edge<F, kPrecF32>(g, eb, false)));
+            if (by != BY_MLP) {
+                TabBatch tb = tab_batch(p0, l, false);
+                MLIP_TRY(launch_edge_tab<F>(g, tb, &k_edge_fwd_tab<F>, kTabFwdWaves));
+            }
+            if (by != BY_TABLE) {
+                EdgeBatch eb{};
+                eb.n = std::min(kBatch, P - p0);
+                eb.c.A1 = base + pk.A1;
+                eb.c.A1s = base + pk.A1s;
+                eb.c.A2t = base + pk.W2t;
+                eb.c.bp = bp;
+                eb.c.gate = gate;
+                int64_t n_edges = 0;
+                for (int q = 0; q < eb.n; ++q) n_edges += views[p0 + q].n_edges_owned;
+                eb.c.group = std::max(1, chunk_span(n_edges) / std::max(1, views[p0].span));   // longer items pay for their pipeline fill
+                for (int q = 0; q < eb.n; ++q) {
+                    SlabView &v = views[p0 + q];
+                    EdgeArgs &ea = eb.s[q];
+                    ea.n_rows = v.n_owned;
+                    ea.n_chunks = chunks_of(v.n_edges_owned, v.span);
+                    ea.chunk_row = v.chunk_row;
+                    ea.n_nodes = v.n_local;
+                    ea.row_ptr = v.row_ptr;
+                    ea.senders = v.senders;
+                    ea.recv = v.recv;
+                    ea.d = v.d;
+                    ea.g = gslice(v, l);
+                    ea.out = aslice(v, l);
+                    ea.uslot = v.pairs.uslot;
+                    ea.wstore = l >= 1 ? wslice(v, l) : nullptr;
+                }
+                MLIP_TRY(prec == kPrecBf16 ? (launch_edge<F, kPrecBf16>(g, eb, false))
+                         : prec == kPrecF16x3 ? (launch_edge<F, kPrecF16x3>(g, eb, false)) : (launch_edge<F, kPrecF32>(g, eb, false)));
+            }
+            ++g->work_next;
             prof_end(g);
         }
         if (any_bonds) {   // bond term of the filters: a_i += sum_b wb_b * g_send(b)
@@ -623,40 +771,49 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         const float *base = wp + pk.per_layer * l;
         const bool need_gbar = l > 0;  // dE/dh0 is never used: the embedding does not depend on positions
         for (int p0 = 0; p0 < P; p0 += kBatch) {
-            EdgeBatch eb{};
-            eb.n = std::min(kBatch, P - p0);
-            eb.c.A1 = base + pk.A1;
-            eb.c.A1s = base + pk.A1s;
-            eb.c.A2t = base + pk.W2t;
-            eb.c.A2n = base + pk.W2n;
-            eb.c.bp = bp;
-            eb.c.need_gbar = need_gbar ? 1 : 0;
-            eb.c.first = (l == L - 1) ? 1 : 0;
-            for (int q = 0; q < eb.n; ++q) {
-                SlabView &v = views[p0 + q];
-                EdgeArgs &ea = eb.s[q];
-                const PairGraph &Q = v.pairs;
-                ea.n_rows = v.n_owned;
-                ea.n_chunks = chunks_of(Q.n_upper, Q.span);
-                ea.chunk_row = Q.u_chunk_row;
-                ea.n_nodes = v.n_local;
-                ea.row_ptr = Q.u_row_ptr;
-                ea.senders = Q.u_senders;
-                ea.recv = Q.u_recv;
-                ea.d = Q.u_d;
-                ea.mirror = Q.u_mirror;
-                ea.eid = Q.u_eid;
-                ea.g = gslice(v, l);
-                ea.abar = abarslice(v, l);
-                ea.out = v.ws.gbar;
-                ea.dsum = v.ws.dsum;
-                ea.wstore = need_gbar ? wslice(v, l) : nullptr;
-            }
             prof_begin(g, MLIP_PROF_EDGE_BWD);
-            MLIP_TRY(prec == kPrecBf16 ? (launch_edge<F, kPrecBf16>(g, eb, true))
-                     : prec == kPrecF16x3 ? (launch_edge<F, kPrecF16x3>(g, eb, true)) : (launch_edge<F, kPrecF32>(g, eb, true)));
+            if (by != BY_MLP) {
+                TabBatch tb = tab_batch(p0, l, true);
+                MLIP_TRY(launch_edge_tab<F>(g, tb, need_gbar ? &k_edge_bwd_tab<F, true> : &k_edge_bwd_tab<F, false>, kTabBwdWaves));
+            }
+            if (by != BY_TABLE) {
+                EdgeBatch eb{};
+                eb.n = std::min(kBatch, P - p0);
+                eb.c.A1 = base + pk.A1;
+                eb.c.A1s = base + pk.A1s;
+                eb.c.A2t = base + pk.W2t;
+                eb.c.A2n = base + pk.W2n;
+                eb.c.bp = bp;
+                eb.c.need_gbar = need_gbar ? 1 : 0;
+                eb.c.first = (l == L - 1) ? 1 : 0;
+                eb.c.gate = gate;
+                eb.c.group = 1;
+                for (int q = 0; q < eb.n; ++q) {
+                    SlabView &v = views[p0 + q];
+                    EdgeArgs &ea = eb.s[q];
+                    const PairGraph &Q = v.pairs;
+                    ea.n_rows = v.n_owned;
+                    ea.n_chunks = chunks_of(Q.n_upper, Q.span);
+                    ea.chunk_row = Q.u_chunk_row;
+                    ea.n_nodes = v.n_local;
+                    ea.row_ptr = Q.u_row_ptr;
+                    ea.senders = Q.u_senders;
+                    ea.recv = Q.u_recv;
+                    ea.d = Q.u_d;
+                    ea.mirror = Q.u_mirror;
+                    ea.eid = Q.u_eid;
+                    ea.g = gslice(v, l);
+                    ea.abar = abarslice(v, l);
+                    ea.out = v.ws.gbar;
+                    ea.dsum = v.ws.dsum;
+                    ea.wstore = need_gbar ? wslice(v, l) : nullptr;
+                }
+                MLIP_TRY(prec == kPrecBf16 ? (launch_edge<F, kPrecBf16>(g, eb, true))
+                         : prec == kPrecF16x3 ? (launch_edge<F, kPrecF16x3>(g, eb, true)) : (launch_edge<F, kPrecF32>(g, eb, true)));
+            }
+            ++g->work_next;
             prof_end(g);
-            if (need_gbar) {   // second pass: the lower edges' terms of the rows' sums
+            if (need_gbar && (by != BY_TABLE || any_bonds)) {   // second pass: the lower edges' terms of the rows' sums, and the bonds'
                 prof_begin(g, MLIP_PROF_EDGE_BWD_LOWER);
                 const SmallBatch sb = small_batch(p0, U_OWNED, l);
                 if (sb.start[sb.n] > 0)
@@ -666,7 +823,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             }
         }
         if (need_gbar) {
-            if (slabs) {
+            if (slabs && (by != BY_TABLE || any_bonds)) {
                 prof_begin(g, MLIP_PROF_GHOST);
                 for (int p0 = 0; p0 < P; p0 += kBatch) {   // the ghost rows' gradients; the owners collect them below
                     const SmallBatch sb = small_batch(p0, U_GHOST, l);
@@ -776,6 +933,8 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
 }
 
 }  // namespace
+
+size_t table_bytes(int F, int L) { return kTabHeader + (size_t)L * (F / 32) * kTabFloats * sizeof(float); }
 
 int forward_impl(mlip_graph *g, const mlip_weights_t *w, int32_t mode, double *energy, float *forces, float *atom_energy,
                  Carver *scratch)

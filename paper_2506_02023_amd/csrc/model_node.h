@@ -256,6 +256,8 @@ struct SmallArgs {   // one partition
     const int64_t *l_row_ptr;      // the owned rows' lower edges: CSR, sender row, where the pair's filter values are kept
     const int32_t *l_senders, *l_slot;
     const float *dsum, *wstore, *d;
+    const float *dsum2;            // on tables: null or the second half of the features' share, and the elements between two edges' sums
+    int dsum_step;
     const int32_t *bond_of_edge;   // three-body variant (or nullptr): bond of an edge, bonds per owned row, sender, reverse bond
     const int64_t *b_ptr;
     const int32_t *b_sender, *b_mirror;
@@ -265,6 +267,9 @@ struct SmallArgs {   // one partition
 
 struct SmallBatch {
     int n;
+    int tables;            // whether the edge steps run on tables; if not, the filter values are kept, edge by edge
+    const int32_t *gate;   // != null: not known when this is launched, *gate == 0 says that they did
+    __device__ bool on_tables() const { return gate ? *gate == 0 : tables != 0; }
     int64_t start[kBatch + 1];
     SmallArgs s[kBatch];
 };
@@ -299,9 +304,11 @@ __global__ void __launch_bounds__(256) k_edge_lower(SmallBatch B)
     const SmallArgs &A = B.s[part];
     const int64_t r = gk - B.start[part];
     const unsigned f = lane & (F - 1);
+    const bool kept = !B.on_tables();   // on tables the reverse step has the lower edges already
+    if (!kept && !A.b_ptr) return;
     // the row's lower edges (wave-uniform, kept scalar; edge indices fit 32 bits)
-    const int64_t e0 = __builtin_amdgcn_readfirstlane((int32_t)A.l_row_ptr[r]);
-    const int64_t e1 = __builtin_amdgcn_readfirstlane((int32_t)A.l_row_ptr[r + 1]);
+    const int64_t e0 = kept ? __builtin_amdgcn_readfirstlane((int32_t)A.l_row_ptr[r]) : 0;
+    const int64_t e1 = kept ? __builtin_amdgcn_readfirstlane((int32_t)A.l_row_ptr[r + 1]) : 0;
     const float before = A.gbar[r * F + f];   // (requested with the indices)
     float acc = 0.f;
     for (int64_t eb = e0; eb < e1; eb += 64) {
@@ -362,20 +369,22 @@ __global__ void __launch_bounds__(256) k_ghost_gbar(SmallBatch B)
     const SmallArgs &A = B.s[part];
     const int64_t r = A.n_owned + (gk - B.start[part]);
     const unsigned f = lane & (F - 1);
+    const bool kept = !B.on_tables();
+    if (!kept && !A.bond_of_edge) return;
     const int64_t e0 = A.row_ptr[r], e1 = A.row_ptr[r + 1];
-    float acc = 0.f;
+    float acc = kept ? 0.f : A.gbar[r * F + f];   // on tables the reverse step has summed the edges' terms: the bonds' are added
     for (int64_t eb = e0; eb < e1; eb += 16) {   // 16 edges at a time: ids by lane, then all rows in flight together
         const int n = (int)min((int64_t)16, e1 - eb);
         const int64_t el = min(eb + (lane & 15), e1 - 1);
         const int32_t jl = A.senders[el], ml = A.mirror[el];
         const int32_t bl = A.bond_of_edge ? A.bond_of_edge[ml] : -1;   // three-body variant: the reverse edge's bond
-        const int32_t sl = A.uslot[ml];   // where the reverse edge (an upper one: its sender is a ghost) keeps its filter values
+        const int32_t sl = kept ? A.uslot[ml] : 0;   // where the reverse edge (an upper one: its sender is a ghost) keeps its filter values
         float wv[16], av[16];
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
             const int64_t j = __builtin_amdgcn_readlane(jl, k), m = __builtin_amdgcn_readlane(sl, k);
             const int64_t b = __builtin_amdgcn_readlane(bl, k);
-            wv[k] = A.wstore[m * F + f];
+            wv[k] = kept ? A.wstore[m * F + f] : 0.f;
             if (b >= 0)
                 wv[k] += A.wb_bf16 ? Elem<__bf16>::load(static_cast<const __bf16 *>(A.wb) + b * F + f)
                                    : static_cast<const float *>(A.wb)[b * F + f];
@@ -431,6 +440,7 @@ k_force_rows(SmallBatch B, const double *__restrict__ pos, CellParams cp, float 
     const double xi = pos[3 * ig], yi = pos[3 * ig + 1], zi = pos[3 * ig + 2];
     double fx = 0, fy = 0, fz = 0;
     const int64_t e1 = A.row_ptr[r + 1];
+    const bool tables = B.on_tables();
     for (int64_t e = A.row_ptr[r] + (threadIdx.x & 15); e < e1; e += 16) {
         const int64_t jl = A.senders[e];
         const int64_t jg = nodes ? nodes[jl] : jl;
@@ -441,7 +451,19 @@ k_force_rows(SmallBatch B, const double *__restrict__ pos, CellParams cp, float 
         const double t2 = (pos[3 * jg + 2] - zi) + (((double)S0 * cp.C[2] + (double)S1 * cp.C[5]) + (double)S2 * cp.C[8]);
         // dE/dd times the unit vector: the edge's stored length (the fp64 length rounded once to fp32) is accurate
         // to 6e-8, far inside the force bound, and spares an fp64 square root and division per edge
-        const double s = (double)(A.dsum[e] * __builtin_amdgcn_rcpf(A.d[e]));
+        float dd = A.dsum[e];
+        if (tables) {   // an edge holds the share in which its receiver's row of g took part: the reverse edge has the other one
+            const int64_t m = A.mirror[e];
+            if (!A.dsum2) {
+                dd += A.dsum[m];
+            } else if (A.dsum_step == 2) {
+                const f32x2 own = reinterpret_cast<const f32x2 *>(A.dsum)[e], other = reinterpret_cast<const f32x2 *>(A.dsum)[m];
+                dd = (own[0] + own[1]) + (other[0] + other[1]);
+            } else {
+                dd = (dd + A.dsum2[e]) + (A.dsum[m] + A.dsum2[m]);
+            }
+        }
+        const double s = (double)(dd * __builtin_amdgcn_rcpf(A.d[e]));
         fx += s * t0;
         fy += s * t1;
         fz += s * t2;

@@ -1,0 +1,660 @@
+// Edge kernels on tabulated filters.  The filter w(d) = SiLU(b(d) W1) W2 of a layer is a function of the edge length alone, smooth
+// on [0, rc], so its F values are kept as piecewise polynomials in LDS and an edge costs a look-up instead of a filter MLP:
+// the forward and the reverse step walk the full edge lists once per layer, nothing is kept between them and no pair lists are needed.
+// Part of model.hip (one translation unit): included inside namespace mlip, anonymous namespace.
+#ifndef MLIP_MODEL_TABLE_H
+#define MLIP_MODEL_TABLE_H
+
+#include <utility>
+
+// ---------------------------------------------------------------- the table
+//
+// kTabN intervals over [0, rc], degree 5 in the local coordinate s in [-1, 1], fp32 coefficients computed in fp64.  In units of rc / kTabUnits the intervals have
+// the length 1/2 below kTabSmall (at short distances the basis functions are large and SiLU bends most), 1/4 from kTabEnd on (at
+// the cutoff the filter vanishes with its first three derivatives, so its error has to vanish too) and 1 between.
+// What is cut off is below what the rounding of the length to fp32 makes (checked when the table is made, see k_filter_table); coefficients
+// and evaluation round to 4e-8 (values) and 5e-8 (slopes) of the filter, the fp32 evaluation of the MLP to 1.7e-7 of both.
+// One block of 32 features is 768 bytes per interval, [3][32][2] coefficients 2 q, 2 q + 1: 162,816 bytes of the
+// compute unit's 160 KB.  With F = 64 every block of the grid holds the table of one half of the features.
+constexpr int kTabUnits = 179, kTabSmall = 27, kTabEnd = kTabUnits - 2;
+constexpr int kTabM0 = 2 * kTabSmall, kTabE0 = kTabM0 + kTabEnd - kTabSmall, kTabN = kTabE0 + 4 * (kTabUnits - kTabEnd);
+constexpr int kTabStride = 32 * 6 * 4;                   // bytes of an interval
+constexpr int kTabFloats = kTabN * kTabStride / 4;       // floats of one block of 32 features
+constexpr int kTabLds = kTabFloats * 4 + 32;             // the table and a work counter per partition of the launch
+constexpr int kTabHeader = 256;                          // bytes in front of the first table: TabState
+constexpr int kTabNodes = 8;                             // Chebyshev nodes of an interval: coefficients 0..7, 6 and 7 measure what is cut off
+static_assert(kTabLds <= 160 * 1024, "the table has to fit a compute unit's LDS");
+
+// Whether the tables of a model represent its filters, and the handshake that tells the host.
+struct TabState {
+    int32_t bad;       // an interval of some layer is not represented: the edge steps may not use the tables
+    int32_t done;      // blocks of k_filter_table that are through, plus kTabBad for every one that found its interval bad
+};
+
+constexpr int32_t kTabBad = 1 << 16;
+
+struct TabJob {
+    const float *W1, *W2;   // [L][8][F], [L][F][F]
+    float *tab;             // [L][F / 32][kTabFloats]
+    TabState *state;
+    int64_t *publish;       // pinned host word: generation * 2 + bad, written when the last block is through
+    int64_t generation;
+    double inv_h;           // kTabUnits / rc, rounded to fp32 as the edge kernels use it
+    double rc;
+    int p, F;
+    int bf16;   // the mode with bf16 products: W2 rounded to bf16 as the forward MLP has it, scaled (the activations need no rounding here)
+};
+
+// cos(m pi / 16)
+__constant__ const double kCosTab[32] = {
+    1.0, 0.98078528040323044913, 0.92387953251128675613, 0.83146961230254523708, 0.70710678118654752440, 0.55557023301960222474,
+    0.38268343236508977173, 0.19509032201612826785, 0.0, -0.19509032201612826785, -0.38268343236508977173, -0.55557023301960222474,
+    -0.70710678118654752440, -0.83146961230254523708, -0.92387953251128675613, -0.98078528040323044913, -1.0, -0.98078528040323044913,
+    -0.92387953251128675613, -0.83146961230254523708, -0.70710678118654752440, -0.55557023301960222474, -0.38268343236508977173,
+    -0.19509032201612826785, 0.0, 0.19509032201612826785, 0.38268343236508977173, 0.55557023301960222474, 0.70710678118654752440,
+    0.83146961230254523708, 0.92387953251128675613, 0.98078528040323044913};
+
+// One block per interval and layer, one wavefront per Chebyshev node, lane = feature; everything in fp64.  Bound by the latency
+// of one chain of loads, an exponential and 64 multiply-adds; W2 is requested before the chain.
+template <int F>
+__global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
+{
+    __shared__ double sv[kTabNodes][64], wv[kTabNodes][64];
+    __shared__ float W2[F * F];
+    const int iv = blockIdx.x, layer = blockIdx.y;
+    const int node = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, f = lane & (F - 1);
+    const double lo = iv < kTabM0 ? 0.5 * iv : iv < kTabE0 ? kTabSmall + (iv - kTabM0) : kTabEnd + 0.25 * (iv - kTabE0);
+    const double wd = iv < kTabM0 ? 0.5 : iv < kTabE0 ? 1.0 : 0.25;
+    float w1[8];
+#pragma unroll
+    for (int n = 0; n < 8; ++n) w1[n] = J.W1[((size_t)layer * 8 + n) * F + f];
+    float w2[F * F / (kTabNodes * 64)];   // this thread's part on its way to LDS (the caller's array: no alignment assumed)
+#pragma unroll
+    for (int i = 0; i < F * F / (kTabNodes * 64); ++i) w2[i] = J.W2[(size_t)layer * F * F + i * kTabNodes * 64 + threadIdx.x];
+    {   // t_k = sum_n b_n(d) W1[n][k], s_k = SiLU(t_k)
+        const double d = (lo + wd * (0.5 + 0.5 * kCosTab[2 * node + 1])) / J.inv_h;
+        const double x = fmin(d / J.rc, 1.0), y = 1.0 - x;
+        double q = 0.5 * J.p * (J.p + 1);
+        for (int k = J.p - 2; k >= 0; --k) q = q * x + 0.5 * (k + 1) * (k + 2);
+        const double u = y * y * y * q / d;   // the envelope in its factored form, over d
+        // sin((n + 1) pi x) by angle addition from the nearer end, where it is small
+        const double near = x < 0.5 ? x : y, s1 = sinpi(near), c1 = x < 0.5 ? cospi(near) : -cospi(near);
+        double sn = s1, cn = c1, t = 0;
+#pragma unroll
+        for (int n = 0; n < 8; ++n) {
+            t += sn * u * (double)w1[n];
+            const double nx = sn * c1 + cn * s1;
+            cn = cn * c1 - sn * s1;
+            sn = nx;
+        }
+        sv[node][lane] = t / (1.0 + exp(-t));
+    }
+#pragma unroll
+    for (int i = 0; i < F * F / (kTabNodes * 64); ++i) W2[i * kTabNodes * 64 + threadIdx.x] = w2[i];
+    __syncthreads();
+    {   // w_f = sum_k s_k W2[k][f]
+        double w = 0;
+#pragma unroll 16
+        for (int k = 0; k < F; ++k) {
+            const float v = W2[k * F + f];
+            w = fma(sv[node][k], J.bf16 ? (double)(float)(__bf16)(v * kSiluScaleInv) / kSiluScaleInv : (double)v, w);
+        }
+        wv[node][lane] = w;
+    }
+    __syncthreads();
+    double a = 0;   // Chebyshev coefficient `node` of this lane's feature
+#pragma unroll
+    for (int j = 0; j < kTabNodes; ++j) a += wv[j][lane] * kCosTab[node * (2 * j + 1) % 32];
+    a *= node == 0 ? 1.0 / kTabNodes : 2.0 / kTabNodes;
+    __syncthreads();
+    sv[node][lane] = a;
+    __syncthreads();
+    if (node != 0) return;
+    const double a0 = sv[0][lane], a1 = sv[1][lane], a2 = sv[2][lane], a3 = sv[3][lane], a4 = sv[4][lane], a5 = sv[5][lane],
+                 a6 = fabs(sv[6][lane]), a7 = fabs(sv[7][lane]);
+    const double c[6] = {a0 - a2 + a4, a1 - 3 * a3 + 5 * a5, 2 * a2 - 8 * a4, 4 * a3 - 20 * a5, 8 * a4, 16 * a5};
+    if (lane < F) {
+        float *at = J.tab + ((size_t)layer * (F / 32) + (lane >> 5)) * kTabFloats + (size_t)iv * (kTabStride / 4);
+        const int l = lane & 31;
+        for (int k = 0; k < 6; ++k) at[64 * (k / 2) + 2 * l + k % 2] = (float)c[k];
+    }
+    // What is cut off, as root mean squares over the interval and the features: a6 T6 + a7 T7 of the values, 8 a6 + 10 a7 of the slopes
+    // (rms of T6' and T7').  Allowed is 1e-7 of the value or slope itself and what half an ulp of the length, rounded to fp32,
+    // changes on average: 2^-26 of the length times the next derivative.
+    double ew = a6 + a7, ed = 8 * a6 + 10 * a7, sw = 0, sd = 0;
+    const double dl = 0x1p-26 * 2 * (lo + 0.5 * wd) / wd;   // the length's rounding in units of s
+    for (int i = -1; i <= 1; ++i) {
+        const double s = 0.8 * i;
+        const double w0 = c[0] + s * (c[1] + s * (c[2] + s * (c[3] + s * (c[4] + s * c[5]))));
+        const double w1 = c[1] + s * (2 * c[2] + s * (3 * c[3] + s * (4 * c[4] + s * 5 * c[5])));
+        const double w2 = 2 * c[2] + s * (6 * c[3] + s * (12 * c[4] + s * 20 * c[5]));
+        sw += (1e-14 * w0 * w0 + dl * dl * w1 * w1) / 3;
+        sd += (1e-14 * w1 * w1 + dl * dl * w2 * w2) / 3;
+    }
+    ew *= ew;
+    ed *= ed;
+    for (int off = 32; off > 0; off >>= 1) {
+        ew += __shfl_xor(ew, off, 64);
+        ed += __shfl_xor(ed, off, 64);
+        sw += __shfl_xor(sw, off, 64);
+        sd += __shfl_xor(sd, off, 64);
+    }
+    if (lane == 0) {
+        const bool bad = !(ew <= sw && ed <= sd);   // (not a number: not represented)
+        if (bad) J.state->bad = 1;
+        // one word counts the blocks and the bad ones among them, so that the last one needs no fence to know
+        const int32_t now = 1 + (bad ? kTabBad : 0) +
+                            __hip_atomic_fetch_add(&J.state->done, 1 + (bad ? kTabBad : 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (now % kTabBad == (int32_t)(gridDim.x * gridDim.y))
+            __hip_atomic_store(J.publish, J.generation * 2 + (now >= kTabBad ? 1 : 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
+// ---------------------------------------------------------------- edge steps
+//
+// A wavefront is two workers of 32 lanes, lane = feature of the block's half.  A worker walks work items, each a few consecutive rows, in steps
+// of 16 edges; items follow one another without a break in the pipeline (records two steps ahead, gathered rows one), and
+// each worker has its own.  Lane l of a row of 16 lanes holds the record of edge l mod 16 of its worker's step, so that a DPP row
+// broadcast hands a record to the 32 lanes as part of the instruction that uses it, or for one instruction more.
+//
+// Measured at a million atoms in 8 slabs (F = 64, 45.8 M edges), per launch: forward 3.13 -> 1.27 ms, reverse 2.87 and 1.22 for the second
+// pass over the lower edges -> 2.00 ms.  Both are bound by the vector unit (forward 13.5 instructions for an edge and 32 features, 9 of them the
+// look-up and the row sum; reverse 25, of which 15) at 1.9 GHz; LDS is busy for 75 % and 53 % of the time.
+
+struct TabArgs {               // one partition
+    int32_t n_rows, n_edges;   // receiver rows processed and their edges (below 2^29: 32-bit byte offsets of 8-byte sums)
+    int32_t n_nodes;           // rows of g / abar
+    int32_t dsum_step;         // floats from an edge's sum to the next one's
+    const int64_t *row_ptr;
+    const int32_t *chunk_row;  // the graph's work-item table: first row whose first edge lies at or after c * span
+    int32_t span;
+    const int32_t *senders, *recv;
+    const float *d, *g, *abar;
+    float *out;                // forward: a [n_rows][F]; reverse: gbar [n_rows][F]
+    float *dsum[2];            // reverse: per edge its share of dE/dd, summed over the layers, of each block of 32 features
+};
+struct TabBatch {
+    const float *tab;      // the layer's table
+    const int32_t *gate;   // != null: the tables may be used only if *gate == 0;
+    int exact;             // if not, the launch takes the filters from the MLP, slowly (1), or leaves the work to another one (0)
+    const float *W1, *W2;  // the layer's, for that
+    BasisParams bp;
+    int bf16;
+    float inv_h;
+    int rows;              // rows of a work item
+    int first;             // reverse: dsum is written, not added to
+    int n;
+    int64_t edge_start[kBatch + 1];
+    TabArgs s[kBatch];
+};
+#ifndef MLIP_TAB_FWD_WAVES
+#define MLIP_TAB_FWD_WAVES 16
+#endif
+#ifndef MLIP_TAB_BWD_WAVES
+#define MLIP_TAB_BWD_WAVES 16
+#endif
+#ifndef MLIP_TAB_GROUP
+#define MLIP_TAB_GROUP 8
+#endif
+#ifndef MLIP_TAB_ROWS
+#define MLIP_TAB_ROWS 6
+#endif
+constexpr int kTabRows = MLIP_TAB_ROWS;     // most rows of a work item
+constexpr int kTabGroup = MLIP_TAB_GROUP;   // edges whose values are computed together
+constexpr int kTabFwdWaves = MLIP_TAB_FWD_WAVES, kTabBwdWaves = MLIP_TAB_BWD_WAVES;
+
+template <int K> __device__ inline int row_bcast(int v) { return __builtin_amdgcn_mov_dpp(v, 0x150 + K, 0xf, 0xf, true); }
+template <int K> __device__ inline float row_bcast(float v)
+{
+    return __builtin_bit_cast(float, row_bcast<K>(__builtin_bit_cast(int, v)));
+}
+__device__ inline void pin(float &v) { asm volatile("" : "+v"(v)); }   // v is computed by here, not where it is used
+template <class Fn, int... K> __device__ __forceinline__ void unrolled(std::integer_sequence<int, K...>, Fn fn)
+{
+    (fn(std::integral_constant<int, K>{}), ...);
+}
+
+struct TabRec {      // as loaded
+    int32_t sj, rk;
+    float d, before; // before: reverse, the sum of the later layers at edge tb + k_out
+};
+struct TabStep {     // one step of a worker
+    int32_t tb, last;   // first edge, the item's last edge
+    int32_t r1;         // the row after the item's
+    int32_t r0;         // the item's first row if this is its first step, or 2^31 - 1
+};
+struct TabEdge {     // what the 32 lanes of the worker need of an edge
+    int32_t goff;    // byte offset of the sender's row; past the end of the array for an edge past the item's last: its row reads 0
+    int32_t loff;    // byte offset of the interval in the table
+    float s, slope;  // place in the interval, ds / dd
+    int32_t rk, raw; // receiver; r1 for an edge past the end / the clamped record's
+};
+__device__ inline TabEdge tab_edge(const TabRec &R, const TabStep &S, float inv_h, int l16, int row_bytes)
+{
+    TabEdge E;
+    const float v = R.d * inv_h;
+    const bool small = v < (float)kTabSmall, end = v >= (float)kTabEnd, valid = S.tb + l16 <= S.last;
+    const float sc = small ? 2.f : end ? 4.f : 1.f;
+    const float b = small ? 0.f : end ? (float)(kTabE0 - 4 * kTabEnd) : (float)(kTabM0 - kTabSmall);
+    const int iv = min((int)fmaf(v, sc, b), kTabN - 1);
+    E.slope = (2.f * inv_h) * sc;
+    E.s = fmaf(R.d, E.slope, fmaf(2.f, b - (float)iv, -1.f));
+    E.loff = __mul24(iv, kTabStride);
+    E.goff = valid ? R.sj * row_bytes : (int32_t)0x80000000;
+    E.rk = valid ? R.rk : S.r1;
+    E.raw = R.rk;
+    return E;
+}
+
+struct TabCoeff { f32x2 a, m, b; };
+__device__ inline TabCoeff tab_read(const char *at)
+{
+    return TabCoeff{*reinterpret_cast<const f32x2 *>(at), *reinterpret_cast<const f32x2 *>(at + 256), *reinterpret_cast<const f32x2 *>(at + 512)};
+}
+
+// bit k (worker 0) and bit 32 + k (worker 1): edge k is the last one of its row; rnext: receiver of the following edge, r1 after the last
+__device__ inline uint64_t tab_ends(const TabEdge &E, const TabStep &S, int32_t next_first, int l16, int32_t &rnext)
+{
+    const int32_t up = __builtin_amdgcn_mov_dpp(E.rk, 0x101, 0xf, 0xf, true);   // row_shl:1, the next lane's
+    rnext = l16 == 15 ? (S.tb + 16 <= S.last ? next_first : S.r1) : up;
+    return __ballot(rnext != E.rk) & 0x0000ffff0000ffffull;   // (past the end both are r1)
+}
+
+template <int F, int NW> __device__ inline void tab_load(const float *tab, int hb, float *lds)
+{
+    LdsFill<kTabFloats / 4, NW * 64> fill;
+    fill.load(tab + (size_t)hb * kTabFloats);
+    fill.store(lds);
+    __syncthreads();
+}
+
+// Work items.  Every XCD takes a contiguous eighth of the launch's edges, cut at the rows where the graph's work-item tables (chunk_row)
+// have an entry; the F / 32 blocks of features each go through all of it, on the same XCD.  The XCD's rows are dealt to its
+// blocks in turn, kTabDeal items at a time, so that at any moment they work on a short run of rows whose neighbourhoods share the L2; within
+// its block's share every worker starts at its own item and then draws from a counter in LDS.  (Draws from one counter per XCD in memory: one per 35 ns,
+// 140 us a launch at 32,000 rows.)
+constexpr int kTabDeal = 8;
+struct TabShare {            // one block's share of one partition
+    int32_t lo, hi;          // the XCD's rows
+    __device__ int32_t row(int32_t item, int32_t rows, int32_t slot, int32_t n_slots) const   // first row of the share's item; >= hi: none
+    {
+        return lo + ((item / kTabDeal * n_slots + slot) * kTabDeal + item % kTabDeal) * rows;
+    }
+};
+__device__ inline int32_t tab_cut(const TabArgs &A, int64_t edge)   // the row at which the partition is cut for its edge `edge`
+{
+    return edge <= 0 ? 0 : edge >= A.n_edges ? A.n_rows : min(A.chunk_row[edge / A.span], A.n_rows);
+}
+
+// What both kernels share: the walk over partitions, items and steps.  Per partition open(A); per step load(step) -> TabRec two steps ahead,
+// gather(edge, rows) one step ahead and compute(step, edge, before, rows, next_first); zero_rows(r0, r1) for rows without edges.
+template <int F, int NW, class Rows, class Open, class Load, class Gather, class Compute, class Zero>
+__device__ __forceinline__ void tab_walk(const TabBatch &B, float *lds, int hb, Open open, Load load, Gather gather, Compute compute, Zero zero_rows)
+{
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5, l16 = lane & 15;
+    constexpr int NH = F / 32;
+    const int32_t n_slots = (int32_t)(gridDim.x >> 3) / NH, xcd = blockIdx.x & 7, slot = (int32_t)(blockIdx.x >> 3) / NH;
+    const int64_t total = B.edge_start[B.n], share = (total + 7) >> 3;
+    int32_t *counter = reinterpret_cast<int32_t *>(lds) + kTabFloats;   // items drawn, per partition
+    if (threadIdx.x < kBatch) counter[threadIdx.x] = 2 * NW;
+    const int32_t rows = B.rows;
+    int32_t r0 = 0, r1 = 0, e0 = 0, e1 = 0;   // rows and edges of the worker's next item
+    int32_t drawn = 0;                        // the item after it, as the worker's first lane drew it
+    int part = 0;
+    bool have = false;
+    TabArgs A = B.s[0];
+    TabShare mine{0, 0};
+    auto fetch = [&](int32_t item) {
+        r0 = mine.row(item, rows, slot, n_slots);
+        have = r0 < mine.hi;
+        if (have) {
+            r1 = min(r0 + rows, mine.hi);
+            e0 = (int32_t)A.row_ptr[r0];
+            e1 = (int32_t)A.row_ptr[r1];
+        }
+    };
+    auto draw = [&]() {
+        int zero = 0;
+        asm("" : "+v"(zero));   // (an address that looks uniform would be combined over the lanes, and the result waited for at once)
+        if ((lane & 31) == 0) drawn = __hip_atomic_fetch_add(counter + part + zero, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    auto next_part = [&]() {   // the first partition from `part` on in which the wavefront has an item
+        for (; part < B.n; ++part) {
+            A = B.s[part];
+            const int64_t at = B.edge_start[part];
+            mine.lo = tab_cut(A, xcd * share - at);
+            mine.hi = xcd == 7 ? A.n_rows : tab_cut(A, (xcd + 1) * share - at);
+            fetch(2 * wave + half);
+            if (__any(have)) break;
+        }
+        if (part < B.n) open(A);
+    };
+    next_part();
+    tab_load<F, NW>(B.tab, hb, lds);
+    for (; part < B.n; ++part, next_part()) {
+        draw();
+        TabStep front{1, 0, 0, 0x7fffffff};   // no edges
+        auto advance = [&]() {
+            front.tb += 16;
+            front.r0 = 0x7fffffff;
+            const bool pop = front.tb > front.last;
+            if (__any(pop)) {
+                if (pop) {
+                    front = TabStep{1, 0, 0, 0x7fffffff};
+                    if (have) {
+                        if (e0 < e1) front = TabStep{e0, e1 - 1, r1, r0};
+                        else zero_rows(r0, r1);
+                        const int32_t a = __builtin_amdgcn_readlane(drawn, 0), b = __builtin_amdgcn_readlane(drawn, 32);
+                        fetch(half ? b : a);
+                        draw();
+                    }
+                }
+            }
+        };
+        Rows ga, gb;
+        advance();
+        TabStep SA = front;
+        TabRec RA = load(SA);
+        advance();
+        TabStep SB = front;
+        TabRec RB = load(SB);
+        TabEdge EA = tab_edge(RA, SA, B.inv_h, l16, F * 4), EB;
+        float before_a = RA.before, before_b;
+        gather(EA, ga);
+        while (__any(have || SA.tb <= SA.last || SB.tb <= SB.last)) {
+            advance();
+            const TabStep SC = front;
+            RA = load(SC);
+            EB = tab_edge(RB, SB, B.inv_h, l16, F * 4);
+            before_b = RB.before;
+            gather(EB, gb);
+            __builtin_amdgcn_sched_barrier(0);
+            compute(SA, EA, before_a, ga, row_bcast<0>(EB.rk));
+            advance();
+            SA = SC;
+            const TabStep SD = front;
+            RB = load(SD);
+            EA = tab_edge(RA, SA, B.inv_h, l16, F * 4);
+            before_a = RA.before;
+            gather(EA, ga);
+            __builtin_amdgcn_sched_barrier(0);
+            compute(SB, EB, before_b, gb, row_bcast<0>(EA.rk));
+            SB = SD;
+        }
+    }
+}
+
+// a buffer of n bytes from p on, as 32-bit accesses see it (beyond n they read 0 and write nothing)
+__device__ inline __amdgpu_buffer_rsrc_t tab_buffer(const void *p, uint32_t n)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)n, kBufferFlags);
+}
+__device__ inline int32_t buffer_load_i32(__amdgpu_buffer_rsrc_t r, uint32_t off) { return (int32_t)__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0); }
+
+// Either step with the filters from the MLP itself, in fp32, a wavefront per row, lane = feature: what a launch on tables does when the tables turn out
+// not to represent the filters and nothing else was launched (the call after the first one that learns it takes the MLP's own
+// kernels).  Correct at any size, several times slower than those.
+template <int F, int NW, bool BWD, bool GBAR> __device__ __forceinline__ void tab_exact(const TabBatch &B, float *lds)
+{
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, f = lane & (F - 1);
+    float *W2 = lds, *s_of = lds + F * F + wave * 2 * F, *ds_of = s_of + F;
+    for (int i = threadIdx.x; i < F * F; i += NW * 64) W2[i] = B.bf16 ? (float)(__bf16)(B.W2[i] * kSiluScaleInv) / kSiluScaleInv : B.W2[i];
+    __syncthreads();
+    float w1[8];
+#pragma unroll
+    for (int n = 0; n < 8; ++n) w1[n] = B.W1[n * F + f];
+    for (int part = 0; part < B.n; ++part) {
+        const TabArgs &A = B.s[part];
+        for (int64_t i = (int64_t)blockIdx.x * NW + wave; i < A.n_rows; i += (int64_t)gridDim.x * NW) {
+            const float gi = BWD ? A.g[i * F + f] : 0.f;
+            float acc = 0.f;
+            for (int64_t e = A.row_ptr[i]; e < A.row_ptr[i + 1]; ++e) {
+                const float row = (BWD ? A.abar : A.g)[(int64_t)A.senders[e] * F + f];
+                float t = 0.f, dt = 0.f;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    float b[4], db[4];
+                    radial_basis<true>(A.d[e], B.bp, h, b, db);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        t = fmaf(b[k], w1[2 * k + h], t);
+                        dt = fmaf(db[k], w1[2 * k + h], dt);
+                    }
+                }
+                const float sg = sigmoidf_fast(t);
+                wave_lds_fence();
+                s_of[f] = t * sg;
+                ds_of[f] = sg * (1.f + t * (1.f - sg)) * dt;
+                wave_lds_fence();
+                float w = 0.f, dw = 0.f;
+#pragma unroll 4
+                for (int k = 0; k < F; ++k) {
+                    w = fmaf(s_of[k], W2[k * F + f], w);
+                    if (BWD) dw = fmaf(ds_of[k], W2[k * F + f], dw);
+                }
+                acc = fmaf(w, row, acc);
+                if (BWD) {
+                    float q = lane < F ? dw * (row * gi) : 0.f;
+                    for (int off = 32; off > 0; off >>= 1) q += __shfl_xor(q, off, 64);
+                    if (lane == 0) {
+                        A.dsum[0][e * A.dsum_step] = B.first ? q : A.dsum[0][e * A.dsum_step] + q;
+                        if (F == 64 && B.first) A.dsum[1][e * A.dsum_step] = 0.f;
+                    }
+                }
+            }
+            if (lane < F && (!BWD || GBAR)) A.out[i * F + f] = acc;
+        }
+    }
+}
+
+// Forward step over the owned rows: a_i = sum_e w_e * g_send(e).
+template <int F>
+__global__ void __launch_bounds__(kTabFwdWaves * 64, kTabFwdWaves / 4) k_edge_fwd_tab(TabBatch B)
+{
+    constexpr int kRow = F * 4;
+    extern __shared__ float lds[];
+    if (B.gate && *B.gate != 0) {
+        if (B.exact) tab_exact<F, kTabFwdWaves, false, false>(B, lds);
+        return;
+    }
+    const int lane = threadIdx.x & 63, half = lane >> 5, l16 = lane & 15, fl = lane & 31;
+    const int hb = (blockIdx.x >> 3) & (F / 32 - 1);
+    const char *tab = reinterpret_cast<const char *>(lds) + fl * 8;
+    struct Rows { float g[16]; };
+    __amdgpu_buffer_rsrc_t send, recv, dist, g, out;
+    float acc = 0.f;
+    auto zero_rows = [&](int32_t r, int32_t end) {
+        for (; r < end; ++r) buffer_store_f32(0.f, out, r * kRow + fl * 4, 0, 0);
+    };
+    tab_walk<F, kTabFwdWaves, Rows>(B, lds, hb,
+        [&](const TabArgs &A) {
+            const uint32_t n_rec = (uint32_t)A.n_edges * 4u;
+            send = tab_buffer(A.senders, n_rec);
+            recv = tab_buffer(A.recv, n_rec);
+            dist = tab_buffer(A.d, n_rec);
+            g = tab_buffer(A.g + 32 * hb, (uint32_t)A.n_nodes * kRow - 128u * hb);
+            out = tab_buffer(A.out + 32 * hb, (uint32_t)A.n_rows * kRow - 128u * hb);
+        },
+        [&](const TabStep &S) {
+            const uint32_t at = (uint32_t)min(S.tb + l16, S.last) * 4u;
+            return TabRec{buffer_load_i32(send, at), buffer_load_i32(recv, at), buffer_load_f32(dist, at, 0, 0), 0.f};
+        },
+        [&](const TabEdge &E, Rows &R) {
+            unrolled(std::make_integer_sequence<int, 16>{}, [&](auto k) { R.g[k] = buffer_load_f32(g, row_bcast<k>(E.goff) + fl * 4, 0, 0); });
+        },
+        [&](const TabStep &S, const TabEdge &E, float, const Rows &R, int32_t next_first) {
+            int32_t rnext;
+            const uint64_t ends = tab_ends(E, S, next_first, l16, rnext);
+            const uint32_t any = (uint32_t)ends | (uint32_t)(ends >> 32);
+            const uint32_t mine = half ? (uint32_t)(ends >> 32) : (uint32_t)ends;
+            const int32_t first = row_bcast<0>(E.raw);
+            if (__any(S.r0 < first)) zero_rows(S.r0, first);   // rows of the item before its first edge are empty
+            // values first, kTabGroup edges together with nothing in between that could stop their reads and chains from overlapping;
+            // then the row sums with their branches
+            unrolled(std::make_integer_sequence<int, 16 / kTabGroup>{}, [&](auto grp) {
+                constexpr int k0 = grp * kTabGroup;
+                float p[kTabGroup];
+                unrolled(std::make_integer_sequence<int, kTabGroup>{}, [&](auto t) {
+                    const TabCoeff c = tab_read(tab + row_bcast<k0 + t>(E.loff));
+                    const float s = row_bcast<k0 + t>(E.s);
+                    p[t] = fmaf(s, fmaf(s, fmaf(s, fmaf(s, fmaf(s, c.b[1], c.b[0]), c.m[1]), c.m[0]), c.a[1]), c.a[0]);
+                });
+#pragma unroll
+                for (int t = 0; t < kTabGroup; ++t) pin(p[t]);
+                unrolled(std::make_integer_sequence<int, kTabGroup>{}, [&](auto t) {
+                    constexpr int k = k0 + t;
+                    acc = fmaf(p[t], R.g[k], acc);
+                    if (__builtin_expect((any & (1u << k)) != 0, 0)) {
+                        const int32_t row = row_bcast<k>(E.rk), nrow = row_bcast<k>(rnext);
+                        if (mine & (1u << k)) {
+                            buffer_store_f32(acc, out, row * kRow + fl * 4, 0, 0);
+                            acc = 0.f;
+                            zero_rows(row + 1, nrow);   // empty rows in between
+                        }
+                    }
+                });
+            });
+        },
+        zero_rows);
+}
+
+// Sums of q[0..15] over the 32 lanes of each half: lane l returns the sum of q[k], k = tab_edge_of(l).
+__device__ inline int tab_edge_of(int lane)
+{
+    return 8 * ((lane >> 4) & 1) + ((lane & 8) ? 0 : 4) + ((lane & 4) ? 0 : 2) + (lane & 1);
+}
+template <int CTRL> __device__ inline float add_dpp(float v)   // v plus what the pattern brings of it
+{
+    return v + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+template <int BANKS> __device__ inline float keep_banks(float v, float w)   // w in the named quads of every row of 16 lanes, v in the others
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, v), __builtin_bit_cast(int, w), 0xe4, 0xf, BANKS, false));
+}
+__device__ inline float tab_reduce(const float (&q)[16], int lane)
+{
+    float z[8], y[4], x[2];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {   // rows of 16 lanes: even rows keep edge k, odd ones k + 8
+        const auto sw = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, q[k]), __builtin_bit_cast(unsigned, q[k + 8]), false, false);
+        const unsigned own = sw[0], other = sw[1];   // (a bit_cast of a vector's element reads element 0)
+        z[k] = __builtin_bit_cast(float, own) + __builtin_bit_cast(float, other);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)     // lanes 0-7 of a row keep edge k + 4, lanes 8-15 edge k
+        y[k] = keep_banks<0xc>(add_dpp<0x128>(z[k + 4]), add_dpp<0x128>(z[k]));
+#pragma unroll
+    for (int k = 0; k < 2; ++k)     // even quads keep edge k + 2, odd ones edge k
+        x[k] = keep_banks<0xa>(add_dpp<0x141>(y[k + 2]), add_dpp<0x141>(y[k]));
+    const float u = (lane & 1) ? x[1] : x[0], v = (lane & 1) ? x[0] : x[1];
+    float r = u + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xb1, 0xf, 0xf, true));   // quad_perm 1,0,3,2
+    return r + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, r), 0x4e, 0xf, 0xf, true));      // quad_perm 2,3,0,1
+}
+
+// Reverse step over all local rows, owned and ghost: gbar_i = sum_e w_e * abar_send(e) and, added up over the layers, for every edge
+// its share sum_f w'_f (abar_j g_i)_f of dE/dd.  The share with abar_i g_j is the reverse edge's, whose row gathers abar_i: the forces
+// take both (k_force_rows), and the step gathers one row per edge instead of two.  (In a partition an owned row's edges from
+// ghosts have no share, abar of a ghost being zero, and the ghosts' rows hold the other ones.)
+template <int F, bool GBAR>
+__global__ void __launch_bounds__(kTabBwdWaves * 64, kTabBwdWaves / 4) k_edge_bwd_tab(TabBatch B)
+{
+    constexpr int kRow = F * 4;
+    extern __shared__ float lds[];
+    if (B.gate && *B.gate != 0) {
+        if (B.exact) tab_exact<F, kTabBwdWaves, true, GBAR>(B, lds);
+        return;
+    }
+    const int lane = threadIdx.x & 63, half = lane >> 5, l16 = lane & 15, fl = lane & 31;
+    const int hb = (blockIdx.x >> 3) & (F / 32 - 1);
+    const char *tab = reinterpret_cast<const char *>(lds) + fl * 8;
+    const int k_out = tab_edge_of(lane);                 // the edge of a step whose sum this lane gets
+    const int slope_from = ((lane & 48) | k_out) * 4;    // and the lane that has its record
+    struct Rows { float a[16], gi0, gi1; };              // the senders' rows of abar, and g of the first and the last receiver
+    __amdgpu_buffer_rsrc_t send, recv, dist, g, abar, out, sums;
+    int sum_shift = 2;
+    float acc = 0.f;
+    auto zero_rows = [&](int32_t r, int32_t end) {
+        if (GBAR)
+            for (; r < end; ++r) buffer_store_f32(0.f, out, r * kRow + fl * 4, 0, 0);
+    };
+    tab_walk<F, kTabBwdWaves, Rows>(B, lds, hb,
+        [&](const TabArgs &A) {
+            const uint32_t n_rec = (uint32_t)A.n_edges * 4u;
+            send = tab_buffer(A.senders, n_rec);
+            recv = tab_buffer(A.recv, n_rec);
+            dist = tab_buffer(A.d, n_rec);
+            g = tab_buffer(A.g + 32 * hb, (uint32_t)A.n_nodes * kRow - 128u * hb);
+            abar = tab_buffer(A.abar + 32 * hb, (uint32_t)A.n_nodes * kRow - 128u * hb);
+            out = tab_buffer(A.out + 32 * hb, (uint32_t)A.n_rows * kRow - 128u * hb);
+            sum_shift = A.dsum_step == 2 ? 3 : 2;
+            sums = tab_buffer(hb ? A.dsum[1] : A.dsum[0], ((uint32_t)A.n_edges << sum_shift) - (sum_shift == 3 ? 4u * hb : 0u));
+        },
+        [&](const TabStep &S) {
+            const uint32_t at = (uint32_t)min(S.tb + l16, S.last) * 4u;
+            return TabRec{buffer_load_i32(send, at), buffer_load_i32(recv, at), buffer_load_f32(dist, at, 0, 0),
+                          B.first ? 0.f : buffer_load_f32(sums, (uint32_t)min(S.tb + k_out, S.last) << sum_shift, 0, 0)};
+        },
+        [&](const TabEdge &E, Rows &R) {
+            R.gi0 = buffer_load_f32(g, row_bcast<0>(E.raw) * kRow + fl * 4, 0, 0);
+            R.gi1 = buffer_load_f32(g, row_bcast<15>(E.raw) * kRow + fl * 4, 0, 0);
+            unrolled(std::make_integer_sequence<int, 16>{}, [&](auto k) { R.a[k] = buffer_load_f32(abar, row_bcast<k>(E.goff) + fl * 4, 0, 0); });
+        },
+        [&](const TabStep &S, const TabEdge &E, float before, const Rows &R, int32_t next_first) {
+            int32_t rnext;
+            const uint64_t ends = tab_ends(E, S, next_first, l16, rnext);
+            const uint32_t any = (uint32_t)ends | (uint32_t)(ends >> 32);
+            const uint32_t mine = half ? (uint32_t)(ends >> 32) : (uint32_t)ends;
+            if (GBAR) {
+                const int32_t first = row_bcast<0>(E.raw);
+                if (__any(S.r0 < first)) zero_rows(S.r0, first);   // rows of the item before its first edge are empty
+            }
+            const int32_t row_last = row_bcast<15>(E.raw);
+            float gi = R.gi0, q[16];
+            unrolled(std::make_integer_sequence<int, 16 / kTabGroup>{}, [&](auto grp) {
+                constexpr int k0 = grp * kTabGroup;
+                __builtin_amdgcn_sched_barrier(0);
+                float p[kTabGroup], dp[kTabGroup];
+                unrolled(std::make_integer_sequence<int, kTabGroup>{}, [&](auto t) {   // value and slope
+                    const TabCoeff c = tab_read(tab + row_bcast<k0 + t>(E.loff));
+                    const float s = row_bcast<k0 + t>(E.s);
+                    const float p4 = fmaf(s, c.b[1], c.b[0]), p3 = fmaf(s, p4, c.m[1]), p2 = fmaf(s, p3, c.m[0]), p1 = fmaf(s, p2, c.a[1]);
+                    dp[t] = fmaf(s, fmaf(s, fmaf(s, fmaf(s, c.b[1], p4), p3), p2), p1);
+                    p[t] = GBAR ? fmaf(s, p1, c.a[0]) : 0.f;
+                });
+#pragma unroll
+                for (int t = 0; t < kTabGroup; ++t) {
+                    if (GBAR) pin(p[t]);
+                    pin(dp[t]);
+                }
+                unrolled(std::make_integer_sequence<int, kTabGroup>{}, [&](auto t) {
+                    constexpr int k = k0 + t;
+                    if (GBAR) acc = fmaf(p[t], R.a[k], acc);
+                    q[k] = dp[t] * (R.a[k] * gi);
+                    pin(q[k]);
+                    if (__builtin_expect((any & (1u << k)) != 0, 0)) {
+                        const int32_t row = row_bcast<k>(E.rk), nrow = row_bcast<k>(rnext);
+                        if (mine & (1u << k)) {
+                            if (GBAR) buffer_store_f32(acc, out, row * kRow + fl * 4, 0, 0);
+                            acc = 0.f;
+                            zero_rows(row + 1, nrow);   // empty rows in between
+                            if (k < 15 && S.tb + k < S.last) {   // the next row starts inside this step
+                                gi = R.gi1;
+                                if (nrow != row_last) {   // a third row inside one step (short rows): fetch it now
+                                    gi = buffer_load_f32(g, nrow * kRow + fl * 4, 0, 0);
+                                    pin(gi);   // (completed here: left pending, every later use would wait)
+                                }
+                            }
+                        }
+                    }
+                });
+            });
+            __builtin_amdgcn_sched_barrier(0);
+            const float sum = tab_reduce(q, lane);
+            const float slope = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(slope_from, __builtin_bit_cast(int, E.slope)));
+            if (!(lane & 2) && S.tb + k_out <= S.last)
+                buffer_store_f32(fmaf(sum, slope, before), sums, (uint32_t)(S.tb + k_out) << sum_shift, 0, 0);
+        },
+        zero_rows);
+}
+
+#endif  // MLIP_MODEL_TABLE_H

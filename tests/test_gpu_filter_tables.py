@@ -1,0 +1,120 @@
+"""The edge steps on tabulated filters against the oracle, where the table's intervals change length, at both ends of the range and among rows
+without edges; and the choice between the tables and the filter MLP, which the device makes from the weights."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from oracle import graph as og
+from oracle import model as om
+
+from gpu_util import E_RTOL, F_RTOL
+
+pytestmark = pytest.mark.gpu
+
+R_CUT = 5.0
+UNIT = R_CUT / 179   # the intervals' unit: half of it below 27 units, a quarter from 177 on
+
+
+def _weights(F, L, seed, scale=1.0):
+    w = wl.rmp_weights(4, F, L, seed)
+    w["W1"] = (w["W1"] * np.float32(scale)).astype(np.float32)
+    return w
+
+
+def _run(g, W, mode):
+    import torch
+    import paper_2506_02023_amd as M
+    e, f, a = M.mlip_forward(g, W, mode)
+    torch.cuda.synchronize()
+    return float(e.cpu()[0]), f.cpu().numpy().astype(np.float64), a.cpu().numpy().astype(np.float64)
+
+
+def _check(got, ref, what):
+    """Energy relative to the sum of the atoms' magnitudes (these seeds are not chosen for a large total)."""
+    assert abs(got[0] - ref["energy"]) <= E_RTOL * np.abs(ref["atom_energy"]).sum(), what
+    assert np.abs(got[1] - ref["forces"]).max() <= F_RTOL * np.abs(ref["forces"]).max(), what
+
+
+def _by_mlp(g, W, mode):
+    """Whether a call with weights that were judged before goes by the MLP: only then are there passes over the lower edges."""
+    g.profile_enable(True)
+    g.profile_read(reset=True)
+    _run(g, W, mode)
+    n = g.profile_read(reset=True)["edge_bwd_lower"][1]
+    g.profile_enable(False)
+    return n > 0
+
+
+@pytest.mark.parametrize("F", [32, 64])
+def test_pairs_at_the_ends_of_intervals(F):
+    """Pairs of atoms far from all others, single atoms (rows without edges) before, between and behind them.  A pair's force is
+    held relative to itself: 2e-5 (rounding of the filters' values and slopes, 1e-7 of each, through three layers) and what the
+    rounding of the length to fp32, up to 2^-22 at 5, makes of the fourth power of its distance from the cutoff."""
+    import torch
+    import paper_2506_02023_amd as M
+    edges = [x * UNIT for x in (13.5, 26.5, 27, 28, 90, 176, 177, 177.25, 178, 178.75)]
+    ds = sorted(x + o for x in edges for o in (-1e-6, 1e-6)) + [0.3, 1.0, 2.5, 4.97, 4.99, 4.999]
+    pos, kind = [], []
+    for k, d in enumerate(ds):
+        at = np.array([12.0 * (k % 6), 12.0 * (k // 6), 0.0]) + 3.0
+        if k % 3 == 0:
+            pos.append(at + [0, 0, 6.0])
+            kind.append(-1)
+        u = np.array([np.cos(k), np.sin(k), 0.5])
+        pos += [at, at + d * u / np.linalg.norm(u)]
+        kind += [k, k]
+    pos += [np.array([70.0, 70.0, 9.0])]
+    kind += [-1]
+    pos, kind = np.array(pos), np.array(kind)
+    spec = (np.arange(len(pos)) % 4).astype(np.int32)
+    cell = np.diag([84.0, 84.0, 15.0])
+    w = _weights(F, 3, 5)
+    ref = om.energy_forces(pos, cell, spec, w, og.build_graph(pos, cell, R_CUT), R_CUT, 8, 6)
+    g = M.mlip_build_graph(torch.as_tensor(pos, device="cuda"), cell, torch.as_tensor(spec, device="cuda"), R_CUT)
+    W = M.Weights(w, 6)
+    first, again = _run(g, W, M.MODE_WHOLE), _run(g, W, M.MODE_WHOLE)
+    assert first[0] == again[0] and np.array_equal(first[1], again[1])
+    assert not _by_mlp(g, W, M.MODE_WHOLE)
+    for k, d in enumerate(ds):
+        mine = kind == k
+        err = np.abs(first[1][mine] - ref["forces"][mine]).max() / np.abs(ref["forces"][mine]).max()
+        assert err <= 2e-5 + 4 * 2.0 ** -22 / (R_CUT - d), (d, err)
+    assert np.all(first[1][kind < 0] == 0)
+    assert np.abs(first[2] - ref["atom_energy"]).max() <= 1e-5 * np.abs(ref["atom_energy"]).max()
+
+
+@pytest.mark.parametrize("F,L,slabs", [(32, 2, 1), (64, 3, 1), (64, 1, 3), (64, 3, 3)])
+def test_the_way_follows_the_weights(F, L, slabs):
+    """Filters that bend too fast for the tables (W1 thirty times larger) go by the MLP, ordinary ones by the tables; a handle that
+    only knows ordinary ones gets such weights right too, and every order of calls gives a handle's first results again."""
+    import torch
+    import paper_2506_02023_amd as M
+    c = wl.make_config(1, n=4)
+    mode = M.MODE_SLABS if slabs > 1 else M.MODE_WHOLE
+    pos, sp = torch.as_tensor(c["positions"], device="cuda"), torch.as_tensor(c["species"], device="cuda")
+    ref_g = og.build_graph(c["positions"], c["cell"], c["r_cut"])
+    models = [_weights(F, L, 7), _weights(F, L, 8, 30.0)]
+    refs = [om.energy_forces(c["positions"], c["cell"], c["species"], w, ref_g, c["r_cut"], 8, 6) for w in models]
+    Ws = [M.Weights(w, 6) for w in models]
+    new = lambda: M.mlip_build_graph(pos, c["cell"], sp, c["r_cut"], n_slabs=slabs)  # noqa: E731
+    fresh = [_run(new(), W, mode) for W in Ws]
+    for got, ref in zip(fresh, refs):
+        _check(got, ref, "fresh handle")
+    for k, W in enumerate(Ws):
+        g = new()
+        _run(g, W, mode)
+        if L > 1:
+            assert _by_mlp(g, W, mode) == (k == 1)
+    g = new()
+    for k in (0, 0, 1):   # the third call learns on the device that the tables do not do
+        got = _run(g, Ws[k], mode)
+        _check(got, refs[k], f"model {k}")
+    scale = np.abs(refs[1]["forces"]).max()
+    assert np.abs(got[1] - fresh[1][1]).max() <= F_RTOL * scale
+    for k in (1, 0, 1, 0):
+        got = _run(g, Ws[k], mode)
+        assert got[0] == fresh[k][0] and np.array_equal(got[1], fresh[k][1]) and np.array_equal(got[2], fresh[k][2])
+    for k in (0, 1):
+        s = M.mlip_forward_static(g, Ws[k], mode)
+        torch.cuda.synchronize()
+        assert float(s[0].cpu()[0]) == fresh[k][0] and np.array_equal(s[1].cpu().numpy(), fresh[k][1].astype(np.float32))
