@@ -910,9 +910,9 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         const SmallBatch sb = small_batch(p0, U_LOCAL, -1);
         EnergySum es = energy_sum;
         if (p0 > 0) es.energy = nullptr;
-        const unsigned force_blocks = (unsigned)((sb.start[sb.n] + 15) / 16 + (es.energy ? 1 : 0));
+        const int64_t force_blocks = (sb.start[sb.n] + 15) / 16 + (es.energy ? 1 : 0);
         if (L > 0 && force_blocks > 0)
-            k_force_rows<<<force_blocks, 256, 0, s>>>(sb, pos, g->cell, direct ? forces : nullptr, atom_energy, es);
+            k_force_rows<<<grid8(force_blocks), 256, 0, s>>>(sb, pos, g->cell, direct ? forces : nullptr, atom_energy, es);
         else if (L == 0 && sb.start[sb.n] > 0)
             k_zero_floc<<<blocks_for(sb.start[sb.n], 256), 256, 0, s>>>(sb);
         MLIP_HIP(hipGetLastError());

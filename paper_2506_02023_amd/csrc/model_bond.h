@@ -653,9 +653,13 @@ __global__ void __launch_bounds__(BondStage<STAGE>::NW * 64) k_bond_mlp(BondArgs
     extern __shared__ float packs[];
     const int n_lds_layers = BondStage<STAGE>::PER_LAYER ? min(A.n_layers, 3) : 0;
     const int n_packs = BondStage<STAGE>::PER_LAYER ? 1 + n_lds_layers : NPACK;
-    for (int q = 0; q < n_packs; ++q)
-        for (int i = threadIdx.x; i < PACK / 4; i += NW * 64)
-            reinterpret_cast<f32x4 *>(packs + q * PACK)[i] = reinterpret_cast<const f32x4 *>(A.W[q])[i];
+    LdsFill<PACK / 4, NW * 64> fill[NPACK];
+#pragma unroll
+    for (int q = 0; q < NPACK; ++q)
+        if (q < n_packs) fill[q].load(A.W[q]);
+#pragma unroll
+    for (int q = 0; q < NPACK; ++q)
+        if (q < n_packs) fill[q].store(packs + q * PACK);
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int c32 = lane & 31, h4 = 4 * (lane >> 5);

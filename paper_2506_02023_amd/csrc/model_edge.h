@@ -162,10 +162,14 @@ __global__ void __launch_bounds__(kFwdWaves * 64, 3) k_edge_fwd(EdgeBatch B)
     float *A2t = lds;
     float *A1s = A2t + pack_floats<F>(PREC);
     float *tiles = A1s + D::PACK1;
-    for (int i = threadIdx.x; i < D::PACK1 / 4; i += kFwdWaves * 64)
-        reinterpret_cast<f32x4 *>(A1s)[i] = reinterpret_cast<const f32x4 *>(B.c.A1s)[i];
-    for (int i = threadIdx.x; i < pack_floats<F>(PREC) / 4; i += kFwdWaves * 64)
-        reinterpret_cast<f32x4 *>(A2t)[i] = reinterpret_cast<const f32x4 *>(B.c.A2t)[i];
+    {
+        LdsFill<D::PACK1 / 4, kFwdWaves * 64> f1;
+        LdsFill<pack_floats<F>(PREC) / 4, kFwdWaves * 64> f2;
+        f1.load(B.c.A1s);
+        f2.load(B.c.A2t);
+        f1.store(A1s);
+        f2.store(A2t);
+    }
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int c32 = lane & 31;
@@ -330,10 +334,14 @@ __global__ void __launch_bounds__(kBwdWaves * 64, kBwdWaves == 4 ? 2 : 1) k_edge
     float *A2n = lds;
     float *A1l = A2n + pack_floats<F>(PREC);
     float *queues = A1l + D::PACK1;
-    for (int i = threadIdx.x; i < pack_floats<F>(PREC) / 4; i += kBwdWaves * 64)
-        reinterpret_cast<f32x4 *>(A2n)[i] = reinterpret_cast<const f32x4 *>(B.c.A2n)[i];
-    for (int i = threadIdx.x; i < D::PACK1 / 4; i += kBwdWaves * 64)
-        reinterpret_cast<f32x4 *>(A1l)[i] = reinterpret_cast<const f32x4 *>(B.c.A1)[i];
+    {
+        LdsFill<D::PACK1 / 4, kBwdWaves * 64> f1;
+        LdsFill<pack_floats<F>(PREC) / 4, kBwdWaves * 64> f2;
+        f1.load(B.c.A1);
+        f2.load(B.c.A2n);
+        f1.store(A1l);
+        f2.store(A2n);
+    }
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int c32 = lane & 31;

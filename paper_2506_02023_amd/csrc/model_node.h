@@ -65,13 +65,11 @@ __global__ void __launch_bounds__(NodeOp<OP>::NW * 64) k_node(NodeBatch B)
 {
     constexpr int NB = Dims<F>::NB, NP = NodeOp<OP>::NPACK, NW = NodeOp<OP>::NW, PACK = Dims<F>::PACK3;
     extern __shared__ float lds[];
+    LdsFill<PACK / 4, NW * 64> fill[NP];   // all packs requested at once, and the first tile's rows with them
 #pragma unroll
-    for (int q = 0; q < NP; ++q)
-        for (int i = threadIdx.x; i < PACK / 4; i += NW * 64)
-            reinterpret_cast<f32x4 *>(lds + q * PACK)[i] = reinterpret_cast<const f32x4 *>(B.P[q])[i];
+    for (int q = 0; q < NP; ++q) fill[q].load(B.P[q]);
     if (OP == OP_EMBED)
         for (int64_t i = (int64_t)blockIdx.x * (NW * 64) + threadIdx.x; i < B.n_clear; i += (int64_t)gridDim.x * (NW * 64)) B.clear[i] = 0;
-    __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int c32 = lane & 31, h4 = 4 * (lane >> 5);
     auto pack = [&](int q) { return reinterpret_cast<const __bf16 *>(lds + q * PACK); };
@@ -119,6 +117,9 @@ __global__ void __launch_bounds__(NodeOp<OP>::NW * 64) k_node(NodeBatch B)
         if (OP == OP_UPDATE || OP == OP_TURN || OP == OP_BACK) load(z, A.Z, row, ok);
     };
     if (ti < n_tiles) fetch(ti);
+#pragma unroll
+    for (int q = 0; q < NP; ++q) fill[q].store(lds + q * PACK);
+    __syncthreads();
     for (; ti < n_tiles; ti += stride) {
         const int part = batch_find(B.tile_start, B.n, ti);
         const NodeArgs &A = B.s[part];
@@ -426,11 +427,12 @@ __global__ void __launch_bounds__(256)
 k_force_rows(SmallBatch B, const double *__restrict__ pos, CellParams cp, float *__restrict__ forces,
              float *__restrict__ atom_energy, EnergySum E)
 {
-    if (E.energy && blockIdx.x == gridDim.x - 1) {
-        energy_total(E.n, E.part, E.energy);
+    const int64_t block = xcd_block();   // neighbouring rows gather the same atoms and, on tables, one another's sums
+    if (block * 16 >= B.start[B.n]) {
+        if (E.energy && block * 16 < B.start[B.n] + 16) energy_total(E.n, E.part, E.energy);
         return;
     }
-    const int64_t gr = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+    const int64_t gr = block * 16 + (threadIdx.x >> 4);
     if (gr >= B.start[B.n]) return;   // whole groups of 16 lanes leave together; the shuffles below stay inside a group
     const int part = batch_find(B.start, B.n, gr);
     const SmallArgs &A = B.s[part];
