@@ -216,13 +216,14 @@ template <int F> int launch_edge_tab(mlip_graph *g, TabBatch &b, void (*kernel)(
         MLIP_HIP(hipGetDevice(&dev));
         MLIP_HIP(hipDeviceGetAttribute(&g->n_cu, hipDeviceAttributeMultiprocessorCount, dev));
     }
-    // A few rows at a time, so that the rows all workers of an XCD are at, with their neighbours, stay in its L2 (a million atoms: 1.8 GB
-    // fetched by a forward launch; 8.2 with 22 rows at a time; 3, 6 and 12 rows: 15.4, 15.4 and 15.6 ms a pass); less where
-    // there are not even eight items for every worker.
+    // A few rows at a time, so that the rows all workers of an XCD are at, with their neighbours, stay in its L2 (a million atoms: 1.6 GB
+    // fetched by a forward launch with two, 8.2 with 22; 1.10 ms with two, 1.12 with one or three, 1.22 with six); one where there
+    // are not even eight items for every worker.
     int64_t rows = 0;
     for (int q = 0; q < b.n; ++q) rows += b.s[q].n_rows;
-    const int64_t workers = (int64_t)(g->n_cu / NH) * waves * 2;
+    const int64_t workers = (int64_t)(g->n_cu / NH) * waves * 4;
     b.rows = (int)std::min<int64_t>(kTabRows, std::max<int64_t>(1, rows / (8 * workers)));
+    b.few = rows <= workers;
     b.edge_start[0] = 0;
     for (int q = 0; q < kBatch; ++q) b.edge_start[q + 1] = b.edge_start[q] + (q < b.n ? b.s[q].n_edges : 0);
     if (rows <= 0) return MLIP_OK;

@@ -14,8 +14,8 @@
 // the cutoff the filter vanishes with its first three derivatives, so its error has to vanish too) and 1 between.
 // What is cut off is below what the rounding of the length to fp32 makes (checked when the table is made, see k_filter_table); coefficients
 // and evaluation round to 4e-8 (values) and 5e-8 (slopes) of the filter, the fp32 evaluation of the MLP to 1.7e-7 of both.
-// One block of 32 features is 768 bytes per interval, [3][32][2] coefficients 2 q, 2 q + 1: 162,816 bytes of the
-// compute unit's 160 KB.  With F = 64 every block of the grid holds the table of one half of the features.
+// One block of 32 features is 768 bytes per interval, [3][16][2][2]: coefficients 2 q and 2 q + 1 of features l and l + 16, 16 bytes for one lane; 162,816
+// bytes of the compute unit's 160 KB.  With F = 64 every block of the grid holds the table of one half of the features.
 constexpr int kTabUnits = 179, kTabSmall = 27, kTabEnd = kTabUnits - 2;
 constexpr int kTabM0 = 2 * kTabSmall, kTabE0 = kTabM0 + kTabEnd - kTabSmall, kTabN = kTabE0 + 4 * (kTabUnits - kTabEnd);
 constexpr int kTabStride = 32 * 6 * 4;                   // bytes of an interval
@@ -116,7 +116,7 @@ __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
     if (lane < F) {
         float *at = J.tab + ((size_t)layer * (F / 32) + (lane >> 5)) * kTabFloats + (size_t)iv * (kTabStride / 4);
         const int l = lane & 31;
-        for (int k = 0; k < 6; ++k) at[64 * (k / 2) + 2 * l + k % 2] = (float)c[k];
+        for (int k = 0; k < 6; ++k) at[64 * (k / 2) + 4 * (l % 16) + 2 * (k % 2) + l / 16] = (float)c[k];
     }
     // What is cut off, as root mean squares over the interval and the features: a6 T6 + a7 T7 of the values, 8 a6 + 10 a7 of the slopes
     // (rms of T6' and T7').  Allowed is 1e-7 of the value or slope itself and what half an ulp of the length, rounded to fp32,
@@ -152,14 +152,15 @@ __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
 
 // ---------------------------------------------------------------- edge steps
 //
-// A wavefront is two workers of 32 lanes, lane = feature of the block's half.  A worker walks work items, each a few consecutive rows, in steps
+// A wavefront is four workers of 16 lanes, lane = two features of the block's 32.  A worker walks work items, each a few consecutive rows, in steps
 // of 16 edges; items follow one another without a break in the pipeline (records two steps ahead, gathered rows one), and
-// each worker has its own.  Lane l of a row of 16 lanes holds the record of edge l mod 16 of its worker's step, so that a DPP row
-// broadcast hands a record to the 32 lanes as part of the instruction that uses it, or for one instruction more.
+// each worker has its own.  Lane l of a worker holds the record of edge l of its step; a DPP row broadcast hands it to the others.
 //
-// Measured at a million atoms in 8 slabs (F = 64, 45.8 M edges), per launch: forward 3.13 -> 1.27 ms, reverse 2.87 and 1.22 for the second
-// pass over the lower edges -> 2.00 ms.  Both are bound by the vector unit (forward 13.5 instructions for an edge and 32 features, 9 of them the
-// look-up and the row sum; reverse 25, of which 15) at 1.9 GHz; LDS is busy for 75 % and 53 % of the time.
+// Measured at a million atoms in 8 slabs (F = 64, 45.8 M edges), per launch: forward 3.13 ms by MLP, 1.04 here; reverse 2.87 and 1.22 for the
+// second pass over the lower edges, 1.85 here (layer 0, without gbar, 1.70).  Bound by the vector unit: for four edges and 32 features the
+// forward step takes 20 instructions, 15 of them the look-up and the row sum, the reverse step 38, of which 24; broadcasts and other
+// cross-lane instructions cost 4.4 clocks, plain fp32 ones 2.8.  The chip runs at 1.8 GHz under them.  With two workers of 32 lanes, one feature
+// each, the broadcasts, the sums over lanes and the bookkeeping served two edges instead of four: 1.27 and 2.00 ms.
 
 struct TabArgs {               // one partition
     int32_t n_rows, n_edges;   // receiver rows processed and their edges (below 2^29: 32-bit byte offsets of 8-byte sums)
@@ -182,25 +183,26 @@ struct TabBatch {
     int bf16;
     float inv_h;
     int rows;              // rows of a work item
+    int few;               // few rows for the workers: every XCD takes rows of one partition, 8 / n XCDs each
     int first;             // reverse: dsum is written, not added to
     int n;
     int64_t edge_start[kBatch + 1];
     TabArgs s[kBatch];
 };
 #ifndef MLIP_TAB_FWD_WAVES
-#define MLIP_TAB_FWD_WAVES 16
+#define MLIP_TAB_FWD_WAVES 12
 #endif
 #ifndef MLIP_TAB_BWD_WAVES
-#define MLIP_TAB_BWD_WAVES 16
+#define MLIP_TAB_BWD_WAVES 12
 #endif
 #ifndef MLIP_TAB_GROUP
-#define MLIP_TAB_GROUP 8
+#define MLIP_TAB_GROUP 4
 #endif
 #ifndef MLIP_TAB_ROWS
-#define MLIP_TAB_ROWS 6
+#define MLIP_TAB_ROWS 2
 #endif
 constexpr int kTabRows = MLIP_TAB_ROWS;     // most rows of a work item
-constexpr int kTabGroup = MLIP_TAB_GROUP;   // edges whose values are computed together
+constexpr int kTabGroup = MLIP_TAB_GROUP;   // edges whose values are computed together (8: the reverse step spills, 4 % slower; 2: 4 % slower)
 constexpr int kTabFwdWaves = MLIP_TAB_FWD_WAVES, kTabBwdWaves = MLIP_TAB_BWD_WAVES;
 
 template <int K> __device__ inline int row_bcast(int v) { return __builtin_amdgcn_mov_dpp(v, 0x150 + K, 0xf, 0xf, true); }
@@ -223,7 +225,7 @@ struct TabStep {     // one step of a worker
     int32_t r1;         // the row after the item's
     int32_t r0;         // the item's first row if this is its first step, or 2^31 - 1
 };
-struct TabEdge {     // what the 32 lanes of the worker need of an edge
+struct TabEdge {     // what the lanes of the worker need of an edge
     int32_t goff;    // byte offset of the sender's row; past the end of the array for an edge past the item's last: its row reads 0
     int32_t loff;    // byte offset of the interval in the table
     float s, slope;  // place in the interval, ds / dd
@@ -246,41 +248,47 @@ __device__ inline TabEdge tab_edge(const TabRec &R, const TabStep &S, float inv_
     return E;
 }
 
-struct TabCoeff { f32x2 a, m, b; };
+// the six coefficients of the lane's two features
+struct TabCoeff { f32x4 q0, q1, q2; };
 __device__ inline TabCoeff tab_read(const char *at)
 {
-    return TabCoeff{*reinterpret_cast<const f32x2 *>(at), *reinterpret_cast<const f32x2 *>(at + 256), *reinterpret_cast<const f32x2 *>(at + 512)};
+    return TabCoeff{*reinterpret_cast<const f32x4 *>(at), *reinterpret_cast<const f32x4 *>(at + 256), *reinterpret_cast<const f32x4 *>(at + 512)};
 }
 
-// bit k (worker 0) and bit 32 + k (worker 1): edge k is the last one of its row; rnext: receiver of the following edge, r1 after the last
+// bit 16 w + k: edge k of worker w is the last one of its row; rnext: receiver of the following edge, r1 after the last
 __device__ inline uint64_t tab_ends(const TabEdge &E, const TabStep &S, int32_t next_first, int l16, int32_t &rnext)
 {
     const int32_t up = __builtin_amdgcn_mov_dpp(E.rk, 0x101, 0xf, 0xf, true);   // row_shl:1, the next lane's
     rnext = l16 == 15 ? (S.tb + 16 <= S.last ? next_first : S.r1) : up;
-    return __ballot(rnext != E.rk) & 0x0000ffff0000ffffull;   // (past the end both are r1)
+    return __ballot(rnext != E.rk);   // (past the end both are r1)
 }
 
-template <int F, int NW> __device__ inline void tab_load(const float *tab, int hb, float *lds)
+// a buffer of n bytes from p on, as 32-bit accesses see it (beyond n they read 0 and write nothing)
+__device__ inline __amdgpu_buffer_rsrc_t tab_buffer(const void *p, uint32_t n)
 {
-    LdsFill<kTabFloats / 4, NW * 64> fill;
-    fill.load(tab + (size_t)hb * kTabFloats);
-    fill.store(lds);
-    __syncthreads();
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)n, kBufferFlags);
 }
+// The lane's two features, l and l + 16: 64 bytes of 16 lanes at a time.  (Features 2 l and 2 l + 1 as 8 bytes of a lane: twice the cache accesses for the
+// same rows, and the address unit busy for 82 % of the forward step.)
+__device__ inline f32x2 buffer_load_2(__amdgpu_buffer_rsrc_t r, uint32_t off)
+{
+    return f32x2{buffer_load_f32(r, off, 0, 0), buffer_load_f32(r, off + 64, 0, 0)};
+}
+__device__ inline void buffer_store_2(f32x2 v, __amdgpu_buffer_rsrc_t r, uint32_t off)
+{
+    buffer_store_f32(v[0], r, off, 0, 0);
+    buffer_store_f32(v[1], r, off + 64, 0, 0);
+}
+__device__ inline int32_t buffer_load_i32(__amdgpu_buffer_rsrc_t r, uint32_t off) { return (int32_t)__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0); }
 
 // Work items.  Every XCD takes a contiguous eighth of the launch's edges, cut at the rows where the graph's work-item tables (chunk_row)
-// have an entry; the F / 32 blocks of features each go through all of it, on the same XCD.  The XCD's rows are dealt to its
+// have an entry (of a launch with about a row for a worker, where one partition after the other and a look at those tables would be most of its
+// time, 21 us for 8 x 192 rows, rows of one partition); the F / 32 blocks of features each go through all of it, on the same XCD.  The XCD's rows are dealt to its
 // blocks in turn, kTabDeal items at a time, so that at any moment they work on a short run of rows whose neighbourhoods share the L2; within
 // its block's share every worker starts at its own item and then draws from a counter in LDS.  (Draws from one counter per XCD in memory: one per 35 ns,
 // 140 us a launch at 32,000 rows.)
 constexpr int kTabDeal = 8;
-struct TabShare {            // one block's share of one partition
-    int32_t lo, hi;          // the XCD's rows
-    __device__ int32_t row(int32_t item, int32_t rows, int32_t slot, int32_t n_slots) const   // first row of the share's item; >= hi: none
-    {
-        return lo + ((item / kTabDeal * n_slots + slot) * kTabDeal + item % kTabDeal) * rows;
-    }
-};
+static_assert(kTabDeal == 8, "tab_walk shifts by three");
 __device__ inline int32_t tab_cut(const TabArgs &A, int64_t edge)   // the row at which the partition is cut for its edge `edge`
 {
     return edge <= 0 ? 0 : edge >= A.n_edges ? A.n_rows : min(A.chunk_row[edge / A.span], A.n_rows);
@@ -291,75 +299,94 @@ __device__ inline int32_t tab_cut(const TabArgs &A, int64_t edge)   // the row a
 template <int F, int NW, class Rows, class Open, class Load, class Gather, class Compute, class Zero>
 __device__ __forceinline__ void tab_walk(const TabBatch &B, float *lds, int hb, Open open, Load load, Gather gather, Compute compute, Zero zero_rows)
 {
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5, l16 = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, l16 = lane & 15;
     constexpr int NH = F / 32;
     const int32_t n_slots = (int32_t)(gridDim.x >> 3) / NH, xcd = blockIdx.x & 7, slot = (int32_t)(blockIdx.x >> 3) / NH;
     const int64_t total = B.edge_start[B.n], share = (total + 7) >> 3;
+    const int64_t from = xcd * share, to = xcd == 7 ? total + 1 : from + share;   // the XCD's edges
+    const int32_t mine = xcd * B.n >> 3, mine_from = (8 * mine + B.n - 1) / B.n, mine_n = (8 * mine + 8 + B.n - 1) / B.n - mine_from;   // B.few
     int32_t *counter = reinterpret_cast<int32_t *>(lds) + kTabFloats;   // items drawn, per partition
-    if (threadIdx.x < kBatch) counter[threadIdx.x] = 2 * NW;
+    if (threadIdx.x < kBatch) counter[threadIdx.x] = 4 * NW;
     const int32_t rows = B.rows;
     int32_t r0 = 0, r1 = 0, e0 = 0, e1 = 0;   // rows and edges of the worker's next item
     int32_t drawn = 0;                        // the item after it, as the worker's first lane drew it
     int part = 0;
-    bool have = false;
-    TabArgs A = B.s[0];
-    TabShare mine{0, 0};
+    bool have = false;                        // whether there is a next item
+    int32_t lo = 0, hi = 0;                   // the XCD's rows; lo: the first one dealt to this block
+    __amdgpu_buffer_rsrc_t ptr;
+    const int32_t turn = n_slots * kTabDeal * rows;   // rows from one of the block's turns to the next
     auto fetch = [&](int32_t item) {
-        r0 = mine.row(item, rows, slot, n_slots);
-        have = r0 < mine.hi;
-        if (have) {
-            r1 = min(r0 + rows, mine.hi);
-            e0 = (int32_t)A.row_ptr[r0];
-            e1 = (int32_t)A.row_ptr[r1];
-        }
+        r0 = lo + __mul24(item >> 3, turn) + __mul24(item & (kTabDeal - 1), rows);
+        r1 = min(r0 + rows, hi);
+        have = r0 < hi;
+        e0 = buffer_load_i32(ptr, (uint32_t)r0 * 8u);   // (past the last row: reads 0)
+        e1 = buffer_load_i32(ptr, (uint32_t)r1 * 8u);
     };
     auto draw = [&]() {
         int zero = 0;
         asm("" : "+v"(zero));   // (an address that looks uniform would be combined over the lanes, and the result waited for at once)
-        if ((lane & 31) == 0) drawn = __hip_atomic_fetch_add(counter + part + zero, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (l16 == 0) drawn = __hip_atomic_fetch_add(counter + part + zero, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
     auto next_part = [&]() {   // the first partition from `part` on in which the wavefront has an item
         for (; part < B.n; ++part) {
-            A = B.s[part];
-            const int64_t at = B.edge_start[part];
-            mine.lo = tab_cut(A, xcd * share - at);
-            mine.hi = xcd == 7 ? A.n_rows : tab_cut(A, (xcd + 1) * share - at);
-            fetch(2 * wave + half);
-            if (__any(have)) break;
+            const TabArgs &A = B.s[part];
+            if (B.few) {
+                if (part != mine) continue;
+                lo = (int32_t)((int64_t)A.n_rows * (xcd - mine_from) / mine_n);
+                hi = (int32_t)((int64_t)A.n_rows * (xcd - mine_from + 1) / mine_n);
+            } else {
+                // decided from the arguments alone, without a look at every partition's arrays; one without edges goes to the XCD of the edge behind it
+                const int64_t at = B.edge_start[part], end = B.edge_start[part + 1];
+                if (at < end ? at >= to || end <= from : at < from || at >= to) continue;
+                lo = tab_cut(A, from - at);
+                hi = to > total ? A.n_rows : tab_cut(A, to - at);
+            }
+            lo += slot * kTabDeal * rows;
+            ptr = tab_buffer(A.row_ptr, ((uint32_t)A.n_rows + 1u) * 8u);
+            fetch(4 * wave + (lane >> 4));
+            if (__any(have)) {
+                open(A);
+                break;
+            }
         }
-        if (part < B.n) open(A);
+    };
+    TabStep front, SA, SB;
+    TabRec RA, RB;
+    TabEdge EA, EB;
+    float before_a = 0.f, before_b;
+    Rows ga, gb;
+    auto advance = [&]() {
+        front.tb += 16;
+        front.r0 = 0x7fffffff;
+        const bool pop = front.tb > front.last;
+        if (__any(pop)) {
+            if (pop) {
+                const bool edges = have && e0 < e1;
+                front = TabStep{edges ? e0 : 1, edges ? e1 - 1 : 0, r1, edges ? r0 : 0x7fffffff};
+                if (have && e0 == e1) zero_rows(r0, r1);
+                fetch(row_bcast<0>(drawn));
+                draw();
+            }
+        }
     };
     next_part();
-    tab_load<F, NW>(B.tab, hb, lds);
+    {
+        LdsFill<kTabFloats / 4, NW * 64> fill;
+        fill.load(B.tab + (size_t)hb * kTabFloats);
+        fill.store(lds);
+    }
+    __syncthreads();
     for (; part < B.n; ++part, next_part()) {
         draw();
-        TabStep front{1, 0, 0, 0x7fffffff};   // no edges
-        auto advance = [&]() {
-            front.tb += 16;
-            front.r0 = 0x7fffffff;
-            const bool pop = front.tb > front.last;
-            if (__any(pop)) {
-                if (pop) {
-                    front = TabStep{1, 0, 0, 0x7fffffff};
-                    if (have) {
-                        if (e0 < e1) front = TabStep{e0, e1 - 1, r1, r0};
-                        else zero_rows(r0, r1);
-                        const int32_t a = __builtin_amdgcn_readlane(drawn, 0), b = __builtin_amdgcn_readlane(drawn, 32);
-                        fetch(half ? b : a);
-                        draw();
-                    }
-                }
-            }
-        };
-        Rows ga, gb;
+        front = TabStep{1, 0, 0, 0x7fffffff};   // no edges
         advance();
-        TabStep SA = front;
-        TabRec RA = load(SA);
+        SA = front;
+        RA = load(SA);
         advance();
-        TabStep SB = front;
-        TabRec RB = load(SB);
-        TabEdge EA = tab_edge(RA, SA, B.inv_h, l16, F * 4), EB;
-        float before_a = RA.before, before_b;
+        SB = front;
+        RB = load(SB);
+        EA = tab_edge(RA, SA, B.inv_h, l16, F * 4);
+        before_a = RA.before;
         gather(EA, ga);
         while (__any(have || SA.tb <= SA.last || SB.tb <= SB.last)) {
             advance();
@@ -384,12 +411,6 @@ __device__ __forceinline__ void tab_walk(const TabBatch &B, float *lds, int hb, 
     }
 }
 
-// a buffer of n bytes from p on, as 32-bit accesses see it (beyond n they read 0 and write nothing)
-__device__ inline __amdgpu_buffer_rsrc_t tab_buffer(const void *p, uint32_t n)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)n, kBufferFlags);
-}
-__device__ inline int32_t buffer_load_i32(__amdgpu_buffer_rsrc_t r, uint32_t off) { return (int32_t)__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0); }
 
 // Either step with the filters from the MLP itself, in fp32, a wavefront per row, lane = feature: what a launch on tables does when the tables turn out
 // not to represent the filters and nothing else was launched (the call after the first one that learns it takes the MLP's own
@@ -457,14 +478,14 @@ __global__ void __launch_bounds__(kTabFwdWaves * 64, kTabFwdWaves / 4) k_edge_fw
         if (B.exact) tab_exact<F, kTabFwdWaves, false, false>(B, lds);
         return;
     }
-    const int lane = threadIdx.x & 63, half = lane >> 5, l16 = lane & 15, fl = lane & 31;
+    const int lane = threadIdx.x & 63, l16 = lane & 15, at_f = l16 * 4;   // byte offset of the lane's first feature in a block of 32
     const int hb = (blockIdx.x >> 3) & (F / 32 - 1);
-    const char *tab = reinterpret_cast<const char *>(lds) + fl * 8;
-    struct Rows { float g[16]; };
+    const char *tab = reinterpret_cast<const char *>(lds) + l16 * 16;
+    struct Rows { f32x2 g[16]; };
     __amdgpu_buffer_rsrc_t send, recv, dist, g, out;
-    float acc = 0.f;
+    f32x2 acc = {0.f, 0.f};
     auto zero_rows = [&](int32_t r, int32_t end) {
-        for (; r < end; ++r) buffer_store_f32(0.f, out, r * kRow + fl * 4, 0, 0);
+        for (; r < end; ++r) buffer_store_2(f32x2{0.f, 0.f}, out, r * kRow + at_f);
     };
     tab_walk<F, kTabFwdWaves, Rows>(B, lds, hb,
         [&](const TabArgs &A) {
@@ -480,35 +501,42 @@ __global__ void __launch_bounds__(kTabFwdWaves * 64, kTabFwdWaves / 4) k_edge_fw
             return TabRec{buffer_load_i32(send, at), buffer_load_i32(recv, at), buffer_load_f32(dist, at, 0, 0), 0.f};
         },
         [&](const TabEdge &E, Rows &R) {
-            unrolled(std::make_integer_sequence<int, 16>{}, [&](auto k) { R.g[k] = buffer_load_f32(g, row_bcast<k>(E.goff) + fl * 4, 0, 0); });
+            unrolled(std::make_integer_sequence<int, 16>{}, [&](auto k) { R.g[k] = buffer_load_2(g, row_bcast<k>(E.goff) + at_f); });
         },
         [&](const TabStep &S, const TabEdge &E, float, const Rows &R, int32_t next_first) {
             int32_t rnext;
             const uint64_t ends = tab_ends(E, S, next_first, l16, rnext);
-            const uint32_t any = (uint32_t)ends | (uint32_t)(ends >> 32);
-            const uint32_t mine = half ? (uint32_t)(ends >> 32) : (uint32_t)ends;
+            const uint32_t two = (uint32_t)ends | (uint32_t)(ends >> 32), any = two | two >> 16;
+            const uint32_t mine = (uint32_t)(ends >> (lane & 48));
             const int32_t first = row_bcast<0>(E.raw);
             if (__any(S.r0 < first)) zero_rows(S.r0, first);   // rows of the item before its first edge are empty
             // values first, kTabGroup edges together with nothing in between that could stop their reads and chains from overlapping;
             // then the row sums with their branches
             unrolled(std::make_integer_sequence<int, 16 / kTabGroup>{}, [&](auto grp) {
                 constexpr int k0 = grp * kTabGroup;
-                float p[kTabGroup];
+                __builtin_amdgcn_sched_barrier(0);
+                float p[kTabGroup][2];
                 unrolled(std::make_integer_sequence<int, kTabGroup>{}, [&](auto t) {
                     const TabCoeff c = tab_read(tab + row_bcast<k0 + t>(E.loff));
                     const float s = row_bcast<k0 + t>(E.s);
-                    p[t] = fmaf(s, fmaf(s, fmaf(s, fmaf(s, fmaf(s, c.b[1], c.b[0]), c.m[1]), c.m[0]), c.a[1]), c.a[0]);
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+                        p[t][i] = fmaf(s, fmaf(s, fmaf(s, fmaf(s, fmaf(s, c.q2[2 + i], c.q2[i]), c.q1[2 + i]), c.q1[i]), c.q0[2 + i]), c.q0[i]);
                 });
 #pragma unroll
-                for (int t = 0; t < kTabGroup; ++t) pin(p[t]);
+                for (int t = 0; t < kTabGroup; ++t) {
+                    pin(p[t][0]);
+                    pin(p[t][1]);
+                }
                 unrolled(std::make_integer_sequence<int, kTabGroup>{}, [&](auto t) {
                     constexpr int k = k0 + t;
-                    acc = fmaf(p[t], R.g[k], acc);
+                    acc[0] = fmaf(p[t][0], R.g[k][0], acc[0]);
+                    acc[1] = fmaf(p[t][1], R.g[k][1], acc[1]);
                     if (__builtin_expect((any & (1u << k)) != 0, 0)) {
                         const int32_t row = row_bcast<k>(E.rk), nrow = row_bcast<k>(rnext);
                         if (mine & (1u << k)) {
-                            buffer_store_f32(acc, out, row * kRow + fl * 4, 0, 0);
-                            acc = 0.f;
+                            buffer_store_2(acc, out, row * kRow + at_f);
+                            acc = f32x2{0.f, 0.f};
                             zero_rows(row + 1, nrow);   // empty rows in between
                         }
                     }
@@ -518,11 +546,9 @@ __global__ void __launch_bounds__(kTabFwdWaves * 64, kTabFwdWaves / 4) k_edge_fw
         zero_rows);
 }
 
-// Sums of q[0..15] over the 32 lanes of each half: lane l returns the sum of q[k], k = tab_edge_of(l).
-__device__ inline int tab_edge_of(int lane)
-{
-    return 8 * ((lane >> 4) & 1) + ((lane & 8) ? 0 : 4) + ((lane & 4) ? 0 : 2) + (lane & 1);
-}
+// Sums of q[0..15] over the 16 lanes of each row: lane l returns the sum of q[tab_edge_of(l)].  Each step adds lanes across one bit of the lane
+// number and lets the lanes on either side go on with one of two edges.
+__device__ inline int tab_edge_of(int lane) { return ((lane & 8) ? 0 : 8) + ((lane & 4) ? 0 : 4) + (lane & 3); }
 template <int CTRL> __device__ inline float add_dpp(float v)   // v plus what the pattern brings of it
 {
     return v + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
@@ -535,20 +561,19 @@ __device__ inline float tab_reduce(const float (&q)[16], int lane)
 {
     float z[8], y[4], x[2];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {   // rows of 16 lanes: even rows keep edge k, odd ones k + 8
-        const auto sw = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, q[k]), __builtin_bit_cast(unsigned, q[k + 8]), false, false);
-        const unsigned own = sw[0], other = sw[1];   // (a bit_cast of a vector's element reads element 0)
-        z[k] = __builtin_bit_cast(float, own) + __builtin_bit_cast(float, other);
-    }
+    for (int k = 0; k < 8; ++k)     // row_ror:8; lanes 0-7 of a row keep edge k + 8, lanes 8-15 edge k
+        z[k] = keep_banks<0xc>(add_dpp<0x128>(q[k + 8]), add_dpp<0x128>(q[k]));
 #pragma unroll
-    for (int k = 0; k < 4; ++k)     // lanes 0-7 of a row keep edge k + 4, lanes 8-15 edge k
-        y[k] = keep_banks<0xc>(add_dpp<0x128>(z[k + 4]), add_dpp<0x128>(z[k]));
+    for (int k = 0; k < 4; ++k)     // row_half_mirror; even quads keep edge k + 4, odd ones edge k
+        y[k] = keep_banks<0xa>(add_dpp<0x141>(z[k + 4]), add_dpp<0x141>(z[k]));
+    const unsigned bit1 = (lane & 2) ? ~0u : 0u, bit0 = (lane & 1) ? ~0u : 0u;
+    auto keep = [](unsigned mask, float v, float w) {   // w where the mask is set
+        return __builtin_bit_cast(float, (__builtin_bit_cast(unsigned, w) & mask) | (__builtin_bit_cast(unsigned, v) & ~mask));
+    };
 #pragma unroll
-    for (int k = 0; k < 2; ++k)     // even quads keep edge k + 2, odd ones edge k
-        x[k] = keep_banks<0xa>(add_dpp<0x141>(y[k + 2]), add_dpp<0x141>(y[k]));
-    const float u = (lane & 1) ? x[1] : x[0], v = (lane & 1) ? x[0] : x[1];
-    float r = u + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xb1, 0xf, 0xf, true));   // quad_perm 1,0,3,2
-    return r + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, r), 0x4e, 0xf, 0xf, true));      // quad_perm 2,3,0,1
+    for (int k = 0; k < 2; ++k)     // quad_perm 2,3,0,1
+        x[k] = keep(bit1, add_dpp<0x4e>(y[k]), add_dpp<0x4e>(y[k + 2]));
+    return keep(bit0, add_dpp<0xb1>(x[0]), add_dpp<0xb1>(x[1]));   // quad_perm 1,0,3,2
 }
 
 // Reverse step over all local rows, owned and ghost: gbar_i = sum_e w_e * abar_send(e) and, added up over the layers, for every edge
@@ -564,18 +589,18 @@ __global__ void __launch_bounds__(kTabBwdWaves * 64, kTabBwdWaves / 4) k_edge_bw
         if (B.exact) tab_exact<F, kTabBwdWaves, true, GBAR>(B, lds);
         return;
     }
-    const int lane = threadIdx.x & 63, half = lane >> 5, l16 = lane & 15, fl = lane & 31;
+    const int lane = threadIdx.x & 63, l16 = lane & 15, at_f = l16 * 4;   // byte offset of the lane's first feature in a block of 32
     const int hb = (blockIdx.x >> 3) & (F / 32 - 1);
-    const char *tab = reinterpret_cast<const char *>(lds) + fl * 8;
+    const char *tab = reinterpret_cast<const char *>(lds) + l16 * 16;
     const int k_out = tab_edge_of(lane);                 // the edge of a step whose sum this lane gets
     const int slope_from = ((lane & 48) | k_out) * 4;    // and the lane that has its record
-    struct Rows { float a[16], gi0, gi1; };              // the senders' rows of abar, and g of the first and the last receiver
+    struct Rows { f32x2 a[16], gi0, gi1; };              // the senders' rows of abar, and g of the first and the last receiver
     __amdgpu_buffer_rsrc_t send, recv, dist, g, abar, out, sums;
     int sum_shift = 2;
-    float acc = 0.f;
+    f32x2 acc = {0.f, 0.f};
     auto zero_rows = [&](int32_t r, int32_t end) {
         if (GBAR)
-            for (; r < end; ++r) buffer_store_f32(0.f, out, r * kRow + fl * 4, 0, 0);
+            for (; r < end; ++r) buffer_store_2(f32x2{0.f, 0.f}, out, r * kRow + at_f);
     };
     tab_walk<F, kTabBwdWaves, Rows>(B, lds, hb,
         [&](const TabArgs &A) {
@@ -595,53 +620,66 @@ __global__ void __launch_bounds__(kTabBwdWaves * 64, kTabBwdWaves / 4) k_edge_bw
                           B.first ? 0.f : buffer_load_f32(sums, (uint32_t)min(S.tb + k_out, S.last) << sum_shift, 0, 0)};
         },
         [&](const TabEdge &E, Rows &R) {
-            R.gi0 = buffer_load_f32(g, row_bcast<0>(E.raw) * kRow + fl * 4, 0, 0);
-            R.gi1 = buffer_load_f32(g, row_bcast<15>(E.raw) * kRow + fl * 4, 0, 0);
-            unrolled(std::make_integer_sequence<int, 16>{}, [&](auto k) { R.a[k] = buffer_load_f32(abar, row_bcast<k>(E.goff) + fl * 4, 0, 0); });
+            R.gi0 = buffer_load_2(g, row_bcast<0>(E.raw) * kRow + at_f);
+            R.gi1 = buffer_load_2(g, row_bcast<15>(E.raw) * kRow + at_f);
+            unrolled(std::make_integer_sequence<int, 16>{}, [&](auto k) { R.a[k] = buffer_load_2(abar, row_bcast<k>(E.goff) + at_f); });
         },
         [&](const TabStep &S, const TabEdge &E, float before, const Rows &R, int32_t next_first) {
             int32_t rnext;
             const uint64_t ends = tab_ends(E, S, next_first, l16, rnext);
-            const uint32_t any = (uint32_t)ends | (uint32_t)(ends >> 32);
-            const uint32_t mine = half ? (uint32_t)(ends >> 32) : (uint32_t)ends;
+            const uint32_t two = (uint32_t)ends | (uint32_t)(ends >> 32), any = two | two >> 16;
+            const uint32_t mine = (uint32_t)(ends >> (lane & 48));
             if (GBAR) {
                 const int32_t first = row_bcast<0>(E.raw);
                 if (__any(S.r0 < first)) zero_rows(S.r0, first);   // rows of the item before its first edge are empty
             }
             const int32_t row_last = row_bcast<15>(E.raw);
-            float gi = R.gi0, q[16];
+            f32x2 gi = R.gi0;
+            float q[16];
             unrolled(std::make_integer_sequence<int, 16 / kTabGroup>{}, [&](auto grp) {
                 constexpr int k0 = grp * kTabGroup;
                 __builtin_amdgcn_sched_barrier(0);
-                float p[kTabGroup], dp[kTabGroup];
+                float p[kTabGroup][2], dp[kTabGroup][2];
                 unrolled(std::make_integer_sequence<int, kTabGroup>{}, [&](auto t) {   // value and slope
                     const TabCoeff c = tab_read(tab + row_bcast<k0 + t>(E.loff));
                     const float s = row_bcast<k0 + t>(E.s);
-                    const float p4 = fmaf(s, c.b[1], c.b[0]), p3 = fmaf(s, p4, c.m[1]), p2 = fmaf(s, p3, c.m[0]), p1 = fmaf(s, p2, c.a[1]);
-                    dp[t] = fmaf(s, fmaf(s, fmaf(s, fmaf(s, c.b[1], p4), p3), p2), p1);
-                    p[t] = GBAR ? fmaf(s, p1, c.a[0]) : 0.f;
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        const float p4 = fmaf(s, c.q2[2 + i], c.q2[i]), p3 = fmaf(s, p4, c.q1[2 + i]), p2 = fmaf(s, p3, c.q1[i]),
+                                    p1 = fmaf(s, p2, c.q0[2 + i]);
+                        dp[t][i] = fmaf(s, fmaf(s, fmaf(s, fmaf(s, c.q2[2 + i], p4), p3), p2), p1);
+                        p[t][i] = GBAR ? fmaf(s, p1, c.q0[i]) : 0.f;
+                    }
                 });
 #pragma unroll
-                for (int t = 0; t < kTabGroup; ++t) {
-                    if (GBAR) pin(p[t]);
-                    pin(dp[t]);
-                }
+                for (int t = 0; t < kTabGroup; ++t)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        if (GBAR) pin(p[t][i]);
+                        pin(dp[t][i]);
+                    }
                 unrolled(std::make_integer_sequence<int, kTabGroup>{}, [&](auto t) {
                     constexpr int k = k0 + t;
-                    if (GBAR) acc = fmaf(p[t], R.a[k], acc);
-                    q[k] = dp[t] * (R.a[k] * gi);
+                    if (GBAR) {
+                        acc[0] = fmaf(p[t][0], R.a[k][0], acc[0]);
+                        acc[1] = fmaf(p[t][1], R.a[k][1], acc[1]);
+                    }
+                    q[k] = fmaf(dp[t][0], R.a[k][0] * gi[0], dp[t][1] * (R.a[k][1] * gi[1]));
                     pin(q[k]);
                     if (__builtin_expect((any & (1u << k)) != 0, 0)) {
                         const int32_t row = row_bcast<k>(E.rk), nrow = row_bcast<k>(rnext);
                         if (mine & (1u << k)) {
-                            if (GBAR) buffer_store_f32(acc, out, row * kRow + fl * 4, 0, 0);
-                            acc = 0.f;
+                            if (GBAR) buffer_store_2(acc, out, row * kRow + at_f);
+                            acc = f32x2{0.f, 0.f};
                             zero_rows(row + 1, nrow);   // empty rows in between
                             if (k < 15 && S.tb + k < S.last) {   // the next row starts inside this step
                                 gi = R.gi1;
                                 if (nrow != row_last) {   // a third row inside one step (short rows): fetch it now
-                                    gi = buffer_load_f32(g, nrow * kRow + fl * 4, 0, 0);
-                                    pin(gi);   // (completed here: left pending, every later use would wait)
+                                    const f32x2 third = buffer_load_2(g, nrow * kRow + at_f);
+                                    float a0 = third[0], a1 = third[1];
+                                    pin(a0);
+                                    pin(a1);
+                                    gi = f32x2{a0, a1};   // (completed here: left pending, every later use would wait)
                                 }
                             }
                         }
@@ -651,7 +689,7 @@ __global__ void __launch_bounds__(kTabBwdWaves * 64, kTabBwdWaves / 4) k_edge_bw
             __builtin_amdgcn_sched_barrier(0);
             const float sum = tab_reduce(q, lane);
             const float slope = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(slope_from, __builtin_bit_cast(int, E.slope)));
-            if (!(lane & 2) && S.tb + k_out <= S.last)
+            if (S.tb + k_out <= S.last)
                 buffer_store_f32(fmaf(sum, slope, before), sums, (uint32_t)(S.tb + k_out) << sum_shift, 0, 0);
         },
         zero_rows);
