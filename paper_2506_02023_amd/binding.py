@@ -306,7 +306,8 @@ class Weights:
 
     def __init__(self, weights, p, K=8, device="cuda", precision=0):
         """precision: 0 = fp32, 1 = bf16 operands for the filter MLP's F x F products (fp32 accumulation),
-        2 = those products as split-fp16 triples (fp32-grade results)."""
+        2 = those products as split-fp16 triples (fp32-grade results).  Filters looked up in tables: 1 rounds W2 to
+        bf16, 2 is the same as 0."""
         self.t = {k: torch.as_tensor(np.ascontiguousarray(weights[k], np.float32)).to(device).contiguous()
                   for k in ("emb", "W1", "W2", "Wm", "Wo", "Wr1", "wr2")}
         self.serial = next(_serial)

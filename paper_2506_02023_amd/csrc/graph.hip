@@ -1971,7 +1971,7 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
     MLIP_TRY(g->mirror.ensure((size_t)std::max<int64_t>(E, 1) * 4));
 
     {
-        g->whole.span = chunk_span(E, kSpanTable);
+        g->whole.span = chunk_span(E);
         const int64_t nc = chunks_of(E, g->whole.span);
         MLIP_TRY(g->chunk_row.ensure((size_t)(nc + 1) * 4));
         k_chunk_rows<<<blocks_for(nc + 1, 256), 256, 0, s>>>(N, nc, g->whole.span, g->row_ptr.as<int64_t>(), g->chunk_row.as<int32_t>());
@@ -2085,7 +2085,7 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
             set_error("internal error: an edge without its reverse edge");
             return MLIP_EHIP;
         }
-        const int32_t span = chunk_span(E * std::min(P, kPairBatch) / P, kSpanTable);   // edges of one launch over up to kPairBatch partitions
+        const int32_t span = chunk_span(E * std::min(P, kPairBatch) / P);   // edges of one launch over up to kPairBatch partitions
         int64_t TE = 0;
         std::vector<int64_t> ebase(P + 1);
         for (int q = 0; q < P; ++q) {

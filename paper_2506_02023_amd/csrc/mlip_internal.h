@@ -93,19 +93,19 @@ __device__ inline unsigned xcd_block() { return (blockIdx.x & 7u) * (gridDim.x >
 #endif
 inline unsigned grid8(int64_t blocks) { return (unsigned)(((blocks > 0 ? blocks : 1) + 7) / 8 * 8); }
 
-// Work item of the edge kernels: the rows whose first edge lies in one span of `span` edges.  A wavefront walks an item
-// serially (about 5 us per 32 edges when little else runs), so the span is taken from the edges of the launch: 8 items
-// for each of the 2048 wavefronts that are resident at once (256 compute units, 8 wavefronts of the reverse kernel on
-// each), at most 1024 edges (longer items no longer pay for their pipeline fill, shorter ones do at a million atoms), and
-// at least two tiles of 32, or one where there are not even 1024 items of two.  Measured, us per pass of graph + energy +
-// forces: 1024 edges throughout -> 8 items per wavefront 500 atoms 1587 -> 632, 108,000 atoms in 8 slabs 4732 -> 4233, a
-// million unchanged (4 items 4302 and 2 items 4591 at 108,000); least span 32 -> 64 later 4,000 atoms 367 -> 347, four
-// models on 16,000 atoms 1190 -> 1106, but 500 atoms 252 -> 275.
-constexpr int kEdgeWaves = 2048, kItemsPerWave = 8, kSpanMin = 64, kSpanMax = 1024, kSpanTable = 256;
-inline int32_t chunk_span(int64_t n_edges, int32_t most = kSpanMax)
+// Work item of the edge kernels by MLP (those on tables only cut a launch into its XCDs' shares at these places): the rows whose first edge
+// lies in one span of `span` edges.  A wavefront walks an item serially (about 5 us per 32 edges when little else runs), so the span is
+// taken from the edges of the launch: 8 items for each of the 2048 wavefronts that are resident at once (256 compute units, 8 wavefronts of
+// the reverse kernel on each), at most 1024 edges (longer items no longer pay for their pipeline fill, shorter ones do at a million atoms),
+// and at least two tiles of 32, or one where there are not even 1024 items of two.  Measured, us per pass of graph + energy + forces: 1024
+// edges throughout -> 8 items per wavefront 500 atoms 1587 -> 632, 108,000 atoms in 8 slabs 4732 -> 4233, a million unchanged (4 items 4302
+// and 2 items 4591 at 108,000); least span 32 -> 64 later 4,000 atoms 367 -> 347, four models on 16,000 atoms 1190 -> 1106, but 500 atoms
+// 252 -> 275.
+constexpr int kEdgeWaves = 2048, kItemsPerWave = 8, kSpanMin = 64, kSpanMax = 1024;
+inline int32_t chunk_span(int64_t n_edges)
 {
     const int64_t even = n_edges / (kEdgeWaves * kItemsPerWave), least = n_edges < 1024 * kSpanMin ? kSpanMin / 2 : kSpanMin;
-    return (int32_t)(even < least ? least : even > most ? most : even);
+    return (int32_t)(even < least ? least : even > kSpanMax ? kSpanMax : even);
 }
 inline int64_t chunks_of(int64_t n_edges, int32_t span) { return n_edges > 0 ? (n_edges + span - 1) / span : 1; }
 
@@ -271,9 +271,9 @@ int forward_impl(mlip_graph *g, const mlip_weights_t *w, int32_t mode, double *e
 int unpack_shifts(const mlip_graph *g, int32_t *out);
 // bond list of one partition for cutoff r_bond (kept until the graph is rebuilt or r_bond changes); synchronises
 int build_bonds_impl(mlip_graph *g, SlabView &v, double r_bond, int p_envelope);
-// Upper / lower split of the views' owned-row edges (PairGraph), all views in the same launches; does nothing if all are valid.  With a block to carve from,
-// the arrays are taken from it (and the caller invalidates the structure when the block is given up).
-// gate != nullptr: the lists are made only if *gate != 0 when the kernels run.  launch = false: only their place is taken.
+// Upper / lower split of the views' owned-row edges (PairGraph), all views in the same launches; does nothing if all are valid.  With a
+// block to carve from, the arrays are taken from it (and the caller invalidates the structure when the block is given up). gate != nullptr:
+// the lists are made only if *gate != 0 when the kernels run.  launch = false: only their place is taken.
 int build_pairs_impl(mlip_graph *g, SlabView *views, int n_views, Carver *scratch, const int32_t *gate = nullptr, bool launch = true);
 int forward_bonds_impl(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t *bw, int32_t mode,
                        double *energy, float *forces, float *atom_energy);

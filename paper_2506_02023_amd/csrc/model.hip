@@ -179,7 +179,7 @@ template <int F, int PREC> int launch_edge(mlip_graph *g, EdgeBatch &b, bool bac
     }
     b.work = g->work_ptr + (size_t)g->work_next * (8 * kWorkCounterStride);
     b.chunk_start[0] = 0;
-    for (int q = 0; q < b.n; ++q) b.chunk_start[q + 1] = b.chunk_start[q] + (b.s[q].n_rows > 0 ? (b.s[q].n_chunks + b.c.group - 1) / b.c.group : 0);
+    for (int q = 0; q < b.n; ++q) b.chunk_start[q + 1] = b.chunk_start[q] + (b.s[q].n_rows > 0 ? b.s[q].n_chunks : 0);
     for (int q = b.n; q < kBatch; ++q) b.chunk_start[q + 1] = b.chunk_start[b.n];
     const int64_t items = b.chunk_start[b.n];
     if (items <= 0) return MLIP_OK;
@@ -693,9 +693,6 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
                 eb.c.A2t = base + pk.W2t;
                 eb.c.bp = bp;
                 eb.c.gate = gate;
-                int64_t n_edges = 0;
-                for (int q = 0; q < eb.n; ++q) n_edges += views[p0 + q].n_edges_owned;
-                eb.c.group = std::max(1, chunk_span(n_edges) / std::max(1, views[p0].span));   // longer items pay for their pipeline fill
                 for (int q = 0; q < eb.n; ++q) {
                     SlabView &v = views[p0 + q];
                     EdgeArgs &ea = eb.s[q];
@@ -788,7 +785,6 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
                 eb.c.need_gbar = need_gbar ? 1 : 0;
                 eb.c.first = (l == L - 1) ? 1 : 0;
                 eb.c.gate = gate;
-                eb.c.group = 1;
                 for (int q = 0; q < eb.n; ++q) {
                     SlabView &v = views[p0 + q];
                     EdgeArgs &ea = eb.s[q];

@@ -31,7 +31,6 @@ struct EdgeCommon {
     const float *A1, *A1s, *A2t, *A2n;   // A1s = c W1, A2t = W2 / c (see kSiluScale), A1 and A2n unscaled
     BasisParams bp;
     int need_gbar, first;
-    int group;             // chunks of rows per work item
     const int32_t *gate;   // != null: the launch runs only if *gate != 0 (the filters are not represented by tables)
 };
 
@@ -109,13 +108,12 @@ __device__ inline int32_t uniform_load(const int32_t *p, int64_t i)
     return reinterpret_cast<const_i32_ptr>(reinterpret_cast<uintptr_t>(p))[i];
 }
 
-// wavefront work item: the rows whose first edge lies in [item * group * span, (item + 1) * group * span)
-__device__ inline bool chunk_rows(const EdgeArgs &A, int64_t item, int group, int64_t &r0, int64_t &r1)
+// wavefront work item: the rows whose first edge lies in [chunk * span, (chunk + 1) * span)
+__device__ inline bool chunk_rows(const EdgeArgs &A, int64_t chunk, int64_t &r0, int64_t &r1)
 {
-    const int64_t end = min((item + 1) * group, A.n_chunks);
-    r0 = uniform_load(A.chunk_row, item * group);
-    r1 = uniform_load(A.chunk_row, end);
-    if (end == A.n_chunks) r1 = A.n_rows;   // the forward step stops at the owned rows
+    r0 = uniform_load(A.chunk_row, chunk);
+    r1 = uniform_load(A.chunk_row, chunk + 1);
+    if (chunk == A.n_chunks - 1) r1 = A.n_rows;   // the forward step stops at the owned rows
     return r0 < r1;
 }
 
@@ -194,7 +192,7 @@ __global__ void __launch_bounds__(kFwdWaves * 64, 3) k_edge_fwd(EdgeBatch B)
     drawn = items.draw(lane);
     const int64_t chunk = item - B.chunk_start[part];
     int64_t r0, r1;
-    if (!chunk_rows(A, chunk, C.group, r0, r1)) continue;
+    if (!chunk_rows(A, chunk, r0, r1)) continue;
     // wave-uniform values loaded through vector instructions: keep them scalar (edge indices fit 32 bits)
     const int32_t e_lo = __builtin_amdgcn_readfirstlane((int32_t)A.row_ptr[r0]);
     const int32_t e_hi = __builtin_amdgcn_readfirstlane((int32_t)A.row_ptr[r1]);
@@ -533,7 +531,7 @@ __global__ void __launch_bounds__(kBwdWaves * 64, kBwdWaves == 4 ? 2 : 1) k_edge
         drawn = items.draw(lane);
         const int64_t chunk = item - B.chunk_start[part];
         int64_t r0_, r1_;
-        if (!chunk_rows(A, chunk, C.group, r0_, r1_)) continue;
+        if (!chunk_rows(A, chunk, r0_, r1_)) continue;
         const int32_t r0 = (int32_t)r0_;
         r1 = (int32_t)r1_;
         const int32_t e_lo = __builtin_amdgcn_readfirstlane((int32_t)A.row_ptr[r0]);   // wave-uniform: keep them scalar

@@ -9,12 +9,12 @@
 
 // ---------------------------------------------------------------- the table
 //
-// kTabN intervals over [0, rc], degree 5 in the local coordinate s in [-1, 1], fp32 coefficients computed in fp64.  In units of rc / kTabUnits the intervals have
-// the length 1/2 below kTabSmall (at short distances the basis functions are large and SiLU bends most), 1/4 from kTabEnd on (at
-// the cutoff the filter vanishes with its first three derivatives, so its error has to vanish too) and 1 between.
-// What is cut off is below what the rounding of the length to fp32 makes (checked when the table is made, see k_filter_table); coefficients
-// and evaluation round to 4e-8 (values) and 5e-8 (slopes) of the filter, the fp32 evaluation of the MLP to 1.7e-7 of both.
-// One block of 32 features is 768 bytes per interval, [3][16][2][2]: coefficients 2 q and 2 q + 1 of features l and l + 16, 16 bytes for one lane; 162,816
+// kTabN intervals over [0, rc], degree 5 in the local coordinate s in [-1, 1], fp32 coefficients computed in fp64.  In units of rc /
+// kTabUnits the intervals have the length 1/2 below kTabSmall (at short distances the basis functions are large and SiLU bends most), 1/4
+// from kTabEnd on (at the cutoff the filter vanishes with its first three derivatives, so its error has to vanish too) and 1 between. What
+// is cut off is below what the rounding of the length to fp32 makes (checked when the table is made, see k_filter_table); coefficients and
+// evaluation round to 4e-8 (values) and 5e-8 (slopes) of the filter, the fp32 evaluation of the MLP to 1.7e-7 of both. One block of 32
+// features is 768 bytes per interval, [3][16][2][2]: coefficients 2 q and 2 q + 1 of features l and l + 16, 16 bytes for one lane; 162,816
 // bytes of the compute unit's 160 KB.  With F = 64 every block of the grid holds the table of one half of the features.
 constexpr int kTabUnits = 179, kTabSmall = 27, kTabEnd = kTabUnits - 2;
 constexpr int kTabM0 = 2 * kTabSmall, kTabE0 = kTabM0 + kTabEnd - kTabSmall, kTabN = kTabE0 + 4 * (kTabUnits - kTabEnd);
@@ -268,8 +268,8 @@ __device__ inline __amdgpu_buffer_rsrc_t tab_buffer(const void *p, uint32_t n)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)n, kBufferFlags);
 }
-// The lane's two features, l and l + 16: 64 bytes of 16 lanes at a time.  (Features 2 l and 2 l + 1 as 8 bytes of a lane: twice the cache accesses for the
-// same rows, and the address unit busy for 82 % of the forward step.)
+// The lane's two features, l and l + 16: 64 bytes of 16 lanes at a time.  (Features 2 l and 2 l + 1 as 8 bytes of a lane: twice the cache
+// accesses for the same rows, and the address unit busy for 82 % of the forward step.)
 __device__ inline f32x2 buffer_load_2(__amdgpu_buffer_rsrc_t r, uint32_t off)
 {
     return f32x2{buffer_load_f32(r, off, 0, 0), buffer_load_f32(r, off + 64, 0, 0)};
@@ -282,11 +282,11 @@ __device__ inline void buffer_store_2(f32x2 v, __amdgpu_buffer_rsrc_t r, uint32_
 __device__ inline int32_t buffer_load_i32(__amdgpu_buffer_rsrc_t r, uint32_t off) { return (int32_t)__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0); }
 
 // Work items.  Every XCD takes a contiguous eighth of the launch's edges, cut at the rows where the graph's work-item tables (chunk_row)
-// have an entry (of a launch with about a row for a worker, where one partition after the other and a look at those tables would be most of its
-// time, 21 us for 8 x 192 rows, rows of one partition); the F / 32 blocks of features each go through all of it, on the same XCD.  The XCD's rows are dealt to its
-// blocks in turn, kTabDeal items at a time, so that at any moment they work on a short run of rows whose neighbourhoods share the L2; within
-// its block's share every worker starts at its own item and then draws from a counter in LDS.  (Draws from one counter per XCD in memory: one per 35 ns,
-// 140 us a launch at 32,000 rows.)
+// have an entry (of a launch with about a row for a worker, where one partition after the other and a look at those tables would be most of
+// its time, 21 us for 8 x 192 rows, rows of one partition); the F / 32 blocks of features each go through all of it, on the same XCD.  The
+// XCD's rows are dealt to its blocks in turn, kTabDeal items at a time, so that at any moment they work on a short run of rows whose
+// neighbourhoods share the L2; within its block's share every worker starts at its own item and then draws from a counter in LDS.  (Draws
+// from one counter per XCD in memory: one per 35 ns, 140 us a launch at 32,000 rows.)
 constexpr int kTabDeal = 8;
 static_assert(kTabDeal == 8, "tab_walk shifts by three");
 __device__ inline int32_t tab_cut(const TabArgs &A, int64_t edge)   // the row at which the partition is cut for its edge `edge`
@@ -335,7 +335,8 @@ __device__ __forceinline__ void tab_walk(const TabBatch &B, float *lds, int hb, 
                 lo = (int32_t)((int64_t)A.n_rows * (xcd - mine_from) / mine_n);
                 hi = (int32_t)((int64_t)A.n_rows * (xcd - mine_from + 1) / mine_n);
             } else {
-                // decided from the arguments alone, without a look at every partition's arrays; one without edges goes to the XCD of the edge behind it
+                // decided from the arguments alone, without a look at every partition's arrays; one without edges goes to the XCD of the
+                // edge behind it
                 const int64_t at = B.edge_start[part], end = B.edge_start[part + 1];
                 if (at < end ? at >= to || end <= from : at < from || at >= to) continue;
                 lo = tab_cut(A, from - at);
@@ -412,9 +413,9 @@ __device__ __forceinline__ void tab_walk(const TabBatch &B, float *lds, int hb, 
 }
 
 
-// Either step with the filters from the MLP itself, in fp32, a wavefront per row, lane = feature: what a launch on tables does when the tables turn out
-// not to represent the filters and nothing else was launched (the call after the first one that learns it takes the MLP's own
-// kernels).  Correct at any size, several times slower than those.
+// Either step with the filters from the MLP itself, in fp32, a wavefront per row, lane = feature: what a launch on tables does when the
+// tables turn out not to represent the filters and nothing else was launched (the call after the first one that learns it takes the MLP's
+// own kernels).  Correct at any size, several times slower than those.
 template <int F, int NW, bool BWD, bool GBAR> __device__ __forceinline__ void tab_exact(const TabBatch &B, float *lds)
 {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, f = lane & (F - 1);
