@@ -15,9 +15,12 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-# The products run on the bf16 / fp16 matrix pipeline (2.5 PFLOP/s dense): an fp32 product as the six terms of operands in
-# three bf16 parts, a split-fp16 one as three.  The precision mode applies to the F x F products; those with the K = 8 basis
-# functions are fp32 in every mode.  A kernel's peak is that of the pipeline by the terms it executes per counted flop.
+# The radial edge kernels look the filters up in tables (k_edge_fwd_tab, k_edge_bwd_tab) and run on the vector unit:
+# their peak is PEAK_FP32_VECTOR_TFLOPS.  With weights that the tables do not represent they evaluate the filter MLP
+# (k_edge_fwd, k_edge_bwd, k_edge_lower): these products run on the bf16 / fp16 matrix pipeline (2.5 PFLOP/s dense), an
+# fp32 product as the six terms of operands in three bf16 parts, a split-fp16 one as three.  The precision mode applies
+# to the F x F products; those with the K = 8 basis functions are fp32 in every mode.  A kernel's peak is that of the
+# pipeline by the terms it executes per counted flop.
 PEAK_MFMA16_TFLOPS = 2500.0
 PRODUCT_TERMS = {"f32": 6, "f32split": 3, "bf16": 1}
 BASIS_TERMS = 6
@@ -53,14 +56,25 @@ def flops_bwd_edge(F, K=8):
     return flops_bwd_edge_as_defined(F, K) // 2
 
 
+# Executed on tables per directed edge, layer and feature: forward five multiply-adds for the filter value and one into the
+# row's sum; reverse value and slope (nine), the sum, and slope x g_i x abar_j into the edge's sum (3).  Reverse of layer
+# 0: slope only (eight) and the latter.
+def flops_fwd_tab(F):
+    return 12 * F
+
+
+def flops_bwd_tab(F, L):
+    """Mean over the layers."""
+    return F * (23 * (L - 1) + 19) / L
+
+
 # HBM bytes per launch (one layer over all 8 slabs) on the default workload, from rocprofv3 --pmc FETCH_SIZE and
 # WRITE_SIZE (profiles/edge_traffic_configs3_8slabs.md): KiB x copy-kernel scale (1.9976 for FETCH_SIZE, 1.000 for
 # WRITE_SIZE)
 TRAFFIC_SOURCE = ("profiled constant, not measured by this run: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of this kernel on "
                   "this workload, profiles/edge_traffic_configs3_8slabs.md")
-TRAFFIC_BWD_LAUNCH_BYTES = (6232198 * 1.9976 + 1002206) * 1024         # k_edge_bwd on the upper-edge graphs
-TRAFFIC_FWD_LAUNCH_BYTES = (3108844 * 1.9976 + 4329365) * 1024         # k_edge_fwd on the full edge lists
-TRAFFIC_BWD_LOWER_LAUNCH_BYTES = (3861533 * 1.9976 + 250047) * 1024    # k_edge_lower
+TRAFFIC_BWD_LAUNCH_BYTES = (1966894 * 1.9976 + 1173831) * 1024   # k_edge_bwd_tab, mean of the three layers
+TRAFFIC_FWD_LAUNCH_BYTES = (786371 * 1.9976 + 250047) * 1024     # k_edge_fwd_tab
 
 
 # fp32 vector peak that applies to this build: 256 CUs x 4 SIMDs x 16 lanes x 2 flop per FMA x 2.4 GHz = 78.6 TFLOP/s.
@@ -198,6 +212,21 @@ def main():
     L = c["L"]
     default_workload = args.config == 3 and args.cells is None and args.precision == "f32"   # what the traffic constants were profiled on
 
+    # The reverse step has a second pass only with the filters from the MLP (with bonds always, for their terms; the seeded
+    # weights of that workload are represented by tables too).
+    on_tables = three_body or prof["edge_bwd_lower"][1] == 0
+
+    def table_roofline(group, kernel, flops_edge, as_defined, traffic):
+        ms, n = prof[group]
+        avg_ms = ms / max(n, 1)
+        rate = E * L * args.steps / (ms * 1e-3) / 1e12 if ms > 0 else 0.0   # T edges and layers / s
+        return {"kernel": kernel, "bound": "alu", "achieved": rate * flops_edge, "peak": PEAK_FP32_VECTOR_TFLOPS, "unit": "TFLOP/s",
+                "frac": rate * flops_edge / PEAK_FP32_VECTOR_TFLOPS, "traffic": traffic if default_workload else None,
+                "traffic_source": TRAFFIC_SOURCE if default_workload else None, "avg_launch_ms": avg_ms, "launches": int(n),
+                "flops_per_launch": E * flops_edge * L * args.steps / max(n, 1), "ms_per_step": ms / args.steps,
+                "as_defined_tflops": rate * as_defined, "flops_per_edge_layer": {"executed": flops_edge, "as_defined": as_defined},
+                "note": "filters from tables: no filter MLP per edge; peak: fp32 vector unit without packed instructions"}
+
     def edge_roofline(group, kernel, flops_edge, n_basis, traffic, as_defined=None):
         ms, n = prof[group]
         per_launch = E * flops_edge * L * args.steps / max(n, 1)
@@ -217,10 +246,16 @@ def main():
         return r
 
     F = c["F"]
-    roof_bwd = edge_roofline("edge_bwd", f"k_edge_bwd<{F}> (reverse edge step)", flops_bwd_edge(F), 2,
-                             TRAFFIC_BWD_LAUNCH_BYTES, flops_bwd_edge_as_defined(F))
-    roof_fwd = edge_roofline("edge_fwd", f"k_edge_fwd<{F}> (forward edge step)", flops_fwd_edge(F), 1, TRAFFIC_FWD_LAUNCH_BYTES)
-    if prof["edge_bwd_lower"][1] > 0:   # the reverse operation as defined takes both of its passes
+    if on_tables:
+        roof_bwd = table_roofline("edge_bwd", f"k_edge_bwd_tab<{F}> (reverse edge step)", flops_bwd_tab(F, L),
+                                  flops_bwd_edge_as_defined(F), TRAFFIC_BWD_LAUNCH_BYTES)
+        roof_fwd = table_roofline("edge_fwd", f"k_edge_fwd_tab<{F}> (forward edge step)", flops_fwd_tab(F), flops_fwd_edge(F),
+                                  TRAFFIC_FWD_LAUNCH_BYTES)
+    else:
+        roof_bwd = edge_roofline("edge_bwd", f"k_edge_bwd<{F}> (reverse edge step)", flops_bwd_edge(F), 2, None,
+                                 flops_bwd_edge_as_defined(F))
+        roof_fwd = edge_roofline("edge_fwd", f"k_edge_fwd<{F}> (forward edge step)", flops_fwd_edge(F), 1, None)
+        # the reverse operation as defined takes both of its passes
         both_ms = prof["edge_bwd"][0] + prof["edge_bwd_lower"][0]
         roof_bwd["kernel"] = f"k_edge_bwd<{F}> on the upper-edge graphs (reverse edge step, first pass)"
         roof_bwd["as_defined_tflops"] = E * flops_bwd_edge_as_defined(F) * L * args.steps / (both_ms * 1e-3) / 1e12
@@ -228,16 +263,15 @@ def main():
     roof = roof_fwd if roof_fwd["ms_per_step"] >= roof_bwd["ms_per_step"] else roof_bwd   # the dominant kernel
     roof_lower = {}
     ms, n = prof["edge_bwd_lower"]
-    if n > 0:   # bound by its row traffic; compulsory bytes: per lower edge the kept filter values (read once), per
-                # atom the row that is gathered (once if the caches were perfect) and the sum (read, written)
+    if n > 0 and not on_tables:   # bound by its row traffic; compulsory bytes: per lower edge the kept filter values (read once),
+                # per atom the row that is gathered (once if the caches were perfect) and the sum (read, written)
         per_launch = E / 2 * F * 4 + N * 3 * F * 4
         avg_ms = ms / n
         ach = per_launch / (avg_ms * 1e-3) / 1e9 if avg_ms > 0 else 0.0
         roof_lower["edge_bwd_lower"] = {"kernel": f"k_edge_lower<{F}> (reverse edge step, second pass: lower edges)",
                                         "bound": "hbm", "achieved": ach, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                                         "frac": ach / PEAK_HBM_GBS,
-                                        "traffic": TRAFFIC_BWD_LOWER_LAUNCH_BYTES if default_workload else None,
-                                        "traffic_source": TRAFFIC_SOURCE if default_workload else None,
+                                        "traffic": None, "traffic_source": None,
                                         "avg_launch_ms": avg_ms, "launches": int(n),
                                         "bytes_per_launch": per_launch, "ms_per_step": ms / args.steps}
     roof_trip = {}
@@ -263,8 +297,8 @@ def main():
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms_step, "ms_per_step_min": per_step[0],
         "ms_per_step_median": per_step[len(per_step) // 2], "higher_is_better": True,
         "scaling": "weak", "vs_baseline": None,
-        "dtype": {"f32": "f32", "bf16": "f32 with bf16 operands in the filter MLP's F x F products",
-                  "f32split": "f32, the filter MLP's F x F products as split-fp16 MFMA triples"}[args.precision],
+        "dtype": {"f32": "f32", "bf16": "f32 with W2 of the filter MLP and the bond MLPs' F x F products in bf16",
+                  "f32split": "f32 (split-fp16 products where the filter MLP is evaluated per edge)"}[args.precision],
         "data": "synthetic",
         "config": {"workload": c["name"] + f", {N} atoms, {E} directed edges, r_cut 5.0, F={c['F']} L={L} K=8, "
                                + (f"three-body variant (bonds within {c['r_bond']}), graph build + whole-graph energy+forces"
@@ -282,8 +316,8 @@ def main():
     if split_ms is not None:
         res["split_fp16_products"] = {"ms_per_step": split_ms, "value": N / (split_ms * 1e-3), "unit": "atoms/s",
                                       "energy": energy_split,
-                                      "note": "MLIP_PRECISION_FP32_SPLIT: same step, W2 products as three fp16 MFMA products "
-                                              "of split operands; held to the fp32 bounds by the parity tests"}
+                                      "note": "MLIP_PRECISION_FP32_SPLIT: same step; on filter tables the fp32 mode's own, otherwise "
+                                              "W2 products as three fp16 MFMA products of split operands"}
     if whole_ms is not None:
         res["whole_graph"] = {"ms_per_step": whole_ms, "value": N / (whole_ms * 1e-3), "unit": "atoms/s",
                               "energy": energy_whole, "rel_energy_difference_to_slabs": abs(energy_whole - energy) / abs(energy),

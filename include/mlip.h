@@ -50,6 +50,10 @@ typedef enum {
 
 enum { MLIP_MODE_WHOLE = 0, MLIP_MODE_SLABS = 1 };
 /*
+ * Filters: w_e = MLP(basis(d_e)) is a function of the edge length alone.  A model's filters are tabulated on the device
+ * (piecewise polynomials made in fp64, kept and evaluated in fp32), checked there against what fp32 rounding of the length
+ * makes, and looked up per edge; weights whose filters the tables do not represent take the MLP per edge.
+ *
  * MLIP_PRECISION_FP32: everything from the basis on in fp32 (products as exact sums of three bf16 parts per operand on the
  *   bf16 matrix units, all terms down to 2^-24, accumulated in fp32).  An operand beyond the bf16 range (3.39e38; fp32 ends
  *   at 3.40e38) or infinite makes its row of the product NaN, as it does in the fp32 products of the other modes: a result
@@ -58,13 +62,13 @@ enum { MLIP_MODE_WHOLE = 0, MLIP_MODE_SLABS = 1 };
  *   take bf16 operands with fp32 accumulation (benchmark configuration 4: "edge MLPs in bf16 with fp32
  *   accumulation"), and in mlip_forward_bonds the F x F products of the bond MLPs as well; everything else stays
  *   fp32 (arrays, the K = 8 products, activations, sums).  Forces then agree with the fp64 result to about
- *   4e-3 max|F|.
+ *   4e-3 max|F|.  Tables are made from W2 rounded to bf16 and from activations that are not rounded.
  * MLIP_PRECISION_FP32_SPLIT: the same products (the bond MLPs' included) with every operand split into two fp16 parts (hi + lo, 22
  *   significant bits) and taken as three fp16 MFMA products with fp32 accumulation.  The results meet the fp32
  *   mode's bounds (the dropped terms are of the size of fp32 accumulation rounding) in a fraction of the matrix
  *   time; the operands of those products - SiLU outputs and the products abar * g of the reverse pass - must
  *   stay below the fp16 range (65504), which holds for any physical input but is not checked: a value beyond it
- *   becomes infinite in the split and the energy and forces come out non-finite.
+ *   becomes infinite in the split and the energy and forces come out non-finite.  On tables the mode is the fp32 one.
  */
 enum { MLIP_PRECISION_FP32 = 0, MLIP_PRECISION_BF16 = 1, MLIP_PRECISION_FP32_SPLIT = 2 };
 
@@ -211,8 +215,9 @@ int mlip_graph_skin_stats(const mlip_graph_t *graph, int64_t *list_builds, int64
  * Asynchronous on the graph's stream; does not modify the graph's topology (it uses
  * workspace owned by the handle, so two forwards on one handle must not overlap).
  *
- * The weights are re-laid-out for the matrix units on the first call and kept in the handle: a later call whose
- * mlip_weights_t (pointers, dimensions, precision) is identical reuses them.  After changing weight VALUES in
+ * The weights are re-laid-out for the matrix units and the filters tabulated (0.17 MB per layer and 32 features) on the
+ * first call and kept in the handle: a later call whose mlip_weights_t (pointers, dimensions, precision) and graph cutoff
+ * are identical reuses them.  After changing weight VALUES in
  * place, or when another model's arrays have come to lie at the same addresses, call mlip_graph_invalidate_weights.
  */
 int mlip_forward(mlip_graph_t *graph, const mlip_weights_t *weights, int32_t mode,
@@ -223,14 +228,15 @@ int mlip_forward(mlip_graph_t *graph, const mlip_weights_t *weights, int32_t mod
  * loops, harnesses that forbid hipMalloc.  Same arguments, results and error codes as mlip_forward, but every
  * piece of workspace (node features and their gradients, kept filter values, per-edge accumulators, packed
  * weights, energy partial sums) is carved from one fixed device array inside the library of
- * mlip_static_scratch_bytes() = 64 MiB per GPU, held until the process ends; the call allocates and frees
+ * mlip_static_scratch_bytes() = 64 MiB per GPU (beside it 2.6 MB for the filter tables), held until the process ends; the
+ * call allocates and frees
  * nothing and clears what must start at zero with fill kernels.  A graph and model whose workspace
  * (about n_local (4 + 2 L) F 4 + n_edges (36 + (L - 1) F 2) bytes summed over the partitions of the mode - the kept
  * filter values take one row per edge pair and layer, the lists of the pairs' edges are rebuilt in the array on
  * every call - plus the packed weights) exceeds the array are rejected with MLIP_EINVAL; with the event profiler enabled the call
  * returns MLIP_ESTATE.  All calls on one GPU, from any handle, share the array and find the previous call's
  * contents in it: calls that overlap on one GPU (two streams, two threads) race and must be serialised by the
- * caller.  Weights are packed on every call (nothing is cached in the shared array).  The graph itself must
+ * caller.  Weights are packed and filters tabulated on every call (nothing is cached in the shared array).  The graph itself must
  * have been built before (mlip_build_graph allocates).
  */
 int mlip_forward_static(mlip_graph_t *graph, const mlip_weights_t *weights, int32_t mode,
@@ -276,7 +282,7 @@ int mlip_graph_bonds(const mlip_graph_t *graph, int32_t p, const int32_t **bond_
 
 /*
  * Upper / lower split of the edges of partition p's owned rows (p = -1: of the whole graph), the form in which the
- * reverse edge kernels walk them.  The filter of the radial message-passing layer is a function of the edge length
+ * reverse edge kernels that evaluate the filter MLP walk them.  The filter of the radial message-passing layer is a function of the edge length
  * alone (benchmark description: w_e = MLP(basis(d_e))), and the two edges of an edge / reverse-edge pair have the
  * same length, so its values are kept for one of them, the "upper" one: the edge whose reverse edge lies at a
  * larger index of the partition's edge list.  (An edge from a ghost sender is always upper: its reverse edge is in
@@ -287,7 +293,8 @@ int mlip_graph_bonds(const mlip_graph_t *graph, int32_t p, const int32_t **bond_
  *   u_d [n_upper]             edge length
  *   l_row_ptr [n_owned + 1], l_senders [n_lower]   the same for the lower edges
  *   l_slot [n_lower]          index of the pair's upper edge in the upper-edge lists
- * Built on the handle's stream on first use after a graph build (mlip_forward does the same); n_upper and n_lower
+ * Built on the handle's stream on first use after a graph build (mlip_forward does the same unless it looks the filters up
+ * in tables); n_upper and n_lower
  * are HOST values.  Errors: MLIP_ESTATE without a graph, MLIP_EINVAL for a partition index out of range.
  */
 typedef struct {
@@ -366,8 +373,8 @@ enum {
     MLIP_PROF_TRIPLET_FWD = 7,   /* three-body variant: the triplet sum           */
     MLIP_PROF_TRIPLET_BWD = 8,   /* three-body variant: its reverse               */
     MLIP_PROF_EDGE_FWD_LOWER = 9,  /* no launches: the forward edge step is one pass over the full edge list */
-    MLIP_PROF_EDGE_BWD_LOWER = 10, /* reverse edge step, second pass: the lower edges' share of the projected rows' gradients, from
-                                     the kept filter values; in the three-body variant the bonds' share too */
+    MLIP_PROF_EDGE_BWD_LOWER = 10, /* reverse edge step, second pass (none on filter tables): the lower edges' share of the projected rows'
+                                     gradients, from the kept filter values; in the three-body variant the bonds' share, always */
     MLIP_PROF_COUNT = 11
 };
 int mlip_profile_enable(mlip_graph_t *graph, int32_t on);
