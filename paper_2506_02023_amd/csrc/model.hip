@@ -287,7 +287,10 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         g->packed_w_valid = false;
         PackBatch pb{};
         pb.F = F;
-        pb.clear = L > 0 ? &tab_state->bad : nullptr;
+        if (L > 0) {
+            pb.clear = &tab_state->bad;
+            pb.n_clear = kTabHeader / 4;
+        }
         const size_t ff = (size_t)F * F;   // floats of a weight matrix
         for (int l = 0; l < L; ++l) {
             float *base = wp + pk.per_layer * l;

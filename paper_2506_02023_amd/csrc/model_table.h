@@ -21,14 +21,15 @@ constexpr int kTabM0 = 2 * kTabSmall, kTabE0 = kTabM0 + kTabEnd - kTabSmall, kTa
 constexpr int kTabStride = 32 * 6 * 4;                   // bytes of an interval
 constexpr int kTabFloats = kTabN * kTabStride / 4;       // floats of one block of 32 features
 constexpr int kTabLds = kTabFloats * 4 + 32;             // the table and a work counter per partition of the launch
-constexpr int kTabHeader = 256;                          // bytes in front of the first table: TabState
+constexpr int kTabCounters = 16;                         // counters of k_filter_table's blocks, each on a cache line of its own
+constexpr int kTabHeader = 256 + 128 * kTabCounters;     // bytes in front of the first table: TabState, then those counters
 constexpr int kTabNodes = 8;                             // Chebyshev nodes of an interval: coefficients 0..7, 6 and 7 measure what is cut off
 static_assert(kTabLds <= 160 * 1024, "the table has to fit a compute unit's LDS");
 
 // Whether the tables of a model represent its filters, and the handshake that tells the host.
 struct TabState {
     int32_t bad;       // an interval of some layer is not represented: the edge steps may not use the tables
-    int32_t done;      // blocks of k_filter_table that are through, plus kTabBad for every one that found its interval bad
+    int32_t done;      // counters that are through, plus kTabBad for every one with a bad interval
 };
 
 constexpr int32_t kTabBad = 1 << 16;
@@ -55,12 +56,13 @@ __constant__ const double kCosTab[32] = {
     0.83146961230254523708, 0.92387953251128675613, 0.98078528040323044913};
 
 // One block per interval and layer, one wavefront per Chebyshev node, lane = feature; everything in fp64.  Bound by the latency
-// of one chain of loads, an exponential and 64 multiply-adds; W2 is requested before the chain.
+// of one chain of loads, an exponential and 64 multiply-adds; W2 is requested before the chain and converted once, on its way to LDS
+// (per use: F = 64, L = 3 19.2 us, so 15.3; with the blocks' count spread over addresses 12.9; F = 32, L = 2 12.2, 10.7 and 8.2).
 template <int F>
 __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
 {
     __shared__ double sv[kTabNodes][64], wv[kTabNodes][64];
-    __shared__ float W2[F * F];
+    __shared__ double W2[F * F];
     const int iv = blockIdx.x, layer = blockIdx.y;
     const int node = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, f = lane & (F - 1);
     const double lo = iv < kTabM0 ? 0.5 * iv : iv < kTabE0 ? kTabSmall + (iv - kTabM0) : kTabEnd + 0.25 * (iv - kTabE0);
@@ -90,15 +92,13 @@ __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
         sv[node][lane] = t / (1.0 + exp(-t));
     }
 #pragma unroll
-    for (int i = 0; i < F * F / (kTabNodes * 64); ++i) W2[i * kTabNodes * 64 + threadIdx.x] = w2[i];
+    for (int i = 0; i < F * F / (kTabNodes * 64); ++i)
+        W2[i * kTabNodes * 64 + threadIdx.x] = J.bf16 ? (double)(float)(__bf16)(w2[i] * kSiluScaleInv) / kSiluScaleInv : (double)w2[i];
     __syncthreads();
     {   // w_f = sum_k s_k W2[k][f]
         double w = 0;
 #pragma unroll 16
-        for (int k = 0; k < F; ++k) {
-            const float v = W2[k * F + f];
-            w = fma(sv[node][k], J.bf16 ? (double)(float)(__bf16)(v * kSiluScaleInv) / kSiluScaleInv : (double)v, w);
-        }
+        for (int k = 0; k < F; ++k) w = fma(sv[node][k], W2[k * F + f], w);
         wv[node][lane] = w;
     }
     __syncthreads();
@@ -142,10 +142,17 @@ __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
     if (lane == 0) {
         const bool bad = !(ew <= sw && ed <= sd);   // (not a number: not represented)
         if (bad) J.state->bad = 1;
-        // one word counts the blocks and the bad ones among them, so that the last one needs no fence to know
-        const int32_t now = 1 + (bad ? kTabBad : 0) +
-                            __hip_atomic_fetch_add(&J.state->done, 1 + (bad ? kTabBad : 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (now % kTabBad == (int32_t)(gridDim.x * gridDim.y))
+        // A word counts blocks and the bad ones among them, so that the last one needs no fence to know.  The blocks are spread over
+        // kTabCounters of them, whose last ones go on to state->done: some 20 ns per addition to one address made up most of the launch.
+        auto count = [](int32_t *word, bool is_bad) {
+            const int32_t add = 1 + (is_bad ? kTabBad : 0);
+            return add + __hip_atomic_fetch_add(word, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        };
+        const int c = iv % kTabCounters;
+        int32_t now = count(reinterpret_cast<int32_t *>(J.state) + 64 + 32 * c, bad);
+        if (now % kTabBad != ((kTabN - 1 - c) / kTabCounters + 1) * (int32_t)gridDim.y) return;
+        now = count(&J.state->done, now >= kTabBad);
+        if (now % kTabBad == kTabCounters)
             __hip_atomic_store(J.publish, J.generation * 2 + (now >= kTabBad ? 1 : 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }

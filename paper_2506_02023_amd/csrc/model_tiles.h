@@ -178,7 +178,8 @@ struct PackJob {
 constexpr int kPackJobs = 66;   // 8 layers x 8 packs and the readout's two; the bond part has 6 + 2 x 8 + 2
 struct PackBatch {
     int n, F;
-    int32_t *clear;   // null, or two words to clear
+    int32_t *clear;   // words to clear
+    int n_clear;
     PackJob job[kPackJobs];
     void add(const float *W, float *out, int kind, int trans, float scale) { job[n++] = PackJob{W, out, scale, (int16_t)kind, (int16_t)trans}; }
 };
@@ -186,7 +187,8 @@ struct PackBatch {
 __global__ void k_pack(PackBatch B)
 {
     const PackJob &J = B.job[blockIdx.y];
-    if (B.clear && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 2) B.clear[threadIdx.x] = 0;
+    if (blockIdx.x == 0 && blockIdx.y == 0)
+        for (int i = threadIdx.x; i < B.n_clear; i += blockDim.x) B.clear[i] = 0;
     const int F = B.F, NB = F / 32;
     const float *__restrict__ W = J.W;
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
