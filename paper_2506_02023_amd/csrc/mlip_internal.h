@@ -249,7 +249,6 @@ struct mlip_graph {
     mlip::DevBuf tables;
     int64_t table_generation = 0, kept_generation = 0;   // of the tables made last (the static variant's among them), of those in the handle
     double table_rcut = 0.0;  // the cutoff they were made for
-    bool table_good = false, table_failed = false;   // whether a model's tables have represented its filters / ever did not, as far as the host has heard
     mlip::DevBuf bond_wpack;  // packed weights of the three-body variant's bond part
     mutable bool tail = false;   // the last build's final kernels (edge arrays, reverse edges) may still run
     void *pinned = nullptr;  // pinned host area in which kernels leave counts and flags for the host

@@ -79,7 +79,7 @@ constexpr int kNodeBlocks = 256;   // one per compute unit (512: 38 us against 2
 template <int F> struct Lds {
     using D = Dims<F>;
     static constexpr size_t edge_fwd(int prec) { return sizeof(float) * (pack_floats<F>(prec) + D::PACK1 + kFwdWaves * D::TILE); }
-    static constexpr size_t edge_bwd(int prec) { return sizeof(float) * (pack_floats<F>(prec) + D::PACK1 + kBwdWaves * kQueue * D::FS); }
+    static constexpr size_t edge_bwd(int prec, int waves) { return sizeof(float) * (pack_floats<F>(prec) + D::PACK1 + waves * kQueue * D::FS); }
 };
 
 // Dynamic LDS size of a kernel, set once per handle (a handle lives on one device and is used by one thread at a
@@ -153,26 +153,21 @@ template <int F, int OP, class Fill> int node_pass(mlip_graph *g, SlabView *view
 // Edge-kernel launches of one call: two per layer and batch of partitions (L <= 8, at most 64 / kBatch batches).
 constexpr int kWorkLaunches = 2 * 8 * (64 / kBatch);
 
-template <int F, int PREC> int launch_edge(mlip_graph *g, EdgeBatch &b, bool backward)
+int count_compute_units(mlip_graph *g)   // once per handle
 {
-    const size_t lds = backward ? Lds<F>::edge_bwd(PREC) : Lds<F>::edge_fwd(PREC);
-    const int threads = (backward ? kBwdWaves : kFwdWaves) * 64;
-    // resident blocks per compute unit, queried once per kernel and handle
-    const void *fn = backward ? reinterpret_cast<const void *>(&k_edge_bwd<F, PREC>) : reinterpret_cast<const void *>(&k_edge_fwd<F, PREC>);
-    int slot = 0;
-    MLIP_TRY(configure_kernel(g, fn, lds, &slot));
-    int occ = g->fn_occ[slot].second;
-    if (occ == 0) {
-        int dev = 0, o = 0;
-        MLIP_HIP(hipGetDevice(&dev));
-        MLIP_HIP(hipDeviceGetAttribute(&g->n_cu, hipDeviceAttributeMultiprocessorCount, dev));
-        MLIP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, fn, threads, lds));
-        if (o < 1 || g->n_cu < 8) {
-            set_error("edge kernel does not fit the device (occupancy %d, %d compute units)", o, g->n_cu);
-            return MLIP_EHIP;
-        }
-        occ = g->fn_occ[slot].second = o;
-    }
+    if (g->n_cu != 0) return MLIP_OK;
+    int dev = 0, n = 0;
+    MLIP_HIP(hipGetDevice(&dev));
+    MLIP_HIP(hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev));
+    if (n < 8) { set_error("%d compute units: the edge kernels take eighths of the device", n); return MLIP_EHIP; }
+    g->n_cu = n;
+    return MLIP_OK;
+}
+
+// Work items and counters of an edge step by MLP.
+int plan_edge(mlip_graph *g, EdgeBatch &b)
+{
+    MLIP_TRY(count_compute_units(g));
     if (g->work_next >= kWorkLaunches) {
         set_error("more than %d edge-kernel launches in one call", kWorkLaunches);
         return MLIP_ESTATE;
@@ -181,12 +176,33 @@ template <int F, int PREC> int launch_edge(mlip_graph *g, EdgeBatch &b, bool bac
     b.chunk_start[0] = 0;
     for (int q = 0; q < b.n; ++q) b.chunk_start[q + 1] = b.chunk_start[q] + (b.s[q].n_rows > 0 ? b.s[q].n_chunks : 0);
     for (int q = b.n; q < kBatch; ++q) b.chunk_start[q + 1] = b.chunk_start[b.n];
-    const int64_t items = b.chunk_start[b.n];
-    if (items <= 0) return MLIP_OK;
-    // persistent grid: what is resident at once, a multiple of the 8 XCDs, no more than the work needs
-    const int64_t resident = (int64_t)(g->n_cu / 8) * occ;
-    const int64_t needed = (items + 7) / 8;   // few items: one per block, so that they spread over the compute units
-    const unsigned blocks = (unsigned)(8 * std::max<int64_t>(1, std::min(resident, needed)));
+    return MLIP_OK;
+}
+
+// Blocks of a persistent launch on an XCD: what is resident at once, no more than the work needs (few items: one per block, so that they
+// spread over the compute units).
+int64_t edge_slots(const mlip_graph *g, const EdgeBatch &b, int occ)
+{
+    return std::min<int64_t>((int64_t)(g->n_cu / 8) * occ, (b.chunk_start[b.n] + 7) / 8);
+}
+
+template <int F, int PREC> int launch_edge(mlip_graph *g, EdgeBatch &b, bool backward)
+{
+    const size_t lds = backward ? Lds<F>::edge_bwd(PREC, kBwdWaves) : Lds<F>::edge_fwd(PREC);
+    const int threads = (backward ? kBwdWaves : kFwdWaves) * 64;
+    // resident blocks per compute unit, queried once per kernel and handle
+    const void *fn = backward ? reinterpret_cast<const void *>(&k_edge_bwd<F, PREC>) : reinterpret_cast<const void *>(&k_edge_fwd<F, PREC>);
+    int slot = 0;
+    MLIP_TRY(configure_kernel(g, fn, lds, &slot));
+    int occ = g->fn_occ[slot].second;
+    if (occ == 0) {
+        MLIP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, threads, lds));
+        if (occ < 1) { set_error("edge kernel does not fit the device"); return MLIP_EHIP; }
+        g->fn_occ[slot].second = occ;
+    }
+    MLIP_TRY(plan_edge(g, b));
+    const unsigned blocks = (unsigned)(8 * edge_slots(g, b, occ));
+    if (blocks == 0) return MLIP_OK;
     if (backward)
         k_edge_bwd<F, PREC><<<blocks, threads, lds, g->stream>>>(b);
     else
@@ -203,19 +219,11 @@ int64_t upper_edges(const SlabView &v)
     return (v.n_edges_owned - n_ghost_edges) / 2 + n_ghost_edges;
 }
 
-// Edge steps on tables, one launch for up to kBatch partitions: K is the forward kernel or one of the reverse ones.
-template <int F> int launch_edge_tab(mlip_graph *g, TabBatch &b, void (*kernel)(TabBatch), int waves)
+// Rows of an edge step on tables, split over the chip; blocks of `waves` wavefronts.
+template <int F> int plan_edge_tab(mlip_graph *g, TabBatch &b, int waves)
 {
     constexpr int NH = F / 32;   // blocks of 32 features, each with a table of its own
-    constexpr size_t lds = kTabLds;
-    const void *fn = reinterpret_cast<const void *>(kernel);
-    int slot = 0;
-    MLIP_TRY(configure_kernel(g, fn, lds, &slot));
-    if (g->n_cu == 0) {
-        int dev = 0;
-        MLIP_HIP(hipGetDevice(&dev));
-        MLIP_HIP(hipDeviceGetAttribute(&g->n_cu, hipDeviceAttributeMultiprocessorCount, dev));
-    }
+    MLIP_TRY(count_compute_units(g));
     // A few rows at a time, so that the rows all workers of an XCD are at, with their neighbours, stay in its L2 (a million atoms: 1.6 GB
     // fetched by a forward launch with two, 8.2 with 22; 1.10 ms with two, 1.12 with one or three, 1.22 with six); one where there
     // are not even eight items for every worker.
@@ -226,11 +234,42 @@ template <int F> int launch_edge_tab(mlip_graph *g, TabBatch &b, void (*kernel)(
     b.few = rows <= workers;
     b.edge_start[0] = 0;
     for (int q = 0; q < kBatch; ++q) b.edge_start[q + 1] = b.edge_start[q] + (q < b.n ? b.s[q].n_edges : 0);
-    if (rows <= 0) return MLIP_OK;
     // persistent grid: one block per compute unit (the table fills its LDS), fewer where there are not even kTabDeal items for each
     const int64_t items = (rows + b.rows - 1) / b.rows;
-    const int64_t slots = std::max<int64_t>(1, std::min<int64_t>(g->n_cu / 8 / NH, (items + 8 * kTabDeal - 1) / (8 * kTabDeal)));
-    kernel<<<(unsigned)(8 * NH * slots), waves * 64, lds, g->stream>>>(b);
+    b.slots = (int)std::max<int64_t>(rows > 0, std::min<int64_t>(g->n_cu / 8 / NH, (items + 8 * kTabDeal - 1) / (8 * kTabDeal)));
+    return MLIP_OK;
+}
+
+// Edge steps on tables, one launch for up to kBatch partitions: the forward kernel or one of the reverse ones.
+template <int F> int launch_edge_tab(mlip_graph *g, TabBatch &b, void (*kernel)(TabBatch), int waves)
+{
+    int slot = 0;
+    MLIP_TRY(configure_kernel(g, reinterpret_cast<const void *>(kernel), kTabLds, &slot));
+    MLIP_TRY(plan_edge_tab<F>(g, b, waves));
+    if (b.slots == 0) return MLIP_OK;
+    kernel<<<(unsigned)(8 * (F / 32) * b.slots), waves * 64, kTabLds, g->stream>>>(b);
+    MLIP_HIP(hipGetLastError());
+    return MLIP_OK;
+}
+
+// The same with the way left to the device: *bad != 0 by MLP.
+template <int F, int PREC> int launch_edge_both(mlip_graph *g, TabBatch &tab, EdgeBatch &mlp, const int32_t *bad, bool backward)
+{
+    void (*kernel)(BothBatch) = !backward ? &k_edge_fwd_both<F, PREC>
+                                : mlp.c.need_gbar ? &k_edge_bwd_both<F, PREC, true> : &k_edge_bwd_both<F, PREC, false>;
+    const int waves = backward ? kBothBwdWaves : kFwdWaves;
+    const size_t lds = std::max<size_t>(kTabLds, backward ? Lds<F>::edge_bwd(PREC, waves) : Lds<F>::edge_fwd(PREC));
+    int slot = 0;
+    MLIP_TRY(configure_kernel(g, reinterpret_cast<const void *>(kernel), lds, &slot));
+    MLIP_TRY(plan_edge_tab<F>(g, tab, waves));
+    MLIP_TRY(plan_edge(g, mlp));
+    const int64_t slots = std::max<int64_t>((F / 32) * tab.slots, edge_slots(g, mlp, 1));
+    if (slots == 0) return MLIP_OK;
+    BothBatch b;
+    b.tab = tab;
+    b.mlp = mlp;
+    b.bad = bad;
+    kernel<<<(unsigned)(8 * slots), waves * 64, lds, g->stream>>>(b);
     MLIP_HIP(hipGetLastError());
     return MLIP_OK;
 }
@@ -330,25 +369,19 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         }
         prof_end(g);
     }
-    // Whether the tables represent this model's filters is decided on the device when they are made.  Until the host has seen the word, a handle
-    // on which they always did goes by them, and the launches fall back by themselves should it be different this time; any other handle
-    // launches the edge steps both ways, and those of the other way end at once.
+    // Whether the tables represent this model's filters is decided on the device when they are made.  Until the host has seen the word, the
+    // launches go by the device's: the way depends on the weights alone, not on what the handle has seen before or on when the host looks.
     enum { BY_TABLE, BY_MLP, BOTH_WAYS };
     int by = BOTH_WAYS;
-    bool decided = false;
     int64_t most_edges = 0;
     for (int p = 0; p < P; ++p) most_edges = std::max(most_edges, views[p].n_edges);
     if (L == 0 || most_edges >= (int64_t)1 << 29) {   // the steps on tables address an edge's 8 bytes of sums by 32-bit offsets
         by = BY_MLP;
-    } else {
+    } else if (!repack) {
         const int64_t word = __atomic_load_n(verdict, __ATOMIC_RELAXED);
-        if (word >> 1) ((word & 1) ? g->table_failed : g->table_good) = true;
-        decided = !repack && word >> 1 == g->kept_generation;
-        if (decided) by = (word & 1) ? BY_MLP : BY_TABLE;
-        else if (g->table_good && !g->table_failed) by = BY_TABLE;
+        if (word >> 1 == g->kept_generation) by = (word & 1) ? BY_MLP : BY_TABLE;
     }
-    const int32_t *verdict_dev = decided || by == BY_MLP ? nullptr : &tab_state->bad;
-    const int32_t *gate = by == BOTH_WAYS ? verdict_dev : nullptr;   // != null: the launches of both ways look at it
+    const int32_t *gate = by == BOTH_WAYS ? &tab_state->bad : nullptr;   // != null: the launches look at it
 
     const int dsum_step = F == 64 && !scratch ? 2 : 1;   // on tables: the halves' sums of an edge side by side, in the fixed block one array each
 
@@ -445,6 +478,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             a.l_senders = v.pairs.l_senders;
             a.l_slot = v.pairs.l_slot;
             const bool bonds = bw && v.bonds.n > 0;
+            sb.bonds |= bonds;
             a.b_ptr = bonds ? v.bonds.ptr.as<int64_t>() : nullptr;
             a.b_sender = bonds ? v.bonds.sender.as<int32_t>() : nullptr;
             a.b_mirror = bonds ? v.bonds.mirror.as<int32_t>() : nullptr;
@@ -622,12 +656,6 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         TabBatch b{};                                      // too, as what they get goes back to their owners
         b.n = std::min(kBatch, P - p0);
         b.tab = layer_table(l);
-        b.gate = verdict_dev;
-        b.exact = by == BY_TABLE;
-        b.W1 = w->W1 + (size_t)l * 8 * F;
-        b.W2 = w->W2 + (size_t)l * F * F;
-        b.bp = bp;
-        b.bf16 = prec == kPrecBf16;
         b.inv_h = tab_inv_h;
         b.first = l == L - 1;
         for (int q = 0; q < b.n; ++q) {
@@ -650,6 +678,70 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             a.dsum_step = dsum_step;
         }
         return b;
+    };
+    auto edge_batch = [&](int p0, int l, bool backward) {   // by MLP: forward over the owned rows, reverse over their upper edges
+        EdgeBatch b{};
+        const float *base = layer_pack(l);
+        b.n = std::min(kBatch, P - p0);
+        b.c.A1 = base + pk.A1;
+        b.c.A1s = base + pk.A1s;
+        b.c.A2t = base + pk.W2t;
+        b.c.A2n = base + pk.W2n;
+        b.c.bp = bp;
+        b.c.need_gbar = backward && l > 0;   // dE/dh0 is never used: the embedding does not depend on positions
+        b.c.first = l == L - 1;
+        for (int q = 0; q < b.n; ++q) {
+            SlabView &v = views[p0 + q];
+            EdgeArgs &a = b.s[q];
+            const PairGraph &Q = v.pairs;
+            a.n_rows = v.n_owned;
+            a.n_nodes = v.n_local;
+            a.g = gslice(v, l);
+            a.wstore = l >= 1 ? wslice(v, l) : nullptr;
+            if (backward) {
+                a.n_chunks = chunks_of(Q.n_upper, Q.span);
+                a.chunk_row = Q.u_chunk_row;
+                a.row_ptr = Q.u_row_ptr;
+                a.senders = Q.u_senders;
+                a.recv = Q.u_recv;
+                a.d = Q.u_d;
+                a.mirror = Q.u_mirror;
+                a.eid = Q.u_eid;
+                a.abar = abarslice(v, l);
+                a.out = v.ws.gbar;
+                a.dsum = v.ws.dsum;
+            } else {
+                a.n_chunks = chunks_of(v.n_edges_owned, v.span);
+                a.chunk_row = v.chunk_row;
+                a.row_ptr = v.row_ptr;
+                a.senders = v.senders;
+                a.recv = v.recv;
+                a.d = v.d;
+                a.out = aslice(v, l);
+                a.uslot = Q.uslot;
+            }
+        }
+        return b;
+    };
+    auto edge_step_at = [&](auto precision, int p0, int l, bool backward) -> int {
+        constexpr int PREC = decltype(precision)::value;
+        TabBatch tab{};
+        EdgeBatch mlp{};
+        if (by != BY_MLP) tab = tab_batch(p0, l, backward);
+        if (by != BY_TABLE) mlp = edge_batch(p0, l, backward);
+        if (by == BOTH_WAYS) return launch_edge_both<F, PREC>(g, tab, mlp, gate, backward);
+        if (by == BY_MLP) return launch_edge<F, PREC>(g, mlp, backward);
+        if (!backward) return launch_edge_tab<F>(g, tab, &k_edge_fwd_tab<F>, kTabFwdWaves);
+        return launch_edge_tab<F>(g, tab, l > 0 ? &k_edge_bwd_tab<F, true> : &k_edge_bwd_tab<F, false>, kTabBwdWaves);
+    };
+    auto edge_step = [&](int p0, int l, bool backward) -> int {   // of up to kBatch partitions from p0 on
+        prof_begin(g, backward ? MLIP_PROF_EDGE_BWD : MLIP_PROF_EDGE_FWD);
+        MLIP_TRY(prec == kPrecBf16    ? edge_step_at(std::integral_constant<int, kPrecBf16>{}, p0, l, backward)
+                 : prec == kPrecF16x3 ? edge_step_at(std::integral_constant<int, kPrecF16x3>{}, p0, l, backward)
+                                      : edge_step_at(std::integral_constant<int, kPrecF32>{}, p0, l, backward));
+        ++g->work_next;
+        prof_end(g);
+        return MLIP_OK;
     };
     int64_t tiles_before = 0;
     auto tile_sums = [&](SlabView &v) {
@@ -682,42 +774,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             })));
         }
         prof_end(g);
-        for (int p0 = 0; p0 < P; p0 += kBatch) {   // the partitions in order, up to kBatch per launch
-            prof_begin(g, MLIP_PROF_EDGE_FWD);
-            if (by != BY_MLP) {
-                TabBatch tb = tab_batch(p0, l, false);
-                MLIP_TRY(launch_edge_tab<F>(g, tb, &k_edge_fwd_tab<F>, kTabFwdWaves));
-            }
-            if (by != BY_TABLE) {
-                EdgeBatch eb{};
-                eb.n = std::min(kBatch, P - p0);
-                eb.c.A1 = base + pk.A1;
-                eb.c.A1s = base + pk.A1s;
-                eb.c.A2t = base + pk.W2t;
-                eb.c.bp = bp;
-                eb.c.gate = gate;
-                for (int q = 0; q < eb.n; ++q) {
-                    SlabView &v = views[p0 + q];
-                    EdgeArgs &ea = eb.s[q];
-                    ea.n_rows = v.n_owned;
-                    ea.n_chunks = chunks_of(v.n_edges_owned, v.span);
-                    ea.chunk_row = v.chunk_row;
-                    ea.n_nodes = v.n_local;
-                    ea.row_ptr = v.row_ptr;
-                    ea.senders = v.senders;
-                    ea.recv = v.recv;
-                    ea.d = v.d;
-                    ea.g = gslice(v, l);
-                    ea.out = aslice(v, l);
-                    ea.uslot = v.pairs.uslot;
-                    ea.wstore = l >= 1 ? wslice(v, l) : nullptr;
-                }
-                MLIP_TRY(prec == kPrecBf16 ? (launch_edge<F, kPrecBf16>(g, eb, false))
-                         : prec == kPrecF16x3 ? (launch_edge<F, kPrecF16x3>(g, eb, false)) : (launch_edge<F, kPrecF32>(g, eb, false)));
-            }
-            ++g->work_next;
-            prof_end(g);
-        }
+        for (int p0 = 0; p0 < P; p0 += kBatch) MLIP_TRY(edge_step(p0, l, false));   // the partitions in order, up to kBatch per launch
         if (any_bonds) {   // bond term of the filters: a_i += sum_b wb_b * g_send(b)
             prof_begin(g, MLIP_PROF_BOND);
             for (int p = 0; p < P; ++p) {
@@ -770,49 +827,9 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
     MLIP_HIP(hipGetLastError());
     for (int l = L - 1; l >= 0; --l) {
         const float *base = wp + pk.per_layer * l;
-        const bool need_gbar = l > 0;  // dE/dh0 is never used: the embedding does not depend on positions
+        const bool need_gbar = l > 0;  // (as in edge_batch)
         for (int p0 = 0; p0 < P; p0 += kBatch) {
-            prof_begin(g, MLIP_PROF_EDGE_BWD);
-            if (by != BY_MLP) {
-                TabBatch tb = tab_batch(p0, l, true);
-                MLIP_TRY(launch_edge_tab<F>(g, tb, need_gbar ? &k_edge_bwd_tab<F, true> : &k_edge_bwd_tab<F, false>, kTabBwdWaves));
-            }
-            if (by != BY_TABLE) {
-                EdgeBatch eb{};
-                eb.n = std::min(kBatch, P - p0);
-                eb.c.A1 = base + pk.A1;
-                eb.c.A1s = base + pk.A1s;
-                eb.c.A2t = base + pk.W2t;
-                eb.c.A2n = base + pk.W2n;
-                eb.c.bp = bp;
-                eb.c.need_gbar = need_gbar ? 1 : 0;
-                eb.c.first = (l == L - 1) ? 1 : 0;
-                eb.c.gate = gate;
-                for (int q = 0; q < eb.n; ++q) {
-                    SlabView &v = views[p0 + q];
-                    EdgeArgs &ea = eb.s[q];
-                    const PairGraph &Q = v.pairs;
-                    ea.n_rows = v.n_owned;
-                    ea.n_chunks = chunks_of(Q.n_upper, Q.span);
-                    ea.chunk_row = Q.u_chunk_row;
-                    ea.n_nodes = v.n_local;
-                    ea.row_ptr = Q.u_row_ptr;
-                    ea.senders = Q.u_senders;
-                    ea.recv = Q.u_recv;
-                    ea.d = Q.u_d;
-                    ea.mirror = Q.u_mirror;
-                    ea.eid = Q.u_eid;
-                    ea.g = gslice(v, l);
-                    ea.abar = abarslice(v, l);
-                    ea.out = v.ws.gbar;
-                    ea.dsum = v.ws.dsum;
-                    ea.wstore = need_gbar ? wslice(v, l) : nullptr;
-                }
-                MLIP_TRY(prec == kPrecBf16 ? (launch_edge<F, kPrecBf16>(g, eb, true))
-                         : prec == kPrecF16x3 ? (launch_edge<F, kPrecF16x3>(g, eb, true)) : (launch_edge<F, kPrecF32>(g, eb, true)));
-            }
-            ++g->work_next;
-            prof_end(g);
+            MLIP_TRY(edge_step(p0, l, true));
             if (need_gbar && (by != BY_TABLE || any_bonds)) {   // second pass: the lower edges' terms of the rows' sums, and the bonds'
                 prof_begin(g, MLIP_PROF_EDGE_BWD_LOWER);
                 const SmallBatch sb = small_batch(p0, U_OWNED, l);

@@ -31,7 +31,6 @@ struct EdgeCommon {
     const float *A1, *A1s, *A2t, *A2n;   // A1s = c W1, A2t = W2 / c (see kSiluScale), A1 and A2n unscaled
     BasisParams bp;
     int need_gbar, first;
-    const int32_t *gate;   // != null: the launch runs only if *gate != 0 (the filters are not represented by tables)
 };
 
 // One launch covers up to kBatch partitions, taken in order: work item w belongs to partition p
@@ -151,12 +150,9 @@ __device__ inline uint32_t row_ends(int32_t rk, int32_t rn_first, bool valid, in
 }
 
 // PREC selects how the F x F product with W2 runs: kPrecF32 three-part bf16, kPrecBf16 bf16 operands, kPrecF16x3 split fp16
-template <int F, int PREC>
-__global__ void __launch_bounds__(kFwdWaves * 64, 3) k_edge_fwd(EdgeBatch B)
+template <int F, int PREC> __device__ __forceinline__ void edge_fwd(const EdgeBatch &B, float *lds)
 {
     using D = Dims<F>;
-    extern __shared__ float lds[];
-    if (B.c.gate && *B.c.gate == 0) return;
     float *A2t = lds;
     float *A1s = A2t + pack_floats<F>(PREC);
     float *tiles = A1s + D::PACK1;
@@ -287,6 +283,12 @@ __global__ void __launch_bounds__(kFwdWaves * 64, 3) k_edge_fwd(EdgeBatch B)
     }   // work items
     }   // partitions
 }
+template <int F, int PREC>
+__global__ void __launch_bounds__(kFwdWaves * 64, 3) k_edge_fwd(EdgeBatch B)
+{
+    extern __shared__ float lds[];
+    edge_fwd<F, PREC>(B, lds);
+}
 
 // Reverse edge step.
 //
@@ -321,20 +323,17 @@ constexpr int kQueueTrigger = (kQueue - kStep < 32) ? kQueue - kStep : 32;
 // (Letting this kernel hand w * abar_i to the lower edge's row through memory instead was measured: vector stores
 // return in order with the loads on this chip, and 16 scattered row stores per step stalled the load pipeline:
 // 5.2 ms per launch against 3.5 ms.)
-template <int F, int PREC>
-__global__ void __launch_bounds__(kBwdWaves * 64, kBwdWaves == 4 ? 2 : 1) k_edge_bwd(EdgeBatch B)
+template <int F, int PREC, int NW> __device__ __forceinline__ void edge_bwd(const EdgeBatch &B, float *lds)
 {
     using D = Dims<F>;
     constexpr int FS = D::FS;
     constexpr int kRowBytes = F * 4;
-    extern __shared__ float lds[];
-    if (B.c.gate && *B.c.gate == 0) return;
     float *A2n = lds;
     float *A1l = A2n + pack_floats<F>(PREC);
     float *queues = A1l + D::PACK1;
     {
-        LdsFill<D::PACK1 / 4, kBwdWaves * 64> f1;
-        LdsFill<pack_floats<F>(PREC) / 4, kBwdWaves * 64> f2;
+        LdsFill<D::PACK1 / 4, NW * 64> f1;
+        LdsFill<pack_floats<F>(PREC) / 4, NW * 64> f2;
         f1.load(B.c.A1);
         f2.load(B.c.A2n);
         f1.store(A1l);
@@ -355,7 +354,7 @@ __global__ void __launch_bounds__(kBwdWaves * 64, kBwdWaves == 4 ? 2 : 1) k_edge
     int q_head = 0, q_count = 0;   // first queued slot, queued pairs
     int q_tail = 0;                // (q_head + q_count) % kQueue, the slot the next pair goes to
 
-    const ItemQueue items = edge_items(B.chunk_start[B.n], B.work, wave, kBwdWaves);
+    const ItemQueue items = edge_items(B.chunk_start[B.n], B.work, wave, NW);
     int64_t item = items.first;
     int32_t drawn = 0;
     for (int part = 0; part < B.n; ++part) {
@@ -569,6 +568,11 @@ __global__ void __launch_bounds__(kBwdWaves * 64, kBwdWaves == 4 ? 2 : 1) k_edge
     while (q_count > 0) phase2();   // queued pairs index this partition's arrays
     }   // partitions
 }
-
+template <int F, int PREC>
+__global__ void __launch_bounds__(kBwdWaves * 64, kBwdWaves == 4 ? 2 : 1) k_edge_bwd(EdgeBatch B)
+{
+    extern __shared__ float lds[];
+    edge_bwd<F, PREC, kBwdWaves>(B, lds);
+}
 
 #endif  // MLIP_MODEL_EDGE_H

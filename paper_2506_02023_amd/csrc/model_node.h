@@ -269,6 +269,7 @@ struct SmallArgs {   // one partition
 struct SmallBatch {
     int n;
     int tables;            // whether the edge steps run on tables; if not, the filter values are kept, edge by edge
+    int bonds;             // whether a partition has bonds
     const int32_t *gate;   // != null: not known when this is launched, *gate == 0 says that they did
     __device__ bool on_tables() const { return gate ? *gate == 0 : tables != 0; }
     int64_t start[kBatch + 1];
@@ -298,6 +299,8 @@ constexpr int kLowerChunk = 16;   // lower edges whose rows are in flight togeth
 template <int F>
 __global__ void __launch_bounds__(256) k_edge_lower(SmallBatch B)
 {
+    const bool kept = !B.on_tables();   // on tables the reverse step has the lower edges already
+    if (!kept && !B.bonds) return;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int64_t gk = (int64_t)blockIdx.x * 4 + wave;
     if (gk >= B.start[B.n]) return;
@@ -305,7 +308,6 @@ __global__ void __launch_bounds__(256) k_edge_lower(SmallBatch B)
     const SmallArgs &A = B.s[part];
     const int64_t r = gk - B.start[part];
     const unsigned f = lane & (F - 1);
-    const bool kept = !B.on_tables();   // on tables the reverse step has the lower edges already
     if (!kept && !A.b_ptr) return;
     // the row's lower edges (wave-uniform, kept scalar; edge indices fit 32 bits)
     const int64_t e0 = kept ? __builtin_amdgcn_readfirstlane((int32_t)A.l_row_ptr[r]) : 0;
@@ -363,6 +365,8 @@ __global__ void __launch_bounds__(256) k_edge_lower(SmallBatch B)
 template <int F>
 __global__ void __launch_bounds__(256) k_ghost_gbar(SmallBatch B)
 {
+    const bool kept = !B.on_tables();
+    if (!kept && !B.bonds) return;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int64_t gk = (int64_t)blockIdx.x * 4 + wave;
     if (gk >= B.start[B.n]) return;
@@ -370,7 +374,6 @@ __global__ void __launch_bounds__(256) k_ghost_gbar(SmallBatch B)
     const SmallArgs &A = B.s[part];
     const int64_t r = A.n_owned + (gk - B.start[part]);
     const unsigned f = lane & (F - 1);
-    const bool kept = !B.on_tables();
     if (!kept && !A.bond_of_edge) return;
     const int64_t e0 = A.row_ptr[r], e1 = A.row_ptr[r + 1];
     float acc = kept ? 0.f : A.gbar[r * F + f];   // on tables the reverse step has summed the edges' terms: the bonds' are added

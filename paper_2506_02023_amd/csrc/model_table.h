@@ -183,12 +183,8 @@ struct TabArgs {               // one partition
 };
 struct TabBatch {
     const float *tab;      // the layer's table
-    const int32_t *gate;   // != null: the tables may be used only if *gate == 0;
-    int exact;             // if not, the launch takes the filters from the MLP, slowly (1), or leaves the work to another one (0)
-    const float *W1, *W2;  // the layer's, for that
-    BasisParams bp;
-    int bf16;
     float inv_h;
+    int slots;             // blocks of an XCD for each block of 32 features; blocks beyond them have no rows
     int rows;              // rows of a work item
     int few;               // few rows for the workers: every XCD takes rows of one partition, 8 / n XCDs each
     int first;             // reverse: dsum is written, not added to
@@ -308,7 +304,7 @@ __device__ __forceinline__ void tab_walk(const TabBatch &B, float *lds, int hb, 
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, l16 = lane & 15;
     constexpr int NH = F / 32;
-    const int32_t n_slots = (int32_t)(gridDim.x >> 3) / NH, xcd = blockIdx.x & 7, slot = (int32_t)(blockIdx.x >> 3) / NH;
+    const int32_t n_slots = B.slots, xcd = blockIdx.x & 7, slot = (int32_t)(blockIdx.x >> 3) / NH;
     const int64_t total = B.edge_start[B.n], share = (total + 7) >> 3;
     const int64_t from = xcd * share, to = xcd == 7 ? total + 1 : from + share;   // the XCD's edges
     const int32_t mine = xcd * B.n >> 3, mine_from = (8 * mine + B.n - 1) / B.n, mine_n = (8 * mine + 8 + B.n - 1) / B.n - mine_from;   // B.few
@@ -419,73 +415,10 @@ __device__ __forceinline__ void tab_walk(const TabBatch &B, float *lds, int hb, 
     }
 }
 
-
-// Either step with the filters from the MLP itself, in fp32, a wavefront per row, lane = feature: what a launch on tables does when the
-// tables turn out not to represent the filters and nothing else was launched (the call after the first one that learns it takes the MLP's
-// own kernels).  Correct at any size, several times slower than those.
-template <int F, int NW, bool BWD, bool GBAR> __device__ __forceinline__ void tab_exact(const TabBatch &B, float *lds)
-{
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, f = lane & (F - 1);
-    float *W2 = lds, *s_of = lds + F * F + wave * 2 * F, *ds_of = s_of + F;
-    for (int i = threadIdx.x; i < F * F; i += NW * 64) W2[i] = B.bf16 ? (float)(__bf16)(B.W2[i] * kSiluScaleInv) / kSiluScaleInv : B.W2[i];
-    __syncthreads();
-    float w1[8];
-#pragma unroll
-    for (int n = 0; n < 8; ++n) w1[n] = B.W1[n * F + f];
-    for (int part = 0; part < B.n; ++part) {
-        const TabArgs &A = B.s[part];
-        for (int64_t i = (int64_t)blockIdx.x * NW + wave; i < A.n_rows; i += (int64_t)gridDim.x * NW) {
-            const float gi = BWD ? A.g[i * F + f] : 0.f;
-            float acc = 0.f;
-            for (int64_t e = A.row_ptr[i]; e < A.row_ptr[i + 1]; ++e) {
-                const float row = (BWD ? A.abar : A.g)[(int64_t)A.senders[e] * F + f];
-                float t = 0.f, dt = 0.f;
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    float b[4], db[4];
-                    radial_basis<true>(A.d[e], B.bp, h, b, db);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        t = fmaf(b[k], w1[2 * k + h], t);
-                        dt = fmaf(db[k], w1[2 * k + h], dt);
-                    }
-                }
-                const float sg = sigmoidf_fast(t);
-                wave_lds_fence();
-                s_of[f] = t * sg;
-                ds_of[f] = sg * (1.f + t * (1.f - sg)) * dt;
-                wave_lds_fence();
-                float w = 0.f, dw = 0.f;
-#pragma unroll 4
-                for (int k = 0; k < F; ++k) {
-                    w = fmaf(s_of[k], W2[k * F + f], w);
-                    if (BWD) dw = fmaf(ds_of[k], W2[k * F + f], dw);
-                }
-                acc = fmaf(w, row, acc);
-                if (BWD) {
-                    float q = lane < F ? dw * (row * gi) : 0.f;
-                    for (int off = 32; off > 0; off >>= 1) q += __shfl_xor(q, off, 64);
-                    if (lane == 0) {
-                        A.dsum[0][e * A.dsum_step] = B.first ? q : A.dsum[0][e * A.dsum_step] + q;
-                        if (F == 64 && B.first) A.dsum[1][e * A.dsum_step] = 0.f;
-                    }
-                }
-            }
-            if (lane < F && (!BWD || GBAR)) A.out[i * F + f] = acc;
-        }
-    }
-}
-
 // Forward step over the owned rows: a_i = sum_e w_e * g_send(e).
-template <int F>
-__global__ void __launch_bounds__(kTabFwdWaves * 64, kTabFwdWaves / 4) k_edge_fwd_tab(TabBatch B)
+template <int F, int NW> __device__ __forceinline__ void edge_fwd_tab(const TabBatch &B, float *lds)
 {
     constexpr int kRow = F * 4;
-    extern __shared__ float lds[];
-    if (B.gate && *B.gate != 0) {
-        if (B.exact) tab_exact<F, kTabFwdWaves, false, false>(B, lds);
-        return;
-    }
     const int lane = threadIdx.x & 63, l16 = lane & 15, at_f = l16 * 4;   // byte offset of the lane's first feature in a block of 32
     const int hb = (blockIdx.x >> 3) & (F / 32 - 1);
     const char *tab = reinterpret_cast<const char *>(lds) + l16 * 16;
@@ -495,7 +428,7 @@ __global__ void __launch_bounds__(kTabFwdWaves * 64, kTabFwdWaves / 4) k_edge_fw
     auto zero_rows = [&](int32_t r, int32_t end) {
         for (; r < end; ++r) buffer_store_2(f32x2{0.f, 0.f}, out, r * kRow + at_f);
     };
-    tab_walk<F, kTabFwdWaves, Rows>(B, lds, hb,
+    tab_walk<F, NW, Rows>(B, lds, hb,
         [&](const TabArgs &A) {
             const uint32_t n_rec = (uint32_t)A.n_edges * 4u;
             send = tab_buffer(A.senders, n_rec);
@@ -553,6 +486,12 @@ __global__ void __launch_bounds__(kTabFwdWaves * 64, kTabFwdWaves / 4) k_edge_fw
         },
         zero_rows);
 }
+template <int F>
+__global__ void __launch_bounds__(kTabFwdWaves * 64, kTabFwdWaves / 4) k_edge_fwd_tab(TabBatch B)
+{
+    extern __shared__ float lds[];
+    edge_fwd_tab<F, kTabFwdWaves>(B, lds);
+}
 
 // Sums of q[0..15] over the 16 lanes of each row: lane l returns the sum of q[tab_edge_of(l)].  Each step adds lanes across one bit of the lane
 // number and lets the lanes on either side go on with one of two edges.
@@ -588,15 +527,9 @@ __device__ inline float tab_reduce(const float (&q)[16], int lane)
 // its share sum_f w'_f (abar_j g_i)_f of dE/dd.  The share with abar_i g_j is the reverse edge's, whose row gathers abar_i: the forces
 // take both (k_force_rows), and the step gathers one row per edge instead of two.  (In a partition an owned row's edges from
 // ghosts have no share, abar of a ghost being zero, and the ghosts' rows hold the other ones.)
-template <int F, bool GBAR>
-__global__ void __launch_bounds__(kTabBwdWaves * 64, kTabBwdWaves / 4) k_edge_bwd_tab(TabBatch B)
+template <int F, bool GBAR, int NW> __device__ __forceinline__ void edge_bwd_tab(const TabBatch &B, float *lds)
 {
     constexpr int kRow = F * 4;
-    extern __shared__ float lds[];
-    if (B.gate && *B.gate != 0) {
-        if (B.exact) tab_exact<F, kTabBwdWaves, true, GBAR>(B, lds);
-        return;
-    }
     const int lane = threadIdx.x & 63, l16 = lane & 15, at_f = l16 * 4;   // byte offset of the lane's first feature in a block of 32
     const int hb = (blockIdx.x >> 3) & (F / 32 - 1);
     const char *tab = reinterpret_cast<const char *>(lds) + l16 * 16;
@@ -610,7 +543,7 @@ __global__ void __launch_bounds__(kTabBwdWaves * 64, kTabBwdWaves / 4) k_edge_bw
         if (GBAR)
             for (; r < end; ++r) buffer_store_2(f32x2{0.f, 0.f}, out, r * kRow + at_f);
     };
-    tab_walk<F, kTabBwdWaves, Rows>(B, lds, hb,
+    tab_walk<F, NW, Rows>(B, lds, hb,
         [&](const TabArgs &A) {
             const uint32_t n_rec = (uint32_t)A.n_edges * 4u;
             send = tab_buffer(A.senders, n_rec);
@@ -701,6 +634,46 @@ __global__ void __launch_bounds__(kTabBwdWaves * 64, kTabBwdWaves / 4) k_edge_bw
                 buffer_store_f32(fmaf(sum, slope, before), sums, (uint32_t)(S.tb + k_out) << sum_shift, 0, 0);
         },
         zero_rows);
+}
+template <int F, bool GBAR>
+__global__ void __launch_bounds__(kTabBwdWaves * 64, kTabBwdWaves / 4) k_edge_bwd_tab(TabBatch B)
+{
+    extern __shared__ float lds[];
+    edge_bwd_tab<F, GBAR, kTabBwdWaves>(B, lds);
+}
+
+// ---------------------------------------------------------------- either way
+//
+// The edge steps of a call whose host has not heard yet whether the tables represent the filters: one launch that goes by *bad, so that
+// the way and every bit of the result follow from the weights alone, whatever the handle has seen before.  A row's or an edge's sum does
+// not depend on the wavefronts of a block, so either way gives what its own kernel gives; the reverse step takes 8 of them, the most that
+// leave the way by MLP the registers it needs.  Per launch on tables 20.0 us forward (20.1 in k_edge_fwd_tab), 25.8 and 24.9 reverse (24.4,
+// 24.5) at 15,600 rows and F = 32.  With a launch for each way, the other one's ending at once, a pass of four models took 691 us there, here
+// 669; 500 atoms in the fixed workspace 248 and 240.
+constexpr int kBothBwdWaves = 8;
+static_assert(kTabFwdWaves == kFwdWaves, "the forward step has one block size for both ways");
+struct BothBatch {
+    TabBatch tab;
+    EdgeBatch mlp;
+    const int32_t *bad;
+};
+template <int F, int PREC>
+__global__ void __launch_bounds__(kFwdWaves * 64, kFwdWaves / 4) k_edge_fwd_both(BothBatch B)
+{
+    extern __shared__ float lds[];
+    if (*B.bad != 0)
+        edge_fwd<F, PREC>(B.mlp, lds);
+    else if ((int)(blockIdx.x >> 3) < B.tab.slots * (F / 32))
+        edge_fwd_tab<F, kFwdWaves>(B.tab, lds);
+}
+template <int F, int PREC, bool GBAR>
+__global__ void __launch_bounds__(kBothBwdWaves * 64, kBothBwdWaves / 4) k_edge_bwd_both(BothBatch B)
+{
+    extern __shared__ float lds[];
+    if (*B.bad != 0)
+        edge_bwd<F, PREC, kBothBwdWaves>(B.mlp, lds);
+    else if ((int)(blockIdx.x >> 3) < B.tab.slots * (F / 32))
+        edge_bwd_tab<F, GBAR, kBothBwdWaves>(B.tab, lds);
 }
 
 #endif  // MLIP_MODEL_TABLE_H

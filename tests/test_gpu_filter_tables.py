@@ -118,3 +118,30 @@ def test_the_way_follows_the_weights(F, L, slabs):
         s = M.mlip_forward_static(g, Ws[k], mode)
         torch.cuda.synchronize()
         assert float(s[0].cpu()[0]) == fresh[k][0] and np.array_equal(s[1].cpu().numpy(), fresh[k][1].astype(np.float32))
+
+
+@pytest.mark.parametrize("precision", [0, 1, 2])
+@pytest.mark.parametrize("F,L,slabs", [(32, 2, 1), (64, 3, 3)])
+def test_results_do_not_depend_on_what_a_handle_saw_before(F, L, slabs, precision):
+    """Calls in any order, none of them waited for, give bit for bit what a fresh handle gives for the same weights, whether or not the
+    host has heard what the device found about them; the fixed workspace's too."""
+    import torch
+    import paper_2506_02023_amd as M
+    c = wl.make_config(1, n=4)
+    mode = M.MODE_SLABS if slabs > 1 else M.MODE_WHOLE
+    pos, sp = torch.as_tensor(c["positions"], device="cuda"), torch.as_tensor(c["species"], device="cuda")
+    new = lambda: M.mlip_build_graph(pos, c["cell"], sp, c["r_cut"], n_slabs=slabs)  # noqa: E731
+    Ws = [M.Weights(_weights(F, L, 7 + k, 30.0 if k == 1 else 1.0), 6, precision=precision) for k in range(3)]   # the second: by MLP
+    fresh = [_run(new(), W, mode) for W in Ws]
+    order = (0, 0, 1, 1, 2, 1, 0, 2, 2, 1)
+    g = new()
+    for k in (0, 0):
+        _run(g, Ws[k], mode)   # the host knows that the first model's tables are good
+    outs = []
+    for n, k in enumerate(order):
+        outs.append(M.mlip_forward_static(g, Ws[k], mode) if n % 4 == 3 else M.mlip_forward(g, Ws[k], mode))
+    torch.cuda.synchronize()
+    for k, (e, f, a) in zip(order, outs):
+        assert float(e.cpu()[0]) == fresh[k][0], k
+        assert np.array_equal(f.cpu().numpy(), fresh[k][1].astype(np.float32)), k
+        assert np.array_equal(a.cpu().numpy(), fresh[k][2].astype(np.float32)), k
