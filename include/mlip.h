@@ -51,8 +51,10 @@ typedef enum {
 enum { MLIP_MODE_WHOLE = 0, MLIP_MODE_SLABS = 1 };
 /*
  * Filters: w_e = MLP(basis(d_e)) is a function of the edge length alone.  A model's filters are tabulated on the device
- * (piecewise polynomials made in fp64, kept and evaluated in fp32), checked there against what fp32 rounding of the length
- * makes, and looked up per edge; weights whose filters the tables do not represent take the MLP per edge.
+ * (piecewise polynomials made in fp64, kept and evaluated in fp32), checked there feature by feature against what the
+ * evaluation of the MLP in fp32 rounds, and looked up per edge; weights whose filters the tables do not represent (they bend
+ * too fast: large W1, or a cutoff short in the units of W1) take the MLP per edge.  Which of the two a call takes follows
+ * from the weights and the cutoff alone.
  *
  * MLIP_PRECISION_FP32: everything from the basis on in fp32 (products as exact sums of three bf16 parts per operand on the
  *   bf16 matrix units, all terms down to 2^-24, accumulated in fp32).  An operand beyond the bf16 range (3.39e38; fp32 ends

@@ -12,11 +12,14 @@
 // kTabN intervals over [0, rc], degree 5 in the local coordinate s in [-1, 1], fp32 coefficients computed in fp64.  In units of rc /
 // kTabUnits the intervals have the length 1/2 below kTabSmall (at short distances the basis functions are large and SiLU bends most), 1/4
 // from kTabEnd on (at the cutoff the filter vanishes with its first three derivatives, so its error has to vanish too) and 1 between. What
-// is cut off is below what the rounding of the length to fp32 makes (checked when the table is made, see k_filter_table); coefficients and
-// evaluation round to 4e-8 (values) and 5e-8 (slopes) of the filter, the fp32 evaluation of the MLP to 1.7e-7 of both. One block of 32
-// features is 768 bytes per interval, [3][16][2][2]: coefficients 2 q and 2 q + 1 of features l and l + 16, 16 bytes for one lane; 162,816
+// is cut off is below what the evaluation of the MLP in fp32 rounds, feature by feature (checked when the table is made, see k_filter_table);
+// coefficients and evaluation round to 4e-8 (values) and 5e-8 (slopes) of the filter, the fp32 evaluation of the MLP to 1.7e-7 of both.
+// kTabUnits and kTabSmall share the intervals out between short lengths and the rest: of 300 random layers with W1 of variance 1/8 all
+// are represented at rc 4.5 to 5.5, 96 % at F = 64 with one and a half times that W1 or with rc 3 (the same thing: the basis goes as 1 / d), 68 %
+// with twice at 4.5, 83 % at 5 (179 and 27 in their place, features pooled: 97 to 100 %, 56 %, 10 %, 21 %).
+// One block of 32 features is 768 bytes per interval, [3][16][2][2]: coefficients 2 q and 2 q + 1 of features l and l + 16, 16 bytes for one lane; 162,816
 // bytes of the compute unit's 160 KB.  With F = 64 every block of the grid holds the table of one half of the features.
-constexpr int kTabUnits = 179, kTabSmall = 27, kTabEnd = kTabUnits - 2;
+constexpr int kTabUnits = 160, kTabSmall = 46, kTabEnd = kTabUnits - 2;
 constexpr int kTabM0 = 2 * kTabSmall, kTabE0 = kTabM0 + kTabEnd - kTabSmall, kTabN = kTabE0 + 4 * (kTabUnits - kTabEnd);
 constexpr int kTabStride = 32 * 6 * 4;                   // bytes of an interval
 constexpr int kTabFloats = kTabN * kTabStride / 4;       // floats of one block of 32 features
@@ -61,7 +64,7 @@ __constant__ const double kCosTab[32] = {
 template <int F>
 __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
 {
-    __shared__ double sv[kTabNodes][64], wv[kTabNodes][64];
+    __shared__ double sv[kTabNodes][64], wv[kTabNodes][64], uv[kTabNodes][64], gv[kTabNodes][64];
     __shared__ double W2[F * F];
     const int iv = blockIdx.x, layer = blockIdx.y;
     const int node = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, f = lane & (F - 1);
@@ -81,25 +84,34 @@ __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
         const double u = y * y * y * q / d;   // the envelope in its factored form, over d
         // sin((n + 1) pi x) by angle addition from the nearer end, where it is small
         const double near = x < 0.5 ? x : y, s1 = sinpi(near), c1 = x < 0.5 ? cospi(near) : -cospi(near);
-        double sn = s1, cn = c1, t = 0;
+        double sn = s1, cn = c1, t = 0, tt = 0;
 #pragma unroll
         for (int n = 0; n < 8; ++n) {
-            t += sn * u * (double)w1[n];
+            const double term = sn * u * (double)w1[n];
+            t += term;
+            tt += term * term;
             const double nx = sn * c1 + cn * s1;
             cn = cn * c1 - sn * s1;
             sn = nx;
         }
-        sv[node][lane] = t / (1.0 + exp(-t));
+        const double sg = 1.0 / (1.0 + exp(-t)), slope = sg * (1.0 + t * (1.0 - sg));
+        sv[node][lane] = t * sg;
+        uv[node][lane] = tt * (slope * slope + 1.0 / 16);   // (see the verdict below)
     }
 #pragma unroll
     for (int i = 0; i < F * F / (kTabNodes * 64); ++i)
         W2[i * kTabNodes * 64 + threadIdx.x] = J.bf16 ? (double)(float)(__bf16)(w2[i] * kSiluScaleInv) / kSiluScaleInv : (double)w2[i];
     __syncthreads();
     {   // w_f = sum_k s_k W2[k][f]
-        double w = 0;
+        double w = 0, g = 0;
 #pragma unroll 16
-        for (int k = 0; k < F; ++k) w = fma(sv[node][k], W2[k * F + f], w);
+        for (int k = 0; k < F; ++k) {
+            const double v = W2[k * F + f];
+            w = fma(sv[node][k], v, w);
+            g = fma(uv[node][k], v * v, g);
+        }
         wv[node][lane] = w;
+        gv[node][lane] = g;
     }
     __syncthreads();
     double a = 0;   // Chebyshev coefficient `node` of this lane's feature
@@ -118,29 +130,22 @@ __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
         const int l = lane & 31;
         for (int k = 0; k < 6; ++k) at[64 * (k / 2) + 4 * (l % 16) + 2 * (k % 2) + l / 16] = (float)c[k];
     }
-    // What is cut off, as root mean squares over the interval and the features: a6 T6 + a7 T7 of the values, 8 a6 + 10 a7 of the slopes
-    // (rms of T6' and T7').  Allowed is 1e-7 of the value or slope itself and what half an ulp of the length, rounded to fp32,
-    // changes on average: 2^-26 of the length times the next derivative.
-    double ew = a6 + a7, ed = 8 * a6 + 10 * a7, sw = 0, sd = 0;
-    const double dl = 0x1p-26 * 2 * (lo + 0.5 * wd) / wd;   // the length's rounding in units of s
-    for (int i = -1; i <= 1; ++i) {
-        const double s = 0.8 * i;
-        const double w0 = c[0] + s * (c[1] + s * (c[2] + s * (c[3] + s * (c[4] + s * c[5]))));
-        const double w1 = c[1] + s * (2 * c[2] + s * (3 * c[3] + s * (4 * c[4] + s * 5 * c[5])));
-        const double w2 = 2 * c[2] + s * (6 * c[3] + s * (12 * c[4] + s * 20 * c[5]));
-        sw += (1e-14 * w0 * w0 + dl * dl * w1 * w1) / 3;
-        sd += (1e-14 * w1 * w1 + dl * dl * w2 * w2) / 3;
-    }
-    ew *= ew;
-    ed *= ed;
-    for (int off = 32; off > 0; off >>= 1) {
-        ew += __shfl_xor(ew, off, 64);
-        ed += __shfl_xor(ed, off, 64);
-        sw += __shfl_xor(sw, off, 64);
-        sd += __shfl_xor(sd, off, 64);
-    }
+    // What is cut off: a6 T6 + a7 T7 of the values, root mean square a6 + a7 at most, and 8 a6 + 10 a7 of the slopes (rms of T6' and T7').
+    // Every feature is held to what the fp32 evaluation of the MLP rounds of it, 1e-7 of G, G^2 = sum_k W2[k][f]^2 tau_k^2 SiLU'(t_k)^2, tau_k^2 the
+    // sum of the squares of t_k's eight terms, and for the slopes 1e-7 kappa G, kappa what a basis function grows by along a unit of length relative
+    // to itself: 8 pi / rc from the sine, 4 / (rc - d) where it vanishes as (rc - d)^4; further to what the length's rounding to fp32, half an
+    // ulp, changes on average: 2^-26 of the length times kappa.  Where SiLU' is near zero a sixteenth stands for SiLU'^2: there the feature is small
+    // beside what it is elsewhere (a unit's t goes to 0 at the cutoff, so -0.28 is always passed).  G goes with the feature's column of W2:
+    // scaling that against the later maps does not change the verdict.
+    double g2 = 0;
+#pragma unroll
+    for (int j = 0; j < kTabNodes; ++j) g2 += gv[j][lane] * (1.0 / kTabNodes);
+    const double mid = lo + 0.5 * wd, kappa = (8 * 3.141592653589793 / kTabUnits + 4.0 / (kTabUnits - mid)) * 0.5 * wd;   // in units of s
+    const double rounding = 0x1p-26 * 2 * mid / wd * kappa;
+    const double cut = fmax(a6 + a7, (8 * a6 + 10 * a7) / kappa);
+    const bool feature_bad = !(cut * cut <= g2 * (1e-14 + rounding * rounding));   // (not a number: not represented)
+    const bool bad = __any(feature_bad);
     if (lane == 0) {
-        const bool bad = !(ew <= sw && ed <= sd);   // (not a number: not represented)
         if (bad) J.state->bad = 1;
         // A word counts blocks and the bad ones among them, so that the last one needs no fence to know.  The blocks are spread over
         // kTabCounters of them, whose last ones go on to state->done: some 20 ns per addition to one address made up most of the launch.

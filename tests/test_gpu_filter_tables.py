@@ -12,7 +12,7 @@ from gpu_util import E_RTOL, F_RTOL
 pytestmark = pytest.mark.gpu
 
 R_CUT = 5.0
-UNIT = R_CUT / 179   # the intervals' unit: half of it below 27 units, a quarter from 177 on
+UNIT = R_CUT / 160   # the intervals' unit: half of it below 46 units, a quarter from 158 on
 
 
 def _weights(F, L, seed, scale=1.0):
@@ -52,7 +52,7 @@ def test_pairs_at_the_ends_of_intervals(F):
     rounding of the length to fp32, up to 2^-22 at 5, makes of the fourth power of its distance from the cutoff."""
     import torch
     import paper_2506_02023_amd as M
-    edges = [x * UNIT for x in (13.5, 26.5, 27, 28, 90, 176, 177, 177.25, 178, 178.75)]
+    edges = [x * UNIT for x in (13.5, 45.5, 46, 47, 90, 157, 158, 158.25, 159, 159.75)]
     ds = sorted(x + o for x in edges for o in (-1e-6, 1e-6)) + [0.3, 1.0, 2.5, 4.97, 4.99, 4.999]
     pos, kind = [], []
     for k, d in enumerate(ds):
@@ -145,3 +145,43 @@ def test_results_do_not_depend_on_what_a_handle_saw_before(F, L, slabs, precisio
         assert float(e.cpu()[0]) == fresh[k][0], k
         assert np.array_equal(f.cpu().numpy(), fresh[k][1].astype(np.float32)), k
         assert np.array_equal(a.cpu().numpy(), fresh[k][2].astype(np.float32)), k
+
+
+def _sharp(F, L, seed, sharper, scale):
+    """Four features fed by four hidden units of their own, with W1 `sharper` times larger; their filters scaled by `scale` and their share of
+    the sender projection by its inverse (powers of two: the same model)."""
+    w, r = _weights(F, L, seed), np.random.default_rng(seed)
+    w["W1"][:, :, :4] *= np.float32(sharper)
+    w["W2"][:, :4, :] = w["W2"][:, :, :4] = 0
+    w["W2"][:, :4, :4] = r.standard_normal((L, 4, 4)).astype(np.float32) / 2
+    w["W2"][:, :, :4] *= np.float32(scale)
+    w["Wm"][:, :, :4] /= np.float32(scale)
+    return w
+
+
+@pytest.mark.parametrize("F", [32, 64])
+def test_small_features_are_judged_by_themselves(F):
+    """Features that bend fast and are small beside the others go by the MLP as they do at the others' size, and pairs at short distances have
+    its forces.  Bound, of the largest force: 4e-6 for values and slopes rounded to some 4e-7 in three layers forward and back, and for the
+    sharp units, whose t is a sum of terms of up to 3 x `sharper`, 2^-24 of those through SiLU'' / SiLU' <= 1/2 in each of the six steps."""
+    import torch
+    import paper_2506_02023_amd as M
+    ds = np.linspace(0.25, 2.45, 45)
+    pos = np.concatenate([[at, at + d * np.array([np.cos(k), np.sin(k), 0.5]) / np.sqrt(1.25)]
+                          for k, d in enumerate(ds) for at in [np.array([12.0 * (k % 7), 12.0 * (k // 7), 0.0]) + 3.0]])
+    spec, cell = (np.arange(len(pos)) % 4).astype(np.int32), np.diag([84.0, 84.0, 15.0])
+    g = M.mlip_build_graph(torch.as_tensor(pos, device="cuda"), cell, torch.as_tensor(spec, device="cuda"), R_CUT)
+    ref_g = og.build_graph(pos, cell, R_CUT)
+    for seed in (1, 2, 3):
+        for sharper in (1.0, 2.0, 4.0, 8.0, 30.0):
+            way = []
+            for scale in (1.0, 2.0 ** -10, 2.0 ** -19):
+                w = _sharp(F, 3, seed, sharper, scale)
+                W = M.Weights(w, 6)
+                got = _run(g, W, M.MODE_WHOLE)
+                way.append(_by_mlp(g, W, M.MODE_WHOLE))
+            assert way == [way[0]] * 3, (seed, sharper, way)
+            assert way[0] if sharper == 30.0 else not way[0] or sharper > 1.0
+            ref = om.energy_forces(pos, cell, spec, w, ref_g, R_CUT, 8, 6)
+            err = np.abs(got[1] - ref["forces"]).max() / np.abs(ref["forces"]).max()
+            assert err <= 4e-6 + 6 * 0.5 * 3 * 2.0 ** -24 * sharper, (seed, sharper, err)
