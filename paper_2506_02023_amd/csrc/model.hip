@@ -390,7 +390,11 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
     // row-wise kernel adds the lower edges' terms.
     if (L > 0 && (by != BY_TABLE || scratch)) {   // (the fixed block has their place in any case: its limit does not depend on the way)
         prof_begin(g, MLIP_PROF_GRAPH);
-        MLIP_TRY(build_pairs_impl(g, views, P, scratch, scratch ? gate : nullptr, by != BY_TABLE));   // (kept for later calls unless they are carved)
+        // Undecided calls make the lists only if the device says that they are needed where they are carved or long (4.2 M edges, 80 us; four
+        // launches that end at once take 9), and keep those of a smaller graph for the next model of a committee (700,000 edges, 28 us).
+        int64_t edges = 0;
+        for (int p = 0; p < P; ++p) edges += views[p].n_edges;
+        MLIP_TRY(build_pairs_impl(g, views, P, scratch, scratch || edges >= (int64_t)1 << 22 ? gate : nullptr, by != BY_TABLE));
         prof_end(g);
     }
     int64_t n_parts = 0;

@@ -185,3 +185,25 @@ def test_small_features_are_judged_by_themselves(F):
             ref = om.energy_forces(pos, cell, spec, w, ref_g, R_CUT, 8, 6)
             err = np.abs(got[1] - ref["forces"]).max() / np.abs(ref["forces"]).max()
             assert err <= 4e-6 + 6 * 0.5 * 3 * 2.0 ** -24 * sharper, (seed, sharper, err)
+
+
+def test_first_call_on_a_large_graph():
+    """From 4.2 million edges on a first call makes the pair lists only if the device finds that its weights need them: the same results as
+    the calls after it, and the lists are complete when they are asked for."""
+    import torch
+    import paper_2506_02023_amd as M
+    c = wl.make_config(1, n=30)
+    pos, sp = torch.as_tensor(c["positions"], device="cuda"), torch.as_tensor(c["species"], device="cuda")
+    pairs = []
+    for scale in (1.0, 30.0):
+        g = M.mlip_build_graph(pos, c["cell"], sp, c["r_cut"], n_slabs=3)
+        assert g.sizes()[1] >= 1 << 22
+        W = M.Weights(_weights(32, 2, 3, scale), 6)
+        first, again = _run(g, W, M.MODE_SLABS), _run(g, W, M.MODE_SLABS)
+        assert first[0] == again[0] and np.array_equal(first[1], again[1]) and np.array_equal(first[2], again[2])
+        g = M.mlip_build_graph(pos, c["cell"], sp, c["r_cut"], n_slabs=3)
+        _run(g, W, M.MODE_SLABS)
+        pairs.append(g.pairs(1))
+    g = M.mlip_build_graph(pos, c["cell"], sp, c["r_cut"], n_slabs=3)
+    for k, x in g.pairs(1).items():
+        assert np.array_equal(pairs[0][k], x) and np.array_equal(pairs[1][k], x), k
