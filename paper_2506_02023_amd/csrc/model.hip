@@ -423,11 +423,12 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         v.ws.dsum2 = nullptr;
         if (F == 64 && L > 0 && by != BY_MLP) {   // on tables every block of 32 features has its own sums
             if (!scratch) v.ws.dsum2 = v.ws.dsum + 1;
-            // in the fixed block the second ones lie where the way by MLP has its kept filter values (F per pair, at least one per
-            // edge) or, in a model of one layer, its gradients of g: its limit does not depend on the way
+            // in the fixed block, whose limit does not depend on the way, the second ones lie where the way by MLP has its kept filter values
+            // (F per pair, at least one per edge) or, in a model of one layer, its gradients of g or its lists of the upper edges (five
+            // in a row, two of them hold a float per edge)
             else if (L >= 2) v.ws.dsum2 = v.ws.wst;
             else if (v.n_edges <= (int64_t)nl * F) v.ws.dsum2 = v.ws.gbar;
-            else v.ws.dsum2 = static_cast<float *>(scratch->take(ne * sizeof(float)));
+            else if (!v.pairs.valid) v.ws.dsum2 = reinterpret_cast<float *>(v.pairs.u_senders);
         }
         n_parts += (v.n_owned + 31) / 32;
     }
@@ -441,6 +442,16 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         set_error("this graph and model need more than the %zu bytes of static workspace", scratch->size);
         return MLIP_EINVAL;
     }
+    if (scratch && F == 64 && by != BY_MLP)   // one layer, and lists of the handle's that were not carved: theirs would have been the room
+        for (int p = 0; p < P; ++p) {
+            if (views[p].ws.dsum2) continue;
+            views[p].ws.dsum2 = static_cast<float *>(scratch->take((size_t)views[p].n_edges * sizeof(float)));
+            if (scratch->failed()) {   // a call that only fits without them
+                by = BY_MLP;
+                gate = nullptr;
+                break;
+            }
+        }
     double *energy_part = reinterpret_cast<double *>(energy_part_f);
     g->work_ptr = reinterpret_cast<int32_t *>(work_f);
     g->work_next = 0;

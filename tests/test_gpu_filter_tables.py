@@ -207,3 +207,35 @@ def test_first_call_on_a_large_graph():
     g = M.mlip_build_graph(pos, c["cell"], sp, c["r_cut"], n_slabs=3)
     for k, x in g.pairs(1).items():
         assert np.array_equal(pairs[0][k], x) and np.array_equal(pairs[1][k], x), k
+
+
+def test_limit_of_the_fixed_workspace_with_many_edges_and_one_layer():
+    """A graph of 77 edges per atom that fills the 64 MiB but for less than 4 bytes per edge: the second sums per edge of F = 64 take no room of
+    their own.  With the pair lists in the handle already (and so not in the workspace) the call gives the same."""
+    import torch
+    import paper_2506_02023_amd as M
+    F = 64
+    n = (16, 17, 17)
+    corner = np.stack(np.meshgrid(*[np.arange(k) for k in n], indexing="ij"), -1).reshape(-1, 1, 3)
+    fcc = np.array([[0, 0, 0], [0, 0.5, 0.5], [0.5, 0, 0.5], [0.5, 0.5, 0]])
+    pos = 3.0 * (corner + fcc).reshape(-1, 3) + 0.1 * np.random.default_rng(3).standard_normal((4 * n[0] * n[1] * n[2], 3))
+    cell, spec = 3.0 * np.diag(n).astype(np.float64), (np.arange(len(pos)) % 4).astype(np.int32)
+    args = torch.as_tensor(pos, device="cuda"), cell, torch.as_tensor(spec, device="cuda"), R_CUT
+    g = M.mlip_build_graph(*args)
+    N, E, _ = g.sizes()
+    span = 64   # of the pair lists' work-item table, the finest
+    blocks = ([4 * (36864 + 1536 + 12288)]                                          # packed weights
+              + [8 * (N + 1), 4 * E] + 5 * [2 * E] + [4 * (E // 2 // span + 2)]      # upper edges
+              + [8 * (N + 1)] + 2 * [2 * E] + 2 * [4 * (N + 1)] + [2 * (E + 1)]      # lower edges, counts and ranks
+              + 6 * [4 * F * N] + [4 * N, 12 * N, 4 * E] + [N // 4 + 8, 2048])       # node rows, sums
+    need, room = sum((b + 255) // 256 * 256 for b in blocks), M.lib().mlip_static_scratch_bytes()
+    assert E > F * N and room - 4 * E < need <= room - 256, (E / N, need, room)
+    W = M.Weights(_weights(F, 1, 4), 6)
+    want = _run(g, W, M.MODE_WHOLE)
+    for lists in (False, True):
+        g = M.mlip_build_graph(*args)
+        if lists:
+            g.pairs()
+        e, f, a = M.mlip_forward_static(g, W, M.MODE_WHOLE)
+        torch.cuda.synchronize()
+        assert float(e.cpu()[0]) == want[0] and np.array_equal(f.cpu().numpy(), want[1].astype(np.float32))
