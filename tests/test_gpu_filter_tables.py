@@ -189,7 +189,7 @@ def test_small_features_are_judged_by_themselves(F):
 
 def test_first_call_on_a_large_graph():
     """From 4.2 million edges on a first call makes the pair lists only if the device finds that its weights need them: the same results as
-    the calls after it, and the lists are complete when they are asked for."""
+    the calls after it and, rounding apart, as without slabs, and the lists are complete when they are asked for."""
     import torch
     import paper_2506_02023_amd as M
     c = wl.make_config(1, n=30)
@@ -201,6 +201,9 @@ def test_first_call_on_a_large_graph():
         W = M.Weights(_weights(32, 2, 3, scale), 6)
         first, again = _run(g, W, M.MODE_SLABS), _run(g, W, M.MODE_SLABS)
         assert first[0] == again[0] and np.array_equal(first[1], again[1]) and np.array_equal(first[2], again[2])
+        whole = _run(g, W, M.MODE_WHOLE)
+        assert abs(whole[0] - first[0]) <= E_RTOL * np.abs(first[2]).sum()
+        assert np.abs(whole[1] - first[1]).max() <= F_RTOL * np.abs(first[1]).max()
         g = M.mlip_build_graph(pos, c["cell"], sp, c["r_cut"], n_slabs=3)
         _run(g, W, M.MODE_SLABS)
         pairs.append(g.pairs(1))
