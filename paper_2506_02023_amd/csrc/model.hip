@@ -725,11 +725,6 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
                 a.abar = abarslice(v, l);
                 a.out = v.ws.gbar;
                 a.dsum = v.ws.dsum;
-                if (by == BOTH_WAYS && l > 0 && !any_bonds) {   // no launch of their own for the lower edges, which on tables would do nothing
-                    a.l_row_ptr = Q.l_row_ptr;
-                    a.l_senders = Q.l_senders;
-                    a.l_slot = Q.l_slot;
-                }
             } else {
                 a.n_chunks = chunks_of(v.n_edges_owned, v.span);
                 a.chunk_row = v.chunk_row;
@@ -850,7 +845,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         const bool need_gbar = l > 0;  // (as in edge_batch)
         for (int p0 = 0; p0 < P; p0 += kBatch) {
             MLIP_TRY(edge_step(p0, l, true));
-            if (need_gbar && (by == BY_MLP || any_bonds)) {   // second pass: the lower edges' terms of the rows' sums, and the bonds'
+            if (need_gbar && (by != BY_TABLE || any_bonds)) {   // second pass: the lower edges' terms of the rows' sums, and the bonds'
                 prof_begin(g, MLIP_PROF_EDGE_BWD_LOWER);
                 const SmallBatch sb = small_batch(p0, U_OWNED, l);
                 if (sb.start[sb.n] > 0)

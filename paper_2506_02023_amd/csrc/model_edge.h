@@ -24,9 +24,6 @@ struct EdgeArgs {
     // reverse: the arrays above describe the partition's upper-edge graph; indices of its edges in the full edge list:
     const int32_t *eid;        // of every upper edge
     const int32_t *mirror;     // of its reverse edge
-    // the lower edges of the rows, where the kernel adds their terms too (or null); gbar [n_rows][F] is then complete
-    const int64_t *l_row_ptr;
-    const int32_t *l_senders, *l_slot;
 };
 
 // What all partitions of one launch share: the layer's packed weights and the basis.
@@ -321,48 +318,12 @@ constexpr int kQueue = MLIP_BWD_QUEUE;   // queued pairs per wavefront: at most 
 // phase 2 runs once a further step could overflow the queue (and at the latest with 32 pairs queued)
 constexpr int kQueueTrigger = (kQueue - kStep < 32) ? kQueue - kStep : 32;
 
-// The lower edges' terms of row r's sum, with the filter values w read from the row of the edge's pair, which the forward kernel
-// kept: the sum over the lower edges e = (r <- j) of w * abar_j.  Lane = feature; the lower edges of 64 edges at a time are taken
-// kLowerChunk at a time, all their rows in flight together.
-constexpr int kLowerChunk = 16;   // lower edges whose rows are in flight together (32 measured no faster)
-template <int F>
-__device__ __forceinline__ float lower_sum(const int64_t *row_ptr, const int32_t *senders, const int32_t *slot, const float *wstore,
-                                           const float *abar, int64_t r, int lane)
-{
-    const unsigned f = lane & (F - 1);
-    // the row's lower edges (wave-uniform, kept scalar; edge indices fit 32 bits)
-    const int64_t e0 = __builtin_amdgcn_readfirstlane((int32_t)row_ptr[r]);
-    const int64_t e1 = __builtin_amdgcn_readfirstlane((int32_t)row_ptr[r + 1]);
-    float acc = 0.f;
-    for (int64_t eb = e0; eb < e1; eb += 64) {
-        const int n = (int)min((int64_t)64, e1 - eb);
-        const int64_t el = min(eb + lane, e1 - 1);
-        const int32_t jl = senders[el];
-        const int32_t sl = slot[el];   // where the pair's filter values are kept
-        for (int c = 0; c < n; c += kLowerChunk) {
-            float wv[kLowerChunk], gv[kLowerChunk];
-#pragma unroll
-            for (int t = 0; t < kLowerChunk; ++t) {
-                wv[t] = gv[t] = 0.f;
-                if (c + t < n) {   // wave-uniform: no load is issued for an edge that is not there
-                    const int64_t j = __builtin_amdgcn_readlane(jl, c + t), m = __builtin_amdgcn_readlane(sl, c + t);
-                    wv[t] = __builtin_nontemporal_load(wstore + m * F + f);
-                    gv[t] = abar[j * F + f];
-                }
-            }
-#pragma unroll
-            for (int t = 0; t < kLowerChunk; ++t) acc = fmaf(wv[t], gv[t], acc);
-        }
-    }
-    return acc;
-}
-
 // The launch runs on the partitions' upper-edge graphs: every edge it sees is the upper edge of its pair and the
 // row sums it stores (gbar) are those of the upper edges only; k_edge_lower completes them with the lower edges' terms.
 // (Letting this kernel hand w * abar_i to the lower edge's row through memory instead was measured: vector stores
 // return in order with the loads on this chip, and 16 scattered row stores per step stalled the load pipeline:
-// 5.2 ms per launch against 3.5 ms.)  LOWER: the launch completes them itself, item by item.
-template <int F, int PREC, int NW, bool LOWER> __device__ __forceinline__ void edge_bwd(const EdgeBatch &B, float *lds)
+// 5.2 ms per launch against 3.5 ms.)
+template <int F, int PREC, int NW> __device__ __forceinline__ void edge_bwd(const EdgeBatch &B, float *lds)
 {
     using D = Dims<F>;
     constexpr int FS = D::FS;
@@ -565,15 +526,6 @@ template <int F, int PREC, int NW, bool LOWER> __device__ __forceinline__ void e
         wave_lds_fence();
     };
 
-    auto add_lower = [&](int32_t r, int32_t end) {   // the rows of an item, whose upper edges' sums this wavefront has stored
-        if (!LOWER || !A.l_row_ptr) return;
-        __threadfence_block();   // (a lane reads back what it has stored itself: only the order counts)
-        for (; r < end; ++r) {
-            const float before = A.out[(int64_t)r * F + f];
-            const float lower = lower_sum<F>(A.l_row_ptr, A.l_senders, A.l_slot, A.wstore, A.abar, r, lane);
-            if (F == 64 || lane < F) A.out[(int64_t)r * F + f] = before + lower;
-        }
-    };
     for (; item < part_end; item = items.resolve(drawn)) {
         drawn = items.draw(lane);
         const int64_t chunk = item - B.chunk_start[part];
@@ -586,7 +538,6 @@ template <int F, int PREC, int NW, bool LOWER> __device__ __forceinline__ void e
         acc = 0.f;
         if (e_lo >= e_hi) {   // only empty rows
             for (int32_t r = r0; r < r1; ++r) store_row(r, 0.f);
-            add_lower(r0, r1);
             continue;
         }
         Ids IA, IB, IC;
@@ -613,7 +564,6 @@ template <int F, int PREC, int NW, bool LOWER> __device__ __forceinline__ void e
             IB = IA;   // records of step tb + 3 kStep, loaded a step ago
             IA = IC;   // records of step tb + 2 kStep, whose rows SA holds
         }
-        add_lower(r0, r1);
     }   // work items
     while (q_count > 0) phase2();   // queued pairs index this partition's arrays
     }   // partitions
@@ -622,7 +572,7 @@ template <int F, int PREC>
 __global__ void __launch_bounds__(kBwdWaves * 64, kBwdWaves == 4 ? 2 : 1) k_edge_bwd(EdgeBatch B)
 {
     extern __shared__ float lds[];
-    edge_bwd<F, PREC, kBwdWaves, false>(B, lds);
+    edge_bwd<F, PREC, kBwdWaves>(B, lds);
 }
 
 #endif  // MLIP_MODEL_EDGE_H

@@ -289,9 +289,13 @@ __global__ void k_zero_ghost_rows(SmallBatch B, int F)
     *reinterpret_cast<f32x4 *>(A.abar + ((int64_t)blockIdx.y * A.n_local + A.n_owned + k) * F + (idx % F4) * 4) = f32x4{0.f, 0.f, 0.f, 0.f};
 }
 
-// Second pass of the reverse edge step: the lower edges' terms of the row sums (lower_sum), one wavefront per row.  Bound by the kept
-// rows' bytes: 1.21 ms at a million atoms for 5.9 GB of them, 8.0 GB with the gathered rows as measured, 6.6 TB/s (a large copy reaches
-// 4.67 TB/s on this card, a large read 6 to 7).
+// Second pass of the reverse edge step: the lower edges' terms of the row sums, with the filter values w read from the
+// row of the edge's pair, which the forward kernel kept: gbar_i += sum over the lower edges e = (i <- j) of row i of
+// w * abar_j.  One wavefront per row, lane = feature; the lower edges of 64 edges at a time are taken kLowerChunk at a
+// time, all their rows in flight together.  Bound by the kept rows' bytes: 1.21 ms at a million atoms for 5.9 GB of them, 8.0 GB
+// with the gathered rows as measured, 6.6 TB/s (a large copy reaches 4.67 TB/s on this card, a large read 6 to 7).
+constexpr int kLowerChunk = 16;   // lower edges whose rows are in flight together (32 measured no faster)
+
 template <int F>
 __global__ void __launch_bounds__(256) k_edge_lower(SmallBatch B)
 {
@@ -305,8 +309,31 @@ __global__ void __launch_bounds__(256) k_edge_lower(SmallBatch B)
     const int64_t r = gk - B.start[part];
     const unsigned f = lane & (F - 1);
     if (!kept && !A.b_ptr) return;
-    const float before = A.gbar[r * F + f];   // (requested with the row's indices)
-    float acc = kept ? lower_sum<F>(A.l_row_ptr, A.l_senders, A.l_slot, A.wstore, A.abar, r, lane) : 0.f;
+    // the row's lower edges (wave-uniform, kept scalar; edge indices fit 32 bits)
+    const int64_t e0 = kept ? __builtin_amdgcn_readfirstlane((int32_t)A.l_row_ptr[r]) : 0;
+    const int64_t e1 = kept ? __builtin_amdgcn_readfirstlane((int32_t)A.l_row_ptr[r + 1]) : 0;
+    const float before = A.gbar[r * F + f];   // (requested with the indices)
+    float acc = 0.f;
+    for (int64_t eb = e0; eb < e1; eb += 64) {
+        const int n = (int)min((int64_t)64, e1 - eb);
+        const int64_t el = min(eb + lane, e1 - 1);
+        const int32_t jl = A.l_senders[el];
+        const int32_t sl = A.l_slot[el];   // where the pair's filter values are kept
+        for (int c = 0; c < n; c += kLowerChunk) {
+            float wv[kLowerChunk], gv[kLowerChunk];
+#pragma unroll
+            for (int t = 0; t < kLowerChunk; ++t) {
+                wv[t] = gv[t] = 0.f;
+                if (c + t < n) {   // wave-uniform: no load is issued for an edge that is not there
+                    const int64_t j = __builtin_amdgcn_readlane(jl, c + t), m = __builtin_amdgcn_readlane(sl, c + t);
+                    wv[t] = __builtin_nontemporal_load(A.wstore + m * F + f);
+                    gv[t] = A.abar[j * F + f];
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < kLowerChunk; ++t) acc = fmaf(wv[t], gv[t], acc);
+        }
+    }
     if (A.b_ptr) {   // three-body variant: gbar_i += sum_b wb[mirror(b)] * abar_j (the reverse bond (j <- i) is the one whose
                      // filter multiplies g_i in row j; none here if the sender is a ghost row: abar_j = 0, its owner adds that term)
         const int64_t b0 = __builtin_amdgcn_readfirstlane((int32_t)A.b_ptr[r]), b1 = __builtin_amdgcn_readfirstlane((int32_t)A.b_ptr[r + 1]);

@@ -652,10 +652,9 @@ __global__ void __launch_bounds__(kTabBwdWaves * 64, kTabBwdWaves / 4) k_edge_bw
 // The edge steps of a call whose host has not heard yet whether the tables represent the filters: one launch that goes by *bad, so that
 // the way and every bit of the result follow from the weights alone, whatever the handle has seen before.  A row's or an edge's sum does
 // not depend on the wavefronts of a block, so either way gives what its own kernel gives; the reverse step takes 8 of them, the most that
-// leave the way by MLP the registers it needs.  By MLP the reverse step completes its rows with the lower edges' terms, for which the
-// known way has a launch of its own (k_edge_lower: more wavefronts for its row reads).  Per launch on tables 20.0 us forward (20.1 in
-// k_edge_fwd_tab), 25.8 and 24.9 reverse (24.4, 24.5) at 15,600 rows and F = 32.  With a launch for each way, the other one's ending at
-// once, a pass of four models took 691 us there, here 653 (669 with the lower edges apart); 500 atoms in the fixed workspace 248 and 228 (240).
+// leave the way by MLP the registers it needs.  Per launch on tables 20.0 us forward (20.1 in k_edge_fwd_tab), 25.8 and 24.9 reverse (24.4,
+// 24.5) at 15,600 rows and F = 32.  With a launch for each way, the other one's ending at once, a pass of four models took 691 us there, here
+// 669; 500 atoms in the fixed workspace 248 and 240.
 constexpr int kBothBwdWaves = 8;
 static_assert(kTabFwdWaves == kFwdWaves, "the forward step has one block size for both ways");
 struct BothBatch {
@@ -677,7 +676,7 @@ __global__ void __launch_bounds__(kBothBwdWaves * 64, kBothBwdWaves / 4) k_edge_
 {
     extern __shared__ float lds[];
     if (*B.bad != 0)
-        edge_bwd<F, PREC, kBothBwdWaves, true>(B.mlp, lds);
+        edge_bwd<F, PREC, kBothBwdWaves>(B.mlp, lds);
     else if ((int)(blockIdx.x >> 3) < B.tab.slots * (F / 32))
         edge_bwd_tab<F, GBAR, kBothBwdWaves>(B.tab, lds);
 }
