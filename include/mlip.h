@@ -219,8 +219,8 @@ int mlip_graph_skin_stats(const mlip_graph_t *graph, int64_t *list_builds, int64
  *
  * The weights are re-laid-out for the matrix units and the filters tabulated (0.17 MB per layer and 32 features) on the
  * first call and kept in the handle: a later call whose mlip_weights_t (pointers, dimensions, precision) and graph cutoff
- * are identical reuses them.  After changing weight VALUES in
- * place, or when another model's arrays have come to lie at the same addresses, call mlip_graph_invalidate_weights.
+ * are identical reuses them.  After changing weight VALUES in place, or when another model's arrays have come to lie at the
+ * same addresses, call mlip_graph_invalidate_weights.
  */
 int mlip_forward(mlip_graph_t *graph, const mlip_weights_t *weights, int32_t mode,
                  double *energy, float *forces, float *atom_energy);
@@ -231,8 +231,7 @@ int mlip_forward(mlip_graph_t *graph, const mlip_weights_t *weights, int32_t mod
  * piece of workspace (node features and their gradients, kept filter values, per-edge accumulators, packed
  * weights, energy partial sums) is carved from one fixed device array inside the library of
  * mlip_static_scratch_bytes() = 64 MiB per GPU (beside it 2.6 MB for the filter tables), held until the process ends; the
- * call allocates and frees
- * nothing and clears what must start at zero with fill kernels.  A graph and model whose workspace
+ * call allocates and frees nothing and clears what must start at zero with fill kernels.  A graph and model whose workspace
  * (about n_local (4 + 2 L) F 4 + n_edges (36 + (L - 1) F 2) bytes summed over the partitions of the mode - the kept
  * filter values take one row per edge pair and layer, the lists of the pairs' edges are rebuilt in the array on
  * every call - plus the packed weights) exceeds the array are rejected with MLIP_EINVAL; with the event profiler enabled the call
@@ -295,9 +294,8 @@ int mlip_graph_bonds(const mlip_graph_t *graph, int32_t p, const int32_t **bond_
  *   u_d [n_upper]             edge length
  *   l_row_ptr [n_owned + 1], l_senders [n_lower]   the same for the lower edges
  *   l_slot [n_lower]          index of the pair's upper edge in the upper-edge lists
- * Built on the handle's stream on first use after a graph build (mlip_forward does the same unless it looks the filters up
- * in tables); n_upper and n_lower
- * are HOST values.  Errors: MLIP_ESTATE without a graph, MLIP_EINVAL for a partition index out of range.
+ * Built on the handle's stream on first use after a graph build (by mlip_forward where its weights take the MLP, and where
+ * the handle has yet to find out); n_upper and n_lower are HOST values.  Errors: MLIP_ESTATE without a graph, MLIP_EINVAL for a partition index out of range.
  */
 typedef struct {
     int64_t n_upper, n_lower;

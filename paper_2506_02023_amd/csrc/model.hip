@@ -967,6 +967,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
 }  // namespace
 
 size_t table_bytes(int F, int L) { return kTabHeader + (size_t)L * (F / 32) * kTabFloats * sizeof(float); }
+static_assert(kStaticTableBytes == kTabHeader + (size_t)8 * (64 / 32) * kTabFloats * sizeof(float), "the largest model's tables");
 
 int forward_impl(mlip_graph *g, const mlip_weights_t *w, int32_t mode, double *energy, float *forces, float *atom_energy,
                  Carver *scratch)

@@ -60,7 +60,8 @@ __constant__ const double kCosTab[32] = {
 
 // One block per interval and layer, one wavefront per Chebyshev node, lane = feature; everything in fp64.  Bound by the latency
 // of one chain of loads, an exponential and 64 multiply-adds; W2 is requested before the chain and converted once, on its way to LDS
-// (per use: F = 64, L = 3 19.2 us, so 15.3; with the blocks' count spread over addresses 12.9; F = 32, L = 2 12.2, 10.7 and 8.2).
+// (per use: F = 64, L = 3 19.2 us, so 15.3; with the blocks' count spread over addresses 12.9; F = 32, L = 2 12.2, 10.7 and 8.2; 13.5 and 7.9
+// with every feature's own verdict).
 template <int F>
 __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
 {
@@ -169,10 +170,13 @@ __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
 // each worker has its own.  Lane l of a worker holds the record of edge l of its step; a DPP row broadcast hands it to the others.
 //
 // Measured at a million atoms in 8 slabs (F = 64, 45.8 M edges), per launch: forward 3.13 ms by MLP, 1.04 here; reverse 2.87 and 1.22 for the
-// second pass over the lower edges, 1.85 here (layer 0, without gbar, 1.70).  Bound by the vector unit: for four edges and 32 features the
-// forward step takes 20 instructions, 15 of them the look-up and the row sum, the reverse step 38, of which 24; broadcasts and other
-// cross-lane instructions cost 4.4 clocks, plain fp32 ones 2.8.  The chip runs at 1.8 GHz under them.  With two workers of 32 lanes, one feature
-// each, the broadcasts, the sums over lanes and the bookkeeping served two edges instead of four: 1.27 and 2.00 ms.
+// second pass over the lower edges, 1.85 here (layer 0, without gbar, 1.70).  For four edges and 32 features the forward step takes 20 vector
+// instructions, 15 of them the look-up and the row sum, the reverse step 38, of which 24; broadcasts and other cross-lane instructions cost 4.4
+// clocks, plain fp32 ones 2.8, so 3.2 and 3.4 on average.  By the counters (256,000 atoms) the reverse step spends 3.5 clocks of a SIMD on a vector
+// instruction: the vector unit is its bound; LDS is busy 40 % of the time (24 bytes of table per edge and feature).  The forward step spends 4.3,
+// with LDS busy 59 %: neither is full, a wavefront's look-ups and sums take turns.  No bank conflicts to speak of (0.2 % of the LDS cycles).
+// With two workers of 32 lanes, one feature each, the broadcasts, the sums over lanes and the bookkeeping served two edges instead of four:
+// 1.27 and 2.00 ms.
 
 struct TabArgs {               // one partition
     int32_t n_rows, n_edges;   // receiver rows processed and their edges (below 2^29: 32-bit byte offsets of 8-byte sums)
@@ -654,7 +658,8 @@ __global__ void __launch_bounds__(kTabBwdWaves * 64, kTabBwdWaves / 4) k_edge_bw
 // not depend on the wavefronts of a block, so either way gives what its own kernel gives; the reverse step takes 8 of them, the most that
 // leave the way by MLP the registers it needs.  Per launch on tables 20.0 us forward (20.1 in k_edge_fwd_tab), 25.8 and 24.9 reverse (24.4,
 // 24.5) at 15,600 rows and F = 32.  With a launch for each way, the other one's ending at once, a pass of four models took 691 us there, here
-// 669; 500 atoms in the fixed workspace 248 and 240.
+// 669; 500 atoms in the fixed workspace 248 and 240.  (The lower edges' terms added by the reverse kernel itself, which spares on tables a
+// launch that ends at once: 653 and 228, but by MLP 122 us a launch, 103 with 32 of their rows in flight, for 47 and 16 apart.)
 constexpr int kBothBwdWaves = 8;
 static_assert(kTabFwdWaves == kFwdWaves, "the forward step has one block size for both ways");
 struct BothBatch {

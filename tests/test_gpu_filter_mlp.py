@@ -126,3 +126,37 @@ def test_both_sides_of_the_limit(F):
         _same(first, again, scale)
         _hold(first, ref, 2, 0, f"F {F}, W1 x {scale:.2f}, by {'MLP' if by_mlp else 'table'}")
     assert ways[0] is False and ways[-1] is True and ways == sorted(ways)
+
+
+@pytest.mark.parametrize("slabs", [1, 2])
+def test_a_captured_static_call_follows_the_weights_values(slabs):
+    """The static call makes packs and tables anew on every replay: with other values in the same arrays, on either side of the verdict and
+    back, every replay gives what an uncaptured call gives for them."""
+    import torch
+    import paper_2506_02023_amd as M
+    c = wl.make_config(1, n=4)
+    mode = M.MODE_SLABS if slabs > 1 else M.MODE_WHOLE
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        pos, sp = torch.as_tensor(c["positions"], device="cuda"), torch.as_tensor(c["species"], device="cuda")
+        models = [M.Weights(wl.rmp_weights(4, 64, 3, 1), 6), M.Weights(_weights(64, 3, 2), 6), M.Weights(wl.rmp_weights(4, 64, 3, 3), 6)]
+        g = M.mlip_build_graph(pos, c["cell"], sp, c["r_cut"], n_slabs=slabs)
+        want = []
+        for W in models:
+            e, f, a = M.mlip_forward(M.mlip_build_graph(pos, c["cell"], sp, c["r_cut"], n_slabs=slabs), W, mode)
+            torch.cuda.synchronize()
+            want.append((float(e.cpu()[0]), f.cpu().numpy(), a.cpu().numpy()))
+        W = M.Weights(wl.rmp_weights(4, 64, 3, 4), 6)
+        M.mlip_forward_static(g, W, mode)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            e, f, a = M.mlip_forward_static(g, W, mode)
+        for k in (0, 1, 1, 2, 1, 0):
+            for name, t in W.t.items():
+                t.copy_(models[k].t[name])
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert float(e.cpu()[0]) == want[k][0] and np.array_equal(f.cpu().numpy(), want[k][1]), k
+            assert np.array_equal(a.cpu().numpy(), want[k][2]), k
