@@ -412,7 +412,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         MLIP_TRY(place(v.gbar, nl * rowb, v.ws.gbar));
         MLIP_TRY(place(v.eps, no * sizeof(float), v.ws.eps));
         const size_t ne = (size_t)std::max<int64_t>(v.n_edges, 1);
-        MLIP_TRY(place(v.dsum, ne * sizeof(float) * (scratch || by == BY_MLP ? 1 : F / 32), v.ws.dsum));
+        MLIP_TRY(place(v.dsum, ne * sizeof(float) * (scratch ? 1 : F / 32), v.ws.dsum));
         MLIP_TRY(place(v.floc, nl * 3 * sizeof(float), v.ws.floc));
         MLIP_TRY(place(v.g, nl * rowb * (size_t)std::max(L, 1), v.ws.g));
         MLIP_TRY(place(v.a, no * rowb * (size_t)std::max(L, 1), v.ws.a));
