@@ -264,7 +264,7 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
 // scratch != nullptr: every piece of workspace is carved from it (nothing is allocated, nothing cached)
 // bytes of the filter tables of an L-layer model (and of the words in front of them)
 size_t table_bytes(int F, int L);
-constexpr size_t kStaticTableBytes = 2607360;   // table_bytes(64, 8): what the static variant holds beside its workspace
+constexpr size_t kStaticTableBytes = 5212416;   // table_bytes(64, 8): what the static variant holds beside its workspace
 int forward_impl(mlip_graph *g, const mlip_weights_t *w, int32_t mode, double *energy, float *forces,
                  float *atom_energy, Carver *scratch);
 int unpack_shifts(const mlip_graph *g, int32_t *out);

@@ -219,51 +219,57 @@ int64_t upper_edges(const SlabView &v)
     return (v.n_edges_owned - n_ghost_edges) / 2 + n_ghost_edges;
 }
 
-// Rows of an edge step on tables, split over the chip; blocks of `waves` wavefronts.
-template <int F> int plan_edge_tab(mlip_graph *g, TabBatch &b, int waves)
+// Rows of an edge step on tables, split over the chip; blocks of `waves` wavefronts, `blocks` of them for the blocks of features.
+int plan_edge_tab(mlip_graph *g, TabBatch &b, int blocks, int waves)
 {
-    constexpr int NH = F / 32;   // blocks of 32 features, each with a table of its own
     MLIP_TRY(count_compute_units(g));
     // A few rows at a time, so that the rows all workers of an XCD are at, with their neighbours, stay in its L2 (a million atoms: 1.6 GB
     // fetched by a forward launch with two, 8.2 with 22; 1.10 ms with two, 1.12 with one or three, 1.22 with six); one where there
     // are not even eight items for every worker.
     int64_t rows = 0;
     for (int q = 0; q < b.n; ++q) rows += b.s[q].n_rows;
-    const int64_t workers = (int64_t)(g->n_cu / NH) * waves * 4;
+    const int64_t workers = (int64_t)(g->n_cu / blocks) * waves * 4;
     b.rows = (int)std::min<int64_t>(kTabRows, std::max<int64_t>(1, rows / (8 * workers)));
     b.few = rows <= workers;
     b.edge_start[0] = 0;
     for (int q = 0; q < kBatch; ++q) b.edge_start[q + 1] = b.edge_start[q] + (q < b.n ? b.s[q].n_edges : 0);
     // persistent grid: one block per compute unit (the table fills its LDS), fewer where there are not even kTabDeal items for each
     const int64_t items = (rows + b.rows - 1) / b.rows;
-    b.slots = (int)std::max<int64_t>(rows > 0, std::min<int64_t>(g->n_cu / 8 / NH, (items + 8 * kTabDeal - 1) / (8 * kTabDeal)));
+    b.slots = (int)std::max<int64_t>(rows > 0, std::min<int64_t>(g->n_cu / 8 / blocks, (items + 8 * kTabDeal - 1) / (8 * kTabDeal)));
     return MLIP_OK;
 }
 
-// Edge steps on tables, one launch for up to kBatch partitions: the forward kernel or one of the reverse ones.
-template <int F> int launch_edge_tab(mlip_graph *g, TabBatch &b, void (*kernel)(TabBatch), int waves)
+// Edge steps on tables, one launch for up to kBatch partitions.
+template <int F, int KIND> int launch_edge_tab(mlip_graph *g, TabBatch &b)
 {
+    using K = TabKind<F, KIND>;
+    void (*kernel)(TabBatch) = KIND == TAB_FWD ? &k_edge_fwd_tab<F> : KIND == TAB_BWD ? &k_edge_bwd_tab<F> : &k_edge_last_tab<F>;
+    constexpr int waves = (KIND == TAB_FWD ? kTabFwd : KIND == TAB_BWD ? kTabBwd : kTabLast).waves, lds = tab_lds(K::kFloats);
     int slot = 0;
-    MLIP_TRY(configure_kernel(g, reinterpret_cast<const void *>(kernel), kTabLds, &slot));
-    MLIP_TRY(plan_edge_tab<F>(g, b, waves));
+    MLIP_TRY(configure_kernel(g, reinterpret_cast<const void *>(kernel), lds, &slot));
+    b.tab += K::kOffset;
+    MLIP_TRY(plan_edge_tab(g, b, K::kBlocks, waves));
     if (b.slots == 0) return MLIP_OK;
-    kernel<<<(unsigned)(8 * (F / 32) * b.slots), waves * 64, kTabLds, g->stream>>>(b);
+    kernel<<<(unsigned)(8 * K::kBlocks * b.slots), waves * 64, lds, g->stream>>>(b);
     MLIP_HIP(hipGetLastError());
     return MLIP_OK;
 }
 
 // The same with the way left to the device: *bad != 0 by MLP.
-template <int F, int PREC> int launch_edge_both(mlip_graph *g, TabBatch &tab, EdgeBatch &mlp, const int32_t *bad, bool backward)
+template <int F, int PREC, int KIND> int launch_edge_both(mlip_graph *g, TabBatch &tab, EdgeBatch &mlp, const int32_t *bad)
 {
-    void (*kernel)(BothBatch) = !backward ? &k_edge_fwd_both<F, PREC>
-                                : mlp.c.need_gbar ? &k_edge_bwd_both<F, PREC, true> : &k_edge_bwd_both<F, PREC, false>;
-    const int waves = backward ? kBothBwdWaves : kFwdWaves;
-    const size_t lds = std::max<size_t>(kTabLds, backward ? Lds<F>::edge_bwd(PREC, waves) : Lds<F>::edge_fwd(PREC));
+    using K = TabKind<F, KIND>;
+    void (*kernel)(BothBatch);
+    if constexpr (KIND == TAB_FWD) kernel = &k_edge_fwd_both<F, PREC>;
+    else kernel = &k_edge_bwd_both<F, PREC, KIND>;
+    constexpr int waves = KIND == TAB_FWD ? kFwdWaves : kBothBwdWaves;
+    const size_t lds = std::max<size_t>(tab_lds(K::kFloats), KIND == TAB_FWD ? Lds<F>::edge_fwd(PREC) : Lds<F>::edge_bwd(PREC, waves));
     int slot = 0;
     MLIP_TRY(configure_kernel(g, reinterpret_cast<const void *>(kernel), lds, &slot));
-    MLIP_TRY(plan_edge_tab<F>(g, tab, waves));
+    tab.tab += K::kOffset;
+    MLIP_TRY(plan_edge_tab(g, tab, K::kBlocks, waves));
     MLIP_TRY(plan_edge(g, mlp));
-    const int64_t slots = std::max<int64_t>((F / 32) * tab.slots, edge_slots(g, mlp, 1));
+    const int64_t slots = std::max<int64_t>(K::kBlocks * tab.slots, edge_slots(g, mlp, 1));
     if (slots == 0) return MLIP_OK;
     BothBatch b;
     b.tab = tab;
@@ -316,7 +322,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
     }
     TabState *tab_state = reinterpret_cast<TabState *>(tables);
     float *tab0 = reinterpret_cast<float *>(tables + kTabHeader);
-    auto layer_table = [&](int l) { return tab0 + (size_t)l * (F / 32) * kTabFloats; };
+    auto layer_table = [&](int l) { return tab0 + (size_t)l * tab_layer(F); };
     const float tab_inv_h = (float)(kTabUnits / g->r_cut);
     const bool repack = scratch != nullptr || !g->packed_w_valid || std::memcmp(&g->packed_w, w, sizeof(*w)) != 0 || g->table_rcut != g->r_cut;
     const int w2_kind = prec == kPrecBf16 ? PACK_FF_BF16 : prec == kPrecF16x3 ? PACK_FF_F16X2 : PACK_FF_BF16X3;
@@ -383,7 +389,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
     }
     const int32_t *gate = by == BOTH_WAYS ? &tab_state->bad : nullptr;   // != null: the launches look at it
 
-    const int dsum_step = F == 64 && !scratch ? 2 : 1;   // on tables: the halves' sums of an edge side by side, in the fixed block one array each
+    const int dsum_step = F == 64 && L > 1 && !scratch ? 2 : 1;   // on tables: the halves' sums of an edge side by side, in the fixed block one array each
 
     // By MLP: both edges of an edge / reverse-edge pair have the same length, hence bit for bit the same filter values: the
     // forward kernel keeps those of the upper edges, the reverse kernel runs on the partitions' upper-edge graphs and a
@@ -421,15 +427,10 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
                      // the fixed block holds none for it)
             MLIP_TRY(place(v.wst, (size_t)std::max<int64_t>(upper_edges(v), 1) * rowb * (size_t)(scratch ? L - 1 : L), v.ws.wst));
         v.ws.dsum2 = nullptr;
-        if (F == 64 && L > 0 && by != BY_MLP) {   // on tables every block of 32 features has its own sums
-            if (!scratch) v.ws.dsum2 = v.ws.dsum + 1;
-            // in the fixed block, whose limit does not depend on the way, the second ones lie where the way by MLP has its kept filter values
-            // (F per pair, at least one per edge) or, in a model of one layer, its gradients of g or its lists of the upper edges (five
-            // in a row, two of them hold a float per edge)
-            else if (L >= 2) v.ws.dsum2 = v.ws.wst;
-            else if (v.n_edges <= (int64_t)nl * F) v.ws.dsum2 = v.ws.gbar;
-            else if (!v.pairs.valid) v.ws.dsum2 = reinterpret_cast<float *>(v.pairs.u_senders);
-        }
+        if (F == 64 && L > 1 && by != BY_MLP)   // on tables every block of 32 features has its own sums (the one step of a model of one layer takes all
+                                                // 64 at a time); in the fixed block, whose limit does not depend on the way, the second ones
+                                                // lie where the way by MLP has its kept filter values (F per pair, at least one per edge)
+            v.ws.dsum2 = scratch ? v.ws.wst : v.ws.dsum + 1;
         n_parts += (v.n_owned + 31) / 32;
     }
     float *energy_part_f = nullptr;
@@ -442,16 +443,6 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         set_error("this graph and model need more than the %zu bytes of static workspace", scratch->size);
         return MLIP_EINVAL;
     }
-    if (scratch && F == 64 && by != BY_MLP)   // one layer, and lists of the handle's that were not carved: theirs would have been the room
-        for (int p = 0; p < P; ++p) {
-            if (views[p].ws.dsum2) continue;
-            views[p].ws.dsum2 = static_cast<float *>(scratch->take((size_t)views[p].n_edges * sizeof(float)));
-            if (scratch->failed()) {   // a call that only fits without them
-                by = BY_MLP;
-                gate = nullptr;
-                break;
-            }
-        }
     double *energy_part = reinterpret_cast<double *>(energy_part_f);
     g->work_ptr = reinterpret_cast<int32_t *>(work_f);
     g->work_next = 0;
@@ -683,7 +674,6 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             a.chunk_row = v.chunk_row;
             a.span = v.span;
             a.senders = v.senders;
-            a.recv = v.recv;
             a.d = v.d;
             a.g = gslice(v, l);
             a.abar = backward ? abarslice(v, l) : nullptr;
@@ -744,10 +734,14 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         EdgeBatch mlp{};
         if (by != BY_MLP) tab = tab_batch(p0, l, backward);
         if (by != BY_TABLE) mlp = edge_batch(p0, l, backward);
-        if (by == BOTH_WAYS) return launch_edge_both<F, PREC>(g, tab, mlp, gate, backward);
         if (by == BY_MLP) return launch_edge<F, PREC>(g, mlp, backward);
-        if (!backward) return launch_edge_tab<F>(g, tab, &k_edge_fwd_tab<F>, kTabFwdWaves);
-        return launch_edge_tab<F>(g, tab, l > 0 ? &k_edge_bwd_tab<F, true> : &k_edge_bwd_tab<F, false>, kTabBwdWaves);
+        auto on_tables = [&](auto kind) {
+            constexpr int KIND = decltype(kind)::value;
+            return by == BOTH_WAYS ? launch_edge_both<F, PREC, KIND>(g, tab, mlp, gate) : launch_edge_tab<F, KIND>(g, tab);
+        };
+        if (!backward) return on_tables(std::integral_constant<int, TAB_FWD>{});
+        if (l > 0) return on_tables(std::integral_constant<int, TAB_BWD>{});
+        return on_tables(std::integral_constant<int, TAB_LAST>{});
     };
     auto edge_step = [&](int p0, int l, bool backward) -> int {   // of up to kBatch partitions from p0 on
         prof_begin(g, backward ? MLIP_PROF_EDGE_BWD : MLIP_PROF_EDGE_FWD);
@@ -966,8 +960,8 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
 
 }  // namespace
 
-size_t table_bytes(int F, int L) { return kTabHeader + (size_t)L * (F / 32) * kTabFloats * sizeof(float); }
-static_assert(kStaticTableBytes == kTabHeader + (size_t)8 * (64 / 32) * kTabFloats * sizeof(float), "the largest model's tables");
+size_t table_bytes(int F, int L) { return kTabHeader + (size_t)L * tab_layer(F) * sizeof(float); }
+static_assert(kStaticTableBytes == kTabHeader + (size_t)8 * tab_layer(64) * sizeof(float), "the largest model's tables");
 
 int forward_impl(mlip_graph *g, const mlip_weights_t *w, int32_t mode, double *energy, float *forces, float *atom_energy,
                  Carver *scratch)

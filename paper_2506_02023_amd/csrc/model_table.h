@@ -1,6 +1,6 @@
 // Edge kernels on tabulated filters.  The filter w(d) = SiLU(b(d) W1) W2 of a layer is a function of the edge length alone, smooth
-// on [0, rc], so its F values are kept as piecewise polynomials in LDS and an edge costs a look-up instead of a filter MLP:
-// the forward and the reverse step walk the full edge lists once per layer, nothing is kept between them and no pair lists are needed.
+// on [0, rc], so its F values and their slopes are kept as piecewise polynomials and an edge costs a look-up in LDS instead of a filter
+// MLP: the forward and the reverse step walk the edge lists, nothing is kept between them and no pair lists are needed.
 // Part of model.hip (one translation unit): included inside namespace mlip, anonymous namespace.
 #ifndef MLIP_MODEL_TABLE_H
 #define MLIP_MODEL_TABLE_H
@@ -9,25 +9,55 @@
 
 // ---------------------------------------------------------------- the table
 //
-// kTabN intervals over [0, rc], degree 5 in the local coordinate s in [-1, 1], fp32 coefficients computed in fp64.  In units of rc /
-// kTabUnits the intervals have the length 1/2 below kTabSmall (at short distances the basis functions are large and SiLU bends most), 1/4
-// from kTabEnd on (at the cutoff the filter vanishes with its first three derivatives, so its error has to vanish too) and 1 between. What
-// is cut off is below what the evaluation of the MLP in fp32 rounds, feature by feature (checked when the table is made, see k_filter_table);
-// coefficients and evaluation round to 4e-8 (values) and 5e-8 (slopes) of the filter, the fp32 evaluation of the MLP to 1.7e-7 of both.
-// kTabUnits and kTabSmall share the intervals out between short lengths and the rest: of 300 random layers with W1 of variance 1/8 all
-// are represented at rc 4.5 to 5.5, 96 % at F = 64 with one and a half times that W1 or with rc 3 (the same thing: the basis goes as 1 / d), 68 %
-// with twice at 4.5, 83 % at 5 (179 and 27 in their place, features pooled: 97 to 100 %, 56 %, 10 %, 21 %).
-// One block of 32 features is 768 bytes per interval, [3][16][2][2]: coefficients 2 q and 2 q + 1 of features l and l + 16, 16 bytes for one lane; 162,816
-// bytes of the compute unit's 160 KB.  With F = 64 every block of the grid holds the table of one half of the features.
-constexpr int kTabUnits = 160, kTabSmall = 46, kTabEnd = kTabUnits - 2;
-constexpr int kTabM0 = 2 * kTabSmall, kTabE0 = kTabM0 + kTabEnd - kTabSmall, kTabN = kTabE0 + 4 * (kTabUnits - kTabEnd);
-constexpr int kTabStride = 32 * 6 * 4;                   // bytes of an interval
-constexpr int kTabFloats = kTabN * kTabStride / 4;       // floats of one block of 32 features
-constexpr int kTabLds = kTabFloats * 4 + 32;             // the table and a work counter per partition of the launch
+// Polynomials of degree 5 in the local coordinate s in [-1, 1] on intervals of [0, rc], fp32 coefficients computed in fp64.  [0, rc] is cut
+// into 64 units of one length, a unit into 1 to 10 intervals (kTabPer): many where the filters of ordinary weights bend most (from rc/16 to
+// rc/5) and at the cutoff, where the filter vanishes with its first three derivatives, so that its error has to vanish too.  Three tables a
+// layer, for the three kinds of steps:
+//   values  w, kTabN intervals, for all F features: the forward step needs nothing else;
+//   slopes  dw/dd, the same intervals, for all F features: the last reverse step (layer 0), which needs no sums over rows;
+//   both    w on intervals half as long, 32 features at a time: the other reverse steps take w and, as the polynomial's derivative, dw/dd.
+// A derivative is as good as a polynomial of its own only on intervals 0.55 times as long, and the table has to fit LDS: one that serves for
+// both holds 32 features, the other two all 64, which spares an edge's second look at its record and its broadcasts (20 vector instructions
+// for four edges and 32 features, 17 with 64 at a time).  What is cut off is below what the evaluation of the MLP in fp32 rounds, feature by
+// feature (checked when the tables are made, see k_filter_table); coefficients and evaluation round to 3.6e-8 of values and slopes (5e-8 of the
+// slopes as a derivative), the fp32 evaluation of the MLP to 1.7e-7 of both.
+// An interval is, for 64 features, [6 coefficients][64], for 32 features [3][16 lanes][2 coefficients][2 features]: 16 bytes of a lane at a
+// time, 16 lanes 256 bytes of a row.  Values or slopes of F = 64 and both of 32 features take 162,816 bytes of the compute unit's 160 KB.
+constexpr int kTabUnits = 64, kTabN = 106;
+constexpr int kTabPer[kTabUnits] = {1, 1, 2, 2, 2, 3, 3, 4, 4, 4, 3, 2, 2, 2, 2, 2, 2, 2, 2, 2, 2, 2, 2, 2, 2, 1, 1, 1, 1, 1, 1, 1,
+                                    1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 2, 10};
+struct TabGrid {
+    struct Unit { float n, at; } unit[kTabUnits];   // its intervals and the first one's number
+    int unit_of[kTabN];
+};
+constexpr TabGrid make_tab_grid()
+{
+    TabGrid G{};
+    int at = 0;
+    for (int j = 0; j < kTabUnits; ++j) {
+        G.unit[j].n = (float)kTabPer[j];
+        G.unit[j].at = (float)at;
+        for (int i = 0; i < kTabPer[j]; ++i) G.unit_of[at++] = j;
+    }
+    return G;
+}
+constexpr int tab_intervals()
+{
+    int n = 0;
+    for (int j = 0; j < kTabUnits; ++j) n += kTabPer[j];
+    return n;
+}
+static_assert(tab_intervals() == kTabN, "the units' intervals");
+__constant__ const TabGrid kTabGrid = make_tab_grid();
+constexpr int tab_floats(int F) { return kTabN * F * 6; }               // of the values or the slopes
+constexpr int tab_layer(int F) { return 4 * tab_floats(F); }            // of a layer: values, slopes, both
+constexpr int kTabLut = kTabUnits * (int)sizeof(TabGrid::Unit);         // the units, behind the table in LDS
+constexpr int kTabBothFloats = 2 * kTabN * 32 * 6;                      // of both for 32 features
+constexpr int tab_lds(int floats) { return floats * 4 + kTabLut + 32; } // and a work counter per partition of the launch
 constexpr int kTabCounters = 16;                         // counters of k_filter_table's blocks, each on a cache line of its own
 constexpr int kTabHeader = 256 + 128 * kTabCounters;     // bytes in front of the first table: TabState, then those counters
 constexpr int kTabNodes = 8;                             // Chebyshev nodes of an interval: coefficients 0..7, 6 and 7 measure what is cut off
-static_assert(kTabLds <= 160 * 1024, "the table has to fit a compute unit's LDS");
+static_assert(tab_lds(tab_floats(64)) <= 160 * 1024 && tab_lds(kTabBothFloats) <= 160 * 1024, "the table has to fit a compute unit's LDS");
 
 // Whether the tables of a model represent its filters, and the handshake that tells the host.
 struct TabState {
@@ -39,7 +69,7 @@ constexpr int32_t kTabBad = 1 << 16;
 
 struct TabJob {
     const float *W1, *W2;   // [L][8][F], [L][F][F]
-    float *tab;             // [L][F / 32][kTabFloats]
+    float *tab;             // [L][tab_layer(F)]: values, slopes, both
     TabState *state;
     int64_t *publish;       // pinned host word: generation * 2 + bad, written when the last block is through
     int64_t generation;
@@ -59,18 +89,21 @@ __constant__ const double kCosTab[32] = {
     0.83146961230254523708, 0.92387953251128675613, 0.98078528040323044913};
 
 // One block per interval and layer, one wavefront per Chebyshev node, lane = feature; everything in fp64.  Bound by the latency
-// of one chain of loads, an exponential and 64 multiply-adds; W2 is requested before the chain and converted once, on its way to LDS
-// (per use: F = 64, L = 3 19.2 us, so 15.3; with the blocks' count spread over addresses 12.9; F = 32, L = 2 12.2, 10.7 and 8.2; 13.5 and 7.9
-// with every feature's own verdict).
+// of one chain of loads, an exponential and 64 multiply-adds; W2 is requested before the chain and converted once, on its way to LDS.
 template <int F>
 __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
 {
-    __shared__ double sv[kTabNodes][64], wv[kTabNodes][64], uv[kTabNodes][64], gv[kTabNodes][64];
-    __shared__ double W2[F * F];
+    __shared__ double sv[kTabNodes][64], wv[kTabNodes][64], uv[kTabNodes][64], gv[kTabNodes][64], slope_g[kTabNodes];
+    __shared__ double W2[F * F], half[2][kTabNodes][64];
+    __shared__ int any_bad;
     const int iv = blockIdx.x, layer = blockIdx.y;
     const int node = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, f = lane & (F - 1);
-    const double lo = iv < kTabM0 ? 0.5 * iv : iv < kTabE0 ? kTabSmall + (iv - kTabM0) : kTabEnd + 0.25 * (iv - kTabE0);
-    const double wd = iv < kTabM0 ? 0.5 : iv < kTabE0 ? 1.0 : 0.25;
+    // The place s of the interval as the edge kernels compute it from a length d: d * per_d - at, the product's factor rounded to fp32.
+    const TabGrid::Unit unit = kTabGrid.unit[kTabGrid.unit_of[iv]];
+    if (threadIdx.x == 0) any_bad = 0;
+    const double per_d = (double)(2.0f * (float)J.inv_h * unit.n), at = 2.0 * (kTabGrid.unit_of[iv] * (double)unit.n + iv - (double)unit.at) + 1.0;
+    auto length = [&](double s) { return fmin((s + at) / per_d, J.rc); };
+    auto kappa = [&](double d) { return 8 * 3.141592653589793 / J.rc + 4.0 / (J.rc - d); };   // (see the verdict below)
     float w1[8];
 #pragma unroll
     for (int n = 0; n < 8; ++n) w1[n] = J.W1[((size_t)layer * 8 + n) * F + f];
@@ -78,8 +111,8 @@ __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
 #pragma unroll
     for (int i = 0; i < F * F / (kTabNodes * 64); ++i) w2[i] = J.W2[(size_t)layer * F * F + i * kTabNodes * 64 + threadIdx.x];
     {   // t_k = sum_n b_n(d) W1[n][k], s_k = SiLU(t_k)
-        const double d = (lo + wd * (0.5 + 0.5 * kCosTab[2 * node + 1])) / J.inv_h;
-        const double x = fmin(d / J.rc, 1.0), y = 1.0 - x;
+        const double d = length(kCosTab[2 * node + 1]);
+        const double x = d / J.rc, y = 1.0 - x;
         double q = 0.5 * J.p * (J.p + 1);
         for (int k = J.p - 2; k >= 0; --k) q = q * x + 0.5 * (k + 1) * (k + 2);
         const double u = y * y * y * q / d;   // the envelope in its factored form, over d
@@ -98,6 +131,7 @@ __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
         const double sg = 1.0 / (1.0 + exp(-t)), slope = sg * (1.0 + t * (1.0 - sg));
         sv[node][lane] = t * sg;
         uv[node][lane] = tt * (slope * slope + 1.0 / 16);   // (see the verdict below)
+        if (lane == 0) slope_g[node] = kappa(d) * kappa(d);
     }
 #pragma unroll
     for (int i = 0; i < F * F / (kTabNodes * 64); ++i)
@@ -115,37 +149,71 @@ __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
         gv[node][lane] = g;
     }
     __syncthreads();
-    double a = 0;   // Chebyshev coefficient `node` of this lane's feature
+    auto coefficient = [&](const double (&v)[kTabNodes][64]) {   // Chebyshev coefficient `node` of this lane's feature, of the values at the nodes
+        double a = 0;
 #pragma unroll
-    for (int j = 0; j < kTabNodes; ++j) a += wv[j][lane] * kCosTab[node * (2 * j + 1) % 32];
-    a *= node == 0 ? 1.0 / kTabNodes : 2.0 / kTabNodes;
+        for (int j = 0; j < kTabNodes; ++j) a += v[j][lane] * kCosTab[node * (2 * j + 1) % 32];
+        return a * (node == 0 ? 1.0 / kTabNodes : 2.0 / kTabNodes);
+    };
+    sv[node][lane] = coefficient(wv);
     __syncthreads();
-    sv[node][lane] = a;
+    {   // at the nodes: dw/dd, T_m'(cos t) = m sin(m t) / sin t; at those of the interval's halves: w
+        double dw = 0, h0 = 0, h1 = 0, hp0 = 0, hp1 = 0;
+#pragma unroll
+        for (int m = 1; m < kTabNodes; ++m) dw += sv[m][lane] * (m * kCosTab[(m * (2 * node + 1) + 24) % 32]);
+        const double x0 = 0.5 * (kCosTab[2 * node + 1] - 1.0), x1 = x0 + 1.0;
+#pragma unroll
+        for (int m = kTabNodes - 1; m >= 0; --m) {   // Clenshaw, one step late: (h, its predecessor) in hp
+            const double a = sv[m][lane], n0 = a + 2.0 * x0 * h0 - hp0, n1 = a + 2.0 * x1 * h1 - hp1;
+            hp0 = h0;
+            hp1 = h1;
+            h0 = n0;
+            h1 = n1;
+        }
+        wv[node][lane] = dw / kCosTab[(2 * node + 25) % 32] * per_d;
+        half[0][node][lane] = h0 - x0 * hp0;
+        half[1][node][lane] = h1 - x1 * hp1;
+    }
+    __syncthreads();
+    uv[node][lane] = coefficient(wv);
+    const double half0 = coefficient(half[0]), half1 = coefficient(half[1]);
+    __syncthreads();
+    half[0][node][lane] = half0;
+    half[1][node][lane] = half1;
+    __syncthreads();
+    // What is cut off: a6 T6 + a7 T7 of the values and of the slopes, a6 + a7 at most; of a derivative 8 a6 + 10 a7 (root mean squares of T6' and
+    // T7').  Every feature is held to what the fp32 evaluation of the MLP rounds of it, 1e-7 of G, G^2 = sum_k W2[k][f]^2 tau_k^2 SiLU'(t_k)^2,
+    // tau_k^2 the sum of the squares of t_k's eight terms, and for the slopes 1e-7 kappa G, kappa what a basis function grows by along a unit
+    // of length relative to itself: 8 pi / rc from the sine, 4 / (rc - d) where it vanishes as (rc - d)^4; further to what the length's
+    // rounding to fp32, half an ulp, changes on average: 2^-26 of the length times kappa.  Where SiLU' is near zero a sixteenth stands for
+    // SiLU'^2: there the feature is small beside what it is elsewhere (a unit's t goes to 0 at the cutoff, so -0.28 is always passed).  G
+    // goes with the feature's column of W2: scaling that against the later maps does not change the verdict.
+    if (node < 4) {   // the wavefronts' tables: values, slopes, both on either half
+        const double(&a)[kTabNodes][64] = node == 0 ? sv : node == 1 ? uv : half[node - 2];
+        const double a0 = a[0][lane], a1 = a[1][lane], a2 = a[2][lane], a3 = a[3][lane], a4 = a[4][lane], a5 = a[5][lane];
+        const double c[6] = {a0 - a2 + a4, a1 - 3 * a3 + 5 * a5, 2 * a2 - 8 * a4, 4 * a3 - 20 * a5, 8 * a4, 16 * a5};
+        if (lane < F) {
+            float *to = J.tab + (size_t)layer * tab_layer(F);
+            const int of_lane = 4 * (lane % 32 / 2) + lane % 2;   // 32 features: where the lane's lie in [16][2][2]
+            to += node >= 2 ? 2 * tab_floats(F) + lane / 32 * kTabBothFloats + (2 * iv + node - 2) * 192 + of_lane
+                            : node * tab_floats(F) + iv * (F * 6) + (F == 64 ? lane : of_lane);
+            const bool wide = F == 64 && node < 2;
+#pragma unroll
+            for (int k = 0; k < 6; ++k) to[wide ? 64 * k : 64 * (k / 2) + 2 * (k % 2)] = (float)c[k];
+        }
+        double g2 = 0;
+#pragma unroll
+        for (int j = 0; j < kTabNodes; ++j) g2 += gv[j][lane] * (node == 1 ? slope_g[j] : 1.0) * (1.0 / kTabNodes);
+        const double mid = length(node == 2 ? -0.5 : node == 3 ? 0.5 : 0.0), rounding = 0x1p-26 * mid * kappa(mid);
+        const double a6 = fabs(a[6][lane]), a7 = fabs(a[7][lane]);
+        // (a place grows by 2 per_d along a unit of length in a half)
+        const double cut = node < 2 ? a6 + a7 : fmax(a6 + a7, (8 * a6 + 10 * a7) * 2 * per_d / kappa(mid));
+        const bool feature_bad = !(cut * cut <= g2 * (1e-14 + rounding * rounding));   // (not a number: not represented)
+        if (__any(feature_bad) && lane == 0) any_bad = 1;
+    }
     __syncthreads();
     if (node != 0) return;
-    const double a0 = sv[0][lane], a1 = sv[1][lane], a2 = sv[2][lane], a3 = sv[3][lane], a4 = sv[4][lane], a5 = sv[5][lane],
-                 a6 = fabs(sv[6][lane]), a7 = fabs(sv[7][lane]);
-    const double c[6] = {a0 - a2 + a4, a1 - 3 * a3 + 5 * a5, 2 * a2 - 8 * a4, 4 * a3 - 20 * a5, 8 * a4, 16 * a5};
-    if (lane < F) {
-        float *at = J.tab + ((size_t)layer * (F / 32) + (lane >> 5)) * kTabFloats + (size_t)iv * (kTabStride / 4);
-        const int l = lane & 31;
-        for (int k = 0; k < 6; ++k) at[64 * (k / 2) + 4 * (l % 16) + 2 * (k % 2) + l / 16] = (float)c[k];
-    }
-    // What is cut off: a6 T6 + a7 T7 of the values, root mean square a6 + a7 at most, and 8 a6 + 10 a7 of the slopes (rms of T6' and T7').
-    // Every feature is held to what the fp32 evaluation of the MLP rounds of it, 1e-7 of G, G^2 = sum_k W2[k][f]^2 tau_k^2 SiLU'(t_k)^2, tau_k^2 the
-    // sum of the squares of t_k's eight terms, and for the slopes 1e-7 kappa G, kappa what a basis function grows by along a unit of length relative
-    // to itself: 8 pi / rc from the sine, 4 / (rc - d) where it vanishes as (rc - d)^4; further to what the length's rounding to fp32, half an
-    // ulp, changes on average: 2^-26 of the length times kappa.  Where SiLU' is near zero a sixteenth stands for SiLU'^2: there the feature is small
-    // beside what it is elsewhere (a unit's t goes to 0 at the cutoff, so -0.28 is always passed).  G goes with the feature's column of W2:
-    // scaling that against the later maps does not change the verdict.
-    double g2 = 0;
-#pragma unroll
-    for (int j = 0; j < kTabNodes; ++j) g2 += gv[j][lane] * (1.0 / kTabNodes);
-    const double mid = lo + 0.5 * wd, kappa = (8 * 3.141592653589793 / kTabUnits + 4.0 / (kTabUnits - mid)) * 0.5 * wd;   // in units of s
-    const double rounding = 0x1p-26 * 2 * mid / wd * kappa;
-    const double cut = fmax(a6 + a7, (8 * a6 + 10 * a7) / kappa);
-    const bool feature_bad = !(cut * cut <= g2 * (1e-14 + rounding * rounding));   // (not a number: not represented)
-    const bool bad = __any(feature_bad);
+    const bool bad = any_bad != 0;
     if (lane == 0) {
         if (bad) J.state->bad = 1;
         // A word counts blocks and the bad ones among them, so that the last one needs no fence to know.  The blocks are spread over
@@ -165,18 +233,14 @@ __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
 
 // ---------------------------------------------------------------- edge steps
 //
-// A wavefront is four workers of 16 lanes, lane = two features of the block's 32.  A worker walks work items, each a few consecutive rows, in steps
-// of 16 edges; items follow one another without a break in the pipeline (records two steps ahead, gathered rows one), and
-// each worker has its own.  Lane l of a worker holds the record of edge l of its step; a DPP row broadcast hands it to the others.
+// A wavefront is four workers of 16 lanes, lane = neighbouring features.  A worker walks work items, each one or two rows, in steps of 16 edges;
+// items follow one another without a break in the pipeline (records two steps ahead, gathered rows a few edges), and each worker has its
+// own.  Lane l of a worker holds the record of edge l of its step; a DPP row broadcast hands it to the others.
 //
-// Measured at a million atoms in 8 slabs (F = 64, 45.8 M edges), per launch: forward 3.13 ms by MLP, 1.04 here; reverse 2.87 and 1.22 for the
-// second pass over the lower edges, 1.85 here (layer 0, without gbar, 1.70).  For four edges and 32 features the forward step takes 20 vector
-// instructions, 15 of them the look-up and the row sum, the reverse step 38, of which 24; broadcasts and other cross-lane instructions cost 4.4
-// clocks, plain fp32 ones 2.8, so 3.2 and 3.4 on average.  By the counters (256,000 atoms) the reverse step spends 3.5 clocks of a SIMD on a vector
-// instruction: the vector unit is its bound; LDS is busy 40 % of the time (24 bytes of table per edge and feature).  The forward step spends 4.3,
-// with LDS busy 59 %: neither is full, a wavefront's look-ups and sums take turns.  No bank conflicts to speak of (0.2 % of the LDS cycles).
-// With two workers of 32 lanes, one feature each, the broadcasts, the sums over lanes and the bookkeeping served two edges instead of four:
-// 1.27 and 2.00 ms.
+// What a step costs (measured one thing at a time): a wavefront issues a vector instruction every 5 clocks, one that takes its
+// predecessor's result every 8.25, a DPP one every 8, and a SIMD issues two of them at a time, whatever the number of wavefronts; LDS reads 256
+// bytes a clock with 16-byte reads, less than half of that with 8-byte ones; a row of 256 bytes takes the vector-memory path 4.2
+// clocks where it lies in the L2, whatever the width of the load, and a store of 4 bytes a lane as much as one of 16.
 
 struct TabArgs {               // one partition
     int32_t n_rows, n_edges;   // receiver rows processed and their edges (below 2^29: 32-bit byte offsets of 8-byte sums)
@@ -185,15 +249,15 @@ struct TabArgs {               // one partition
     const int64_t *row_ptr;
     const int32_t *chunk_row;  // the graph's work-item table: first row whose first edge lies at or after c * span
     int32_t span;
-    const int32_t *senders, *recv;
+    const int32_t *senders;
     const float *d, *g, *abar;
     float *out;                // forward: a [n_rows][F]; reverse: gbar [n_rows][F]
     float *dsum[2];            // reverse: per edge its share of dE/dd, summed over the layers, of each block of 32 features
 };
 struct TabBatch {
-    const float *tab;      // the layer's table
+    const float *tab;      // the layer's table of the step's kind
     float inv_h;
-    int slots;             // blocks of an XCD for each block of 32 features; blocks beyond them have no rows
+    int slots;             // blocks of an XCD for each block of features; blocks beyond them have no rows
     int rows;              // rows of a work item
     int few;               // few rows for the workers: every XCD takes rows of one partition, 8 / n XCDs each
     int first;             // reverse: dsum is written, not added to
@@ -201,138 +265,238 @@ struct TabBatch {
     int64_t edge_start[kBatch + 1];
     TabArgs s[kBatch];
 };
-#ifndef MLIP_TAB_FWD_WAVES
-#define MLIP_TAB_FWD_WAVES 12
+// Wavefronts per block, values that are computed together (of one edge or of several), and edges whose rows are on their way.
+#ifndef MLIP_TAB_FWD
+#define MLIP_TAB_FWD 16, 8, 4
 #endif
-#ifndef MLIP_TAB_BWD_WAVES
-#define MLIP_TAB_BWD_WAVES 12
+#ifndef MLIP_TAB_BWD
+#define MLIP_TAB_BWD 16, 4, 8
 #endif
-#ifndef MLIP_TAB_GROUP
-#define MLIP_TAB_GROUP 4
+#ifndef MLIP_TAB_LAST
+#define MLIP_TAB_LAST 12, 8, 8
 #endif
-#ifndef MLIP_TAB_ROWS
-#define MLIP_TAB_ROWS 2
-#endif
-constexpr int kTabRows = MLIP_TAB_ROWS;     // most rows of a work item
-constexpr int kTabGroup = MLIP_TAB_GROUP;   // edges whose values are computed together (8: the reverse step spills, 4 % slower; 2: 4 % slower)
-constexpr int kTabFwdWaves = MLIP_TAB_FWD_WAVES, kTabBwdWaves = MLIP_TAB_BWD_WAVES;
+struct TabShape { int waves, values, ring; };
+constexpr TabShape kTabFwd = {MLIP_TAB_FWD}, kTabBwd = {MLIP_TAB_BWD}, kTabLast = {MLIP_TAB_LAST};
+constexpr int kTabRows = 2;     // most rows of a work item
+enum { TAB_FWD, TAB_BWD, TAB_LAST };   // the forward step, a reverse step, the reverse step of layer 0 (no sums over rows)
+template <int F, int KIND> struct TabKind {
+    static constexpr int kI = KIND == TAB_BWD ? 2 : F / 16;              // features of a lane
+    static constexpr int kBlocks = F / (16 * kI);                        // blocks of features, each with a table of its own
+    static constexpr int kFloats = KIND == TAB_BWD ? kTabBothFloats : tab_floats(F);
+    static constexpr int kPerUnit = KIND == TAB_BWD ? 2 : 1;             // its intervals to one of the grid
+    static constexpr int kOffset = KIND == TAB_FWD ? 0 : KIND == TAB_LAST ? tab_floats(F) : 2 * tab_floats(F);   // in the layer's tables
+};
 
 template <int K> __device__ inline int row_bcast(int v) { return __builtin_amdgcn_mov_dpp(v, 0x150 + K, 0xf, 0xf, true); }
 template <int K> __device__ inline float row_bcast(float v)
 {
     return __builtin_bit_cast(float, row_bcast<K>(__builtin_bit_cast(int, v)));
 }
-__device__ inline void pin(float &v) { asm volatile("" : "+v"(v)); }   // v is computed by here, not where it is used
 template <class Fn, int... K> __device__ __forceinline__ void unrolled(std::integer_sequence<int, K...>, Fn fn)
 {
     (fn(std::integral_constant<int, K>{}), ...);
 }
+template <int N, class Fn> __device__ __forceinline__ void unrolled(Fn fn) { unrolled(std::make_integer_sequence<int, N>{}, fn); }
+// All N values are computed by here, and nothing is done with one of them before: what is done step by step for N values stays so (left alone,
+// the compiler puts the steps for one value behind one another).
+template <int N> __device__ __forceinline__ void fence(float *v)
+{
+    static_assert(N == 1 || N % 2 == 0);
+    if constexpr (N == 1) asm volatile("" : "+v"(v[0]));
+    else if constexpr (N == 2) asm volatile("" : "+v"(v[0]), "+v"(v[1]));
+    else if constexpr (N == 4) asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]));
+    else {
+        asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]));
+        if constexpr (N > 8) fence<N - 8>(v + 8);
+    }
+}
 
-struct TabRec {      // as loaded
-    int32_t sj, rk;
-    float d, before; // before: reverse, the sum of the later layers at edge tb + k_out
+// I neighbouring features of a row, the lane's, at byte offset off
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+template <int I> struct TabRow {
+    typedef float vec __attribute__((ext_vector_type(I)));
+    float v[I];
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t off)
+    {
+        vec x;
+        if constexpr (I == 4) x = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+        else x = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+#pragma unroll
+        for (int i = 0; i < I; ++i) v[i] = x[i];
+    }
+    __device__ __forceinline__ void store(__amdgpu_buffer_rsrc_t r, uint32_t off) const
+    {
+        vec x;
+#pragma unroll
+        for (int i = 0; i < I; ++i) x[i] = v[i];
+        if constexpr (I == 4) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), r, off, 0, 0);
+        else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), r, off, 0, 0);
+    }
+    __device__ __forceinline__ void clear()
+    {
+#pragma unroll
+        for (int i = 0; i < I; ++i) v[i] = 0.f;
+    }
 };
-struct TabStep {     // one step of a worker
-    int32_t tb, last;   // first edge, the item's last edge
-    int32_t r1;         // the row after the item's
-    int32_t r0;         // the item's first row if this is its first step, or 2^31 - 1
+// the six coefficients of the lane's I features in an interval
+template <int I> struct TabCoeff {
+    f32x4 q[I * 6 / 4];
+    __device__ __forceinline__ void read(const char *at)
+    {
+#pragma unroll
+        for (int i = 0; i < I * 6 / 4; ++i) q[i] = *reinterpret_cast<const f32x4 *>(at + 256 * i);
+    }
+    __device__ __forceinline__ float c(int k, int i) const { return I == 4 ? q[k][i] : q[k / 2][2 * (k % 2) + i]; }
+};
+// The polynomials of G edges at their places s, p[t][i] of the lane's i-th feature, and with DERIVE their derivatives dp, step by step for all
+// of them.
+template <bool DERIVE, int G, int I>
+__device__ __forceinline__ void tab_values(const TabCoeff<I> (&c)[G], const float (&s)[G], float (&p)[G][I], float (&dp)[G][I])
+{
+#pragma unroll
+    for (int t = 0; t < G; ++t)
+#pragma unroll
+        for (int i = 0; i < I; ++i) p[t][i] = dp[t][i] = c[t].c(5, i);
+#pragma unroll
+    for (int k = 4; k >= 0; --k) {
+        if (DERIVE && k < 4) {
+#pragma unroll
+            for (int t = 0; t < G; ++t)
+#pragma unroll
+                for (int i = 0; i < I; ++i) dp[t][i] = fmaf(s[t], dp[t][i], p[t][i]);
+            fence<G * I>(&dp[0][0]);
+        }
+#pragma unroll
+        for (int t = 0; t < G; ++t)
+#pragma unroll
+            for (int i = 0; i < I; ++i) p[t][i] = fmaf(s[t], p[t][i], c[t].c(k, i));
+        fence<G * I>(&p[0][0]);
+    }
+}
+
+struct TabItem {     // a work item: row r0 and, if there is one, row r0 + 1
+    int32_t r0, e0;  // and the first edge
+    int32_t n0, n;   // edges of the first row, of both
+};
+struct TabStep {     // one step of a worker: edges tb to tb + 15 of an item, as far as they go
+    int32_t tb;
+    TabItem item;
+};
+struct TabRec {      // as loaded
+    int32_t sj;
+    float d, before; // before: reverse, the sum of the later layers at the lane's edge
 };
 struct TabEdge {     // what the lanes of the worker need of an edge
     int32_t goff;    // byte offset of the sender's row; past the end of the array for an edge past the item's last: its row reads 0
     int32_t loff;    // byte offset of the interval in the table
-    float s, slope;  // place in the interval, ds / dd
-    int32_t rk, raw; // receiver; r1 for an edge past the end / the clamped record's
+    float s, slope;  // place in the interval; of the lane's own edge ds / dd
 };
-__device__ inline TabEdge tab_edge(const TabRec &R, const TabStep &S, float inv_h, int l16, int row_bytes)
-{
-    TabEdge E;
-    const float v = R.d * inv_h;
-    const bool small = v < (float)kTabSmall, end = v >= (float)kTabEnd, valid = S.tb + l16 <= S.last;
-    const float sc = small ? 2.f : end ? 4.f : 1.f;
-    const float b = small ? 0.f : end ? (float)(kTabE0 - 4 * kTabEnd) : (float)(kTabM0 - kTabSmall);
-    const int iv = min((int)fmaf(v, sc, b), kTabN - 1);
-    E.slope = (2.f * inv_h) * sc;
-    E.s = fmaf(R.d, E.slope, fmaf(2.f, b - (float)iv, -1.f));
-    E.loff = __mul24(iv, kTabStride);
-    E.goff = valid ? R.sj * row_bytes : (int32_t)0x80000000;
-    E.rk = valid ? R.rk : S.r1;
-    E.raw = R.rk;
-    return E;
-}
-
-// the six coefficients of the lane's two features
-struct TabCoeff { f32x4 q0, q1, q2; };
-__device__ inline TabCoeff tab_read(const char *at)
-{
-    return TabCoeff{*reinterpret_cast<const f32x4 *>(at), *reinterpret_cast<const f32x4 *>(at + 256), *reinterpret_cast<const f32x4 *>(at + 512)};
-}
-
-// bit 16 w + k: edge k of worker w is the last one of its row; rnext: receiver of the following edge, r1 after the last
-__device__ inline uint64_t tab_ends(const TabEdge &E, const TabStep &S, int32_t next_first, int l16, int32_t &rnext)
-{
-    const int32_t up = __builtin_amdgcn_mov_dpp(E.rk, 0x101, 0xf, 0xf, true);   // row_shl:1, the next lane's
-    rnext = l16 == 15 ? (S.tb + 16 <= S.last ? next_first : S.r1) : up;
-    return __ballot(rnext != E.rk);   // (past the end both are r1)
-}
+// bit 16 w + k where a worker w's lane k has it: the workers' bits together, and the lane's own worker's
+struct TabBits {
+    uint32_t any, mine;
+    __device__ __forceinline__ TabBits(bool bit, int lane)
+    {
+        const uint64_t b = __ballot(bit);
+        const uint32_t two = (uint32_t)b | (uint32_t)(b >> 32);
+        any = two | two >> 16;
+        mine = (uint32_t)(b >> (lane & 48));
+    }
+};
 
 // a buffer of n bytes from p on, as 32-bit accesses see it (beyond n they read 0 and write nothing)
 __device__ inline __amdgpu_buffer_rsrc_t tab_buffer(const void *p, uint32_t n)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)n, kBufferFlags);
 }
-// The lane's two features, l and l + 16: 64 bytes of 16 lanes at a time.  (Features 2 l and 2 l + 1 as 8 bytes of a lane: twice the cache
-// accesses for the same rows, and the address unit busy for 82 % of the forward step.)
-__device__ inline f32x2 buffer_load_2(__amdgpu_buffer_rsrc_t r, uint32_t off)
-{
-    return f32x2{buffer_load_f32(r, off, 0, 0), buffer_load_f32(r, off + 64, 0, 0)};
-}
-__device__ inline void buffer_store_2(f32x2 v, __amdgpu_buffer_rsrc_t r, uint32_t off)
-{
-    buffer_store_f32(v[0], r, off, 0, 0);
-    buffer_store_f32(v[1], r, off + 64, 0, 0);
-}
 __device__ inline int32_t buffer_load_i32(__amdgpu_buffer_rsrc_t r, uint32_t off) { return (int32_t)__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0); }
 
 // Work items.  Every XCD takes a contiguous eighth of the launch's edges, cut at the rows where the graph's work-item tables (chunk_row)
 // have an entry (of a launch with about a row for a worker, where one partition after the other and a look at those tables would be most of
-// its time, 21 us for 8 x 192 rows, rows of one partition); the F / 32 blocks of features each go through all of it, on the same XCD.  The
+// its time, 21 us for 8 x 192 rows, rows of one partition); the blocks of features each go through all of it, on the same XCD.  The
 // XCD's rows are dealt to its blocks in turn, kTabDeal items at a time, so that at any moment they work on a short run of rows whose
 // neighbourhoods share the L2; within its block's share every worker starts at its own item and then draws from a counter in LDS.  (Draws
 // from one counter per XCD in memory: one per 35 ns, 140 us a launch at 32,000 rows.)
 constexpr int kTabDeal = 8;
-static_assert(kTabDeal == 8, "tab_walk shifts by three");
+static_assert(kTabDeal == 8, "edge_tab shifts by three");
 __device__ inline int32_t tab_cut(const TabArgs &A, int64_t edge)   // the row at which the partition is cut for its edge `edge`
 {
     return edge <= 0 ? 0 : edge >= A.n_edges ? A.n_rows : min(A.chunk_row[edge / A.span], A.n_rows);
 }
 
-// What both kernels share: the walk over partitions, items and steps.  Per partition open(A); per step load(step) -> TabRec two steps ahead,
-// gather(edge, rows) one step ahead and compute(step, edge, before, rows, next_first); zero_rows(r0, r1) for rows without edges.
-template <int F, int NW, class Rows, class Open, class Load, class Gather, class Compute, class Zero>
-__device__ __forceinline__ void tab_walk(const TabBatch &B, float *lds, int hb, Open open, Load load, Gather gather, Compute compute, Zero zero_rows)
+// Sums of q[0..15] over the 16 lanes of each row of lanes: lane l returns the sum of q[l].  Each step adds lanes across one bit of the
+// lane number and lets the lanes on either side go on with one of two edges.
+template <int CTRL> __device__ inline float add_dpp(float v)   // v plus what the pattern brings of it
 {
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, l16 = lane & 15;
-    constexpr int NH = F / 32;
-    const int32_t n_slots = B.slots, xcd = blockIdx.x & 7, slot = (int32_t)(blockIdx.x >> 3) / NH;
+    return v + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+template <int BANKS> __device__ inline float keep_banks(float v, float w)   // w in the named quads of every row of 16 lanes, v in the others
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, v), __builtin_bit_cast(int, w), 0xe4, 0xf, BANKS, false));
+}
+__device__ inline float tab_reduce(const float (&q)[16], int lane)
+{
+    float z[8], y[4], x[2];
+#pragma unroll
+    for (int k = 0; k < 8; ++k)     // row_ror:8; lanes 8-15 of a row keep edge k + 8, lanes 0-7 edge k
+        z[k] = keep_banks<0xc>(add_dpp<0x128>(q[k]), add_dpp<0x128>(q[k + 8]));
+#pragma unroll
+    for (int k = 0; k < 4; ++k)     // row_half_mirror; odd quads keep edge k + 4, even ones edge k
+        y[k] = keep_banks<0xa>(add_dpp<0x141>(z[k]), add_dpp<0x141>(z[k + 4]));
+    const unsigned bit1 = (lane & 2) ? ~0u : 0u, bit0 = (lane & 1) ? ~0u : 0u;
+    auto keep = [](unsigned mask, float v, float w) {   // w where the mask is set
+        return __builtin_bit_cast(float, (__builtin_bit_cast(unsigned, w) & mask) | (__builtin_bit_cast(unsigned, v) & ~mask));
+    };
+#pragma unroll
+    for (int k = 0; k < 2; ++k)     // quad_perm 2,3,0,1
+        x[k] = keep(bit1, add_dpp<0x4e>(y[k]), add_dpp<0x4e>(y[k + 2]));
+    return keep(bit0, add_dpp<0xb1>(x[0]), add_dpp<0xb1>(x[1]));   // quad_perm 1,0,3,2
+}
+
+// TAB_FWD over the owned rows: a_i = sum_e w_e * g_send(e).
+// TAB_BWD over all local rows, owned and ghost: gbar_i = sum_e w_e * abar_send(e) and, added up over the layers, for every edge its share
+// sum_f w'_f (abar_j g_i)_f of dE/dd.  The share with abar_i g_j is the reverse edge's, whose row gathers abar_i: the forces take both
+// (k_force_rows), and the step gathers one row per edge instead of two.  (In a partition an owned row's edges from ghosts have no share,
+// abar of a ghost being zero, and the ghosts' rows hold the other ones.)  TAB_LAST: the shares alone.
+template <int F, int KIND, int NW, int VALUES, int RING> __device__ __forceinline__ void edge_tab(const TabBatch &B, char *lds)
+{
+    using K = TabKind<F, KIND>;
+    constexpr int kRow = F * 4, kI = K::kI, GROUP = VALUES / kI;   // edges that are computed together
+    constexpr bool SUMS = KIND != TAB_LAST, SHARES = KIND != TAB_FWD;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, l16 = lane & 15, at_f = l16 * (4 * kI);
+    const int hb = K::kBlocks > 1 ? (blockIdx.x >> 3) & (K::kBlocks - 1) : 0;   // the block of features
+    const char *tab = lds + l16 * 16, *lut = lds + K::kFloats * 4;
+    const int32_t n_slots = B.slots, xcd = blockIdx.x & 7, slot = (int32_t)(blockIdx.x >> 3) / K::kBlocks;
     const int64_t total = B.edge_start[B.n], share = (total + 7) >> 3;
     const int64_t from = xcd * share, to = xcd == 7 ? total + 1 : from + share;   // the XCD's edges
     const int32_t mine = xcd * B.n >> 3, mine_from = (8 * mine + B.n - 1) / B.n, mine_n = (8 * mine + 8 + B.n - 1) / B.n - mine_from;   // B.few
-    int32_t *counter = reinterpret_cast<int32_t *>(lds) + kTabFloats;   // items drawn, per partition
+    int32_t *counter = reinterpret_cast<int32_t *>(lds + K::kFloats * 4 + kTabLut);   // items drawn, per partition
     if (threadIdx.x < kBatch) counter[threadIdx.x] = 4 * NW;
+    if (threadIdx.x < kTabUnits) {
+        const TabGrid::Unit unit = kTabGrid.unit[threadIdx.x];
+        reinterpret_cast<TabGrid::Unit *>(lds + K::kFloats * 4)[threadIdx.x] = TabGrid::Unit{unit.n * K::kPerUnit, unit.at * K::kPerUnit};
+    }
     const int32_t rows = B.rows;
-    int32_t r0 = 0, r1 = 0, e0 = 0, e1 = 0;   // rows and edges of the worker's next item
+    int32_t r0 = 0, r1 = 0;                   // rows of the worker's next item
+    int32_t p0 = 0, p1 = 0, p2 = 0;           // row_ptr from r0 on
     int32_t drawn = 0;                        // the item after it, as the worker's first lane drew it
     int part = 0;
     bool have = false;                        // whether there is a next item
     int32_t lo = 0, hi = 0;                   // the XCD's rows; lo: the first one dealt to this block
-    __amdgpu_buffer_rsrc_t ptr;
+    __amdgpu_buffer_rsrc_t ptr, send, dist, g, abar, out, sums;
+    int sum_shift = 2;
     const int32_t turn = n_slots * kTabDeal * rows;   // rows from one of the block's turns to the next
-    auto fetch = [&](int32_t item) {
-        r0 = lo + __mul24(item >> 3, turn) + __mul24(item & (kTabDeal - 1), rows);
+    auto choose = [&](int32_t k) {
+        r0 = lo + __mul24(k >> 3, turn) + __mul24(k & (kTabDeal - 1), rows);
         r1 = min(r0 + rows, hi);
         have = r0 < hi;
-        e0 = buffer_load_i32(ptr, (uint32_t)r0 * 8u);   // (past the last row: reads 0)
-        e1 = buffer_load_i32(ptr, (uint32_t)r1 * 8u);
+    };
+    // Where the next item's edges lie: asked for at every step, whether or not the item is a new one, so that the answer has its registers
+    // to itself (in the branch of those workers that take an item the compiler moves it, and waits for every load under way).
+    auto fetch = [&]() {   // (past the last row: reads 0)
+        p0 = buffer_load_i32(ptr, (uint32_t)r0 * 8u);
+        p1 = buffer_load_i32(ptr, (uint32_t)r0 * 8u + 8u);
+        p2 = buffer_load_i32(ptr, (uint32_t)r1 * 8u);
     };
     auto draw = [&]() {
         int zero = 0;
@@ -356,299 +520,189 @@ __device__ __forceinline__ void tab_walk(const TabBatch &B, float *lds, int hb, 
             }
             lo += slot * kTabDeal * rows;
             ptr = tab_buffer(A.row_ptr, ((uint32_t)A.n_rows + 1u) * 8u);
-            fetch(4 * wave + (lane >> 4));
+            choose(4 * wave + (lane >> 4));
             if (__any(have)) {
-                open(A);
+                fetch();
+                const uint32_t n_rec = (uint32_t)A.n_edges * 4u, n_nodes = (uint32_t)A.n_nodes * kRow - 128u * hb;
+                send = tab_buffer(A.senders, n_rec);
+                dist = tab_buffer(A.d, n_rec);
+                g = tab_buffer(A.g + 32 * hb, n_nodes);
+                if (SHARES) {
+                    abar = tab_buffer(A.abar + 32 * hb, n_nodes);
+                    sum_shift = A.dsum_step == 2 ? 3 : 2;
+                    sums = tab_buffer(hb ? A.dsum[1] : A.dsum[0], ((uint32_t)A.n_edges << sum_shift) - (sum_shift == 3 ? 4u * hb : 0u));
+                }
+                if (SUMS) out = tab_buffer(A.out + 32 * hb, (uint32_t)A.n_rows * kRow - 128u * hb);
                 break;
             }
         }
     };
+
+    TabRow<kI> ring[RING], acc, none;
+    acc.clear();
+    none.clear();
+    struct Heads { TabRow<kI> first, second; };   // g of the receivers of a step's first edge and of its item's second row
     TabStep front, SA, SB;
     TabRec RA, RB;
     TabEdge EA, EB;
-    float before_a = 0.f, before_b;
-    Rows ga, gb;
+    Heads HA, HB;
+    auto load = [&](const TabStep &S) {   // (past the item's last edge another item's, or nothing: not counted)
+        const int32_t e = S.item.e0 + S.tb + l16;
+        return TabRec{buffer_load_i32(send, (uint32_t)e * 4u), buffer_load_f32(dist, (uint32_t)e * 4u, 0, 0),
+                      SHARES && !B.first ? buffer_load_f32(sums, (uint32_t)e << sum_shift, 0, 0) : 0.f};
+    };
+    auto edge = [&](const TabRec &R, const TabStep &S) {
+        TabEdge E;
+        const float v = R.d * B.inv_h;
+        const int j = min((int)v, kTabUnits - 1);
+        const f32x2 unit = *reinterpret_cast<const f32x2 *>(lut + 8 * j);
+        // the interval within the unit; the last one of its own at most, as the place and the slope are in this unit's measure
+        const float k = fminf(truncf((v - (float)j) * unit[0]), unit[0] - 1.f);
+        E.slope = (2.f * B.inv_h) * unit[0];
+        E.s = fmaf(R.d, E.slope, fmaf(-2.f, fmaf((float)j, unit[0], k), -1.f));
+        E.loff = __mul24((int)(unit[1] + k), 16 * kI * 24);
+        E.goff = S.tb + l16 < S.item.n ? R.sj * kRow : (int32_t)0x80000000;
+        return E;
+    };
+    auto heads = [&](const TabStep &S, Heads &H) {
+        if (SHARES) {
+            H.first.load(g, (S.item.r0 + (S.tb >= S.item.n0 ? 1 : 0)) * kRow + at_f);
+            H.second.load(g, (S.item.r0 + 1) * kRow + at_f);
+        }
+    };
+    auto gather = [&](const TabEdge &E, auto k) { ring[k % RING].load(SHARES ? abar : g, row_bcast<k>(E.goff) + at_f); };
+    auto compute = [&](const TabStep &S, const TabEdge &E, float before, const Heads &H, const TabEdge &next) {
+        const int32_t u = S.tb + l16 + 1;
+        const TabBits ends((u == S.item.n0 || u == S.item.n) && u <= S.item.n, lane);   // an edge that is its row's last
+        TabRow<kI> gi = H.first;
+        float q[16];
+        unrolled<16 / GROUP>([&](auto grp) {
+            constexpr int k0 = grp * GROUP;
+            __builtin_amdgcn_sched_barrier(0);
+            TabCoeff<kI> c[GROUP];
+            float s[GROUP], p[GROUP][kI], dp[GROUP][kI];
+            unrolled<GROUP>([&](auto t) { c[t].read(tab + row_bcast<k0 + t>(E.loff)); });
+            unrolled<GROUP>([&](auto t) { s[t] = row_bcast<k0 + t>(E.s); });
+            tab_values<KIND == TAB_BWD>(c, s, p, dp);
+            unrolled<GROUP>([&](auto t) {
+                constexpr int k = k0 + t;
+                const TabRow<kI> &x = ring[k % RING];
+                if (SUMS) {
+#pragma unroll
+                    for (int i = 0; i < kI; ++i) acc.v[i] = fmaf(p[t][i], x.v[i], acc.v[i]);
+                }
+                if (SHARES) {
+                    float a[kI];
+#pragma unroll
+                    for (int i = 0; i < kI; ++i) a[i] = x.v[i] * gi.v[i];
+                    const float(&w)[kI] = KIND == TAB_BWD ? dp[t] : p[t];
+                    q[k] = w[0] * a[0];
+#pragma unroll
+                    for (int i = 1; i < kI; ++i) q[k] = fmaf(w[i], a[i], q[k]);
+                    fence<1>(q + k);
+                }
+                if (__builtin_expect((ends.any & (1u << k)) != 0, 0)) {
+                    if (ends.mine & (1u << k)) {
+                        if (SUMS) {
+                            acc.store(out, (S.item.r0 + (S.tb + k >= S.item.n0 ? 1 : 0)) * kRow + at_f);
+                            acc.clear();
+                        }
+                        if (SHARES) gi = H.second;
+                    }
+                }
+            });
+            unrolled<GROUP>([&](auto t) {
+                constexpr int k = k0 + t + RING;
+                if constexpr (k < 16) gather(E, std::integral_constant<int, k>{});
+                else gather(next, std::integral_constant<int, k - 16>{});
+            });
+        });
+        if (SHARES) {
+            __builtin_amdgcn_sched_barrier(0);
+            const float sum = tab_reduce(q, lane);
+            if (S.tb + l16 < S.item.n)
+                buffer_store_f32(KIND == TAB_BWD ? fmaf(sum, E.slope, before) : sum + before, sums, (uint32_t)(S.item.e0 + S.tb + l16) << sum_shift, 0, 0);
+        }
+    };
     auto advance = [&]() {
         front.tb += 16;
-        front.r0 = 0x7fffffff;
-        const bool pop = front.tb > front.last;
+        const bool pop = front.tb >= front.item.n;
         if (__any(pop)) {
             if (pop) {
-                const bool edges = have && e0 < e1;
-                front = TabStep{edges ? e0 : 1, edges ? e1 - 1 : 0, r1, edges ? r0 : 0x7fffffff};
-                if (have && e0 == e1) zero_rows(r0, r1);
-                fetch(row_bcast<0>(drawn));
+                front = TabStep{0, TabItem{r0, p0, (r1 - r0 == 2 ? p1 : p2) - p0, have ? p2 - p0 : 0}};
+                if (SUMS) {
+                    const bool none0 = have && front.item.n0 == 0, none1 = have && r1 - r0 == 2 && front.item.n == front.item.n0;
+                    if (__builtin_expect(__any(none0 || none1), 0)) {   // rows without edges
+                        if (none0) none.store(out, r0 * kRow + at_f);
+                        if (none1) none.store(out, (r0 + 1) * kRow + at_f);
+                    }
+                }
+                choose(row_bcast<0>(drawn));
                 draw();
             }
         }
+        fetch();
     };
     next_part();
     {
-        LdsFill<kTabFloats / 4, NW * 64> fill;
-        fill.load(B.tab + (size_t)hb * kTabFloats);
+        LdsFill<K::kFloats / 4, NW * 64> fill;
+        fill.load(B.tab + (size_t)hb * K::kFloats);
         fill.store(lds);
     }
     __syncthreads();
     for (; part < B.n; ++part, next_part()) {
         draw();
-        front = TabStep{1, 0, 0, 0x7fffffff};   // no edges
+        front = TabStep{0, TabItem{0, 0, 0, 0}};   // no edges
+        float before_a, before_b;
         advance();
         SA = front;
         RA = load(SA);
         advance();
         SB = front;
         RB = load(SB);
-        EA = tab_edge(RA, SA, B.inv_h, l16, F * 4);
+        EA = edge(RA, SA);
         before_a = RA.before;
-        gather(EA, ga);
-        while (__any(have || SA.tb <= SA.last || SB.tb <= SB.last)) {
+        heads(SA, HA);
+        unrolled<RING>([&](auto k) { gather(EA, k); });
+        while (__any(have || SA.tb < SA.item.n || SB.tb < SB.item.n)) {
             advance();
             const TabStep SC = front;
             RA = load(SC);
-            EB = tab_edge(RB, SB, B.inv_h, l16, F * 4);
+            EB = edge(RB, SB);
             before_b = RB.before;
-            gather(EB, gb);
+            heads(SB, HB);
             __builtin_amdgcn_sched_barrier(0);
-            compute(SA, EA, before_a, ga, row_bcast<0>(EB.rk));
+            compute(SA, EA, before_a, HA, EB);
             advance();
             SA = SC;
             const TabStep SD = front;
             RB = load(SD);
-            EA = tab_edge(RA, SA, B.inv_h, l16, F * 4);
+            EA = edge(RA, SA);
             before_a = RA.before;
-            gather(EA, ga);
+            heads(SA, HA);
             __builtin_amdgcn_sched_barrier(0);
-            compute(SB, EB, before_b, gb, row_bcast<0>(EA.rk));
+            compute(SB, EB, before_b, HB, EA);
             SB = SD;
         }
     }
 }
-
-// Forward step over the owned rows: a_i = sum_e w_e * g_send(e).
-template <int F, int NW> __device__ __forceinline__ void edge_fwd_tab(const TabBatch &B, float *lds)
+template <int F>
+__global__ void __launch_bounds__(kTabFwd.waves * 64, kTabFwd.waves / 4) k_edge_fwd_tab(TabBatch B)
 {
-    constexpr int kRow = F * 4;
-    const int lane = threadIdx.x & 63, l16 = lane & 15, at_f = l16 * 4;   // byte offset of the lane's first feature in a block of 32
-    const int hb = (blockIdx.x >> 3) & (F / 32 - 1);
-    const char *tab = reinterpret_cast<const char *>(lds) + l16 * 16;
-    struct Rows { f32x2 g[16]; };
-    __amdgpu_buffer_rsrc_t send, recv, dist, g, out;
-    f32x2 acc = {0.f, 0.f};
-    auto zero_rows = [&](int32_t r, int32_t end) {
-        for (; r < end; ++r) buffer_store_2(f32x2{0.f, 0.f}, out, r * kRow + at_f);
-    };
-    tab_walk<F, NW, Rows>(B, lds, hb,
-        [&](const TabArgs &A) {
-            const uint32_t n_rec = (uint32_t)A.n_edges * 4u;
-            send = tab_buffer(A.senders, n_rec);
-            recv = tab_buffer(A.recv, n_rec);
-            dist = tab_buffer(A.d, n_rec);
-            g = tab_buffer(A.g + 32 * hb, (uint32_t)A.n_nodes * kRow - 128u * hb);
-            out = tab_buffer(A.out + 32 * hb, (uint32_t)A.n_rows * kRow - 128u * hb);
-        },
-        [&](const TabStep &S) {
-            const uint32_t at = (uint32_t)min(S.tb + l16, S.last) * 4u;
-            return TabRec{buffer_load_i32(send, at), buffer_load_i32(recv, at), buffer_load_f32(dist, at, 0, 0), 0.f};
-        },
-        [&](const TabEdge &E, Rows &R) {
-            unrolled(std::make_integer_sequence<int, 16>{}, [&](auto k) { R.g[k] = buffer_load_2(g, row_bcast<k>(E.goff) + at_f); });
-        },
-        [&](const TabStep &S, const TabEdge &E, float, const Rows &R, int32_t next_first) {
-            int32_t rnext;
-            const uint64_t ends = tab_ends(E, S, next_first, l16, rnext);
-            const uint32_t two = (uint32_t)ends | (uint32_t)(ends >> 32), any = two | two >> 16;
-            const uint32_t mine = (uint32_t)(ends >> (lane & 48));
-            const int32_t first = row_bcast<0>(E.raw);
-            if (__any(S.r0 < first)) zero_rows(S.r0, first);   // rows of the item before its first edge are empty
-            // values first, kTabGroup edges together with nothing in between that could stop their reads and chains from overlapping;
-            // then the row sums with their branches
-            unrolled(std::make_integer_sequence<int, 16 / kTabGroup>{}, [&](auto grp) {
-                constexpr int k0 = grp * kTabGroup;
-                __builtin_amdgcn_sched_barrier(0);
-                float p[kTabGroup][2];
-                unrolled(std::make_integer_sequence<int, kTabGroup>{}, [&](auto t) {
-                    const TabCoeff c = tab_read(tab + row_bcast<k0 + t>(E.loff));
-                    const float s = row_bcast<k0 + t>(E.s);
-#pragma unroll
-                    for (int i = 0; i < 2; ++i)
-                        p[t][i] = fmaf(s, fmaf(s, fmaf(s, fmaf(s, fmaf(s, c.q2[2 + i], c.q2[i]), c.q1[2 + i]), c.q1[i]), c.q0[2 + i]), c.q0[i]);
-                });
-#pragma unroll
-                for (int t = 0; t < kTabGroup; ++t) {
-                    pin(p[t][0]);
-                    pin(p[t][1]);
-                }
-                unrolled(std::make_integer_sequence<int, kTabGroup>{}, [&](auto t) {
-                    constexpr int k = k0 + t;
-                    acc[0] = fmaf(p[t][0], R.g[k][0], acc[0]);
-                    acc[1] = fmaf(p[t][1], R.g[k][1], acc[1]);
-                    if (__builtin_expect((any & (1u << k)) != 0, 0)) {
-                        const int32_t row = row_bcast<k>(E.rk), nrow = row_bcast<k>(rnext);
-                        if (mine & (1u << k)) {
-                            buffer_store_2(acc, out, row * kRow + at_f);
-                            acc = f32x2{0.f, 0.f};
-                            zero_rows(row + 1, nrow);   // empty rows in between
-                        }
-                    }
-                });
-            });
-        },
-        zero_rows);
+    extern __shared__ __align__(16) char tab_mem[];
+    edge_tab<F, TAB_FWD, kTabFwd.waves, kTabFwd.values, kTabFwd.ring>(B, tab_mem);
 }
 template <int F>
-__global__ void __launch_bounds__(kTabFwdWaves * 64, kTabFwdWaves / 4) k_edge_fwd_tab(TabBatch B)
+__global__ void __launch_bounds__(kTabBwd.waves * 64, kTabBwd.waves / 4) k_edge_bwd_tab(TabBatch B)
 {
-    extern __shared__ float lds[];
-    edge_fwd_tab<F, kTabFwdWaves>(B, lds);
+    extern __shared__ __align__(16) char tab_mem[];
+    edge_tab<F, TAB_BWD, kTabBwd.waves, kTabBwd.values, kTabBwd.ring>(B, tab_mem);
 }
-
-// Sums of q[0..15] over the 16 lanes of each row: lane l returns the sum of q[tab_edge_of(l)].  Each step adds lanes across one bit of the lane
-// number and lets the lanes on either side go on with one of two edges.
-__device__ inline int tab_edge_of(int lane) { return ((lane & 8) ? 0 : 8) + ((lane & 4) ? 0 : 4) + (lane & 3); }
-template <int CTRL> __device__ inline float add_dpp(float v)   // v plus what the pattern brings of it
+template <int F>
+__global__ void __launch_bounds__(kTabLast.waves * 64, kTabLast.waves / 4) k_edge_last_tab(TabBatch B)
 {
-    return v + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
-}
-template <int BANKS> __device__ inline float keep_banks(float v, float w)   // w in the named quads of every row of 16 lanes, v in the others
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, v), __builtin_bit_cast(int, w), 0xe4, 0xf, BANKS, false));
-}
-__device__ inline float tab_reduce(const float (&q)[16], int lane)
-{
-    float z[8], y[4], x[2];
-#pragma unroll
-    for (int k = 0; k < 8; ++k)     // row_ror:8; lanes 0-7 of a row keep edge k + 8, lanes 8-15 edge k
-        z[k] = keep_banks<0xc>(add_dpp<0x128>(q[k + 8]), add_dpp<0x128>(q[k]));
-#pragma unroll
-    for (int k = 0; k < 4; ++k)     // row_half_mirror; even quads keep edge k + 4, odd ones edge k
-        y[k] = keep_banks<0xa>(add_dpp<0x141>(z[k + 4]), add_dpp<0x141>(z[k]));
-    const unsigned bit1 = (lane & 2) ? ~0u : 0u, bit0 = (lane & 1) ? ~0u : 0u;
-    auto keep = [](unsigned mask, float v, float w) {   // w where the mask is set
-        return __builtin_bit_cast(float, (__builtin_bit_cast(unsigned, w) & mask) | (__builtin_bit_cast(unsigned, v) & ~mask));
-    };
-#pragma unroll
-    for (int k = 0; k < 2; ++k)     // quad_perm 2,3,0,1
-        x[k] = keep(bit1, add_dpp<0x4e>(y[k]), add_dpp<0x4e>(y[k + 2]));
-    return keep(bit0, add_dpp<0xb1>(x[0]), add_dpp<0xb1>(x[1]));   // quad_perm 1,0,3,2
-}
-
-// Reverse step over all local rows, owned and ghost: gbar_i = sum_e w_e * abar_send(e) and, added up over the layers, for every edge
-// its share sum_f w'_f (abar_j g_i)_f of dE/dd.  The share with abar_i g_j is the reverse edge's, whose row gathers abar_i: the forces
-// take both (k_force_rows), and the step gathers one row per edge instead of two.  (In a partition an owned row's edges from
-// ghosts have no share, abar of a ghost being zero, and the ghosts' rows hold the other ones.)
-template <int F, bool GBAR, int NW> __device__ __forceinline__ void edge_bwd_tab(const TabBatch &B, float *lds)
-{
-    constexpr int kRow = F * 4;
-    const int lane = threadIdx.x & 63, l16 = lane & 15, at_f = l16 * 4;   // byte offset of the lane's first feature in a block of 32
-    const int hb = (blockIdx.x >> 3) & (F / 32 - 1);
-    const char *tab = reinterpret_cast<const char *>(lds) + l16 * 16;
-    const int k_out = tab_edge_of(lane);                 // the edge of a step whose sum this lane gets
-    const int slope_from = ((lane & 48) | k_out) * 4;    // and the lane that has its record
-    struct Rows { f32x2 a[16], gi0, gi1; };              // the senders' rows of abar, and g of the first and the last receiver
-    __amdgpu_buffer_rsrc_t send, recv, dist, g, abar, out, sums;
-    int sum_shift = 2;
-    f32x2 acc = {0.f, 0.f};
-    auto zero_rows = [&](int32_t r, int32_t end) {
-        if (GBAR)
-            for (; r < end; ++r) buffer_store_2(f32x2{0.f, 0.f}, out, r * kRow + at_f);
-    };
-    tab_walk<F, NW, Rows>(B, lds, hb,
-        [&](const TabArgs &A) {
-            const uint32_t n_rec = (uint32_t)A.n_edges * 4u;
-            send = tab_buffer(A.senders, n_rec);
-            recv = tab_buffer(A.recv, n_rec);
-            dist = tab_buffer(A.d, n_rec);
-            g = tab_buffer(A.g + 32 * hb, (uint32_t)A.n_nodes * kRow - 128u * hb);
-            abar = tab_buffer(A.abar + 32 * hb, (uint32_t)A.n_nodes * kRow - 128u * hb);
-            out = tab_buffer(A.out + 32 * hb, (uint32_t)A.n_rows * kRow - 128u * hb);
-            sum_shift = A.dsum_step == 2 ? 3 : 2;
-            sums = tab_buffer(hb ? A.dsum[1] : A.dsum[0], ((uint32_t)A.n_edges << sum_shift) - (sum_shift == 3 ? 4u * hb : 0u));
-        },
-        [&](const TabStep &S) {
-            const uint32_t at = (uint32_t)min(S.tb + l16, S.last) * 4u;
-            return TabRec{buffer_load_i32(send, at), buffer_load_i32(recv, at), buffer_load_f32(dist, at, 0, 0),
-                          B.first ? 0.f : buffer_load_f32(sums, (uint32_t)min(S.tb + k_out, S.last) << sum_shift, 0, 0)};
-        },
-        [&](const TabEdge &E, Rows &R) {
-            R.gi0 = buffer_load_2(g, row_bcast<0>(E.raw) * kRow + at_f);
-            R.gi1 = buffer_load_2(g, row_bcast<15>(E.raw) * kRow + at_f);
-            unrolled(std::make_integer_sequence<int, 16>{}, [&](auto k) { R.a[k] = buffer_load_2(abar, row_bcast<k>(E.goff) + at_f); });
-        },
-        [&](const TabStep &S, const TabEdge &E, float before, const Rows &R, int32_t next_first) {
-            int32_t rnext;
-            const uint64_t ends = tab_ends(E, S, next_first, l16, rnext);
-            const uint32_t two = (uint32_t)ends | (uint32_t)(ends >> 32), any = two | two >> 16;
-            const uint32_t mine = (uint32_t)(ends >> (lane & 48));
-            if (GBAR) {
-                const int32_t first = row_bcast<0>(E.raw);
-                if (__any(S.r0 < first)) zero_rows(S.r0, first);   // rows of the item before its first edge are empty
-            }
-            const int32_t row_last = row_bcast<15>(E.raw);
-            f32x2 gi = R.gi0;
-            float q[16];
-            unrolled(std::make_integer_sequence<int, 16 / kTabGroup>{}, [&](auto grp) {
-                constexpr int k0 = grp * kTabGroup;
-                __builtin_amdgcn_sched_barrier(0);
-                float p[kTabGroup][2], dp[kTabGroup][2];
-                unrolled(std::make_integer_sequence<int, kTabGroup>{}, [&](auto t) {   // value and slope
-                    const TabCoeff c = tab_read(tab + row_bcast<k0 + t>(E.loff));
-                    const float s = row_bcast<k0 + t>(E.s);
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) {
-                        const float p4 = fmaf(s, c.q2[2 + i], c.q2[i]), p3 = fmaf(s, p4, c.q1[2 + i]), p2 = fmaf(s, p3, c.q1[i]),
-                                    p1 = fmaf(s, p2, c.q0[2 + i]);
-                        dp[t][i] = fmaf(s, fmaf(s, fmaf(s, fmaf(s, c.q2[2 + i], p4), p3), p2), p1);
-                        p[t][i] = GBAR ? fmaf(s, p1, c.q0[i]) : 0.f;
-                    }
-                });
-#pragma unroll
-                for (int t = 0; t < kTabGroup; ++t)
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) {
-                        if (GBAR) pin(p[t][i]);
-                        pin(dp[t][i]);
-                    }
-                unrolled(std::make_integer_sequence<int, kTabGroup>{}, [&](auto t) {
-                    constexpr int k = k0 + t;
-                    if (GBAR) {
-                        acc[0] = fmaf(p[t][0], R.a[k][0], acc[0]);
-                        acc[1] = fmaf(p[t][1], R.a[k][1], acc[1]);
-                    }
-                    q[k] = fmaf(dp[t][0], R.a[k][0] * gi[0], dp[t][1] * (R.a[k][1] * gi[1]));
-                    pin(q[k]);
-                    if (__builtin_expect((any & (1u << k)) != 0, 0)) {
-                        const int32_t row = row_bcast<k>(E.rk), nrow = row_bcast<k>(rnext);
-                        if (mine & (1u << k)) {
-                            if (GBAR) buffer_store_2(acc, out, row * kRow + at_f);
-                            acc = f32x2{0.f, 0.f};
-                            zero_rows(row + 1, nrow);   // empty rows in between
-                            if (k < 15 && S.tb + k < S.last) {   // the next row starts inside this step
-                                gi = R.gi1;
-                                if (nrow != row_last) {   // a third row inside one step (short rows): fetch it now
-                                    const f32x2 third = buffer_load_2(g, nrow * kRow + at_f);
-                                    float a0 = third[0], a1 = third[1];
-                                    pin(a0);
-                                    pin(a1);
-                                    gi = f32x2{a0, a1};   // (completed here: left pending, every later use would wait)
-                                }
-                            }
-                        }
-                    }
-                });
-            });
-            __builtin_amdgcn_sched_barrier(0);
-            const float sum = tab_reduce(q, lane);
-            const float slope = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(slope_from, __builtin_bit_cast(int, E.slope)));
-            if (S.tb + k_out <= S.last)
-                buffer_store_f32(fmaf(sum, slope, before), sums, (uint32_t)(S.tb + k_out) << sum_shift, 0, 0);
-        },
-        zero_rows);
-}
-template <int F, bool GBAR>
-__global__ void __launch_bounds__(kTabBwdWaves * 64, kTabBwdWaves / 4) k_edge_bwd_tab(TabBatch B)
-{
-    extern __shared__ float lds[];
-    edge_bwd_tab<F, GBAR, kTabBwdWaves>(B, lds);
+    extern __shared__ __align__(16) char tab_mem[];
+    edge_tab<F, TAB_LAST, kTabLast.waves, kTabLast.values, kTabLast.ring>(B, tab_mem);
 }
 
 // ---------------------------------------------------------------- either way
@@ -656,34 +710,32 @@ __global__ void __launch_bounds__(kTabBwdWaves * 64, kTabBwdWaves / 4) k_edge_bw
 // The edge steps of a call whose host has not heard yet whether the tables represent the filters: one launch that goes by *bad, so that
 // the way and every bit of the result follow from the weights alone, whatever the handle has seen before.  A row's or an edge's sum does
 // not depend on the wavefronts of a block, so either way gives what its own kernel gives; the reverse step takes 8 of them, the most that
-// leave the way by MLP the registers it needs.  Per launch on tables 20.0 us forward (20.1 in k_edge_fwd_tab), 25.8 and 24.9 reverse (24.4,
-// 24.5) at 15,600 rows and F = 32.  With a launch for each way, the other one's ending at once, a pass of four models took 691 us there, here
-// 669; 500 atoms in the fixed workspace 248 and 240.  (The lower edges' terms added by the reverse kernel itself, which spares on tables a
-// launch that ends at once: 653 and 228, but by MLP 122 us a launch, 103 with 32 of their rows in flight, for 47 and 16 apart.)
+// leave the way by MLP the registers it needs.
 constexpr int kBothBwdWaves = 8;
-static_assert(kTabFwdWaves == kFwdWaves, "the forward step has one block size for both ways");
 struct BothBatch {
     TabBatch tab;
     EdgeBatch mlp;
     const int32_t *bad;
 };
+static_assert(sizeof(BothBatch) <= 4096, "kernel arguments");
 template <int F, int PREC>
 __global__ void __launch_bounds__(kFwdWaves * 64, kFwdWaves / 4) k_edge_fwd_both(BothBatch B)
 {
-    extern __shared__ float lds[];
+    extern __shared__ __align__(16) float lds[];
     if (*B.bad != 0)
         edge_fwd<F, PREC>(B.mlp, lds);
-    else if ((int)(blockIdx.x >> 3) < B.tab.slots * (F / 32))
-        edge_fwd_tab<F, kFwdWaves>(B.tab, lds);
+    else if ((int)(blockIdx.x >> 3) < B.tab.slots)
+        edge_tab<F, TAB_FWD, kFwdWaves, kTabFwd.values, kTabFwd.ring>(B.tab, reinterpret_cast<char *>(lds));
 }
-template <int F, int PREC, bool GBAR>
+template <int F, int PREC, int KIND>
 __global__ void __launch_bounds__(kBothBwdWaves * 64, kBothBwdWaves / 4) k_edge_bwd_both(BothBatch B)
 {
-    extern __shared__ float lds[];
+    extern __shared__ __align__(16) float lds[];
+    constexpr TabShape shape = KIND == TAB_BWD ? kTabBwd : kTabLast;
     if (*B.bad != 0)
         edge_bwd<F, PREC, kBothBwdWaves>(B.mlp, lds);
-    else if ((int)(blockIdx.x >> 3) < B.tab.slots * (F / 32))
-        edge_bwd_tab<F, GBAR, kBothBwdWaves>(B.tab, lds);
+    else if ((int)(blockIdx.x >> 3) < B.tab.slots * TabKind<F, KIND>::kBlocks)
+        edge_tab<F, KIND, kBothBwdWaves, shape.values, shape.ring>(B.tab, reinterpret_cast<char *>(lds));
 }
 
 #endif  // MLIP_MODEL_TABLE_H
