@@ -240,9 +240,10 @@ __device__ inline double frac_k(const double *r, const double *n, double V)
     return ((r[0] * n[0] + r[1] * n[1]) + r[2] * n[2]) / V;
 }
 
-// err[0] = flag bits, err[1] = max species seen, err[2] = min species seen (both start at 0); one atomic pair per wavefront
+// err[0] = flag bits, err[1] = max species seen, err[2] = min species seen (both start at 0); called by all threads of a block (up to 1024)
 __device__ inline void track_species(int z, int32_t *err)
 {
+    __shared__ int32_t ext[2][16];
     int zmax = z, zmin = z;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
@@ -250,10 +251,21 @@ __device__ inline void track_species(int z, int32_t *err)
         zmin = min(zmin, __shfl_xor(zmin, off, 64));
     }
     if ((threadIdx.x & 63) == 0) {
-        // the running extremes only move one way, so a wavefront that cannot move them skips its atomics
-        // (thousands of atomics on one address would serialise and dominate the kernel)
-        if (zmax > __atomic_load_n(err + 1, __ATOMIC_RELAXED)) atomicMax(err + 1, zmax);
-        if (zmin < __atomic_load_n(err + 2, __ATOMIC_RELAXED)) atomicMin(err + 2, zmin);
+        ext[0][threadIdx.x >> 6] = zmax;
+        ext[1][threadIdx.x >> 6] = zmin;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (unsigned w = 1; w < blockDim.x / 64; ++w) {
+            zmax = max(zmax, ext[0][w]);
+            zmin = min(zmin, ext[1][w]);
+        }
+        // The running extremes only move one way, so a block that cannot move them skips its atomics, and what it looks at may be old: an
+        // ordinary load, which the XCD's L2 answers.  (Some 25 ns for every wavefront that asked past it, one after the other: most of the
+        // 102 us that k_bin took for 256,000 atoms.)
+        const volatile int32_t *seen = err;
+        if (zmax > seen[1]) atomicMax(err + 1, zmax);
+        if (zmin < seen[2]) atomicMin(err + 2, zmin);
     }
 }
 
@@ -296,7 +308,18 @@ __global__ void k_bin(int64_t N, const double *__restrict__ pos, const int32_t *
     cell_of[i] = c;
     wrapp[i] = pack3(w[0], w[1], w[2]);
     slab_of[i] = slab;
-    const int32_t place = atomicAdd(&cell_cnt[c], 1);   // the atom's place among its cell's
+    // The atom's place among its cell's: one addition for all the wavefront's atoms of a cell (in lattice order some six, which the counter would
+    // take one after the other: 131 us for a million atoms, so 100).
+    const int lane = threadIdx.x & 63;
+    uint64_t left = __ballot(true), same = 0;
+    while (left) {
+        const uint64_t m = __ballot(c == __builtin_amdgcn_readlane(c, __builtin_ctzll(left)));
+        if (m >> lane & 1) same = m;
+        left &= ~m;
+    }
+    const int first = __builtin_ctzll(same);
+    int32_t place = lane == first ? atomicAdd(&cell_cnt[c], __popcll(same)) : 0;
+    place = __shfl(place, first, 64) + __popcll(same & ((1ull << lane) - 1ull));
     in_cell[i] = place;
     if (place == kCrowd) atomicOr(err, FLAG_CROWDED);
 }
@@ -661,13 +684,15 @@ __global__ void k_pair_partners(int64_t N, const int32_t *__restrict__ sid, cons
     else atomicOr(err, FLAG_STAGE_OVERFLOW);
 }
 
+struct ChunkTab { int32_t *row; int64_t n; int32_t span; };   // work-item table of n items of `span` edges (row == nullptr: none)
+
 // k_sort_rows for the pair-wise search: the row's keys come from the atom's two staging rows; the rank of every
 // staging slot is kept for the reverse-edge index
 __global__ void __launch_bounds__(64)
 k_sort_rows_pairs(int64_t N, CellParams cp, const double *__restrict__ pos, const int32_t *__restrict__ sid,
                   const int64_t *__restrict__ row_ptr, const uint64_t *__restrict__ stage_own, const uint64_t *__restrict__ stage_par,
                   const int32_t *__restrict__ n_own, uint8_t *rank_own, uint8_t *rank_par, int32_t *senders, int32_t *recv,
-                  uint32_t *shiftp, float *d)
+                  uint32_t *shiftp, float *d, ChunkTab chunks)
 {
     __shared__ uint64_t lds[kOwn + kPar];
     const int64_t s = xcd_block();
@@ -677,6 +702,11 @@ k_sort_rows_pairs(int64_t N, CellParams cp, const double *__restrict__ pos, cons
     const int no = n_own[s];
     const int64_t base = row_ptr[i];
     const int n = (int)(row_ptr[i + 1] - base);
+    if (chunks.row) {   // the places of the work-item table (k_chunk_rows) that this row is the first for
+        const int64_t to = i == N - 1 ? chunks.n : base / chunks.span;
+        for (int64_t c = (i == 0 ? 0 : row_ptr[i - 1] / chunks.span + 1) + lane; c <= to; c += 64)
+            chunks.row[c] = c == chunks.n || c * chunks.span > base ? (int32_t)N : (int32_t)i;
+    }
     for (int m = lane; m < n; m += 64)
         lds[m] = (m < no) ? stage_own[s * kOwn + m] : stage_par[s * kPar + (m - no)];
     __syncthreads();
@@ -1664,6 +1694,7 @@ namespace {
 
 struct CsrOut {   // where a neighbour search puts its receiver-sorted CSR (mirror: the reverse-edge index, or nullptr)
     DevBuf *row_ptr, *senders, *recv, *shiftp, *d, *mirror;
+    DevBuf *chunk_row;   // the work-item table, made by the pair-wise search on the way, not by the other one; or nullptr
 };
 
 // waits for the edge count and the flag words, which the scan of the row lengths published, and turns the flags into errors
@@ -1794,10 +1825,17 @@ int search_csr(mlip_graph *g, const CellParams &cp, int64_t N, int32_t P, const 
             MLIP_TRY(out.shiftp->ensure(Ecap * 4));
             MLIP_TRY(out.recv->ensure(Ecap * 4));
             MLIP_TRY(out.d->ensure(Ecap * 4));
+            ChunkTab chunks{};
+            if (out.chunk_row) {
+                chunks.span = chunk_span(E);
+                chunks.n = chunks_of(E, chunks.span);
+                MLIP_TRY(out.chunk_row->ensure((size_t)(chunks.n + 1) * 4));
+                chunks.row = out.chunk_row->as<int32_t>();
+            }
             k_sort_rows_pairs<<<grid8(N), 64, 0, s>>>(N, cp, pos, g->sid.as<int32_t>(), out.row_ptr->as<int64_t>(), stage_own, stage_par, n_own,
                                                       rank_own, rank_par, out.senders->as<int32_t>(),
                                                       out.recv->as<int32_t>(), out.shiftp->as<uint32_t>(),
-                                                      out.d->as<float>());
+                                                      out.d->as<float>(), chunks);
             MLIP_HIP(hipGetLastError());
             if (out.mirror) {
                 MLIP_TRY(out.mirror->ensure(Ecap * 4));
@@ -1945,7 +1983,7 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
             CellParams cps;
             rc = prepare_cell(cell, r_cut + g->skin, P, N, cps);
             if (rc == MLIP_OK)
-                rc = search_csr(g, cps, N, P, nullptr, nullptr, CsrOut{&g->cand_row_ptr, &g->cand_senders, &g->cand_recv, &g->cand_shiftp, &g->cand_d, &g->cand_mirror},
+                rc = search_csr(g, cps, N, P, nullptr, nullptr, CsrOut{&g->cand_row_ptr, &g->cand_senders, &g->cand_recv, &g->cand_shiftp, &g->cand_d, &g->cand_mirror, nullptr},
                                 &g->cand_E, &unchecked);
             if (rc == MLIP_OK) rc = g->ref_pos.ensure((size_t)N * 3 * sizeof(double));
             if (rc == MLIP_OK) {
@@ -1964,7 +2002,7 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
         }
         if (rc != MLIP_OK) { prof_end(g); return rc; }
     } else {
-        const int rc = search_csr(g, cp, N, P, positions, species, CsrOut{&g->row_ptr, &g->senders, &g->recv, &g->shiftp, &g->d, &g->mirror}, &E,
+        const int rc = search_csr(g, cp, N, P, positions, species, CsrOut{&g->row_ptr, &g->senders, &g->recv, &g->shiftp, &g->d, &g->mirror, &g->chunk_row}, &E,
                                   &unchecked);
         if (rc != MLIP_OK) { prof_end(g); return rc; }
     }
@@ -1974,8 +2012,10 @@ int build_graph_impl(mlip_graph *g, const double *positions, const double *cell,
         g->whole.span = chunk_span(E);
         const int64_t nc = chunks_of(E, g->whole.span);
         MLIP_TRY(g->chunk_row.ensure((size_t)(nc + 1) * 4));
-        k_chunk_rows<<<blocks_for(nc + 1, 256), 256, 0, s>>>(N, nc, g->whole.span, g->row_ptr.as<int64_t>(), g->chunk_row.as<int32_t>());
-        MLIP_HIP(hipGetLastError());
+        if (unchecked) {   // (the list came from the candidates or the one-sided search; the pair-wise one has made the table)
+            k_chunk_rows<<<blocks_for(nc + 1, 256), 256, 0, s>>>(N, nc, g->whole.span, g->row_ptr.as<int64_t>(), g->chunk_row.as<int32_t>());
+            MLIP_HIP(hipGetLastError());
+        }
     }
 
     SlabView &W = g->whole;

@@ -643,23 +643,27 @@ template <int F, int KIND, int NW, int VALUES, int RING> __device__ __forceinlin
         }
         fetch();
     };
-    next_part();
-    {
-        LdsFill<K::kFloats / 4, NW * 64> fill;
-        fill.load(B.tab + (size_t)hb * K::kFloats);
-        fill.store(lds);
-    }
-    __syncthreads();
-    for (; part < B.n; ++part, next_part()) {
+    auto begin = [&]() {   // the records of a partition's first two steps
         draw();
         front = TabStep{0, TabItem{0, 0, 0, 0}};   // no edges
-        float before_a, before_b;
         advance();
         SA = front;
         RA = load(SA);
         advance();
         SB = front;
         RB = load(SB);
+    };
+    next_part();
+    __syncthreads();   // (the counters)
+    {
+        LdsFill<K::kFloats / 4, NW * 64> fill;
+        fill.load(B.tab + (size_t)hb * K::kFloats);
+        if (part < B.n) begin();   // asked for while the table is under way
+        fill.store(lds);
+    }
+    __syncthreads();
+    for (; part < B.n; begin()) {
+        float before_a, before_b;
         EA = edge(RA, SA);
         before_a = RA.before;
         heads(SA, HA);
@@ -684,6 +688,9 @@ template <int F, int KIND, int NW, int VALUES, int RING> __device__ __forceinlin
             compute(SB, EB, before_b, HB, EA);
             SB = SD;
         }
+        ++part;
+        next_part();
+        if (part >= B.n) break;
     }
 }
 template <int F>
