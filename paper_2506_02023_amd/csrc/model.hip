@@ -219,6 +219,11 @@ int64_t upper_edges(const SlabView &v)
     return (v.n_edges_owned - n_ghost_edges) / 2 + n_ghost_edges;
 }
 
+// Rows for a compute unit up to which the four workers of a wavefront take a row together: a launch of so few rows takes as long as one
+// row's chain, one step for 45 edges instead of three (108 atoms, F = 32: forward 10.6 us, so 7.3; 500 atoms, F = 64, 13.0 and 10.9). With
+// more rows the step's empty fourth costs more (4,000 atoms, 15 rows: 14.0 and 15.9).
+constexpr int kTabTogether = 4;
+
 // Rows of an edge step on tables, split over the chip; blocks of `waves` wavefronts, `blocks` of them for the blocks of features.
 int plan_edge_tab(mlip_graph *g, TabBatch &b, int blocks, int waves)
 {
@@ -231,6 +236,8 @@ int plan_edge_tab(mlip_graph *g, TabBatch &b, int blocks, int waves)
     const int64_t workers = (int64_t)(g->n_cu / blocks) * waves * 4;
     b.rows = (int)std::min<int64_t>(kTabRows, std::max<int64_t>(1, rows / (8 * workers)));
     b.few = rows <= workers;
+    b.together = rows <= (int64_t)(g->n_cu / blocks) * kTabTogether;
+    if (b.together) b.rows = 1;
     b.edge_start[0] = 0;
     for (int q = 0; q < kBatch; ++q) b.edge_start[q + 1] = b.edge_start[q] + (q < b.n ? b.s[q].n_edges : 0);
     // persistent grid: one block per compute unit (the table fills its LDS), fewer where there are not even kTabDeal items for each

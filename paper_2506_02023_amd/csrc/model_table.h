@@ -260,6 +260,7 @@ struct TabBatch {
     int slots;             // blocks of an XCD for each block of features; blocks beyond them have no rows
     int rows;              // rows of a work item
     int few;               // few rows for the workers: every XCD takes rows of one partition, 8 / n XCDs each
+    int together;          // fewer still: a wavefront's four workers take a row together
     int first;             // reverse: dsum is written, not added to
     int n;
     int64_t edge_start[kBatch + 1];
@@ -270,7 +271,7 @@ struct TabBatch {
 #define MLIP_TAB_FWD 16, 8, 4
 #endif
 #ifndef MLIP_TAB_BWD
-#define MLIP_TAB_BWD 16, 4, 8
+#define MLIP_TAB_BWD 16, 4, 4
 #endif
 #ifndef MLIP_TAB_LAST
 #define MLIP_TAB_LAST 12, 8, 8
@@ -458,7 +459,7 @@ __device__ inline float tab_reduce(const float (&q)[16], int lane)
 // sum_f w'_f (abar_j g_i)_f of dE/dd.  The share with abar_i g_j is the reverse edge's, whose row gathers abar_i: the forces take both
 // (k_force_rows), and the step gathers one row per edge instead of two.  (In a partition an owned row's edges from ghosts have no share,
 // abar of a ghost being zero, and the ghosts' rows hold the other ones.)  TAB_LAST: the shares alone.
-template <int F, int KIND, int NW, int VALUES, int RING> __device__ __forceinline__ void edge_tab(const TabBatch &B, char *lds)
+template <int F, int KIND, int NW, int VALUES, int RING, bool TOGETHER> __device__ __forceinline__ void edge_tab_walk(const TabBatch &B, char *lds)
 {
     using K = TabKind<F, KIND>;
     constexpr int kRow = F * 4, kI = K::kI, GROUP = VALUES / kI;   // edges that are computed together
@@ -471,7 +472,11 @@ template <int F, int KIND, int NW, int VALUES, int RING> __device__ __forceinlin
     const int64_t from = xcd * share, to = xcd == 7 ? total + 1 : from + share;   // the XCD's edges
     const int32_t mine = xcd * B.n >> 3, mine_from = (8 * mine + B.n - 1) / B.n, mine_n = (8 * mine + 8 + B.n - 1) / B.n - mine_from;   // B.few
     int32_t *counter = reinterpret_cast<int32_t *>(lds + K::kFloats * 4 + kTabLut);   // items drawn, per partition
-    if (threadIdx.x < kBatch) counter[threadIdx.x] = 4 * NW;
+    // A wavefront's workers take items of their own or, where there are few rows for them (plan_edge_tab), one row together, every fourth
+    // step of it each.
+    constexpr int stride = TOGETHER ? 64 : 16;            // from a worker's step to its next one
+    const int offset = TOGETHER ? lane & 48 : 0;          // its first one
+    if (threadIdx.x < kBatch) counter[threadIdx.x] = TOGETHER ? NW : 4 * NW;
     if (threadIdx.x < kTabUnits) {
         const TabGrid::Unit unit = kTabGrid.unit[threadIdx.x];
         reinterpret_cast<TabGrid::Unit *>(lds + K::kFloats * 4)[threadIdx.x] = TabGrid::Unit{unit.n * K::kPerUnit, unit.at * K::kPerUnit};
@@ -501,7 +506,7 @@ template <int F, int KIND, int NW, int VALUES, int RING> __device__ __forceinlin
     auto draw = [&]() {
         int zero = 0;
         asm("" : "+v"(zero));   // (an address that looks uniform would be combined over the lanes, and the result waited for at once)
-        if (l16 == 0) drawn = __hip_atomic_fetch_add(counter + part + zero, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (TOGETHER ? lane == 0 : l16 == 0) drawn = __hip_atomic_fetch_add(counter + part + zero, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
     auto next_part = [&]() {   // the first partition from `part` on in which the wavefront has an item
         for (; part < B.n; ++part) {
@@ -520,7 +525,7 @@ template <int F, int KIND, int NW, int VALUES, int RING> __device__ __forceinlin
             }
             lo += slot * kTabDeal * rows;
             ptr = tab_buffer(A.row_ptr, ((uint32_t)A.n_rows + 1u) * 8u);
-            choose(4 * wave + (lane >> 4));
+            choose(TOGETHER ? wave : 4 * wave + (lane >> 4));
             if (__any(have)) {
                 fetch();
                 const uint32_t n_rec = (uint32_t)A.n_edges * 4u, n_nodes = (uint32_t)A.n_nodes * kRow - 128u * hb;
@@ -573,7 +578,7 @@ template <int F, int KIND, int NW, int VALUES, int RING> __device__ __forceinlin
     auto gather = [&](const TabEdge &E, auto k) { ring[k % RING].load(SHARES ? abar : g, row_bcast<k>(E.goff) + at_f); };
     auto compute = [&](const TabStep &S, const TabEdge &E, float before, const Heads &H, const TabEdge &next) {
         const int32_t u = S.tb + l16 + 1;
-        const TabBits ends((u == S.item.n0 || u == S.item.n) && u <= S.item.n, lane);   // an edge that is its row's last
+        const TabBits ends(!TOGETHER && (u == S.item.n0 || u == S.item.n) && u <= S.item.n, lane);   // an edge that is its row's last
         TabRow<kI> gi = H.first;
         float q[16];
         unrolled<16 / GROUP>([&](auto grp) {
@@ -617,6 +622,14 @@ template <int F, int KIND, int NW, int VALUES, int RING> __device__ __forceinlin
                 else gather(next, std::integral_constant<int, k - 16>{});
             });
         });
+        if (SUMS && TOGETHER && __any(S.item.n > 0 && S.tb - offset + 64 >= S.item.n)) {   // the row's last step: the workers' sums together
+#pragma unroll
+            for (int i = 0; i < kI; ++i) acc.v[i] += __shfl_xor(acc.v[i], 16, 64);
+#pragma unroll
+            for (int i = 0; i < kI; ++i) acc.v[i] += __shfl_xor(acc.v[i], 32, 64);
+            if (lane < 16) acc.store(out, S.item.r0 * kRow + at_f);
+            acc.clear();
+        }
         if (SHARES) {
             __builtin_amdgcn_sched_barrier(0);
             const float sum = tab_reduce(q, lane);
@@ -625,11 +638,11 @@ template <int F, int KIND, int NW, int VALUES, int RING> __device__ __forceinlin
         }
     };
     auto advance = [&]() {
-        front.tb += 16;
-        const bool pop = front.tb >= front.item.n;
+        front.tb += stride;
+        const bool pop = front.tb - offset >= front.item.n;
         if (__any(pop)) {
             if (pop) {
-                front = TabStep{0, TabItem{r0, p0, (r1 - r0 == 2 ? p1 : p2) - p0, have ? p2 - p0 : 0}};
+                front = TabStep{offset, TabItem{r0, p0, (r1 - r0 == 2 ? p1 : p2) - p0, have ? p2 - p0 : 0}};
                 if (SUMS) {
                     const bool none0 = have && front.item.n0 == 0, none1 = have && r1 - r0 == 2 && front.item.n == front.item.n0;
                     if (__builtin_expect(__any(none0 || none1), 0)) {   // rows without edges
@@ -637,7 +650,7 @@ template <int F, int KIND, int NW, int VALUES, int RING> __device__ __forceinlin
                         if (none1) none.store(out, (r0 + 1) * kRow + at_f);
                     }
                 }
-                choose(row_bcast<0>(drawn));
+                choose(TOGETHER ? __builtin_amdgcn_readfirstlane(drawn) : row_bcast<0>(drawn));
                 draw();
             }
         }
@@ -645,7 +658,7 @@ template <int F, int KIND, int NW, int VALUES, int RING> __device__ __forceinlin
     };
     auto begin = [&]() {   // the records of a partition's first two steps
         draw();
-        front = TabStep{0, TabItem{0, 0, 0, 0}};   // no edges
+        front = TabStep{offset, TabItem{0, 0, 0, 0}};   // no edges
         advance();
         SA = front;
         RA = load(SA);
@@ -654,21 +667,20 @@ template <int F, int KIND, int NW, int VALUES, int RING> __device__ __forceinlin
         RB = load(SB);
     };
     next_part();
-    __syncthreads();   // (the counters)
     {
         LdsFill<K::kFloats / 4, NW * 64> fill;
         fill.load(B.tab + (size_t)hb * K::kFloats);
-        if (part < B.n) begin();   // asked for while the table is under way
         fill.store(lds);
     }
     __syncthreads();
-    for (; part < B.n; begin()) {
+    for (; part < B.n; ++part, next_part()) {
         float before_a, before_b;
+        begin();
         EA = edge(RA, SA);
         before_a = RA.before;
         heads(SA, HA);
         unrolled<RING>([&](auto k) { gather(EA, k); });
-        while (__any(have || SA.tb < SA.item.n || SB.tb < SB.item.n)) {
+        while (__any(have || SA.tb - offset < SA.item.n || SB.tb - offset < SB.item.n)) {
             advance();
             const TabStep SC = front;
             RA = load(SC);
@@ -688,28 +700,31 @@ template <int F, int KIND, int NW, int VALUES, int RING> __device__ __forceinlin
             compute(SB, EB, before_b, HB, EA);
             SB = SD;
         }
-        ++part;
-        next_part();
-        if (part >= B.n) break;
     }
+}
+template <int F, int KIND, int NW> __device__ __forceinline__ void edge_tab(const TabBatch &B, char *lds)
+{
+    constexpr TabShape shape = KIND == TAB_FWD ? kTabFwd : KIND == TAB_BWD ? kTabBwd : kTabLast;
+    if (B.together) edge_tab_walk<F, KIND, NW, shape.values, shape.ring, true>(B, lds);
+    else edge_tab_walk<F, KIND, NW, shape.values, shape.ring, false>(B, lds);
 }
 template <int F>
 __global__ void __launch_bounds__(kTabFwd.waves * 64, kTabFwd.waves / 4) k_edge_fwd_tab(TabBatch B)
 {
     extern __shared__ __align__(16) char tab_mem[];
-    edge_tab<F, TAB_FWD, kTabFwd.waves, kTabFwd.values, kTabFwd.ring>(B, tab_mem);
+    edge_tab<F, TAB_FWD, kTabFwd.waves>(B, tab_mem);
 }
 template <int F>
 __global__ void __launch_bounds__(kTabBwd.waves * 64, kTabBwd.waves / 4) k_edge_bwd_tab(TabBatch B)
 {
     extern __shared__ __align__(16) char tab_mem[];
-    edge_tab<F, TAB_BWD, kTabBwd.waves, kTabBwd.values, kTabBwd.ring>(B, tab_mem);
+    edge_tab<F, TAB_BWD, kTabBwd.waves>(B, tab_mem);
 }
 template <int F>
 __global__ void __launch_bounds__(kTabLast.waves * 64, kTabLast.waves / 4) k_edge_last_tab(TabBatch B)
 {
     extern __shared__ __align__(16) char tab_mem[];
-    edge_tab<F, TAB_LAST, kTabLast.waves, kTabLast.values, kTabLast.ring>(B, tab_mem);
+    edge_tab<F, TAB_LAST, kTabLast.waves>(B, tab_mem);
 }
 
 // ---------------------------------------------------------------- either way
@@ -732,17 +747,16 @@ __global__ void __launch_bounds__(kFwdWaves * 64, kFwdWaves / 4) k_edge_fwd_both
     if (*B.bad != 0)
         edge_fwd<F, PREC>(B.mlp, lds);
     else if ((int)(blockIdx.x >> 3) < B.tab.slots)
-        edge_tab<F, TAB_FWD, kFwdWaves, kTabFwd.values, kTabFwd.ring>(B.tab, reinterpret_cast<char *>(lds));
+        edge_tab<F, TAB_FWD, kFwdWaves>(B.tab, reinterpret_cast<char *>(lds));
 }
 template <int F, int PREC, int KIND>
 __global__ void __launch_bounds__(kBothBwdWaves * 64, kBothBwdWaves / 4) k_edge_bwd_both(BothBatch B)
 {
     extern __shared__ __align__(16) float lds[];
-    constexpr TabShape shape = KIND == TAB_BWD ? kTabBwd : kTabLast;
     if (*B.bad != 0)
         edge_bwd<F, PREC, kBothBwdWaves>(B.mlp, lds);
     else if ((int)(blockIdx.x >> 3) < B.tab.slots * TabKind<F, KIND>::kBlocks)
-        edge_tab<F, KIND, kBothBwdWaves, shape.values, shape.ring>(B.tab, reinterpret_cast<char *>(lds));
+        edge_tab<F, KIND, kBothBwdWaves>(B.tab, reinterpret_cast<char *>(lds));
 }
 
 #endif  // MLIP_MODEL_TABLE_H
