@@ -485,6 +485,7 @@ k_sort_rows(int64_t N, CellParams cp, const double *__restrict__ pos, const int6
 // follows from these notes without any search: half the candidate loads of the one-sided search and no binary
 // searches.  Rows are sorted afterwards, so the order in which the atomics hand out slots does not matter.
 constexpr int64_t kSharedCells = 4096;   // below this many cells four wavefronts share one (four cells fit a block otherwise)
+constexpr int64_t kFewCells = 64;      // below this many 16 do
 constexpr int kOwn = 64, kPar = 64;   // staging slots per atom for edges found by the atom itself / by its partners
 
 struct PairSearch {   // arrays of the pair-wise search
@@ -496,15 +497,16 @@ struct PairSearch {   // arrays of the pair-wise search
 };
 
 // n_home (at most kCrowd) atoms of cell c, in cell order from hb on, against the candidates of the cell, by one wavefront or
-// (SHARED) by the four of a block.  The candidates of a cell's atoms are the same: lanes first take the surrounding cells (64
+// (WAVES = 4, 16) by those of a block.  The candidates of a cell's atoms are the same: lanes first take the surrounding cells (64
 // at a time: first atom, length, image), then their atoms, flattened (a cell holds about 11), 64 at a time; every lane
 // keeps one candidate in registers and the home atoms are tested against it one after another, their records
-// broadcast from the lanes that loaded them.  Wavefronts that share a cell take its candidates in turn and count an
-// atom's finds in LDS.
-template <bool SHARED>
+// broadcast from the lanes that loaded them.  Wavefronts that share a cell take its candidates in turn, four at a time, of 16 every group of
+// four a fourth of the home atoms, and count an atom's finds in LDS.
+template <int WAVES>
 __device__ inline void search_home(int32_t c, int32_t hb, int n_home, const CellParams &cp, const PairSearch &A, int32_t *found,
                                    bool &coincident, bool &overflow)
 {
+    constexpr bool SHARED = WAVES > 1;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int cr = c;
     const int b2 = cr % cp.nb[2];
@@ -542,7 +544,7 @@ __device__ inline void search_home(int32_t c, int32_t hb, int n_home, const Cell
         }
         const int32_t inc = wave_inclusive_scan(len);
         const int32_t total = __builtin_amdgcn_readlane(inc, 63);
-        for (int32_t t0 = SHARED ? 64 * wave : 0; t0 < total; t0 += SHARED ? 256 : 64) {
+        for (int32_t t0 = SHARED ? 64 * (wave & 3) : 0; t0 < total; t0 += SHARED ? 256 : 64) {
             // lane = candidate t: the cell it lies in is the first whose running total exceeds t
             const int32_t t = t0 + lane;
             int k = 0;
@@ -564,7 +566,7 @@ __device__ inline void search_home(int32_t c, int32_t hb, int n_home, const Cell
             uint32_t w_cur = 0;   // wrap counts of the atom the shift below was worked out for (0: none)
             int S0 = 0, S1 = 0, S2 = 0;
             double s0 = 0, s1 = 0, s2 = 0;
-            for (int hk = 0; hk < n_home; ++hk) {
+            for (int hk = SHARED ? wave >> 2 : 0; hk < n_home; hk += SHARED ? WAVES / 4 : 1) {
                 const uint32_t wi = (uint32_t)__builtin_amdgcn_readlane((int)hw, hk);
                 if (wi != w_cur) {   // wave-uniform; atoms of one cell mostly share their wrap counts
                     w_cur = wi;
@@ -617,21 +619,22 @@ __device__ inline void search_home(int32_t c, int32_t hb, int n_home, const Cell
     if (lane < n_home && (!SHARED || wave == 0)) A.n_own[hb + lane] = cnt;
 }
 
-// One cell per wavefront or (SHARED) per block of four, in the first cell_blocks blocks.  A candidate is loaded once
+// One cell per wavefront or (WAVES = 4, 16) per block, in the first cell_blocks blocks.  A candidate is loaded once
 // per cell instead of once per atom, and nothing waits in a chain of dependent loads: one thread per atom walking the
 // cells was bound by that chain, 118 us at any size below 60,000 atoms and 544 us at a million;
 // here 19 us at 500 atoms, 28 us at 32,000 and 390 us at a million.
 // Crowded cells (a cluster in a large box, where there are at most 8 cells per atom and a cell is much wider than the
 // cutoff) are left to the blocks behind those: one per run of kCrowd places in cell order, four wavefronts on the run's part
 // of a crowded cell.  A crowded cell is longer than a run, so it holds the first or the last place of every run it
-// reaches into.  A build in us with one wavefront on every cell -> here: 4,000 atoms in a box of 500 A (340 atoms per cell) 3450
+// reaches into.  Blocks of 16 below kFewCells cells: 108 atoms 13.7 us, so 9.4, 500 atoms 18.6 and 12.0 (343 cells 12.8 and 13.8).  A build in us with one wavefront on every cell -> here: 4,000 atoms in a box of 500 A (340 atoms per cell) 3450
 // -> 169, 32,000 in 1,000 A 7900 -> 430, 256,000 in 1,500 A 5850 -> 1360; in lattices, where no cell is crowded, the same
 // from 108 atoms to a million.
-template <bool SHARED>
-__global__ void __launch_bounds__(256)
+template <int WAVES>
+__global__ void __launch_bounds__(WAVES == 16 ? 1024 : 256)
 k_neighbours_pairs(int64_t N, int64_t n_cells, unsigned cell_blocks, CellParams cp, PairSearch A,
                    const int32_t *__restrict__ cell_of, int32_t *err)
 {
+    constexpr bool SHARED = WAVES > 1;
     __shared__ int32_t found[kCrowd];   // SHARED: edges found so far by the home atoms
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     bool coincident = false, overflow = false;
@@ -642,7 +645,7 @@ k_neighbours_pairs(int64_t N, int64_t n_cells, unsigned cell_blocks, CellParams 
         const int32_t h0 = __builtin_amdgcn_readfirstlane(A.cell_start[c]);
         const int n = __builtin_amdgcn_readfirstlane(A.cell_start[c + 1]) - h0;
         if (n <= 0 || n > kCrowd) return;
-        search_home<SHARED>((int32_t)c, h0, n, cp, A, found, coincident, overflow);
+        search_home<WAVES>((int32_t)c, h0, n, cp, A, found, coincident, overflow);
     } else {
         if (!(__atomic_load_n(err, __ATOMIC_RELAXED) & FLAG_CROWDED)) return;   // (set before this launch: the same for the block)
         const unsigned run = blockIdx.x - cell_blocks, runs = gridDim.x - cell_blocks;
@@ -656,7 +659,7 @@ k_neighbours_pairs(int64_t N, int64_t n_cells, unsigned cell_blocks, CellParams 
             const int32_t h1 = __builtin_amdgcn_readfirstlane(A.cell_start[c + 1]);
             if (h1 - h0 <= kCrowd) continue;
             const int32_t from = max((int32_t)p0, h0), to = min((int32_t)p1, h1);
-            search_home<true>(c, from, to - from, cp, A, found, coincident, overflow);
+            search_home<WAVES == 1 ? 4 : WAVES>(c, from, to - from, cp, A, found, coincident, overflow);
         }
     }
     if (overflow) atomicOr(err, FLAG_STAGE_OVERFLOW);
@@ -1800,18 +1803,19 @@ int search_csr(mlip_graph *g, const CellParams &cp, int64_t N, int32_t P, const 
         int32_t *stage_q = n_own + N;
         uint8_t *pslot_own = reinterpret_cast<uint8_t *>(stage_q + (size_t)N * kOwn);
         uint8_t *rank_own = pslot_own + (size_t)N * kOwn, *rank_par = rank_own + (size_t)N * kOwn;
-        // few cells: four wavefronts share each, so that the chip has something to do and a crowded cell is not one chain
-        auto search = [&](auto shared) {
-            constexpr bool SHARED = decltype(shared)::value;
-            const unsigned cell_blocks = grid8(SHARED ? ncell : (ncell + 3) / 4);
-            k_neighbours_pairs<SHARED><<<cell_blocks + grid8((N + kCrowd - 1) / kCrowd), 256, 0, s>>>(
+        // few cells: four wavefronts or 16 share each, so that the chip has something to do and a crowded cell is not one chain
+        auto search = [&](auto waves) {
+            constexpr int WAVES = decltype(waves)::value;
+            const unsigned cell_blocks = grid8(WAVES > 1 ? ncell : (ncell + 3) / 4);
+            k_neighbours_pairs<WAVES><<<cell_blocks + grid8((N + kCrowd - 1) / kCrowd), WAVES == 16 ? 1024 : 256, 0, s>>>(
                 N, ncell, cell_blocks, cp,
                 PairSearch{g->cell_start.as<int32_t>(), g->sid.as<int32_t>(), g->sx.as<double>(), g->sy.as<double>(),
                            g->sz.as<double>(), g->swrap.as<uint32_t>(), stage_own, stage_q, n_own},
                 g->cell_of.as<int32_t>(), err);
         };
-        if (ncell < kSharedCells) search(std::true_type{});
-        else search(std::false_type{});
+        if (ncell < kFewCells) search(std::integral_constant<int, 16>{});
+        else if (ncell < kSharedCells) search(std::integral_constant<int, 4>{});
+        else search(std::integral_constant<int, 1>{});
         MLIP_HIP(hipGetLastError());
         k_pair_partners<<<blocks_for(N * kOwn, 256), 256, 0, s>>>(N, g->sid.as<int32_t>(), n_own, stage_own, stage_q, stage_par,
                                                                   pslot_own, n_par, err);
