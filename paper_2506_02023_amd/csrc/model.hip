@@ -492,9 +492,6 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             a.l_slot = v.pairs.l_slot;
             const bool bonds = bw && v.bonds.n > 0;
             sb.bonds |= bonds;
-            a.b_ptr = bonds ? v.bonds.ptr.as<int64_t>() : nullptr;
-            a.b_sender = bonds ? v.bonds.sender.as<int32_t>() : nullptr;
-            a.b_mirror = bonds ? v.bonds.mirror.as<int32_t>() : nullptr;
             a.bond_of_edge = bonds ? v.bonds.of_edge.as<int32_t>() : nullptr;
             a.wb_bf16 = (prec == kPrecBf16);
             a.wb = (bonds && layer >= 0)
@@ -759,6 +756,23 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         prof_end(g);
         return MLIP_OK;
     };
+    auto bond_sum = [&](int p0, int l, bool backward) -> int {   // the bonds' terms of the rows that edge_step has summed
+        prof_begin(g, MLIP_PROF_BOND);
+        BondSumBatch b{};
+        b.n = std::min(kBatch, P - p0);
+        for (int q = 0; q < b.n; ++q) {
+            SlabView &v = views[p0 + q];
+            b.start[q + 1] = b.start[q] + v.n_owned;
+            if (v.bonds.n > 0)
+                b.s[q] = BondSumArgs{v.bonds.ptr.as<int64_t>(), v.bonds.sender.as<int32_t>(), backward ? v.bonds.mirror.as<int32_t>() : nullptr,
+                                     wbslice(v, l), backward ? abarslice(v, l) : gslice(v, l), backward ? v.ws.gbar : aslice(v, l)};
+        }
+        if (b.start[b.n] > 0)
+            bond_elem([&](auto zero) { k_bond_sum<F, decltype(zero)><<<grid8((b.start[b.n] + 3) / 4), 256, 0, s>>>(b); });
+        MLIP_HIP(hipGetLastError());
+        prof_end(g);
+        return MLIP_OK;
+    };
     int64_t tiles_before = 0;
     auto tile_sums = [&](SlabView &v) {
         double *at = energy_part + tiles_before;
@@ -790,21 +804,9 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             })));
         }
         prof_end(g);
-        for (int p0 = 0; p0 < P; p0 += kBatch) MLIP_TRY(edge_step(p0, l, false));   // the partitions in order, up to kBatch per launch
-        if (any_bonds) {   // bond term of the filters: a_i += sum_b wb_b * g_send(b)
-            prof_begin(g, MLIP_PROF_BOND);
-            for (int p = 0; p < P; ++p) {
-                SlabView &v = views[p];
-                if (v.bonds.n > 0)
-                    bond_elem([&](auto zero) {
-                        using BT = decltype(zero);
-                        k_bond_aggregate<F, BT><<<blocks_for(v.n_owned, 4), 256, 0, s>>>(
-                            v.n_owned, v.bonds.ptr.as<int64_t>(), v.bonds.sender.as<int32_t>(),
-                            static_cast<const BT *>(wbslice(v, l)), gslice(v, l), aslice(v, l));
-                    });
-            }
-            MLIP_HIP(hipGetLastError());
-            prof_end(g);
+        for (int p0 = 0; p0 < P; p0 += kBatch) {   // the partitions in order, up to kBatch per launch
+            MLIP_TRY(edge_step(p0, l, false));
+            if (any_bonds) MLIP_TRY(bond_sum(p0, l, false));
         }
     }
 
@@ -846,7 +848,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         const bool need_gbar = l > 0;  // (as in edge_batch)
         for (int p0 = 0; p0 < P; p0 += kBatch) {
             MLIP_TRY(edge_step(p0, l, true));
-            if (need_gbar && (by != BY_TABLE || any_bonds)) {   // second pass: the lower edges' terms of the rows' sums, and the bonds'
+            if (need_gbar && by != BY_TABLE) {   // second pass: the lower edges' terms of the rows' sums
                 prof_begin(g, MLIP_PROF_EDGE_BWD_LOWER);
                 const SmallBatch sb = small_batch(p0, U_OWNED, l);
                 if (sb.start[sb.n] > 0)
@@ -854,6 +856,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
                 MLIP_HIP(hipGetLastError());
                 prof_end(g);
             }
+            if (need_gbar && any_bonds) MLIP_TRY(bond_sum(p0, l, true));
         }
         if (need_gbar) {
             if (slabs && (by != BY_TABLE || any_bonds)) {

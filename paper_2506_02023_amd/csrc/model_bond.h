@@ -273,36 +273,66 @@ k_triplet_fwd(int64_t N, const int64_t *__restrict__ bptr, const float *__restri
     else triplet_fwd_any<F, BT>(b0, b1e, lane, rhat, u, P, Q, Wtc, S);
 }
 
-// bond term of a layer's aggregation: a[i] += sum over the bonds b = (i <- j) of wb[b] * g[j].  One wavefront per centre, lane =
-// feature, 16 bonds' rows in flight together; 215 us per layer at 2.4 M bonds (622 MB of bond rows).  The share of gbar, in which the reverse bonds' filters appear, is taken by k_edge_lower.
-template <int F, typename BT>
-__global__ void __launch_bounds__(256)
-k_bond_aggregate(int64_t N, const int64_t *__restrict__ bptr, const int32_t *__restrict__ sender,
-                 const BT *__restrict__ wb, const float *__restrict__ g, float *__restrict__ a)
+// Bond terms of a layer's rows, of up to kBatch partitions: out_i += sum over the bonds b = (i <- j) of wb[m_b] * from_j, forward m_b = b, from g
+// and out a; reverse m_b the reverse bond (j <- i), whose filter multiplies g_i in row j, from abar and out gbar (no term if the sender is a
+// ghost row: abar_j = 0, its owner adds that one).  One wavefront per centre, a row for F / 4 lanes of 16 bytes (8 in bf16), 16 bonds' rows in
+// flight together whose places the lanes look up for themselves.  Bound by the bond rows (2.4 M bonds, 622 MB:
+// 164 us per layer; 214 forward and 246 reverse with lane = feature, rows looked up one after another).
+struct BondSumArgs {
+    const int64_t *ptr;
+    const int32_t *sender, *mirror;   // mirror == nullptr: forward
+    const void *wb;
+    const float *from;
+    float *out;
+};
+struct BondSumBatch {
+    int n;
+    int64_t start[kBatch + 1];
+    BondSumArgs s[kBatch];
+};
+template <int F, typename BT> __global__ void __launch_bounds__(256) k_bond_sum(BondSumBatch B)
 {
+    constexpr int kLanes = F / 4, kRows = 64 / kLanes, kTurns = 16 / kRows;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int64_t i = (int64_t)blockIdx.x * 4 + wave;
-    if (i >= N) return;
-    const int f = lane & (F - 1);
-    const int64_t b0 = __builtin_amdgcn_readfirstlane((int32_t)bptr[i]), b1 = __builtin_amdgcn_readfirstlane((int32_t)bptr[i + 1]);
-    const float before = a[i * F + f];   // (requested with the indices)
-    float acc = 0.f;
+    const int64_t gi = (int64_t)xcd_block() * 4 + wave;
+    if (gi >= B.start[B.n]) return;
+    const int part = batch_find(B.start, B.n, gi);
+    const BondSumArgs &A = B.s[part];
+    if (!A.ptr) return;   // (no bonds)
+    const int64_t i = gi - B.start[part];
+    const int sub = lane / kLanes, f = 4 * (lane % kLanes);
+    const int64_t b0 = A.ptr[i], b1 = A.ptr[i + 1];
+    if (b0 >= b1) return;
+    float *out = A.out + i * F + f;
+    const f32x4 before = *reinterpret_cast<const f32x4 *>(out);   // (requested with the indices)
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     for (int64_t bb = b0; bb < b1; bb += 16) {
-        const int n = (int)min((int64_t)16, b1 - bb);
-        const int32_t jl = sender[min(bb + (lane & 15), b1 - 1)];
-        float wv[16], gv[16];
+        int64_t m[kTurns], j[kTurns];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            wv[k] = gv[k] = 0.f;
-            if (k < n) {
-                wv[k] = Elem<BT>::load(wb + (bb + k) * F + f);
-                gv[k] = g[(int64_t)__builtin_amdgcn_readlane(jl, k) * F + f];
+        for (int t = 0; t < kTurns; ++t) {
+            const int64_t b = bb + t * kRows + sub;
+            m[t] = b < b1 ? (A.mirror ? (int64_t)A.mirror[b] : b) : -1;
+            j[t] = A.sender[min(b, b1 - 1)];
+        }
+        f32x4 w[kTurns], x[kTurns];
+#pragma unroll
+        for (int t = 0; t < kTurns; ++t) {
+            w[t] = x[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (m[t] >= 0) {
+                w[t] = Elem<BT>::load4(static_cast<const BT *>(A.wb) + m[t] * F + f);
+                x[t] = *reinterpret_cast<const f32x4 *>(A.from + j[t] * F + f);
             }
         }
 #pragma unroll
-        for (int k = 0; k < 16; ++k) acc = fmaf(wv[k], gv[k], acc);
+        for (int t = 0; t < kTurns; ++t)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[c] = fmaf(w[t][c], x[t][c], acc[c]);
     }
-    if (F == 64 || lane < F) a[i * F + f] = before + acc;
+#pragma unroll
+    for (int off = kLanes; off < 64; off *= 2)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[c] += __shfl_xor(acc[c], off, 64);
+    if (lane < kLanes) *reinterpret_cast<f32x4 *>(out) = before + acc;
 }
 
 // Reverse of k_triplet_fwd for one centre, any number of bonds, no LDS.  Pbar[b1] and rbar[b1] accumulate over the

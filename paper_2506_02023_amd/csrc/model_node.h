@@ -259,9 +259,7 @@ struct SmallArgs {   // one partition
     const float *dsum, *wstore, *d;
     const float *dsum2;            // on tables: null or the second half of the features' share, and the elements between two edges' sums
     int dsum_step;
-    const int32_t *bond_of_edge;   // three-body variant (or nullptr): bond of an edge, bonds per owned row, sender, reverse bond
-    const int64_t *b_ptr;
-    const int32_t *b_sender, *b_mirror;
+    const int32_t *bond_of_edge;   // three-body variant (or nullptr): bond of an edge
     const void *wb;                // bond filter rows of the layer: fp32, or bf16 if wb_bf16
     int wb_bf16;
 };
@@ -299,8 +297,7 @@ constexpr int kLowerChunk = 16;   // lower edges whose rows are in flight togeth
 template <int F>
 __global__ void __launch_bounds__(256) k_edge_lower(SmallBatch B)
 {
-    const bool kept = !B.on_tables();   // on tables the reverse step has the lower edges already
-    if (!kept && !B.bonds) return;
+    if (B.on_tables()) return;   // the reverse step has the lower edges already
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int64_t gk = (int64_t)blockIdx.x * 4 + wave;
     if (gk >= B.start[B.n]) return;
@@ -308,10 +305,9 @@ __global__ void __launch_bounds__(256) k_edge_lower(SmallBatch B)
     const SmallArgs &A = B.s[part];
     const int64_t r = gk - B.start[part];
     const unsigned f = lane & (F - 1);
-    if (!kept && !A.b_ptr) return;
     // the row's lower edges (wave-uniform, kept scalar; edge indices fit 32 bits)
-    const int64_t e0 = kept ? __builtin_amdgcn_readfirstlane((int32_t)A.l_row_ptr[r]) : 0;
-    const int64_t e1 = kept ? __builtin_amdgcn_readfirstlane((int32_t)A.l_row_ptr[r + 1]) : 0;
+    const int64_t e0 = __builtin_amdgcn_readfirstlane((int32_t)A.l_row_ptr[r]);
+    const int64_t e1 = __builtin_amdgcn_readfirstlane((int32_t)A.l_row_ptr[r + 1]);
     const float before = A.gbar[r * F + f];   // (requested with the indices)
     float acc = 0.f;
     for (int64_t eb = e0; eb < e1; eb += 64) {
@@ -332,28 +328,6 @@ __global__ void __launch_bounds__(256) k_edge_lower(SmallBatch B)
             }
 #pragma unroll
             for (int t = 0; t < kLowerChunk; ++t) acc = fmaf(wv[t], gv[t], acc);
-        }
-    }
-    if (A.b_ptr) {   // three-body variant: gbar_i += sum_b wb[mirror(b)] * abar_j (the reverse bond (j <- i) is the one whose
-                     // filter multiplies g_i in row j; none here if the sender is a ghost row: abar_j = 0, its owner adds that term)
-        const int64_t b0 = __builtin_amdgcn_readfirstlane((int32_t)A.b_ptr[r]), b1 = __builtin_amdgcn_readfirstlane((int32_t)A.b_ptr[r + 1]);
-        for (int64_t bb = b0; bb < b1; bb += 16) {
-            const int n = (int)min((int64_t)16, b1 - bb);
-            const int64_t bl = min(bb + (lane & 15), b1 - 1);
-            const int32_t jl = A.b_sender[bl], ml = A.b_mirror[bl];
-            float wv[16], gv[16];
-#pragma unroll
-            for (int t = 0; t < 16; ++t) {
-                wv[t] = gv[t] = 0.f;
-                const int64_t m = __builtin_amdgcn_readlane(ml, t);
-                if (t < n && m >= 0) {
-                    wv[t] = A.wb_bf16 ? Elem<__bf16>::load(static_cast<const __bf16 *>(A.wb) + m * F + f)
-                                      : static_cast<const float *>(A.wb)[m * F + f];
-                    gv[t] = A.abar[(int64_t)__builtin_amdgcn_readlane(jl, t) * F + f];
-                }
-            }
-#pragma unroll
-            for (int t = 0; t < 16; ++t) acc = fmaf(wv[t], gv[t], acc);
         }
     }
     if (F == 64 || lane < F) A.gbar[r * F + f] = before + acc;
