@@ -396,7 +396,6 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
     }
     const int32_t *gate = by == BOTH_WAYS ? &tab_state->bad : nullptr;   // != null: the launches look at it
 
-    const int dsum_step = F == 64 && L > 1 && !scratch ? 2 : 1;   // on tables: the halves' sums of an edge side by side, in the fixed block one array each
 
     // By MLP: both edges of an edge / reverse-edge pair have the same length, hence bit for bit the same filter values: the
     // forward kernel keeps those of the upper edges, the reverse kernel runs on the partitions' upper-edge graphs and a
@@ -437,7 +436,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
         if (F == 64 && L > 1 && by != BY_MLP)   // on tables every block of 32 features has its own sums (the one step of a model of one layer takes all
                                                 // 64 at a time); in the fixed block, whose limit does not depend on the way, the second ones
                                                 // lie where the way by MLP has its kept filter values (F per pair, at least one per edge)
-            v.ws.dsum2 = scratch ? v.ws.wst : v.ws.dsum + 1;
+            v.ws.dsum2 = scratch ? v.ws.wst : v.ws.dsum + ne;
         n_parts += (v.n_owned + 31) / 32;
     }
     float *energy_part_f = nullptr;
@@ -482,8 +481,6 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             a.floc = v.ws.floc;
             a.eps = v.ws.eps;
             a.dsum = v.ws.dsum;
-            a.dsum2 = v.ws.dsum2;
-            a.dsum_step = dsum_step;
             a.d = v.d;
             a.wstore = layer >= 1 ? wslice(v, layer) : nullptr;
             a.uslot = v.pairs.uslot;
@@ -684,7 +681,6 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
             a.out = backward ? v.ws.gbar : aslice(v, l);
             a.dsum[0] = v.ws.dsum;
             a.dsum[1] = v.ws.dsum2;
-            a.dsum_step = dsum_step;
         }
         return b;
     };

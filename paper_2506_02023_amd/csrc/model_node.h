@@ -257,8 +257,6 @@ struct SmallArgs {   // one partition
     const int64_t *l_row_ptr;      // the owned rows' lower edges: CSR, sender row, where the pair's filter values are kept
     const int32_t *l_senders, *l_slot;
     const float *dsum, *wstore, *d;
-    const float *dsum2;            // on tables: null or the second half of the features' share, and the elements between two edges' sums
-    int dsum_step;
     const int32_t *bond_of_edge;   // three-body variant (or nullptr): bond of an edge
     const void *wb;                // bond filter rows of the layer: fp32, or bf16 if wb_bf16
     int wb_bf16;
@@ -431,17 +429,7 @@ k_force_rows(SmallBatch B, const double *__restrict__ pos, CellParams cp, float 
         // dE/dd times the unit vector: the edge's stored length (the fp64 length rounded once to fp32) is accurate
         // to 6e-8, far inside the force bound, and spares an fp64 square root and division per edge
         float dd = A.dsum[e];
-        if (tables) {   // an edge holds the share in which its receiver's row of g took part: the reverse edge has the other one
-            const int64_t m = A.mirror[e];
-            if (!A.dsum2) {
-                dd += A.dsum[m];
-            } else if (A.dsum_step == 2) {
-                const f32x2 own = reinterpret_cast<const f32x2 *>(A.dsum)[e], other = reinterpret_cast<const f32x2 *>(A.dsum)[m];
-                dd = (own[0] + own[1]) + (other[0] + other[1]);
-            } else {
-                dd = (dd + A.dsum2[e]) + (A.dsum[m] + A.dsum2[m]);
-            }
-        }
+        if (tables) dd += A.dsum[A.mirror[e]];   // an edge holds the share in which its receiver's row of g took part: the reverse edge has the other one
         const double s = (double)(dd * __builtin_amdgcn_rcpf(A.d[e]));
         fx += s * t0;
         fy += s * t1;

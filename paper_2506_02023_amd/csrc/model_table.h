@@ -243,16 +243,16 @@ __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
 // clocks where it lies in the L2, whatever the width of the load, and a store of 4 bytes a lane as much as one of 16.
 
 struct TabArgs {               // one partition
-    int32_t n_rows, n_edges;   // receiver rows processed and their edges (below 2^29: 32-bit byte offsets of 8-byte sums)
+    int32_t n_rows, n_edges;   // receiver rows processed and their edges (below 2^29: 32-bit byte offsets)
     int32_t n_nodes;           // rows of g / abar
-    int32_t dsum_step;         // floats from an edge's sum to the next one's
     const int64_t *row_ptr;
     const int32_t *chunk_row;  // the graph's work-item table: first row whose first edge lies at or after c * span
     int32_t span;
     const int32_t *senders;
     const float *d, *g, *abar;
     float *out;                // forward: a [n_rows][F]; reverse: gbar [n_rows][F]
-    float *dsum[2];            // reverse: per edge its share of dE/dd, summed over the layers, of each block of 32 features
+    float *dsum[2];            // reverse: per edge its share of dE/dd, summed over the layers, of each block of 32 features; layer 0's step adds
+                               // up the blocks' sums and its own share in the first
 };
 struct TabBatch {
     const float *tab;      // the layer's table of the step's kind
@@ -386,7 +386,7 @@ struct TabStep {     // one step of a worker: edges tb to tb + 15 of an item, as
 };
 struct TabRec {      // as loaded
     int32_t sj;
-    float d, before; // before: reverse, the sum of the later layers at the lane's edge
+    float d, before, before1; // reverse: the sums of the later layers at the lane's edge
 };
 struct TabEdge {     // what the lanes of the worker need of an edge
     int32_t goff;    // byte offset of the sender's row; past the end of the array for an edge past the item's last: its row reads 0
@@ -488,8 +488,7 @@ template <int F, int KIND, int NW, int VALUES, int RING, bool TOGETHER> __device
     int part = 0;
     bool have = false;                        // whether there is a next item
     int32_t lo = 0, hi = 0;                   // the XCD's rows; lo: the first one dealt to this block
-    __amdgpu_buffer_rsrc_t ptr, send, dist, g, abar, out, sums;
-    int sum_shift = 2;
+    __amdgpu_buffer_rsrc_t ptr, send, dist, g, abar, out, sums, sums1;
     const int32_t turn = n_slots * kTabDeal * rows;   // rows from one of the block's turns to the next
     auto choose = [&](int32_t k) {
         r0 = lo + __mul24(k >> 3, turn) + __mul24(k & (kTabDeal - 1), rows);
@@ -534,8 +533,8 @@ template <int F, int KIND, int NW, int VALUES, int RING, bool TOGETHER> __device
                 g = tab_buffer(A.g + 32 * hb, n_nodes);
                 if (SHARES) {
                     abar = tab_buffer(A.abar + 32 * hb, n_nodes);
-                    sum_shift = A.dsum_step == 2 ? 3 : 2;
-                    sums = tab_buffer(hb ? A.dsum[1] : A.dsum[0], ((uint32_t)A.n_edges << sum_shift) - (sum_shift == 3 ? 4u * hb : 0u));
+                    sums = tab_buffer(hb ? A.dsum[1] : A.dsum[0], n_rec);
+                    if (KIND == TAB_LAST && F == 64) sums1 = tab_buffer(A.dsum[1], B.first ? 0 : n_rec);
                 }
                 if (SUMS) out = tab_buffer(A.out + 32 * hb, (uint32_t)A.n_rows * kRow - 128u * hb);
                 break;
@@ -553,8 +552,9 @@ template <int F, int KIND, int NW, int VALUES, int RING, bool TOGETHER> __device
     Heads HA, HB;
     auto load = [&](const TabStep &S) {   // (past the item's last edge another item's, or nothing: not counted)
         const int32_t e = S.item.e0 + S.tb + l16;
+        const float before1 = KIND == TAB_LAST && F == 64 ? buffer_load_f32(sums1, (uint32_t)e * 4u, 0, 0) : 0.f;
         return TabRec{buffer_load_i32(send, (uint32_t)e * 4u), buffer_load_f32(dist, (uint32_t)e * 4u, 0, 0),
-                      SHARES && !B.first ? buffer_load_f32(sums, (uint32_t)e << sum_shift, 0, 0) : 0.f};
+                      SHARES && !B.first ? buffer_load_f32(sums, (uint32_t)e * 4u, 0, 0) : 0.f, before1};
     };
     auto edge = [&](const TabRec &R, const TabStep &S) {
         TabEdge E;
@@ -634,7 +634,7 @@ template <int F, int KIND, int NW, int VALUES, int RING, bool TOGETHER> __device
             __builtin_amdgcn_sched_barrier(0);
             const float sum = tab_reduce(q, lane);
             if (S.tb + l16 < S.item.n)
-                buffer_store_f32(KIND == TAB_BWD ? fmaf(sum, E.slope, before) : sum + before, sums, (uint32_t)(S.item.e0 + S.tb + l16) << sum_shift, 0, 0);
+                buffer_store_f32(KIND == TAB_BWD ? fmaf(sum, E.slope, before) : sum + before, sums, (uint32_t)(S.item.e0 + S.tb + l16) * 4u, 0, 0);
         }
     };
     auto advance = [&]() {
@@ -677,7 +677,7 @@ template <int F, int KIND, int NW, int VALUES, int RING, bool TOGETHER> __device
         float before_a, before_b;
         begin();
         EA = edge(RA, SA);
-        before_a = RA.before;
+        before_a = RA.before + RA.before1;
         heads(SA, HA);
         unrolled<RING>([&](auto k) { gather(EA, k); });
         while (__any(have || SA.tb - offset < SA.item.n || SB.tb - offset < SB.item.n)) {
@@ -685,7 +685,7 @@ template <int F, int KIND, int NW, int VALUES, int RING, bool TOGETHER> __device
             const TabStep SC = front;
             RA = load(SC);
             EB = edge(RB, SB);
-            before_b = RB.before;
+            before_b = RB.before + RB.before1;
             heads(SB, HB);
             __builtin_amdgcn_sched_barrier(0);
             compute(SA, EA, before_a, HA, EB);
@@ -694,7 +694,7 @@ template <int F, int KIND, int NW, int VALUES, int RING, bool TOGETHER> __device
             const TabStep SD = front;
             RB = load(SD);
             EA = edge(RA, SA);
-            before_a = RA.before;
+            before_a = RA.before + RA.before1;
             heads(SA, HA);
             __builtin_amdgcn_sched_barrier(0);
             compute(SB, EB, before_b, HB, EA);
