@@ -1,0 +1,77 @@
+"""Sizes at which an edge step on tables changes how it shares rows out (four workers of a wavefront to a row up to four rows for a compute
+unit, a row each beyond), with rows longer than a wavefront takes at once and rows without an edge; and the sums over a row's bonds,
+sixteen at a time, at 32 features."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from oracle import graph as og
+from oracle import model as om
+from oracle import three_body as tb
+
+from gpu_util import E_RTOL, F_RTOL, gpu_graph
+
+pytestmark = pytest.mark.gpu
+
+
+def _system(n):
+    """n atoms: a ball of 80 with up to 79 neighbours, four far from everything, the rest a jittered lattice of some 12"""
+    rng = np.random.default_rng(n)
+    ball = [rng.uniform(0, 6.5, 3)]
+    while len(ball) < 80:
+        p = rng.uniform(0, 6.5, 3)
+        if np.linalg.norm(np.array(ball) - p, axis=1).min() >= 1.0:
+            ball.append(p)
+    lone = np.array([[70.0, 10.0 * k + 5.0, 20.0] for k in range(4)])
+    sites = np.stack(np.meshgrid(*[np.arange(10)] * 3, indexing="ij"), -1).reshape(-1, 3)[:n - 84] * 3.5 + 22.0
+    pos = np.concatenate([sites + rng.uniform(-0.3, 0.3, sites.shape), np.array(ball) + 4.0, lone])
+    return pos[rng.permutation(n)], np.diag([82.0, 60.0, 60.0])
+
+
+@pytest.mark.parametrize("n", [511, 512, 513, 1023, 1024, 1025])   # (256 compute units: 512 rows with 64 features reverse, else 1024)
+@pytest.mark.parametrize("F", [32, 64])
+def test_rows_to_a_wavefront_or_a_worker(n, F):
+    import torch
+    import paper_2506_02023_amd as M
+    pos, cell = _system(n)
+    spec = (np.arange(n) % 4).astype(np.int32)
+    w = wl.rmp_weights(4, F, 2, 21)
+    ref_g = og.build_graph(pos, cell, 5.0)
+    rows = np.diff(ref_g.row_ptr)
+    assert rows.max() > 64 and rows.min() == 0
+    ref = om.energy_forces(pos, cell, spec, w, ref_g, 5.0, 8, 6)
+    W = M.Weights(w, 6)
+    for P in (1, 3):
+        g = gpu_graph(pos, cell, spec, 5.0, n_slabs=P)
+        first = None
+        for call in ("undecided", "on tables"):   # (the first launches hold both ways: the same bits)
+            e, f, ae = M.mlip_forward(g, W, M.MODE_SLABS if P > 1 else M.MODE_WHOLE)
+            torch.cuda.synchronize()
+            got = [x.cpu().numpy() for x in (e, f, ae)]
+            assert abs(float(got[0][0]) - ref["energy"]) <= E_RTOL * np.abs(ref["atom_energy"]).sum(), (P, call)
+            assert np.abs(got[1] - ref["forces"]).max() <= F_RTOL * np.abs(ref["forces"]).max(), (P, call)
+            assert np.abs(got[2] - ref["atom_energy"]).max() <= 1e-5 * np.abs(ref["atom_energy"]).max(), (P, call)
+            assert first is None or all(np.array_equal(a, b) for a, b in zip(first, got)), (P, call)
+            first = got
+
+
+@pytest.mark.parametrize("precision,bound", [(0, F_RTOL), (1, 2e-2)])   # (1: bond rows in bf16, the bound of that mode)
+@pytest.mark.parametrize("P", [1, 2])
+def test_bond_sums_of_long_and_empty_rows(precision, bound, P):
+    """Rows of more than sixteen bonds, fewer, and none, 32 features"""
+    import torch
+    import paper_2506_02023_amd as M
+    pos, cell = _system(300)
+    spec = (np.arange(300) % 4).astype(np.int32)
+    w = wl.rmp_weights(4, 32, 2, 33)
+    w.update(wl.three_body_weights(32, 2, 33))
+    ref_g = og.build_graph(pos, cell, 5.0)
+    _, bptr, _ = tb.bond_graph(pos, cell, ref_g, 3.4)
+    assert np.diff(bptr).max() > 32 and np.any(np.diff(bptr) == 0) and np.any((np.diff(bptr) > 0) & (np.diff(bptr) < 8))
+    ref = tb.energy_forces3(pos, cell, spec, w, ref_g, 5.0, 3.4, 8, 6)
+    g = gpu_graph(pos, cell, spec, 5.0, n_slabs=P)
+    W = M.Weights({k: w[k] for k in ("emb", "W1", "W2", "Wm", "Wo", "Wr1", "wr2")}, 6, precision=precision)
+    for _ in range(2):
+        f = M.mlip_forward_bonds(g, W, M.BondWeights(w, 3.4, 8), M.MODE_SLABS if P > 1 else M.MODE_WHOLE)[1]
+        torch.cuda.synchronize()
+        assert np.abs(f.cpu().numpy() - ref["forces"]).max() <= bound * np.abs(ref["forces"]).max()
