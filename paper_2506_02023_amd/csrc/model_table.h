@@ -181,8 +181,8 @@ __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
     half[0][node][lane] = half0;
     half[1][node][lane] = half1;
     __syncthreads();
-    // What is cut off: a6 T6 + a7 T7 of the values and of the slopes, a6 + a7 at most; of a derivative 8 a6 + 10 a7 (root mean squares of T6' and
-    // T7').  Every feature is held to what the fp32 evaluation of the MLP rounds of it, 1e-7 of G, G^2 = sum_k W2[k][f]^2 tau_k^2 SiLU'(t_k)^2,
+    // What is cut off: a6 T6 + a7 T7 of the values, a6 + a7 at most; of the slopes root mean squares, 0.71 (a6 + a7) of polynomials of their own
+    // and 8 a6 + 10 a7 of derivatives (those of T6' and T7').  Every feature is held to what the fp32 evaluation of the MLP rounds of it, 1e-7 of G, G^2 = sum_k W2[k][f]^2 tau_k^2 SiLU'(t_k)^2,
     // tau_k^2 the sum of the squares of t_k's eight terms, and for the slopes 1e-7 kappa G, kappa what a basis function grows by along a unit
     // of length relative to itself: 8 pi / rc from the sine, 4 / (rc - d) where it vanishes as (rc - d)^4; further to what the length's
     // rounding to fp32, half an ulp, changes on average: 2^-26 of the length times kappa.  Where SiLU' is near zero a sixteenth stands for
@@ -207,7 +207,9 @@ __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
         const double mid = length(node == 2 ? -0.5 : node == 3 ? 0.5 : 0.0), rounding = 0x1p-26 * mid * kappa(mid);
         const double a6 = fabs(a[6][lane]), a7 = fabs(a[7][lane]);
         // (a place grows by 2 per_d along a unit of length in a half)
-        const double cut = node < 2 ? a6 + a7 : fmax(a6 + a7, (8 * a6 + 10 * a7) * 2 * per_d / kappa(mid));
+        const double cut = node == 0   ? a6 + a7
+                           : node == 1 ? 0.71 * (a6 + a7)
+                                       : fmax(a6 + a7, (8 * a6 + 10 * a7) * 2 * per_d / kappa(mid));
         const bool feature_bad = !(cut * cut <= g2 * (1e-14 + rounding * rounding));   // (not a number: not represented)
         if (__any(feature_bad) && lane == 0) any_bad = 1;
     }
