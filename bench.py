@@ -15,7 +15,7 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-# The radial edge kernels look the filters up in tables (k_edge_fwd_tab, k_edge_bwd_tab) and run on the vector unit:
+# The radial edge kernels look the filters up in tables (k_edge_fwd_tab, k_edge_bwd_tab, k_edge_last_tab) and run on the vector unit:
 # their peak is PEAK_FP32_VECTOR_TFLOPS.  With weights that the tables do not represent they evaluate the filter MLP
 # (k_edge_fwd, k_edge_bwd, k_edge_lower): these products run on the bf16 / fp16 matrix pipeline (2.5 PFLOP/s dense), an
 # fp32 product as the six terms of operands in three bf16 parts, a split-fp16 one as three.  The precision mode applies
@@ -58,14 +58,14 @@ def flops_bwd_edge(F, K=8):
 
 # Executed on tables per directed edge, layer and feature: forward five multiply-adds for the filter value and one into the
 # row's sum; reverse value and slope (nine), the sum, and slope x g_i x abar_j into the edge's sum (3).  Reverse of layer
-# 0: slope only (eight) and the latter.
+# 0: slope only (five) and the latter.
 def flops_fwd_tab(F):
     return 12 * F
 
 
 def flops_bwd_tab(F, L):
     """Mean over the layers."""
-    return F * (23 * (L - 1) + 19) / L
+    return F * (23 * (L - 1) + 13) / L
 
 
 # HBM bytes per launch (one layer over all 8 slabs) on the default workload, from rocprofv3 --pmc FETCH_SIZE and
@@ -73,8 +73,8 @@ def flops_bwd_tab(F, L):
 # WRITE_SIZE)
 TRAFFIC_SOURCE = ("profiled constant, not measured by this run: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of this kernel on "
                   "this workload, profiles/edge_traffic_configs3_8slabs.md")
-TRAFFIC_BWD_LAUNCH_BYTES = (1966894 * 1.9976 + 1173831) * 1024   # k_edge_bwd_tab, mean of the three layers
-TRAFFIC_FWD_LAUNCH_BYTES = (786371 * 1.9976 + 250047) * 1024     # k_edge_fwd_tab
+TRAFFIC_BWD_LAUNCH_BYTES = (2470086 * 1.9976 + 811000) * 1024   # k_edge_bwd_tab, k_edge_last_tab, mean of the three layers
+TRAFFIC_FWD_LAUNCH_BYTES = (2085393 * 1.9976 + 250047) * 1024    # k_edge_fwd_tab
 
 
 # fp32 vector peak that applies to this build: 256 CUs x 4 SIMDs x 16 lanes x 2 flop per FMA x 2.4 GHz = 78.6 TFLOP/s.
@@ -212,9 +212,8 @@ def main():
     L = c["L"]
     default_workload = args.config == 3 and args.cells is None and args.precision == "f32"   # what the traffic constants were profiled on
 
-    # The reverse step has a second pass only with the filters from the MLP (with bonds always, for their terms; the seeded
-    # weights of that workload are represented by tables too).
-    on_tables = three_body or prof["edge_bwd_lower"][1] == 0
+    # The reverse step has a second pass only with the filters from the MLP.
+    on_tables = prof["edge_bwd_lower"][1] == 0
 
     def table_roofline(group, kernel, flops_edge, as_defined, traffic):
         ms, n = prof[group]
@@ -247,7 +246,7 @@ def main():
 
     F = c["F"]
     if on_tables:
-        roof_bwd = table_roofline("edge_bwd", f"k_edge_bwd_tab<{F}> (reverse edge step)", flops_bwd_tab(F, L),
+        roof_bwd = table_roofline("edge_bwd", f"k_edge_bwd_tab<{F}>, k_edge_last_tab<{F}> (reverse edge step)", flops_bwd_tab(F, L),
                                   flops_bwd_edge_as_defined(F), TRAFFIC_BWD_LAUNCH_BYTES)
         roof_fwd = table_roofline("edge_fwd", f"k_edge_fwd_tab<{F}> (forward edge step)", flops_fwd_tab(F), flops_fwd_edge(F),
                                   TRAFFIC_FWD_LAUNCH_BYTES)

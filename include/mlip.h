@@ -230,7 +230,7 @@ int mlip_forward(mlip_graph_t *graph, const mlip_weights_t *weights, int32_t mod
  * loops, harnesses that forbid hipMalloc.  Same arguments, results and error codes as mlip_forward, but every
  * piece of workspace (node features and their gradients, kept filter values, per-edge accumulators, packed
  * weights, energy partial sums) is carved from one fixed device array inside the library of
- * mlip_static_scratch_bytes() = 64 MiB per GPU (beside it 2.6 MB for the filter tables), held until the process ends; the
+ * mlip_static_scratch_bytes() = 64 MiB per GPU (beside it 5.2 MB for the filter tables), held until the process ends; the
  * call allocates and frees nothing and clears what must start at zero with fill kernels.  A graph and model whose workspace
  * (about n_local (4 + 2 L) F 4 + n_edges (36 + (L - 1) F 2) bytes summed over the partitions of the mode - the kept
  * filter values take one row per edge pair and layer, the lists of the pairs' edges are rebuilt in the array on
@@ -369,12 +369,12 @@ enum {
     MLIP_PROF_EDGE_BWD = 3,
     MLIP_PROF_GHOST = 4,   /* ghost row copies and gradient add-backs         */
     MLIP_PROF_FORCE = 5,   /* force assembly and energy reduction            */
-    MLIP_PROF_BOND = 6,    /* three-body variant: bond list and the kernels over bonds */
+    MLIP_PROF_BOND = 6,    /* three-body variant: bond list, the kernels over bonds and the bonds' share of the rows' sums */
     MLIP_PROF_TRIPLET_FWD = 7,   /* three-body variant: the triplet sum           */
     MLIP_PROF_TRIPLET_BWD = 8,   /* three-body variant: its reverse               */
     MLIP_PROF_EDGE_FWD_LOWER = 9,  /* no launches: the forward edge step is one pass over the full edge list */
     MLIP_PROF_EDGE_BWD_LOWER = 10, /* reverse edge step, second pass (none on filter tables): the lower edges' share of the projected rows'
-                                     gradients, from the kept filter values; in the three-body variant the bonds' share, always */
+                                     gradients, from the kept filter values */
     MLIP_PROF_COUNT = 11
 };
 int mlip_profile_enable(mlip_graph_t *graph, int32_t on);

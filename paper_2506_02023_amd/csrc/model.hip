@@ -228,9 +228,9 @@ constexpr int kTabTogether = 4;
 int plan_edge_tab(mlip_graph *g, TabBatch &b, int blocks, int waves)
 {
     MLIP_TRY(count_compute_units(g));
-    // A few rows at a time, so that the rows all workers of an XCD are at, with their neighbours, stay in its L2 (a million atoms: 1.6 GB
-    // fetched by a forward launch with two, 8.2 with 22; 1.10 ms with two, 1.12 with one or three, 1.22 with six); one where there
-    // are not even eight items for every worker.
+    // A few rows at a time, so that the rows all workers of an XCD are at stay close together (a million atoms, forward, 32 features in a
+    // block: 1.6 GB fetched with two, 8.2 with 22; 1.10 ms with two, 1.12 with one or three, 1.22 with six.  64 features in a block: 4.3 GB;
+    // 0.83 to 0.87 ms with one or two, the reverse steps 2 % slower with one); one where there are not even eight items for every worker.
     int64_t rows = 0;
     for (int q = 0; q < b.n; ++q) rows += b.s[q].n_rows;
     const int64_t workers = (int64_t)(g->n_cu / blocks) * waves * 4;
