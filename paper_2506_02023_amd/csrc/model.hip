@@ -220,9 +220,10 @@ int64_t upper_edges(const SlabView &v)
 }
 
 // Rows for a compute unit up to which the four workers of a wavefront take a row together: a launch of so few rows takes as long as one
-// row's chain, one step for 45 edges instead of three (108 atoms, F = 32: forward 10.6 us, so 7.3; 500 atoms, F = 64, 13.0 and 10.9). With
-// more rows the step's empty fourth costs more (4,000 atoms, 15 rows: 14.0 and 15.9).
-constexpr int kTabTogether = 4;
+// row's chain, one step for 45 edges instead of three (108 atoms, F = 32: forward 10.6 us, so 6.2).  With more rows the step's empty fourth
+// costs more.  Energy and forces, three layers, us a call with a limit of 4, 16, 32 and 64 rows: F = 64, 2,048 atoms 124, 101, 100, 100;
+// 4,000 133, 119, 117, 117; 6,912 150, 150, 148, 148; 10,976 179, 179, 179, 182; F = 32, 5,324 atoms 108, 107, 96, 95; 16,384 144, 144, 144, 150.
+constexpr int kTabTogether = 32;
 
 // Rows of an edge step on tables, split over the chip; blocks of `waves` wavefronts, `blocks` of them for the blocks of features.
 int plan_edge_tab(mlip_graph *g, TabBatch &b, int blocks, int waves)

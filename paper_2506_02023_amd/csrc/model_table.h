@@ -695,6 +695,9 @@ template <int F, int KIND, int NW, int VALUES, int RING, bool TOGETHER> __device
             heads(SB, HB);
             __builtin_amdgcn_sched_barrier(0);
             compute(SA, EA, before_a, HA, EB);
+            // Few rows: where the second step would be empty it is most of what is left of the launch (108 atoms, a row a wavefront: 8.0 us forward,
+            // 6.2 without; 4,000 atoms, a row a worker: 13.5 and 12.3).  Layer 0's step, a row a worker, has no registers for the way out.
+            if ((TOGETHER || KIND != TAB_LAST) && B.few && !__any(have || SB.tb - offset < SB.item.n || SC.tb - offset < SC.item.n)) break;
             advance();
             SA = SC;
             const TabStep SD = front;

@@ -1,4 +1,4 @@
-"""Sizes at which an edge step on tables changes how it shares rows out (four workers of a wavefront to a row up to four rows for a compute
+"""Sizes at which an edge step on tables changes how it shares rows out (four workers of a wavefront to a row up to 32 rows for a compute
 unit, a row each beyond), with rows longer than a wavefront takes at once and rows without an edge; and the sums over a row's bonds,
 sixteen at a time, at 32 features."""
 import numpy as np
@@ -22,13 +22,14 @@ def _system(n):
         p = rng.uniform(0, 6.5, 3)
         if np.linalg.norm(np.array(ball) - p, axis=1).min() >= 1.0:
             ball.append(p)
-    lone = np.array([[70.0, 10.0 * k + 5.0, 20.0] for k in range(4)])
-    sites = np.stack(np.meshgrid(*[np.arange(10)] * 3, indexing="ij"), -1).reshape(-1, 3)[:n - 84] * 3.5 + 22.0
+    lone = np.array([[14.0, 7.0 * k + 22.0, 14.0] for k in range(4)])
+    m = int(np.ceil((n - 84) ** (1 / 3)))
+    sites = np.stack(np.meshgrid(*[np.arange(m)] * 3, indexing="ij"), -1).reshape(-1, 3)[:n - 84] * 3.5 + 22.0
     pos = np.concatenate([sites + rng.uniform(-0.3, 0.3, sites.shape), np.array(ball) + 4.0, lone])
-    return pos[rng.permutation(n)], np.diag([82.0, 60.0, 60.0])
+    return pos[rng.permutation(n)], np.diag([3.5 * max(m, 7) + 28.0] * 3)
 
 
-@pytest.mark.parametrize("n", [511, 512, 513, 1023, 1024, 1025])   # (256 compute units: 512 rows with 64 features reverse, else 1024)
+@pytest.mark.parametrize("n", [513, 4095, 4096, 4097, 8192, 8193])   # (256 compute units: 4096 rows with 64 features reverse, else 8192)
 @pytest.mark.parametrize("F", [32, 64])
 def test_rows_to_a_wavefront_or_a_worker(n, F):
     import torch
