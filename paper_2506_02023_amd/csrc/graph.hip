@@ -240,7 +240,7 @@ __device__ inline double frac_k(const double *r, const double *n, double V)
     return ((r[0] * n[0] + r[1] * n[1]) + r[2] * n[2]) / V;
 }
 
-// err[0] = flag bits, err[1] = max species seen, err[2] = min species seen (both start at 0); called by all threads of a block (up to 1024)
+// err[0] = flag bits, err[1] = max species seen, err[2] = min species seen (both start at 0); called by all threads of a block
 __device__ inline void track_species(int z, int32_t *err)
 {
     __shared__ int32_t ext[2][16];
@@ -260,12 +260,14 @@ __device__ inline void track_species(int z, int32_t *err)
             zmax = max(zmax, ext[0][w]);
             zmin = min(zmin, ext[1][w]);
         }
-        // The running extremes only move one way, so a block that cannot move them skips its atomics, and what it looks at may be old: an
-        // ordinary load, which the XCD's L2 answers.  (Some 25 ns for every wavefront that asked past it, one after the other: most of the
-        // 102 us that k_bin took for 256,000 atoms.)
-        const volatile int32_t *seen = err;
-        if (zmax > seen[1]) atomicMax(err + 1, zmax);
-        if (zmin < seen[2]) atomicMin(err + 2, zmin);
+        // The running extremes only move one way, so a block that cannot move them skips its atomics, and what it looks at may be old: loads of
+        // workgroup scope, which the XCD's L2 answers.  (Loads that go past it, a volatile one's too, queue at the one line, some 25 ns each:
+        // k_bin for 256,000 atoms 102 us with one for every wavefront, 28 with one for every block, 19 so; for a million 86 with one for every
+        // block, 55 so.)
+        const int32_t seen_max = __hip_atomic_load(err + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        const int32_t seen_min = __hip_atomic_load(err + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (zmax > seen_max) atomicMax(err + 1, zmax);
+        if (zmin < seen_min) atomicMin(err + 2, zmin);
     }
 }
 

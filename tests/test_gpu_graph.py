@@ -200,3 +200,28 @@ def test_pair_split_medium_8_slabs_and_many_slabs():
     _check_pairs(c["positions"], c["cell"], c["species"], c["r_cut"], 8)
     c = wl.make_config(0, n=6)
     _check_pairs(c["positions"], c["cell"], c["species"], c["r_cut"], 64)   # thin slabs: most edges come from ghosts
+
+
+@pytest.mark.parametrize("skin", [0.0, 0.4])
+def test_species_extremes_of_every_build(skin):
+    """A species out of range is refused wherever its atom lies, and only by the builds that held it: one handle, several blocks of atoms on
+    every XCD, its extremes those of the build before until the call looks at them again."""
+    import torch
+    import paper_2506_02023_amd as M
+    c = wl.make_config(1, n=11)
+    N = len(c["positions"])
+    pos, W = torch.as_tensor(c["positions"], device="cuda"), M.Weights(wl.rmp_weights(4, 32, 1, 3), 6)
+    g = M.Graph()
+    if skin:
+        g.set_skin(skin)
+    for at in (0, 63, 64, 2500, N - 1):
+        for z in (9, 3, -1, 0):
+            sp = np.zeros(N, np.int32)
+            sp[at] = z
+            M.mlip_build_graph(pos, c["cell"], torch.as_tensor(sp, device="cuda"), c["r_cut"], graph=g)
+            if 0 <= z < 4:
+                M.mlip_forward(g, W)
+            else:
+                with pytest.raises(M.MlipError):
+                    M.mlip_forward(g, W)
+    torch.cuda.synchronize()
