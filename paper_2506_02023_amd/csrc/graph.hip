@@ -487,7 +487,7 @@ k_sort_rows(int64_t N, CellParams cp, const double *__restrict__ pos, const int6
 // follows from these notes without any search: half the candidate loads of the one-sided search and no binary
 // searches.  Rows are sorted afterwards, so the order in which the atomics hand out slots does not matter.
 constexpr int64_t kSharedCells = 4096;   // below this many cells four wavefronts share one (four cells fit a block otherwise)
-constexpr int64_t kFewCells = 64;      // below this many 16 do
+constexpr int64_t kFewCells = 256;       // below this many 16 do (see k_neighbours_pairs)
 constexpr int kOwn = 64, kPar = 64;   // staging slots per atom for edges found by the atom itself / by its partners
 
 struct PairSearch {   // arrays of the pair-wise search
@@ -624,11 +624,14 @@ __device__ inline void search_home(int32_t c, int32_t hb, int n_home, const Cell
 // One cell per wavefront or (WAVES = 4, 16) per block, in the first cell_blocks blocks.  A candidate is loaded once
 // per cell instead of once per atom, and nothing waits in a chain of dependent loads: one thread per atom walking the
 // cells was bound by that chain, 118 us at any size below 60,000 atoms and 544 us at a million;
-// here 19 us at 500 atoms, 28 us at 32,000 and 390 us at a million.
+// here 12 us at 500 atoms, 28 us at 32,000 and 390 us at a million.
+// Blocks of 16 while every cell has a compute unit of its own, below kFewCells (us with 4 wavefronts and with 16, 45 neighbours an atom: 8 cells 13.8 and
+// 10.6, 27 19.3 and 12.7, 64 15.4 and 11.1, 125 11.5 and 8.7, 216 16.1 and 11.2; 343 of 11.7 atoms 12.9 and 15.5, 1000 15.4 and 27.2; 18
+// neighbours: 64 8.6 and 7.3, 216 9.8 and 7.5, 343 10.4 and 12.2; 81: 27 45.8 and 28.2, 216 31.6 and 18.2).
 // Crowded cells (a cluster in a large box, where there are at most 8 cells per atom and a cell is much wider than the
 // cutoff) are left to the blocks behind those: one per run of kCrowd places in cell order, four wavefronts on the run's part
-// of a crowded cell.  A crowded cell is longer than a run, so it holds the first or the last place of every run it
-// reaches into.  Blocks of 16 below kFewCells cells: 108 atoms 13.7 us, so 9.4, 500 atoms 18.6 and 12.0 (343 cells 12.8 and 13.8).  A build in us with one wavefront on every cell -> here: 4,000 atoms in a box of 500 A (340 atoms per cell) 3450
+// of a crowded cell (16 below kFewCells cells).  A crowded cell is longer than a run, so it holds the first or the last place of every run it
+// reaches into.  A build in us with one wavefront on every cell -> here: 4,000 atoms in a box of 500 A (340 atoms per cell) 3450
 // -> 169, 32,000 in 1,000 A 7900 -> 430, 256,000 in 1,500 A 5850 -> 1360; in lattices, where no cell is crowded, the same
 // from 108 atoms to a million.
 template <int WAVES>

@@ -225,3 +225,14 @@ def test_species_extremes_of_every_build(skin):
                 with pytest.raises(M.MlipError):
                     M.mlip_forward(g, W)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("cells", [(7, 6, 6), (17, 5, 3), (8, 8, 4), (16, 4, 4)])   # 252, 255: sixteen wavefronts to a cell; 256: four
+def test_cells_of_sixteen_and_four_wavefronts(cells):
+    """Uneven cells, empty ones, one of 40 atoms (taken in runs of 32) and its neighbours, on either side of the limit"""
+    rng = np.random.default_rng(sum(cells))
+    cell = np.diag([5.0 * k + 0.1 for k in cells])
+    pos = rng.uniform(0, 1, (5 * int(np.prod(cells)), 3)) @ cell
+    pos = np.concatenate([pos[pos[:, 1] > 3.0], 5.2 + rng.uniform(0, 4.6, (40, 3))])
+    ref = og.build_graph(pos, cell, 5.0)
+    assert_graph_equal(gpu_graph(pos, cell, (np.arange(len(pos)) % 4).astype(np.int32), 5.0), ref, pos, cell)
