@@ -220,10 +220,19 @@ int64_t upper_edges(const SlabView &v)
 }
 
 // Rows for a compute unit up to which the four workers of a wavefront take a row together: a launch of so few rows takes as long as one
-// row's chain, one step for 45 edges instead of three (108 atoms, F = 32: forward 10.6 us, so 6.2).  With more rows the step's empty fourth
-// costs more.  Energy and forces, three layers, us a call with a limit of 4, 16, 32 and 64 rows: F = 64, 2,048 atoms 124, 101, 100, 100;
-// 4,000 133, 119, 117, 117; 6,912 150, 150, 148, 148; 10,976 179, 179, 179, 182; F = 32, 5,324 atoms 108, 107, 96, 95; 16,384 144, 144, 144, 150.
-constexpr int kTabTogether = 32;
+// row's chain, `one` steps of 64 edges instead of `four` of 16 (108 atoms, F = 32: forward 10.6 us, so 6.2).  With more rows the launch takes the
+// sum of the steps, of which the row alone is `four` and together 4 `one`: the line lies where what the chain gains is what the empty workers cost, 16
+// measured.  Energy and forces, three layers, us a call with rows for workers and taken together, at 6 edges a row never the faster (F = 64, 1,536 atoms 93
+// and 97, 8,192 111 and 134); 20 edges: F = 32, 2,048 atoms (8 rows for a compute unit) 85 and 80, 4,096 87 and 90, 8,192 96 and 107; 42: F = 64, 2,048
+// 123 and 102, 4,096 134 and 119, 8,192 154 and 154, F = 32 115 and 110; 70: F = 32, 4,096 117 and 106, 8,192 132 and 152, F = 64, 4,096 154 and
+// 147, 8,192 185 and 207.  (At 34 to 40 edges and F = 64 the last fifth below the limit of 32 is 3 % the slower.)
+int64_t tab_together(int64_t rows, int64_t edges)
+{
+    const int64_t mean = (edges + rows - 1) / rows;   // (a row in two has more)
+    const int64_t four = (mean + 1 + 15) / 16, one = (mean + 1 + 63) / 64, empty = 4 * one - four;
+    constexpr int64_t kMost = 32;
+    return empty > 0 ? std::min(kMost, 16 * (four - one) / empty) : kMost;
+}
 
 // Rows of an edge step on tables, split over the chip; blocks of `waves` wavefronts, `blocks` of them for the blocks of features.
 int plan_edge_tab(mlip_graph *g, TabBatch &b, int blocks, int waves)
@@ -232,12 +241,15 @@ int plan_edge_tab(mlip_graph *g, TabBatch &b, int blocks, int waves)
     // A few rows at a time, so that the rows all workers of an XCD are at stay close together (a million atoms, forward, 32 features in a
     // block: 1.6 GB fetched with two, 8.2 with 22; 1.10 ms with two, 1.12 with one or three, 1.22 with six.  64 features in a block: 4.3 GB;
     // 0.83 to 0.87 ms with one or two, the reverse steps 2 % slower with one); one where there are not even eight items for every worker.
-    int64_t rows = 0;
-    for (int q = 0; q < b.n; ++q) rows += b.s[q].n_rows;
+    int64_t rows = 0, edges = 0;
+    for (int q = 0; q < b.n; ++q) {
+        rows += b.s[q].n_rows;
+        edges += b.s[q].n_edges;
+    }
     const int64_t workers = (int64_t)(g->n_cu / blocks) * waves * 4;
     b.rows = (int)std::min<int64_t>(kTabRows, std::max<int64_t>(1, rows / (8 * workers)));
     b.few = rows <= workers;
-    b.together = rows <= (int64_t)(g->n_cu / blocks) * kTabTogether;
+    b.together = rows > 0 && rows <= (g->n_cu / blocks) * tab_together(rows, edges);
     if (b.together) b.rows = 1;
     b.edge_start[0] = 0;
     for (int q = 0; q < kBatch; ++q) b.edge_start[q + 1] = b.edge_start[q] + (q < b.n ? b.s[q].n_edges : 0);

@@ -1,6 +1,6 @@
-"""Sizes at which an edge step on tables changes how it shares rows out (four workers of a wavefront to a row up to 32 rows for a compute
-unit, a row each beyond), with rows longer than a wavefront takes at once and rows without an edge; and the sums over a row's bonds,
-sixteen at a time, at 32 features."""
+"""Sizes at which an edge step on tables changes how it shares rows out (four workers of a wavefront to a row up to a number of rows for a compute
+unit that the rows' mean length gives, a row each beyond), with rows longer than a wavefront takes at once and rows without an edge; and the
+sums over a row's bonds, sixteen at a time, at 32 features."""
 import numpy as np
 import pytest
 
@@ -14,8 +14,8 @@ from gpu_util import E_RTOL, F_RTOL, gpu_graph
 pytestmark = pytest.mark.gpu
 
 
-def _system(n):
-    """n atoms: a ball of 80 with up to 79 neighbours, four far from everything, the rest a jittered lattice of some 12"""
+def _system(n, a=3.5):
+    """n atoms: a ball of 80 with up to 79 neighbours, four far from everything, the rest a jittered lattice, at 3.5 of some 12 neighbours"""
     rng = np.random.default_rng(n)
     ball = [rng.uniform(0, 6.5, 3)]
     while len(ball) < 80:
@@ -24,22 +24,29 @@ def _system(n):
             ball.append(p)
     lone = np.array([[14.0, 7.0 * k + 22.0, 14.0] for k in range(4)])
     m = int(np.ceil((n - 84) ** (1 / 3)))
-    sites = np.stack(np.meshgrid(*[np.arange(m)] * 3, indexing="ij"), -1).reshape(-1, 3)[:n - 84] * 3.5 + 22.0
+    sites = np.stack(np.meshgrid(*[np.arange(m)] * 3, indexing="ij"), -1).reshape(-1, 3)[:n - 84] * a + 22.0
     pos = np.concatenate([sites + rng.uniform(-0.3, 0.3, sites.shape), np.array(ball) + 4.0, lone])
-    return pos[rng.permutation(n)], np.diag([3.5 * max(m, 7) + 28.0] * 3)
+    return pos[rng.permutation(n)], np.diag([max(a * m, 24.5) + 28.0] * 3)
 
 
-@pytest.mark.parametrize("n", [513, 4095, 4096, 4097, 8192, 8193])   # (256 compute units: 4096 rows with 64 features reverse, else 8192)
+def _limit(mean):   # rows for a compute unit
+    four, one = int(np.ceil((mean + 1) / 16)), int(np.ceil((mean + 1) / 64))
+    return min(32, 16 * (four - one) // (4 * one - four)) if 4 * one > four else 32
+
+
+# 256 compute units: the limit is that of rows times 128 with 64 features in a reverse step, else 256
+@pytest.mark.parametrize("n,a,limit", [(513, 3.5, 8), (1023, 2.7, 8), (1024, 2.7, 8), (1025, 2.7, 8), (2048, 2.7, 8), (2049, 2.7, 8), (4000, 4.6, 0),
+                                       (4095, 2.2, 32), (4096, 2.2, 32), (4097, 2.2, 32), (8192, 2.2, 32), (8193, 2.2, 32)])
 @pytest.mark.parametrize("F", [32, 64])
-def test_rows_to_a_wavefront_or_a_worker(n, F):
+def test_rows_to_a_wavefront_or_a_worker(n, a, limit, F):
     import torch
     import paper_2506_02023_amd as M
-    pos, cell = _system(n)
+    pos, cell = _system(n, a)
     spec = (np.arange(n) % 4).astype(np.int32)
     w = wl.rmp_weights(4, F, 2, 21)
     ref_g = og.build_graph(pos, cell, 5.0)
     rows = np.diff(ref_g.row_ptr)
-    assert rows.max() > 64 and rows.min() == 0
+    assert rows.max() > 64 and rows.min() == 0 and _limit(np.ceil(rows.mean())) == limit
     ref = om.energy_forces(pos, cell, spec, w, ref_g, 5.0, 8, 6)
     W = M.Weights(w, 6)
     for P in (1, 3):
