@@ -567,8 +567,10 @@ template <int F, int KIND, int NW, int VALUES, int RING, bool TOGETHER> __device
         const float v = R.d * B.inv_h;
         const int j = min((int)v, kTabUnits - 1);
         const f32x2 unit = *reinterpret_cast<const f32x2 *>(lut + 8 * j);
-        // the interval within the unit; the last one of its own at most, as the place and the slope are in this unit's measure
-        const float k = fminf(truncf((v - (float)j) * unit[0]), unit[0] - 1.f);
+        // the interval within the unit; the last one of its own at most, as the place and the slope are in this unit's measure.  (Products and sums
+        // that decide about it are spelled out: left to the compiler, one copy of the loop rounds v and another does not, and a length at an
+        // interval's end takes one or the other with the step that its worker happens to be at.)
+        const float k = fminf(truncf(fmaf(R.d, B.inv_h, -(float)j) * unit[0]), unit[0] - 1.f);
         E.slope = (2.f * B.inv_h) * unit[0];
         E.s = fmaf(R.d, E.slope, fmaf(-2.f, fmaf((float)j, unit[0], k), -1.f));
         E.loff = __mul24((int)(unit[1] + k), 16 * kI * 24);

@@ -1,5 +1,7 @@
 """Helpers for the GPU parity tests: run libmlip through the binding, run the oracle, compare."""
 import functools
+import os
+import re
 
 import numpy as np
 
@@ -56,3 +58,20 @@ def assert_energy_forces(e, f, ref, what=""):
     assert de <= E_RTOL, f"{what}: relative energy error {de:.3e}"
     assert df <= F_RTOL, f"{what}: force error {df:.3e} of max|F|"
     return de, df
+
+
+def table_intervals():
+    """Intervals of the filter tables in each of the units of [0, r_cut], as the header has them"""
+    import paper_2506_02023_amd as M
+    with open(os.path.join(os.path.dirname(M.__file__), "csrc", "model_table.h")) as f:
+        text = f.read()
+    per = np.array([int(n) for n in re.search(r"kTabPer\[kTabUnits\] = \{([^}]*)\}", text).group(1).split(",")])
+    units, total = (int(re.search(name + r" = (\d+)", text).group(1)) for name in ("kTabUnits", "kTabN"))
+    assert len(per) == units and per.sum() == total
+    return per
+
+
+def table_interval_ends(r_cut):
+    """Their ends, those of the intervals of half the length among them"""
+    per = table_intervals()
+    return np.array([(j + i / (2 * n)) * r_cut / len(per) for j, n in enumerate(per) for i in range(2 * n)][1:])

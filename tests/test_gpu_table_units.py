@@ -1,6 +1,6 @@
-"""The tables' units: lengths at and next to every limit between two of the 64 units of [0, rc], on whose sides the intervals have different
-lengths, so that an interval of one unit taken in the other's measure shows as a wrong slope; first by the launch that holds both ways, then by
-the kernels on tables."""
+"""The tables' intervals: lengths at and next to every end of one and every middle (the end of one of half the length, on which a reverse step's
+polynomial changes), so that a place taken in another interval's measure shows as a wrong slope; first by the launch that holds both ways, then
+by the kernels on tables, which have to take the same interval for a length within rounding of an end: the same bits."""
 import numpy as np
 import pytest
 
@@ -8,32 +8,66 @@ import workloads as wl
 from oracle import graph as og
 from oracle import model as om
 
+from gpu_util import gpu_graph, table_interval_ends, table_intervals
+
 pytestmark = pytest.mark.gpu
 
 R_CUT = 5.0
 
 
 @pytest.mark.parametrize("F,L", [(32, 1), (32, 3), (64, 1), (64, 2)])
-def test_pairs_at_the_limits_of_units(F, L):
-    """Bound per pair, of the largest force at its limit and the ones beside it (a pair's own may vanish): 2e-5 (rounding of the filters' values and
+def test_pairs_at_the_ends_of_intervals(F, L):
+    """Bound per pair, of the largest force at its end and the ones beside it (a pair's own may vanish): 2e-5 (rounding of the filters' values and
     slopes, 1e-7 of each, through the layers) and what the rounding of the length to fp32 makes of the fourth power of its distance
-    from the cutoff.  A slope in the wrong measure is off by a third at least."""
+    from the cutoff.  A slope in the wrong measure is off by a third at least, where the units' numbers of intervals differ, a place in the wrong
+    interval by the whole polynomial."""
     import torch
     import paper_2506_02023_amd as M
-    at_limit = (np.arange(5, 64) * R_CUT / 64).astype(np.float32)
-    ds = np.concatenate([np.nextafter(at_limit, np.float32(0)), at_limit, np.nextafter(at_limit, np.float32(9))]).astype(np.float64)
-    at = np.array([[12.0 * (k % 14), 12.0 * (k // 14), 0.0] for k in range(len(ds))]) + 3.0
+    at_end = table_interval_ends(R_CUT).astype(np.float32)
+    assert at_end[0] < 0.05 and at_end[-1] > 4.99
+    ds = np.concatenate([np.nextafter(at_end, np.float32(0)), at_end, np.nextafter(at_end, np.float32(9))]).astype(np.float64)
+    side = 26
+    at = np.array([[12.0 * (k % side), 12.0 * (k // side), 0.0] for k in range(len(ds))]) + 3.0
     pos = np.stack([at, at + np.stack([0 * ds, 0 * ds, ds], 1)], 1).reshape(-1, 3)
-    spec, cell = (np.arange(len(pos)) % 4).astype(np.int32), np.diag([168.0, 168.0, 20.0])
+    spec, cell = (np.arange(len(pos)) % 4).astype(np.int32), np.diag([12.0 * side, 12.0 * side, 20.0])
     w = wl.rmp_weights(4, F, L, 9)
     ref = om.energy_forces(pos, cell, spec, w, og.build_graph(pos, cell, R_CUT), R_CUT, 8, 6)
     g = M.mlip_build_graph(torch.as_tensor(pos, device="cuda"), cell, torch.as_tensor(spec, device="cuda"), R_CUT)
     W = M.Weights(w, 6)
+    first = None
     for call in ("undecided", "on tables"):
-        f = M.mlip_forward(g, W)[1]
-        torch.cuda.synchronize()
+        f = M.mlip_forward(g, W)[1].cpu().numpy()
         size = np.abs(ref["forces"]).reshape(3, -1, 6).max((0, 2))
         size = np.tile(np.maximum(size, np.maximum(np.roll(size, 1), np.roll(size, -1))), 3)
-        err = np.abs(f.cpu().numpy() - ref["forces"]).reshape(-1, 6).max(1) / size
+        err = np.abs(f - ref["forces"]).reshape(-1, 6).max(1) / size
         bound = 2e-5 + 4 * 2.0 ** -22 / (R_CUT - ds)
         assert np.all(err <= bound), (call, ds[err > bound], err[err > bound])
+        assert first is None or np.array_equal(f, first), ds[np.any((f != first).reshape(-1, 6), 1)]
+        first = f
+
+
+@pytest.mark.parametrize("F", [32, 64])
+def test_equal_pairs_have_equal_forces(F):
+    """Pairs of one length and one pair of species, more rows than there are workers: the same bits whichever worker has a row and whichever step
+    of its loop an edge comes to.  The lengths lie where the rounding of the place decides about the interval."""
+    import torch
+    import paper_2506_02023_amd as M
+    per = table_intervals()
+    ends = table_interval_ends(R_CUT).astype(np.float32)
+    ds = np.concatenate([np.nextafter(ends, np.float32(0)), ends, np.nextafter(ends, np.float32(9))])
+    inv_h = np.float32(len(per) / R_CUT)
+    rounded, exact = (ds * inv_h).astype(np.float64), ds.astype(np.float64) * float(inv_h)
+    unit = np.minimum(rounded.astype(int), len(per) - 1)
+    differ = [np.trunc((rounded - unit) * n * per[unit]) != np.trunc((exact - unit) * n * per[unit]) for n in (1, 2)]
+    ds = ds[(differ[0] | differ[1]) & (ds > 0.3)].astype(np.float64)
+    assert len(ds) >= 2
+    side, d = 142, np.resize(ds, 142 * 142)
+    at = np.array([[12.0 * (k % side), 12.0 * (k // side), 0.0] for k in range(side * side)]) + 3.0
+    pos = np.stack([at, at + np.stack([0 * d, 0 * d, d], 1)], 1).reshape(-1, 3)
+    g = gpu_graph(pos, np.diag([12.0 * side, 12.0 * side, 20.0]), np.arange(len(pos)) % 2, R_CUT)
+    assert g.sizes()[:2] == (len(pos), len(pos))
+    W = M.Weights(wl.rmp_weights(4, F, 2, 9), 6)
+    for _ in range(3):
+        f = M.mlip_forward(g, W)[1].cpu().numpy().reshape(-1, 6)
+        for k in range(len(ds)):
+            assert np.all(f[k::len(ds)] == f[k]), (ds[k], np.unique(f[k::len(ds)], axis=0))
