@@ -10,8 +10,11 @@
 // ---------------------------------------------------------------- the table
 //
 // Polynomials of degree 5 in the local coordinate s in [-1, 1] on intervals of [0, rc], fp32 coefficients computed in fp64.  [0, rc] is cut
-// into 64 units of one length, a unit into 1 to 10 intervals (kTabPer): many where the filters of ordinary weights bend most (from rc/16 to
-// rc/5) and at the cutoff, where the filter vanishes with its first three derivatives, so that its error has to vanish too.  Three tables a
+// into 60 units of one length, a unit into 1 to 11 intervals (kTabPer): many where the filters of ordinary weights bend most (from rc/15 to
+// rc/5) and at the cutoff, where the filter vanishes with its first three derivatives, so that its error has to vanish too.  They are shared out
+// so that few models are refused, sampled at W1 of twice and two and a half times the usual size, where the slopes are the first to be: of those at
+// two and a half times, F = 64, 43 %; 60 % with 64 units and the intervals beyond 2/5 rc one to a unit, 57 % with one table of 212 intervals
+// and 32 features for values and slopes.  (48 units refuse as few, and the slopes are off by a third more from rc/2 on.)  Three tables a
 // layer, for the three kinds of steps:
 //   values  w, kTabN intervals, for all F features: the forward step needs nothing else;
 //   slopes  dw/dd, the same intervals, for all F features: the last reverse step (layer 0), which needs no sums over rows;
@@ -23,9 +26,9 @@
 // slopes as a derivative), the fp32 evaluation of the MLP to 1.7e-7 of both.
 // An interval is, for 64 features, [6 coefficients][64], for 32 features [3][16 lanes][2 coefficients][2 features]: 16 bytes of a lane at a
 // time, 16 lanes 256 bytes of a row.  Values or slopes of F = 64 and both of 32 features take 162,816 bytes of the compute unit's 160 KB.
-constexpr int kTabUnits = 64, kTabN = 106;
-constexpr int kTabPer[kTabUnits] = {1, 1, 2, 2, 2, 3, 3, 4, 4, 4, 3, 2, 2, 2, 2, 2, 2, 2, 2, 2, 2, 2, 2, 2, 2, 1, 1, 1, 1, 1, 1, 1,
-                                    1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 2, 10};
+constexpr int kTabUnits = 60, kTabN = 106;
+constexpr int kTabPer[kTabUnits] = {1, 1, 2, 2, 3, 3, 4, 4, 4, 4, 3, 2, 2, 2, 2, 2, 2, 2, 2, 2, 2, 2, 2, 2, 2, 2, 1, 1, 1, 1,
+                                    1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 2, 11};
 struct TabGrid {
     struct Unit { float n, at; } unit[kTabUnits];   // its intervals and the first one's number
     int unit_of[kTabN];
