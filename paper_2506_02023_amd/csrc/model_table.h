@@ -22,7 +22,7 @@
 // A derivative is as good as a polynomial of its own only on intervals 0.55 times as long, and the table has to fit LDS: one that serves for
 // both holds 32 features, the other two all 64, which spares an edge's second look at its record and its broadcasts (20 vector instructions
 // for four edges and 32 features, 17 with 64 at a time).  What is cut off is below what the evaluation of the MLP in fp32 rounds, feature by
-// feature (checked when the tables are made, see k_filter_table); coefficients and evaluation round to 3.6e-8 of values and slopes (5e-8 of the
+// feature, of the slopes in root mean square over an interval (checked when the tables are made, see k_filter_table); coefficients and evaluation round to 3.6e-8 of values and slopes (5e-8 of the
 // slopes as a derivative), the fp32 evaluation of the MLP to 1.7e-7 of both.
 // An interval is, for 64 features, [6 coefficients][64], for 32 features [3][16 lanes][2 coefficients][2 features]: 16 bytes of a lane at a
 // time, 16 lanes 256 bytes of a row.  Values or slopes of F = 64 and both of 32 features take 162,816 bytes of the compute unit's 160 KB.
@@ -113,26 +113,32 @@ __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
     float w2[F * F / (kTabNodes * 64)];   // this thread's part on its way to LDS (the caller's array: no alignment assumed)
 #pragma unroll
     for (int i = 0; i < F * F / (kTabNodes * 64); ++i) w2[i] = J.W2[(size_t)layer * F * F + i * kTabNodes * 64 + threadIdx.x];
-    {   // t_k = sum_n b_n(d) W1[n][k], s_k = SiLU(t_k)
+    {   // t_k = sum_n b_n(d) W1[n][k], s_k = SiLU(t_k), and their slopes along d
         const double d = length(kCosTab[2 * node + 1]);
         const double x = d / J.rc, y = 1.0 - x;
-        double q = 0.5 * J.p * (J.p + 1);
-        for (int k = J.p - 2; k >= 0; --k) q = q * x + 0.5 * (k + 1) * (k + 2);
-        const double u = y * y * y * q / d;   // the envelope in its factored form, over d
+        double q = 0.5 * J.p * (J.p + 1), power = 1;
+        for (int k = J.p - 2; k >= 0; --k) {
+            q = q * x + 0.5 * (k + 1) * (k + 2);
+            power *= x;
+        }
+        // the envelope in its factored form, over d
+        const double u = y * y * y * q / d, du = (-0.5 * J.p * (J.p + 1) * (J.p + 2) * power * y * y / J.rc - u) / d, per_x = 3.141592653589793 / J.rc;
         // sin((n + 1) pi x) by angle addition from the nearer end, where it is small
         const double near = x < 0.5 ? x : y, s1 = sinpi(near), c1 = x < 0.5 ? cospi(near) : -cospi(near);
-        double sn = s1, cn = c1, t = 0, tt = 0;
+        double sn = s1, cn = c1, t = 0, tt = 0, dt = 0;
 #pragma unroll
         for (int n = 0; n < 8; ++n) {
             const double term = sn * u * (double)w1[n];
             t += term;
             tt += term * term;
+            dt += (cn * u * (per_x * (n + 1)) + sn * du) * (double)w1[n];
             const double nx = sn * c1 + cn * s1;
             cn = cn * c1 - sn * s1;
             sn = nx;
         }
         const double sg = 1.0 / (1.0 + exp(-t)), slope = sg * (1.0 + t * (1.0 - sg));
         sv[node][lane] = t * sg;
+        half[0][node][lane] = dt * slope;
         uv[node][lane] = tt * (slope * slope + 1.0 / 16);   // (see the verdict below)
         if (lane == 0) slope_g[node] = kappa(d) * kappa(d);
     }
@@ -141,15 +147,18 @@ __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
         W2[i * kTabNodes * 64 + threadIdx.x] = J.bf16 ? (double)(float)(__bf16)(w2[i] * kSiluScaleInv) / kSiluScaleInv : (double)w2[i];
     __syncthreads();
     {   // w_f = sum_k s_k W2[k][f]
-        double w = 0, g = 0;
+        double w = 0, dw = 0, g = 0;
 #pragma unroll 16
         for (int k = 0; k < F; ++k) {
             const double v = W2[k * F + f];
             w = fma(sv[node][k], v, w);
+            dw = fma(half[0][node][k], v, dw);
             g = fma(uv[node][k], v * v, g);
         }
         wv[node][lane] = w;
         gv[node][lane] = g;
+        __syncthreads();
+        uv[node][lane] = dw;
     }
     __syncthreads();
     auto coefficient = [&](const double (&v)[kTabNodes][64]) {   // Chebyshev coefficient `node` of this lane's feature, of the values at the nodes
@@ -158,12 +167,13 @@ __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
         for (int j = 0; j < kTabNodes; ++j) a += v[j][lane] * kCosTab[node * (2 * j + 1) % 32];
         return a * (node == 0 ? 1.0 / kTabNodes : 2.0 / kTabNodes);
     };
-    sv[node][lane] = coefficient(wv);
+    const double value = coefficient(wv), slope = coefficient(uv);
     __syncthreads();
-    {   // at the nodes: dw/dd, T_m'(cos t) = m sin(m t) / sin t; at those of the interval's halves: w
-        double dw = 0, h0 = 0, h1 = 0, hp0 = 0, hp1 = 0;
-#pragma unroll
-        for (int m = 1; m < kTabNodes; ++m) dw += sv[m][lane] * (m * kCosTab[(m * (2 * node + 1) + 24) % 32]);
+    sv[node][lane] = value;
+    uv[node][lane] = slope;
+    __syncthreads();
+    {   // w at the nodes of the interval's halves
+        double h0 = 0, h1 = 0, hp0 = 0, hp1 = 0;
         const double x0 = 0.5 * (kCosTab[2 * node + 1] - 1.0), x1 = x0 + 1.0;
 #pragma unroll
         for (int m = kTabNodes - 1; m >= 0; --m) {   // Clenshaw, one step late: (h, its predecessor) in hp
@@ -173,24 +183,24 @@ __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
             h0 = n0;
             h1 = n1;
         }
-        wv[node][lane] = dw / kCosTab[(2 * node + 25) % 32] * per_d;
         half[0][node][lane] = h0 - x0 * hp0;
         half[1][node][lane] = h1 - x1 * hp1;
     }
     __syncthreads();
-    uv[node][lane] = coefficient(wv);
     const double half0 = coefficient(half[0]), half1 = coefficient(half[1]);
     __syncthreads();
     half[0][node][lane] = half0;
     half[1][node][lane] = half1;
     __syncthreads();
-    // What is cut off: a6 T6 + a7 T7 of the values, a6 + a7 at most; of the slopes root mean squares, 0.71 (a6 + a7) of polynomials of their own
-    // and 8 a6 + 10 a7 of derivatives (those of T6' and T7').  Every feature is held to what the fp32 evaluation of the MLP rounds of it, 1e-7 of G, G^2 = sum_k W2[k][f]^2 tau_k^2 SiLU'(t_k)^2,
-    // tau_k^2 the sum of the squares of t_k's eight terms, and for the slopes 1e-7 kappa G, kappa what a basis function grows by along a unit
-    // of length relative to itself: 8 pi / rc from the sine, 4 / (rc - d) where it vanishes as (rc - d)^4; further to what the length's
-    // rounding to fp32, half an ulp, changes on average: 2^-26 of the length times kappa.  Where SiLU' is near zero a sixteenth stands for
-    // SiLU'^2: there the feature is small beside what it is elsewhere (a unit's t goes to 0 at the cutoff, so -0.28 is always passed).  G
-    // goes with the feature's column of W2: scaling that against the later maps does not change the verdict.
+    // What is cut off: a6 T6 + a7 T7 of the values, a6 + a7 at most; of the slopes root mean squares over an interval, 0.71 (a6 + a7) of polynomials
+    // of their own and 8 a6 + 10 a7 of derivatives (those of T6' and T7'), which an interval's ends exceed by 1.4 and by 5.  The halves'
+    // polynomials come from the whole one of degree 7: the first term that this leaves out, a8 T8, is known from the slopes, whose a7 is 16 times that,
+    // and its derivative, 12 a8, added.  Every feature is held to what the fp32 evaluation of the MLP rounds of it, 1e-7 of G,
+    // G^2 = sum_k W2[k][f]^2 tau_k^2 SiLU'(t_k)^2, tau_k^2 the sum of the squares of t_k's eight terms, and for the slopes 1e-7 kappa G, kappa
+    // what a basis function grows by along a unit of length relative to itself: 8 pi / rc from the sine, 4 / (rc - d) where it vanishes as
+    // (rc - d)^4; further to what the length's rounding to fp32, half an ulp, changes on average: 2^-26 of the length times kappa.  Where SiLU' is
+    // near zero a sixteenth stands for SiLU'^2: there the feature is small beside what it is elsewhere (a unit's t goes to 0 at the cutoff,
+    // so -0.28 is always passed).  G goes with the feature's column of W2: scaling that against the later maps does not change the verdict.
     if (node < 4) {   // the wavefronts' tables: values, slopes, both on either half
         const double(&a)[kTabNodes][64] = node == 0 ? sv : node == 1 ? uv : half[node - 2];
         const double a0 = a[0][lane], a1 = a[1][lane], a2 = a[2][lane], a3 = a[3][lane], a4 = a[4][lane], a5 = a[5][lane];
@@ -212,7 +222,7 @@ __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
         // (a place grows by 2 per_d along a unit of length in a half)
         const double cut = node == 0   ? a6 + a7
                            : node == 1 ? 0.71 * (a6 + a7)
-                                       : fmax(a6 + a7, (8 * a6 + 10 * a7) * 2 * per_d / kappa(mid));
+                                       : fmax(a6 + a7, ((8 * a6 + 10 * a7) * 2 * per_d + 0.75 * fabs(uv[7][lane])) / kappa(mid));
         const bool feature_bad = !(cut * cut <= g2 * (1e-14 + rounding * rounding));   // (not a number: not represented)
         if (__any(feature_bad) && lane == 0) any_bad = 1;
     }
