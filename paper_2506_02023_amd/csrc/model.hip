@@ -401,7 +401,7 @@ int forward_t(mlip_graph *g, const mlip_weights_t *w, const mlip_bond_weights_t 
     int by = BOTH_WAYS;
     int64_t most_edges = 0;
     for (int p = 0; p < P; ++p) most_edges = std::max(most_edges, views[p].n_edges);
-    if (L == 0 || most_edges >= (int64_t)1 << 29) {   // the steps on tables address an edge's 8 bytes of sums by 32-bit offsets
+    if (L == 0 || most_edges >= (int64_t)1 << 29) {   // the steps on tables address an edge's records and sums, 4 bytes each, by offsets below 2^31
         by = BY_MLP;
     } else if (!repack) {
         const int64_t word = __atomic_load_n(verdict, __ATOMIC_RELAXED);

@@ -262,7 +262,7 @@ __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
 // million atoms in 8 slabs: 867, 1767, 1175 (1052, 1764, 1654).
 
 struct TabArgs {               // one partition
-    int32_t n_rows, n_edges;   // receiver rows processed and their edges (below 2^29: 32-bit byte offsets)
+    int32_t n_rows, n_edges;   // receiver rows processed and their edges (below 2^29: byte offsets below 2^31)
     int32_t n_nodes;           // rows of g / abar
     const int64_t *row_ptr;
     const int32_t *chunk_row;  // the graph's work-item table: first row whose first edge lies at or after c * span

@@ -83,3 +83,47 @@ def test_bond_sums_of_long_and_empty_rows(precision, bound, P):
         f = M.mlip_forward_bonds(g, W, M.BondWeights(w, 3.4, 8), M.MODE_SLABS if P > 1 else M.MODE_WHOLE)[1]
         torch.cuda.synchronize()
         assert np.abs(f.cpu().numpy() - ref["forces"]).max() <= bound * np.abs(ref["forces"]).max()
+
+
+def _irregular():
+    """91 atoms in a box of 30: a ball of 80 whose rows go beyond 64 edges, three pairs, five atoms without a neighbour, in an order in which rows
+    without an edge come alone and in twos between long ones"""
+    rng = np.random.default_rng(11)
+    ball = [np.array([10.0, 10.0, 10.0])]
+    while len(ball) < 80:
+        p = 7.0 + rng.uniform(0, 6.5, 3)
+        if np.linalg.norm(np.array(ball) - p, axis=1).min() >= 1.0:
+            ball.append(p)
+    lone = [np.array([3.0 + 6 * k, 24.0, 3.0]) for k in range(4)] + [np.array([24.0, 14.0, 20.0])]
+    pair = [np.array([3.0 + 8 * k, 24.0, 21.0 + d]) for k in range(3) for d in (0.0, 1.1 + k)]
+    pos = lone[:2] + ball[:20] + lone[2:3] + ball[20:41] + pair[:3] + lone[3:] + ball[41:] + pair[3:]
+    return np.array(pos), np.diag([30.0] * 3)
+
+
+@pytest.mark.parametrize("F", [32, 64])
+def test_items_of_two_irregular_rows(F):
+    """Copies of an irregular system, of an odd number of atoms, further apart than the cutoff: more than sixteen rows for a worker, which it takes
+    two at a time, whatever is in them: no edge in the first, the second or both, more than four steps in either.  Every copy as the
+    system alone."""
+    import torch
+    import paper_2506_02023_amd as M
+    one, box = _irregular()
+    spec, side = (np.arange(len(one)) % 4).astype(np.int32), 15
+    w = wl.rmp_weights(4, F, 2, 17)
+    ref_g = og.build_graph(one, box, 5.0)
+    empty = np.diff(ref_g.row_ptr) == 0
+    assert len(one) % 2 == 1 and empty.sum() == 5 and np.any(empty[1:] & empty[:-1]) and np.diff(ref_g.row_ptr).max() > 64
+    ref = om.energy_forces(one, box, spec, w, ref_g, 5.0, 8, 6)
+    at = 30.0 * np.stack(np.meshgrid(*[np.arange(side)] * 3, indexing="ij"), -1).reshape(-1, 1, 3)
+    copies = side ** 3
+    assert copies * len(one) > 16 * 256 * 16 * 4
+    g = gpu_graph((at + one).reshape(-1, 3), box * side, np.tile(spec, copies), 5.0)
+    assert g.sizes()[1] == copies * ref_g.E
+    W = M.Weights(w, 6)
+    first = None
+    for call in ("undecided", "on tables"):
+        got = [x.cpu().numpy() for x in M.mlip_forward(g, W)]
+        assert np.abs(got[1].reshape(copies, -1, 3) - ref["forces"]).max() <= F_RTOL * np.abs(ref["forces"]).max(), call
+        assert np.abs(got[2].reshape(copies, -1) - ref["atom_energy"]).max() <= 1e-5 * np.abs(ref["atom_energy"]).max(), call
+        assert first is None or all(np.array_equal(a, b) for a, b in zip(first, got)), call
+        first = got

@@ -237,8 +237,8 @@ def test_first_call_on_a_large_graph():
 
 
 def test_limit_of_the_fixed_workspace_with_many_edges_and_one_layer():
-    """A graph of 77 edges per atom that fills the 64 MiB but for less than 4 bytes per edge: the second sums per edge of F = 64 take no room of
-    their own.  With the pair lists in the handle already (and so not in the workspace) the call gives the same."""
+    """A graph of 77 edges per atom that fills the 64 MiB but for less than 4 bytes per edge: one layer's step sums an edge over all features at a
+    time, so there is one sum per edge.  With the pair lists in the handle already (and so not in the workspace) the call gives the same."""
     import torch
     import paper_2506_02023_amd as M
     F = 64
@@ -266,3 +266,31 @@ def test_limit_of_the_fixed_workspace_with_many_edges_and_one_layer():
         e, f, a = M.mlip_forward_static(g, W, M.MODE_WHOLE)
         torch.cuda.synchronize()
         assert float(e.cpu()[0]) == want[0] and np.array_equal(f.cpu().numpy(), want[1].astype(np.float32))
+
+
+def test_limit_of_the_fixed_workspace_with_many_edges_and_two_layers():
+    """The largest of a row of graphs of 77 edges per atom that fits the 64 MiB, the next one, with 80 atoms more, being refused: the second sums
+    per edge of F = 64, four bytes each and more than those atoms take, lie in the place of the filter MLP's kept values.  The
+    same bits as with the workspace that grows."""
+    import torch
+    import paper_2506_02023_amd as M
+    fcc = np.array([[0, 0, 0], [0, 0.5, 0.5], [0.5, 0, 0.5], [0.5, 0.5, 0]])
+    W = M.Weights(_weights(64, 2, 4), 6)
+    fits = []
+    for nx in range(40, 90):
+        n = (nx, 5, 4)
+        corner = np.stack(np.meshgrid(*[np.arange(k) for k in n], indexing="ij"), -1).reshape(-1, 1, 3)
+        pos = 3.0 * (corner + fcc).reshape(-1, 3) + 0.1 * np.random.default_rng(3).standard_normal((80 * nx, 3))
+        g = M.mlip_build_graph(torch.as_tensor(pos, device="cuda"), 3.0 * np.diag(n).astype(np.float64),
+                               torch.as_tensor((np.arange(len(pos)) % 4).astype(np.int32), device="cuda"), R_CUT)
+        N, E, _ = g.sizes()
+        try:
+            got = M.mlip_forward_static(g, W, M.MODE_WHOLE)
+        except M.MlipError:
+            break
+        torch.cuda.synchronize()
+        fits.append((N, E))
+        want = _run(g, W, M.MODE_WHOLE)
+        assert float(got[0].cpu()[0]) == want[0] and np.array_equal(got[1].cpu().numpy(), want[1].astype(np.float32)), N
+        assert not _by_mlp(g, W, M.MODE_WHOLE)
+    assert 1 < len(fits) < 50 and 80 * M.lib().mlip_static_scratch_bytes() / N < 4 * fits[-1][1], (N, fits[-1:])
