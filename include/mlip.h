@@ -214,10 +214,13 @@ int mlip_graph_skin_stats(const mlip_graph_t *graph, int64_t *list_builds, int64
  *   forces        DEVICE [n_atoms][3] fp32, F = -dE/dr, input atom order
  *   atom_energy   DEVICE [n_atoms] fp32 or NULL
  *
+ * Forces are the energy's derivative to rounding: where the filters come from tables, values and slopes are tabulated apart,
+ * each to some 5e-8 of the filter.
+ *
  * Asynchronous on the graph's stream; does not modify the graph's topology (it uses
  * workspace owned by the handle, so two forwards on one handle must not overlap).
  *
- * The weights are re-laid-out for the matrix units and the filters tabulated (0.17 MB per layer and 32 features) on the
+ * The weights are re-laid-out for the matrix units and the filters tabulated (0.33 MB per layer and 32 features) on the
  * first call and kept in the handle: a later call whose mlip_weights_t (pointers, dimensions, precision) and graph cutoff
  * are identical reuses them.  After changing weight VALUES in place, or when another model's arrays have come to lie at the
  * same addresses, call mlip_graph_invalidate_weights.

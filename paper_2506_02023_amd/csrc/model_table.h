@@ -259,7 +259,8 @@ __global__ void __launch_bounds__(kTabNodes * 64) k_filter_table(TabJob J)
 //
 // Bounds and times, 256,000 atoms, F = 64, us a launch (with one table for values and slopes, 32 features a block, in brackets): forward, LDS 83 %
 // busy, 214 (260); reverse, the vector unit, 3.4 clocks an instruction, 381 (383); layer 0, LDS 62 %, address unit 73 %, 259 (357).  A
-// million atoms in 8 slabs: 867, 1767, 1175 (1052, 1764, 1654).
+// million atoms in 8 slabs: 867, 1767, 1175 (1052, 1764, 1654).  Of these the forward and layer 0's steps fetch 4.3 and 6.4 GB, rows gathered
+// again from beyond the L2 (half a plane of the lattice under way in an XCD), layer 0's at 5.9 TB/s.
 
 struct TabArgs {               // one partition
     int32_t n_rows, n_edges;   // receiver rows processed and their edges (below 2^29: byte offsets below 2^31)
