@@ -22,8 +22,8 @@
 // A derivative is as good as a polynomial of its own only on intervals 0.55 times as long, and the table has to fit LDS: one that serves for
 // both holds 32 features, the other two all 64, which spares an edge's second look at its record and its broadcasts (20 vector instructions
 // for four edges and 32 features, 17 with 64 at a time).  What is cut off is below what the evaluation of the MLP in fp32 rounds, feature by
-// feature, of the slopes in root mean square over an interval (checked when the tables are made, see k_filter_table); coefficients and evaluation round to 3.6e-8 of values and slopes (5e-8 of the
-// slopes as a derivative), the fp32 evaluation of the MLP to 1.7e-7 of both.
+// feature, of the slopes in root mean square over an interval (checked when the tables are made, see k_filter_table); coefficients and
+// evaluation round to 3.6e-8 of values and slopes (5e-8 of the slopes as a derivative), the fp32 evaluation of the MLP to 1.7e-7 of both.
 // An interval is, for 64 features, [6 coefficients][64], for 32 features [3][16 lanes][2 coefficients][2 features]: 16 bytes of a lane at a
 // time, 16 lanes 256 bytes of a row.  Values or slopes of F = 64 and both of 32 features take 162,816 bytes of the compute unit's 160 KB.
 constexpr int kTabUnits = 60, kTabN = 106;
